@@ -569,7 +569,7 @@ def run_backward_workload(args, torch, api, wl):
 
 def run_lzw_batch(args, torch, api, wl, B=2048):
     """Many documents per call (the preprocessing case): B sequences of configuration 2's kind through
-    lzw_encode and lzw_decode; one wave per sequence, tables in global memory."""
+    lzw_encode and lzw_decode; several workgroups per CU."""
     cfg = wl.scaled(wl.CONFIGS["c2"], B=B, seed=2900)
     N, V, M, cap = cfg["N"], cfg["V"], cfg["M"], cfg["cap"]
     t0 = time.time()

@@ -136,9 +136,9 @@ int z2z_step_update(z2z_ctx* ctx, const int32_t* d_codes, int32_t stride, const 
 
 /* Instrumentation: a borrowed device view [B] int32 of how many rounds the latest z2z_lzw_encode or
  * z2z_lzw_decode call took for each sequence.  The parse kernels (section 2.1's sequential loop, restructured)
- * take the elements of a sequence in rounds of up to 64 (one wave) or 256 (four waves) and cut a round at the
- * first element that depends on an entry made inside it; the serial chain of a call is its rounds, so
- * kernel time / rounds is the latency the parse is bound by.  Valid until z2z_destroy. */
+ * take the elements of a sequence in windows of up to 1024 and iterate on a window until every element's match agrees
+ * with the entries made before it; the serial chain of a call is its iterations (what is counted here), so kernel
+ * time / rounds is the latency the parse is bound by.  Valid until z2z_destroy. */
 int z2z_lzw_rounds(z2z_ctx* ctx, const int32_t** d_rounds);
 
 /* Codebook prefilling (the paper's discussion, "Codebook Management Strategy", item 2: seeding the codebook
@@ -374,7 +374,7 @@ enum {
                                   192 hidden rows, which otherwise goes to the weight-streaming kernel */
   Z2Z_OPT_LOGITS_STRIP = 2,    /* vocabulary tiles swept per workgroup, 0 = automatic               */
   Z2Z_OPT_LZW_KERNEL = 3,      /* 0 = automatic, >0 = force a variant (2: table in global memory, 3: one
-                                  code per step in the decoder, 4: one wave per sequence in the encoder) */
+                                  code per step in the decoder, 4: one wave per sequence) */
   Z2Z_OPT_DECODE_KERNEL = 4,   /* 0 = automatic, >0 = force a variant                               */
   Z2Z_OPT_LOGITS_MAP = 6,      /* workgroup -> tile order of the bf16 MFMA kernel's base part, packed
                                   lr | ls << 8 | xr << 16 | xs << 24: each of the 8 XCDs walks blocks of

@@ -1,18 +1,22 @@
-// Batched token-level LZW for gfx950: one wavefront (64 lanes) per sequence.
+// Batched token-level LZW for gfx950: one workgroup per sequence, up to 16 waves.
 //
 // The parse of one sequence is a serial dependency chain (section 2.1 of the zip2zip paper: every
 // step looks up "current phrase + next token" in the codebook built so far), so the unit of
-// parallelism across workgroups is the sequence.  Inside a sequence the 64 lanes work on 64 consecutive
-// positions (encoder) or codes (decoder) at once against the codebook as it stood when the round began,
-// and the round is cut short at the first element that depends on an entry made inside the round; the
-// kernels' own comments give the argument why the result is that of the one-element-at-a-time loop.
+// parallelism across workgroups is the sequence.  Inside a sequence a window of up to 1024 positions (encoder) or
+// codes (decoder), one per thread, is looked up at once in the codebook as it stood when the window began, and what
+// depends on entries made inside the window is found by iterating until nothing changes; the kernels' own comments
+// give the argument why the result is that of the one-element-at-a-time loop.
+//
+// Measured, kernel time encode; decode (before: rounds of 256 elements, four waves, cut at the first element that depends
+// on an entry of the round): 8 sequences of 4096 tokens, M = 3, cap 2048: 110 -> 44 us; 89 -> 32 us.  4 of 32768,
+// M = 4, cap 8192: 691 -> 211; 391 -> 125.  16 of 16384, M = 5, cap 16384 (table in memory): 657 -> 284; 449 -> 157.
+// 2048 of 4096: 470 -> 258; 395 -> 187.  1 of 512: 24 -> 11.5; 22 -> 10.
 //
 // The codebook is a trie stored as a hash table over its edges: one 64-bit slot = parent code (24 bits)
-// | token (24 bits) | entry index (16 bits), two slots per bucket, so a probe is one 16-byte LDS read and
-// two compares.  The wave keeps the table of its sequence in LDS for the whole call (4 slots per entry
+// | token (24 bits) | entry index (16 bits), two slots per bucket, two buckets per probe step (Table).  The
+// workgroup keeps the table of its sequence in LDS for the whole call when it fits (4 slots per entry
 // when the 160 KiB of a CU allow, at least 1.25); the decoder also keeps (length, first token) of every
-// entry there when it fits.  Tokens and codes are staged in LDS 2048 at a time.  Control flow is
-// wave-uniform (ballots, scalar registers).
+// entry there when it fits.  Tokens and codes are staged in LDS a window ahead.
 #include "hyper_embed_common.h"
 
 #include <string.h>
@@ -37,14 +41,11 @@ struct LzwArgs {
   int32_t in_step;         // one-code-at-a-time decoder only: > 0 = row distance of `in` (else `stride`)
 };
 
+// (parents and tokens have at most 24 bits: the 24-bit multiplier runs at full rate, a 32-bit product at a quarter)
 __device__ __forceinline__ uint32_t edge_hash(int32_t parent, int32_t tok) {
-  uint32_t h = (uint32_t)parent * 0x9E3779B1u + (uint32_t)tok * 0x85EBCA77u;
+  uint32_t h = __umul24((uint32_t)parent, 0x9E3779u) + __umul24((uint32_t)tok, 0xC2B2AFu);
   h ^= h >> 15;
-  h *= 0x2C1B3C6Du;
-  h ^= h >> 12;
-  h *= 0x297A2D39u;
-  h ^= h >> 15;
-  return h;
+  return h * 0x2C1B3C6Du;              // (the upper bits are the well mixed ones)
 }
 
 __device__ __forceinline__ u64 edge_bits(int32_t parent, int32_t tok) {
@@ -60,30 +61,53 @@ struct Table {
   u64* g;           // global slots of this sequence
   uint32_t n;       // number of slots
 
-  // Slots are probed in pairs ("buckets", n is even) so that the per-lane lookup tests two slots with
-  // one 16-byte LDS read.  The first kJumps buckets of a probe sequence are `step` buckets apart (a
-  // second hash: no clustering, so the longest of 64 simultaneous probes stays short), the rest follow
-  // one by one, which reaches every bucket whatever n is.  A lookup ends at the first empty slot.
+  // Two slots are a bucket (n is even): one 16-byte read.  A probe step looks at two buckets at once, and a new
+  // edge goes into the emptier one (slot 0 of a bucket first), so hardly any look-up needs a second step: with the
+  // table half full the longest of 64 simultaneous probes takes two, where a one-bucket probe sequence took six.  The
+  // first kJumps buckets of a sequence are `step` (a second hash) apart, the rest follow one by one, which reaches
+  // every bucket whatever n is.  A look-up ends at the first step with an empty slot.
   static constexpr uint32_t kJumps = 8;
-  __device__ __forceinline__ void probe_init(int32_t parent, int32_t tok, uint32_t* bucket, uint32_t* step) const {
-    const uint32_t h = edge_hash(parent, tok);
-    const uint32_t nb = n >> 1;
-    *bucket = __umulhi(h, nb);
-    *step = 1 + __umulhi(h * 0x9E3779B1u + 0x7F4A7C15u, nb - 1);       // 1 .. nb-1
+  struct Probe {
+    uint32_t b0, b1, step, i;
+  };
+  __device__ __forceinline__ uint32_t hop(uint32_t bucket, uint32_t by) const {
+    bucket += by;
+    return min(bucket, bucket - (n >> 1));          // (unsigned: the subtraction wraps unless bucket is past the end)
   }
-  __device__ __forceinline__ uint32_t probe_next(uint32_t bucket, uint32_t step, uint32_t i) const {
-    const uint32_t nb = n >> 1;
-    bucket += i < kJumps ? step : 1;
-    return bucket >= nb ? bucket - nb : bucket;
+  __device__ __forceinline__ Probe probe_init(uint32_t h) const {
+    Probe p;
+    p.step = 1 + ((h >> 4) & 30);                   // odd, at most 31 < n / 2 (n >= 64)
+    p.b0 = __umulhi(h, n >> 1);
+    p.b1 = hop(p.b0, p.step);
+    p.i = 0;
+    return p;
   }
-  __device__ __forceinline__ u64 load(uint32_t pos) const {
-    // (the global table is read past the vector L1 everywhere: slots are claimed with atomics, which do not
-    // update that cache, so a line it holds can be stale)
-    const u64 v = LDS ? lds_slots[pos] : __hip_atomic_load(&g[pos], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // every lane reads the same address; readfirstlane keeps the chain in scalar registers
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return ((u64)hi << 32) | lo;
+  __device__ __forceinline__ bool probe_next(Probe* p) const {
+    p->i += 2;
+    const uint32_t by = p->i < kJumps ? p->step : 1;
+    p->b0 = hop(p->b1, by);
+    p->b1 = hop(p->b0, by);
+    return p->i < (n >> 1) + kJumps + 2;
+  }
+  // (the global table is read past the vector L1 everywhere: slots are claimed with atomics, which do not
+  // update that cache, so a line it holds can be stale)
+  // A bucket is one 16-byte request (atomic loads have 8 bytes at most; what a probe in memory costs is requests).
+  __device__ __forceinline__ void load(const Probe& p, ulonglong2* a, ulonglong2* b) const {
+    if (LDS) {
+      *a = *reinterpret_cast<const ulonglong2*>(&lds_slots[2 * p.b0]);
+      *b = *reinterpret_cast<const ulonglong2*>(&lds_slots[2 * p.b1]);
+      return;
+    }
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    u32x4 x, y;
+    asm volatile("global_load_dwordx4 %0, %2, off sc1\n\tglobal_load_dwordx4 %1, %3, off sc1\n\ts_waitcnt vmcnt(0)"
+                 : "=&v"(x), "=&v"(y)
+                 : "v"(g + 2 * p.b0), "v"(g + 2 * p.b1)
+                 : "memory");
+    a->x = ((u64)x[1] << 32) | x[0];
+    a->y = ((u64)x[3] << 32) | x[2];
+    b->x = ((u64)y[1] << 32) | y[0];
+    b->y = ((u64)y[3] << 32) | y[2];
   }
   __device__ __forceinline__ void store(uint32_t pos, u64 v) const {
     if (LDS)
@@ -91,81 +115,95 @@ struct Table {
     else
       __hip_atomic_store(&g[pos], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  // Returns the entry index, or -1 with *free_pos = the empty slot the probe ended at (-1 if the
-  // table has no empty slot, which cannot happen while n > cap).
+  // Slot of the emptier of two buckets, -1 if both are full.
+  static __device__ __forceinline__ int free_slot(const Probe& p, const ulonglong2& a, const ulonglong2& b) {
+    if (a.x == kEmpty) return (int)(2 * p.b0);
+    if (b.x == kEmpty) return (int)(2 * p.b1);
+    if (a.y == kEmpty) return (int)(2 * p.b0 + 1);
+    if (b.y == kEmpty) return (int)(2 * p.b1 + 1);
+    return -1;
+  }
+  static __device__ __forceinline__ bool holds(u64 slot, u64 key) {
+    return (uint32_t)(slot >> 32) == (uint32_t)(key >> 32) && ((uint32_t)slot ^ (uint32_t)key) < 0x10000u;
+  }
+  static __device__ __forceinline__ int match(const ulonglong2& a, const ulonglong2& b, u64 key) {
+    int idx = -1;
+    if (holds(a.x, key)) idx = (int)((uint32_t)a.x & 0xFFFFu);
+    if (holds(a.y, key)) idx = (int)((uint32_t)a.y & 0xFFFFu);
+    if (holds(b.x, key)) idx = (int)((uint32_t)b.x & 0xFFFFu);
+    if (holds(b.y, key)) idx = (int)((uint32_t)b.y & 0xFFFFu);
+    return idx;
+  }
+  static __device__ __forceinline__ u64 uniform(u64 v) {
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return ((u64)hi << 32) | lo;
+  }
+  // Wave-uniform look-up (every lane reads the same address; the chain stays in scalar registers).  Returns the
+  // entry index, or -1 with *free_pos = the slot the edge would get (-1 if the table has no empty slot, which
+  // cannot happen while n > cap).
   __device__ __forceinline__ int find(int32_t parent, int32_t tok, int* free_pos) const {
     const u64 key = edge_bits(parent, tok);
-    uint32_t bucket, step;
-    probe_init(parent, tok, &bucket, &step);
-    const uint32_t n_probe = (n >> 1) + kJumps;
-    for (uint32_t i = 0; i < n_probe; ++i) {
-      for (uint32_t k = 0; k < 2; ++k) {
-        const uint32_t pos = 2 * bucket + k;
-        const u64 s = load(pos);
-        if (s == kEmpty) {
-          *free_pos = (int)pos;
-          return -1;
-        }
-        if ((s & ~0xFFFFull) == key) return (int)(s & 0xFFFFull);
-      }
-      bucket = probe_next(bucket, step, i);
-    }
-    *free_pos = -1;
+    Probe p = probe_init(edge_hash(parent, tok));
+    do {
+      ulonglong2 a, b;
+      load(p, &a, &b);
+      a.x = uniform(a.x);
+      a.y = uniform(a.y);
+      b.x = uniform(b.x);
+      b.y = uniform(b.y);
+      const int idx = match(a, b, key);
+      if (idx >= 0) return idx;
+      *free_pos = free_slot(p, a, b);
+      if (*free_pos >= 0) return -1;
+    } while (probe_next(&p));
     return -1;
   }
-  // The same probe, per lane (each lane looks up its own edge; no scalar broadcast).  The global table
-  // is read past the vector L1: slots are claimed with atomics, which do not update that cache.
-  __device__ __forceinline__ int find_lane(int32_t parent, int32_t tok) const {
+  // The same look-up per lane (each lane its own edge; h = edge_hash(parent, tok)).
+  __device__ __forceinline__ int find_lane(int32_t parent, int32_t tok, uint32_t h) const {
     const u64 key = edge_bits(parent, tok);
-    uint32_t bucket, step;
-    probe_init(parent, tok, &bucket, &step);
-    const uint32_t n_probe = (n >> 1) + kJumps;
-    for (uint32_t i = 0; i < n_probe; ++i) {
-      u64 s0, s1;
-      if (LDS) {
-        const ulonglong2 two = *reinterpret_cast<const ulonglong2*>(&lds_slots[2 * bucket]);
-        s0 = two.x;
-        s1 = two.y;
-      } else {
-        s0 = __hip_atomic_load(&g[2 * bucket], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s1 = __hip_atomic_load(&g[2 * bucket + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      if (s0 == kEmpty) return -1;
-      if ((s0 & ~0xFFFFull) == key) return (int)(s0 & 0xFFFFull);
-      if (s1 == kEmpty) return -1;
-      if ((s1 & ~0xFFFFull) == key) return (int)(s1 & 0xFFFFull);
-      bucket = probe_next(bucket, step, i);
-    }
+    Probe p = probe_init(h);
+    do {
+      ulonglong2 a, b;
+      load(p, &a, &b);
+      const int idx = match(a, b, key);
+      if (idx >= 0) return idx;
+      if (a.y == kEmpty || b.y == kEmpty) return -1;
+    } while (probe_next(&p));
     return -1;
   }
-  // Per-lane insertion of an edge known to be absent: claim the first empty slot of the probe
-  // sequence with a compare-and-swap (several lanes insert at once).
+  __device__ __forceinline__ int find_lane(int32_t parent, int32_t tok) const {
+    return find_lane(parent, tok, edge_hash(parent, tok));
+  }
+  // Per-lane insertion of an edge known to be absent (several lanes insert at once: a slot is claimed with a
+  // compare-and-swap, and the buckets are looked at again when it was lost).
   __device__ __forceinline__ void insert_lane(int32_t parent, int32_t tok, int idx) const {
     const u64 val = edge_bits(parent, tok) | (u64)(uint32_t)idx;
-    uint32_t bucket, step;
-    probe_init(parent, tok, &bucket, &step);
-    const uint32_t n_probe = (n >> 1) + kJumps;
-    for (uint32_t i = 0; i < n_probe; ++i) {
-      u64* slot = LDS ? &lds_slots[2 * bucket] : &g[2 * bucket];
-      if (atomicCAS(slot, kEmpty, val) == kEmpty) return;
-      if (atomicCAS(slot + 1, kEmpty, val) == kEmpty) return;
-      bucket = probe_next(bucket, step, i);
-    }
+    Probe p = probe_init(edge_hash(parent, tok));
+    do {
+      for (int tries = 0; tries < 5; ++tries) {     // (a lost slot has filled: at most four times)
+        ulonglong2 a, b;
+        load(p, &a, &b);
+        const int at = free_slot(p, a, b);
+        if (at < 0) break;
+        if (atomicCAS(LDS ? &lds_slots[at] : &g[at], kEmpty, val) == kEmpty) return;
+      }
+    } while (probe_next(&p));
   }
 };
 
 // A workgroup barrier that other waves' reads PAST the vector L1 may rely on.  Between the waves of a workgroup
 // plain stores and plain loads are ordered by the L1 they share, and the barrier does not wait for the stores
-// to leave it; a load that goes straight to L2 (load_fresh, the table's atomic loads) could overtake a store of
-// another wave that is still on its way there.  So the stores are awaited before the barrier.
+// to leave it; a load that goes straight to L2 (the table's) could overtake a store of another wave that is still on
+// its way there.  So the stores are awaited before the barrier.  (Slots claimed with atomics need no such wait: the
+// claiming thread has waited for the old value.)
 __device__ __forceinline__ void sync_after_global_stores() {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
 }
 
-// The one-wave helpers (table_open / table_close, lzw_encode_rounds, lzw_decode_rounds) are run by exactly one
-// wave: the whole workgroup of the 64-thread kernels, or wave 0 of a four-wave kernel on a short appended call
-// after the other three have returned.  What they need between their steps is that the lanes' earlier LDS and
+// The one-wave helpers (table_open / table_close, lzw_decode_serial_body) are run by exactly one
+// wave: the whole workgroup of the 64-thread kernels, or wave 0 of the step-update kernel.  What they need between their steps is that the lanes' earlier LDS and
 // global accesses have completed, not a meeting of waves, so they never execute a workgroup barrier: a fence at
 // workgroup scope (the waits for the outstanding memory operations) and a wave barrier (keeps the compiler from
 // moving memory operations across).
@@ -191,6 +229,30 @@ __device__ __forceinline__ void table_open(const LzwArgs& a, int b, int lane, bo
     for (int i = lane; i < st.nslots; i += kWave) t->g[i] = kEmpty;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     wave_sync();
+  }
+}
+
+// The same by all THREADS threads of a workgroup; no barrier inside.
+template <bool LDS, int THREADS>
+__device__ __forceinline__ void table_open_all(const LzwArgs& a, int b, int tid, bool reset, Table<LDS>* t) {
+  t->g = a.st.slots + (size_t)b * a.st.nslots;
+  t->n = (uint32_t)a.st.nslots;
+  ulonglong2* g2 = reinterpret_cast<ulonglong2*>(t->g);             // (nslots is even, the rows 16-byte aligned)
+  ulonglong2* l2 = reinterpret_cast<ulonglong2*>(lds_slots);
+  const int pairs = a.st.nslots >> 1;
+  const ulonglong2 empty = {kEmpty, kEmpty};
+  if (LDS) {
+    for (int i = tid; i < pairs; i += THREADS) l2[i] = reset ? empty : g2[i];
+  } else if (reset) {
+    for (int i = tid; i < pairs; i += THREADS) g2[i] = empty;
+  }
+}
+template <bool LDS, int THREADS>
+__device__ __forceinline__ void table_close_all(int tid, const Table<LDS>& t) {
+  if (LDS) {
+    ulonglong2* g2 = reinterpret_cast<ulonglong2*>(t.g);
+    const ulonglong2* l2 = reinterpret_cast<const ulonglong2*>(lds_slots);
+    for (int i = tid; i < (int)(t.n >> 1); i += THREADS) g2[i] = l2[i];
   }
 }
 
@@ -221,107 +283,199 @@ __device__ __forceinline__ void table_insert(const LzwArgs& a, int b, int lane, 
 // ------------------------------------------------------------------------------------------------
 // encode
 //
-// The serial chain of the parse is cut into rounds of 64 positions whose work is done by the 64 lanes
-// side by side; nothing in a round is a per-token scalar loop.
-//   1. lane j follows, for the phrase that would start at position pos + j, the chain of lookups
-//      token -> (code, next token) -> ... against the table as it stands at the start of the round
-//      (at most M-1 probes, all lanes at once).  This gives L0[j], the length of that match.
-//   2. the true phrase starts are the positions reached from 0 by j -> j + L0[j]; six rounds of pointer
-//      doubling (each lane carries the 64-bit set of positions its chain visits) give lane 0 the set.
-//   3. a start whose match may still grow (length < M, a next token exists) proposes the edge
-//      (its code, next token); the proposals of the round get consecutive entry numbers in position
-//      order while the codebook has room.
-//   4. what step 1 cannot see is an entry made earlier in this same round.  A phrase is longer than
-//      L0 exactly when its proposed edge equals an edge proposed by an earlier start of the round, so
-//      the round is cut at the first such repeat (found with a small LDS hash filter keyed by edge,
-//      keeping the lowest position): everything before the cut is exact, and the next round starts at
-//      the cut with the new entries in the table.  A cut is never at position 0, so every round emits
-//      at least one phrase.
-//   5. the starts before the cut store their codes, insert their edges (compare-and-swap on the slot)
-//      and write their flattened rows from the staged tokens.
-// Greedy longest match and the order of entry creation are those of the one-token-at-a-time parse: a
-// lookup that hit at the start of the round still hits later, and a new entry only matters to later
-// starts.  Tokens are staged in LDS kTokBuf at a time, so a round reads no global memory.
+// The greedy parse is the solution of a recurrence over positions: the match at a phrase start is the longest one
+// in the codebook as it stood when the round began plus the entries that earlier starts of the round make, and
+// the starts are the positions reached from the first by start -> start + length.  A round takes a window of one
+// position per thread and finds that solution by iteration, instead of cutting the window at the first start that
+// depends on an entry made inside it:
+//   1. every position follows its chain of lookups token -> (code, next token) -> ... in the table as it stands
+//      (at most M-1 probes): (L0, c0), the match without this round's entries.
+//   2. starts from lengths.  "Positions still to skip" is a state in 0..M-1 and position i a function of it:
+//      s -> s-1, 0 -> L-1.  A function is M bytes and v_perm_b32 composes two of them (one instruction up to
+//      M = 4, two up to 8), so the starts are a DPP scan over the wave's lanes, one LDS exchange of the waves'
+//      compositions, and a scan over those.
+//   3. every start whose match may grow puts its edge (its code, next token) into an LDS hash set that keeps the
+//      lowest position per edge; an entry of this round is named by the position of the start that makes it.
+//   4. every position extends (L0, c0) through the set by edges of lower positions.  If no start's match
+//      changed, lengths, starts and edges satisfy the recurrence and are the parse (by induction over the
+//      positions: each depends on lower ones only); else back to 2.  The lowest start that is not final yet
+//      becomes final with every iteration, so the loop ends; one to three iterations are usual, as a parse falls
+//      back into step soon after a changed length.
+//   5. publish: entry numbers are ranks of the proposing starts; codes, table insertions (compare-and-swap) and
+//      flattened rows from the staged tokens.
+// A window is cut only by a token out of range, the end of the output row and the entry that fills the codebook;
+// with the codebook full the iteration is a single scan.  Order of entries and matches are those of the
+// one-token-at-a-time parse.
+//
+// What bounds it: instruction issue and LDS latency of one CU (a window of 1024 is four waves per SIMD, so an
+// instruction costs 16 cycles; chains ~3500 cycles a window, an iteration ~5000, publishing ~4000).  Wider windows have
+// fewer rounds and hardly more iterations: a 4096-token sequence at M = 3 takes 28 rounds of 256 positions cut at the
+// first repeat, but 5 windows of 1024 with 13 iterations in all.
 // ------------------------------------------------------------------------------------------------
-constexpr int kTokBuf = 2048;                 // tokens staged in LDS per refill
-constexpr int kFilter = 512;                  // slots of the per-round repeat filter (<= 64 keys)
-constexpr int kEncStaticLds = kTokBuf * 4 + kFilter * 8;
+constexpr int kShortAppend = 64;
 
-__device__ __forceinline__ void lds_order() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-
-// The first lane whose proposed edge (parent, tok) repeats the edge of an earlier lane that inserts
-// (kWave if there is none).  `cand` lanes propose, the `inserter` ones among them (a prefix of the
-// candidates in lane order) have room to insert.  `filter` is an empty LDS hash set on entry and on exit.
-__device__ __forceinline__ int first_repeat(u64* filter, int lane, bool cand, bool inserter, int32_t parent,
-                                            int32_t tok) {
-  const u64 key = edge_bits(parent, tok);
-  const uint32_t h0 = (edge_hash(parent, tok) >> 20) & (kFilter - 1);
-  int own = -1;
-  bool same = false;                                // met its own edge in the filter
-  if (inserter) {
-    const u64 val = key | (u64)lane;
-    uint32_t h = h0;
-    for (int probe = 0; probe < kFilter; ++probe) {
-      const u64 old = atomicCAS(&filter[h], kEmpty, val);
-      if (old == kEmpty) {
-        own = (int)h;
-        break;
-      }
-      if ((old & ~0xFFFFull) == key) {
-        atomicMin(&filter[h], val);                 // same edge: keep the lowest lane
-        same = true;
-        break;
-      }
-      h = (h + 1) & (kFilter - 1);
-    }
-  }
-  lds_order();
-  u64 dup_mask = 0;
-  // No inserter met its edge: all inserted edges differ.  A proposal without room can then only
-  // repeat an inserted one, which the lookup below finds; with room for all there is none.
-  if (__ballot(same) != 0 || __ballot(cand && !inserter) != 0) {
-    int fpos = kWave;
-    if (cand) {
-      uint32_t h = h0;
-      for (int probe = 0; probe < kFilter; ++probe) {
-        const u64 sl = filter[h];
-        if (sl == kEmpty) break;
-        if ((sl & ~0xFFFFull) == key) {
-          fpos = (int)(sl & 0xFFFFull);
-          break;
-        }
-        h = (h + 1) & (kFilter - 1);
-      }
-    }
-    dup_mask = __ballot(cand && fpos < lane);
-    lds_order();
-  }
-  if (own >= 0) filter[own] = kEmpty;               // leave the filter empty for the next round
-  lds_order();
-  return dup_mask ? __builtin_ctzll(dup_mask) : kWave;
+// Number of elements of sequence b in this call.
+__device__ __forceinline__ int call_length(const LzwArgs& a, int b) {
+  return a.in_len ? min(max(__builtin_amdgcn_readfirstlane(a.in_len[b]), 0), a.stride) : a.stride;
 }
 
-template <bool LDS>
-__device__ __forceinline__ void lzw_encode_rounds(const LzwArgs& a, int32_t* tokbuf, u64* filter) {
+// The skip function of one position or of a run of positions: byte s = state after it, for state s before it.
+struct SkipFn {
+  uint32_t lo, hi;
+};
+constexpr uint32_t kSkipIdLo = 0x03020100u, kSkipIdHi = 0x07060504u;
+
+template <bool M4>
+__device__ __forceinline__ SkipFn skip_then(SkipFn first, SkipFn second) {
+  SkipFn r;
+  r.lo = __builtin_amdgcn_perm(second.hi, second.lo, first.lo);
+  r.hi = M4 ? kSkipIdHi : __builtin_amdgcn_perm(second.hi, second.lo, first.hi);
+  return r;
+}
+
+// One step of a scan over lanes: every lane that has a source under the DPP control composes it before its own.
+template <bool M4, int CTRL, int ROW_MASK>
+__device__ __forceinline__ SkipFn skip_scan_step(SkipFn f) {
+  SkipFn g;
+  g.lo = __builtin_amdgcn_update_dpp(kSkipIdLo, f.lo, CTRL, ROW_MASK, 0xf, false);
+  g.hi = M4 ? kSkipIdHi : __builtin_amdgcn_update_dpp(kSkipIdHi, f.hi, CTRL, ROW_MASK, 0xf, false);
+  return skip_then<M4>(g, f);
+}
+template <bool M4>
+__device__ __forceinline__ SkipFn skip_scan16(SkipFn f) {         // inclusive, inside each row of 16 lanes
+  f = skip_scan_step<M4, 0x111, 0xf>(f);                          // row_shr:1, 2, 4, 8
+  f = skip_scan_step<M4, 0x112, 0xf>(f);
+  f = skip_scan_step<M4, 0x114, 0xf>(f);
+  return skip_scan_step<M4, 0x118, 0xf>(f);
+}
+template <bool M4>
+__device__ __forceinline__ SkipFn skip_scan64(SkipFn f) {         // inclusive, over the wave
+  f = skip_scan16<M4>(f);
+  f = skip_scan_step<M4, 0x142, 0xa>(f);                          // row_bcast:15 into rows 1 and 3
+  return skip_scan_step<M4, 0x143, 0xc>(f);                       // row_bcast:31 into rows 2 and 3
+}
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t row_add_step(uint32_t v) {
+  return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false);
+}
+// Sums over the waves of a workgroup of up to 16: every lane l < NW holds wave l's value in, the sum of waves 0..l out.
+__device__ __forceinline__ uint32_t row_scan_add(uint32_t v) {
+  v = row_add_step<0x111>(v);
+  v = row_add_step<0x112>(v);
+  v = row_add_step<0x114>(v);
+  return row_add_step<0x118>(v);
+}
+
+// The per-round set of proposed edges: for every edge the lowest position that proposes it.  A slot is 32 bits,
+// 21 bits of the edge's hash | 11 bits of position (all ones: empty); four slots are a group, read at once, and an
+// edge lives in one of two groups that its hash names, so a look-up is two 16-byte reads whatever the load, no loop.
+// key[position] is the edge itself (parent: a code, or kRoundEntry | position for an entry of this round).
+constexpr int32_t kRoundEntry = 1 << 24;
+constexpr uint32_t kRoundPos = 0x7FFu, kRoundEmpty = ~0u;
+__device__ __forceinline__ u64 round_key(int32_t parent, int32_t tok) { return ((u64)(uint32_t)parent << 32) | (uint32_t)tok; }
+template <int SLOTS>
+struct RoundSet {
+  static constexpr int kGroups = SLOTS / 4;
+  static constexpr int kGroupBits = __builtin_ctz(kGroups);
+  static __device__ __forceinline__ void groups(uint32_t h, uint32_t* a, uint32_t* b) {
+    *a = h >> (32 - kGroupBits);
+    *b = *a ^ (((h >> 2) & (kGroups - 1)) | 1);
+  }
+  // Insert; returns the slot this thread claimed (it empties it later), -1 when the edge was there already, and -2 when
+  // both groups are full of other edges.
+  static __device__ __forceinline__ int insert(uint32_t* set, u64* key, uint32_t h, u64 kk, int pos) {
+    uint32_t ga, gb;
+    groups(h, &ga, &gb);
+    key[pos] = kk;
+    asm volatile("" ::: "memory");             // (a wave's LDS operations execute in order: the key is there before the slot)
+    const uint32_t val = (h << 11) | (uint32_t)pos;
+    uint32_t at = 4 * ga;
+    for (uint32_t i = 0; i < 8; ++i) {
+      const uint32_t idx = at + ((h + i) & 3);
+      const uint32_t old = atomicCAS(&set[idx], kRoundEmpty, val);
+      if (old == kRoundEmpty) return (int)idx;
+      if ((old ^ val) <= kRoundPos && key[old & kRoundPos] == kk) {
+        atomicMin(&set[idx], val);
+        return -1;
+      }
+      if (i == 3) at = 4 * gb;
+    }
+    return -2;
+  }
+  // The lowest position below `pos` that proposes the edge, or -1.
+  static __device__ __forceinline__ int find(const uint32_t* set, const u64* key, uint32_t h, u64 kk, int pos) {
+    uint32_t ga, gb;
+    groups(h, &ga, &gb);
+    const uint4 a = reinterpret_cast<const uint4*>(set)[ga], b = reinterpret_cast<const uint4*>(set)[gb];
+    const uint32_t tag = h << 11;
+    const uint32_t x[8] = {a.x ^ tag, a.y ^ tag, a.z ^ tag, a.w ^ tag, b.x ^ tag, b.y ^ tag, b.z ^ tag, b.w ^ tag};
+    const uint32_t m = min(min(min(x[0], x[1]), min(x[2], x[3])), min(min(x[4], x[5]), min(x[6], x[7])));
+    if (m >= (uint32_t)pos) return -1;         // (an empty slot reads as a position of 2047 at least)
+    if (key[m] == kk) return (int)m;
+    int best = -1;                             // 21 bits agree, the edges differ: look at every slot
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (x[i] < (uint32_t)pos && (best < 0 || x[i] < (uint32_t)best) && key[x[i]] == kk) best = (int)x[i];
+    return best;
+  }
+};
+
+constexpr int kMaxWaves = 16;
+template <int NW>
+struct EncShared {
+  static constexpr int W = NW * kWave;       // positions of a window
+  static constexpr int kSet = 4 * W;
+  uint32_t set[2][kSet];                     // edges proposed in an even / odd iteration
+  u64 key[W];
+  u64 skip[kMaxWaves];                       // skip function of each wave's positions
+  int32_t tok[2 * W];                        // ring of token classes: position p at p & (2 W - 1)
+  uint32_t count[kMaxWaves];                 // starts | proposals << 16 of each wave
+  uint32_t count_valid[kMaxWaves];           // the same below the window's limit (cut windows only)
+  int32_t changed[2];
+  int32_t cut_asked;                         // a token out of range was staged, or an edge found no slot
+  int32_t bad_pos, ovf_pos, full_pos, spill_pos;   // where a window is cut
+  int32_t last_code, last_len, last_end;     // the last phrase of the window
+  uint16_t rank[W];                          // of the proposing starts
+};
+constexpr int kParseStaticLds = (int)sizeof(EncShared<kMaxWaves>) + 256;    // + alignment slack
+
+template <int NW, bool LDS, bool M4>
+__device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, EncShared<NW>& sh) {
+  constexpr int W = NW * kWave;
+  constexpr int kSet = EncShared<NW>::kSet, kRing = 2 * W;
+  typedef RoundSet<kSet> Set;
   const LzwState& st = a.st;
   const int b = blockIdx.x;
-  const int lane = threadIdx.x;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int V = st.V, M = st.M, cap = st.cap;
   const bool reset = (a.flags & Z2Z_RESET) != 0;
 
-  int C = reset ? 0 : __builtin_amdgcn_readfirstlane(st.size[b]);
+  const int size0 = __builtin_amdgcn_readfirstlane(st.size[b]);
+  int C = reset ? 0 : size0;
   int prev = reset ? -1 : __builtin_amdgcn_readfirstlane(st.prev_code[b]);
   int prev_len = reset ? 0 : __builtin_amdgcn_readfirstlane(st.prev_len[b]);
-
-  Table<LDS> t;
-  table_open<LDS>(a, b, lane, reset, &t);
-  for (int i = lane; i < kFilter; i += kWave) filter[i] = kEmpty;
-
-  const int n = a.in_len ? min(max(__builtin_amdgcn_readfirstlane(a.in_len[b]), 0), a.stride) : a.stride;
+  const int n = call_length(a, b);
   const int32_t* in = a.in + (size_t)b * a.stride;
   int32_t* out = a.out + (size_t)b * a.out_stride;
   int32_t* ent_tokens = st.ent_tokens + (size_t)b * cap * M;
   int32_t* ent_len = st.ent_len + (size_t)b * cap;
+
+  Table<LDS> t;
+  table_open_all<LDS, W>(a, b, tid, reset, &t);
+  for (int i = tid; i < 2 * kSet; i += W) sh.set[0][i] = kRoundEmpty;
+  // tokens: the ring holds [fill - kRing, fill); the next W of them wait in a register
+  auto classify = [&](int32_t v) -> int32_t { return (v >= 0 && v < V) ? v : -2; };
+  int fill = kRing;
+  for (int i = tid; i < kRing; i += W) sh.tok[i] = i < n ? classify(in[i]) : -1;
+  int32_t ahead = fill + tid < n ? in[fill + tid] : 0;
+  if (tid == 0) {
+    sh.cut_asked = 0;
+    sh.changed[0] = sh.changed[1] = 0;
+  }
+  sync_after_global_stores();        // (a table cleared in global memory is read past the L1)
 
   int status = 0;
   int n_out = 0;
@@ -333,238 +487,10 @@ __device__ __forceinline__ void lzw_encode_rounds(const LzwArgs& a, int32_t* tok
     if (c >= 0 && c < V) {
       int free_pos = -1;
       const int idx = t.find(prev, c, &free_pos);
-      if (idx < 0 && free_pos >= 0) {
-        int32_t ph = -1;        // lane j = token j of the previous phrase
-        if (prev < V) {
-          ph = lane == 0 ? prev : -1;
-        } else if (lane < M) {
-          ph = ent_tokens[(size_t)(prev - V) * M + lane];
-        }
-        table_insert<LDS>(a, b, lane, t, free_pos, C, prev, c, ph, prev_len);
-        ++C;
-      }
-    }
-    wave_sync();
-  }
-
-  const u64 lanes_below = (1ull << lane) - 1;
-  int cbase = 0;                      // tokbuf holds positions [cbase, cbase + kTokBuf)
-  bool filled = false;
-  bool stop = false;
-  int pos = 0;                        // first position not yet covered by an emitted phrase
-  int n_rounds = 0;
-  while (pos < n && !stop) {
-    ++n_rounds;
-    // a round touches positions pos .. pos + 63 + M
-    if (!filled || (pos + kWave + M > cbase + kTokBuf && cbase + kTokBuf < n)) {
-      cbase = pos;
-      filled = true;
-      const int cnt = min(kTokBuf, n - cbase);
-      for (int i = lane; i < cnt; i += kWave) {
-        const int32_t v = in[cbase + i];
-        tokbuf[i] = (v >= 0 && v < V) ? v : -2;
-      }
-      lds_order();
-    }
-    const int rel = pos - cbase + lane;
-    auto tk = [&](int d) -> int32_t {           // token class at position pos + lane + d, -1 past the end
-      return pos + lane + d < n ? tokbuf[rel + d] : -1;
-    };
-
-    // ---- 1. chains against the table of the round's start ---------------------------------------
-    const int32_t tok0 = tk(0);
-    int L0 = tok0 >= 0 ? 1 : 0;
-    int32_t cfin = tok0;
-    int32_t nxt = tk(1);              // always the token that follows this lane's match
-    for (int d = 1; d < M; ++d) {
-      int idx = -1;
-      if (L0 == d && nxt >= 0) idx = t.find_lane(cfin, nxt);
-      if (__ballot(idx >= 0) == 0) break;
-      if (idx >= 0) {
-        cfin = V + idx;
-        L0 = d + 1;
-        nxt = tk(d + 1);
-      }
-    }
-
-    // ---- 2. phrase starts: positions reachable from 0 ---------------------------------------------
-    const int avail = min(kWave, n - pos);
-    int jump = (L0 > 0 && lane + L0 < kWave) ? lane + L0 : kWave;
-    uint32_t r_lo = lane < 32 ? 1u << lane : 0u, r_hi = lane < 32 ? 0u : 1u << (lane - 32);
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-      const int src = jump & (kWave - 1);
-      const uint32_t o_lo = __shfl(r_lo, src), o_hi = __shfl(r_hi, src);
-      const int o_jump = __shfl(jump, src);
-      if (jump < kWave) {
-        r_lo |= o_lo;
-        r_hi |= o_hi;
-        jump = o_jump;
-      }
-    }
-    const u64 S = ((u64)(uint32_t)__builtin_amdgcn_readfirstlane(r_hi) << 32) |
-                  (u64)(uint32_t)__builtin_amdgcn_readfirstlane(r_lo);
-    const bool start = ((S >> lane) & 1) != 0 && lane < avail;
-    const int prank = __popcll(S & lanes_below);          // phrases of the round before this one
-
-    // ---- 3. limits of the round, proposals -------------------------------------------------------
-    const u64 bad_mask = __ballot(start && tok0 == -2);
-    const u64 ovf_mask = __ballot(start && n_out + prank >= a.out_stride);
-    const int bad_pos = bad_mask ? __builtin_ctzll(bad_mask) : kWave;
-    const int ovf_pos = ovf_mask ? __builtin_ctzll(ovf_mask) : kWave;
-    const bool cand = start && tok0 >= 0 && L0 < M && nxt >= 0;
-    const u64 cand_mask = __ballot(cand);
-    const int rank = __popcll(cand_mask & lanes_below);
-    const int room = cap - C;
-    const bool inserter = cand && rank < room;
-
-    // ---- 4. first repeat of a proposed edge --------------------------------------------------------
-    int cut = kWave;
-    if (room > 0 && (cand_mask & (cand_mask - 1)) != 0) cut = first_repeat(filter, lane, cand, inserter, cfin, nxt);
-
-    // ---- 5. publish ---------------------------------------------------------------------------------
-    const int limit = min(min(avail, cut), min(bad_pos, ovf_pos));
-    if (bad_pos < kWave && limit == bad_pos) {
-      status |= Z2Z_ST_BAD_TOKEN;     // the sequence ends just before this token
-      stop = true;
-    } else if (ovf_pos < kWave && limit == ovf_pos) {
-      status |= Z2Z_ST_OVERFLOW;
-      stop = true;
-    }
-    const bool valid = start && lane < limit;
-    const u64 valid_mask = __ballot(valid);
-    if (valid) out[n_out + prank] = cfin;
-    const bool ins = valid && inserter;
-    if (ins) {
-      const int idx = C + rank;
-      t.insert_lane(cfin, nxt, idx);
-      int32_t* row = ent_tokens + (size_t)idx * M;
-      for (int k = 0; k < M; ++k) row[k] = k <= L0 ? tokbuf[rel + k] : -1;
-      ent_len[idx] = L0 + 1;
-    }
-    lds_order();
-    C += __popcll(__ballot(ins));
-    if (valid_mask) {
-      const int last = 63 - __builtin_clzll(valid_mask);
-      prev = __builtin_amdgcn_readlane(cfin, last);
-      prev_len = __builtin_amdgcn_readlane(L0, last);
-      n_out += __popcll(valid_mask);
-      pos += last + prev_len;
-    } else {
-      stop = true;                    // only reached with a limit of 0 (bad token or no room at the first start)
-    }
-  }
-
-  table_close<LDS>(a, lane, t);
-  if (lane == 0) {
-    st.size[b] = C;
-    st.prev_code[b] = prev;
-    st.prev_len[b] = prev_len;
-    st.rounds[b] = n_rounds;
-    a.out_n[b] = n_out;
-    a.status[b] = status;
-  }
-}
-
-// Number of elements of sequence b in this call.
-__device__ __forceinline__ int call_length(const LzwArgs& a, int b) {
-  return a.in_len ? min(max(__builtin_amdgcn_readfirstlane(a.in_len[b]), 0), a.stride) : a.stride;
-}
-
-// A short appended call touches a handful of slots: probing the table where it lives, in global memory,
-// is cheaper than staging all of it in LDS and writing it back (the length is known only on the device,
-// so the LDS kernels take this decision per sequence).
-constexpr int kShortAppend = 64;
-
-template <bool LDS>
-__global__ void __launch_bounds__(kWave) lzw_encode_kernel(LzwArgs a) {
-  __shared__ int32_t tokbuf[kTokBuf];         // token classes: >= 0 valid ID, -2 out of range
-  __shared__ u64 filter[kFilter];
-  if (LDS && !(a.flags & Z2Z_RESET) && call_length(a, blockIdx.x) <= kShortAppend)
-    lzw_encode_rounds<false>(a, tokbuf, filter);
-  else
-    lzw_encode_rounds<LDS>(a, tokbuf, filter);
-}
-
-// ------------------------------------------------------------------------------------------------
-// encode, four waves per sequence
-//
-// With few sequences in a call the machine is nearly empty and a sequence's parse time is what counts: the
-// same rounds, 256 positions wide.  Each of the four waves takes a window of 64 positions and does steps 1
-// and 2 of the round on it, now keeping for every lane also where its chain leaves the window (the offset at
-// which it enters the next one, or "it ends here").  The per-lane (visited set, exit) pairs go to LDS; after a
-// barrier every wave walks the four windows from position 0 (four dependent LDS reads) and knows the phrase
-// starts of the whole round.  Limits, proposal ranks and the publishing of codes are the same with prefix
-// counts over the waves' ballots (exchanged through LDS), the repeat filter is one LDS hash set for all 256
-// positions (insert, barrier, look up, barrier; the first repeat by an LDS atomic minimum), and the table
-// insertions of a round are visible to the next round's chains after the round's last barrier.
-// ------------------------------------------------------------------------------------------------
-constexpr int kWide = 4;
-constexpr int kWideLanes = kWide * kWave;
-constexpr int kWideFilter = 2048;             // slots of the repeat filter (<= 64 * kWide keys)
-struct WideShared {
-  u64 sets[kWide][kWave];
-  int32_t exits[kWide][kWave];
-  u64 cand_mask[kWide], valid_mask[kWide], ins_mask[kWide];
-  int32_t bad_pos[kWide], ovf_pos[kWide], last_code[kWide], last_len[kWide];
-  int32_t cut;
-};
-constexpr int kWideStaticLds = kTokBuf * 4 + kWideFilter * 8 + (int)sizeof(WideShared) + 512;   // + alignment slack
-
-template <bool LDS>
-__global__ void __launch_bounds__(kWideLanes) lzw_encode_wide_kernel(LzwArgs a) {
-  __shared__ int32_t tokbuf[kTokBuf];
-  __shared__ u64 filter[kWideFilter];
-  __shared__ WideShared sh;
-  // a short appended call (its length is known on the device only): one wave, probing the table where it
-  // lives; the other waves leave (the one-wave helper executes no workgroup barrier: see wave_sync)
-  if (!(a.flags & Z2Z_RESET) && call_length(a, blockIdx.x) <= kShortAppend) {
-    if (threadIdx.x < kWave) lzw_encode_rounds<false>(a, tokbuf, filter);
-    return;
-  }
-  const LzwState& st = a.st;
-  const int b = blockIdx.x;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int V = st.V, M = st.M, cap = st.cap;
-  const bool reset = (a.flags & Z2Z_RESET) != 0;
-
-  int C = reset ? 0 : __builtin_amdgcn_readfirstlane(st.size[b]);
-  int prev = reset ? -1 : __builtin_amdgcn_readfirstlane(st.prev_code[b]);
-  int prev_len = reset ? 0 : __builtin_amdgcn_readfirstlane(st.prev_len[b]);
-
-  Table<LDS> t;
-  t.g = st.slots + (size_t)b * st.nslots;
-  t.n = (uint32_t)st.nslots;
-  if (LDS) {
-    for (int i = tid; i < st.nslots; i += kWideLanes) lds_slots[i] = reset ? kEmpty : t.g[i];
-  } else if (reset) {
-    for (int i = tid; i < st.nslots; i += kWideLanes) t.g[i] = kEmpty;
-  }
-  for (int i = tid; i < kWideFilter; i += kWideLanes) filter[i] = kEmpty;
-  if (tid == 0) sh.cut = kWideLanes;
-  sync_after_global_stores();        // (the table cleared in global memory is read past the L1)
-
-  const int n = call_length(a, b);
-  const int32_t* in = a.in + (size_t)b * a.stride;
-  int32_t* out = a.out + (size_t)b * a.out_stride;
-  int32_t* ent_tokens = st.ent_tokens + (size_t)b * cap * M;
-  int32_t* ent_len = st.ent_len + (size_t)b * cap;
-
-  int status = 0;
-  int n_out = 0;
-
-  // an appended call: the entry "last emitted phrase + first token of this call" (see lzw_encode_rounds)
-  if (n > 0 && prev >= 0 && prev_len < M && C < cap) {
-    const int32_t c = __builtin_amdgcn_readfirstlane(in[0]);
-    if (c >= 0 && c < V) {
-      int free_pos = -1;
-      const int idx = t.find(prev, c, &free_pos);
       __syncthreads();     // every wave has looked before wave 0 inserts (else a late wave finds the new edge)
       if (idx < 0 && free_pos >= 0) {
         if (w == 0) {
-          int32_t ph = -1;
+          int32_t ph = -1;        // lane j = token j of the previous phrase
           if (prev < V) {
             ph = lane == 0 ? prev : -1;
           } else if (lane < M) {
@@ -578,206 +504,222 @@ __global__ void __launch_bounds__(kWideLanes) lzw_encode_wide_kernel(LzwArgs a) 
     sync_after_global_stores();
   }
 
-  const u64 lanes_below = (1ull << lane) - 1;
-  const int gpos = w * kWave + lane;      // position of this thread in the round
-  int cbase = 0;
-  bool filled = false;
   bool stop = false;
-  int pos = 0;
+  int pos = 0;                        // first position not yet covered by an emitted phrase
   int n_rounds = 0;
   while (pos < n && !stop) {
-    ++n_rounds;
-    if (!filled || (pos + kWideLanes + M > cbase + kTokBuf && cbase + kTokBuf < n)) {
-      cbase = pos;
-      filled = true;
-      const int cnt = min(kTokBuf, n - cbase);
-      for (int i = tid; i < cnt; i += kWideLanes) {
-        const int32_t v = in[cbase + i];
-        tokbuf[i] = (v >= 0 && v < V) ? v : -2;
-      }
-      __syncthreads();
-    }
-    const int rel = pos - cbase + gpos;
-    auto tk = [&](int d) -> int32_t { return pos + gpos + d < n ? tokbuf[rel + d] : -1; };
+    auto tk = [&](int d) -> int32_t {           // token class at this thread's position + d, -1 past the end
+      const int p = pos + tid + d;
+      return p < n ? sh.tok[p & (kRing - 1)] : -1;
+    };
+    if (tid == 0) sh.bad_pos = sh.ovf_pos = sh.full_pos = sh.spill_pos = W;
 
-    // ---- 1. chains against the table of the round's start ---------------------------------------
+    // ---- 1. chains against the table of the round's start -------------------------------------------
     const int32_t tok0 = tk(0);
     int L0 = tok0 >= 0 ? 1 : 0;
-    int32_t cfin = tok0;
-    int32_t nxt = tk(1);
+    int32_t c0 = tok0;
+    int32_t nxt0 = tk(1);             // always the token that follows this position's match
+    uint32_t h0 = edge_hash(c0, nxt0);
     for (int d = 1; d < M; ++d) {
+      const int32_t after = tk(d + 1);
       int idx = -1;
-      if (L0 == d && nxt >= 0) idx = t.find_lane(cfin, nxt);
+      if (L0 == d && nxt0 >= 0) idx = t.find_lane(c0, nxt0, h0);
       if (__ballot(idx >= 0) == 0) break;
       if (idx >= 0) {
-        cfin = V + idx;
+        c0 = V + idx;
         L0 = d + 1;
-        nxt = tk(d + 1);
+        nxt0 = after;
+        h0 = edge_hash(c0, nxt0);
       }
     }
+    if (__ballot(tok0 == -2) != 0 && lane == 0) sh.cut_asked = 1;
 
-    // ---- 2. the window's chains: visited positions and where they leave the window ----------------
-    int jump = (L0 > 0 && lane + L0 < kWave) ? lane + L0 : kWave;
-    int ex = (L0 > 0 && lane + L0 >= kWave) ? lane + L0 - kWave : -1;
-    uint32_t r_lo = lane < 32 ? 1u << lane : 0u, r_hi = lane < 32 ? 0u : 1u << (lane - 32);
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-      const int src = jump & (kWave - 1);
-      const uint32_t o_lo = __shfl(r_lo, src), o_hi = __shfl(r_hi, src);
-      const int o_jump = __shfl(jump, src), o_ex = __shfl(ex, src);
-      if (jump < kWave) {
-        r_lo |= o_lo;
-        r_hi |= o_hi;
-        ex = o_ex;
-        jump = o_jump;
-      }
-    }
-    sh.sets[w][lane] = ((u64)r_hi << 32) | r_lo;
-    sh.exits[w][lane] = ex;
-    __syncthreads();
-    // the round's phrase starts: walk the windows from position 0
-    u64 S_mine = 0;
-    int starts_before = 0;                      // phrase starts in the windows before this wave's
-    {
-      int e = 0;
-      for (int ww = 0; ww < kWide; ++ww) {
-        u64 S = 0;
-        if (e >= 0) {
-          S = sh.sets[ww][e];
-          e = sh.exits[ww][e];
-        }
-        const int avail_w = min(kWave, n - pos - ww * kWave);      // positions of window ww that exist
-        if (avail_w < kWave) S = avail_w <= 0 ? 0 : (S & ((1ull << avail_w) - 1));
-        if (ww < w) starts_before += __popcll(S);
-        if (ww == w) S_mine = S;
-      }
-    }
-    const int avail = min(kWideLanes, n - pos);
-    const bool start = ((S_mine >> lane) & 1) != 0;
-    const int prank = starts_before + __popcll(S_mine & lanes_below);
-
-    // ---- 3. limits of the round, proposals -------------------------------------------------------
-    const u64 bad_mask = __ballot(start && tok0 == -2);
-    const u64 ovf_mask = __ballot(start && n_out + prank >= a.out_stride);
-    const bool cand = start && tok0 >= 0 && L0 < M && nxt >= 0;
-    const u64 cand_mask = __ballot(cand);
-    if (lane == 0) {
-      sh.bad_pos[w] = bad_mask ? w * kWave + __builtin_ctzll(bad_mask) : kWideLanes;
-      sh.ovf_pos[w] = ovf_mask ? w * kWave + __builtin_ctzll(ovf_mask) : kWideLanes;
-      sh.cand_mask[w] = cand_mask;
-    }
-    __syncthreads();
-    int bad_pos = kWideLanes, ovf_pos = kWideLanes, cand_before = 0, cand_total = 0;
-    for (int ww = 0; ww < kWide; ++ww) {
-      bad_pos = min(bad_pos, sh.bad_pos[ww]);
-      ovf_pos = min(ovf_pos, sh.ovf_pos[ww]);
-      const int cnt = __popcll(sh.cand_mask[ww]);
-      if (ww < w) cand_before += cnt;
-      cand_total += cnt;
-    }
-    const int rank = cand_before + __popcll(cand_mask & lanes_below);
+    const int avail = min(W, n - pos);
     const int room = cap - C;
-    const bool inserter = cand && rank < room;
-
-    // ---- 4. first repeat of a proposed edge (one filter for the whole round) ------------------------
-    int cut = kWideLanes;
-    if (room > 0 && cand_total >= 2) {              // uniform over the workgroup
-      const u64 key = edge_bits(cfin, nxt);
-      const uint32_t h0 = (edge_hash(cfin, nxt) >> 20) & (kWideFilter - 1);
-      int own = -1;
-      if (inserter) {
-        const u64 val = key | (u64)gpos;
-        uint32_t h = h0;
-        for (int probe = 0; probe < kWideFilter; ++probe) {
-          const u64 old = atomicCAS(&filter[h], kEmpty, val);
-          if (old == kEmpty) {
-            own = (int)h;
-            break;
-          }
-          if ((old & ~0xFFFFull) == key) {
-            atomicMin(&filter[h], val);             // same edge: keep the lowest position
-            break;
-          }
-          h = (h + 1) & (kWideFilter - 1);
-        }
+    int L = L0;
+    int32_t code = c0, nxt = nxt0;
+    uint32_t h = h0;
+    bool start = false, cand = false;
+    u64 start_mask = 0, cand_mask = 0;
+    int overrun = 0;                  // positions of the next window that the last phrase covers
+    int own = -1;                     // the slot this thread claimed in the set of this iteration
+    SkipFn before;                    // skip function of the lanes below
+    auto skip_functions = [&]() {
+      SkipFn f = {0x02010000u | (uint32_t)(max(L, 1) - 1), 0x06050403u};
+      f = skip_scan64<M4>(f);
+      if (lane == kWave - 1) sh.skip[w] = ((u64)f.hi << 32) | f.lo;
+      before.lo = __builtin_amdgcn_update_dpp(kSkipIdLo, f.lo, 0x138, 0xf, 0xf, false);        // wave_shr:1
+      before.hi = M4 ? kSkipIdHi : __builtin_amdgcn_update_dpp(kSkipIdHi, f.hi, 0x138, 0xf, 0xf, false);
+    };
+    skip_functions();
+    __syncthreads();
+    for (int it = 0; it <= W; ++it) {           // (a start becomes final with every iteration: the bound is never met)
+      ++n_rounds;
+      // ---- 2. starts ---------------------------------------------------------------------------------
+      SkipFn g = {kSkipIdLo, kSkipIdHi};
+      if (lane < NW) {
+        const u64 v = sh.skip[lane];
+        g.lo = (uint32_t)v;
+        g.hi = (uint32_t)(v >> 32);
       }
-      __syncthreads();
-      int fpos = kWideLanes;
+      g = skip_scan16<M4>(g);
+      overrun = __builtin_amdgcn_readlane((int)g.lo, NW - 1) & 0xFF;
+      const uint32_t s0 = w == 0 ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)g.lo, w == 0 ? 0 : w - 1) & 0xFFu;
+      const uint32_t state = ((s0 < 4 ? before.lo : before.hi) >> (8 * (s0 & 3))) & 0xFFu;
+      start = state == 0 && tid < avail;
+      cand = start && L >= 1 && L < M && nxt >= 0;
+      start_mask = __ballot(start);
+      cand_mask = __ballot(cand);
+      if (lane == 0) sh.count[w] = (uint32_t)__popcll(start_mask) | ((uint32_t)__popcll(cand_mask) << 16);
+      if (room <= 0) break;
+      // ---- 3. proposals -------------------------------------------------------------------------------
+      uint32_t* set = sh.set[it & 1];
+      if (own >= 0) sh.set[(it + 1) & 1][own] = kRoundEmpty;     // the previous iteration's
+      own = -1;
       if (cand) {
-        uint32_t h = h0;
-        for (int probe = 0; probe < kWideFilter; ++probe) {
-          const u64 sl = filter[h];
-          if (sl == kEmpty) break;
-          if ((sl & ~0xFFFFull) == key) {
-            fpos = (int)(sl & 0xFFFFull);
-            break;
-          }
-          h = (h + 1) & (kWideFilter - 1);
+        own = Set::insert(set, sh.key, h, round_key(code, nxt), tid);
+        if (own == -2) {                                         // later positions cannot see this edge
+          atomicMin(&sh.spill_pos, tid + 1);
+          sh.cut_asked = 1;
         }
       }
-      const u64 dup_mask = __ballot(cand && fpos < gpos);
-      if (dup_mask && lane == 0) atomicMin(&sh.cut, w * kWave + __builtin_ctzll(dup_mask));
       __syncthreads();
-      cut = sh.cut;
-      if (own >= 0) filter[own] = kEmpty;           // leave the filter empty for the next round
+      // ---- 4. matches with the entries of the round ------------------------------------------------------
+      if (tid == 0) sh.changed[(it + 1) & 1] = 0;
+      int L2 = L0;
+      int32_t code2 = c0, nxt2 = nxt0;
+      uint32_t h2 = h0;
+      bool more = L0 >= 1 && L0 < M && nxt0 >= 0;
+      while (__ballot(more) != 0) {
+        if (more) {
+          const int q = Set::find(set, sh.key, h2, round_key(code2, nxt2), tid);
+          more = q >= 0;
+          if (more) {
+            code2 = kRoundEntry | q;
+            ++L2;
+            nxt2 = tk(L2);
+            h2 = edge_hash(code2, nxt2);
+            more = L2 < M && nxt2 >= 0;
+          }
+        }
+      }
+      // (which edges found no slot depends on timing; positions from the first of them on are cut off this window)
+      const bool ch = start && (L2 != L || code2 != code) && tid < *(volatile int32_t*)&sh.spill_pos;
+      L = L2;
+      code = code2;
+      nxt = nxt2;
+      h = h2;
+      if (__ballot(ch) != 0 && lane == 0) sh.changed[it & 1] = 1;
+      skip_functions();
+      __syncthreads();
+      if (sh.changed[it & 1] == 0) {
+        if (own >= 0) set[own] = kRoundEmpty;
+        break;
+      }
     }
 
-    // ---- 5. publish ---------------------------------------------------------------------------------
-    const int limit = min(min(avail, cut), min(bad_pos, ovf_pos));
-    if (bad_pos < kWideLanes && limit == bad_pos) {
-      status |= Z2Z_ST_BAD_TOKEN;
-      stop = true;
-    } else if (ovf_pos < kWideLanes && limit == ovf_pos) {
-      status |= Z2Z_ST_OVERFLOW;
-      stop = true;
+    // ---- 5. limits of the window ------------------------------------------------------------------------
+    if (room <= 0) __syncthreads();             // (the counts; after an iteration with proposals they are there)
+    uint32_t counts = row_scan_add(lane < NW ? sh.count[lane] : 0u);
+    const uint32_t below = w == 0 ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)counts, w == 0 ? 0 : w - 1);
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)counts, NW - 1);
+    const u64 lanes_below = (1ull << lane) - 1;
+    const int prank = (int)(below & 0xFFFFu) + __popcll(start_mask & lanes_below);   // phrases before this one
+    const int rank = (int)(below >> 16) + __popcll(cand_mask & lanes_below);         // proposals before this one
+    int n_start = (int)(total & 0xFFFFu), n_cand = (int)(total >> 16);
+    int limit = avail;
+    bool valid = start;
+    u64 valid_mask = start_mask;
+    u64 waves = __ballot(lane < NW && (sh.count[lane & (kMaxWaves - 1)] & 0xFFFFu) != 0);   // waves with a start
+    const bool whole = !(sh.cut_asked || n_out + n_start > a.out_stride || (room > 0 && n_cand > room));   // uniform
+    if (!whole) {
+      const u64 bad_mask = __ballot(start && tok0 == -2);
+      const u64 ovf_mask = __ballot(start && n_out + prank >= a.out_stride);
+      const u64 full_mask = __ballot(room > 0 && cand && rank >= room);
+      if (lane == 0) {
+        if (bad_mask) atomicMin(&sh.bad_pos, w * kWave + (int)__builtin_ctzll(bad_mask));
+        if (ovf_mask) atomicMin(&sh.ovf_pos, w * kWave + (int)__builtin_ctzll(ovf_mask));
+        if (full_mask) atomicMin(&sh.full_pos, w * kWave + (int)__builtin_ctzll(full_mask));
+      }
+      __syncthreads();
+      const int bad_pos = sh.bad_pos, ovf_pos = sh.ovf_pos;
+      limit = min(min(avail, min(sh.full_pos, sh.spill_pos)), min(bad_pos, ovf_pos));
+      if (bad_pos < W && limit == bad_pos) {
+        status |= Z2Z_ST_BAD_TOKEN;             // the sequence ends just before this token
+        stop = true;
+      } else if (ovf_pos < W && limit == ovf_pos) {
+        status |= Z2Z_ST_OVERFLOW;
+        stop = true;
+      }
+      valid = start && tid < limit;
+      valid_mask = __ballot(valid);
+      const u64 ins_mask = __ballot(cand && tid < limit);
+      if (lane == 0) sh.count_valid[w] = (uint32_t)__popcll(valid_mask) | ((uint32_t)__popcll(ins_mask) << 16);
+      __syncthreads();
+      const uint32_t mine = lane < NW ? sh.count_valid[lane] : 0u;
+      waves = __ballot((mine & 0xFFFFu) != 0);
+      const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)row_scan_add(mine), NW - 1);
+      n_start = (int)(all & 0xFFFFu);
+      n_cand = (int)(all >> 16);
     }
-    const bool valid = start && gpos < limit;
-    const u64 valid_mask = __ballot(valid);
-    if (valid) out[n_out + prank] = cfin;
-    const bool ins = valid && inserter;
+
+    // ---- 6. publish ------------------------------------------------------------------------------------
+    int32_t T[M4 ? 4 : Z2Z_MAX_M];              // the tokens of the entry this position makes
+    const bool ins = room > 0 && valid && cand;
+    if (room > 0) {
+      if (cand) sh.rank[tid] = (uint16_t)rank;
+#pragma unroll
+      for (int k = 0; k < (M4 ? 4 : Z2Z_MAX_M); ++k) T[k] = ins && k < M && k <= L ? tk(k) : -1;
+      __syncthreads();
+      if (valid && (code & kRoundEntry) != 0) code = V + C + (int)sh.rank[code & (kRoundEntry - 1)];
+    }
+    // a window published whole ends at pos + W + overrun; the ring takes the next tokens in place of those behind it
+    auto refill = [&](int32_t next_pos) {
+      const int cnt = min(W, next_pos + kRing - fill);
+      const int p = fill + tid;
+      if (tid < cnt) sh.tok[p & (kRing - 1)] = p < n ? classify(ahead) : -1;
+      fill += cnt;
+      ahead = fill + tid < n ? in[fill + tid] : 0;
+    };
+    const bool early = whole && avail == W;
+    if (early && fill < n) refill(pos + W + overrun);
+    if (valid) out[n_out + prank] = code;
     if (ins) {
       const int idx = C + rank;
-      t.insert_lane(cfin, nxt, idx);
+      t.insert_lane(code, nxt, idx);
       int32_t* row = ent_tokens + (size_t)idx * M;
-      for (int k = 0; k < M; ++k) row[k] = k <= L0 ? tokbuf[rel + k] : -1;
-      ent_len[idx] = L0 + 1;
+#pragma unroll
+      for (int k = 0; k < (M4 ? 4 : Z2Z_MAX_M); ++k)
+        if (k < M) row[k] = T[k];
+      ent_len[idx] = L + 1;
     }
-    const u64 ins_mask = __ballot(ins);
-    if (valid_mask) {
-      const int last = 63 - __builtin_clzll(valid_mask);
-      const int lc = __builtin_amdgcn_readlane(cfin, last), ll = __builtin_amdgcn_readlane(L0, last);
-      if (lane == 0) {
-        sh.last_code[w] = lc;
-        sh.last_len[w] = ll;
-      }
+    if (waves != 0 && w == 63 - (int)__builtin_clzll(waves) && lane == 63 - (int)__builtin_clzll(valid_mask)) {
+      sh.last_code = code;
+      sh.last_len = L;
+      sh.last_end = pos + tid + L;
     }
-    if (lane == 0) {
-      sh.valid_mask[w] = valid_mask;
-      sh.ins_mask[w] = ins_mask;
-    }
-    sync_after_global_stores();
-    if (tid == 0) sh.cut = kWideLanes;              // everybody has read it; next written after two more barriers
-    int last_w = -1;
-    for (int ww = 0; ww < kWide; ++ww) {
-      const u64 vm = sh.valid_mask[ww];
-      C += __popcll(sh.ins_mask[ww]);
-      n_out += __popcll(vm);
-      if (vm) last_w = ww;
-    }
-    if (last_w >= 0) {
-      const int last = 63 - __builtin_clzll(sh.valid_mask[last_w]);
-      prev = sh.last_code[last_w];
-      prev_len = sh.last_len[last_w];
-      pos += last_w * kWave + last + prev_len;
+    __syncthreads();                            // insertions, last phrase, staged tokens
+    if (room > 0) C += n_cand;
+    n_out += n_start;
+    if (waves != 0) {
+      prev = sh.last_code;
+      prev_len = sh.last_len;
+      pos = sh.last_end;
     } else {
-      stop = true;
+      stop = true;                              // a limit of 0: bad token or no room at the first start
     }
-    __syncthreads();                                // the exchange arrays are free for the next round
+    // after a cut window, or when the last phrases of many windows have used up the slack
+    while (fill < n && (!early || fill < pos + W + 32)) {
+      refill(pos);
+      __syncthreads();
+      if (fill >= pos + W + 32) break;
+    }
   }
 
-  if (LDS) {
-    __syncthreads();
-    for (int i = tid; i < st.nslots; i += kWideLanes) t.g[i] = lds_slots[i];
+  table_close_all<LDS, W>(tid, t);
+  if (reset) {                                  // rows of the codebook that was there before
+    for (int i = C + tid; i < size0; i += W) ent_len[i] = 0;
+    for (int i = C * M + tid; i < size0 * M; i += W) ent_tokens[i] = -1;
   }
   if (tid == 0) {
     st.size[b] = C;
@@ -786,6 +728,22 @@ __global__ void __launch_bounds__(kWideLanes) lzw_encode_wide_kernel(LzwArgs a) 
     st.rounds[b] = n_rounds;
     a.out_n[b] = n_out;
     a.status[b] = status;
+  }
+}
+
+// A short appended call touches a handful of slots: probing the table where it lives, in global memory,
+// is cheaper than staging all of it in LDS and writing it back (the length is known only on the device,
+// so the LDS kernels take this decision per sequence).
+template <int NW, bool LDS>
+__global__ void __launch_bounds__(NW * kWave) lzw_encode_kernel(LzwArgs a) {
+  __shared__ EncShared<NW> sh;
+  const bool short_append = !(a.flags & Z2Z_RESET) && call_length(a, blockIdx.x) <= kShortAppend;
+  if (LDS && short_append) {
+    lzw_encode_windows<NW, false, false>(a, sh);
+  } else if (a.st.M <= 4) {
+    lzw_encode_windows<NW, LDS, true>(a, sh);
+  } else {
+    lzw_encode_windows<NW, LDS, false>(a, sh);
   }
 }
 
@@ -982,537 +940,300 @@ __global__ void __launch_bounds__(kStepWaves * kWave) lzw_step_update_kernel(Lzw
   if (w < ea.split) z2z_embed::embed_row<BF16>(ea, toks, L, row, lane, w);
 }
 
-// Entry data written earlier in the same launch is read past the vector L1.
-__device__ __forceinline__ int32_t load_fresh(const int32_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Rounds of up to 63 codes, one code per lane; lane 0 stands for the code before the round (its phrase
-// is the parent of the entry the first code of the round may cause).
-//   1. (length, first token) of every code whose entry existed when the round began; the round ends
-//      before the first code that names a later entry (or no entry at all).  If that is the very first
-//      code of the round it is taken alone, the textbook way (the one not-yet-defined code, or an error).
-//   2. code i proposes the edge (code i-1, first token of code i) if code i-1 is shorter than M; the
-//      table is probed for all proposals at once; absent ones get consecutive entry numbers while the
-//      codebook has room.  As in the encoder the round is cut at the first proposal that repeats an
-//      earlier one of the same round (only streams that no greedy parse produced have such repeats).
-//   3. token offsets are a prefix sum of the lengths (lengths are < 16: four ballots); the round is cut
-//      before the first code whose tokens do not fit.
-//   4. the lanes before the cut insert their edges, lane i-1 writes the flattened row of the entry that
-//      code i caused (its own tokens + that first token), and every lane writes its tokens.
-template <bool LDS>
-__device__ __forceinline__ void lzw_decode_rounds(const LzwArgs& a, int32_t* codebuf, u64* filter) {
-  const LzwState& st = a.st;
-  const int b = blockIdx.x;
-  const int lane = threadIdx.x;
-  const int V = st.V, M = st.M, cap = st.cap;
-  const bool reset = (a.flags & Z2Z_RESET) != 0;
-  const bool ef_lds = LDS && a.lds_ef;
-  uint32_t* ef = reinterpret_cast<uint32_t*>(lds_slots + st.nslots);   // [cap], valid when ef_lds
-  int32_t* ent_tokens = st.ent_tokens + (size_t)b * cap * M;
-  int32_t* ent_len = st.ent_len + (size_t)b * cap;
-
-  int C = reset ? 0 : __builtin_amdgcn_readfirstlane(st.size[b]);
-  int prev = reset ? -1 : __builtin_amdgcn_readfirstlane(st.prev_code[b]);
-  int prev_len = reset ? 0 : __builtin_amdgcn_readfirstlane(st.prev_len[b]);
-
-  Table<LDS> t;
-  if (ef_lds && !reset) {
-    for (int i = lane; i < C; i += kWave) ef[i] = pack_ef(ent_len[i], ent_tokens[(size_t)i * M]);
-  }
-  table_open<LDS>(a, b, lane, reset, &t);
-  for (int i = lane; i < kFilter; i += kWave) filter[i] = kEmpty;
-
-  const int n = a.in_len ? min(max(__builtin_amdgcn_readfirstlane(a.in_len[b]), 0), a.stride) : a.stride;
-  const int32_t* in = a.in + (size_t)b * a.stride;
-  int32_t* out = a.out ? a.out + (size_t)b * a.out_stride : nullptr;
-
-  const u64 lanes_upto = lane == 63 ? ~0ull : (2ull << lane) - 1;     // lanes 0..lane
-  const u64 lanes_below = (1ull << lane) - 1;
-  int status = 0;
-  int n_out = 0;
-  bool stop = false;
-  int cbase = 0;                      // codebuf holds codes [cbase, cbase + kTokBuf)
-  bool filled = false;
-  int cpos = 0;                       // codes consumed
-  int n_rounds = 0;
-  while (cpos < n && !stop) {
-    ++n_rounds;
-    if (!filled || (cpos + kWave > cbase + kTokBuf && cbase + kTokBuf < n)) {
-      cbase = cpos;
-      filled = true;
-      const int cnt = min(kTokBuf, n - cbase);
-      for (int i = lane; i < cnt; i += kWave) codebuf[i] = in[cbase + i];
-      lds_order();
-    }
-    // ---- 1. the codes of the round ------------------------------------------------------------------
-    const int ci = cpos + lane - 1;
-    const bool present = lane == 0 ? prev >= 0 : ci < n;
-    const int32_t k = lane == 0 ? prev : (ci < n ? codebuf[ci - cbase] : -1);
-    int len = 0;
-    int32_t first = 0;
-    bool known = false;
-    if (present && k >= 0 && k < V) {
-      len = 1;
-      first = k;
-      known = true;
-    } else if (present && k >= V && k - V < C) {
-      const uint32_t e = ef_lds ? ef[k - V]
-                                : pack_ef(load_fresh(&ent_len[k - V]), load_fresh(&ent_tokens[(size_t)(k - V) * M]));
-      len = (int)(e >> 28);
-      first = (int32_t)(e & 0x0FFFFFFFu);
-      known = true;
-    }
-    const u64 hard_mask = __ballot(present && !known);          // never lane 0
-    const int hard_pos = hard_mask ? __builtin_ctzll(hard_mask) : kWave;
-
-    if (hard_pos == 1) {
-      // the first code of the round names no entry of the codebook as it stands: it is either
-      // "previous phrase + its own first token", which must be legal and absent, or an error
-      const int32_t k1 = __builtin_amdgcn_readlane(k, 1);
-      bool ok = false;
-      if (k1 >= V && k1 - V == C && prev >= 0 && prev_len < M && C < cap) {
-        const int32_t pf = __builtin_amdgcn_readlane(first, 0);
-        int free_pos = -1;
-        const int idx = t.find(prev, pf, &free_pos);
-        if (idx < 0 && free_pos >= 0) {
-          const int cur_len = prev_len + 1;
-          if (out != nullptr && n_out + cur_len > a.out_stride) {
-            status |= Z2Z_ST_OVERFLOW;
-            stop = true;
-          } else {
-            int32_t tokj = -1;        // lane j: token j of the new phrase
-            if (lane < prev_len) tokj = prev < V ? prev : load_fresh(&ent_tokens[(size_t)(prev - V) * M + lane]);
-            if (lane == prev_len) tokj = pf;
-            if (lane == 0) {
-              t.store((uint32_t)free_pos, edge_bits(prev, pf) | (u64)(uint32_t)C);
-              if (ef_lds) ef[C] = pack_ef(cur_len, pf);
-              ent_len[C] = cur_len;
-            }
-            if (lane < M) ent_tokens[(size_t)C * M + lane] = tokj;
-            if (out != nullptr && lane < cur_len) out[n_out + lane] = tokj;
-            prev = k1;
-            prev_len = cur_len;
-            ++C;
-            n_out += cur_len;
-            ++cpos;
-          }
-          ok = true;
-        }
-      }
-      if (!ok) {
-        status |= Z2Z_ST_BAD_CODE;
-        stop = true;
-      }
-      wave_sync();                    // the new row is in memory before a later round reads it
-      continue;
-    }
-
-    // ---- 2. proposals --------------------------------------------------------------------------------
-    const int limit0 = min(hard_pos, min(kWave, n - cpos + 1));  // lanes 1 .. limit0-1 hold known codes
-    const int32_t pk = __shfl_up(k, 1);
-    const int plen = __shfl_up(len, 1);
-    const int32_t pfirst = __shfl_up(first, 1);
-    const bool pknown = __shfl_up((int)known, 1) != 0;
-    const int room = cap - C;
-    const bool prop = lane >= 1 && lane < limit0 && pknown && plen < M && room > 0;
-    int found = -1;
-    if (prop) found = t.find_lane(pk, first);
-    const bool cand = prop && found < 0;
-    const u64 cand_mask = __ballot(cand);
-    const int rank = __popcll(cand_mask & lanes_below);
-    const bool inserter = cand && rank < room;
-    int cut = kWave;
-    if ((cand_mask & (cand_mask - 1)) != 0) cut = first_repeat(filter, lane, cand, inserter, pk, first);
-
-    // ---- 3. token offsets -------------------------------------------------------------------------------
-    const int mylen = (lane >= 1 && lane < limit0) ? len : 0;
-    int incl = 0;                     // tokens of codes 1 .. lane of the round
-#pragma unroll
-    for (int bit = 0; bit < 4; ++bit) incl += __popcll(__ballot((mylen >> bit) & 1) & lanes_upto) << bit;
-    const u64 ovf_mask = __ballot(out != nullptr && mylen > 0 && n_out + incl > a.out_stride);
-    const int ovf_pos = ovf_mask ? __builtin_ctzll(ovf_mask) : kWave;
-    const int limit = min(limit0, min(cut, ovf_pos));
-    if (ovf_pos < kWave && limit == ovf_pos) {
-      status |= Z2Z_ST_OVERFLOW;
-      stop = true;
-    }
-
-    // ---- 4. publish ---------------------------------------------------------------------------------------
-    const bool valid = lane >= 1 && lane < limit;
-    const bool ins = valid && inserter;
-    const int idx = C + rank;
-    if (ins) {
-      t.insert_lane(pk, first, idx);
-      if (ef_lds) ef[idx] = pack_ef(plen + 1, pfirst);
-    }
-    // the tokens of this lane's own code (lane 0: of the code before the round)
-    int32_t T[Z2Z_MAX_M];
-#pragma unroll
-    for (int j = 0; j < Z2Z_MAX_M; ++j) T[j] = -1;
-    if (lane < limit && known) {
-      if (k < V) {
-        T[0] = k;
-      } else {
-        const int32_t* row = ent_tokens + (size_t)(k - V) * M;
-#pragma unroll
-        for (int j = 0; j < Z2Z_MAX_M; ++j)
-          if (j < len) T[j] = load_fresh(&row[j]);
-      }
-    }
-    // the entry caused by the next lane's code: this lane's tokens + that code's first token
-    const bool s_ins = __shfl_down((int)ins, 1) != 0 && lane < kWave - 1;
-    const int s_idx = __shfl_down(idx, 1);
-    const int32_t s_first = __shfl_down(first, 1);
-    if (s_ins) {
-      int32_t* row = ent_tokens + (size_t)s_idx * M;
-#pragma unroll
-      for (int j = 0; j < Z2Z_MAX_M; ++j)
-        if (j < M) row[j] = j < len ? T[j] : (j == len ? s_first : -1);
-      ent_len[s_idx] = len + 1;
-    }
-    if (valid && out != nullptr) {
-      int32_t* dst = out + n_out + incl - len;
-#pragma unroll
-      for (int j = 0; j < Z2Z_MAX_M; ++j)
-        if (j < len) dst[j] = T[j];
-    }
-    C += __popcll(__ballot(ins));
-    if (limit >= 2) {
-      const int last = limit - 1;
-      prev = __builtin_amdgcn_readlane(k, last);
-      prev_len = __builtin_amdgcn_readlane(len, last);
-      n_out += __builtin_amdgcn_readlane(incl, last);
-      cpos += last;
-    } else {
-      stop = true;                    // only reached when the first code of the round does not fit
-    }
-    wave_sync();                      // rows written above are in memory before a later round reads them
-  }
-
-  table_close<LDS>(a, lane, t);
-  if (lane == 0) {
-    st.size[b] = C;
-    st.prev_code[b] = prev;
-    st.prev_len[b] = prev_len;
-    st.rounds[b] = n_rounds;
-    a.out_n[b] = n_out;
-    a.status[b] = status;
-  }
-}
-
-template <bool LDS>
-__global__ void __launch_bounds__(kWave) lzw_decode_kernel(LzwArgs a) {
-  __shared__ int32_t codebuf[kTokBuf];
-  __shared__ u64 filter[kFilter];
-  if (LDS && !(a.flags & Z2Z_RESET) && call_length(a, blockIdx.x) <= kShortAppend)
-    lzw_decode_rounds<false>(a, codebuf, filter);
-  else
-    lzw_decode_rounds<LDS>(a, codebuf, filter);
-}
-
 // ------------------------------------------------------------------------------------------------
-// decode, four waves per sequence (few long sequences: see the encoder's counterpart)
+// decode
 //
-// A round takes up to 255 codes: global lane g = 64 * wave + lane holds code cpos + g - 1, global lane 0 the code
-// before the round.  The steps are those of lzw_decode_rounds; what crosses a window boundary goes through LDS:
-// the first code that names no entry yet (minimum over the waves), the (code, length, first token) of every
-// window's last lane for the next window's first proposal, proposal ranks and token offsets as prefix counts
-// over the waves, one repeat filter for the round.  A lane that inserts writes the new entry's row itself (the
-// previous code's tokens, which are older than the round, plus its own first token), so no registers cross
-// the boundary.  The one code that may name the entry it creates is taken alone at the head of a round by
-// every wave alike, wave 0 doing the stores.
+// Rounds like the encoder's: thread g of a window holds code cpos + g - 1, thread 0 the code before the window.
+// Code g makes the entry (code g-1, first token of code g) if code g-1 is shorter than M, the codebook has room and
+// the edge is absent; (length, first token) of a code come from the codebook as it stood when the round began, or,
+// for an entry of this round, from the code before its maker.  Again a recurrence over lower positions, solved by
+// iteration:
+//   1. codes that are base tokens or old entries have their (length, first token); edges between those are looked
+//      up in the table at once.  Codes that name entries of this round start from a guess.
+//   2. who makes an entry follows from the lengths; the makers' ranks are a prefix count, maker[rank] = position.
+//   3. a code that names entry `rank` of this round takes (length + 1, first token) from the position before its
+//      maker, or is invalid if that entry is made after it.  When nothing changes the values are exact.
+//   4. what 1-3 assume about edges that involve this round's entries (that they are new) is checked: edges a late
+//      look-up finds in the table, and edges proposed twice in the window (the encoder's round set); the window is cut at
+//      the first such position, which the next round meets as its first code, where everything is known.  Streams
+//      of a greedy parse have none.
+//   5. publish: token offsets are prefix sums of the lengths; a thread writes its code's tokens to the output and,
+//      with the next code's first token behind them, to the row of the entry the next code makes.
+// A chain of entries of this round is at most M long, so two to four iterations are usual.
 // ------------------------------------------------------------------------------------------------
-struct WideDecShared {
-  int32_t hard[kWide], edge_k[kWide], edge_len[kWide], edge_first[kWide], edge_known[kWide];
-  int32_t k1, first0;
-  u64 cand_mask[kWide];
-  int32_t lensum[kWide], ovf[kWide], ins_cnt[kWide];
-  int32_t last_k, last_len, last_incl;
-  int32_t cut;
+template <int NW>
+struct DecShared {
+  static constexpr int W = NW * kWave;
+  static constexpr int kSet = 4 * W;
+  uint32_t set[kSet];
+  u64 key[W];
+  u64 makes[kMaxWaves];                      // codes that make an entry, a mask per wave
+  int32_t ring[2 * W];                       // codes: code p at p & (2 W - 1)
+  int32_t code[W];                           // of the window
+  uint32_t info[W];                          // pack_ef(length, first token)
+  uint32_t count[kMaxWaves];                 // entries made | tokens << 16 of each wave
+  int32_t changed[2];
+  int32_t bad_pos, ovf_pos, cut;             // where the window ends early
+  int32_t last_code, last_len, last_tokens, last_made;
+  uint16_t maker[W];                         // position of the code that makes entry `rank` of the round
 };
-static_assert(sizeof(WideDecShared) <= sizeof(WideShared), "the decoder's exchange area fits the encoder's LDS budget");
+static_assert(sizeof(DecShared<kMaxWaves>) <= sizeof(EncShared<kMaxWaves>), "one LDS budget for both directions");
 
-template <bool LDS>
-__global__ void __launch_bounds__(kWideLanes) lzw_decode_wide_kernel(LzwArgs a) {
-  __shared__ int32_t codebuf[kTokBuf];
-  __shared__ u64 filter[kWideFilter];
-  __shared__ WideDecShared sh;
-  if (!(a.flags & Z2Z_RESET) && call_length(a, blockIdx.x) <= kShortAppend) {      // see the encoder
-    if (threadIdx.x < kWave) lzw_decode_rounds<false>(a, codebuf, filter);
-    return;
-  }
+template <int NW, bool LDS, bool M4>
+__device__ __forceinline__ void lzw_decode_windows(const LzwArgs& a, DecShared<NW>& sh) {
+  constexpr int W = NW * kWave;
+  constexpr int kSet = DecShared<NW>::kSet, kRing = 2 * W;
+  constexpr int kTok = M4 ? 4 : Z2Z_MAX_M;
+  constexpr int32_t kFirst = 0x0FFFFFFF;
+  typedef RoundSet<kSet> Set;
   const LzwState& st = a.st;
   const int b = blockIdx.x;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int g = tid;                                 // global lane of the round
   const int V = st.V, M = st.M, cap = st.cap;
   const bool reset = (a.flags & Z2Z_RESET) != 0;
   const bool ef_lds = LDS && a.lds_ef;
-  uint32_t* ef = reinterpret_cast<uint32_t*>(lds_slots + st.nslots);
-  int32_t* ent_tokens = st.ent_tokens + (size_t)b * cap * M;
-  int32_t* ent_len = st.ent_len + (size_t)b * cap;
+  uint32_t* ef = reinterpret_cast<uint32_t*>(lds_slots + st.nslots);   // [cap], valid when ef_lds
 
-  int C = reset ? 0 : __builtin_amdgcn_readfirstlane(st.size[b]);
+  const int size0 = __builtin_amdgcn_readfirstlane(st.size[b]);
+  int C = reset ? 0 : size0;
   int prev = reset ? -1 : __builtin_amdgcn_readfirstlane(st.prev_code[b]);
   int prev_len = reset ? 0 : __builtin_amdgcn_readfirstlane(st.prev_len[b]);
-
-  Table<LDS> t;
-  t.g = st.slots + (size_t)b * st.nslots;
-  t.n = (uint32_t)st.nslots;
-  if (ef_lds && !reset) {
-    for (int i = tid; i < C; i += kWideLanes) ef[i] = pack_ef(ent_len[i], ent_tokens[(size_t)i * M]);
-  }
-  if (LDS) {
-    for (int i = tid; i < st.nslots; i += kWideLanes) lds_slots[i] = reset ? kEmpty : t.g[i];
-  } else if (reset) {
-    for (int i = tid; i < st.nslots; i += kWideLanes) t.g[i] = kEmpty;
-  }
-  for (int i = tid; i < kWideFilter; i += kWideLanes) filter[i] = kEmpty;
-  if (tid == 0) sh.cut = kWideLanes;
-  sync_after_global_stores();        // (the table cleared in global memory is read past the L1)
-
   const int n = call_length(a, b);
   const int32_t* in = a.in + (size_t)b * a.stride;
   int32_t* out = a.out ? a.out + (size_t)b * a.out_stride : nullptr;
+  int32_t* ent_tokens = st.ent_tokens + (size_t)b * cap * M;
+  int32_t* ent_len = st.ent_len + (size_t)b * cap;
 
-  const u64 lanes_upto = lane == 63 ? ~0ull : (2ull << lane) - 1;
+  Table<LDS> t;
+  table_open_all<LDS, W>(a, b, tid, reset, &t);
+  if (ef_lds && !reset) {
+    for (int i = tid; i < C; i += W) ef[i] = pack_ef(ent_len[i], ent_tokens[(size_t)i * M]);
+  }
+  for (int i = tid; i < kSet; i += W) sh.set[i] = kRoundEmpty;
+  int fill = kRing;
+  for (int i = tid; i < kRing; i += W) sh.ring[i] = i < n ? in[i] : -1;
+  int32_t ahead = fill + tid < n ? in[fill + tid] : -1;
+  if (tid == 0) sh.changed[0] = sh.changed[1] = 0;
+  sync_after_global_stores();        // (a table cleared in global memory is read past the L1)
+
   const u64 lanes_below = (1ull << lane) - 1;
   int status = 0;
   int n_out = 0;
   bool stop = false;
-  int cbase = 0;
-  bool filled = false;
-  int cpos = 0;
+  int cpos = 0;                       // codes consumed
   int n_rounds = 0;
   while (cpos < n && !stop) {
-    ++n_rounds;
-    if (!filled || (cpos + kWideLanes > cbase + kTokBuf && cbase + kTokBuf < n)) {
-      cbase = cpos;
-      filled = true;
-      const int cnt = min(kTokBuf, n - cbase);
-      for (int i = tid; i < cnt; i += kWideLanes) codebuf[i] = in[cbase + i];
-      __syncthreads();
-    }
-    // ---- 1. the codes of the round ------------------------------------------------------------------
-    const int ci = cpos + g - 1;
-    const bool present = g == 0 ? prev >= 0 : ci < n;
-    const int32_t k = g == 0 ? prev : (ci < n ? codebuf[ci - cbase] : -1);
+    // ---- 1. the codes of the window ---------------------------------------------------------------------
+    const int ci = cpos + tid - 1;
+    const bool present = tid == 0 ? prev >= 0 : ci < n;
+    const int32_t k = tid == 0 ? prev : (ci < n ? sh.ring[ci & (kRing - 1)] : -1);
+    const bool old_entry = present && k >= V && k - V < C;
+    const bool new_entry = present && tid > 0 && k >= V + C;
     int len = 0;
     int32_t first = 0;
-    bool known = false;
+    int32_t T[kTok];                  // the tokens of a base token or an old entry
+#pragma unroll
+    for (int j = 0; j < kTok; ++j) T[j] = -1;
     if (present && k >= 0 && k < V) {
       len = 1;
-      first = k;
-      known = true;
-    } else if (present && k >= V && k - V < C) {
-      const uint32_t e = ef_lds ? ef[k - V]
-                                : pack_ef(load_fresh(&ent_len[k - V]), load_fresh(&ent_tokens[(size_t)(k - V) * M]));
-      len = (int)(e >> 28);
-      first = (int32_t)(e & 0x0FFFFFFFu);
-      known = true;
-    }
-    const u64 hard_mask = __ballot(present && !known);            // never global lane 0
-    if (lane == 0) sh.hard[w] = hard_mask ? w * kWave + __builtin_ctzll(hard_mask) : kWideLanes;
-    if (lane == kWave - 1) {
-      sh.edge_k[w] = k;
-      sh.edge_len[w] = len;
-      sh.edge_first[w] = first;
-      sh.edge_known[w] = known ? 1 : 0;
-    }
-    if (tid == 0) sh.first0 = first;
-    if (tid == 1) sh.k1 = k;
-    __syncthreads();
-    int hard_pos = kWideLanes;
-    for (int ww = 0; ww < kWide; ++ww) hard_pos = min(hard_pos, sh.hard[ww]);
-
-    if (hard_pos == 1) {
-      // the first code of the round names no entry of the codebook as it stands: "previous phrase + its own
-      // first token", legal and absent, or an error.  Every wave takes the same decisions (hence the barrier between the
-      // lookup and the store); wave 0 stores.
-      const int32_t k1 = sh.k1;
-      bool ok = false;
-      if (k1 >= V && k1 - V == C && prev >= 0 && prev_len < M && C < cap) {
-        const int32_t pf = sh.first0;
-        int free_pos = -1;
-        const int idx = t.find(prev, pf, &free_pos);
-        __syncthreads();   // every wave has looked before wave 0 stores (else a late wave finds the new edge)
-        if (idx < 0 && free_pos >= 0) {
-          const int cur_len = prev_len + 1;
-          if (out != nullptr && n_out + cur_len > a.out_stride) {
-            status |= Z2Z_ST_OVERFLOW;
-            stop = true;
-          } else {
-            if (w == 0) {
-              int32_t tokj = -1;        // lane j: token j of the new phrase
-              if (lane < prev_len) tokj = prev < V ? prev : load_fresh(&ent_tokens[(size_t)(prev - V) * M + lane]);
-              if (lane == prev_len) tokj = pf;
-              if (lane == 0) {
-                t.store((uint32_t)free_pos, edge_bits(prev, pf) | (u64)(uint32_t)C);
-                if (ef_lds) ef[C] = pack_ef(cur_len, pf);
-                ent_len[C] = cur_len;
-              }
-              if (lane < M) ent_tokens[(size_t)C * M + lane] = tokj;
-              if (out != nullptr && lane < cur_len) out[n_out + lane] = tokj;
-            }
-            prev = k1;
-            prev_len = cur_len;
-            ++C;
-            n_out += cur_len;
-            ++cpos;
-          }
-          ok = true;
-        }
+      first = T[0] = k;
+    } else if (old_entry) {
+      const int32_t* row = ent_tokens + (size_t)(k - V) * M;
+#pragma unroll
+      for (int j = 0; j < kTok; ++j)
+        if (j < M) T[j] = row[j];
+      if (ef_lds) {
+        const uint32_t e = ef[k - V];
+        len = (int)(e >> 28);
+        first = (int32_t)(e & kFirst);
+      } else {
+#pragma unroll
+        for (int j = 0; j < kTok; ++j) len += T[j] >= 0 ? 1 : 0;
+        first = T[0];
       }
-      if (!ok) {
-        status |= Z2Z_ST_BAD_CODE;
+    } else if (new_entry) {
+      len = min(2, M);                // a guess
+    }
+    sh.code[tid] = k;
+    sh.info[tid] = pack_ef(len, first);
+    if (tid == 0) sh.bad_pos = sh.ovf_pos = sh.cut = W;
+    __syncthreads();
+    const int32_t pk = tid > 0 ? sh.code[tid - 1] : -1;
+    uint32_t pinfo = tid > 0 ? sh.info[tid - 1] : 0u;
+    const int room = cap - C;
+    const bool may_add = tid > 0 && present && pk >= 0 && room > 0;
+    const bool old_parent = pk < V + C;
+    bool taken = false;               // the edge is an entry already
+    // (the first code of the window may name the entry it makes itself: its first token is then the previous code's)
+    const int32_t first_guess = tid == 1 && new_entry ? (int32_t)(pinfo & kFirst) : first;
+    if (may_add && old_parent && (!new_entry || tid == 1) && (int)(pinfo >> 28) < M)
+      taken = t.find_lane(pk, first_guess) >= 0;
+
+    // ---- 2., 3. lengths and makers -----------------------------------------------------------------------
+    bool makes = false;
+    int rank = 0, incl = 0, n_made = 0, n_tokens = 0;
+    for (int it = 0; it <= W; ++it) {           // (a position becomes final with every iteration: the bound is never met)
+      ++n_rounds;
+      makes = may_add && !taken && (int)(pinfo >> 28) < M;
+      const u64 makes_mask = __ballot(makes);
+      const int mylen = tid > 0 ? len : 0;
+      incl = 0;                                 // tokens of the codes up to this one
+#pragma unroll
+      for (int bit = 0; bit < 4; ++bit) {
+        const u64 m = __ballot((mylen >> bit) & 1);
+        incl += (__popcll(m & lanes_below) + ((mylen >> bit) & 1)) << bit;
+      }
+      if (lane == kWave - 1) {
+        sh.makes[w] = makes_mask;
+        sh.count[w] = (uint32_t)__popcll(makes_mask) | ((uint32_t)incl << 16);
+      }
+      __syncthreads();
+      const uint32_t counts = row_scan_add(lane < NW ? sh.count[lane] : 0u);
+      const uint32_t below = w == 0 ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)counts, w == 0 ? 0 : w - 1);
+      const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)counts, NW - 1);
+      rank = (int)(below & 0xFFFFu) + __popcll(makes_mask & lanes_below);
+      incl += (int)(below >> 16);
+      n_made = min((int)(total & 0xFFFFu), room);
+      n_tokens = (int)(total >> 16);
+      if (makes && rank < room) sh.maker[rank] = (uint16_t)tid;
+      if (tid == 0) sh.changed[(it + 1) & 1] = 0;
+      __syncthreads();
+      bool ch = false;
+      if (new_entry) {
+        const int e = k - V - C;
+        int len2 = 0;                           // (invalid)
+        int32_t first2 = 0;
+        if (e < n_made) {
+          const int p = sh.maker[e];
+          if (p <= tid) {
+            const uint32_t pi = sh.info[p - 1];
+            len2 = min((int)(pi >> 28) + 1, M);
+            first2 = (int32_t)(pi & kFirst);
+          }
+        }
+        ch = len2 != len || first2 != first;
+        len = len2;
+        first = first2;
+        sh.info[tid] = pack_ef(len, first);
+      }
+      if (__ballot(ch) != 0 && lane == 0) sh.changed[it & 1] = 1;
+      __syncthreads();
+      if (sh.changed[it & 1] == 0) break;
+      if (tid > 0) pinfo = sh.info[tid - 1];
+    }
+
+    // ---- 4. limits of the window --------------------------------------------------------------------------
+    const bool makes_it = makes && rank < room;
+    if (n_made > 1) {
+      const uint32_t h = edge_hash(pk, first);
+      int own = -1;
+      bool clash = false;
+      if (makes_it) {
+        own = Set::insert(sh.set, sh.key, h, round_key(pk, first), tid);
+        if (own == -2) atomicMin(&sh.cut, tid + 1);              // later positions cannot see this edge
+        if (new_entry && tid > 1 && old_parent) clash = t.find_lane(pk, first, h) >= 0;
+      }
+      __syncthreads();
+      if (makes_it && !clash) clash = Set::find(sh.set, sh.key, h, round_key(pk, first), tid) >= 0;
+      if (clash) atomicMin(&sh.cut, tid);
+      if (tid > 0 && present && len == 0) atomicMin(&sh.bad_pos, tid);
+      __syncthreads();
+      if (own >= 0) sh.set[own] = kRoundEmpty;
+    } else {
+      if (makes_it && new_entry && tid > 1 && old_parent && t.find_lane(pk, first) >= 0) atomicMin(&sh.cut, tid);
+      if (tid > 0 && present && len == 0) atomicMin(&sh.bad_pos, tid);
+      __syncthreads();
+    }
+    const int bad_pos = sh.bad_pos;
+    int limit = min(min(W, n - cpos + 1), min(bad_pos, sh.cut));    // codes 1 .. limit-1 of the window are taken
+    if (out != nullptr && n_out + n_tokens > a.out_stride) {        // uniform
+      const u64 ovf_mask = __ballot(tid > 0 && present && len > 0 && n_out + incl > a.out_stride);
+      if (ovf_mask && lane == 0) atomicMin(&sh.ovf_pos, w * kWave + (int)__builtin_ctzll(ovf_mask));
+      __syncthreads();
+      limit = min(limit, sh.ovf_pos);
+      if (sh.ovf_pos < W && limit == sh.ovf_pos) {
+        status |= Z2Z_ST_OVERFLOW;
         stop = true;
       }
-      sync_after_global_stores();
-      continue;
     }
-
-    // ---- 2. proposals --------------------------------------------------------------------------------
-    const int limit0 = min(hard_pos, min(kWideLanes, n - cpos + 1));   // global lanes 1 .. limit0-1 hold known codes
-    int32_t pk = __shfl_up(k, 1);
-    int plen = __shfl_up(len, 1);
-    int32_t pfirst = __shfl_up(first, 1);
-    bool pknown = __shfl_up((int)known, 1) != 0;
-    if (lane == 0 && w > 0) {
-      pk = sh.edge_k[w - 1];
-      plen = sh.edge_len[w - 1];
-      pfirst = sh.edge_first[w - 1];
-      pknown = sh.edge_known[w - 1] != 0;
-    }
-    const int room = cap - C;
-    const bool prop = g >= 1 && g < limit0 && pknown && plen < M && room > 0;
-    int found = -1;
-    if (prop) found = t.find_lane(pk, first);
-    const bool cand = prop && found < 0;
-    const u64 cand_mask = __ballot(cand);
-    // token offsets inside the window
-    const int mylen = (g >= 1 && g < limit0) ? len : 0;
-    int incl = 0;
-#pragma unroll
-    for (int bit = 0; bit < 4; ++bit) incl += __popcll(__ballot((mylen >> bit) & 1) & lanes_upto) << bit;
-    if (lane == 0) sh.cand_mask[w] = cand_mask;
-    if (lane == kWave - 1) sh.lensum[w] = incl;
-    __syncthreads();
-    int cand_before = 0, cand_total = 0, len_before = 0;
-    for (int ww = 0; ww < kWide; ++ww) {
-      const int cnt = __popcll(sh.cand_mask[ww]);
-      if (ww < w) {
-        cand_before += cnt;
-        len_before += sh.lensum[ww];
-      }
-      cand_total += cnt;
-    }
-    const int rank = cand_before + __popcll(cand_mask & lanes_below);
-    const bool inserter = cand && rank < room;
-    incl += len_before;                               // tokens of codes 1 .. g of the round
-    const u64 ovf_mask = __ballot(out != nullptr && mylen > 0 && n_out + incl > a.out_stride);
-    if (lane == 0) sh.ovf[w] = ovf_mask ? w * kWave + __builtin_ctzll(ovf_mask) : kWideLanes;
-    // first repeat of a proposed edge: insert phase
-    const bool filtering = cand_total >= 2;           // uniform
-    const u64 key = edge_bits(pk, first);
-    const uint32_t h0 = (edge_hash(pk, first) >> 20) & (kWideFilter - 1);
-    int own = -1;
-    if (filtering && inserter) {
-      const u64 val = key | (u64)g;
-      uint32_t h = h0;
-      for (int probe = 0; probe < kWideFilter; ++probe) {
-        const u64 old = atomicCAS(&filter[h], kEmpty, val);
-        if (old == kEmpty) {
-          own = (int)h;
-          break;
-        }
-        if ((old & ~0xFFFFull) == key) {
-          atomicMin(&filter[h], val);
-          break;
-        }
-        h = (h + 1) & (kWideFilter - 1);
-      }
-    }
-    __syncthreads();
-    if (filtering) {
-      int fpos = kWideLanes;
-      if (cand) {
-        uint32_t h = h0;
-        for (int probe = 0; probe < kWideFilter; ++probe) {
-          const u64 sl = filter[h];
-          if (sl == kEmpty) break;
-          if ((sl & ~0xFFFFull) == key) {
-            fpos = (int)(sl & 0xFFFFull);
-            break;
-          }
-          h = (h + 1) & (kWideFilter - 1);
-        }
-      }
-      const u64 dup_mask = __ballot(cand && fpos < g);
-      if (dup_mask && lane == 0) atomicMin(&sh.cut, w * kWave + __builtin_ctzll(dup_mask));
-    }
-    __syncthreads();
-    const int cut = sh.cut;
-    if (own >= 0) filter[own] = kEmpty;
-    int ovf_pos = kWideLanes;
-    for (int ww = 0; ww < kWide; ++ww) ovf_pos = min(ovf_pos, sh.ovf[ww]);
-    const int limit = min(limit0, min(cut, ovf_pos));
-    if (ovf_pos < kWideLanes && limit == ovf_pos) {
-      status |= Z2Z_ST_OVERFLOW;
+    if (!stop && bad_pos < W && limit == bad_pos) {
+      status |= Z2Z_ST_BAD_CODE;
       stop = true;
     }
 
-    // ---- 3. publish ---------------------------------------------------------------------------------------
-    const bool valid = g >= 1 && g < limit;
-    const bool ins = valid && inserter;
-    if (ins) {
-      const int idx = C + rank;
-      t.insert_lane(pk, first, idx);
-      if (ef_lds) ef[idx] = pack_ef(plen + 1, pfirst);
-      // the new entry's row: the previous code's tokens (older than the round) and this code's first token
-      int32_t* row = ent_tokens + (size_t)idx * M;
-      for (int j = 0; j < M; ++j) {
-        int32_t v = -1;
-        if (j < plen) v = pk < V ? pk : load_fresh(&ent_tokens[(size_t)(pk - V) * M + j]);
-        if (j == plen) v = first;
-        row[j] = v;
+    // ---- 5. publish ---------------------------------------------------------------------------------------
+    if (makes_it && tid < limit) t.insert_lane(pk, first, C + rank);
+    const int next = tid + 1;
+    const int next_rank = rank + (makes ? 1 : 0);
+    const bool next_makes = next < limit && ((sh.makes[next >> 6] >> (next & 63)) & 1) != 0 && next_rank < room;
+    int32_t* dst = tid > 0 && tid < limit && out != nullptr ? out + n_out + incl - len : nullptr;
+    int32_t* row = next_makes ? ent_tokens + (size_t)(C + next_rank) * M : nullptr;
+    if (dst != nullptr || row != nullptr) {
+      int l = len;
+      int32_t kk = k;
+      while (kk >= V + C) {                     // entries of this round: last token first (at most M - 1 steps)
+        const int p = sh.maker[kk - V - C];
+        const int32_t tok = (int32_t)(sh.info[p] & kFirst);
+        --l;
+        if (dst != nullptr) dst[l] = tok;
+        if (row != nullptr) row[l] = tok;
+        kk = sh.code[p - 1];
       }
-      ent_len[idx] = plen + 1;
-    }
-    if (valid && out != nullptr) {
-      int32_t* dst = out + n_out + incl - len;
-      if (k < V) {
-        dst[0] = k;
-      } else {
-        const int32_t* row = ent_tokens + (size_t)(k - V) * M;
-        for (int j = 0; j < len; ++j) dst[j] = load_fresh(&row[j]);
+      if (kk != k) {
+        if (kk < V) {
+          T[0] = kk;
+        } else {
+          const int32_t* src = ent_tokens + (size_t)(kk - V) * M;
+#pragma unroll
+          for (int j = 0; j < kTok; ++j)
+            if (j < l) T[j] = src[j];
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < kTok; ++j) {
+        if (j < l && dst != nullptr) dst[j] = T[j];
+        if (j < l && row != nullptr) row[j] = T[j];
+      }
+      if (row != nullptr) {
+        const int32_t tok = (int32_t)(sh.info[next] & kFirst);
+#pragma unroll
+        for (int j = 1; j < kTok; ++j)
+          if (j >= len && j < M) row[j] = j == len ? tok : -1;
+        ent_len[C + next_rank] = len + 1;
+        if (ef_lds) ef[C + next_rank] = pack_ef(len + 1, first);
       }
     }
-    const u64 ins_mask = __ballot(ins);
-    if (lane == 0) sh.ins_cnt[w] = __popcll(ins_mask);
-    if (limit >= 2 && g == limit - 1) {
-      sh.last_k = k;
+    if (limit >= 2 && tid == limit - 1) {
+      sh.last_code = k;
       sh.last_len = len;
-      sh.last_incl = incl;
+      sh.last_tokens = incl;
+      sh.last_made = min(next_rank, room);
     }
-    sync_after_global_stores();
-    for (int ww = 0; ww < kWide; ++ww) C += sh.ins_cnt[ww];
+    if (fill < n) {                             // the ring takes the next codes in place of those behind the window
+      const int cnt = min(W, cpos + limit - 1 + kRing - fill);
+      const int p = fill + tid;
+      if (tid < cnt) sh.ring[p & (kRing - 1)] = p < n ? ahead : -1;
+      fill += cnt;
+      ahead = fill + tid < n ? in[fill + tid] : -1;
+    }
+    __syncthreads();                            // rows, insertions, the ring
     if (limit >= 2) {
-      prev = sh.last_k;
+      prev = sh.last_code;
       prev_len = sh.last_len;
-      n_out += sh.last_incl;
+      n_out += sh.last_tokens;
+      C += sh.last_made;
       cpos += limit - 1;
     } else {
       stop = true;
     }
-    if (tid == 0) sh.cut = kWideLanes;
-    sync_after_global_stores();                  // rows written above are in memory, the exchange area is free
   }
 
-  if (LDS) {
-    for (int i = tid; i < st.nslots; i += kWideLanes) t.g[i] = lds_slots[i];
+  table_close_all<LDS, W>(tid, t);
+  if (reset) {                                  // rows of the codebook that was there before
+    for (int i = C + tid; i < size0; i += W) ent_len[i] = 0;
+    for (int i = C * M + tid; i < size0 * M; i += W) ent_tokens[i] = -1;
   }
   if (tid == 0) {
     st.size[b] = C;
@@ -1521,6 +1242,19 @@ __global__ void __launch_bounds__(kWideLanes) lzw_decode_wide_kernel(LzwArgs a) 
     st.rounds[b] = n_rounds;
     a.out_n[b] = n_out;
     a.status[b] = status;
+  }
+}
+
+template <int NW, bool LDS>
+__global__ void __launch_bounds__(NW * kWave) lzw_decode_kernel(LzwArgs a) {
+  __shared__ DecShared<NW> sh;
+  const bool short_append = !(a.flags & Z2Z_RESET) && call_length(a, blockIdx.x) <= kShortAppend;
+  if (LDS && short_append) {
+    lzw_decode_windows<NW, false, false>(a, sh);
+  } else if (a.st.M <= 4) {
+    lzw_decode_windows<NW, LDS, true>(a, sh);
+  } else {
+    lzw_decode_windows<NW, LDS, false>(a, sh);
   }
 }
 
@@ -1548,28 +1282,38 @@ __global__ void lzw_clear_entries_kernel(LzwState st) {
     st.ent_tokens[(size_t)b * st.cap * st.M + i] = -1;
 }
 
-// Which table variant a call uses, and how much LDS it needs.
-void plan(const z2z_ctx* c, int32_t stride, int32_t flags, bool decode, bool* lds, LzwArgs* a, size_t* smem) {
-  const size_t slot_bytes = (size_t)c->st.nslots * sizeof(u64);
-  const size_t ef_bytes = (size_t)c->st.cap * sizeof(uint32_t);
-  const size_t limit = (size_t)c->lds_limit - kEncStaticLds;
-  // a short append (a decode step) touches a handful of slots: probing global memory directly is
-  // cheaper than staging the table
-  const bool tiny_append = !(flags & Z2Z_RESET) && stride <= 64;
-  // with thousands of sequences the LDS a table takes limits a CU to a few waves; probing the table in
-  // global memory (L2) with the CU full of waves is then faster (measured crossover between 512 and 2048
-  // sequences of 4096 tokens)
-  const bool crowd = c->cfg.B >= 1024;
-  *lds = c->st.slots_fit_lds && !tiny_append && !crowd && c->opt_lzw_kernel != 2;
-  a->lds_ef = 0;
-  *smem = 0;
-  if (*lds) {
-    *smem = slot_bytes;
-    if (decode && slot_bytes + ef_bytes <= limit) {
-      a->lds_ef = 1;
-      *smem += ef_bytes;
+// How a call is launched: table in LDS or in memory, waves per sequence, dynamic LDS.
+//   - A short appended call (a decode step) touches a handful of slots: one wave, the table where it is.
+//   - While every sequence has a CU to itself, the widest window is the fastest (4096 tokens, 8 sequences: 44 us
+//     with 16 waves, 54 with 8); up to 512 elements a call is a single window of 8 waves.
+//   - With more sequences than CUs, two workgroups per CU hide each other's latencies: 8 waves each when the LDS
+//     allows (2048 sequences of 4096 tokens, cap 2048: 260 us; 16 waves 576), else 4 (cap 4096: 397 us; one workgroup of 8
+//     waves 501), the decoder then without its (length, first token) copy; else one workgroup of 8.
+struct ParsePlan {
+  bool lds;
+  int nw;
+  size_t smem;
+};
+ParsePlan plan(const z2z_ctx* c, int32_t stride, int32_t flags, bool decode, LzwArgs* a) {
+  ParsePlan p;
+  const bool tiny_append = !(flags & Z2Z_RESET) && stride <= kShortAppend;
+  p.lds = c->st.slots_fit_lds && !tiny_append && c->opt_lzw_kernel != 2;
+  p.nw = tiny_append || c->opt_lzw_kernel == 4 ? 1 : stride <= 512 ? 8 : 16;
+  p.smem = p.lds ? (size_t)c->st.nslots * sizeof(u64) : 0;
+  const size_t all = (size_t)c->lds_limit, fixed8 = decode ? sizeof(DecShared<8>) : sizeof(EncShared<8>),
+               fixed4 = decode ? sizeof(DecShared<4>) : sizeof(EncShared<4>);
+  size_t ef = decode && p.lds ? (size_t)c->st.cap * sizeof(uint32_t) : 0;
+  if (p.smem + ef + kParseStaticLds > all) ef = 0;
+  if (c->cfg.B > c->num_cu && p.nw > 1) {
+    p.nw = 8;
+    if (p.lds && 2 * (p.smem + ef + fixed8) > all && 2 * (p.smem + fixed4) <= all) {
+      p.nw = 4;
+      if (2 * (p.smem + ef + fixed4) > all) ef = 0;
     }
   }
+  a->lds_ef = ef != 0;
+  p.smem += ef;
+  return p;
 }
 
 // How often each entry is named by a code stream: usage[b][e] += number of codes equal to V + e (codes of base
@@ -1767,11 +1511,23 @@ int z2z_launch_codebook_prefill(z2z_ctx* c, const int32_t* phrases, const int32_
   return Z2Z_OK;
 }
 
-// Four waves per sequence beat one as long as the machine is not full of sequences anyway: measured faster up
-// to 1024 sequences of 4096 tokens (B = 512: encode 218 -> 155 us, decode 168 -> 120 us), about equal at 1024
-// tokens, slower from 2048 sequences on.
-static bool wide_pays(int B, int stride) {
-  return stride >= 512 && (B <= 256 || (B <= 1024 && stride >= 2048));
+template <bool LDS>
+static void launch_encode(const LzwArgs& a, int B, int nw, size_t smem, hipStream_t s) {
+  switch (nw) {
+    case 1: hipLaunchKernelGGL((lzw_encode_kernel<1, LDS>), dim3(B), dim3(64), smem, s, a); break;
+    case 4: hipLaunchKernelGGL((lzw_encode_kernel<4, LDS>), dim3(B), dim3(256), smem, s, a); break;
+    case 8: hipLaunchKernelGGL((lzw_encode_kernel<8, LDS>), dim3(B), dim3(512), smem, s, a); break;
+    default: hipLaunchKernelGGL((lzw_encode_kernel<16, LDS>), dim3(B), dim3(1024), smem, s, a); break;
+  }
+}
+template <bool LDS>
+static void launch_decode(const LzwArgs& a, int B, int nw, size_t smem, hipStream_t s) {
+  switch (nw) {
+    case 1: hipLaunchKernelGGL((lzw_decode_kernel<1, LDS>), dim3(B), dim3(64), smem, s, a); break;
+    case 4: hipLaunchKernelGGL((lzw_decode_kernel<4, LDS>), dim3(B), dim3(256), smem, s, a); break;
+    case 8: hipLaunchKernelGGL((lzw_decode_kernel<8, LDS>), dim3(B), dim3(512), smem, s, a); break;
+    default: hipLaunchKernelGGL((lzw_decode_kernel<16, LDS>), dim3(B), dim3(1024), smem, s, a); break;
+  }
 }
 
 int z2z_launch_lzw_encode(z2z_ctx* c, const int32_t* tokens, const int32_t* lens, int32_t stride, int32_t flags,
@@ -1788,21 +1544,11 @@ int z2z_launch_lzw_encode(z2z_ctx* c, const int32_t* tokens, const int32_t* lens
   a.out_n = n_codes;
   a.out_stride = out_stride;
   a.status = status;
-  size_t smem = 0;
-  bool lds = false;
-  plan(c, stride, flags, false, &lds, &a, &smem);
-  if (flags & Z2Z_RESET) hipLaunchKernelGGL(lzw_clear_entries_kernel, dim3(c->cfg.B), dim3(256), 0, s, c->st);
-  // few long sequences: four waves per sequence (the machine is nearly empty, a sequence's parse time counts)
-  const bool wide = wide_pays(c->cfg.B, stride) && c->opt_lzw_kernel != 4 &&
-                    (!lds || smem + kWideStaticLds <= (size_t)c->lds_limit);
-  if (wide && lds)
-    hipLaunchKernelGGL(lzw_encode_wide_kernel<true>, dim3(c->cfg.B), dim3(kWideLanes), smem, s, a);
-  else if (wide)
-    hipLaunchKernelGGL(lzw_encode_wide_kernel<false>, dim3(c->cfg.B), dim3(kWideLanes), 0, s, a);
-  else if (lds)
-    hipLaunchKernelGGL(lzw_encode_kernel<true>, dim3(c->cfg.B), dim3(kWave), smem, s, a);
+  const ParsePlan p = plan(c, stride, flags, false, &a);
+  if (p.lds)
+    launch_encode<true>(a, c->cfg.B, p.nw, p.smem, s);
   else
-    hipLaunchKernelGGL(lzw_encode_kernel<false>, dim3(c->cfg.B), dim3(kWave), 0, s, a);
+    launch_encode<false>(a, c->cfg.B, p.nw, 0, s);
   Z2Z_HIP_TRY(hipGetLastError());
   return Z2Z_OK;
 }
@@ -1821,25 +1567,18 @@ int z2z_launch_lzw_decode(z2z_ctx* c, const int32_t* codes, const int32_t* n_cod
   a.out_n = n_tokens;
   a.out_stride = out_stride;
   a.status = status;
-  size_t smem = 0;
-  bool lds = false;
-  plan(c, stride, flags, true, &lds, &a, &smem);
-  if (flags & Z2Z_RESET) hipLaunchKernelGGL(lzw_clear_entries_kernel, dim3(c->cfg.B), dim3(256), 0, s, c->st);
+  const ParsePlan p = plan(c, stride, flags, true, &a);
   const bool serial = stride <= 8 || c->opt_lzw_kernel == 3;
-  const bool wide = !serial && wide_pays(c->cfg.B, stride) && c->opt_lzw_kernel != 4 &&
-                    (!lds || smem + kWideStaticLds <= (size_t)c->lds_limit);
-  if (wide && lds)
-    hipLaunchKernelGGL(lzw_decode_wide_kernel<true>, dim3(c->cfg.B), dim3(kWideLanes), smem, s, a);
-  else if (wide)
-    hipLaunchKernelGGL(lzw_decode_wide_kernel<false>, dim3(c->cfg.B), dim3(kWideLanes), 0, s, a);
-  else if (serial && lds)
-    hipLaunchKernelGGL(lzw_decode_serial_kernel<true>, dim3(c->cfg.B), dim3(kWave), smem, s, a);
+  // (the window kernels clear the rows behind the new codebook themselves)
+  if (serial && (flags & Z2Z_RESET)) hipLaunchKernelGGL(lzw_clear_entries_kernel, dim3(c->cfg.B), dim3(256), 0, s, c->st);
+  if (serial && p.lds)
+    hipLaunchKernelGGL(lzw_decode_serial_kernel<true>, dim3(c->cfg.B), dim3(kWave), p.smem, s, a);
   else if (serial)
     hipLaunchKernelGGL(lzw_decode_serial_kernel<false>, dim3(c->cfg.B), dim3(kWave), 0, s, a);
-  else if (lds)
-    hipLaunchKernelGGL(lzw_decode_kernel<true>, dim3(c->cfg.B), dim3(kWave), smem, s, a);
+  else if (p.lds)
+    launch_decode<true>(a, c->cfg.B, p.nw, p.smem, s);
   else
-    hipLaunchKernelGGL(lzw_decode_kernel<false>, dim3(c->cfg.B), dim3(kWave), 0, s, a);
+    launch_decode<false>(a, c->cfg.B, p.nw, 0, s);
   Z2Z_HIP_TRY(hipGetLastError());
   return Z2Z_OK;
 }
@@ -1882,7 +1621,7 @@ int z2z_lzw_prepare(z2z_ctx* c) {
   const int want4 = 4 * cap < 64 ? 64 : 4 * cap;
   const int want = 2 * cap < 64 ? 64 : 2 * cap;
   const int floor125 = cap + cap / 4 + 1;
-  const int lds_slots = (c->lds_limit - kEncStaticLds) / (int)sizeof(u64);   // the encoder's own LDS comes first
+  const int lds_slots = (c->lds_limit - kParseStaticLds) / (int)sizeof(u64);   // the encoder's own LDS comes first
   // With fewer sequences than CUs a workgroup has its CU to itself and the roomier table (shorter probe
   // sequences) is free; with many, LDS decides how many sequences a CU works on at once.
   const bool roomy = c->cfg.B < 256;
@@ -1899,16 +1638,17 @@ int z2z_lzw_prepare(z2z_ctx* c) {
     st.nslots = want;
     st.slots_fit_lds = 0;
   }
-  st.nslots &= ~1;                                     // even: probe sequences start on slot pairs
-  Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(lzw_encode_kernel<true>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_limit - kEncStaticLds));
-  Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(lzw_encode_wide_kernel<true>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_limit - kWideStaticLds));
-  Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(lzw_decode_wide_kernel<true>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_limit - kWideStaticLds));
-  Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(lzw_decode_kernel<true>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_limit - kEncStaticLds));
-  Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(lzw_decode_serial_kernel<true>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_limit - kEncStaticLds));
+  st.nslots &= ~1;                                     // whole buckets
+  const void* parse[] = {reinterpret_cast<const void*>(lzw_encode_kernel<1, true>),
+                         reinterpret_cast<const void*>(lzw_encode_kernel<4, true>),
+                         reinterpret_cast<const void*>(lzw_encode_kernel<8, true>),
+                         reinterpret_cast<const void*>(lzw_encode_kernel<16, true>),
+                         reinterpret_cast<const void*>(lzw_decode_kernel<1, true>),
+                         reinterpret_cast<const void*>(lzw_decode_kernel<4, true>),
+                         reinterpret_cast<const void*>(lzw_decode_kernel<8, true>),
+                         reinterpret_cast<const void*>(lzw_decode_kernel<16, true>),
+                         reinterpret_cast<const void*>(lzw_decode_serial_kernel<true>)};
+  for (const void* f : parse)
+    Z2Z_HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_limit - kParseStaticLds));
   return Z2Z_OK;
 }

@@ -1,0 +1,127 @@
+"""GPU parity of the window kernels of lzw_encode / lzw_decode (up to 1024 elements of a sequence at once, iterated until
+they agree with the entries they make) at the sizes where a window can go wrong, against the oracle, bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import assert_codebook_equal, gpu_decode, gpu_encode, oracle_encode_batch
+
+pytestmark = pytest.mark.gpu
+
+
+def _ctx(B, V, M, cap, kernel=0):
+    from paper_2506_01084_amd import api
+
+    ctx = api.Context(B=B, V=V, M=M, cap=cap, d=64, dtype="bf16")
+    ctx.set_option(api.OPT_LZW_KERNEL, kernel)
+    return ctx
+
+
+def _round_trip(tokens, lens, V, M, cap, kernel=0):
+    B, N = tokens.shape
+    ref = oracle_encode_batch(tokens, lens, V, M, cap)
+    ctx, ctx2 = _ctx(B, V, M, cap, kernel), _ctx(B, V, M, cap, kernel)
+    codes, n_codes, status = gpu_encode(ctx, tokens, lens)
+    assert (status == 0).all()
+    for b, (rc, _, _) in enumerate(ref):
+        assert codes[b, :n_codes[b]].tolist() == rc, f"codes of sequence {b}"
+    assert_codebook_equal(ctx, [r[1] for r in ref], M, cap)
+    toks, n_tok, st = gpu_decode(ctx2, codes, n_codes, out_stride=N)
+    assert (st == 0).all() and (n_tok == lens).all()
+    for b in range(B):
+        assert (toks[b, :lens[b]] == tokens[b, :lens[b]]).all(), f"tokens of sequence {b}"
+    assert_codebook_equal(ctx2, [r[1] for r in ref], M, cap)
+    ctx.close()
+    ctx2.close()
+
+
+@pytest.mark.parametrize("M,cap", [(2, 90), (3, 5000), (4, 1500), (5, 700), (8, 3000)])
+@pytest.mark.parametrize("N", [65, 511, 513, 1023, 1024, 1025, 2049, 3100])
+def test_window_edges(N, M, cap):
+    """Lengths around the windows of 64, 512 and 1024; streams that depend on the window's own entries everywhere (tiny
+    alphabets, runs, periods) or rarely (Zipf); codebooks that fill inside a window, or never."""
+    rng = np.random.default_rng(N * 16 + M)
+    V = 60
+    rows = [rng.integers(0, 2, N), rng.integers(0, 9, N), np.minimum(rng.zipf(1.3, N) - 1, V - 1), np.zeros(N, np.int64),
+            np.tile(rng.integers(0, V, 7), N // 7 + 1)[:N], np.repeat(rng.integers(0, V, N // 11 + 1), 11)[:N]]
+    tokens = np.stack(rows).astype(np.int32)
+    lens = np.full(len(rows), N, dtype=np.int32)
+    lens[1] = N - 1
+    _round_trip(tokens, lens, V, M, cap)
+    if N in (1024, 2049):
+        for kernel in (2, 4):                                # table in memory; one wave, windows of 64
+            _round_trip(tokens, lens, V, M, cap, kernel)
+
+
+@pytest.mark.parametrize("B,cap", [(300, 500), (300, 4096)])
+def test_more_sequences_than_compute_units(B, cap):
+    """Several workgroups per CU: eight waves each, or four where the tables are larger."""
+    rng = np.random.default_rng(B + cap)
+    tokens = np.minimum(rng.zipf(1.2, (B, 700)) - 1, 199).astype(np.int32)
+    lens = rng.integers(0, 701, B).astype(np.int32)
+    lens[0] = 700
+    _round_trip(tokens, lens, 200, 3, cap)
+
+
+def test_largest_ids():
+    """V + cap = 2^24: parents and tokens use all their bits in the table's slots and the round's keys."""
+    rng = np.random.default_rng(7)
+    cap = 1200
+    V = (1 << 24) - cap
+    tokens = (V - 1 - rng.integers(0, 5, (3, 1500))).astype(np.int32)
+    _round_trip(tokens, np.full(3, 1500, np.int32), V, 6, cap)
+
+
+def _random_codes(rng, V, M, cap, n, hot):
+    """A code stream no greedy parse made: any code that is legal when its turn comes, with many repeated pairs."""
+    s, codes = oracle.LZWStream(V, M, cap), []
+    while len(codes) < n:
+        C = len(s.entries)
+        u = rng.random()
+        k = int(rng.integers(0, hot)) if u < 0.5 or C == 0 else V + C if u < 0.53 else V + int(rng.integers(max(0, C - 40), C))
+        _, st = s.decode_chunk([k]) if k < V + C else (None, 1)
+        if k == V + C:                                       # the entry this code makes itself, where that is legal
+            t = oracle.LZWStream(V, M, cap)
+            if t.decode_chunk(codes + [k])[1] != 0:
+                continue
+            s.decode_chunk([k])
+        codes.append(k)
+    return codes
+
+
+@pytest.mark.parametrize("M,cap", [(3, 5000), (5, 400)])
+def test_decode_of_arbitrary_codes(M, cap):
+    """Windows whose codes repeat edges, meet edges of the table and name the window's own entries: cut where they
+    must be; then a code that names nothing, and an output row that ends, at places in different windows."""
+    from paper_2506_01084_amd import api
+
+    V, n = 25, 1300
+    rng = np.random.default_rng(M)
+    streams = [_random_codes(rng, V, M, cap, n, hot) for hot in (2, 6, 25)]
+    B = len(streams)
+    rows = np.asarray(streams, dtype=np.int32)
+    cnt = np.full(B, n, np.int32)
+    ref = [oracle.lzw_decode(s, V, M, cap) for s in streams]
+    longest = max(len(r[0]) for r in ref)
+    for kernel in (0, 2, 4):
+        ctx = _ctx(B, V, M, cap, kernel)
+        toks, n_tok, st = gpu_decode(ctx, rows, cnt, out_stride=longest)
+        assert (st == 0).all()
+        for b in range(B):
+            assert toks[b, :n_tok[b]].tolist() == ref[b][0]
+        assert_codebook_equal(ctx, [r[1] for r in ref], M, cap)
+        for at in (0, 1, 511, 512, 1023, 1030):
+            bad = rows.copy()
+            bad[:, at] = V + cap + 5
+            toks, n_tok, st = gpu_decode(ctx, bad, cnt, out_stride=longest)
+            for b in range(B):
+                rt, re, rst = oracle.lzw_decode(bad[b].tolist(), V, M, cap)
+                assert int(st[b]) == rst == api.ST_BAD_CODE and toks[b, :n_tok[b]].tolist() == rt
+            assert_codebook_equal(ctx, [oracle.lzw_decode(bad[b].tolist(), V, M, cap)[1] for b in range(B)], M, cap)
+        for room in (1, 700, 1500):
+            toks, n_tok, st = gpu_decode(ctx, rows, cnt, out_stride=room)
+            for b in range(B):
+                if len(ref[b][0]) > room:
+                    assert int(st[b]) == api.ST_OVERFLOW and room - M < int(n_tok[b]) <= room
+                assert toks[b, :n_tok[b]].tolist() == ref[b][0][:n_tok[b]]
+        ctx.close()
