@@ -405,7 +405,13 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     z2z_logits_decode_units(&base_columns, &hyper_columns);
     hyp_strips = (cap + hyper_columns - 1) / hyper_columns;
   }
-  if (seq_split) hyp_strips = z2z_logits_decode_seq_units(c);
+  int seq_unit = 0;
+  if (seq_split) {
+    seq_unit = z2z_logits_decode_seq_unit(c);
+    // (the static array may be too small for the parts of the smaller units)
+    if (use_static && (size_t)(base_strips + (cap + seq_unit - 1) / seq_unit) * rows > parts.capacity) seq_unit = 256;
+    hyp_strips = (cap + seq_unit - 1) / seq_unit;
+  }
   const int n_parts = base_strips + hyp_strips;
   int rc = reserve((size_t)n_parts * rows);
   if (rc != Z2Z_OK) return rc;
@@ -439,7 +445,7 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
   if (cap > 0 && (decode_split || seq_split)) {
     int np = 0;
     rc = z2z_launch_logits_decode(c, H, W_base, W_hyper, &np, false, nullptr, nullptr, s, base_strips, &parts,
-                                  seq_split ? rows_per_seq : 1);
+                                  seq_split ? rows_per_seq : 1, seq_unit);
     if (rc != Z2Z_OK) return rc;
   } else if (cap > 0) {
     rc = z2z_launch_logits_part(c, true, fast_hyper, a, W_hyper, cap, V, base_strips, strip_h, rows, rows_per_seq, &ns, false, s);

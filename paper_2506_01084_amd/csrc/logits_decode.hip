@@ -90,9 +90,10 @@ struct DecodeArgs {
   int32_t ksplit;
   float* partial;           // [n_groups * n_base_units][ksplit][unit rows * 64]
   // MODE 4, the hyper part of a call with 2..64 hidden rows per sequence: workgroup (b, u) takes rows
-  // [256 u, 256 u + 256) of W_hyper[b] against the sequence's rows_per_seq hidden rows
+  // [seq_unit * u, seq_unit * (u + 1)) of W_hyper[b] against the sequence's rows_per_seq hidden rows
   int32_t rows_per_seq;
-  int32_t seq_units;        // ceil(cap / 256)
+  int32_t seq_unit;         // 64, 128 or 256 (z2z_logits_decode_seq_unit)
+  int32_t seq_units;        // ceil(cap / seq_unit)
 };
 
 __device__ __forceinline__ void fold_value(Triple& t, float x, int col) {
@@ -195,10 +196,11 @@ __device__ __forceinline__ void base_unit(const DecodeArgs& a, int unit, int gro
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // weight rows per unit: 256 for the vocabulary; a dense layer has few output rows and needs many
   // workgroups to fill the machine, so its units are 64 rows
-  constexpr int UNIT = MODE == 3 ? D_LINEAR_UNIT : D_BASE_UNIT;
   // MODE 4 (a sequence's own weights against its few hidden rows): `group` is the sequence, `unit` the block of
-  // 256 rows of its W_hyper, of which only the first C_b exist
+  // seq_unit rows of its W_hyper, of which only the first C_b exist
   constexpr bool SEQ = MODE == 4;
+  constexpr int MAX_UNIT = MODE == 3 ? D_LINEAR_UNIT : D_BASE_UNIT;
+  const int UNIT = SEQ ? a.seq_unit : MAX_UNIT;
   float* tile = reinterpret_cast<float*>(lds);                      // [UNIT][64]
   float* slots = reinterpret_cast<float*>(lds + D_TILE_BYTES);       // [2][8][64][D_SLOT_STRIDE]
   const int chunks_per_row = a.d >> 3;             // 16-byte chunks per row
@@ -230,7 +232,7 @@ __device__ __forceinline__ void base_unit(const DecodeArgs& a, int unit, int gro
   const int per_part = (MODE == 3 && a.ksplit > 1) ? (n_phases_all + a.ksplit - 1) / a.ksplit : n_phases_all;
   const int phase0 = ks * per_part;
   const int n_phases = min(per_part, n_phases_all - phase0);
-  constexpr int N_BLK = UNIT / 16;
+  constexpr int N_BLK = MAX_UNIT / 16;
 
   for (int i = tid; i < UNIT * 64; i += D_THREADS) tile[i] = 0.f;
 
@@ -349,7 +351,7 @@ __device__ __forceinline__ void base_unit(const DecodeArgs& a, int unit, int gro
     linear_epilogue(a, tile, slots, v0, h0, n_h);
     return;
   }
-  // fold: thread t takes hidden row t & 63 and weight rows (t >> 6) * 32 .. + 32, in increasing order
+  // fold: thread t takes hidden row t & 63 and an eighth of the unit's weight rows, in increasing order
   Triple* xch = reinterpret_cast<Triple*>(lds + D_TILE_BYTES);       // the slots are idle now
   Draw* xdr = reinterpret_cast<Draw*>(xch + D_THREADS);
   const int j = tid & 63;
@@ -358,8 +360,9 @@ __device__ __forceinline__ void base_unit(const DecodeArgs& a, int unit, int gro
   Draw dr = empty_draw();
   Noise noise;
   noise.group = -1;
-  const int r_hi = min(D_BASE_UNIT, w_valid - v0);
-  for (int r = seg * 32; r < min(seg * 32 + 32, r_hi); ++r)
+  const int seg_rows = UNIT / 8;
+  const int r_hi = min(UNIT, w_valid - v0);
+  for (int r = seg * seg_rows; r < min((seg + 1) * seg_rows, r_hi); ++r)
     fold_logit<MODE>(a, t, dr, noise, tile[r * 64 + j], h0 + j, col0 + v0 + r);
   xch[tid] = t;
   if (MODE == 1) xdr[tid] = dr;
@@ -633,14 +636,14 @@ __global__ void __launch_bounds__(D_THREADS) logits_decode_kernel(DecodeArgs a) 
 }
 
 // The per-sequence part of a call with R = 2..4 hidden rows per sequence (R = a.rows_per_seq) on dot-product units:
-// workgroup (b, u) takes rows [256 u, 256 u + 256) of W_hyper[b], one part each (the layout of the matrix-core
-// units that take more rows per sequence); plain logits only.
+// workgroup (b, u) takes rows [seq_unit * u, seq_unit * (u + 1)) of W_hyper[b], one part each (the layout of the
+// matrix-core units that take more rows per sequence); plain logits only.
 template <int R>
 __global__ void __launch_bounds__(D_THREADS) logits_decode_rows_kernel(DecodeArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];
   const int b = blockIdx.x / a.seq_units, u = blockIdx.x % a.seq_units;
   const int C = min(max(a.size[b], 0), a.cap);
-  dot_unit<R, 0>(a, a.W_hyper + (size_t)b * a.cap * (a.d >> 3), b * R, a.V, u * D_BASE_UNIT, min(C, (u + 1) * D_BASE_UNIT),
+  dot_unit<R, 0>(a, a.W_hyper + (size_t)b * a.cap * (a.d >> 3), b * R, a.V, u * a.seq_unit, min(C, (u + 1) * a.seq_unit),
                  a.n_base_units + u, lds);
 }
 
@@ -704,7 +707,7 @@ __global__ void __launch_bounds__(D_THREADS) linear_reduce_kernel(DecodeArgs a) 
 // is given as well: the partials are then those of the scaled logits, and nothing is drawn).
 int z2z_launch_logits_decode(z2z_ctx* c, const void* H, const void* W_base, const void* W_hyper, int* n_parts,
                              bool timed, const z2z_sample_params* sample, float* logits, hipStream_t s,
-                             int hyper_only_base_parts, const z2z_parts* parts, int rows_per_seq) {
+                             int hyper_only_base_parts, const z2z_parts* parts, int rows_per_seq, int seq_unit) {
   c->n_launch[Z2Z_KERNEL_DECODE]++;
   DecodeArgs a;
   memset(&a, 0, sizeof(a));
@@ -744,10 +747,11 @@ int z2z_launch_logits_decode(z2z_ctx* c, const void* H, const void* W_base, cons
   }
   if (rows_per_seq > 1) {
     // the hyper part of a call with 2..64 hidden rows per sequence (the base vocabulary is another launch's):
-    // one workgroup per (sequence, 256 rows of its W_hyper), the matrix-core units
+    // one workgroup per (sequence, seq_unit rows of its W_hyper), the matrix-core units
     if (hyper_only_base_parts < 0 || rows_per_seq > 64 || sample || logits) return Z2Z_EUNSUPPORTED;
     a.rows_per_seq = rows_per_seq;
-    a.seq_units = (a.cap + D_BASE_UNIT - 1) / D_BASE_UNIT;
+    a.seq_unit = seq_unit;
+    a.seq_units = (a.cap + seq_unit - 1) / seq_unit;
     *n_parts = a.n_base_units + a.seq_units;
     a.n_parts = *n_parts;
     grid = (unsigned)(a.B * a.seq_units);
@@ -854,7 +858,16 @@ int z2z_logits_decode_parts(const z2z_ctx* c) {
   return (c->cfg.V + D_BASE_UNIT - 1) / D_BASE_UNIT + (c->cfg.cap + D_UNIT - 1) / D_UNIT;
 }
 
-int z2z_logits_decode_seq_units(const z2z_ctx* c) { return (c->cfg.cap + D_BASE_UNIT - 1) / D_BASE_UNIT; }
+// Rows of W_hyper[b] per unit of the per-sequence part of a call with a few hidden rows per sequence.  A unit walks
+// its rows in steps of 16 with three steps in flight, about 1.3 us each whatever the rest of the machine does, so
+// few large units leave the memory idle: the unit halves until there is one for every CU (64 rows at least: the
+// step loop takes blocks in fours).  5 rows x 8 sequences of 2048 entries, d = 4096 (64 units before, 256 now):
+// the whole call 255 -> 216 us.
+int z2z_logits_decode_seq_unit(const z2z_ctx* c) {
+  int unit = D_BASE_UNIT;
+  while (unit > 64 && (long long)c->cfg.B * ((c->cfg.cap + unit - 1) / unit) < 256) unit >>= 1;
+  return unit;
+}
 
 void z2z_logits_decode_units(int* base_columns, int* hyper_columns) {
   *base_columns = D_BASE_UNIT;
