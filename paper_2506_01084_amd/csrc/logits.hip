@@ -275,29 +275,34 @@ bool static_parts(const z2z_ctx* c, z2z_parts* out) {
 
 }  // namespace
 
-// One launch of a tile kernel over the base part (hyper = false) or the per-sequence hyper part: fills in the
-// shape-dependent fields of `a` (tiles, strips, workgroup mapping) and launches; prob = true selects the
-// epilogue that stores the gradient with respect to the logits (the backward pass of the loss).
-int z2z_launch_logits_part(z2z_ctx* c, bool hyper, bool fast, LogitsArgs a, const void* W, int w_rows, int col0,
-                           int part0, int strip, int rows, int rows_per_seq, int* n_strips_out, bool timed,
-                           hipStream_t s, bool prob, int seq0, int n_seq) {
-  // (seq0, n_seq: the hyper part of a sub-range of the sequences -- the caller passes that range's rows and
-  // its W_hyper; n_seq = 0 means all of them)
-  const int tile = fast ? 256 : 128;
-  const int B = n_seq > 0 ? n_seq : c->cfg.B;
+// The shape-dependent fields of one part's arguments (tiles of `tile` rows, strips); B: sequences of a hyper part.
+static void fill_part(LogitsArgs& a, const int32_t* size, int tile, int B, const void* W, int w_rows, int col0, int part0,
+                      int strip, int rows, int rows_per_seq) {
   a.W = W;
-  a.size = hyper ? c->st.size + seq0 : nullptr;
+  a.size = size;
   a.w_rows = w_rows;
   a.col0 = col0;
   a.n_vtiles = (w_rows + tile - 1) / tile;
   a.strip = strip;
   a.n_strips = (a.n_vtiles + strip - 1) / strip;
   a.part0 = part0;
-  a.row_tiles = hyper ? (rows_per_seq + tile - 1) / tile : (rows + tile - 1) / tile;
-  a.n_work = (hyper ? B : 1) * a.row_tiles * a.n_strips;
+  a.row_tiles = size ? (rows_per_seq + tile - 1) / tile : (rows + tile - 1) / tile;
+  a.n_work = (size ? B : 1) * a.row_tiles * a.n_strips;
+}
+
+// One launch of the bf16 MFMA tile kernel over the base part (hyper = false) or the per-sequence hyper part: fills in
+// the shape-dependent fields of `a` (tiles, strips, workgroup mapping) and launches; prob = true selects the
+// epilogue that stores the gradient with respect to the logits (the backward pass of the loss).
+int z2z_launch_logits_part(z2z_ctx* c, bool hyper, LogitsArgs a, const void* W, int w_rows, int col0,
+                           int part0, int strip, int rows, int rows_per_seq, int* n_strips_out, bool timed,
+                           hipStream_t s, bool prob, int seq0, int n_seq) {
+  // (seq0, n_seq: the hyper part of a sub-range of the sequences -- the caller passes that range's rows and
+  // its W_hyper; n_seq = 0 means all of them)
+  fill_part(a, hyper ? c->st.size + seq0 : nullptr, 256, n_seq > 0 ? n_seq : c->cfg.B, W, w_rows, col0, part0, strip, rows,
+            rows_per_seq);
   *n_strips_out = a.n_strips;
   unsigned grid = (unsigned)a.n_work;
-  if (fast && !hyper) {
+  if (!hyper) {
     const int m = c->opt_logits_map;
     a.map_lr = m ? (m & 0xFF) : 4;
     a.map_ls = m ? ((m >> 8) & 0xFF) : 8;
@@ -314,12 +319,12 @@ int z2z_launch_logits_part(z2z_ctx* c, bool hyper, bool fast, LogitsArgs a, cons
     const int sb_s = (a.n_strips + sb_strips - 1) / sb_strips;
     grid = 8u * (unsigned)(a.map_lr * a.map_ls) * (unsigned)a.map_sb_r * (unsigned)sb_s;
   }
-  c->n_launch[fast ? (hyper ? Z2Z_KERNEL_TILE_HYPER : Z2Z_KERNEL_TILE_BASE) : Z2Z_KERNEL_GENERAL]++;
+  c->n_launch[hyper ? Z2Z_KERNEL_TILE_HYPER : Z2Z_KERNEL_TILE_BASE]++;
   if (timed) Z2Z_HIP_TRY(hipEventRecord(c->ev_start[c->n_timed], s));
   // (measurement probes of the base part: see logits_fast_kernel, modes 8 and 9)
   const int plain_base = c->opt_logits_kernel == 2 ? 8 : (c->opt_logits_kernel == 3 ? 9 : 0);
-  int rc = fast ? z2z_launch_logits_fast(prob ? (hyper ? 4 : 3) : (a.sample && !hyper ? (a.sample == 2 ? 7 : 6) : (hyper ? 1 : plain_base)), a, grid, s)
-                : z2z_launch_logits_general(c->cfg.dtype == Z2Z_BF16, hyper, a, grid, s);
+  const int rc = z2z_launch_logits_fast(prob ? (hyper ? 4 : 3) : (a.sample && !hyper ? (a.sample == 2 ? 7 : 6) : (hyper ? 1 : plain_base)),
+                                        a, grid, s);
   if (timed) {
     Z2Z_HIP_TRY(hipEventRecord(c->ev_stop[c->n_timed], s));
     c->n_timed++;
@@ -327,14 +332,14 @@ int z2z_launch_logits_part(z2z_ctx* c, bool hyper, bool fast, LogitsArgs a, cons
   return rc;
 }
 
-
-
 // A workgroup sweeps a strip of 4 weight tiles with its rows' tile resident; with few row tiles that leaves CUs
-// idle, so the strips shorten until there are two workgroups per CU (or one tile per workgroup).
-static int pick_strip_for(const z2z_ctx* c, long long row_tiles, int n_vt) {
+// idle, so the strips shorten until there are `want` workgroups (or one tile per workgroup): two per CU for the
+// bf16 tile kernel, four for the general kernel, of which two run on a CU at a time (fp32, 600 rows x 32000
+// columns, d = 256: 124 us with two, 115 with four; 1024 rows: 184 and 182).
+static int pick_strip_for(const z2z_ctx* c, long long row_tiles, int n_vt, int want = 512) {
   if (c->opt_logits_strip > 0) return c->opt_logits_strip;
   int st = 4;
-  while (st > 1 && row_tiles * ((n_vt + st - 1) / st) < 512) st >>= 1;
+  while (st > 1 && row_tiles * ((n_vt + st - 1) / st) < want) st >>= 1;
   return st;
 }
 
@@ -381,23 +386,20 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     return launch_combine(parts, n_parts, rows, argmax, mx, lse, s);
   }
 
-  // (the general kernel is many times slower per tile: even a tile with a few valid rows goes to the tile kernel)
-  bool fast_base = fast_ok, fast_hyper = fast_ok;
-  if (c->opt_logits_kernel == 1) fast_base = fast_hyper = false;
+  // (the general kernel is many times slower per bf16 tile: even a tile with a few valid rows goes to the tile kernel)
+  const bool fast = fast_ok && c->opt_logits_kernel != 1;
 
-  // number of parts (strips of both launches), then the scratch for them.  A workgroup sweeps a strip of 4
-  // weight tiles with its rows' tile resident; with few row tiles that leaves CUs idle, so the strips shorten
-  // until there are two workgroups per CU (or one tile per workgroup)
-  const int base_tile = fast_base ? 256 : 128, hyp_tile = fast_hyper ? 256 : 128;
-  const int base_vt = (V + base_tile - 1) / base_tile, hyp_vt = (cap + hyp_tile - 1) / hyp_tile;
-  auto pick_strip = [&](long long row_tiles, int n_vt) { return pick_strip_for(c, row_tiles, n_vt); };
+  // number of parts (strips of both launches), then the scratch for them
+  const int tile = fast ? 256 : 128;
+  const int base_vt = (V + tile - 1) / tile, hyp_vt = (cap + tile - 1) / tile;
+  auto pick_strip = [&](long long row_tiles, int n_vt) { return pick_strip_for(c, row_tiles, n_vt, fast ? 512 : 1024); };
   // few hidden rows in all (several per sequence, or 65..192 sequences): the base part is bound by the bytes of
   // W_base and goes to the kernel that streams the weights past all rows at once, one part per 256 weight rows
   // (measured against the decode kernel's base units in a launch of their own at up to 64 rows: 260 against 305 us
   // for the call at config 2's shape; two or three passes of those units for more rows cost more still)
-  const bool mid_base = fast_base && c->opt_logits_kernel == 0 && z2z_logits_mid_ok(c, rows);
-  const int strip_b = mid_base ? 1 : pick_strip((rows + base_tile - 1) / base_tile, base_vt);
-  const int strip_h = pick_strip((long long)c->cfg.B * ((rows_per_seq + hyp_tile - 1) / hyp_tile), hyp_vt);
+  const bool mid_base = fast && c->opt_logits_kernel == 0 && z2z_logits_mid_ok(c, rows);
+  const int strip_b = mid_base ? 1 : pick_strip((rows + tile - 1) / tile, base_vt);
+  const int strip_h = pick_strip((long long)c->cfg.B * ((rows_per_seq + tile - 1) / tile), hyp_vt);
   const int base_strips = (base_vt + strip_b - 1) / strip_b;
   int hyp_strips = cap > 0 ? (hyp_vt + strip_h - 1) / strip_h : 0;
   if (decode_split) {
@@ -430,6 +432,27 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
   a.n_parts = n_parts;
   a.map_lr = a.map_ls = a.map_xr = a.map_xs = a.map_sb_r = 1;
 
+  if (!fast) {
+    // both parts in one launch of the general kernel
+    LogitsArgs h = a;
+    fill_part(a, nullptr, tile, 1, W_base, V, 0, 0, strip_b, rows, rows_per_seq);
+    if (cap > 0) fill_part(h, c->st.size, tile, c->cfg.B, W_hyper, cap, V, base_strips, strip_h, rows, rows_per_seq);
+    c->n_launch[Z2Z_KERNEL_GENERAL]++;
+    if (timed) Z2Z_HIP_TRY(hipEventRecord(c->ev_start[c->n_timed], s));
+    rc = z2z_launch_logits_general(c->cfg.dtype == Z2Z_BF16, a, cap > 0 ? &h : nullptr, s);
+    if (rc != Z2Z_OK) return rc;
+    if (timed) {
+      Z2Z_HIP_TRY(hipEventRecord(c->ev_stop[c->n_timed], s));
+      c->n_timed++;
+    }
+    if (logits && cap > 0) {
+      hipLaunchKernelGGL(logits_mask_kernel, dim3(rows), dim3(256), 0, s, logits, rows, rows_per_seq, V, cap,
+                         c->st.size);
+      Z2Z_HIP_TRY(hipGetLastError());
+    }
+    return launch_combine(parts, n_parts, rows, argmax, mx, lse, s);
+  }
+
   int ns = 0;
   if (mid_base) {
     if (timed) Z2Z_HIP_TRY(hipEventRecord(c->ev_start[c->n_timed], s));
@@ -439,7 +462,7 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
       c->n_timed++;
     }
   } else {
-    rc = z2z_launch_logits_part(c, false, fast_base, a, W_base, V, 0, 0, strip_b, rows, rows_per_seq, &ns, timed, s);
+    rc = z2z_launch_logits_part(c, false, a, W_base, V, 0, 0, strip_b, rows, rows_per_seq, &ns, timed, s);
   }
   if (rc != Z2Z_OK) return rc;
   if (cap > 0 && (decode_split || seq_split)) {
@@ -448,13 +471,8 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
                                   seq_split ? rows_per_seq : 1, seq_unit);
     if (rc != Z2Z_OK) return rc;
   } else if (cap > 0) {
-    rc = z2z_launch_logits_part(c, true, fast_hyper, a, W_hyper, cap, V, base_strips, strip_h, rows, rows_per_seq, &ns, false, s);
+    rc = z2z_launch_logits_part(c, true, a, W_hyper, cap, V, base_strips, strip_h, rows, rows_per_seq, &ns, false, s);
     if (rc != Z2Z_OK) return rc;
-    if (logits) {
-      hipLaunchKernelGGL(logits_mask_kernel, dim3(rows), dim3(256), 0, s, logits, rows, rows_per_seq, V, cap,
-                         c->st.size);
-      Z2Z_HIP_TRY(hipGetLastError());
-    }
   }
   return launch_combine(parts, n_parts, rows, argmax, mx, lse, s);
 }
@@ -512,7 +530,7 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     if (mid_base)
       rc = z2z_launch_logits_mid(c, a, W_base, c->cfg.V, 0, s);
     else
-      rc = z2z_launch_logits_part(c, false, true, a, W_base, c->cfg.V, 0, 0, strip_b, rows, 1, &ns, timed, s);
+      rc = z2z_launch_logits_part(c, false, a, W_base, c->cfg.V, 0, 0, strip_b, rows, 1, &ns, timed, s);
     if (rc != Z2Z_OK) return rc;
     if (c->cfg.cap > 0) {
       int np = 0;
@@ -584,7 +602,7 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     if (mid_base)
       rc = z2z_launch_logits_mid(c, a, W_base, c->cfg.V, 0, s);
     else
-      rc = z2z_launch_logits_part(c, false, true, a, W_base, c->cfg.V, 0, 0, strip_b, rows, 1, &ns, timed, s);
+      rc = z2z_launch_logits_part(c, false, a, W_base, c->cfg.V, 0, 0, strip_b, rows, 1, &ns, timed, s);
     if (rc != Z2Z_OK) return rc;
     if (c->cfg.cap > 0) {
       int np = 0;

@@ -527,7 +527,7 @@ __device__ __forceinline__ void store_prob_tile(const f32x16 (&acc)[NI][NJ], con
 }  // namespace z2z_logits
 
 // kernel launchers, one per translation unit
-int z2z_launch_logits_general(bool bf16, bool hyper, const z2z_logits::LogitsArgs& a, unsigned grid, hipStream_t s);
+int z2z_launch_logits_general(bool bf16, const z2z_logits::LogitsArgs& base, const z2z_logits::LogitsArgs* hyper, hipStream_t s);
 // mode: 0 base part, 1 hyper part (both fold the joint softmax), 2 dense layer (stores the tile),
 // 3 base part, 4 hyper part storing the gradient with respect to the logits, 5 dense layer with K split
 // (fp32 partial tiles)
@@ -542,7 +542,7 @@ int z2z_launch_linear(z2z_ctx* c, const void* A, const void* W, const float* bia
                       void* out, int R, const int32_t* rows_dev, int N, int K, hipStream_t s, const int32_t* k_dev = nullptr,
                       bool stream_f32 = false);
 int z2z_logits_fast_prepare(z2z_ctx* c);
-int z2z_launch_logits_part(z2z_ctx* c, bool hyper, bool fast, z2z_logits::LogitsArgs a, const void* W, int w_rows, int col0,
+int z2z_launch_logits_part(z2z_ctx* c, bool hyper, z2z_logits::LogitsArgs a, const void* W, int w_rows, int col0,
                            int part0, int strip, int rows, int rows_per_seq, int* n_strips_out, bool timed,
                            hipStream_t s, bool prob = false, int seq0 = 0, int n_seq = 0);
 // temperature sampling (one-row-per-sequence kernel only): softmax(logit / temperature), generator key and

@@ -5,7 +5,17 @@
 // operand: in the 32x32 result block a lane then holds 16 vocabulary entries of ONE hidden row, so the
 // running (max, sum-exp, argmax) of a row is kept in that lane's registers and crosses lanes only once
 // per strip.  A workgroup owns one tile of hidden rows and sweeps a strip of vocabulary tiles.
-// This is the fallback for shapes the fast bf16 kernel does not take, and the fp32 path.
+// This is the fp32 path, and the fallback for shapes the fast bf16 kernel does not take.
+//
+// fp32 is bound by the matrix cores (v_mfma_f32_32x32x2_f32: 256 flop per CU and clock, 157 TFLOP/s): a wave issues
+// 64 of them (4096 cycles) per slab, so two waves per SIMD -- two workgroups per CU -- cover the loads, the barriers
+// and each other's folds, provided nothing of the K loop spills.  The instance that stores the logits is a kernel of
+// its own for that reason (its store addresses and column tests cost the plain one 200 registers, scratch traffic
+// in the loop and the second workgroup), and operand rows are 32-bit offsets from one base address per tile.
+// Both parts share a launch, the hyper part's few tiles first; an XCD walks consecutive row tiles of consecutive
+// strips, so its L2 reads a weight strip once for all of them.
+// Measured, fp32, 1024 rows x 32000 columns and two codebooks, d = 256 (17.6 GFLOP): 421 us in two launches ->
+// 182 us (97 TFLOP/s); 2048 rows: 319 us (111 TFLOP/s).
 #include "logits_common.h"
 
 namespace {
@@ -22,28 +32,82 @@ constexpr int TV = 128;
 constexpr int TR = 128;
 constexpr int SLAB_BYTES = 128;
 constexpr int TILE_BYTES = TV * SLAB_BYTES;   // one operand tile in LDS (16 KiB)
+constexpr int ROW_BLOCK = 8;                  // row tiles that an XCD walks together per strip
 
+struct GeneralArgs {
+  LogitsArgs base, hyper;
+  int32_t hyper_grid;   // workgroups of the hyper part (the first ones), a multiple of 8
+};
+
+// The wave's four 32 x 32 blocks advance by one 16-byte chunk of K per lane.
 template <typename T>
-__device__ __forceinline__ void mfma_chunk(const uint4& a, const uint4& b, f32x16& acc);
+__device__ __forceinline__ void mfma_block(const f32x4 (&fa)[2], const f32x4 (&fb)[2], f32x16 (&acc)[2][2]);
 
 template <>
-__device__ __forceinline__ void mfma_chunk<uint16_t>(const uint4& a, const uint4& b, f32x16& acc) {
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0,
-                                                0, 0);
+__device__ __forceinline__ void mfma_block<uint16_t>(const f32x4 (&fa)[2], const f32x4 (&fb)[2], f32x16 (&acc)[2][2]) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[i]), __builtin_bit_cast(bf16x8, fb[j]),
+                                                          acc[i][j], 0, 0, 0);
 }
 
 template <>
-__device__ __forceinline__ void mfma_chunk<float>(const uint4& a, const uint4& b, f32x16& acc) {
+__device__ __forceinline__ void mfma_block<float>(const f32x4 (&fa)[2], const f32x4 (&fb)[2], f32x16 (&acc)[2][2]) {
   // a 16-byte chunk holds 4 consecutive k; lanes 0-31 and 32-63 hold different chunks, and the
   // pairing of k between the two operands is the same, so any order of the 4 steps is a valid sum
-  const f32x4 af = __builtin_bit_cast(f32x4, a);
-  const f32x4 bf = __builtin_bit_cast(f32x4, b);
 #pragma unroll
-  for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[e], bf[e], acc, 0, 0, 0);
+  for (int e = 0; e < 4; ++e)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][e], fb[j][e],
+                                                         acc[i][j], 0, 0, 0);
 }
 
-template <typename T, int HYPER>
-__global__ void __launch_bounds__(256) logits_general_kernel(LogitsArgs a) {
+// Fold the wave's 64 x 64 logits into the running triples (and store them).  TAIL: the tile has columns that do not exist.
+template <bool STORE, bool TAIL>
+__device__ __forceinline__ void fold_general(const f32x16 (&acc)[2][2], Triple (&run)[2], const LogitsArgs& a, int row0,
+                                             int r_end, int col_base, int n_valid) {
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int hrow = row0 + j * 32;
+    float* out = STORE ? a.logits + (size_t)min(hrow, r_end - 1) * a.ld + a.col0 : nullptr;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      float x[16];
+      float gmax = kNegInf;
+      int targ = 0;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int col = col_base + i * 32 + (v >> 2) * 8 + (v & 3);
+        x[v] = acc[i][j][v];
+        if (TAIL && col >= n_valid) x[v] = kNegInf;
+        if (x[v] > gmax) {
+          gmax = x[v];
+          targ = v;
+        }
+        if (STORE && col < n_valid && hrow < r_end) out[col] = x[v];
+      }
+      if (gmax > run[j].m) {
+        run[j].s = (run[j].m == kNegInf) ? 0.f : run[j].s * __expf(run[j].m - gmax);
+        run[j].m = gmax;
+        run[j].i = a.col0 + col_base + i * 32 + (targ >> 2) * 8 + (targ & 3);
+      }
+      if (run[j].m != kNegInf) {
+        float add = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) add += __expf(x[v] - run[j].m);
+        run[j].s += add;
+      }
+    }
+  }
+}
+
+template <typename T, bool STORE>
+__global__ void __launch_bounds__(256, 2) logits_general_kernel(GeneralArgs g) {
   __shared__ __align__(16) unsigned char lds[4 * TILE_BYTES];   // [buf][A|B][TILE_BYTES]
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -51,15 +115,27 @@ __global__ void __launch_bounds__(256) logits_general_kernel(LogitsArgs a) {
   const int wv = wave & 1;    // which 64 vocabulary rows of the tile
   const int wr = wave >> 1;   // which 64 hidden rows of the tile
 
-  // ---- which rows, which W, which strip ---------------------------------------------------------
-  const int st = blockIdx.x % a.n_strips;
-  const int rt = blockIdx.x / a.n_strips;
-  int r0, r_end, n_valid;
+  // ---- which part, rows, W, strip -----------------------------------------------------------------
+  const bool hyper = (int)blockIdx.x < g.hyper_grid;
+  const LogitsArgs& a = hyper ? g.hyper : g.base;
+  // workgroup ids go round-robin over the XCDs: XCD x takes the x-th eighth of the part's tiles, whose order is
+  // row tile in its block, strip, row block, sequence
+  const int id = hyper ? (int)blockIdx.x : (int)blockIdx.x - g.hyper_grid;
+  const int work = (id & 7) * ((a.n_work + 7) >> 3) + (id >> 3);
+  if ((id >> 3) >= (a.n_work + 7) >> 3 || work >= a.n_work) return;
+  const int per_seq = a.row_tiles * a.n_strips;
+  const int b = work / per_seq;                     // (the base part has one "sequence")
+  const int in_seq = work - b * per_seq;
+  const int blk = in_seq / (ROW_BLOCK * a.n_strips);
+  const int in_blk = in_seq - blk * ROW_BLOCK * a.n_strips;
+  const int blk_tiles = min(ROW_BLOCK, a.row_tiles - blk * ROW_BLOCK);
+  const int st = in_blk / blk_tiles;
+  const int rt = blk * ROW_BLOCK + (in_blk - st * blk_tiles);
   const unsigned char* Wp = reinterpret_cast<const unsigned char*>(a.W);
-  const size_t row_bytes = (size_t)a.d * sizeof(T);
-  if (HYPER) {
-    const int b = rt / a.row_tiles;
-    r0 = b * a.rows_per_seq + (rt % a.row_tiles) * TR;
+  const uint32_t row_bytes = (uint32_t)a.d * (uint32_t)sizeof(T);
+  int r0, r_end, n_valid;
+  if (hyper) {
+    r0 = b * a.rows_per_seq + rt * TR;
     r_end = (b + 1) * a.rows_per_seq;
     n_valid = min(max(a.size[b], 0), a.w_rows);
     Wp += (size_t)b * a.w_rows * row_bytes;
@@ -68,22 +144,34 @@ __global__ void __launch_bounds__(256) logits_general_kernel(LogitsArgs a) {
     r_end = a.rows;
     n_valid = a.w_rows;
   }
-  const unsigned char* Hp = reinterpret_cast<const unsigned char*>(a.H);
+  const unsigned char* Hp = reinterpret_cast<const unsigned char*>(a.H) + (size_t)r0 * row_bytes;
   const int vt0 = st * a.strip;
   const int vt1 = min(vt0 + a.strip, a.n_vtiles);
 
   Triple run[2];
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    run[j] = empty_triple();
-  }
+  for (int j = 0; j < 2; ++j) run[j] = empty_triple();
 
-  // global -> LDS staging: thread t moves chunks t, t+256, t+512, t+768 of each operand tile
+  // global -> LDS staging: thread t moves chunk t & 7 of rows (t >> 3) + 32 i, i < 4, of each operand tile
   const int n_slabs = (int)((row_bytes + SLAB_BYTES - 1) / SLAB_BYTES);
+  const uint32_t my_k = (uint32_t)(tid & 7) * 16;
+  uint32_t off_b[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) off_b[i] = (uint32_t)min((tid >> 3) + 32 * i, r_end - 1 - r0) * row_bytes + my_k;
+  // (the swizzle of row + 32 i is the row's own)
+  const int lds_at = (tid >> 3) * SLAB_BYTES + (((tid & 7) ^ ((tid >> 4) & 7)) << 4);
+  // operand reads: row = 64 w + 32 i + (lane & 31), chunk 2 q + (lane >> 5)
+  const int rd_a = (wv * 64 + (lane & 31)) * SLAB_BYTES;
+  const int rd_b = TILE_BYTES + (wr * 64 + (lane & 31)) * SLAB_BYTES;
+  const int swz = (lane >> 1) & 7;
 
   for (int vt = vt0; vt < vt1; ++vt) {
     const int v0 = vt * TV;
     if (v0 >= n_valid) break;
+    const unsigned char* Wt = Wp + (size_t)v0 * row_bytes;
+    uint32_t off_a[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) off_a[i] = (uint32_t)min((tid >> 3) + 32 * i, n_valid - 1 - v0) * row_bytes + my_k;
 
     f32x16 acc[2][2];
 #pragma unroll
@@ -93,34 +181,23 @@ __global__ void __launch_bounds__(256) logits_general_kernel(LogitsArgs a) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-    uint4 stage_a[4], stage_b[4];
+    f32x4 stage_a[4], stage_b[4];
     auto fetch = [&](int slab) {
-      const size_t kb = (size_t)slab * SLAB_BYTES;
+      const uint32_t kb = (uint32_t)slab * SLAB_BYTES;
+      const bool in_k = kb + my_k < row_bytes;       // (past the end of a row: zeros add nothing)
+      const f32x4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int id = tid + 256 * i;
-        const int row = id >> 3;
-        const int c = id & 7;
-        const size_t off = kb + (size_t)c * 16;
-        const bool in_k = off < row_bytes;
-        const int wrow = min(v0 + row, n_valid - 1);
-        const int hrow = min(r0 + row, r_end - 1);
-        const uint4 z = {0u, 0u, 0u, 0u};
-        stage_a[i] = in_k ? *reinterpret_cast<const uint4*>(Wp + (size_t)wrow * row_bytes + off) : z;
-        stage_b[i] = in_k ? *reinterpret_cast<const uint4*>(Hp + (size_t)hrow * row_bytes + off) : z;
+        stage_a[i] = in_k ? *reinterpret_cast<const f32x4*>(Wt + (off_a[i] + kb)) : z;
+        stage_b[i] = in_k ? *reinterpret_cast<const f32x4*>(Hp + (off_b[i] + kb)) : z;
       }
     };
     auto stash = [&](int buf) {
-      unsigned char* A = lds + (size_t)buf * 2 * TILE_BYTES;
-      unsigned char* Bt = A + TILE_BYTES;
+      unsigned char* A = lds + buf * 2 * TILE_BYTES + lds_at;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int id = tid + 256 * i;
-        const int row = id >> 3;
-        const int c = id & 7;
-        const int o = row * SLAB_BYTES + ((c ^ ((row >> 1) & 7)) << 4);
-        *reinterpret_cast<uint4*>(A + o) = stage_a[i];
-        *reinterpret_cast<uint4*>(Bt + o) = stage_b[i];
+        *reinterpret_cast<f32x4*>(A + i * 32 * SLAB_BYTES) = stage_a[i];
+        *reinterpret_cast<f32x4*>(A + TILE_BYTES + i * 32 * SLAB_BYTES) = stage_b[i];
       }
     };
 
@@ -131,26 +208,17 @@ __global__ void __launch_bounds__(256) logits_general_kernel(LogitsArgs a) {
     for (int slab = 0; slab < n_slabs; ++slab) {
       const int buf = slab & 1;
       if (slab + 1 < n_slabs) fetch(slab + 1);
-      const unsigned char* A = lds + (size_t)buf * 2 * TILE_BYTES;
-      const unsigned char* Bt = A + TILE_BYTES;
+      const unsigned char* L = lds + buf * 2 * TILE_BYTES;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int chunk = 2 * q + (lane >> 5);
-        uint4 fa[2], fb[2];
+        const int o = ((2 * q + (lane >> 5)) ^ swz) << 4;
+        f32x4 fa[2], fb[2];
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-          const int row = wv * 64 + i * 32 + (lane & 31);
-          fa[i] = *reinterpret_cast<const uint4*>(A + row * SLAB_BYTES + ((chunk ^ ((row >> 1) & 7)) << 4));
+          fa[i] = *reinterpret_cast<const f32x4*>(L + rd_a + i * 32 * SLAB_BYTES + o);
+          fb[i] = *reinterpret_cast<const f32x4*>(L + rd_b + i * 32 * SLAB_BYTES + o);
         }
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int row = wr * 64 + j * 32 + (lane & 31);
-          fb[j] = *reinterpret_cast<const uint4*>(Bt + row * SLAB_BYTES + ((chunk ^ ((row >> 1) & 7)) << 4));
-        }
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j) mfma_chunk<T>(fa[i], fb[j], acc[i][j]);
+        mfma_block<T>(fa, fb, acc);
       }
       if (slab + 1 < n_slabs) {
         stash(buf ^ 1);       // buffer buf^1 was last read two slabs ago, behind the barrier below
@@ -159,39 +227,12 @@ __global__ void __launch_bounds__(256) logits_general_kernel(LogitsArgs a) {
     }
 
     // ---- epilogue of this tile: fold the 128 x 128 logits into the running triples -------------
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int hrow = r0 + wr * 64 + j * 32 + (lane & 31);
-      float tmax = kNegInf;
-      int targ = kNoColumn;
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int col = v0 + wv * 64 + i * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-          float x = acc[i][j][v];
-          if (col >= n_valid) x = kNegInf;
-          acc[i][j][v] = x;
-          if (x > tmax) {
-            tmax = x;
-            targ = col;
-          }
-          if (a.logits != nullptr && col < n_valid && hrow < r_end) a.logits[(size_t)hrow * a.ld + a.col0 + col] = x;
-        }
-      if (tmax > run[j].m) {
-        run[j].s = (run[j].m == kNegInf) ? 0.f : run[j].s * __expf(run[j].m - tmax);
-        run[j].m = tmax;
-        run[j].i = a.col0 + targ;
-      }
-      if (run[j].m != kNegInf) {
-        float add = 0.f;
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) add += __expf(acc[i][j][v] - run[j].m);
-        run[j].s += add;
-      }
-    }
+    const int col_base = v0 + wv * 64 + (lane >> 5) * 4;
+    const int row0 = r0 + wr * 64 + (lane & 31);
+    if (v0 + TV <= n_valid)
+      fold_general<STORE, false>(acc, run, a, row0, r_end, col_base, n_valid);
+    else
+      fold_general<STORE, true>(acc, run, a, row0, r_end, col_base, n_valid);
   }
 
   // ---- end of strip: lanes l and l+32 hold the same hidden row; then the two vocabulary halves ---
@@ -227,18 +268,22 @@ __global__ void __launch_bounds__(256) logits_general_kernel(LogitsArgs a) {
 
 }  // namespace
 
-int z2z_launch_logits_general(bool bf16, bool hyper, const LogitsArgs& a, unsigned grid, hipStream_t s) {
-  if (bf16) {
-    if (hyper)
-      hipLaunchKernelGGL((logits_general_kernel<uint16_t, 1>), dim3(grid), dim3(256), 0, s, a);
-    else
-      hipLaunchKernelGGL((logits_general_kernel<uint16_t, 0>), dim3(grid), dim3(256), 0, s, a);
-  } else {
-    if (hyper)
-      hipLaunchKernelGGL((logits_general_kernel<float, 1>), dim3(grid), dim3(256), 0, s, a);
-    else
-      hipLaunchKernelGGL((logits_general_kernel<float, 0>), dim3(grid), dim3(256), 0, s, a);
-  }
+// One launch for both parts; hyper == nullptr: no hyper vocabulary.
+int z2z_launch_logits_general(bool bf16, const LogitsArgs& base, const LogitsArgs* hyper, hipStream_t s) {
+  GeneralArgs g;
+  g.base = base;
+  g.hyper = hyper ? *hyper : base;
+  g.hyper_grid = hyper ? (hyper->n_work + 7) / 8 * 8 : 0;
+  const dim3 grid((unsigned)g.hyper_grid + (unsigned)((base.n_work + 7) / 8 * 8)), block(256);
+  const bool store = base.logits != nullptr;
+  if (bf16 && store)
+    hipLaunchKernelGGL((logits_general_kernel<uint16_t, true>), grid, block, 0, s, g);
+  else if (bf16)
+    hipLaunchKernelGGL((logits_general_kernel<uint16_t, false>), grid, block, 0, s, g);
+  else if (store)
+    hipLaunchKernelGGL((logits_general_kernel<float, true>), grid, block, 0, s, g);
+  else
+    hipLaunchKernelGGL((logits_general_kernel<float, false>), grid, block, 0, s, g);
   Z2Z_HIP_TRY(hipGetLastError());
   return Z2Z_OK;
 }

@@ -142,7 +142,7 @@ int z2z_launch_extended_nll_backward(z2z_ctx* c, const void* H, int32_t rows, in
     int ns = 0;
     a.out = Pb;
     a.ldo = (int)Vp;
-    rc = z2z_launch_logits_part(c, false, true, a, W_base, V, 0, 0, strip, rows_c, rows_per_seq, &ns, false, s, true);
+    rc = z2z_launch_logits_part(c, false, a, W_base, V, 0, 0, strip, rows_c, rows_per_seq, &ns, false, s, true);
     if (rc != Z2Z_OK) return rc;
     if (cap > 0) {
       const size_t n16 = (size_t)rows_c * capp * 2 / 16;
@@ -150,7 +150,7 @@ int z2z_launch_extended_nll_backward(z2z_ctx* c, const void* H, int32_t rows, in
                          reinterpret_cast<uint4*>(Ph), n16);
       a.out = Ph;
       a.ldo = (int)capp;
-      rc = z2z_launch_logits_part(c, true, true, a, Whc, cap, V, 0, strip, rows_c, rows_per_seq, &ns, false, s, true, b0,
+      rc = z2z_launch_logits_part(c, true, a, Whc, cap, V, 0, strip, rows_c, rows_per_seq, &ns, false, s, true, b0,
                                   nb);
       if (rc != Z2Z_OK) return rc;
     }

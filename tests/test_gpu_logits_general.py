@@ -1,0 +1,72 @@
+"""GPU parity of the general tile kernel of extended_logits (fp32, and bf16 shapes the other kernels do not take), with
+and without the full-logits output: section 2.3, steps 7-9.
+
+Shapes sit at the edges of its tiles (128 x 128), of its blocks of eight row tiles, of a K slab (32 floats or 64
+bf16) and of a vocabulary tile; both instances must leave the same picks and maxima."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2506_01084_amd import workloads as wl
+
+from helpers import check_logits_rows, gpu_encode, oracle_encode_batch, torch_storage
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,B,rows_per_seq,V,d,cap", [
+    ("f32", 1, 1153, 300, 36, 40),      # ten row tiles (a block of eight and one of two), the last with one row
+    ("f32", 2, 129, 129, 4, 257),       # one chunk of K; a vocabulary tile with one column; three hyper tiles
+    ("f32", 9, 3, 1000, 100, 130),      # few rows of many sequences; a K slab with one chunk
+    ("f32", 3, 128, 2049, 64, 0),       # no hyper part; whole slabs
+    ("bf16", 2, 200, 700, 72, 150),     # d no multiple of 64
+    ("bf16", 1, 1, 50, 8, 5),           # a single row
+])
+def test_general_kernel(dtype, B, rows_per_seq, V, d, cap):
+    import torch
+
+    from paper_2506_01084_amd import api
+
+    M, N = 3, 700
+    cfg = dict(name="general", B=B, N=N, V=V, d=d, dtype=dtype, M=M, cap=cap, zipf_s=1.2, copy_frac=0.4, span=(2, 7),
+               mode="motif", pool="mean", seed=9500 + V + d)
+    print(f"[case] general kernel {dtype} B={B} rows/seq={rows_per_seq} V={V} d={d} cap={cap}", flush=True)
+    tokens = wl.make_tokens(cfg)
+    lens = np.full(B, N, dtype=np.int32)
+    if B > 2:
+        lens[1], lens[2] = 0, 9
+    E = wl.make_embeddings(cfg)
+    rows = B * rows_per_seq
+    H = wl.make_hidden(cfg, rows)
+    ctx = api.Context(B=B, V=V, M=M, cap=cap, d=d, dtype=dtype, pool="mean")
+    gpu_encode(ctx, tokens, lens)
+    ref = oracle_encode_batch(tokens, lens, V, M, cap)
+    d_E, d_H = torch_storage(E, dtype), torch_storage(H, dtype)
+    d_W = torch.zeros((B, cap, d), dtype=ctx.torch_dtype, device="cuda")
+    if cap:
+        ctx.hyper_embed(d_E, d_W)
+        for b in range(B):
+            d_W[b, len(ref[b][1]):] = 900.0        # rows that do not exist
+    ctx.set_option(api.OPT_LOGITS_KERNEL, 1)
+    ctx.set_option(api.OPT_DECODE_KERNEL, 1)
+    got = []
+    for full in (False, True):
+        am = torch.full((rows,), -5, dtype=torch.int32, device="cuda")
+        mx = torch.full((rows,), 777.0, device="cuda")
+        lse = torch.full((rows,), 777.0, device="cuda")
+        logits = torch.full((rows, V + cap), 777.0, device="cuda") if full else None
+        before = ctx.read_launches()["general"]
+        ctx.extended_logits(d_H, rows_per_seq, d_E, d_W, am, mx, lse, logits)
+        torch.cuda.synchronize()
+        assert ctx.read_launches()["general"] == before + 1
+        got.append([x.cpu().numpy() for x in (am, mx, lse)] + [logits.cpu().numpy() if full else None])
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+    # (the same sums in the same order; a multiply and an add may be contracted in one instance alone: ulps)
+    assert np.allclose(got[0][2], got[1][2], rtol=1e-6, atol=1e-6)
+    am, mx, lse, logits = got[1]
+    for b in range(B):
+        Wr = oracle.hyper_embed(E, dtype, ref[b][1], cap, "mean") if cap else np.zeros((0, d), E.dtype)
+        sl = slice(b * rows_per_seq, (b + 1) * rows_per_seq)
+        want = oracle.extended_logits(H[sl], E, Wr, len(ref[b][1]), dtype)
+        check_logits_rows(want, am[sl], mx[sl], lse[sl], logits[sl])
+    ctx.close()
