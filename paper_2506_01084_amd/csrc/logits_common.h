@@ -206,6 +206,10 @@ struct LogitsArgs {
   // side by side as map_xr x map_xs inside one super block, so that what runs at the same time shares
   // W strips and hidden-row tiles through the XCD's L2 and the memory-side cache.
   int32_t map_lr, map_ls, map_xr, map_xs, map_sb_r;
+  // row tiles behind the map_sb_r blocks along the rows, in up to three pieces of their own: piece k begins with an
+  // XCD's workgroup map_tail_j[k] and holds map_tail_rows[k] row tiles (8: 2 x 4 XCDs, each 4 row tiles; at most
+  // 4: 1 x 8); 0 rows: no piece
+  int32_t map_tail_j[3], map_tail_rows[3];
   float* part_m;          // [rows, n_parts]
   float* part_s;
   int32_t* part_i;

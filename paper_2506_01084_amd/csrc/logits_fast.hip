@@ -123,18 +123,28 @@ __device__ __forceinline__ uint32_t lds_offset_of(const void* p) {
 // Workgroup id -> (row tile, strip) for the base part; returns false when the id maps to no work.
 __device__ __forceinline__ bool map_base(const LogitsArgs& a, int bid, int* rt, int* st) {
   const int xcd = bid & 7;
-  const int j = bid >> 3;
-  const int per = a.map_lr * a.map_ls;
+  int j = bid >> 3;
+  int n_lr = a.map_lr, n_xr = a.map_xr, n_xs = a.map_xs, n_sb_r = a.map_sb_r, row0 = 0;
+  if (a.map_tail_rows[0] && j >= a.map_tail_j[0]) {     // a piece of the row tiles behind the whole blocks
+    const int k = a.map_tail_rows[2] && j >= a.map_tail_j[2] ? 2 : (a.map_tail_rows[1] && j >= a.map_tail_j[1] ? 1 : 0);
+    row0 = n_sb_r * n_xr * n_lr + (k > 0 ? a.map_tail_rows[0] : 0) + (k > 1 ? a.map_tail_rows[1] : 0);
+    j -= a.map_tail_j[k];
+    n_xr = a.map_tail_rows[k] == 8 ? 2 : 1;
+    n_lr = a.map_tail_rows[k] == 8 ? 4 : a.map_tail_rows[k];
+    n_xs = 8 / n_xr;
+    n_sb_r = 1;
+  }
+  const int per = n_lr * a.map_ls;
   const int g = j / per;
   const int within = j - g * per;
-  const int lr = within % a.map_lr;
-  const int ls = within / a.map_lr;
-  const int xr = xcd % a.map_xr;
-  const int xs = xcd / a.map_xr;
-  const int sb_r = g % a.map_sb_r;
-  const int sb_s = g / a.map_sb_r;
-  *rt = (sb_r * a.map_xr + xr) * a.map_lr + lr;
-  *st = (sb_s * a.map_xs + xs) * a.map_ls + ls;
+  const int lr = within % n_lr;
+  const int ls = within / n_lr;
+  const int xr = xcd % n_xr;
+  const int xs = xcd / n_xr;
+  const int sb_r = g % n_sb_r;
+  const int sb_s = g / n_sb_r;
+  *rt = row0 + (sb_r * n_xr + xr) * n_lr + lr;
+  *st = (sb_s * n_xs + xs) * a.map_ls + ls;
   return *rt < a.row_tiles && *st < a.n_strips;
 }
 
