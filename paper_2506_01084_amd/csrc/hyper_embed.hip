@@ -21,7 +21,8 @@ using namespace z2z_embed;
 template <bool BF16>
 __global__ void __launch_bounds__(256) hyper_embed_kernel(EmbedArgs a) {
   const int lane = threadIdx.x & 63;
-  const long long wave_id = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+  // (what a wave needs to know is the same for all its lanes: scalar loads, requested together)
+  const long long wave_id = (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int part = (int)(wave_id % a.split);
   const long long unit = wave_id / a.split;
   const int b = (int)(unit / a.units_per_seq);
@@ -39,9 +40,9 @@ __global__ void __launch_bounds__(256) hyper_embed_kernel(EmbedArgs a) {
       const int L = min(max(a.ent_len[row], 1), a.M);
       embed_row<BF16>(a, a.ent_tokens + row * a.M, L, row, lane, part);
     } else {
-      uint4* W = reinterpret_cast<uint4*>(a.W) + row * (size_t)n_chunks;
-      const uint4 z = {0u, 0u, 0u, 0u};
-      for (int c = part * 64 + lane; c < n_chunks; c += 64 * a.split) W[c] = z;
+      u32x4* W = reinterpret_cast<u32x4*>(a.W) + row * (size_t)n_chunks;
+      const u32x4 z = {0u, 0u, 0u, 0u};
+      for (int c = part * 64 + lane; c < n_chunks; c += 64 * a.split) __builtin_nontemporal_store(z, W + c);
     }
   }
 }
