@@ -807,7 +807,7 @@ int z2z_launch_hyper_encode_train(z2z_ctx* c, int mode, const void* E, const z2z
   if (u_step < 1) u_step = 1;
   if (u_step > cap) u_step = cap;
   const size_t R_max = (size_t)B * (size_t)u_step * M;
-  const size_t Rp = (R_max + 127) / 128 * 128;                  // contraction length of the weight-gradient products
+  const size_t Rp = z2z_contraction_pitch(R_max, 128);          // contraction length of the weight-gradient products
   const size_t n_units_max = (size_t)B * (size_t)u_step;
   const size_t index_bytes = ((n_units_max + 1 + R_max) * sizeof(int32_t) + 255) & ~(size_t)255;
   const size_t pos_bytes = ((size_t)Z2Z_MAX_M * d * sizeof(float) + 255) & ~(size_t)255;
@@ -913,7 +913,7 @@ int z2z_launch_hyper_encode_train(z2z_ctx* c, int mode, const void* E, const z2z
     m.un = (int)(u0 + u_step <= cap ? u_step : cap - u0);
     const int n_units = B * m.un;
     const int R = n_units * M;                       // upper bound; the real count is on the device
-    const int Rk = (R + 127) / 128 * 128;            // contraction length of this pass's weight-gradient products
+    const int Rk = (int)z2z_contraction_pitch(R, 128);   // contraction length of this pass's weight-gradient products
     const int32_t* rows_dev = m.row0 + n_units;
     const unsigned row_blocks = (unsigned)((R + 3) / 4);
     if (mode != 2) hipLaunchKernelGGL(enc_rows_kernel, dim3(1), dim3(1024), 0, s, m, n_units);

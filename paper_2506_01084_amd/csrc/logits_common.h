@@ -542,6 +542,13 @@ int z2z_launch_logits_fast(int mode, const z2z_logits::LogitsArgs& a, unsigned g
 // bf16 transpose with zero padding of the output rows (see dense.hip)
 int z2z_launch_transpose(const void* in, void* out, int R, const int32_t* rows_dev, int C, int ld_in, int ld_out,
                          int batch, size_t in_batch, size_t out_batch, hipStream_t s);
+// Row pitch (and contraction length, the padding holds zeros) of transposed operands whose contraction runs over n
+// rows: a multiple of `align`, and no multiple of 4 KiB -- rows a power of two apart put the slabs that all
+// workgroups read at one time on a few memory channels.
+inline size_t z2z_contraction_pitch(size_t n, size_t align) {
+  const size_t p = (n + align - 1) / align * align;
+  return p % 2048 ? p : p + 128;
+}
 int z2z_launch_linear(z2z_ctx* c, const void* A, const void* W, const float* bias, const void* residual, int act,
                       void* out, int R, const int32_t* rows_dev, int N, int K, hipStream_t s, const int32_t* k_dev = nullptr,
                       bool stream_f32 = false);

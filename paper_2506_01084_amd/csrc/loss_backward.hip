@@ -84,7 +84,7 @@ int z2z_launch_extended_nll_backward(z2z_ctx* c, const void* H, int32_t rows, in
   size_t o_g, o_Pb, o_PbT, o_Ph, o_PhT, o_WbT, o_WhT, o_HT, o_HTs;
   auto take = [&](size_t bytes) { const size_t at = off; off += round_up(bytes, 256); return at; };
   auto layout = [&](int n_seq) {
-    const size_t rc = (size_t)n_seq * rows_per_seq, rcp = round_up(rc, 64);
+    const size_t rc = (size_t)n_seq * rows_per_seq, rcp = z2z_contraction_pitch(rc, 64);
     off = 0;
     o_g = take(rc * 4);                              // float g[rows of the chunk]
     o_Pb = take(rc * Vp * 2);                        // dZ, base columns      [rows, Vp]
@@ -123,7 +123,7 @@ int z2z_launch_extended_nll_backward(z2z_ctx* c, const void* H, int32_t rows, in
   for (int b0 = 0; b0 < B; b0 += n_seq) {
     const int nb = b0 + n_seq <= B ? n_seq : B - b0;
     const int r0 = b0 * rows_per_seq, rows_c = nb * rows_per_seq;
-    const size_t rows_p = round_up(rows_c, 64);
+    const size_t rows_p = z2z_contraction_pitch(rows_c, 64);
     const uint16_t* Hc = H16 + (size_t)r0 * d;
     const uint16_t* Whc = Wh16 + (size_t)b0 * cap * d;
     hipLaunchKernelGGL(row_grad_kernel, dim3((rows_c + 255) / 256), dim3(256), 0, s, targets + r0,
