@@ -116,36 +116,38 @@ int z2z_launch_transpose(const void* in, void* out, int R, const int32_t* rows_d
   return Z2Z_OK;
 }
 
-int z2z_launch_linear(z2z_ctx* c, const void* A, const void* W, const float* bias, const void* residual, int act,
-                      void* out, int R, const int32_t* rows_dev, int N, int K, hipStream_t s, const int32_t* k_dev,
-                      bool stream_f32) {
+namespace {
+
+// The partial tiles' buffer, at least `need` bytes of it.
+int ensure_partial(z2z_ctx* c, size_t need, hipStream_t s) {
+  if (need <= c->skinny_partial_bytes) return Z2Z_OK;
+  Z2Z_TRY_GROW(s);
+  if (c->skinny_partial) (void)hipFree(c->skinny_partial);
+  c->skinny_partial = nullptr;
+  c->skinny_partial_bytes = 0;
+  const size_t want = need > ((size_t)64 << 20) ? need : ((size_t)64 << 20);
+  if (hipMalloc(&c->skinny_partial, want) != hipSuccess) return Z2Z_ENOMEM;
+  c->skinny_partial_bytes = want;
+  return Z2Z_OK;
+}
+
+}  // namespace
+
+int z2z_launch_linear_parts(z2z_ctx* c, const void* A, const void* W, int R, const int32_t* rows_dev, int N, int K,
+                            bool k_on_device, const float** partial, int* ksplit_out, hipStream_t s) {
+  *ksplit_out = 0;
   // up to 128 rows (a decode step's new entries through the learned encoder at a small batch): bound by the weight
   // bytes; the weight-streaming kernel with K split over workgroups, its fp32 partial tiles summed with the layer's
   // epilogue.  (The encoder's newest-entry pass at d = 4096, d_ff = 4 d: 347 -> 302 us for 8 sequences, 401 -> 374
   // for 40; with the 192-row build for 129..192 rows laid out the tile kernel's K split below is faster, 432
   // against 459 us for 64 sequences.)
-  if (R <= 128 && !k_dev && K % 64 == 0 && N % 4 == 0 && c->opt_logits_kernel == 0 && z2z_logits_mid_ok(c, R)) {
+  if (R <= 128 && !k_on_device && K % 64 == 0 && N % 4 == 0 && c->opt_logits_kernel == 0 && z2z_logits_mid_ok(c, R)) {
     const int ksplit = z2z_linear_mid_ksplit(N, K);
-    const size_t need = (size_t)ksplit * R * N * sizeof(float);
-    if (need > c->skinny_partial_bytes) {
-      Z2Z_TRY_GROW(s);
-      if (c->skinny_partial) (void)hipFree(c->skinny_partial);
-      c->skinny_partial = nullptr;
-      c->skinny_partial_bytes = 0;
-      const size_t want = need > ((size_t)64 << 20) ? need : ((size_t)64 << 20);
-      if (hipMalloc(&c->skinny_partial, want) != hipSuccess) return Z2Z_ENOMEM;
-      c->skinny_partial_bytes = want;
-    }
-    int ks = 0;
-    int rc = z2z_launch_linear_mid(c, A, W, R, rows_dev, N, K, reinterpret_cast<float*>(c->skinny_partial),
-                                   c->skinny_partial_bytes / sizeof(float), &ks, s);
+    int rc = ensure_partial(c, (size_t)ksplit * R * N * sizeof(float), s);
     if (rc != Z2Z_OK) return rc;
-    const long long n_threads = (long long)R * (N / 4);
-    hipLaunchKernelGGL(linear_sum_kernel, dim3((unsigned)((n_threads + 255) / 256)), dim3(256), 0, s,
-                       reinterpret_cast<const float*>(c->skinny_partial), ks, R, rows_dev, N, bias, act, residual, out,
-                       stream_f32 ? 1 : 0);
-    Z2Z_HIP_TRY(hipGetLastError());
-    return Z2Z_OK;
+    *partial = reinterpret_cast<const float*>(c->skinny_partial);
+    return z2z_launch_linear_mid(c, A, W, R, rows_dev, N, K, reinterpret_cast<float*>(c->skinny_partial),
+                                 c->skinny_partial_bytes / sizeof(float), ksplit_out, s);
   }
   // more rows than the 64 the decode-step kernel serves per pass over the weights, but fewer 256 x 256 output
   // tiles than would give every CU one (a few hundred rows, or up to a few thousand with a narrow layer): the
@@ -159,16 +161,8 @@ int z2z_launch_linear(z2z_ctx* c, const void* A, const void* W, const float* bia
     if (ksplit > 1) {
       const int per = (n_slabs + ksplit - 1) / ksplit;
       ksplit = (n_slabs + per - 1) / per;
-      const size_t need = (size_t)ksplit * R * N * sizeof(float);
-      if (need > c->skinny_partial_bytes) {
-        Z2Z_TRY_GROW(s);
-        if (c->skinny_partial) (void)hipFree(c->skinny_partial);
-        c->skinny_partial = nullptr;
-        c->skinny_partial_bytes = 0;
-        const size_t want = need > ((size_t)64 << 20) ? need : ((size_t)64 << 20);
-        if (hipMalloc(&c->skinny_partial, want) != hipSuccess) return Z2Z_ENOMEM;
-        c->skinny_partial_bytes = want;
-      }
+      int rc = ensure_partial(c, (size_t)ksplit * R * N * sizeof(float), s);
+      if (rc != Z2Z_OK) return rc;
       LogitsArgs a;
       memset(&a, 0, sizeof(a));
       a.H = A;
@@ -186,15 +180,27 @@ int z2z_launch_linear(z2z_ctx* c, const void* A, const void* W, const float* bia
       a.ksplit = ksplit;
       a.slabs_per_part = per;
       a.partial = reinterpret_cast<float*>(c->skinny_partial);
-      int rc = z2z_launch_logits_fast(5, a, (unsigned)(tiles * ksplit), s);
-      if (rc != Z2Z_OK) return rc;
-      const long long n_threads = (long long)R * (N / 4);
-      hipLaunchKernelGGL(linear_sum_kernel, dim3((unsigned)((n_threads + 255) / 256)), dim3(256), 0, s,
-                         reinterpret_cast<const float*>(c->skinny_partial), ksplit, R, rows_dev, N, bias, act, residual,
-                         out, stream_f32 ? 1 : 0);
-      Z2Z_HIP_TRY(hipGetLastError());
-      return Z2Z_OK;
+      *partial = a.partial;
+      *ksplit_out = ksplit;
+      return z2z_launch_logits_fast(5, a, (unsigned)(tiles * ksplit), s);
     }
+  }
+  return Z2Z_OK;
+}
+
+int z2z_launch_linear(z2z_ctx* c, const void* A, const void* W, const float* bias, const void* residual, int act,
+                      void* out, int R, const int32_t* rows_dev, int N, int K, hipStream_t s, const int32_t* k_dev,
+                      bool stream_f32) {
+  const float* partial = nullptr;
+  int ksplit = 0;
+  int rc = z2z_launch_linear_parts(c, A, W, R, rows_dev, N, K, k_dev != nullptr, &partial, &ksplit, s);
+  if (rc != Z2Z_OK) return rc;
+  if (ksplit > 0) {
+    const long long n_threads = (long long)R * (N / 4);
+    hipLaunchKernelGGL(linear_sum_kernel, dim3((unsigned)((n_threads + 255) / 256)), dim3(256), 0, s, partial, ksplit, R,
+                       rows_dev, N, bias, act, residual, out, stream_f32 ? 1 : 0);
+    Z2Z_HIP_TRY(hipGetLastError());
+    return Z2Z_OK;
   }
   // few rows: bound by the weight bytes, which the decode-step kernel streams at HBM rate (it re-reads them
   // once per 64 rows, so it loses to the tile kernel beyond a few hundred rows)

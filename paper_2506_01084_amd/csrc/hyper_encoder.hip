@@ -204,6 +204,126 @@ __global__ void __launch_bounds__(256) enc_norm_kernel(RowMap m, const uint4* E,
   }
 }
 
+// ---- few rows: a workgroup per row or entry -------------------------------------------------------------------
+// With a hundred rows in a pass every one of these launches is a chain of trips to memory, so a row gets a wave per
+// 256 columns instead of one for all, and what follows a K-split dense layer adds up its partial tiles itself.  Newest
+// entries of 8, 24, 64 sequences at d = 4096, two layers: 297 -> 261 us, 342 -> 307, 430 -> 395.
+struct Parts {
+  const float* partial;          // [ksplit][R][d], added up in order
+  int ksplit, R;
+  const float* bias;             // [d]
+  const float* residual;         // [R, d]
+};
+
+// 4 columns from `col` of row r of the layer's output: sum of the parts, bias, residual.
+__device__ __forceinline__ float4 sum_parts(const Parts& p, int r, int col, int d) {
+  const size_t at = (size_t)r * d + col, plane = (size_t)p.R * d;
+  const float4 rv = *reinterpret_cast<const float4*>(p.residual + at);
+  const float4 b = p.bias ? *reinterpret_cast<const float4*>(p.bias + col) : float4{0.f, 0.f, 0.f, 0.f};
+  float4 x = *reinterpret_cast<const float4*>(p.partial + at);
+#pragma unroll 8
+  for (int k = 1; k < p.ksplit; ++k) {
+    const float4 y = *reinterpret_cast<const float4*>(p.partial + (size_t)k * plane + at);
+    x.x += y.x;
+    x.y += y.y;
+    x.z += y.z;
+    x.w += y.w;
+  }
+  return float4{x.x + b.x + rv.x, x.y + b.y + rv.y, x.z + b.z + rv.z, x.w + b.w + rv.w};
+}
+
+constexpr int E_ROW_THREADS = 1024;    // 4 columns each: d <= 4096
+static_assert(4 * E_ROW_THREADS >= 64 * 8 * E_KCH, "a row fits the workgroup");
+
+__device__ __forceinline__ float row_sum(float v, float* xch) {      // over the workgroup; xch: 16 floats of its own
+  v = wave_sum(v);
+  if ((threadIdx.x & 63) == 0) xch[threadIdx.x >> 6] = v;
+  __syncthreads();
+  float t = 0.f;
+#pragma unroll
+  for (int w = 0; w < E_ROW_THREADS / 64; ++w) t += xch[w];
+  return t;
+}
+
+// enc_norm_kernel for few rows: X[r] = E[token] + P[slot] (GATHER) or the finished sum of a K-split layer, then A[r].
+template <bool GATHER>
+__global__ void __launch_bounds__(E_ROW_THREADS) enc_row_norm_kernel(RowMap m, const uint16_t* E, const uint16_t* P, Parts parts,
+                                                                     float* X, uint16_t* A, const float* gamma,
+                                                                     const float* beta, int n_units) {
+  __shared__ float xch[2][E_ROW_THREADS / 64];
+  const int r = blockIdx.x;
+  if (r >= m.row0[n_units]) return;
+  const int col = 4 * (int)threadIdx.x;
+  const bool in = col < m.d;
+  float4 g = {0.f, 0.f, 0.f, 0.f}, bt = g, x = g;
+  if (in) {
+    g = *reinterpret_cast<const float4*>(gamma + col);
+    bt = *reinterpret_cast<const float4*>(beta + col);
+  }
+  if (GATHER) {
+    const int rs = m.row_slot[r];
+    const int i = rs & 7;
+    const int bu = rs >> 3;
+    const int b = bu / m.un, u = bu % m.un;
+    int C;
+    const int e = entry_of(m, b, u, &C);
+    const int tok = min(max(m.ent_tokens[((size_t)b * m.cap + e) * m.M + i], 0), m.V - 1);
+    if (in) {
+      const uint2 ev = *reinterpret_cast<const uint2*>(E + (size_t)tok * m.d + col);
+      const uint2 pv = P ? *reinterpret_cast<const uint2*>(P + (size_t)i * m.d + col) : uint2{0u, 0u};
+      x.x = __uint_as_float(ev.x << 16) + __uint_as_float(pv.x << 16);
+      x.y = __uint_as_float(ev.x & 0xFFFF0000u) + __uint_as_float(pv.x & 0xFFFF0000u);
+      x.z = __uint_as_float(ev.y << 16) + __uint_as_float(pv.y << 16);
+      x.w = __uint_as_float(ev.y & 0xFFFF0000u) + __uint_as_float(pv.y & 0xFFFF0000u);
+    }
+  } else if (in) {
+    x = sum_parts(parts, r, col, m.d);
+  }
+  if (in) *reinterpret_cast<float4*>(X + (size_t)r * m.d + col) = x;
+  const float mean = row_sum((x.x + x.y) + (x.z + x.w), xch[0]) / (float)m.d;
+  const float dx = x.x - mean, dy = x.y - mean, dz = x.z - mean, dw = x.w - mean;
+  const float rstd = rsqrtf(row_sum(in ? (dx * dx + dy * dy) + (dz * dz + dw * dw) : 0.f, xch[1]) / (float)m.d + E_EPS);
+  if (in) {
+    uint2 o;
+    o.x = bf16_bits_rne(dx * rstd * g.x + bt.x) | (bf16_bits_rne(dy * rstd * g.y + bt.y) << 16);
+    o.y = bf16_bits_rne(dz * rstd * g.z + bt.z) | (bf16_bits_rne(dw * rstd * g.w + bt.w) << 16);
+    *reinterpret_cast<uint2*>(A + (size_t)r * m.d + col) = o;
+  }
+}
+
+// enc_pool_kernel behind a K-split last layer: grid (entries, ceil(d / 256)), a lane per 4 columns, a wave per slot
+// (the first adds the slots up, in order).
+__global__ void __launch_bounds__(64 * Z2Z_MAX_M) enc_sum_pool_kernel(RowMap m, Parts parts, uint16_t* W, int zero_missing) {
+  __shared__ float4 xch[Z2Z_MAX_M][64];
+  const int bu = blockIdx.x, lane = threadIdx.x & 63, i = threadIdx.x >> 6;
+  const int col = 4 * (int)(blockIdx.y * 64 + lane);
+  const int b = bu / m.un, u = bu % m.un;
+  int C;
+  const int e = entry_of(m, b, u, &C);
+  if (e >= m.cap) return;                            // (the whole workgroup)
+  uint2* w = reinterpret_cast<uint2*>(W + ((size_t)b * m.cap + e) * m.d + col);
+  if (e >= C) {
+    if (zero_missing && i == 0 && col < m.d) *w = uint2{0u, 0u};
+    return;
+  }
+  const int r0 = m.row0[bu], L = m.row0[bu + 1] - r0;
+  if (i < L && col < m.d) xch[i][lane] = sum_parts(parts, r0 + i, col, m.d);
+  __syncthreads();
+  if (i > 0 || col >= m.d) return;
+  float4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int j = 0; j < L; ++j) {
+    acc.x += xch[j][lane].x;
+    acc.y += xch[j][lane].y;
+    acc.z += xch[j][lane].z;
+    acc.w += xch[j][lane].w;
+  }
+  const float invL = 1.0f / (float)L;
+  uint2 o;
+  o.x = bf16_bits_rne(acc.x * invL) | (bf16_bits_rne(acc.y * invL) << 16);
+  o.y = bf16_bits_rne(acc.z * invL) | (bf16_bits_rne(acc.w * invL) << 16);
+  *w = o;
+}
+
 // Attention among the slots of one entry.  QKV [rows, 3d] holds q | k | v of every real slot; a wave takes
 // one entry and 512 consecutive features (whole heads: the head width is a power of two of at most 512), lane
 // l the 8 features of chunk l.  Scores are reduced over the lanes_per_head lanes of a head; the softmax runs
@@ -730,38 +850,76 @@ int z2z_launch_hyper_encode(z2z_ctx* c, const void* E, const z2z_encoder* enc, v
     hipLaunchKernelGGL(enc_rows_kernel, dim3(1), dim3(1024), 0, s, m, n_units);
     float* x = X;
     float* y = Y;
+    bool normed = false;                            // A holds the layer's normalised input already
+    bool pooled = false;
+    int rc;
+    // A dense layer that adds to the residual stream: out = in A^T + bias + residual, then the LayerNorm that follows
+    // (gamma, beta -> A) or, behind the last layer, the mean over an entry's rows.  Where K is split those
+    // add up the partial tiles themselves; else *fused stays false and only `out` is written.
+    auto layer_out = [&](const uint16_t* in, const void* w, const float* bias, const float* residual, float* out, int K,
+                         const float* gamma, const float* beta, bool* fused) -> int {
+      Parts parts = {};
+      *fused = false;
+      int ret = z2z_launch_linear_parts(c, in, w, R, rows_dev, d, K, false, &parts.partial, &parts.ksplit, s);
+      if (ret != Z2Z_OK) return ret;
+      if (parts.ksplit == 0) return z2z_launch_linear(c, in, w, bias, residual, 0, out, R, rows_dev, d, K, s, nullptr, true);
+      parts.R = R;
+      parts.bias = bias;
+      parts.residual = residual;
+      *fused = true;
+      if (gamma)
+        hipLaunchKernelGGL(enc_row_norm_kernel<false>, dim3((unsigned)R), dim3(E_ROW_THREADS), 0, s, m, nullptr, nullptr, parts, out,
+                           A, gamma, beta, n_units);
+      else
+        hipLaunchKernelGGL(enc_sum_pool_kernel, dim3((unsigned)n_units, (unsigned)((d + 255) / 256)), dim3((unsigned)(64 * M)), 0, s, m,
+                           parts, reinterpret_cast<uint16_t*>(W_hyper), incremental ? 0 : 1);
+      return Z2Z_OK;
+    };
     for (int l = 0; l < enc->n_layers; ++l) {
       const z2z_encoder_layer& lay = enc->layers[l];
-      if (l == 0)
+      const z2z_encoder_layer* next = l + 1 < enc->n_layers ? &enc->layers[l + 1] : nullptr;
+      if (l == 0 && R <= 2048) {                    // (few rows: a workgroup each, 24 entries, 52 rows: 14 -> 5 us)
+        hipLaunchKernelGGL(enc_row_norm_kernel<true>, dim3((unsigned)R), dim3(E_ROW_THREADS), 0, s, m,
+                           reinterpret_cast<const uint16_t*>(E), reinterpret_cast<const uint16_t*>(enc->pos), Parts{}, x, A,
+                           lay.ln1_g, lay.ln1_b, n_units);
+      } else if (l == 0) {
         hipLaunchKernelGGL(enc_norm_kernel<true>, dim3(row_blocks), dim3(256), 0, s, m,
                            reinterpret_cast<const uint4*>(E), reinterpret_cast<const uint4*>(enc->pos), x,
                            reinterpret_cast<uint4*>(A), lay.ln1_g, lay.ln1_b, n_units);
-      else
+      } else if (!normed) {
         hipLaunchKernelGGL(enc_norm_kernel<false>, dim3(row_blocks), dim3(256), 0, s, m, nullptr, nullptr, x,
                            reinterpret_cast<uint4*>(A), lay.ln1_g, lay.ln1_b, n_units);
-      int rc = z2z_launch_linear(c, A, lay.w_qkv, lay.b_qkv, nullptr, 0, QKV, R, rows_dev, 3 * d, d, s);
+      }
+      rc = z2z_launch_linear(c, A, lay.w_qkv, lay.b_qkv, nullptr, 0, QKV, R, rows_dev, 3 * d, d, s);
       if (rc != Z2Z_OK) return rc;
       const long long att_waves = (long long)n_units * groups;
       hipLaunchKernelGGL(enc_attention_kernel, dim3((unsigned)((att_waves + 3) / 4)), dim3(256), 0, s, m,
                          reinterpret_cast<const uint4*>(QKV), reinterpret_cast<uint4*>(O), dh / 8, scale, groups,
                          n_units);
-      rc = z2z_launch_linear(c, O, lay.w_o, lay.b_o, x, 0, y, R, rows_dev, d, d, s, nullptr, true);
-      if (rc != Z2Z_OK) return rc;
+      bool fused = false;
       if (enc->attention_only) {
+        rc = layer_out(O, lay.w_o, lay.b_o, x, y, d, next ? next->ln1_g : nullptr, next ? next->ln1_b : nullptr, &fused);
+        if (rc != Z2Z_OK) return rc;
         float* t = x;
         x = y;
         y = t;
       } else {
-        hipLaunchKernelGGL(enc_norm_kernel<false>, dim3(row_blocks), dim3(256), 0, s, m, nullptr, nullptr, y,
-                           reinterpret_cast<uint4*>(A), lay.ln2_g, lay.ln2_b, n_units);
+        rc = layer_out(O, lay.w_o, lay.b_o, x, y, d, lay.ln2_g, lay.ln2_b, &fused);
+        if (rc != Z2Z_OK) return rc;
+        if (!fused)
+          hipLaunchKernelGGL(enc_norm_kernel<false>, dim3(row_blocks), dim3(256), 0, s, m, nullptr, nullptr, y,
+                             reinterpret_cast<uint4*>(A), lay.ln2_g, lay.ln2_b, n_units);
         rc = z2z_launch_linear(c, A, lay.w_1, lay.b_1, nullptr, 1, F, R, rows_dev, dff, d, s);
         if (rc != Z2Z_OK) return rc;
-        rc = z2z_launch_linear(c, F, lay.w_2, lay.b_2, y, 0, x, R, rows_dev, d, dff, s, nullptr, true);
+        rc = layer_out(F, lay.w_2, lay.b_2, y, x, dff, next ? next->ln1_g : nullptr, next ? next->ln1_b : nullptr, &fused);
         if (rc != Z2Z_OK) return rc;
       }
+      normed = fused && next;
+      pooled = fused && !next;
     }
-    hipLaunchKernelGGL(enc_pool_kernel, dim3((unsigned)((n_units + 3) / 4)), dim3(256), 0, s, m, x,
-                       reinterpret_cast<uint4*>(W_hyper), n_units, incremental ? 0 : 1);
+    if (!pooled)
+      hipLaunchKernelGGL(enc_pool_kernel, dim3((unsigned)((n_units + 3) / 4)), dim3(256), 0, s, m, x,
+                         reinterpret_cast<uint4*>(W_hyper), n_units, incremental ? 0 : 1);
   }
   Z2Z_HIP_TRY(hipGetLastError());
   return Z2Z_OK;

@@ -552,6 +552,11 @@ inline size_t z2z_contraction_pitch(size_t n, size_t align) {
 int z2z_launch_linear(z2z_ctx* c, const void* A, const void* W, const float* bias, const void* residual, int act,
                       void* out, int R, const int32_t* rows_dev, int N, int K, hipStream_t s, const int32_t* k_dev = nullptr,
                       bool stream_f32 = false);
+// The same product where the layer's K is split over workgroups (few rows): only the fp32 partial tiles,
+// [*ksplit][R][N] at *partial, which the caller adds up in order before the next dense layer is launched; *ksplit = 0:
+// the layer is not split at this shape, nothing was launched.
+int z2z_launch_linear_parts(z2z_ctx* c, const void* A, const void* W, int R, const int32_t* rows_dev, int N, int K,
+                            bool k_on_device, const float** partial, int* ksplit, hipStream_t s);
 int z2z_logits_fast_prepare(z2z_ctx* c);
 int z2z_launch_logits_part(z2z_ctx* c, bool hyper, z2z_logits::LogitsArgs a, const void* W, int w_rows, int col0,
                            int part0, int strip, int rows, int rows_per_seq, int* n_strips_out, bool timed,
