@@ -191,9 +191,16 @@ int z2z_launch_linear_parts(z2z_ctx* c, const void* A, const void* W, int R, con
   return Z2Z_OK;
 }
 
+bool z2z_linear_takes_pitch(const z2z_ctx* c, int R, int N, int K) {
+  // (more rows than the few-row kernels take, and not split over K by z2z_launch_linear_parts)
+  const long long tiles = (long long)((R + 255) / 256) * ((N + 255) / 256);
+  return R > 512 && c->fast_ready && K % 64 == 0 && N % 8 == 0 && (tiles >= 192 || K / 64 < 16);
+}
+
 int z2z_launch_linear(z2z_ctx* c, const void* A, const void* W, const float* bias, const void* residual, int act,
                       void* out, int R, const int32_t* rows_dev, int N, int K, hipStream_t s, const int32_t* k_dev,
-                      bool stream_f32) {
+                      bool stream_f32, const z2z_linear_pitch* pitch) {
+  if (pitch && !z2z_linear_takes_pitch(c, R, N, K)) return Z2Z_EUNSUPPORTED;
   const float* partial = nullptr;
   int ksplit = 0;
   int rc = z2z_launch_linear_parts(c, A, W, R, rows_dev, N, K, k_dev != nullptr, &partial, &ksplit, s);
@@ -229,7 +236,9 @@ int z2z_launch_linear(z2z_ctx* c, const void* A, const void* W, const float* bia
   a.bias = bias;
   a.residual = residual;
   a.act = act;
-  a.ldo = N;
+  a.ldo = pitch ? pitch->out : N;
+  a.ldh = pitch ? pitch->a : 0;
+  a.ldw = pitch ? pitch->w : 0;
   a.stream_f32 = stream_f32 ? 1 : 0;
   a.rows_dev = nullptr;
   a.k_dev = k_dev;

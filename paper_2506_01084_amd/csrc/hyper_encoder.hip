@@ -458,8 +458,8 @@ __global__ void __launch_bounds__(256) enc_pool_backward_kernel(RowMap m, const 
 // out[n] += sum over the pass's rows of G[r, n] (bias gradients).  A thread owns 8 columns and the rows
 // stripe + E_CS_STRIPES * (lane group + 4 i); grid (ceil(N / 512), E_CS_STRIPES): few adds per address.
 constexpr int E_CS_STRIPES = 32;
-__global__ void __launch_bounds__(256) enc_colsum_kernel(const uint4* G, int n_chunks, const int32_t* rows_dev,
-                                                         float* out) {
+__global__ void __launch_bounds__(256) enc_colsum_kernel(const uint4* G, int n_chunks, int pitch,
+                                                         const int32_t* rows_dev, float* out) {
   const int c = blockIdx.x * 64 + (threadIdx.x & 63);
   const int rows = *rows_dev;
   if (c >= n_chunks) return;
@@ -467,10 +467,10 @@ __global__ void __launch_bounds__(256) enc_colsum_kernel(const uint4* G, int n_c
   const uint4 zero = {0u, 0u, 0u, 0u};
   const int step = 4 * E_CS_STRIPES;
   for (int r = blockIdx.y + E_CS_STRIPES * (threadIdx.x >> 6); r < rows; r += 4 * step) {   // four loads in flight
-    const uint4 q0 = G[(size_t)r * n_chunks + c];
-    const uint4 q1 = r + step < rows ? G[(size_t)(r + step) * n_chunks + c] : zero;
-    const uint4 q2 = r + 2 * step < rows ? G[(size_t)(r + 2 * step) * n_chunks + c] : zero;
-    const uint4 q3 = r + 3 * step < rows ? G[(size_t)(r + 3 * step) * n_chunks + c] : zero;
+    const uint4 q0 = G[(size_t)r * pitch + c];
+    const uint4 q1 = r + step < rows ? G[(size_t)(r + step) * pitch + c] : zero;
+    const uint4 q2 = r + 2 * step < rows ? G[(size_t)(r + 2 * step) * pitch + c] : zero;
+    const uint4 q3 = r + 3 * step < rows ? G[(size_t)(r + 3 * step) * pitch + c] : zero;
     float g[8];
     unpack8(q0, g);
 #pragma unroll
@@ -782,6 +782,15 @@ __global__ void __launch_bounds__(256) enc_to_bf16_kernel(const float* in, uint1
 
 }  // namespace
 
+// Row pitch of the feed-forward activations of a call that takes `units` entries per sequence, u_step a pass: the padded
+// one if every pass, the last and shortest too, runs their products on kernels that take it.
+static int ffn_pitch(const z2z_ctx* c, int B, int M, int units, int u_step, int d, int dff) {
+  const int last = (units - 1) % u_step + 1;
+  for (int u : {u_step, last})
+    if (dff == 0 || !z2z_linear_takes_pitch(c, B * u * M, dff, d) || !z2z_linear_takes_pitch(c, B * u * M, d, dff)) return dff;
+  return z2z_activation_pitch(dff);
+}
+
 bool z2z_hyper_encode_ok(const z2z_ctx* c, const z2z_encoder* enc) {
   const int d = c->cfg.d;
   if (c->cfg.dtype != Z2Z_BF16 || !c->fast_ready || d % 64 != 0 || d > 64 * 8 * E_KCH) return false;
@@ -804,10 +813,11 @@ int z2z_launch_hyper_encode(z2z_ctx* c, const void* E, const z2z_encoder* enc, v
   if (u_step < 1) u_step = 1;
   if (u_step > units) u_step = units;
   const size_t R_max = (size_t)B * (size_t)u_step * M;
+  const int dffp = ffn_pitch(c, B, M, units, (int)u_step, d, dff);
   const size_t n_units_max = (size_t)B * (size_t)u_step;
   const size_t index_bytes = ((n_units_max + 1 + R_max) * sizeof(int32_t) + 255) & ~(size_t)255;
   // per row: the stream X and Y in fp32 (2 x 4 bytes x d), A, O (d), QKV (3d) and F (d_ff) in bf16
-  const size_t need = R_max * ((size_t)8 * d + ((size_t)2 * d + (size_t)3 * d + (size_t)dff) * 2) + index_bytes;
+  const size_t need = R_max * ((size_t)8 * d + ((size_t)2 * d + (size_t)3 * d + (size_t)dffp) * 2) + index_bytes;
   if (need > c->enc_ws_bytes) {
     Z2Z_TRY_GROW(s);
     if (c->enc_ws) (void)hipFree(c->enc_ws);
@@ -860,9 +870,13 @@ int z2z_launch_hyper_encode(z2z_ctx* c, const void* E, const z2z_encoder* enc, v
                          const float* gamma, const float* beta, bool* fused) -> int {
       Parts parts = {};
       *fused = false;
-      int ret = z2z_launch_linear_parts(c, in, w, R, rows_dev, d, K, false, &parts.partial, &parts.ksplit, s);
+      const z2z_linear_pitch pitch = {dffp, dff, d};
+      const bool padded = in == F && dffp != dff;
+      int ret = Z2Z_OK;
+      if (!padded) ret = z2z_launch_linear_parts(c, in, w, R, rows_dev, d, K, false, &parts.partial, &parts.ksplit, s);
       if (ret != Z2Z_OK) return ret;
-      if (parts.ksplit == 0) return z2z_launch_linear(c, in, w, bias, residual, 0, out, R, rows_dev, d, K, s, nullptr, true);
+      if (parts.ksplit == 0)
+        return z2z_launch_linear(c, in, w, bias, residual, 0, out, R, rows_dev, d, K, s, nullptr, true, padded ? &pitch : nullptr);
       parts.R = R;
       parts.bias = bias;
       parts.residual = residual;
@@ -909,7 +923,9 @@ int z2z_launch_hyper_encode(z2z_ctx* c, const void* E, const z2z_encoder* enc, v
         if (!fused)
           hipLaunchKernelGGL(enc_norm_kernel<false>, dim3(row_blocks), dim3(256), 0, s, m, nullptr, nullptr, y,
                              reinterpret_cast<uint4*>(A), lay.ln2_g, lay.ln2_b, n_units);
-        rc = z2z_launch_linear(c, A, lay.w_1, lay.b_1, nullptr, 1, F, R, rows_dev, dff, d, s);
+        const z2z_linear_pitch to_wide = {d, d, dffp};
+        rc = z2z_launch_linear(c, A, lay.w_1, lay.b_1, nullptr, 1, F, R, rows_dev, dff, d, s, nullptr, false,
+                               dffp != dff ? &to_wide : nullptr);
         if (rc != Z2Z_OK) return rc;
         rc = layer_out(F, lay.w_2, lay.b_2, y, x, dff, next ? next->ln1_g : nullptr, next ? next->ln1_b : nullptr, &fused);
         if (rc != Z2Z_OK) return rc;
@@ -936,10 +952,9 @@ int transpose_to(const void* in, void* out, int R, const int32_t* rows_dev, int 
   return z2z_launch_transpose(in, out, R, rows_dev, C, ld_in, ld_out, 1, 0, 0, s);
 }
 
-void colsum_to(const void* G, int N, int R, const int32_t* rows_dev, float* out, hipStream_t s) {
-  (void)R;
+void colsum_to(const void* G, int N, int ld, const int32_t* rows_dev, float* out, hipStream_t s) {
   hipLaunchKernelGGL(enc_colsum_kernel, dim3((N / 8 + 63) / 64, E_CS_STRIPES), dim3(256), 0, s,
-                     reinterpret_cast<const uint4*>(G), N / 8, rows_dev, out);
+                     reinterpret_cast<const uint4*>(G), N / 8, ld / 8, rows_dev, out);
 }
 
 unsigned flat_grid(size_t n) {
@@ -960,11 +975,12 @@ int z2z_launch_hyper_encode_train(z2z_ctx* c, int mode, const void* E, const z2z
   const int nl = enc->n_layers;
   const bool ffn = !enc->attention_only;
   const int dff = ffn ? enc->d_ff : 0;
-  const int wide = 3 * d > dff ? 3 * d : dff;                   // widest activation
   long long u_step = 65536 / ((long long)B * M);
   if (u_step < 1) u_step = 1;
   if (u_step > cap) u_step = cap;
   const size_t R_max = (size_t)B * (size_t)u_step * M;
+  const int dffp = ffn_pitch(c, B, M, cap, (int)u_step, d, dff);
+  const int wide = 3 * d > dffp ? 3 * d : dffp;                 // widest activation
   const size_t Rp = z2z_contraction_pitch(R_max, 128);          // contraction length of the weight-gradient products
   const size_t n_units_max = (size_t)B * (size_t)u_step;
   const size_t index_bytes = ((n_units_max + 1 + R_max) * sizeof(int32_t) + 255) & ~(size_t)255;
@@ -972,8 +988,8 @@ int z2z_launch_hyper_encode_train(z2z_ctx* c, int mode, const void* E, const z2z
   // in units of bf16 elements (an fp32 element counts as two): per layer what LayerSave names (Xin and Y fp32);
   // the last layer's output (fp32); the running gradients dX dY dN dO (d each), dQKV (3d), dF (d_ff); two
   // transposed operands [wide, Rp]; one transposed weight
-  const size_t per_layer = R_max * ((size_t)10 * d + (size_t)2 * dff);
-  const size_t elems = (size_t)nl * per_layer + R_max * ((size_t)7 * d + dff) + R_max * 2 * d + 2 * (size_t)wide * Rp +
+  const size_t per_layer = R_max * ((size_t)10 * d + (size_t)2 * dffp);
+  const size_t elems = (size_t)nl * per_layer + R_max * ((size_t)7 * d + dffp) + R_max * 2 * d + 2 * (size_t)wide * Rp +
                        (size_t)wide * d;
   const size_t nb_bytes = (R_max * sizeof(float2) + 255) & ~(size_t)255;   // mean and rstd of every row of a LayerNorm
   const size_t need = index_bytes + pos_bytes + nb_bytes + elems * 2;
@@ -1008,8 +1024,8 @@ int z2z_launch_hyper_encode_train(z2z_ctx* c, int mode, const void* E, const z2z
     sv[l].QKV = take(R_max * 3 * d);
     sv[l].O = take(R_max * d);
     sv[l].N2 = take(R_max * d);
-    sv[l].U = take(R_max * (size_t)dff);
-    sv[l].F = take(R_max * (size_t)dff);
+    sv[l].U = take(R_max * (size_t)dffp);
+    sv[l].F = take(R_max * (size_t)dffp);
   }
   float* Xout = take_f32(R_max * d);
   uint16_t* dX = take(R_max * d);
@@ -1017,7 +1033,7 @@ int z2z_launch_hyper_encode_train(z2z_ctx* c, int mode, const void* E, const z2z
   uint16_t* dN = take(R_max * d);
   uint16_t* dO = take(R_max * d);
   uint16_t* dQKV = take(R_max * 3 * d);
-  uint16_t* dF = take(R_max * (size_t)dff);
+  uint16_t* dF = take(R_max * (size_t)dffp);
   uint16_t* TA = take((size_t)wide * Rp);
   uint16_t* TB = take((size_t)wide * Rp);
   uint16_t* WT = take((size_t)wide * d);
@@ -1065,6 +1081,10 @@ int z2z_launch_hyper_encode_train(z2z_ctx* c, int mode, const void* E, const z2z
     if (rc != Z2Z_OK) return rc; \
   } while (0)
 
+  // pitches of the products into and out of the feed-forward width (the last with a transposed weight of that pitch)
+  const z2z_linear_pitch into = {d, d, dffp}, out_of = {dffp, dff, d}, out_of_t = {dffp, dffp, d};
+  const z2z_linear_pitch *to_wide = dffp != dff ? &into : nullptr, *from_wide = dffp != dff ? &out_of : nullptr,
+                         *from_wide_t = dffp != dff ? &out_of_t : nullptr;
   int pass = 0;
   for (int u0 = 0; u0 < cap; u0 += (int)u_step, ++pass) {
     m.u0 = u0;
@@ -1098,10 +1118,10 @@ int z2z_launch_hyper_encode_train(z2z_ctx* c, int mode, const void* E, const z2z
       if (ffn) {
         hipLaunchKernelGGL(enc_norm_kernel<false>, dim3(row_blocks), dim3(256), 0, s, m, nullptr, nullptr, v.Y,
                            reinterpret_cast<uint4*>(v.N2), lay.ln2_g, lay.ln2_b, n_units);
-        Z2Z_TRY_RC(z2z_launch_linear(c, v.N2, lay.w_1, lay.b_1, nullptr, 0, v.U, R, rows_dev, dff, d, s));
-        hipLaunchKernelGGL(enc_gelu_kernel, dim3(flat_grid((size_t)R * dff / 8)), dim3(256), 0, s,
-                           reinterpret_cast<const uint4*>(v.U), reinterpret_cast<uint4*>(v.F), dff / 8, rows_dev);
-        Z2Z_TRY_RC(z2z_launch_linear(c, v.F, lay.w_2, lay.b_2, v.Y, 0, next, R, rows_dev, d, dff, s, nullptr, true));
+        Z2Z_TRY_RC(z2z_launch_linear(c, v.N2, lay.w_1, lay.b_1, nullptr, 0, v.U, R, rows_dev, dff, d, s, nullptr, false, to_wide));
+        hipLaunchKernelGGL(enc_gelu_kernel, dim3(flat_grid((size_t)R * dffp / 8)), dim3(256), 0, s,
+                           reinterpret_cast<const uint4*>(v.U), reinterpret_cast<uint4*>(v.F), dffp / 8, rows_dev);
+        Z2Z_TRY_RC(z2z_launch_linear(c, v.F, lay.w_2, lay.b_2, v.Y, 0, next, R, rows_dev, d, dff, s, nullptr, true, from_wide));
       }
     }
 
@@ -1130,26 +1150,26 @@ int z2z_launch_hyper_encode_train(z2z_ctx* c, int mode, const void* E, const z2z
       const void* acc = nullptr;                     // weight gradients of later passes add to the earlier ones
       uint16_t* dy = dX;                             // gradient at Y (attention layers: the layer's output)
       if (ffn) {
-        colsum_to(dX, d, R, rows_dev, const_cast<float*>(g.b_2), s);
+        colsum_to(dX, d, d, rows_dev, const_cast<float*>(g.b_2), s);
         Z2Z_TRY_RC(transpose_to(lay.w_2, WT, d, nullptr, dff, dff, d, s));                        // [dff, d]
-        Z2Z_TRY_RC(z2z_launch_linear(c, dX, WT, nullptr, nullptr, 0, dF, R, rows_dev, dff, d, s));
+        Z2Z_TRY_RC(z2z_launch_linear(c, dX, WT, nullptr, nullptr, 0, dF, R, rows_dev, dff, d, s, nullptr, false, to_wide));
         Z2Z_TRY_RC(transpose_to(dX, TA, R, rows_dev, d, d, Rk, s));
-        Z2Z_TRY_RC(transpose_to(v.F, TB, R, rows_dev, dff, dff, Rk, s));
+        Z2Z_TRY_RC(transpose_to(v.F, TB, R, rows_dev, dff, dffp, Rk, s));
         acc = pass > 0 ? g.w_2 : nullptr;
         Z2Z_TRY_RC(z2z_launch_linear(c, TA, TB, nullptr, acc, 0, const_cast<void*>(g.w_2), d, nullptr, dff, Rk, s, rows_dev));
-        hipLaunchKernelGGL(enc_gelu_backward_kernel, dim3(flat_grid((size_t)R * dff / 8)), dim3(256), 0, s,
-                           reinterpret_cast<uint4*>(dF), reinterpret_cast<const uint4*>(v.U), dff / 8, rows_dev);
-        colsum_to(dF, dff, R, rows_dev, const_cast<float*>(g.b_1), s);
-        Z2Z_TRY_RC(transpose_to(dF, TA, R, rows_dev, dff, dff, Rk, s));
+        hipLaunchKernelGGL(enc_gelu_backward_kernel, dim3(flat_grid((size_t)R * dffp / 8)), dim3(256), 0, s,
+                           reinterpret_cast<uint4*>(dF), reinterpret_cast<const uint4*>(v.U), dffp / 8, rows_dev);
+        colsum_to(dF, dff, dffp, rows_dev, const_cast<float*>(g.b_1), s);
+        Z2Z_TRY_RC(transpose_to(dF, TA, R, rows_dev, dff, dffp, Rk, s));
         Z2Z_TRY_RC(transpose_to(v.N2, TB, R, rows_dev, d, d, Rk, s));
         acc = pass > 0 ? g.w_1 : nullptr;
         Z2Z_TRY_RC(z2z_launch_linear(c, TA, TB, nullptr, acc, 0, const_cast<void*>(g.w_1), dff, nullptr, d, Rk, s, rows_dev));
-        Z2Z_TRY_RC(transpose_to(lay.w_1, WT, dff, nullptr, d, d, dff, s));                        // [d, dff]
-        Z2Z_TRY_RC(z2z_launch_linear(c, dF, WT, nullptr, nullptr, 0, dN, R, rows_dev, d, dff, s));
+        Z2Z_TRY_RC(transpose_to(lay.w_1, WT, dff, nullptr, d, d, dffp, s));                       // [d, dffp]
+        Z2Z_TRY_RC(z2z_launch_linear(c, dF, WT, nullptr, nullptr, 0, dN, R, rows_dev, d, dff, s, nullptr, false, from_wide_t));
         norm_backward(dN, v.Y, lay.ln2_g, dX, dY, g.ln2_g, g.ln2_b);
         dy = dY;
       }
-      colsum_to(dy, d, R, rows_dev, const_cast<float*>(g.b_o), s);
+      colsum_to(dy, d, d, rows_dev, const_cast<float*>(g.b_o), s);
       Z2Z_TRY_RC(transpose_to(lay.w_o, WT, d, nullptr, d, d, d, s));
       Z2Z_TRY_RC(z2z_launch_linear(c, dy, WT, nullptr, nullptr, 0, dO, R, rows_dev, d, d, s));
       Z2Z_TRY_RC(transpose_to(dy, TA, R, rows_dev, d, d, Rk, s));
@@ -1165,7 +1185,7 @@ int z2z_launch_hyper_encode_train(z2z_ctx* c, int mode, const void* E, const z2z
         hipLaunchKernelGGL(enc_attention_backward_kernel<Z2Z_MAX_M>, dim3((unsigned)((att_waves + 3) / 4)), dim3(256), 0,
                            s, m, reinterpret_cast<const uint4*>(v.QKV), reinterpret_cast<const uint4*>(dO),
                            reinterpret_cast<uint4*>(dQKV), dh / 8, scale, groups, n_units);
-      colsum_to(dQKV, 3 * d, R, rows_dev, const_cast<float*>(g.b_qkv), s);
+      colsum_to(dQKV, 3 * d, 3 * d, rows_dev, const_cast<float*>(g.b_qkv), s);
       Z2Z_TRY_RC(transpose_to(dQKV, TA, R, rows_dev, 3 * d, 3 * d, Rk, s));
       Z2Z_TRY_RC(transpose_to(v.A, TB, R, rows_dev, d, d, Rk, s));
       acc = pass > 0 ? g.w_qkv : nullptr;

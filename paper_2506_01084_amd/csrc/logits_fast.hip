@@ -204,6 +204,9 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
   int r0, r_end, n_valid;
   const unsigned char* Wp = reinterpret_cast<const unsigned char*>(a.W);
   const size_t row_bytes = (size_t)a.d * 2;
+  // (pitches of their own: dense layers only)
+  const size_t pitch_h = MODE == 2 && a.ldh ? (size_t)a.ldh * 2 : row_bytes;
+  const size_t pitch_w = MODE == 2 && a.ldw ? (size_t)a.ldw * 2 : row_bytes;
   if (MODE == 1 || MODE == 4) {
     if ((int)blockIdx.x >= a.n_work) return;
     rt = blockIdx.x / a.n_strips;
@@ -238,7 +241,7 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
     if (r0 >= r_end) return;                       // a tile beyond the rows that exist
     n_valid = a.w_rows;
   }
-  const unsigned char* Hp = reinterpret_cast<const unsigned char*>(a.H) + (size_t)r0 * row_bytes;
+  const unsigned char* Hp = reinterpret_cast<const unsigned char*>(a.H) + (size_t)r0 * pitch_h;
   const int ks = MODE == 5 ? (int)(blockIdx.x % a.ksplit) : 0;
   if (MODE == 5) {                                   // this part's slabs start here in every row
     Wp += (size_t)ks * a.slabs_per_part * F_SLAB;
@@ -269,19 +272,19 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
   int limA = 0;                                                  // last valid vocabulary row of the tile
   // per-lane global byte offsets of the 8 row groups a wave requests (swizzled chunk folded in); rows
   // past the last valid one are clamped onto it.  B's never change, A's change with the tile.
-  auto row_offset = [&](int i, int lim) -> uint32_t {
+  auto row_offset = [&](int i, int lim, size_t pitch) -> uint32_t {
     const int row = (wave * F_PAIRS + i) * 8 + ld_row;
     const int chunk16 = ((lane & 7) ^ ((row >> 1) & 7)) * 16;
-    return (uint32_t)(min(row, lim) * (int)row_bytes + chunk16);
+    return (uint32_t)(min(row, lim) * (int)pitch + chunk16);
   };
   uint32_t voffA[F_PAIRS], voffB[F_PAIRS];
 #pragma unroll
-  for (int i = 0; i < F_PAIRS; ++i) voffB[i] = row_offset(i, limB);
+  for (int i = 0; i < F_PAIRS; ++i) voffB[i] = row_offset(i, limB, pitch_h);
   auto set_tile = [&](int vt) {
-    Wtile = Wp + (size_t)vt * FT * row_bytes;
+    Wtile = Wp + (size_t)vt * FT * pitch_w;
     limA = n_valid - 1 - vt * FT;
 #pragma unroll
-    for (int i = 0; i < F_PAIRS; ++i) voffA[i] = row_offset(i, limA);
+    for (int i = 0; i < F_PAIRS; ++i) voffA[i] = row_offset(i, limA, pitch_w);
   };
   // request the slab that follows (lslab, lvt) in the stream, if any, and advance the cursor.  A request
   // is 16 instructions per wave; issue_rows<i>() issues the pair for row group i so that the caller can
