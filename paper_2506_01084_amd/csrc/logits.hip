@@ -359,6 +359,16 @@ static int pick_strip_for(const z2z_ctx* c, long long row_tiles, int n_vt, int w
 }
 
 
+// A decode step of 5..64 sequences whose base vocabulary goes to the weight-streaming kernel, with the hyper units in a
+// launch of their own, instead of the decode kernel's base units: where its tiles of 256 weight rows give every CU one.
+// Greedy, d = 4096, V = 128256, 5 / 8 / 24 / 48 sequences: 247 -> 202, 299 -> 211, 304 -> 221, 310 -> 248 us with plain
+// sums (about 8 more with the three levels that keep their precision), 64 with full codebooks of 4096: 523 -> 508.  With 126 tiles (V = 32064, 40 sequences) it is 217 against 203; and a draw, whose
+// generator then runs in that kernel's epilogue with nothing beside it, 375 against 338 us at 64.
+static bool split_few(const z2z_ctx* c, int rows) {
+  return rows > 4 && rows <= 64 && c->opt_decode_kernel == 0 && c->opt_logits_kernel == 0 &&
+         z2z_logits_mid_tiles(c->cfg.V) >= 256 && z2z_logits_mid_ok(c, rows);
+}
+
 int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t rows_per_seq, const void* W_base,
                                const void* W_hyper, int32_t* argmax, float* mx, float* lse, float* logits,
                                hipStream_t s, bool use_static) {
@@ -381,7 +391,7 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
   // Its base units serve 64 rows per pass over W_base, each pass at about the cost of the first; from the second
   // pass on the tile kernel takes the base vocabulary (all rows at once) and only the hyper units run here
   const bool decode_step = rows_per_seq == 1 && c->decode_ready && c->opt_decode_kernel != 1;
-  const bool decode_split = decode_step && fast_ok && rows > 64 && c->opt_logits_kernel != 1;
+  const bool decode_split = decode_step && fast_ok && (rows > 64 || split_few(c, rows)) && c->opt_logits_kernel != 1;
   // a few rows per sequence (2..64: a verification step over drafted codes, a short chunk): every sequence's
   // W_hyper meets only its own rows, so the hyper part is bandwidth-bound like the decode step's; it goes to
   // that kernel's matrix-core units (one pass over each W_hyper), the base vocabulary to the tile kernel
@@ -417,16 +427,11 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
   const int strip_h = pick_strip((long long)c->cfg.B * ((rows_per_seq + tile - 1) / tile), hyp_vt);
   const int base_strips = (base_vt + strip_b - 1) / strip_b;
   int hyp_strips = cap > 0 ? (hyp_vt + strip_h - 1) / strip_h : 0;
-  if (decode_split) {
-    int base_columns, hyper_columns;
-    z2z_logits_decode_units(&base_columns, &hyper_columns);
-    hyp_strips = (cap + hyper_columns - 1) / hyper_columns;
-  }
   int seq_unit = 0;
-  if (seq_split) {
-    seq_unit = z2z_logits_decode_seq_unit(c);
+  if (decode_split || seq_split) {
+    seq_unit = seq_split ? z2z_logits_decode_seq_unit(c) : z2z_logits_decode_hyper_unit(c);
     // (the static array may be too small for the parts of the smaller units)
-    if (use_static && (size_t)(base_strips + (cap + seq_unit - 1) / seq_unit) * rows > parts.capacity) seq_unit = 256;
+    if (use_static && (size_t)(base_strips + (cap + seq_unit - 1) / seq_unit) * rows > parts.capacity) seq_unit = seq_split ? 256 : 512;
     hyp_strips = (cap + seq_unit - 1) / seq_unit;
   }
   const int n_parts = base_strips + hyp_strips;
@@ -515,9 +520,8 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     const int base_vt = (c->cfg.V + 255) / 256;
     const int strip_b = mid_base ? 1 : pick_strip_for(c, (rows + 255) / 256, base_vt);
     const int base_strips = (base_vt + strip_b - 1) / strip_b;
-    int base_columns, hyper_columns;
-    z2z_logits_decode_units(&base_columns, &hyper_columns);
-    n_parts = base_strips + (c->cfg.cap + hyper_columns - 1) / hyper_columns;
+    const int unit = z2z_logits_decode_hyper_unit(c);
+    n_parts = base_strips + (c->cfg.cap + unit - 1) / unit;
     rc = ensure_scratch(c, (size_t)n_parts * rows, s);
     if (rc != Z2Z_OK) return rc;
     rc = ensure_sample_scratch(c, (size_t)n_parts * rows, s);
@@ -549,7 +553,7 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     if (rc != Z2Z_OK) return rc;
     if (c->cfg.cap > 0) {
       int np = 0;
-      rc = z2z_launch_logits_decode(c, H, W_base, W_hyper, &np, false, &sp, nullptr, s, base_strips);
+      rc = z2z_launch_logits_decode(c, H, W_base, W_hyper, &np, false, &sp, nullptr, s, base_strips, nullptr, 1, unit);
       if (rc != Z2Z_OK) return rc;
     }
     hipLaunchKernelGGL(sample_combine_kernel, dim3(rows), dim3(256), 0, s, c->part_m, c->part_s, c->part_v,

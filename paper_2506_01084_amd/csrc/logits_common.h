@@ -584,7 +584,9 @@ struct z2z_sample_params {
 int z2z_launch_logits_decode(z2z_ctx* c, const void* H, const void* W_base, const void* W_hyper, int* n_parts,
                              bool timed, const z2z_sample_params* sample, float* logits, hipStream_t s,
                              int hyper_only_base_parts = -1, const z2z_parts* parts = nullptr, int rows_per_seq = 1,
-                             int seq_unit = 256);
+                             int seq_unit = 512);
+// (hyper_only_base_parts >= 0, one row per sequence: seq_unit weight rows per hyper unit, z2z_logits_decode_hyper_unit)
+int z2z_logits_decode_hyper_unit(const z2z_ctx* c);
 // rows_per_seq in 2..64 (with hyper_only_base_parts >= 0): the hyper part alone, one workgroup per sequence and
 // seq_unit (64, 128 or 256) rows of its W_hyper; parts per row then: base parts + ceil(cap / seq_unit)
 int z2z_logits_decode_seq_unit(const z2z_ctx* c);

@@ -70,7 +70,8 @@ struct DecodeArgs {
   int32_t B, V, cap, d;
   int32_t n_base_units;   // ceil(V / 256)
   int32_t n_groups;       // ceil(B / 64) groups of hidden rows for the base part
-  int32_t units_per_seq;  // ceil(cap / 512)
+  int32_t unit;           // weight rows per hyper unit: 512, or fewer where the hyper units run alone
+  int32_t units_per_seq;  // ceil(cap / unit)
   int32_t n_parts;        // partials per hidden row
   float* part_m;          // [B, n_parts]
   float* part_s;
@@ -457,8 +458,8 @@ __device__ __forceinline__ void hyper_unit(const DecodeArgs& a, int b, int u, un
   Triple* xch = reinterpret_cast<Triple*>(lds);
   Draw* xdr = reinterpret_cast<Draw*>(xch + 8);
   const int C = min(max(a.size[b], 0), a.cap);
-  const int r0 = u * D_UNIT;
-  const int r1 = min(C, r0 + D_UNIT);
+  const int r0 = u * a.unit;
+  const int r1 = min(C, r0 + a.unit);
   Triple t = empty_triple();
   Draw dr = empty_draw();
   if (r0 < r1) {
@@ -643,6 +644,14 @@ __global__ void __launch_bounds__(D_THREADS) logits_decode_kernel(DecodeArgs a) 
   }
 }
 
+// The hyper units alone (the base vocabulary is another launch's): a kernel of its own, since the base units' registers
+// and LDS would leave one workgroup per CU where two fit.
+template <int MODE>
+__global__ void __launch_bounds__(D_THREADS) logits_decode_hyper_kernel(DecodeArgs a) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  hyper_unit<MODE>(a, blockIdx.x / a.units_per_seq, blockIdx.x % a.units_per_seq, lds);
+}
+
 // The per-sequence part of a call with R = 2..4 hidden rows per sequence (R = a.rows_per_seq) on dot-product units:
 // workgroup (b, u) takes rows [seq_unit * u, seq_unit * (u + 1)) of W_hyper[b], one part each (the layout of the
 // matrix-core units that take more rows per sequence); plain logits only.
@@ -729,7 +738,8 @@ int z2z_launch_logits_decode(z2z_ctx* c, const void* H, const void* W_base, cons
   a.d = c->cfg.d;
   a.n_base_units = (a.V + D_BASE_UNIT - 1) / D_BASE_UNIT;
   a.n_groups = (a.B + 63) / 64;
-  a.units_per_seq = (a.cap + D_UNIT - 1) / D_UNIT;
+  a.unit = hyper_only_base_parts >= 0 && rows_per_seq == 1 ? seq_unit : D_UNIT;
+  a.units_per_seq = (a.cap + a.unit - 1) / a.unit;
   a.part_m = parts ? parts->m : c->part_m;
   a.part_s = parts ? parts->s : c->part_s;
   a.part_i = parts ? parts->i : c->part_i;
@@ -782,7 +792,14 @@ int z2z_launch_logits_decode(z2z_ctx* c, const void* H, const void* W_base, cons
     return Z2Z_OK;
   }
   if (timed) Z2Z_HIP_TRY(hipEventRecord(c->ev_start[c->n_timed], s));
-  if (hyper_only_base_parts < 0 && a.B <= D_DOT_BATCH) {
+  if (hyper_only_base_parts >= 0) {
+    if (logits)
+      hipLaunchKernelGGL(logits_decode_hyper_kernel<2>, dim3(grid), dim3(D_THREADS), D_DOT_LDS, s, a);
+    else if (sample)
+      hipLaunchKernelGGL(logits_decode_hyper_kernel<1>, dim3(grid), dim3(D_THREADS), D_DOT_LDS, s, a);
+    else
+      hipLaunchKernelGGL(logits_decode_hyper_kernel<0>, dim3(grid), dim3(D_THREADS), D_DOT_LDS, s, a);
+  } else if (a.B <= D_DOT_BATCH) {
     // up to 4 sequences: their hidden rows fit in registers, so the base vocabulary streams through dot-product
     // units too (whole rows, no hand-over through LDS)
     const int mode = logits ? 2 : (sample ? 1 : 0);
@@ -874,6 +891,13 @@ int z2z_logits_decode_parts(const z2z_ctx* c) {
 int z2z_logits_decode_seq_unit(const z2z_ctx* c) {
   int unit = D_BASE_UNIT;
   while (unit > 64 && (long long)c->cfg.B * ((c->cfg.cap + unit - 1) / unit) < 256) unit >>= 1;
+  return unit;
+}
+
+// The same for one hidden row per sequence where the hyper units run alone, two workgroups per CU.
+int z2z_logits_decode_hyper_unit(const z2z_ctx* c) {
+  int unit = D_UNIT;
+  while (unit > 64 && (long long)c->cfg.B * ((c->cfg.cap + unit - 1) / unit) < 512) unit >>= 1;
   return unit;
 }
 

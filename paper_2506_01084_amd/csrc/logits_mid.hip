@@ -39,6 +39,7 @@ constexpr int M_SLAB = 128;               // bytes per row per K slab (64 bf16)
 constexpr int M_STAGE = M_HT * M_SLAB;    // the hidden rows of one slab: 24 KiB
 constexpr int M_NSTAGE = 3;
 constexpr int M_LDS = M_NSTAGE * M_STAGE;
+constexpr int M_LDS_LEVELS = M_LDS + 32 * M_THREADS * 4;   // decode steps: the third level of their sums
 // weight register buffers per instance (what fits beside 16 NJV accumulators without spilling inside the K loop)
 #ifndef M_NBUF
 #define M_NBUF 6                          // up to 128 hidden rows
@@ -147,6 +148,40 @@ __global__ void __launch_bounds__(M_THREADS) logits_mid_kernel(LogitsArgs a) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[0][j][v] = 0.f;
 
+  // SMODE 4, a decode step of up to 64 sequences: the logits are added up in three levels: two slabs (8 MFMAs) in the accumulators, two rounds of the
+  // buffers in registers, those in LDS (each thread its own words).  One accumulator over all of K rounds every step at the
+  // size of the whole sum: d = 4096, relative error of the maxima 2.7e-7 to 3.3e-7; in two levels 5.7e-8 to 8.0e-8, in
+  // three 4.4e-8 to 5.2e-8; the decode kernel's base units, which such a step ran on before and which add up 128 elements at a
+  // time, 4.5e-8 to 4.9e-8.  (It costs 8 us of 216 in a call with a few rows per sequence, which keep the one accumulator.)
+  constexpr bool LEVELS = SMODE == 4;
+  float* lds_total = reinterpret_cast<float*>(lds + M_LDS) + tid;      // [16 NJV][M_THREADS]
+  f32x16 total[NJV];
+#pragma unroll
+  for (int j = 0; j < NJV; ++j)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      total[j][v] = 0.f;
+      if (LEVELS) lds_total[(j * 16 + v) * M_THREADS] = 0.f;
+    }
+  auto third_level = [&]() {
+#pragma unroll
+    for (int j = 0; j < NJV; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        lds_total[(j * 16 + v) * M_THREADS] += total[j][v];
+        total[j][v] = 0.f;
+      }
+  };
+  auto next_level = [&]() {
+#pragma unroll
+    for (int j = 0; j < NJV; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        total[j][v] += acc[0][j][v];
+        acc[0][j][v] = 0.f;
+      }
+  };
+
   auto compute = [&](const uint4 (&w)[4], int stage) {
     const unsigned char* Bs = lds + stage * M_STAGE + offB;
 #pragma unroll
@@ -188,6 +223,7 @@ __global__ void __launch_bounds__(M_THREADS) logits_mid_kernel(LogitsArgs a) {
   // everything in flight is awaited: a handful of steps per tile.)
   auto finish = [&](int u, bool in_loop) {
     compute(w[u], stage);
+    if (LEVELS && (u & 1)) next_level();
     if (in_loop)
       wait_loads<HL + 8>();
     else
@@ -212,6 +248,7 @@ __global__ void __launch_bounds__(M_THREADS) logits_mid_kernel(LogitsArgs a) {
       requests(u, s0 + u);
       finish(u, true);
     }
+    if (LEVELS && ((s0 / NBUF) & 1)) third_level();
   }
 #pragma unroll
   for (int u = 0; u < NBUF - 1; ++u)
@@ -222,6 +259,15 @@ __global__ void __launch_bounds__(M_THREADS) logits_mid_kernel(LogitsArgs a) {
   // the requests past the end of the stream (slabs clamped onto the last one) must land before the stages are reused
   wait_loads<0>();
   __syncthreads();
+
+  if (LEVELS) {
+    next_level();
+    third_level();
+#pragma unroll
+    for (int j = 0; j < NJV; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[0][j][v] = lds_total[(j * 16 + v) * M_THREADS];
+  }
 
   // ---- fold the tile, then one triple (and draw) per hidden row --------------------------------------------
   Triple run[NJV];
@@ -322,7 +368,9 @@ int z2z_launch_logits_mid(z2z_ctx* c, LogitsArgs a, const void* W, int w_rows, i
     else
       hipLaunchKernelGGL((logits_mid_kernel<6, M_NBUF_6, 2>), grid, block, M_LDS, s, a);
   } else {
-    if (blocks == 2)
+    if (blocks == 2 && a.rows_per_seq == 1)
+      hipLaunchKernelGGL((logits_mid_kernel<2, M_NBUF, 4>), grid, block, M_LDS_LEVELS, s, a);
+    else if (blocks == 2)
       hipLaunchKernelGGL((logits_mid_kernel<2, M_NBUF, 0>), grid, block, M_LDS, s, a);
     else if (blocks == 4)
       hipLaunchKernelGGL((logits_mid_kernel<4, M_NBUF, 0>), grid, block, M_LDS, s, a);
@@ -389,8 +437,9 @@ int z2z_launch_linear_mid(z2z_ctx* c, const void* A, const void* W, int R, const
 int z2z_logits_mid_tiles(int w_rows) { return (w_rows + M_WT - 1) / M_WT; }
 
 int z2z_logits_mid_prepare(z2z_ctx* c) {
-  if (c->lds_limit < M_LDS) return Z2Z_EUNSUPPORTED;
-  const void* kernels[9] = {reinterpret_cast<const void*>(logits_mid_kernel<2, M_NBUF, 3>),
+  if (c->lds_limit < M_LDS_LEVELS) return Z2Z_EUNSUPPORTED;
+  const void* kernels[10] = {reinterpret_cast<const void*>(logits_mid_kernel<2, M_NBUF, 4>),
+                            reinterpret_cast<const void*>(logits_mid_kernel<2, M_NBUF, 3>),
                             reinterpret_cast<const void*>(logits_mid_kernel<4, M_NBUF, 3>),
                             reinterpret_cast<const void*>(logits_mid_kernel<2, M_NBUF, 0>),
                             reinterpret_cast<const void*>(logits_mid_kernel<4, M_NBUF, 0>),
@@ -399,7 +448,7 @@ int z2z_logits_mid_prepare(z2z_ctx* c) {
                             reinterpret_cast<const void*>(logits_mid_kernel<6, M_NBUF_6, 0>),
                             reinterpret_cast<const void*>(logits_mid_kernel<6, M_NBUF_6, 1>),
                             reinterpret_cast<const void*>(logits_mid_kernel<6, M_NBUF_6, 2>)};
-  for (int k = 0; k < 9; ++k)
-    Z2Z_HIP_TRY(hipFuncSetAttribute(kernels[k], hipFuncAttributeMaxDynamicSharedMemorySize, M_LDS));
+  for (int k = 0; k < 10; ++k)
+    Z2Z_HIP_TRY(hipFuncSetAttribute(kernels[k], hipFuncAttributeMaxDynamicSharedMemorySize, M_LDS_LEVELS));
   return Z2Z_OK;
 }

@@ -1,0 +1,59 @@
+"""GPU parity of greedy decode steps of 5..64 sequences over a vocabulary of at least 65281 columns: the base part on the
+weight-streaming kernel (sums in three levels), the hyper units alone, in units of 64..512 rows.  Section 2.3, steps 7-9.
+
+Bound of the largest logit: fp32 sums of d products, 8 at most in one run of the accumulators: 1e-5 of its size."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2506_01084_amd import workloads as wl
+
+from helpers import check_logits_rows, gpu_encode, oracle_encode_batch, torch_storage
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,V,d,cap", [
+    (5, 65281, 128, 40),       # two slabs: fewer than buffers; one unit per sequence
+    (9, 65290, 768, 700),      # twelve slabs: two rounds of the buffers, one flush of the second level
+    (33, 66000, 1664, 100),    # 26 slabs: four rounds and two steps
+    (64, 65281, 256, 520),     # every row valid; nine units of 64 per sequence
+    (4, 65281, 128, 40),       # (four sequences stay on the dot-product units)
+    (40, 65000, 128, 40),      # (254 tiles stay on the decode kernel)
+])
+def test_split_step(B, V, d, cap):
+    import torch
+
+    from paper_2506_01084_amd import api
+
+    M, N = 3, 900
+    cfg = dict(name="split", B=B, N=N, V=V, d=d, dtype="bf16", M=M, cap=cap, zipf_s=1.4, copy_frac=0.5, span=(2, 7),
+               mode="motif", pool="mean", seed=9100 + B)
+    print(f"[case] step of {B} sequences, V={V} d={d} cap={cap}", flush=True)
+    tokens = wl.make_tokens(cfg)
+    lens = np.full(B, N, dtype=np.int32)
+    lens[1] = 0
+    E, H = wl.make_embeddings(cfg), wl.make_hidden(cfg, B)
+    ctx = api.Context(B=B, V=V, M=M, cap=cap, d=d, dtype="bf16", pool="mean")
+    gpu_encode(ctx, tokens, lens)
+    ref = oracle_encode_batch(tokens, lens, V, M, cap)
+    d_E = torch_storage(E, "bf16")
+    d_W = torch.empty((B, cap, d), dtype=torch.bfloat16, device="cuda")
+    ctx.hyper_embed(d_E, d_W)
+    for b in range(B):
+        d_W[b, len(ref[b][1]):] = 900.0
+    am = torch.full((B,), -5, dtype=torch.int32, device="cuda")
+    mx = torch.full((B,), 777.0, device="cuda")
+    lse = torch.full((B,), 777.0, device="cuda")
+    before = ctx.read_launches()
+    ctx.extended_logits(torch_storage(H, "bf16"), 1, d_E, d_W, am, mx, lse, None)
+    torch.cuda.synchronize()
+    after = ctx.read_launches()
+    assert after["mid"] - before["mid"] == (1 if B > 4 and V > 65280 else 0)
+    am, mx, lse = am.cpu().numpy(), mx.cpu().numpy(), lse.cpu().numpy()
+    for b in range(B):
+        Wr = oracle.hyper_embed(E, "bf16", ref[b][1], cap, "mean")
+        want = oracle.extended_logits(H[b:b + 1], E, Wr, len(ref[b][1]), "bf16")
+        check_logits_rows(want, am[b:b + 1], mx[b:b + 1], lse[b:b + 1], None)
+        assert abs(mx[b] - want["max"][0]) <= 1e-5 * abs(want["max"][0])
+    ctx.close()
