@@ -369,6 +369,12 @@ static bool split_few(const z2z_ctx* c, int rows) {
          z2z_logits_mid_tiles(c->cfg.V) >= 256 && z2z_logits_mid_ok(c, rows);
 }
 
+// Parts per row that any kind of step may leave (hyper units of 64 rows): every step sizes the scratch for all of them,
+// so that a greedy one can be captured behind an eager draw at the same shape and the other way round.
+static size_t step_parts(const z2z_ctx* c) {
+  return (size_t)(c->cfg.V + 255) / 256 + (size_t)(c->cfg.cap + 63) / 64;
+}
+
 int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t rows_per_seq, const void* W_base,
                                const void* W_hyper, int32_t* argmax, float* mx, float* lse, float* logits,
                                hipStream_t s, bool use_static) {
@@ -399,7 +405,7 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
                          c->decode_ready && c->opt_decode_kernel != 1 && c->opt_logits_kernel != 1;
   if (decode_step && !decode_split) {
     int n_parts = z2z_logits_decode_parts(c);
-    int rc = reserve((size_t)n_parts * rows);
+    int rc = reserve((use_static ? (size_t)n_parts : step_parts(c)) * rows);
     if (rc != Z2Z_OK) return rc;
     rc = z2z_launch_logits_decode(c, H, W_base, W_hyper, &n_parts, timed, nullptr, logits, s, -1, &parts);
     if (rc != Z2Z_OK) return rc;
@@ -433,6 +439,10 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     // (the static array may be too small for the parts of the smaller units)
     if (use_static && (size_t)(base_strips + (cap + seq_unit - 1) / seq_unit) * rows > parts.capacity) seq_unit = seq_split ? 256 : 512;
     hyp_strips = (cap + seq_unit - 1) / seq_unit;
+  }
+  if (decode_split && !use_static) {
+    const int rc = reserve(step_parts(c) * rows);
+    if (rc != Z2Z_OK) return rc;
   }
   const int n_parts = base_strips + hyp_strips;
   int rc = reserve((size_t)n_parts * rows);
@@ -503,7 +513,7 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
   // built for the generation step: one hidden row per sequence, the bandwidth-bound kernel
   if (rows_per_seq != 1 || !c->decode_ready) return Z2Z_EUNSUPPORTED;
   int n_parts = z2z_logits_decode_parts(c);
-  int rc = ensure_scratch(c, (size_t)n_parts * rows, s);
+  int rc = ensure_scratch(c, step_parts(c) * rows, s);
   if (rc != Z2Z_OK) return rc;
   z2z_sample_params sp;
   sp.temperature = temperature;

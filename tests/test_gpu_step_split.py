@@ -57,3 +57,32 @@ def test_split_step(B, V, d, cap):
         check_logits_rows(want, am[b:b + 1], mx[b:b + 1], lse[b:b + 1], None)
         assert abs(mx[b] - want["max"][0]) <= 1e-5 * abs(want["max"][0])
     ctx.close()
+
+
+def test_greedy_step_is_captured_behind_an_eager_draw():
+    """(the draw's kernels leave fewer parts per row; every kind of step sizes the scratch for all of them)"""
+    import torch
+
+    from paper_2506_01084_amd import api
+
+    B, V, d, cap = 6, 65281, 128, 300
+    ctx = api.Context(B=B, V=V, M=3, cap=cap, d=d, dtype="bf16", pool="mean")
+    ctx.reset()
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    E = (torch.randn((V, d), generator=gen, device="cuda") * 0.1).bfloat16()
+    W = torch.zeros((B, cap, d), dtype=torch.bfloat16, device="cuda")
+    H = torch.randn((B, d), generator=gen, device="cuda").bfloat16()
+    token = torch.zeros(B, dtype=torch.int32, device="cuda")
+    am, mx, lse, lp = torch.zeros_like(token), *(torch.zeros(B, device="cuda") for _ in range(3))
+    ctx.extended_sample(H, 1, E, W, 0.8, 1, 2, token, lp)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ctx.extended_logits(H, 1, E, W, am, mx, lse)
+    want = (H.float() @ E.float().t()).max(1)
+    for _ in range(3):
+        am.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(am.long(), want.indices) and torch.allclose(mx, want.values, rtol=1e-4)
+    ctx.close()
