@@ -422,7 +422,7 @@ def run_decode_workload(args, torch, api, wl):
                 sample_topk50_topp09_frac=bytes_step / (filtered_us * 1e-6) / 1e9 / PEAK_HBM_GBS,
                 learned_encoder_frac=bytes_step / (learned_us * 1e-6) / 1e9 / PEAK_HBM_GBS, algorithmic_bytes=bytes_step, achieved_GBs=gbs,
                 peak_GBs=PEAK_HBM_GBS, frac=gbs / PEAK_HBM_GBS, mean_codebook_size=float(sizes.mean()),
-                roofline={"bound": "hbm", "kernel": "logits_decode_kernel (64 rows, config 3)", "achieved": k_gbs,
+                roofline={"bound": "hbm", "kernel": "logits_mid_kernel + logits_decode_hyper_kernel (64 rows, config 3)", "achieved": k_gbs,
                           "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": k_gbs / PEAK_HBM_GBS,
                           "traffic": TRAFFIC_BYTES.get("logits_decode_kernel@c3"), "avg_kernel_us": k_us,
                           "bytes_per_launch": bytes_step})

@@ -487,7 +487,7 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
   if (mid_base) {
     if (timed) Z2Z_HIP_TRY(hipEventRecord(c->ev_start[c->n_timed], s));
     rc = z2z_launch_logits_mid(c, a, W_base, V, 0, s);
-    if (timed) {
+    if (timed && !decode_split) {
       Z2Z_HIP_TRY(hipEventRecord(c->ev_stop[c->n_timed], s));
       c->n_timed++;
     }
@@ -503,6 +503,10 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
   } else if (cap > 0) {
     rc = z2z_launch_logits_part(c, true, a, W_hyper, cap, V, base_strips, strip_h, rows, rows_per_seq, &ns, false, s);
     if (rc != Z2Z_OK) return rc;
+  }
+  if (timed && mid_base && decode_split) {        // a step's two launches are timed together
+    Z2Z_HIP_TRY(hipEventRecord(c->ev_stop[c->n_timed], s));
+    c->n_timed++;
   }
   return launch_combine(parts, n_parts, rows, argmax, mx, lse, s);
 }
