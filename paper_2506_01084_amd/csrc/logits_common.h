@@ -545,11 +545,20 @@ int z2z_launch_transpose(const void* in, void* out, int R, const int32_t* rows_d
                          int batch, size_t in_batch, size_t out_batch, hipStream_t s);
 // Row pitch (and contraction length, the padding holds zeros) of transposed operands whose contraction runs over n
 // rows: a multiple of `align`, and no multiple of 4 KiB -- rows a power of two apart put the slabs that all
-// workgroups read at one time on a few memory channels.
-inline size_t z2z_contraction_pitch(size_t n, size_t align) {
+// workgroups read at one time on a few memory channels.  One `align` of padding, so that the pitch never falls as n grows:
+// a buffer laid out for the largest n of a call holds every smaller one (a pass's last and shortest chunk).
+constexpr size_t z2z_contraction_pitch(size_t n, size_t align) {
   const size_t p = (n + align - 1) / align * align;
-  return p % 2048 ? p : p + 128;
+  return p % 2048 ? p : p + align;
 }
+constexpr bool z2z_contraction_pitch_grows(size_t align) {
+  for (size_t n = 1; n < 3 * 2048; ++n) {            // (what happens about one multiple of 2048 happens about all)
+    const size_t p = z2z_contraction_pitch(n, align);
+    if (p < n || p % align || p % 2048 == 0 || p > z2z_contraction_pitch(n + 1, align)) return false;
+  }
+  return true;
+}
+static_assert(z2z_contraction_pitch_grows(64) && z2z_contraction_pitch_grows(128), "a shorter chunk would not fit");
 struct z2z_linear_pitch {
   int a, w, out;           // row pitches of A, W and the output (a residual has the output's)
 };

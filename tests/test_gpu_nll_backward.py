@@ -201,3 +201,46 @@ def test_edge_cases_no_hypertokens_no_targets_and_odd_row_counts():
         ctx.extended_nll_backward(z(4, 64), 4, z(100, 64), z(1, 8, 64), torch.zeros(4, dtype=torch.int32, device="cuda"),
                                   z(4), None, z(4, 64), z(100, 64), z(1, 8, 64))
     ctx.close()
+
+
+@pytest.mark.parametrize("cap", [40, 0])
+def test_last_chunk_whose_rows_are_a_multiple_of_2048(cap):
+    """33 + 32 sequences of 64 rows: chunks of 2112 and of 2048 rows, the shorter one with the padded pitch, in a work
+    space that is laid out for the longer one."""
+    import torch
+    from paper_2506_01084_amd import api
+
+    B, N, V, d, M = 65, 64, 500, 64, 3
+    cfg = wl.scaled(wl.CONFIGS["c2"], B=B, N=N, V=V, d=d, M=M, cap=cap, zipf_s=1.3, seed=77)
+    print(f"[case] nll backward, last chunk of 2048 rows, cap={cap}", flush=True)
+    if cap:
+        ctx, ref, E, H, w, targets, grad, d_E, d_W, d_H, d_t, lse = _setup(cfg, np.full(B, N, dtype=np.int32))
+    else:
+        E, H = wl.make_embeddings(cfg), wl.make_hidden(cfg, B * N)
+        rng = np.random.default_rng(3)
+        targets, grad = rng.integers(0, V, size=(B, N)).astype(np.int32), rng.uniform(0.25, 2.0, B * N).astype(np.float32)
+        ref = [(None, [])] * B
+        ctx = api.Context(B=B, V=V, M=M, cap=0, d=d, dtype="bf16")
+        ctx.reset()
+        d_E, d_H = torch_storage(E, "bf16"), torch_storage(H, "bf16")
+        d_W = torch.zeros((B, 0, d), dtype=torch.bfloat16, device="cuda")
+        d_t = torch.from_numpy(targets.reshape(-1)).cuda()
+        lse = torch.empty(B * N, dtype=torch.float32, device="cuda")
+        ctx.extended_nll(d_H, N, d_E, d_W, d_t, torch.empty_like(lse), lse)
+    dH = torch.full((B * N, d), 9.0, dtype=torch.bfloat16, device="cuda")
+    dWb = torch.full((V, d), 9.0, dtype=torch.bfloat16, device="cuda")
+    dWh = torch.full((B, cap, d), 9.0, dtype=torch.bfloat16, device="cuda")
+    ctx.set_option(api.OPT_BACKWARD_CHUNK, 33)
+    ctx.extended_nll_backward(d_H, N, d_E, d_W, d_t, lse, torch.from_numpy(grad).cuda(), dH, dWb, dWh)
+    torch.cuda.synchronize()
+    dH_h, dWb_h, dWh_h, W_h = (storage_to_host(t, "bf16") for t in (dH, dWb, dWh, d_W))
+    want_dWb = np.zeros((V, d))
+    for b in range(B):
+        sl = slice(b * N, (b + 1) * N)
+        r = oracle.extended_nll_backward(H[sl], E, W_h[b], len(ref[b][1]), "bf16", targets[b], grad[sl])
+        _close(dH_h[sl], r["dH"], f"dH seq {b}")
+        if cap:
+            _close(dWh_h[b], r["dW_hyper"], f"dW_hyper seq {b}")
+        want_dWb += r["dW_base"]
+    _close(dWb_h, want_dWb, "dW_base")
+    ctx.close()
