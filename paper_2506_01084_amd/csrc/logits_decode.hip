@@ -618,6 +618,45 @@ __device__ __forceinline__ void dot_unit(const DecodeArgs& a, const uint4* W, in
 
 constexpr size_t D_DOT_LDS = 8 * 4 * (sizeof(Triple) + sizeof(Draw));
 
+// Workgroup id -> (sequence, unit) of the per-sequence part in a launch of its own.  Ids go round-robin over the 8 XCDs.
+// Unit by unit over all sequences, whatever the codebooks hold: units that have rows take consecutive ids, so every XCD has
+// its share, and the empty ones come last.  (Sequence by sequence, with a multiple of 8 units each, a quarter of every
+// codebook filled is work for two XCDs.)  A sequence's own units, too, are to lie on all XCDs, since histories differ:
+// with an even number of sequences they shift by one per unit.  Greedy steps, d = 4096, V = 128256, histories of 330 tokens
+// (about 250 entries): 103 sequences at cap 2048 402 -> 260 us, 64 305 -> 244; 24 at cap 4096, 660 tokens, 258 -> 222; 8
+// rows for each of 24 sequences 335 -> 303; full codebooks level (64 x 4096 entries 508 and 511).
+struct SeqUnit {
+  int b, u;
+};
+__host__ __device__ constexpr SeqUnit seq_unit_of(int id, int B) {
+  const int u = id / B, j = id - u * B;
+  return SeqUnit{B & 1 ? j : (j + u) % B, u};
+}
+// Host check of the order: every (sequence, unit) once, and for any fill of the codebooks (the first k units of all
+// sequences, or all units of the first k sequences) no XCD has more than `slack` units beyond an eighth of them.
+constexpr bool seq_units_spread(int B, int units, int slack) {
+  bool seen[64 * 16] = {};
+  for (int id = 0; id < B * units; ++id) {
+    const SeqUnit q = seq_unit_of(id, B);
+    if (q.b < 0 || q.b >= B || q.u < 0 || q.u >= units || seen[q.b * units + q.u]) return false;
+    seen[q.b * units + q.u] = true;
+  }
+  for (int by_unit = 0; by_unit < 2; ++by_unit)
+    for (int k = 1; k <= (by_unit ? units : B); ++k) {
+      int load[8] = {};
+      for (int id = 0; id < B * units; ++id) {
+        const SeqUnit q = seq_unit_of(id, B);
+        if ((by_unit ? q.u : q.b) < k) ++load[id & 7];
+      }
+      for (int x = 0; x < 8; ++x)
+        if (load[x] * 8 > k * (by_unit ? B : units) + 8 * slack) return false;
+    }
+  return true;
+}
+static_assert(seq_units_spread(1, 16, 2) && seq_units_spread(3, 16, 2) && seq_units_spread(8, 16, 2), "units crowd onto few XCDs");
+static_assert(seq_units_spread(13, 8, 2) && seq_units_spread(16, 8, 2), "units crowd onto few XCDs");
+static_assert(seq_units_spread(24, 8, 2), "units crowd onto few XCDs");
+
 template <int MODE>
 __global__ void __launch_bounds__(D_THREADS) logits_decode_kernel(DecodeArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];
@@ -626,7 +665,8 @@ __global__ void __launch_bounds__(D_THREADS) logits_decode_kernel(DecodeArgs a) 
   const int n_hyper = a.B * a.units_per_seq;
   const int bid = blockIdx.x;
   if (MODE == 4) {
-    base_unit<MODE>(a, bid % a.seq_units, bid / a.seq_units, 0, lds);
+    const SeqUnit q = seq_unit_of(bid, a.B);
+    base_unit<MODE>(a, q.u, q.b, 0, lds);
   } else if (bid < n_hyper) {
     hyper_unit<MODE>(a, bid / a.units_per_seq, bid % a.units_per_seq, lds);
   } else {
@@ -649,7 +689,8 @@ __global__ void __launch_bounds__(D_THREADS) logits_decode_kernel(DecodeArgs a) 
 template <int MODE>
 __global__ void __launch_bounds__(D_THREADS) logits_decode_hyper_kernel(DecodeArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];
-  hyper_unit<MODE>(a, blockIdx.x / a.units_per_seq, blockIdx.x % a.units_per_seq, lds);
+  const SeqUnit q = seq_unit_of(blockIdx.x, a.B);
+  hyper_unit<MODE>(a, q.b, q.u, lds);
 }
 
 // The per-sequence part of a call with R = 2..4 hidden rows per sequence (R = a.rows_per_seq) on dot-product units:
@@ -658,7 +699,8 @@ __global__ void __launch_bounds__(D_THREADS) logits_decode_hyper_kernel(DecodeAr
 template <int R>
 __global__ void __launch_bounds__(D_THREADS) logits_decode_rows_kernel(DecodeArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];
-  const int b = blockIdx.x / a.seq_units, u = blockIdx.x % a.seq_units;
+  const SeqUnit q = seq_unit_of(blockIdx.x, a.B);
+  const int b = q.b, u = q.u;
   const int C = min(max(a.size[b], 0), a.cap);
   dot_unit<R, 0>(a, a.W_hyper + (size_t)b * a.cap * (a.d >> 3), b * R, a.V, u * a.seq_unit, min(C, (u + 1) * a.seq_unit),
                  a.n_base_units + u, lds);
