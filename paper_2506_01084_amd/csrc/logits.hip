@@ -360,13 +360,25 @@ static int pick_strip_for(const z2z_ctx* c, long long row_tiles, int n_vt, int w
 
 
 // A decode step of 5..64 sequences whose base vocabulary goes to the weight-streaming kernel, with the hyper units in a
-// launch of their own, instead of the decode kernel's base units: where its tiles of 256 weight rows give every CU one.
-// Greedy, d = 4096, V = 128256, 5 / 8 / 24 / 48 sequences: 247 -> 202, 299 -> 211, 304 -> 221, 310 -> 248 us with plain
-// sums (about 8 more with the three levels that keep their precision), 64 with full codebooks of 4096: 523 -> 508.  With 126 tiles (V = 32064, 40 sequences) it is 217 against 203; and a draw, whose
-// generator then runs in that kernel's epilogue with nothing beside it, 375 against 338 us at 64.
+// launch of their own, instead of the decode kernel's base and hyper units in one.  Either kernel has one tile of 256 weight
+// rows per CU, so a last round of tiles that leaves CUs idle costs as much as a full one -- but in the decode kernel the
+// hyper units run there.  Greedy, d = 4096, hyper units of 1000 entries, cap = 1024, us, one launch -> split:
+//   tiles (of the rounds')   8 sequences     24             40             64
+//   384 (of 512)             195 -> 188      209 -> 208     230 -> 229     230 -> 260
+//   448 (of 512)             210 -> 193      236 -> 214     286 -> 235     298 -> 266
+//   501 (V = 128256)         280 -> 203      287 -> 223     294 -> 243     300 -> 272
+//   594 (of 768, V = 151936) 289 -> 276      297 -> 297     308 -> 319     322 -> 350
+// Hence: up to 16 sequences, or a last round at least 7/8 full over all rounds, or hyper units that would open another
+// round in one launch (with short histories most of them are empty: 64 sequences with 100 entries over 594 tiles 297 -> 289).
+// At most 256 tiles stay (V = 32064, 40 sequences, 203 -> 217), and so does a draw, whose generator would run in the
+// streaming kernel's epilogue with nothing beside it (V = 128256, 64 sequences: 338 -> 375).
 static bool split_few(const z2z_ctx* c, int rows) {
-  return rows > 4 && rows <= 64 && c->opt_decode_kernel == 0 && c->opt_logits_kernel == 0 &&
-         z2z_logits_mid_tiles(c->cfg.V) >= 256 && z2z_logits_mid_ok(c, rows);
+  const long long tiles = z2z_logits_mid_tiles(c->cfg.V), slots = (tiles + 255) / 256 * 256;
+  int base_columns, hyper_columns;
+  z2z_logits_decode_units(&base_columns, &hyper_columns);
+  const long long units = (long long)rows * ((c->cfg.cap + hyper_columns - 1) / hyper_columns);
+  return rows > 4 && rows <= 64 && c->opt_decode_kernel == 0 && c->opt_logits_kernel == 0 && tiles >= 256 &&
+         (rows <= 16 || 8 * tiles >= 7 * slots || tiles + units > slots) && z2z_logits_mid_ok(c, rows);
 }
 
 // Parts per row that any kind of step may leave (hyper units of 64 rows): every step sizes the scratch for all of them,

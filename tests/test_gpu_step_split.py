@@ -1,5 +1,5 @@
-"""GPU parity of greedy decode steps of 5..64 sequences over a vocabulary of at least 65281 columns: the base part on the
-weight-streaming kernel (sums in three levels), the hyper units alone, in units of 64..512 rows.  Section 2.3, steps 7-9.
+"""GPU parity of greedy decode steps of 5..64 sequences over a vocabulary of at least 65281 columns (256 tiles; with more than 16
+sequences only where the rounds of 256 tiles are 7/8 full, or hyper units would open another): the base part on the weight-streaming kernel (sums in three levels), the hyper units alone, in units of 64..512 rows.  Section 2.3, steps 7-9.
 
 Bound of the largest logit: fp32 sums of d products, 8 at most in one run of the accumulators: 1e-5 of its size."""
 import numpy as np
@@ -13,15 +13,20 @@ from helpers import check_logits_rows, gpu_encode, oracle_encode_batch, torch_st
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,V,d,cap", [
-    (5, 65281, 128, 40),       # two slabs: fewer than buffers; one unit per sequence
-    (9, 65290, 768, 700),      # twelve slabs: two rounds of the buffers, one flush of the second level
-    (33, 66000, 1664, 100),    # 26 slabs: four rounds and two steps
-    (64, 65281, 256, 520),     # every row valid; nine units of 64 per sequence
-    (4, 65281, 128, 40),       # (four sequences stay on the dot-product units)
-    (40, 65000, 128, 40),      # (254 tiles stay on the decode kernel)
+@pytest.mark.parametrize("B,V,d,cap,split", [
+    (5, 65281, 128, 40, 1),       # two slabs: fewer than buffers; one unit per sequence
+    (9, 65290, 768, 700, 1),      # twelve slabs: two rounds of the buffers, one flush of the second level
+    (33, 65500, 1664, 100, 1),    # 26 slabs: four rounds and two steps
+    (64, 65281, 256, 520, 1),     # every row valid; nine units of 64 per sequence
+    (4, 65281, 128, 40, 0),       # (four sequences stay on the dot-product units)
+    (40, 65000, 128, 40, 0),      # (254 tiles stay on the decode kernel)
+    (16, 66000, 128, 40, 1),      # 258 tiles, half of the second round idle: up to 16 sequences
+    (17, 66000, 128, 40, 0),
+    (17, 114433, 128, 40, 1),     # 448 tiles of 512
+    (17, 114432, 128, 40, 0),     # 447
+    (32, 66000, 128, 4000, 1),    # 258 tiles and 256 hyper units
 ])
-def test_split_step(B, V, d, cap):
+def test_split_step(B, V, d, cap, split):
     import torch
 
     from paper_2506_01084_amd import api
@@ -49,7 +54,7 @@ def test_split_step(B, V, d, cap):
     ctx.extended_logits(torch_storage(H, "bf16"), 1, d_E, d_W, am, mx, lse, None)
     torch.cuda.synchronize()
     after = ctx.read_launches()
-    assert after["mid"] - before["mid"] == (1 if B > 4 and V > 65280 else 0)
+    assert after["mid"] - before["mid"] == split
     am, mx, lse = am.cpu().numpy(), mx.cpu().numpy(), lse.cpu().numpy()
     for b in range(B):
         Wr = oracle.hyper_embed(E, "bf16", ref[b][1], cap, "mean")
