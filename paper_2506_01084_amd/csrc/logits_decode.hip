@@ -927,12 +927,13 @@ int z2z_logits_decode_parts(const z2z_ctx* c) {
 
 // Rows of W_hyper[b] per unit of the per-sequence part of a call with a few hidden rows per sequence.  A unit walks
 // its rows in steps of 16 with three steps in flight, about 1.3 us each whatever the rest of the machine does, so
-// few large units leave the memory idle: the unit halves until there is one for every CU (64 rows at least: the
+// few large units leave the memory idle: the unit halves while the halves still find a CU each (64 rows at least: the
 // step loop takes blocks in fours).  5 rows x 8 sequences of 2048 entries, d = 4096 (64 units before, 256 now):
-// the whole call 255 -> 216 us.
+// the whole call 255 -> 216 us.  Beyond one per CU two rounds of half units take longer than one of whole ones: 17
+// sequences of 2048 entries, 5 / 3 rows each, 272 units of 128 304 / 251 us, 136 of 256 287 / 235.
 int z2z_logits_decode_seq_unit(const z2z_ctx* c) {
   int unit = D_BASE_UNIT;
-  while (unit > 64 && (long long)c->cfg.B * ((c->cfg.cap + unit - 1) / unit) < 256) unit >>= 1;
+  while (unit > 64 && (long long)c->cfg.B * ((c->cfg.cap + unit / 2 - 1) / (unit / 2)) <= 256) unit >>= 1;
   return unit;
 }
 
