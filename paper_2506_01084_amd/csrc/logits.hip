@@ -448,8 +448,8 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
   int seq_unit = 0;
   if (decode_split || seq_split) {
     seq_unit = seq_split ? z2z_logits_decode_seq_unit(c) : z2z_logits_decode_hyper_unit(c);
-    // (the static array may be too small for the parts of the smaller units)
-    if (use_static && (size_t)(base_strips + (cap + seq_unit - 1) / seq_unit) * rows > parts.capacity) seq_unit = seq_split ? 256 : 512;
+    // (the static array may be too small for the parts of the smaller units; the other entry point cuts the same way)
+    if ((size_t)(base_strips + (cap + seq_unit - 1) / seq_unit) * rows > Z2Z_STATIC_PARTS) seq_unit = seq_split ? 256 : 512;
     hyp_strips = (cap + seq_unit - 1) / seq_unit;
   }
   if (decode_split && !use_static) {

@@ -161,3 +161,31 @@ def test_static_entry_point_under_graph_capture_on_a_fresh_context():
         junk = torch.randn(1 << 18, device="cuda").sum().item()      # unrelated eager work between replays
         assert np.isfinite(junk)
     ctx.close()
+
+
+def test_static_entry_point_takes_the_same_units_where_its_array_is_nearly_full():
+    """64 sequences x 64 rows over 1022 strips of the base vocabulary: with units of 256 rows of W_hyper the parts fill the
+    array to the last element, with the units of 128 that the call would take otherwise they do not fit.  The
+    allocating entry point has to cut the same way: the log-sum-exp is bit-identical."""
+    import torch
+    from paper_2506_01084_amd import api
+
+    B, R, d, cap, V = 64, 64, 128, 512, 1022 * 1024
+    assert (V // 1024 + 2) * B * R == api.STATIC_PARTS
+    print("[case] static array filled to its last element", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    ctx = api.Context(B=B, V=V, M=3, cap=cap, d=d, dtype="bf16", pool="mean")
+    tokens = torch.randint(0, 50, (B, 2000), generator=gen, device="cuda").cpu().numpy()
+    gpu_encode(ctx, tokens)
+    assert (ctx.codebook()[2] > 300).all()
+    E = (torch.randn((V, d), generator=gen, device="cuda") * 0.1).bfloat16()
+    W = (torch.randn((B, cap, d), generator=gen, device="cuda") * 0.2).bfloat16()
+    H = (torch.randn((B * R, d), generator=gen, device="cuda") * 0.5).bfloat16()
+    H[:, 0], E[:, 0], W[:, :, 0] = 1, -40, -6            # hypertokens alone count, their log-sum-exp is about 0: every bit shows
+    static, grown = _outputs(B * R), _outputs(B * R)
+    ctx.extended_logits_static(H, R, E, W, *static)
+    ctx.extended_logits(H, R, E, W, *grown)
+    torch.cuda.synchronize()
+    for a, b in zip(static, grown):
+        assert torch.equal(a, b), "static and allocating entry points disagree"
+    ctx.close()
