@@ -433,7 +433,7 @@ struct EncShared {
   uint32_t count[kMaxWaves];                 // starts | proposals << 16 of each wave
   uint32_t count_valid[kMaxWaves];           // the same below the window's limit (cut windows only)
   int32_t changed[2];
-  int32_t cut_asked;                         // a token out of range was staged, or an edge found no slot
+  int32_t cut_asked;                         // the window holds a token out of range, or an edge found no slot
   int32_t bad_pos, ovf_pos, full_pos, spill_pos;   // where a window is cut
   int32_t last_code, last_len, last_end;     // the last phrase of the window
   uint16_t rank[W];                          // of the proposing starts
@@ -471,10 +471,7 @@ __device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, EncShared<N
   int fill = kRing;
   for (int i = tid; i < kRing; i += W) sh.tok[i] = i < n ? classify(in[i]) : -1;
   int32_t ahead = fill + tid < n ? in[fill + tid] : 0;
-  if (tid == 0) {
-    sh.cut_asked = 0;
-    sh.changed[0] = sh.changed[1] = 0;
-  }
+  if (tid == 0) sh.changed[0] = sh.changed[1] = 0;
   sync_after_global_stores();        // (a table cleared in global memory is read past the L1)
 
   int status = 0;
@@ -512,7 +509,10 @@ __device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, EncShared<N
       const int p = pos + tid + d;
       return p < n ? sh.tok[p & (kRing - 1)] : -1;
     };
-    if (tid == 0) sh.bad_pos = sh.ovf_pos = sh.full_pos = sh.spill_pos = W;
+    if (tid == 0) {
+      sh.bad_pos = sh.ovf_pos = sh.full_pos = sh.spill_pos = W;
+      sh.cut_asked = 0;               // (this window's: set behind the barrier below, read in step 5)
+    }
 
     // ---- 1. chains against the table of the round's start -------------------------------------------
     const int32_t tok0 = tk(0);
@@ -532,7 +532,6 @@ __device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, EncShared<N
         h0 = edge_hash(c0, nxt0);
       }
     }
-    if (__ballot(tok0 == -2) != 0 && lane == 0) sh.cut_asked = 1;
 
     const int avail = min(W, n - pos);
     const int room = cap - C;
@@ -553,6 +552,7 @@ __device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, EncShared<N
     };
     skip_functions();
     __syncthreads();
+    if (__ballot(tok0 == -2) != 0 && lane == 0) sh.cut_asked = 1;
     for (int it = 0; it <= W; ++it) {           // (a start becomes final with every iteration: the bound is never met)
       ++n_rounds;
       // ---- 2. starts ---------------------------------------------------------------------------------

@@ -125,3 +125,52 @@ def test_decode_of_arbitrary_codes(M, cap):
                     assert int(st[b]) == api.ST_OVERFLOW and room - M < int(n_tok[b]) <= room
                 assert toks[b, :n_tok[b]].tolist() == ref[b][0][:n_tok[b]]
         ctx.close()
+
+
+def _crowded_pairs(V, bits):
+    """Pairs of tokens, the most found, whose edges share both of their groups of the round's set (2^bits groups of four):
+    beyond eight of them in a window the rest find no slot.  (The hash is the kernel's.)"""
+    p, t = np.divmod(np.arange(V * V, dtype=np.uint64), np.uint64(V))
+    h = (p * np.uint64(0x9E3779) + t * np.uint64(0xC2B2AF)) & np.uint64(0xFFFFFFFF)
+    h ^= h >> np.uint64(15)
+    h = (h * np.uint64(0x2C1B3C6D)) & np.uint64(0xFFFFFFFF)
+    a = h >> np.uint64(32 - bits)
+    key = (a << np.uint64(16)) | (a ^ (((h >> np.uint64(2)) & np.uint64((1 << bits) - 1)) | np.uint64(1)))
+    _, at, count = np.unique(key, return_inverse=True, return_counts=True)
+    best = np.nonzero(at == count.argmax())[0]
+    return np.stack([p[best], t[best]], 1).astype(np.int32).reshape(-1)
+
+
+@pytest.mark.parametrize("N,bits,kernel", [(500, 9, 0), (3000, 10, 0), (3000, 10, 2), (400, 6, 4)])
+def test_windows_whose_edges_find_no_slot(N, bits, kernel):
+    """Windows cut because an edge finds both of its groups full, with whole windows between and behind them; then a token
+    out of range, and an output row that ends, in windows of either kind."""
+    from paper_2506_01084_amd import api
+
+    V, M, cap = 1800, 3, 2500
+    rng = np.random.default_rng(N + bits)
+    crowd = _crowded_pairs(V, bits)[:60]
+    assert len(crowd) >= 24
+    B = 4
+    tokens = np.minimum(rng.zipf(1.25, (B, N)) - 1, V - 1).astype(np.int32)
+    tokens[0, :len(crowd)] = crowd
+    tokens[1, N // 2:N // 2 + len(crowd)] = crowd
+    tokens[2, N - len(crowd):] = crowd
+    lens = np.full(B, N, dtype=np.int32)
+    _round_trip(tokens, lens, V, M, cap, kernel)
+    ctx = _ctx(B, V, M, cap, kernel)
+    for at in (5, 40, N // 3, N // 2 + 30, N - 1):
+        bad = tokens.copy()
+        bad[:, at] = V + 7
+        codes, n_codes, status = gpu_encode(ctx, bad, lens)
+        ref = oracle_encode_batch(bad, lens, V, M, cap)
+        for b in range(B):
+            assert int(status[b]) == ref[b][2] == api.ST_BAD_TOKEN and codes[b, :n_codes[b]].tolist() == ref[b][0]
+        assert_codebook_equal(ctx, [r[1] for r in ref], M, cap)
+    for room in (3, 35, N // 2):
+        codes, n_codes, status = gpu_encode(ctx, tokens, lens, out_stride=room)
+        ref = oracle_encode_batch(tokens, lens, V, M, cap)
+        assert (status == api.ST_OVERFLOW).all() and (n_codes == room).all()
+        for b in range(B):
+            assert codes[b].tolist() == ref[b][0][:room]
+    ctx.close()
