@@ -71,9 +71,13 @@ __global__ void __launch_bounds__(256) linear_sum_kernel(const float* partial, i
 // out[b][c][r] = in[b][r][c] (bf16) for r < R (and r < *rows_dev when given), c < C; columns up to ld_out of out
 // beyond that are zero (they pad the contraction of a product over rows).  64 x 64 tiles through LDS, 256
 // threads, 16 bytes per lane on both sides (ld_in and ld_out are multiples of 8, the bases 16-byte aligned); grid
-// (ceil(ld_out / 64), ceil(C / 64), batch).  Both sides pass by the caches (whole lines, each once): the 30 copies of a
-// training step, 46 GB moved, 9.5 -> 8.3 ms.
+// (ceil(ld_out / 64), ceil(C / 64), batch).  A copy that is more than the memory-side cache holds goes PAST the caches on
+// both sides (whole lines, each once): the 30 copies of a training step over 8 x 4096 tokens, 46 GB moved, 9.5 -> 8.3 ms.
+// A smaller one is read by the next launch, and so is what it was made from; with few rows those wait for it: 5 x 107
+// tokens, d = 3584, the four products over transposed weights of a layer 1264 us, 1526 when the copies went past the caches.
 typedef __attribute__((__vector_size__(16))) uint32_t u32x4;
+constexpr size_t kPastCaches = (size_t)256 << 20;
+template <bool PAST>
 __global__ void __launch_bounds__(256) transpose_bf16_kernel(const uint16_t* in, uint16_t* out, int R, const int32_t* rows_dev,
                                                              int C, int ld_in, int ld_out, size_t in_batch,
                                                              size_t out_batch) {
@@ -88,7 +92,10 @@ __global__ void __launch_bounds__(256) transpose_bf16_kernel(const uint16_t* in,
     const int i = line + 32 * h;                     // row of the tile
     const int r = r0 + i, c = c0 + chunk * 8;
     uint4 v = {0u, 0u, 0u, 0u};
-    if (r < R && c < ld_in) v = __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + (size_t)r * ld_in + c)));
+    if (r < R && c < ld_in) {
+      const u32x4* from = reinterpret_cast<const u32x4*>(src + (size_t)r * ld_in + c);
+      v = __builtin_bit_cast(uint4, PAST ? __builtin_nontemporal_load(from) : *from);
+    }
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -101,9 +108,14 @@ __global__ void __launch_bounds__(256) transpose_bf16_kernel(const uint16_t* in,
   for (int h = 0; h < 2; ++h) {
     const int i = line + 32 * h;                     // column of the tile = row of the output
     const int c = c0 + i, r = r0 + chunk * 8;
-    if (c < C && r < ld_out)
-      __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(&t[i][chunk * 8]),
-                                  reinterpret_cast<u32x4*>(dst + (size_t)c * ld_out + r));
+    if (c < C && r < ld_out) {
+      const u32x4 v = *reinterpret_cast<const u32x4*>(&t[i][chunk * 8]);
+      u32x4* to = reinterpret_cast<u32x4*>(dst + (size_t)c * ld_out + r);
+      if (PAST)
+        __builtin_nontemporal_store(v, to);
+      else
+        *to = v;
+    }
   }
 }
 
@@ -112,9 +124,13 @@ __global__ void __launch_bounds__(256) transpose_bf16_kernel(const uint16_t* in,
 int z2z_launch_transpose(const void* in, void* out, int R, const int32_t* rows_dev, int C, int ld_in, int ld_out,
                          int batch, size_t in_batch, size_t out_batch, hipStream_t s) {
   if (R < 1 || C < 1 || batch < 1) return Z2Z_OK;
-  hipLaunchKernelGGL(transpose_bf16_kernel, dim3((ld_out + 63) / 64, (C + 63) / 64, batch), dim3(256), 0, s,
-                     reinterpret_cast<const uint16_t*>(in), reinterpret_cast<uint16_t*>(out), R, rows_dev, C, ld_in,
-                     ld_out, in_batch, out_batch);
+  const dim3 grid((ld_out + 63) / 64, (C + 63) / 64, batch), block(256);
+  const uint16_t* from = reinterpret_cast<const uint16_t*>(in);
+  uint16_t* to = reinterpret_cast<uint16_t*>(out);
+  if ((size_t)batch * C * ld_out * sizeof(uint16_t) > kPastCaches)
+    hipLaunchKernelGGL(transpose_bf16_kernel<true>, grid, block, 0, s, from, to, R, rows_dev, C, ld_in, ld_out, in_batch, out_batch);
+  else
+    hipLaunchKernelGGL(transpose_bf16_kernel<false>, grid, block, 0, s, from, to, R, rows_dev, C, ld_in, ld_out, in_batch, out_batch);
   Z2Z_HIP_TRY(hipGetLastError());
   return Z2Z_OK;
 }
