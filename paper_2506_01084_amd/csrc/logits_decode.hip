@@ -54,11 +54,18 @@ constexpr int D_MAXQ = 8;              // hyper units: d <= 512 * D_MAXQ
 #define D_DOT_BATCH 4                  // sequences per decode step up to which the base vocabulary does too
 #endif
 
-// A weight row that a whole wave streams once: the load leaves nothing in the caches.  (Only where one instruction takes
+// Weight rows that a whole wave streams once: the loads leave nothing in the caches.  (Only where one instruction takes
 // whole lines, as in the dot-product units: the matrix-core units take a line in two halves, and fetch it twice
 // this way: a step of 24 sequences 28 us slower.)  Steps of 1 and 64 sequences: 222 -> 196 us, 550 -> 523.
-__device__ __forceinline__ uint4 load_once(const uint4* p) {
+// Weights of up to kKeepBytes stay with plain loads: a step that follows another finds them in the memory-side cache
+// (256 MB), and the first one is as fast.  One sequence, us in a row / with other weights each time, plain and streamed:
+// V = 32000, d = 1024 (68 MB) 33 / 41 and 41 / 41; V = 32064, d = 3072 (203 MB) 49 / 67 and 65 / 65 -- between two steps
+// of a model of that size its own layers pass through the cache; V = 128256, d = 4096 (1 GB) 199 / 199 and 184 / 184.
+constexpr size_t kKeepBytes = (size_t)128 << 20;
+template <bool ONCE>
+__device__ __forceinline__ uint4 load_weights(const uint4* p) {
   typedef __attribute__((__vector_size__(16))) uint32_t u32x4;
+  if (!ONCE) return *p;
   return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
 }
 
@@ -70,6 +77,7 @@ struct DecodeArgs {
   int32_t B, V, cap, d;
   int32_t n_base_units;   // ceil(V / 256)
   int32_t n_groups;       // ceil(B / 64) groups of hidden rows for the base part
+  int32_t once;           // dot-product units: the weight rows are streamed past the caches
   int32_t unit;           // weight rows per hyper unit: 512, or fewer where the hyper units run alone
   int32_t units_per_seq;  // ceil(cap / unit)
   int32_t n_parts;        // partials per hidden row
@@ -396,7 +404,7 @@ __device__ __forceinline__ void base_unit(const DecodeArgs& a, int unit, int gro
   }
 }
 
-template <int NQ, int MODE>
+template <int NQ, int MODE, bool ONCE>
 __device__ __forceinline__ void hyper_rows(const DecodeArgs& a, int b, int r0, int r1, int lane, int wave, Triple& t,
                                            Draw& dr) {
   Noise noise;
@@ -419,8 +427,8 @@ __device__ __forceinline__ void hyper_rows(const DecodeArgs& a, int b, int r0, i
     for (int q = 0; q < NQ; ++q) {
       const int c = q * 64 + lane;
       const bool in = c < chunks_per_row;
-      wa[q] = in ? load_once(W + (size_t)r * chunks_per_row + c) : uint4{0u, 0u, 0u, 0u};
-      wb[q] = (in && has_b) ? load_once(W + (size_t)rb * chunks_per_row + c) : uint4{0u, 0u, 0u, 0u};
+      wa[q] = in ? load_weights<ONCE>(W + (size_t)r * chunks_per_row + c) : uint4{0u, 0u, 0u, 0u};
+      wb[q] = (in && has_b) ? load_weights<ONCE>(W + (size_t)rb * chunks_per_row + c) : uint4{0u, 0u, 0u, 0u};
     }
     float sa = 0.f, sb = 0.f;
 #pragma unroll
@@ -464,10 +472,14 @@ __device__ __forceinline__ void hyper_unit(const DecodeArgs& a, int b, int u, un
   Draw dr = empty_draw();
   if (r0 < r1) {
     const int nq = (a.d + 511) >> 9;
-    if (nq <= 4)
-      hyper_rows<4, MODE>(a, b, r0, r1, lane, wave, t, dr);
+    if (nq <= 4 && a.once)
+      hyper_rows<4, MODE, true>(a, b, r0, r1, lane, wave, t, dr);
+    else if (nq <= 4)
+      hyper_rows<4, MODE, false>(a, b, r0, r1, lane, wave, t, dr);
+    else if (a.once)
+      hyper_rows<D_MAXQ, MODE, true>(a, b, r0, r1, lane, wave, t, dr);
     else
-      hyper_rows<D_MAXQ, MODE>(a, b, r0, r1, lane, wave, t, dr);
+      hyper_rows<D_MAXQ, MODE, false>(a, b, r0, r1, lane, wave, t, dr);
   }
   // every lane of a wave holds the same triple; waves took rows w, w + 8, ...: merging by value and
   // column restores the lowest-column rule
@@ -500,7 +512,7 @@ __device__ __forceinline__ void hyper_unit(const DecodeArgs& a, int b, int u, un
 // that every weight row streams past once, whole and contiguous -- the access pattern HBM serves best (6.3 TB/s
 // for the per-sequence part of a call with 2 rows per sequence, against 5.2 on the matrix-core units).  Rows
 // [r0, r1) of the matrix W against the hidden rows hrow0 .. hrow0 + R - 1; weight row r is column col0 + r.
-template <int NQ, int R, int MODE>
+template <int NQ, int R, int MODE, bool ONCE>
 __device__ __forceinline__ void dot_rows(const DecodeArgs& a, const uint4* W, int hrow0, int col0, int r0, int r1,
                                          int lane, int wave, Triple (&t)[R], Draw (&dr)[R]) {
   const int chunks_per_row = a.d >> 3;
@@ -524,8 +536,8 @@ __device__ __forceinline__ void dot_rows(const DecodeArgs& a, const uint4* W, in
     for (int q = 0; q < NQ; ++q) {
       const int c = q * 64 + lane;
       const bool in = c < chunks_per_row;
-      wa[q] = in ? load_once(W + (size_t)r * chunks_per_row + c) : uint4{0u, 0u, 0u, 0u};
-      wb[q] = (in && has_b) ? load_once(W + (size_t)rb * chunks_per_row + c) : uint4{0u, 0u, 0u, 0u};
+      wa[q] = in ? load_weights<ONCE>(W + (size_t)r * chunks_per_row + c) : uint4{0u, 0u, 0u, 0u};
+      wb[q] = (in && has_b) ? load_weights<ONCE>(W + (size_t)rb * chunks_per_row + c) : uint4{0u, 0u, 0u, 0u};
     }
     float sa[R], sb[R];
 #pragma unroll
@@ -581,10 +593,14 @@ __device__ __forceinline__ void dot_unit(const DecodeArgs& a, const uint4* W, in
   }
   if (r0 < r1) {
     const int nq = (a.d + 511) >> 9;
-    if (nq <= 4)
-      dot_rows<4, R, MODE>(a, W, hrow0, col0, r0, r1, lane, wave, t, dr);
+    if (nq <= 4 && a.once)
+      dot_rows<4, R, MODE, true>(a, W, hrow0, col0, r0, r1, lane, wave, t, dr);
+    else if (nq <= 4)
+      dot_rows<4, R, MODE, false>(a, W, hrow0, col0, r0, r1, lane, wave, t, dr);
+    else if (a.once)
+      dot_rows<D_MAXQ, R, MODE, true>(a, W, hrow0, col0, r0, r1, lane, wave, t, dr);
     else
-      dot_rows<D_MAXQ, R, MODE>(a, W, hrow0, col0, r0, r1, lane, wave, t, dr);
+      dot_rows<D_MAXQ, R, MODE, false>(a, W, hrow0, col0, r0, r1, lane, wave, t, dr);
   }
   // every lane of a wave holds the same triples; the waves took rows w, w + 8, ...: merging by value and column
   // restores the lowest-column rule
@@ -778,6 +794,7 @@ int z2z_launch_logits_decode(z2z_ctx* c, const void* H, const void* W_base, cons
   a.V = c->cfg.V;
   a.cap = c->cfg.cap;
   a.d = c->cfg.d;
+  a.once = ((size_t)a.V + (size_t)a.B * a.cap) * a.d * sizeof(uint16_t) > kKeepBytes;
   a.n_base_units = (a.V + D_BASE_UNIT - 1) / D_BASE_UNIT;
   a.n_groups = (a.B + 63) / 64;
   a.unit = hyper_only_base_parts >= 0 && rows_per_seq == 1 ? seq_unit : D_UNIT;

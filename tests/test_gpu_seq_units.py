@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("rows_per_seq", [2, 5, 17])
-@pytest.mark.parametrize("B,cap,unit", [(3, 257, 64), (20, 1500, 128), (33, 1500, 256), (130, 300, 256), (1, 64, 64)])
+@pytest.mark.parametrize("B,cap,unit", [(3, 257, 64), (20, 1500, 128), (33, 1500, 256), (130, 300, 256), (1, 64, 64),
+                                        (130, 4200, 256)])   # more than 128 MB of weights: streamed past the caches
 def test_units_of_every_size(B, cap, unit, rows_per_seq):
     import torch
 
