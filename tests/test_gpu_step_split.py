@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
     (33, 65500, 1664, 100, 1),    # 26 slabs: four rounds and two steps
     (64, 65281, 256, 520, 1),     # every row valid; nine units of 64 per sequence
     (4, 65281, 128, 40, 0),       # (four sequences stay on the dot-product units)
-    (4, 65500, 1088, 40, 0),      # (... past the caches with more than 128 MB of weights)
+    (4, 65500, 1152, 40, 0),      # (... past the caches with more than 128 MB of weights)
     (40, 65000, 128, 40, 0),      # (254 tiles stay on the decode kernel)
     (16, 66000, 128, 40, 1),      # 258 tiles, half of the second round idle: up to 16 sequences
     (17, 66000, 128, 40, 0),
