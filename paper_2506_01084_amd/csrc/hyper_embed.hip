@@ -18,7 +18,7 @@ using namespace z2z_embed;
 // decode step, would otherwise be one long chain of loads per wave).  Full mode (first == nullptr,
 // last_n == 0) covers [0, cap): rows below C_b are embedded, the others zeroed.  Incremental modes cover
 // [first[b], C_b) or the last last_n entries only.
-template <bool BF16>
+template <bool BF16, bool PAST>
 __global__ void __launch_bounds__(256) hyper_embed_kernel(EmbedArgs a) {
   const int lane = threadIdx.x & 63;
   // (what a wave needs to know is the same for all its lanes: scalar loads, requested together)
@@ -38,11 +38,11 @@ __global__ void __launch_bounds__(256) hyper_embed_kernel(EmbedArgs a) {
     const size_t row = (size_t)b * a.cap + e;
     if (e < C) {
       const int L = min(max(a.ent_len[row], 1), a.M);
-      embed_row<BF16>(a, a.ent_tokens + row * a.M, L, row, lane, part);
+      embed_row<BF16, PAST>(a, a.ent_tokens + row * a.M, L, row, lane, part);
     } else {
       u32x4* W = reinterpret_cast<u32x4*>(a.W) + row * (size_t)n_chunks;
       const u32x4 z = {0u, 0u, 0u, 0u};
-      for (int c = part * 64 + lane; c < n_chunks; c += 64 * a.split) __builtin_nontemporal_store(z, W + c);
+      for (int c = part * 64 + lane; c < n_chunks; c += 64 * a.split) store_chunk<PAST>(z, W + c);
     }
   }
 }
@@ -66,10 +66,20 @@ int z2z_launch_hyper_embed(z2z_ctx* c, const void* E, void* W_hyper, const int32
   a.split = split;
   const long long total_units = (long long)c->cfg.B * units * split;
   const unsigned grid = (unsigned)((total_units + 3) / 4);
-  if (c->cfg.dtype == Z2Z_BF16)
-    hipLaunchKernelGGL(hyper_embed_kernel<true>, dim3(grid), dim3(256), 0, s, a);
+  // Both unembedding matrices in half of the memory-side cache: the call that follows finds the rows there (2 x 1000
+  // entries, V = 32000, d = 256, a step of both right behind: 40 us with the rows past the caches, 35 with plain
+  // stores).  Beyond that the rows push out what is still needed (8 x 2048, V = 128256, d = 4096, 5 rows per sequence behind:
+  // 263 past the caches, 291).
+  const bool past = ((size_t)c->cfg.V + (size_t)c->cfg.B * c->cfg.cap) * chunks * 16 > ((size_t)128 << 20);
+  const bool bf16 = c->cfg.dtype == Z2Z_BF16;
+  if (bf16 && past)
+    hipLaunchKernelGGL((hyper_embed_kernel<true, true>), dim3(grid), dim3(256), 0, s, a);
+  else if (bf16)
+    hipLaunchKernelGGL((hyper_embed_kernel<true, false>), dim3(grid), dim3(256), 0, s, a);
+  else if (past)
+    hipLaunchKernelGGL((hyper_embed_kernel<false, true>), dim3(grid), dim3(256), 0, s, a);
   else
-    hipLaunchKernelGGL(hyper_embed_kernel<false>, dim3(grid), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((hyper_embed_kernel<false, false>), dim3(grid), dim3(256), 0, s, a);
   Z2Z_HIP_TRY(hipGetLastError());
   return Z2Z_OK;
 }

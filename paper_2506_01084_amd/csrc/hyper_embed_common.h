@@ -35,12 +35,20 @@ __device__ __forceinline__ float div_small(float x, float n, float rcp_n) {
   return c == c ? c : q;
 }
 
+template <bool PAST>
+__device__ __forceinline__ void store_chunk(u32x4 v, u32x4* to) {
+  if (PAST)
+    __builtin_nontemporal_store(v, to);
+  else
+    *to = v;
+}
+
 // One row of L constituents.  U chunks of every constituent row are requested before the first is used: with one
-// load in flight per wave the kernel waits for memory, not for its bandwidth.  The row goes out past the caches
+// load in flight per wave the kernel waits for memory, not for its bandwidth.  PAST: the row goes out past the caches
 // (nothing reads it again before the cache has turned over, and the popular embedding rows stay in L2 instead).
 // 16 x 16384 entries, d = 3584 (1.9 GB written): 578 us; loads ahead 494; stores past the caches 322.
 // 8 x 2048, d = 4096: 50, 37, 34.6 us.
-template <bool BF16, int L>
+template <bool BF16, int L, bool PAST>
 __device__ __forceinline__ void embed_row_l(const EmbedArgs& a, const int32_t* toks, size_t out_row, int lane, int part) {
   constexpr int U = L <= 2 ? 4 : (L <= 4 ? 2 : 1);
   // elements per 16-byte chunk: 8 (bf16) or 4 (f32)
@@ -93,25 +101,25 @@ __device__ __forceinline__ void embed_row_l(const EmbedArgs& a, const int32_t* t
         else
           o[e] = __float_as_uint(acc[e]);
       }
-      if (c0 + u * step < n_chunks) __builtin_nontemporal_store(o, W + c0 + u * step);
+      if (c0 + u * step < n_chunks) store_chunk<PAST>(o, W + c0 + u * step);
     }
   }
 }
 
 // Entry row `out_row`: the pooled rows of its L tokens (L uniform over the wave).
-template <bool BF16>
+template <bool BF16, bool PAST>
 __device__ __forceinline__ void embed_row(const EmbedArgs& a, const int32_t* toks, int L, size_t out_row, int lane,
                                           int part) {
   static_assert(Z2Z_MAX_M == 8, "one case per length");
   switch (L) {
-    case 1: return embed_row_l<BF16, 1>(a, toks, out_row, lane, part);
-    case 2: return embed_row_l<BF16, 2>(a, toks, out_row, lane, part);
-    case 3: return embed_row_l<BF16, 3>(a, toks, out_row, lane, part);
-    case 4: return embed_row_l<BF16, 4>(a, toks, out_row, lane, part);
-    case 5: return embed_row_l<BF16, 5>(a, toks, out_row, lane, part);
-    case 6: return embed_row_l<BF16, 6>(a, toks, out_row, lane, part);
-    case 7: return embed_row_l<BF16, 7>(a, toks, out_row, lane, part);
-    default: return embed_row_l<BF16, 8>(a, toks, out_row, lane, part);
+    case 1: return embed_row_l<BF16, 1, PAST>(a, toks, out_row, lane, part);
+    case 2: return embed_row_l<BF16, 2, PAST>(a, toks, out_row, lane, part);
+    case 3: return embed_row_l<BF16, 3, PAST>(a, toks, out_row, lane, part);
+    case 4: return embed_row_l<BF16, 4, PAST>(a, toks, out_row, lane, part);
+    case 5: return embed_row_l<BF16, 5, PAST>(a, toks, out_row, lane, part);
+    case 6: return embed_row_l<BF16, 6, PAST>(a, toks, out_row, lane, part);
+    case 7: return embed_row_l<BF16, 7, PAST>(a, toks, out_row, lane, part);
+    default: return embed_row_l<BF16, 8, PAST>(a, toks, out_row, lane, part);
   }
 }
 

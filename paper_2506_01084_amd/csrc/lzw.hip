@@ -937,7 +937,7 @@ __global__ void __launch_bounds__(kStepWaves * kWave) lzw_step_update_kernel(Lzw
   int32_t toks[Z2Z_MAX_M];
 #pragma unroll
   for (int j = 0; j < Z2Z_MAX_M; ++j) toks[j] = j < L ? load_fresh_i32(a.st.ent_tokens + row * a.st.M + j) : 0;
-  if (w < ea.split) z2z_embed::embed_row<BF16>(ea, toks, L, row, lane, w);
+  if (w < ea.split) z2z_embed::embed_row<BF16, false>(ea, toks, L, row, lane, w);
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -14,16 +14,18 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("pool", ["mean", "weighted"])
-@pytest.mark.parametrize("dtype,d", [("bf16", 8), ("bf16", 520), ("bf16", 2056), ("f32", 4), ("f32", 260), ("f32", 1028)])
-def test_every_length(dtype, d, pool):
+@pytest.mark.parametrize("dtype,d,cap", [("bf16", 8, 600), ("bf16", 520, 600), ("bf16", 2056, 600), ("f32", 4, 600), ("f32", 260, 600),
+                                         ("f32", 1028, 600),
+                                         ("bf16", 2056, 17000), ("f32", 1028, 17000)])   # over 128 MB: past the caches
+def test_every_length(dtype, d, cap, pool):
     import torch
 
     from paper_2506_01084_amd import api
 
-    B, V, M, cap, N = 2, 3, 8, 600, 4000            # three tokens: entries grow to M quickly
+    B, V, M, N = 2, 3, 8, 4000                      # three tokens: entries grow to M quickly
     cfg = dict(name="lengths", B=B, N=N, V=V, d=d, dtype=dtype, M=M, cap=cap, zipf_s=1.5, copy_frac=0.4, span=(4, 12),
                mode="motif", pool=pool, seed=9900 + d)
-    print(f"[case] {dtype} d={d} {pool}", flush=True)
+    print(f"[case] {dtype} d={d} cap={cap} {pool}", flush=True)
     tokens = wl.make_tokens(cfg)
     E = wl.make_embeddings(cfg)
     w = wl.make_pool_weights(cfg)
