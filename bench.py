@@ -424,7 +424,7 @@ def run_decode_workload(args, torch, api, wl):
                 peak_GBs=PEAK_HBM_GBS, frac=gbs / PEAK_HBM_GBS, mean_codebook_size=float(sizes.mean()),
                 roofline={"bound": "hbm", "kernel": "logits_mid_kernel + logits_decode_hyper_kernel (64 rows, config 3)", "achieved": k_gbs,
                           "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": k_gbs / PEAK_HBM_GBS,
-                          "traffic": TRAFFIC_BYTES.get("logits_decode_kernel@c3"), "avg_kernel_us": k_us,
+                          "traffic": TRAFFIC_BYTES.get("logits_mid_kernel+logits_decode_hyper_kernel@c3"), "avg_kernel_us": k_us,
                           "bytes_per_launch": bytes_step})
 
 

@@ -1,6 +1,6 @@
 // extended_logits, base-vocabulary part for up to 192 hidden rows in all (gfx950, bf16, d a multiple of 64): a
-// decode step of 65..192 sequences, a few rows per sequence at a small batch, a short chunk.  (zip2zip paper,
-// section 2.3, steps 7-9.)
+// decode step of 65..192 sequences, a greedy one of 5..64 where the tiles fill the CUs, a few rows per sequence at a
+// small batch, a short chunk; dense layers on up to 128 rows.  (zip2zip paper, section 2.3, steps 7-9.)
 //
 // With so few rows the part is bound by the bytes of W_base, like the one-row-per-sequence step.  That kernel's
 // base units hold 64 hidden rows in registers (one pass over W_base per 64 rows); the 256 x 256 tile kernel stages

@@ -69,8 +69,7 @@ def test_global_table_variant_bit_exact(name):
 
 @pytest.mark.parametrize("name", ["c2", "c4", "c5"])
 def test_one_wave_per_sequence_variant_bit_exact(name):
-    """Few long sequences take the kernels with four waves per sequence by default; the one-wave kernels (what
-    calls with many sequences run) on the same inputs."""
+    """Few long sequences take windows of up to 16 waves by default; windows of one wave on the same inputs."""
     cfg = wl.CONFIGS[name]
     tokens = wl.make_tokens(cfg)
     lens = wl.make_lens(cfg)
@@ -121,8 +120,8 @@ def test_many_sequences_per_call(B):
 
 @pytest.mark.parametrize("B,N", [(200, 700), (700, 2100)])
 def test_many_long_sequences_on_the_four_wave_kernels(B, N):
-    """Hundreds of sequences of 512 tokens or more still take four waves each (several workgroups per CU, the
-    smaller tables): ragged lengths across every window boundary, results unchanged."""
+    """Hundreds of sequences of 512 tokens or more (wide windows, or two workgroups per CU with more sequences than
+    CUs): ragged lengths across every window boundary, results unchanged."""
     cfg = wl.scaled(wl.CONFIGS["c4"], B=B, N=N, V=900, cap=700, seed=B + N)
     tokens = wl.make_tokens(cfg)
     lens = wl.make_lens(cfg, ragged=True)
@@ -133,10 +132,8 @@ def test_many_long_sequences_on_the_four_wave_kernels(B, N):
 
 @pytest.mark.parametrize("B,V,M,cap,N", [(700, 300, 3, 500, 2100), (1024, 70000, 8, 3000, 4097)])
 def test_four_wave_kernels_with_many_workgroups_in_flight_are_deterministic(B, V, M, cap, N):
-    """Hundreds of four-wave workgroups at once (table in LDS for 700 sequences, in global memory for 1024), on
-    streams of short runs whose codebooks fill up early: the code of the round that names the entry being made
-    is handled by all four waves together, and a wave that looked the edge up after wave 0 had stored it used
-    to take the other branch.  Eight decodes of the same codes and three encodes must agree with the input and
+    """Hundreds of workgroups of several waves at once, on streams of short runs whose codebooks fill up early: codes
+    that name the entry being made, and waves that must not see one another's insertions too early.  Eight decodes of the same codes and three encodes must agree with the input and
     with one another."""
     from paper_2506_01084_amd import api
 
@@ -410,13 +407,12 @@ def test_repeatable_across_runs_and_sequence_order():
     ctx.close()
 
 
-@pytest.mark.parametrize("narrow_only", [0, 4])      # 0: four waves per sequence for long calls; 4: one wave always
+@pytest.mark.parametrize("narrow_only", [0, 4])      # 0: as many waves per sequence as the call's length takes; 4: one always
 def test_long_calls_errors_appends_and_repeats_both_encoders(narrow_only):
-    """Calls of 512 tokens and more with few sequences take the encoder with four waves per sequence (rounds of
-    256 positions); everything a round can meet, against the oracle, for both encoders: an out-of-range token in
-    any of the four windows, an output row that ends in any window, long appended chunks, streams that repeat
-    their proposals (runs, short periods: rounds cut at the first repeat), the merge limit M = 8, a codebook
-    that fills in the middle of a round."""
+    """Long calls of few sequences take windows of 1024 positions on 16 waves (64 on one); everything a window can meet,
+    against the oracle, for both widths: an out-of-range token in any window, an output row that ends in any, long
+    appended chunks, streams that repeat their proposals (runs, short periods: several iterations), the merge limit
+    M = 8, a codebook that fills in the middle of a window."""
     from paper_2506_01084_amd import api
 
     rng = np.random.default_rng(17)
@@ -487,7 +483,7 @@ def test_short_appended_calls_in_wide_rows():
     ctx = _ctx(dict(B=B, V=V, M=M, cap=cap))
     streams = [oracle.LZWStream(V, M, cap) for _ in range(B)]
     full = np.full(B, N, dtype=np.int32)
-    codes, n_codes, st = gpu_encode(ctx, tokens, full)                       # a long call: four waves
+    codes, n_codes, st = gpu_encode(ctx, tokens, full)                       # a long call
     for b in range(B):
         assert codes[b, :n_codes[b]].tolist() == streams[b].encode_chunk(tokens[b].tolist())[0]
     for rep in range(4):                                                     # short ones in rows of 900

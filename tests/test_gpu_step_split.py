@@ -1,5 +1,7 @@
-"""GPU parity of greedy decode steps of 5..64 sequences over a vocabulary of at least 65281 columns (256 tiles; with more than 16
-sequences only where the rounds of 256 tiles are 7/8 full, or hyper units would open another): the base part on the weight-streaming kernel (sums in three levels), the hyper units alone, in units of 64..512 rows.  Section 2.3, steps 7-9.
+"""GPU parity of greedy decode steps of 5..64 sequences over a vocabulary of at least 65281 columns (256 tiles; with more
+than 16 sequences only where the rounds of 256 tiles are 7/8 full, or hyper units would open another): the base part on
+the weight-streaming kernel (sums in three levels), the hyper units alone, in units of 64..512 rows.  Section 2.3, steps
+7-9.
 
 Bound of the largest logit: fp32 sums of d products, 8 at most in one run of the accumulators: 1e-5 of its size."""
 import numpy as np
@@ -91,4 +93,34 @@ def test_greedy_step_is_captured_behind_an_eager_draw():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(am.long(), want.indices) and torch.allclose(mx, want.values, rtol=1e-4)
+    ctx.close()
+
+
+def test_sums_keep_the_decode_kernels_precision():
+    """The largest logits of a step at d = 4096 against float64 products of the stored operands: the streaming kernel's sums
+    in three levels leave 4.4e-8 to 5.2e-8 of their size (root mean square), one accumulator over all of K 2.7e-7 to
+    3.3e-7.  The bound lies between the two, a factor of two from either."""
+    import torch
+
+    from paper_2506_01084_amd import api
+
+    B, V, d, cap = 16, 65500, 4096, 16
+    ctx = api.Context(B=B, V=V, M=3, cap=cap, d=d, dtype="bf16", pool="mean")
+    ctx.reset()
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    E = (torch.randn((V, d), generator=gen, device="cuda") * 0.02).bfloat16()
+    W = torch.zeros((B, cap, d), dtype=torch.bfloat16, device="cuda")
+    am, mx, lse = torch.zeros(B, dtype=torch.int32, device="cuda"), torch.zeros(B, device="cuda"), torch.zeros(B, device="cuda")
+    err = []
+    for _ in range(4):
+        H = torch.randn((B, d), generator=gen, device="cuda").bfloat16()
+        before = ctx.read_launches()["mid"]
+        ctx.extended_logits(H, 1, E, W, am, mx, lse)
+        torch.cuda.synchronize()
+        assert ctx.read_launches()["mid"] == before + 1
+        want = (H.double() * E[am.long()].double()).sum(1)
+        err.append(((mx.double() - want) / want).cpu())
+    rms = float(torch.cat(err).square().mean().sqrt())
+    print(f"[case] largest logits of 64 rows: relative error {rms:.2e}", flush=True)
+    assert rms <= 1.2e-7
     ctx.close()
