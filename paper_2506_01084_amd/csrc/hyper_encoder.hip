@@ -232,6 +232,7 @@ __device__ __forceinline__ float4 sum_parts(const Parts& p, int r, int col, int 
   return float4{x.x + b.x + rv.x, x.y + b.y + rv.y, x.z + b.z + rv.z, x.w + b.w + rv.w};
 }
 
+constexpr int E_FEW_ROWS = 2048;
 constexpr int E_ROW_THREADS = 1024;    // 4 columns each: d <= 4096
 static_assert(4 * E_ROW_THREADS >= 64 * 8 * E_KCH, "a row fits the workgroup");
 
@@ -873,7 +874,10 @@ int z2z_launch_hyper_encode(z2z_ctx* c, const void* E, const z2z_encoder* enc, v
       const z2z_linear_pitch pitch = {dffp, dff, d};
       const bool padded = in == F && dffp != dff;
       int ret = Z2Z_OK;
-      if (!padded) ret = z2z_launch_linear_parts(c, in, w, R, rows_dev, d, K, false, &parts.partial, &parts.ksplit, s);
+      // (with more rows -- K is split there too in a narrow encoder -- a wave per row is the better LayerNorm: 6144 rows,
+      // d = 256: the pass 275 us fused, 267 in launches of their own)
+      if (!padded && R <= E_FEW_ROWS)
+        ret = z2z_launch_linear_parts(c, in, w, R, rows_dev, d, K, false, &parts.partial, &parts.ksplit, s);
       if (ret != Z2Z_OK) return ret;
       if (parts.ksplit == 0)
         return z2z_launch_linear(c, in, w, bias, residual, 0, out, R, rows_dev, d, K, s, nullptr, true, padded ? &pitch : nullptr);
@@ -892,7 +896,7 @@ int z2z_launch_hyper_encode(z2z_ctx* c, const void* E, const z2z_encoder* enc, v
     for (int l = 0; l < enc->n_layers; ++l) {
       const z2z_encoder_layer& lay = enc->layers[l];
       const z2z_encoder_layer* next = l + 1 < enc->n_layers ? &enc->layers[l + 1] : nullptr;
-      if (l == 0 && R <= 2048) {                    // (few rows: a workgroup each, 24 entries, 52 rows: 14 -> 5 us)
+      if (l == 0 && R <= E_FEW_ROWS) {              // (few rows: a workgroup each, 24 entries, 52 rows: 14 -> 5 us)
         hipLaunchKernelGGL(enc_row_norm_kernel<true>, dim3((unsigned)R), dim3(E_ROW_THREADS), 0, s, m,
                            reinterpret_cast<const uint16_t*>(E), reinterpret_cast<const uint16_t*>(enc->pos), Parts{}, x, A,
                            lay.ln1_g, lay.ln1_b, n_units);
