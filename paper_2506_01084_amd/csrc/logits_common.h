@@ -566,12 +566,13 @@ struct z2z_linear_pitch {
 int z2z_launch_linear(z2z_ctx* c, const void* A, const void* W, const float* bias, const void* residual, int act,
                       void* out, int R, const int32_t* rows_dev, int N, int K, hipStream_t s, const int32_t* k_dev = nullptr,
                       bool stream_f32 = false, const z2z_linear_pitch* pitch = nullptr);
-// Row pitch for n columns of an activation that is an operand of dense layers: n, or 64 more where rows are a multiple of
-// 32 KiB apart -- the tile kernel's workgroups read the same slab of 256 rows at a time, and such rows put it on a
-// few memory channels (35400 rows x 4096 columns, K = 16384: 1.07 -> 1.18 PFLOP/s, with a padded transposed weight 1.04
-// -> 1.19).  Other widths stay: with 64 more columns the same product at n = 8192 (29000 rows x 2048) takes 1061 us
-// instead of 970, n = 12288 is level, and 128 more columns gain nothing at any of them.
-inline int z2z_activation_pitch(int n) { return n % 16384 ? n : n + 64; }
+// Row pitch for n columns of an activation that is an operand of dense layers: n, or 64 more where n columns are a
+// multiple of 4 KiB -- the tile kernel's workgroups read the same slab of 256 rows at a time, and rows that far apart
+// on a power of two put it on a few memory channels (35400 rows x 4096 columns, K = 16384: 1.07 -> 1.18
+// PFLOP/s, with a padded transposed weight 1.04 -> 1.19; whole passes at n = 4096 2 % faster, n = 12288 level).  Odd
+// multiples of 16 KiB stay: with 64 more columns the product at n = 8192 (29000 rows x 2048) takes 1061 us instead of
+// 970.  (128 more gain nothing at 8192 and lose the gain at 16384.)
+inline int z2z_activation_pitch(int n) { return n % 2048 || n % 16384 == 8192 ? n : n + 64; }
 // Pitches are taken by the tile kernel alone; true if the layer runs on it, with K whole.
 bool z2z_linear_takes_pitch(const z2z_ctx* c, int R, int N, int K);
 // The same product where the layer's K is split over workgroups (few rows): only the fp32 partial tiles,
