@@ -355,113 +355,6 @@ __device__ __forceinline__ void fold_tile_sample(const f32x16 (&acc)[NI][NJ], Tr
   }
 }
 
-// Store one finished accumulator tile as a dense layer's output (same register layout as fold_tile):
-// out[row, col] = act(acc + bias[col]) + residual[row, col], rounded once to bf16.  A lane holds runs of 4
-// consecutive columns of one row: 8-byte stores.  Columns come in fours, so n_valid must be a multiple of 4.
-// The loads the epilogue needs are issued in batches ahead of their use (the bias of all the lane's columns
-// once, the residual of a whole 32-row block at a time): one memory round trip per batch instead of one per
-// run, during which the matrix cores have nothing to do.
-template <int NI, int NJ>
-__device__ __forceinline__ void store_tile(const f32x16 (&acc)[NI][NJ], const LogitsArgs& a, int row_base, int r_end,
-                                           int col_base, int n_valid) {
-  const int lane31 = threadIdx.x & 31;
-  float4 bias[NI][4];
-#pragma unroll
-  for (int i = 0; i < NI; ++i)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int col = col_base + i * 32 + g * 8;
-      bias[i][g] = (a.bias && col < n_valid) ? *reinterpret_cast<const float4*>(a.bias + col) : float4{0.f, 0.f, 0.f, 0.f};
-    }
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-    const int row = row_base + j * 32 + lane31;
-    const bool row_ok = row < r_end;
-    uint2 res[NI][4];
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int col = col_base + i * 32 + g * 8;
-        res[i][g] = (a.residual && row_ok && col < n_valid)
-                        ? *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(a.residual) +
-                                                          (size_t)row * a.ldo + col)
-                        : uint2{0u, 0u};
-      }
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int col = col_base + i * 32 + g * 8;
-        float x[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = read_acc(acc[i][j][g * 4 + e]);
-        x[0] += bias[i][g].x;
-        x[1] += bias[i][g].y;
-        x[2] += bias[i][g].z;
-        x[3] += bias[i][g].w;
-        if (a.act == 1) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) x[e] = gelu_erf(x[e]);
-        }
-        x[0] += __uint_as_float(res[i][g].x << 16);
-        x[1] += __uint_as_float(res[i][g].x & 0xFFFF0000u);
-        x[2] += __uint_as_float(res[i][g].y << 16);
-        x[3] += __uint_as_float(res[i][g].y & 0xFFFF0000u);
-        if (row_ok && col < n_valid) {
-          uint2 o;
-          o.x = bf16_bits_rne(x[0]) | (bf16_bits_rne(x[1]) << 16);
-          o.y = bf16_bits_rne(x[2]) | (bf16_bits_rne(x[3]) << 16);
-          *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.out) + (size_t)row * a.ldo + col) = o;
-        }
-      }
-    }
-  }
-}
-
-// The same with the residual and the output in fp32 (no rounding): 16-byte loads and stores.
-template <int NI, int NJ>
-__device__ __forceinline__ void store_tile_f32(const f32x16 (&acc)[NI][NJ], const LogitsArgs& a, int row_base, int r_end,
-                                               int col_base, int n_valid) {
-  const int lane31 = threadIdx.x & 31;
-  const float* res = reinterpret_cast<const float*>(a.residual);
-  float* out = reinterpret_cast<float*>(a.out);
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-    const int row = row_base + j * 32 + lane31;
-    if (row >= r_end) continue;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      float4 rv[4], bv[4];
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int col = col_base + i * 32 + g * 8;
-        const bool ok = col < n_valid;
-        rv[g] = (res && ok) ? *reinterpret_cast<const float4*>(res + (size_t)row * a.ldo + col) : float4{0.f, 0.f, 0.f, 0.f};
-        bv[g] = (a.bias && ok) ? *reinterpret_cast<const float4*>(a.bias + col) : float4{0.f, 0.f, 0.f, 0.f};
-      }
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int col = col_base + i * 32 + g * 8;
-        float x[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = read_acc(acc[i][j][g * 4 + e]);
-        x[0] += bv[g].x;
-        x[1] += bv[g].y;
-        x[2] += bv[g].z;
-        x[3] += bv[g].w;
-        if (a.act == 1) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) x[e] = gelu_erf(x[e]);
-        }
-        if (col < n_valid)
-          *reinterpret_cast<float4*>(out + (size_t)row * a.ldo + col) =
-              float4{x[0] + rv[g].x, x[1] + rv[g].y, x[2] + rv[g].z, x[3] + rv[g].w};
-      }
-    }
-  }
-}
-
 // Store one finished accumulator tile as it is (fp32), for a dense layer whose K range is split over several
 // workgroups: 16-byte stores.
 template <int NI, int NJ>
@@ -482,48 +375,6 @@ __device__ __forceinline__ void store_partial_tile(const f32x16 (&acc)[NI][NJ], 
         x.z = read_acc(acc[i][j][q * 4 + 2]);
         x.w = read_acc(acc[i][j][q * 4 + 3]);
         if (row < r_end && col < n_valid) *reinterpret_cast<float4*>(part + (size_t)row * ld + col) = x;
-      }
-    }
-  }
-}
-
-// Store one finished accumulator tile as the gradient of the loss with respect to the logits (same register
-// layout as fold_tile; see LogitsArgs, probability mode).  Columns come in fours; ldo is a multiple of 4.
-template <int NI, int NJ>
-__device__ __forceinline__ void store_prob_tile(const f32x16 (&acc)[NI][NJ], const LogitsArgs& a, int row_base, int r_end,
-                                                int col_base, int n_valid) {
-  const int lane31 = threadIdx.x & 31;
-  float lse[NJ], g[NJ];
-  int tgt[NJ];
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-    const int row = row_base + j * 32 + lane31;
-    const bool ok = row < r_end;
-    lse[j] = ok ? a.lse[row] : 0.f;
-    g[j] = ok ? a.row_grad[row] : 0.f;
-    tgt[j] = ok ? a.targets[row] - a.col0 : -1;
-  }
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-    const int row = row_base + j * 32 + lane31;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int col = col_base + i * 32 + q * 8;
-        float x[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float z = read_acc(acc[i][j][q * 4 + e]);
-          const float p = __expf(z - lse[j]) - (col + e == tgt[j] ? 1.f : 0.f);
-          x[e] = col + e < n_valid ? g[j] * p : 0.f;
-        }
-        if (row < r_end && col < a.ldo) {
-          uint2 o;
-          o.x = bf16_bits_rne(x[0]) | (bf16_bits_rne(x[1]) << 16);
-          o.y = bf16_bits_rne(x[2]) | (bf16_bits_rne(x[3]) << 16);
-          *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.out) + (size_t)row * a.ldo + col) = o;
-        }
       }
     }
   }

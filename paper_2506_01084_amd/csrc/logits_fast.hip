@@ -1,34 +1,39 @@
 // extended_logits, bf16 MFMA kernel for gfx950 (d a multiple of 64), one wave per SIMD.
 //
 // Workgroup tile 256 (vocabulary rows, MFMA "A") x 256 (hidden rows, MFMA "B"), 4 waves in a 2 x 2 grid,
-// each wave 128 x 128 = 4 x 4 blocks of v_mfma_f32_32x32x16_bf16 (256 accumulator registers per lane):
-// per 16-deep k-step a wave reads 8 operand fragments from LDS for 16 MFMAs.  With one wave per SIMD all
-// overlap is inside the instruction stream: the fragments of k-step t+1 are read while the MFMAs of
-// k-step t run, and the global->LDS requests of slab s+2 are handed out one pair at a time between the
-// MFMAs that follow the hand-over of slab s.  (F_WAVES = 8 builds the same kernel with two waves per SIMD,
-// each 128 x 64; measured equal, so the default stays at the layout with the larger register tiles.)
+// each wave 128 x 128 = 8 x 8 blocks of v_mfma_f32_16x16x32_bf16 (256 accumulator registers per lane):
+// per 32-deep k-step a wave reads 16 operand fragments from LDS for 64 MFMAs.  What bounds it is the power limit
+// (the clock falls to 1.5-1.8 GHz under it), so the form of the matrix instruction counts: 32 x 32 x 16 moves the
+// accumulators once per 16 of K, 16 x 16 x 32 once per 32, for the same operand bytes.  32768 x 4096 outputs, K = 128256:
+// 25.4 ms with 32 x 32 x 16 in this schedule, 23.2 with 16 x 16 x 32 (27.2 with 32 x 32 x 16 and one hand-over per slab).
 //
-// K advances in slabs of 64 elements (128 bytes per row, four k-steps): the global -> LDS stream moves
+// K advances in slabs of 64 elements (128 bytes per row, two k-steps): the global -> LDS stream moves
 // whole 128-byte lines, which it does markedly faster than half lines (measured on a bare streaming
 // kernel: 14-22 TB/s against 12-15 TB/s out of L2).  Both operand tiles of a slab (2 x 32 KiB) go straight
-// from global memory into LDS (16-byte global_load ... lds), two stages.  Once per slab, in the middle of
-// its last k-step, the waves meet at a barrier: at that point everybody has read the slab completely (its
-// stage is refilled with slab s+2) and slab s+1 has landed (its first fragments are read next).  The stream
-// runs on across the vocabulary tiles of a strip.  The refill requests are spread over the following
-// ~35 MFMAs: issued as one burst they back up the memory pipeline, the wave then stalls on its next
-// request, and a stalled wave issues no MFMAs (measured: 28.9 ms as a burst, 26.3 ms spread, 22.9 ms with
-// no requests at all on the 32768 x 4096 x 128256 problem); spread over the whole slab they would land
-// too late for the next hand-over.
+// from global memory into LDS (16-byte global_load ... lds), two stages.  With one wave per SIMD all overlap is
+// inside the instruction stream.  A slab's 128 MFMAs are slots, and between them go, each at a slot of its own
+// (kRead2 ... below):
+//   - the 16 fragment reads of the second k-step, then a barrier (everybody holds the rest of slab s in registers:
+//     its stage is free) and the 16 requests for slab s+2, six MFMAs apart;
+//   - late in the second k-step a wait for slab s+1 and a second barrier (it has landed for everybody), then the 16
+//     fragment reads of its first k-step.
+// Freeing the stage that early gives a request more than a slab's time to land; with one barrier per slab for both
+// purposes the same product takes 26.0-26.4 ms.  Taking the waits or the barriers out changes nothing any more (23.1-23.4
+// ms, in a build for timing): fewer stall cycles are answered by a lower clock.  Requests closer together are slower (every
+// 3 MFMAs 25.3 ms, every 4 24.8, 5 24.4, 6 24.1 in one run), and so are the fragment reads spread over twice the slots.
+// The stream runs on across the vocabulary tiles of a strip.
 //
 // LDS layout of an operand tile: row r = 128 bytes = 8 chunks of 16 B; chunk c is stored at position
 // c ^ ((r >> 1) & 7).  The LDS has 64 four-byte banks and serves a 16-byte-per-lane read 16 lanes at a
 // time; an MFMA operand read has 16 consecutive lanes on 16 consecutive rows at one logical chunk, whose
 // bank group is (r & 1) * 8 + position -- all 16 distinct with this swizzle.
 //
-// In the 32x32 result block a lane holds 16 vocabulary entries of one hidden row, so the running
-// (max, sum-exp, argmax) of the joint softmax (zip2zip paper, section 2.3, step 8) lives in registers
-// and crosses lanes once per strip.
+// In the 16 x 16 result block a lane holds 4 vocabulary entries of one hidden row (of 8 rows and 32 entries each in the
+// whole tile), so the running (max, sum-exp, argmax) of the joint softmax (zip2zip paper, section 2.3, step 8) lives in
+// registers and crosses lanes once per strip.
 #include "logits_common.h"
+
+#include <utility>
 
 namespace {
 
@@ -38,67 +43,56 @@ constexpr int FT = 256;                   // tile edge, vocabulary and hidden ro
 constexpr int F_SLAB = 128;               // bytes per row per K slab (64 bf16)
 constexpr int F_OPER = FT * F_SLAB;       // one operand tile of one slab: 32 KiB
 constexpr int F_STAGE = 2 * F_OPER;       // A + B
-constexpr int F_NSTAGE = 2;
-constexpr int F_LDS = F_NSTAGE * F_STAGE; // 128 KiB
-#ifndef F_WAVES
-#define F_WAVES 4
-#endif
-constexpr int F_THREADS = 64 * F_WAVES;
-// waves: 2 along the vocabulary rows (128 each: 4 MFMA blocks), F_WAVES / 2 along the hidden rows
-constexpr int F_NI = 4;
-constexpr int F_WR = F_WAVES / 2;
-constexpr int F_NJ = FT / (F_WR * 32);                 // MFMA blocks of a wave along the hidden rows
-constexpr int F_KSTEP = F_NI * F_NJ;                   // MFMAs of a wave per k-step
-constexpr int F_PAIRS = 32 / F_WAVES;                  // request pairs (8 rows of A + 8 rows of B) per wave and slab
-#ifndef F_SPREAD
-#define F_SPREAD (F_WAVES == 4 ? 5 : 4)
-#endif
-// Pacing of the two operand paths inside the MFMA stream.  With one wave per SIMD, and the four waves of a
-// workgroup in step (they meet at a barrier every slab), whatever a wave issues as a burst arrives at the LDS or
-// at the memory pipeline together with the other waves' bursts, and the MFMAs wait behind it.  Measured on the
-// 32768 x 4096 x 128256 problem, same box, each step on top of the previous one: fragment reads of the next
-// k-step one per MFMA instead of eight ahead of the k-step: -2.1 %; the same for the first k-step of the next slab
-// after the hand-over barrier: -1.4 %; the two requests of a pair two MFMAs apart (a request every 2-3 MFMAs)
-// instead of back to back every five: -0.7 %.  Closer spacing of the requests (every 1.5 MFMAs) or wider (every 3,
-// 3.5) is slower, and so are reads that start right at the first MFMA of a k-step.
-//   F_LDS_SPREAD       1 = read n of the next k-step goes out after MFMA F_RD_FIRST + n * F_RD_EVERY of the
-//                      current one (in the order of first use), 0 = all eight ahead of the k-step
-//   F_HANDOVER_SPREAD  1 = the same for the reads that follow the hand-over barrier
-//   F_SPLIT_PAIR       n > 0 = the hidden-row request of a pair goes out n MFMAs after the vocabulary-row one
-#ifndef F_LDS_SPREAD
-#define F_LDS_SPREAD 1
-#endif
-#ifndef F_SPLIT_PAIR
-#define F_SPLIT_PAIR 2
-#endif
-#ifndef F_HANDOVER_SPREAD
-#define F_HANDOVER_SPREAD 1
-#endif
-#ifndef F_RD_FIRST
-#define F_RD_FIRST 3
-#endif
-#ifndef F_RD_EVERY
-#define F_RD_EVERY 1
-#endif
-// Request pair i goes out after the MFMA with window index 1 + i * F_SPREAD, counted from the slab
-// hand-over: first the rest of the hand-over k-step (F_KSTEP - F_NJ MFMAs), then the first three k-steps
-// of the next slab.
-#ifndef F_ROTATE_FEW
-#define F_ROTATE_FEW 1                   // 0: the rotated-K instances (see the kernel) are never launched
-#endif
-#ifndef F_HO_ROWS
-#define F_HO_ROWS 1
-#endif
-#ifndef F_HO_RD_FIRST
-#define F_HO_RD_FIRST F_RD_FIRST
-#endif
-constexpr int F_REST = F_KSTEP - F_HO_ROWS * F_NJ;   // MFMAs of the hand-over k-step that follow the barrier
-static_assert(!F_LDS_SPREAD || !F_HANDOVER_SPREAD || F_HO_RD_FIRST + (F_NI + F_NJ - 1) * F_RD_EVERY < F_REST,
-              "the reads after the hand-over must all go out before the k-step ends");
-static_assert(!F_LDS_SPREAD || F_RD_FIRST + (F_NI + F_NJ - 1) * F_RD_EVERY < F_KSTEP, "reads of a k-step must fit it");
-constexpr int F_LAST_IN_HANDOVER = (F_REST - 2) / F_SPREAD;          // last pair issued before the slab ends
-static_assert(F_LAST_IN_HANDOVER < F_PAIRS, "spread too small for this layout");
-static_assert(1 + (F_PAIRS - 1) * F_SPREAD < F_REST + 3 * F_KSTEP, "all pairs must be out before the next hand-over");
+constexpr int F_LDS = 2 * F_STAGE;        // 128 KiB
+constexpr int F_THREADS = 256;
+constexpr int F_N = 8;                    // MFMA blocks of a wave along either side (128 x 128)
+constexpr int F_PAIRS = 8;                // request pairs (8 rows of A + 8 rows of B) per wave and slab
+constexpr int F_SLOTS = 2 * F_N * F_N;    // MFMAs of a wave per slab
+
+// What goes out after which MFMA of a slab (barriers: ahead of it).
+constexpr int kRead2 = 0;                 // 16 fragment reads of the second k-step, one per MFMA
+constexpr int kFree = 24;                 // barrier: slab s is in registers
+constexpr int kRequest = 26;              // 16 requests for slab s+2 ...
+constexpr int kRequestEvery = 6;          // ... this far apart
+constexpr int kLanded = 110;              // wait + barrier: slab s+1 is there
+constexpr int kRead1 = 110;               // 16 fragment reads of its first k-step, one per MFMA
+constexpr int kOutAtLanded = (kLanded - kRequest + kRequestEvery - 1) / kRequestEvery;     // requests out ahead of that wait
+static_assert(kFree > kRead2 + 15 && kRequest >= kFree && kRequest + 15 * kRequestEvery < F_SLOTS, "stage s is refilled after its last read");
+static_assert(kRead1 >= kLanded && kRead1 + 15 < F_SLOTS && kLanded > F_SLOTS / 2, "slab s+1 is read after it landed, into registers that are free");
+static_assert(kOutAtLanded <= 2 * F_PAIRS, "");
+
+// f(0) ... f(N - 1) with the index a constant.
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+
+// acc += a * b, or a * b where nothing has been accumulated yet.  Spelled as an instruction: left to the compiler the
+// accumulators are copied about (it knows 16 x 16 blocks of four registers, and allots them anew between the uses),
+// and MFMAs drift across the barriers and requests between which they were put.  The compiler does not know then that an
+// MFMA's result takes its time: see wait_for_mfma.
+template <bool FIRST>
+__device__ __forceinline__ void mfma(f32x4& acc, const uint4& a, const uint4& b) {
+  if (FIRST)
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc) : "v"(__builtin_bit_cast(bf16x8, a)), "v"(__builtin_bit_cast(bf16x8, b)));
+  else
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(__builtin_bit_cast(bf16x8, a)), "v"(__builtin_bit_cast(bf16x8, b)));
+}
+
+// Ahead of the first read of an accumulator: more wait states than any MFMA's result needs.
+__device__ __forceinline__ void wait_for_mfma() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+
+// Waves of the workgroup meet.  (Not __syncthreads, which waits for all outstanding requests as well.)
+__device__ __forceinline__ void barrier_after_lds() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 constexpr int vmcnt_imm(int n) { return (n & 0xF) | ((n >> 4) << 14) | 0x0F70; }
 
 // 16 bytes per lane, global -> LDS without passing through registers: address = 64-bit scalar base +
@@ -175,9 +169,354 @@ __device__ __forceinline__ bool map_rows_dev(const LogitsArgs& a, int bid, int r
 }
 
 struct Frags {
-  uint4 a[F_NI];
-  uint4 b[F_NJ];
+  uint4 a[F_N];
+  uint4 b[F_N];
 };
+
+typedef f32x4 Acc[F_N][F_N];
+
+// ---- epilogues: acc[i][j] is a 16 x 16 result block, register e of this lane is the value of hidden row
+// row_base + j * 16 + (lane & 15) and column col_base + i * 16 + e, where col_base already holds the tile origin, the wave's
+// offset and (lane >> 4) * 4.
+
+// Columns at and beyond n_valid do not exist: they read as -inf.  (A pass of its own over the accumulators of the one
+// tile of a matrix that has such columns: with the tests in the fold, or a second fold with them, the registers of
+// both are more than there are.)
+__device__ __forceinline__ void mask_tail16(Acc& acc, int col_base, int n_valid) {
+#pragma unroll
+  for (int i = 0; i < F_N; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool ok = col_base + i * 16 + e < n_valid;
+#pragma unroll
+      for (int j = 0; j < F_N; ++j) {
+        const float x = read_acc(acc[i][j][e]);
+        float y;
+        asm volatile("v_accvgpr_write_b32 %0, %1" : "=a"(y) : "v"(ok ? x : kNegInf));
+        acc[i][j][e] = y;
+      }
+    }
+}
+
+// Fold one finished tile into the running triples, 16 values of a row at a time, in increasing column order per lane, so
+// strict comparisons keep the lowest column among equal maxima.  The running sum is kept against the running maximum in
+// base-2 units: exp(x - m) is one multiply-add and one hardware exponential.
+__device__ __forceinline__ void fold_tile16(const Acc& acc, Triple (&run)[F_N], int col_base, int col0) {
+  constexpr float kLog2e = 1.4426950408889634f;
+#pragma unroll
+  for (int j = 0; j < F_N; ++j) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      float x[16];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) x[v] = read_acc(acc[h * 4 + (v >> 2)][j][v & 3]);
+      float gmax = max3(x[0], x[1], x[2]);
+#pragma unroll
+      for (int v = 3; v < 15; v += 2) gmax = max3(gmax, x[v], x[v + 1]);
+      gmax = max3(gmax, x[15], x[15]);
+      if (gmax > run[j].m) {
+        int targ = 15;
+#pragma unroll
+        for (int v = 14; v >= 0; --v) targ = (x[v] == gmax) ? v : targ;
+        run[j].s = (run[j].m == kNegInf) ? 0.f : run[j].s * __expf(run[j].m - gmax);
+        run[j].m = gmax;
+        run[j].i = col0 + col_base + h * 64 + (targ >> 2) * 16 + (targ & 3);
+      }
+      if (run[j].m != kNegInf) {
+        const float m2 = -run[j].m * kLog2e;
+        float add0 = 0.f, add1 = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; v += 2) {
+          add0 += __builtin_amdgcn_exp2f(fmaf(x[v], kLog2e, m2));
+          add1 += __builtin_amdgcn_exp2f(fmaf(x[v + 1], kLog2e, m2));
+        }
+        run[j].s += add0 + add1;
+      }
+    }
+  }
+}
+
+// The same for a filtered sampled pick: x = logit * inv_temperature enters the running triple and is stored,
+// fp32, at logits[row, col0 + column] (the selection kernels read the rows back); 16-byte stores where the four
+// columns of a group all exist.
+__device__ __forceinline__ void fold_store16(const Acc& acc, Triple (&run)[F_N], const LogitsArgs& a, int row_base, int r_end,
+                                             int col_base, int n_valid) {
+  const int lane15 = threadIdx.x & 15;
+#pragma unroll
+  for (int j = 0; j < F_N; ++j) {
+    const int row = row_base + j * 16 + lane15;
+    float* out = a.logits + (size_t)min(row, r_end - 1) * a.ld + a.col0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      float x[16];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int col = col_base + h * 64 + (v >> 2) * 16 + (v & 3);
+        const float z = read_acc(acc[h * 4 + (v >> 2)][j][v & 3]);
+        x[v] = col < n_valid ? z * a.inv_temperature : kNegInf;
+      }
+      float gmax = x[0];
+#pragma unroll
+      for (int v = 1; v < 16; ++v) gmax = fmaxf(gmax, x[v]);
+      if (gmax > run[j].m) {
+        int targ = 15;
+#pragma unroll
+        for (int v = 14; v >= 0; --v) targ = (x[v] == gmax) ? v : targ;
+        run[j].s = (run[j].m == kNegInf) ? 0.f : run[j].s * __expf(run[j].m - gmax);
+        run[j].m = gmax;
+        run[j].i = a.col0 + col_base + h * 64 + (targ >> 2) * 16 + (targ & 3);
+      }
+      if (run[j].m != kNegInf) {
+        const float m = run[j].m;
+        float add = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) add += __expf(x[v] - m);
+        run[j].s += add;
+      }
+      if (row < r_end) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int col = col_base + h * 64 + q * 16;
+          // (a row of the logits starts 4-byte aligned only: ld = V + cap is any number)
+          if (col + 3 < n_valid && ((((size_t)row * a.ld + a.col0 + col) & 3) == 0)) {
+            *reinterpret_cast<float4*>(out + col) = float4{x[q * 4], x[q * 4 + 1], x[q * 4 + 2], x[q * 4 + 3]};
+          } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+              if (col + k < n_valid) out[col + k] = x[q * 4 + k];
+          }
+        }
+      }
+    }
+  }
+}
+
+// The same for a sampled pick: x = logit * inv_temperature enters the running triple, and x + Gumbel(u[row, col]) the
+// running draw.  A lane's columns come in aligned fours (one generator call each) and in increasing order, so a strict
+// comparison keeps the lowest column among equal values.  The four groups of 16 values are a real loop (the generator
+// is long: unrolled 64 times per tile it would not fit the register file next to the accumulators).
+__device__ __forceinline__ void fold_sample16(const Acc& acc, Triple (&run)[F_N], Draw (&draw)[F_N], const LogitsArgs& a,
+                                              int row_base, int col_base, int n_valid) {
+  const int lane15 = threadIdx.x & 15;
+#pragma unroll
+  for (int j = 0; j < F_N; ++j) {
+    const uint32_t row = (uint32_t)(row_base + j * 16 + lane15);
+    Triple t = run[j];
+    Draw dr = draw[j];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      float x[16];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) x[v] = read_acc(acc[h * 4 + (v >> 2)][j][v & 3]);
+#pragma unroll 1
+      for (int q = 0; q < 4; ++q) {
+        const int c0 = a.col0 + col_base + h * 64 + q * 16;
+        const uint4 w = philox4x32_10(uint4{(uint32_t)(c0 >> 2), row, a.ctr2, a.ctr3}, a.key0, a.key1);
+        const uint32_t word[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const float xv = q == 0 ? x[k] : (q == 1 ? x[4 + k] : (q == 2 ? x[8 + k] : x[12 + k]));
+          // (columns past the last valid one: -inf never enters the triple or wins the draw)
+          const bool ok = c0 - a.col0 + k < n_valid;
+          const float z = ok ? xv * a.inv_temperature : kNegInf;
+          if (z > t.m) {
+            t.s = (t.m == kNegInf) ? 1.f : t.s * __expf(t.m - z) + 1.f;
+            t.m = z;
+            t.i = c0 + k;
+          } else if (ok) {
+            t.s += __expf(z - t.m);
+          }
+          const float pv = z + gumbel_from_word(word[k]);
+          if (pv > dr.v) {
+            dr.v = pv;
+            dr.l = z;
+            dr.i = c0 + k;
+          }
+        }
+      }
+    }
+    run[j] = t;
+    draw[j] = dr;
+  }
+}
+
+// Eight consecutive columns per lane from two blocks' fours: lanes of the even quarter-waves (lane >> 4) get block i's
+// columns, the odd ones block i + 1's, the lower half of the wave columns 0-7 and the upper 8-15 of it.  `lo`, `hi`: this
+// lane's four bf16 of block i and of block i + 1.
+__device__ __forceinline__ uint4 eight_columns(uint2 lo, uint2 hi) {
+  const auto x = __builtin_amdgcn_permlane16_swap(lo.x, hi.x, false, false);
+  const auto y = __builtin_amdgcn_permlane16_swap(lo.y, hi.y, false, false);
+  return uint4{x[0], y[0], x[1], y[1]};
+}
+
+// Rounds to nearest even (one instruction for two values).
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+  typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+  typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
+
+// Stores two blocks' bf16 (columns col_base + i * 16 ..., and the next 16) of one row in 16-byte pieces; columns come in
+// fours, and n_valid and the row pitch are multiples of 8 (the layers' widths are).
+__device__ __forceinline__ void store_two_blocks(uint16_t* out_row, bool row_ok, int col_base, int i, uint2 lo, uint2 hi,
+                                                 int n_valid) {
+  const uint4 v = eight_columns(lo, hi);
+  const int quarter = (threadIdx.x >> 4) & 3;
+  const int col = col_base - quarter * 4 + (i + (quarter & 1)) * 16 + (quarter >> 1) * 8;
+  if (row_ok && col < n_valid) *reinterpret_cast<uint4*>(out_row + col) = v;
+}
+
+// Store one finished tile as a dense layer's output: out[row, col] = act(acc + bias[col]) + residual[row, col], rounded
+// once to bf16.  The loads the epilogue needs are issued in batches ahead of their use (the bias of all the lane's
+// columns once, the residual of 16 rows at a time): one memory round trip per batch, during which the matrix cores
+// have nothing to do.
+__device__ __forceinline__ void store_tile16(const Acc& acc, const LogitsArgs& a, int row_base, int r_end, int col_base,
+                                             int n_valid) {
+  const int lane15 = threadIdx.x & 15;
+  float4 bias[F_N];
+#pragma unroll
+  for (int i = 0; i < F_N; ++i) {
+    const int col = col_base + i * 16;
+    bias[i] = (a.bias && col < n_valid) ? *reinterpret_cast<const float4*>(a.bias + col) : float4{0.f, 0.f, 0.f, 0.f};
+  }
+#pragma unroll
+  for (int j = 0; j < F_N; ++j) {
+    const int row = row_base + j * 16 + lane15;
+    const bool row_ok = row < r_end;
+    uint16_t* out_row = reinterpret_cast<uint16_t*>(a.out) + (size_t)row * a.ldo;
+    uint2 res[F_N];
+#pragma unroll
+    for (int i = 0; i < F_N; ++i) {
+      const int col = col_base + i * 16;
+      res[i] = (a.residual && row_ok && col < n_valid)
+                   ? *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(a.residual) + (size_t)row * a.ldo + col)
+                   : uint2{0u, 0u};
+    }
+    uint2 o[F_N];
+#pragma unroll
+    for (int i = 0; i < F_N; ++i) {
+      float x[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = read_acc(acc[i][j][e]);
+      x[0] += bias[i].x;
+      x[1] += bias[i].y;
+      x[2] += bias[i].z;
+      x[3] += bias[i].w;
+      if (a.act == 1) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = gelu_erf(x[e]);
+      }
+      x[0] += __uint_as_float(res[i].x << 16);
+      x[1] += __uint_as_float(res[i].x & 0xFFFF0000u);
+      x[2] += __uint_as_float(res[i].y << 16);
+      x[3] += __uint_as_float(res[i].y & 0xFFFF0000u);
+      o[i] = uint2{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3])};
+    }
+#pragma unroll
+    for (int i = 0; i < F_N; i += 2) store_two_blocks(out_row, row_ok, col_base, i, o[i], o[i + 1], n_valid);
+  }
+}
+
+// The same with the residual and the output in fp32 (no rounding): 16-byte loads and stores.
+__device__ __forceinline__ void store_tile16_f32(const Acc& acc, const LogitsArgs& a, int row_base, int r_end, int col_base,
+                                                 int n_valid) {
+  const int lane15 = threadIdx.x & 15;
+  const float* res = reinterpret_cast<const float*>(a.residual);
+  float* out = reinterpret_cast<float*>(a.out);
+  float4 bias[F_N];
+#pragma unroll
+  for (int i = 0; i < F_N; ++i) {
+    const int col = col_base + i * 16;
+    bias[i] = (a.bias && col < n_valid) ? *reinterpret_cast<const float4*>(a.bias + col) : float4{0.f, 0.f, 0.f, 0.f};
+  }
+#pragma unroll
+  for (int j = 0; j < F_N; ++j) {
+    const int row = row_base + j * 16 + lane15;
+    if (row >= r_end) continue;
+    float4 rv[F_N];
+#pragma unroll
+    for (int i = 0; i < F_N; ++i) {
+      const int col = col_base + i * 16;
+      const bool ok = col < n_valid;
+      rv[i] = (res && ok) ? *reinterpret_cast<const float4*>(res + (size_t)row * a.ldo + col) : float4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int i = 0; i < F_N; ++i) {
+      const int col = col_base + i * 16;
+      float x[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = read_acc(acc[i][j][e]);
+      x[0] += bias[i].x;
+      x[1] += bias[i].y;
+      x[2] += bias[i].z;
+      x[3] += bias[i].w;
+      if (a.act == 1) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = gelu_erf(x[e]);
+      }
+      if (col < n_valid)
+        *reinterpret_cast<float4*>(out + (size_t)row * a.ldo + col) =
+            float4{x[0] + rv[i].x, x[1] + rv[i].y, x[2] + rv[i].z, x[3] + rv[i].w};
+    }
+  }
+}
+
+// Store one finished tile as it is (fp32), for a dense layer whose K range is split over several workgroups.
+__device__ __forceinline__ void store_partial16(const Acc& acc, float* part, int ld, int row_base, int r_end, int col_base,
+                                                int n_valid) {
+  const int lane15 = threadIdx.x & 15;
+#pragma unroll
+  for (int j = 0; j < F_N; ++j) {
+    const int row = row_base + j * 16 + lane15;
+#pragma unroll
+    for (int i = 0; i < F_N; ++i) {
+      const int col = col_base + i * 16;
+      float4 x;
+      x.x = read_acc(acc[i][j][0]);
+      x.y = read_acc(acc[i][j][1]);
+      x.z = read_acc(acc[i][j][2]);
+      x.w = read_acc(acc[i][j][3]);
+      if (row < r_end && col < n_valid) *reinterpret_cast<float4*>(part + (size_t)row * ld + col) = x;
+    }
+  }
+}
+
+// Store one finished tile as the gradient of the loss with respect to the logits (see LogitsArgs, probability mode).
+// Columns come in fours; ldo is a multiple of 64.
+__device__ __forceinline__ void store_prob16(const Acc& acc, const LogitsArgs& a, int row_base, int r_end, int col_base,
+                                             int n_valid) {
+  const int lane15 = threadIdx.x & 15;
+  float lse[F_N], g[F_N];
+  int tgt[F_N];
+#pragma unroll
+  for (int j = 0; j < F_N; ++j) {
+    const int row = row_base + j * 16 + lane15;
+    const bool ok = row < r_end;
+    lse[j] = ok ? a.lse[row] : 0.f;
+    g[j] = ok ? a.row_grad[row] : 0.f;
+    tgt[j] = ok ? a.targets[row] - a.col0 : -1;
+  }
+#pragma unroll
+  for (int j = 0; j < F_N; ++j) {
+    const int row = row_base + j * 16 + lane15;
+    uint16_t* out_row = reinterpret_cast<uint16_t*>(a.out) + (size_t)row * a.ldo;
+    uint2 o[F_N];
+#pragma unroll
+    for (int i = 0; i < F_N; ++i) {
+      const int col = col_base + i * 16;
+      float x[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float z = read_acc(acc[i][j][e]);
+        const float p = __expf(z - lse[j]) - (col + e == tgt[j] ? 1.f : 0.f);
+        x[e] = col + e < n_valid ? g[j] * p : 0.f;
+      }
+      o[i] = uint2{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3])};
+    }
+#pragma unroll
+    for (int i = 0; i < F_N; i += 2) store_two_blocks(out_row, row < r_end, col_base, i, o[i], o[i + 1], a.ldo);
+  }
+}
 
 // MODE 8 and 9 are measurement probes of the base part (their results are NOT the logits' reduction): 8 stops
 // requesting operands after the first two slabs (the matrix cores, the LDS reads and the fold run as usual on
@@ -198,7 +537,7 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wv = wave & 1;    // which 128 vocabulary rows of the tile
-  const int wr = wave >> 1;   // which F_NJ * 32 hidden rows of the tile
+  const int wr = wave >> 1;   // which 128 hidden rows of the tile
 
   int rt, st;
   int r0, r_end, n_valid;
@@ -254,10 +593,10 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
                           : (int)(row_bytes / F_SLAB);
   if (MODE == 2 && a.k_dev) n_slabs = max(1, min(n_slabs, (*a.k_dev * 2 + F_SLAB - 1) / F_SLAB));
 
-  Triple run[F_NJ];
-  Draw draw[F_NJ];                                   // MODE 6 only
+  Triple run[F_N];
+  Draw draw[F_N];                                   // MODE 6 only
 #pragma unroll
-  for (int j = 0; j < F_NJ; ++j) {
+  for (int j = 0; j < F_N; ++j) {
     run[j] = empty_triple();
     draw[j] = empty_draw();
   }
@@ -306,13 +645,14 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
       is_gb = Hp + (size_t)sl * F_SLAB;
     }
   };
-#define Z2Z_ISSUE_PAIR(i)                                             \
-  do {                                                                \
-    load16_to_lds<(i) * 1024>(is_ga, voffA[i], isA);                  \
-    load16_to_lds<F_OPER + (i) * 1024>(is_gb, voffB[i], isA);         \
-  } while (0)
-#define Z2Z_ISSUE_A(i) load16_to_lds<(i) * 1024>(is_ga, voffA[i], isA)
-#define Z2Z_ISSUE_B(i) load16_to_lds<F_OPER + (i) * 1024>(is_gb, voffB[i], isA)
+  // request n of the 16 of a slab: 8 rows of the vocabulary tile (n even) or of the hidden rows' (n odd)
+  auto request = [&](auto n_) __attribute__((always_inline)) {
+    constexpr int n = decltype(n_)::value;
+    if constexpr (n & 1)
+      load16_to_lds<F_OPER + (n >> 1) * 1024>(is_gb, voffB[n >> 1], isA);
+    else
+      load16_to_lds<(n >> 1) * 1024>(is_ga, voffA[n >> 1], isA);
+  };
   auto issue_end = [&]() {
     if (lvt < vt_end && ++lslab == n_slabs) {
       lslab = 0;
@@ -322,261 +662,167 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
   };
   // ---- MFMA operand addresses (bytes inside an operand tile), swizzle folded in ---------------------
   const int sw = (lane >> 1) & 7;   // ((row >> 1) & 7) of every row this lane reads
-  const int half = lane >> 5;
-  const int offA0 = (wv * 128 + (lane & 31)) * F_SLAB;
-  const int offB0 = (wr * (F_NJ * 32) + (lane & 31)) * F_SLAB;
-  auto read_frags = [&](Frags& f, int stage, int q) {
-    const unsigned char* A = lds + stage * F_STAGE + offA0 + (((2 * q + half) ^ sw) << 4);
-    const unsigned char* Bt = lds + stage * F_STAGE + F_OPER + offB0 + (((2 * q + half) ^ sw) << 4);
-#pragma unroll
-    for (int i = 0; i < F_NI; ++i) f.a[i] = *reinterpret_cast<const uint4*>(A + i * 32 * F_SLAB);
-#pragma unroll
-    for (int j = 0; j < F_NJ; ++j) f.b[j] = *reinterpret_cast<const uint4*>(Bt + j * 32 * F_SLAB);
-  };
-
-  // one fragment of a k-step, so that the reads of the next k-step can be handed out between the MFMAs of the
-  // current one; n counts them in the order the MFMAs (vocabulary block i outer, hidden-row block j inner) first
-  // need them: b0, a0, b1 .. b(NJ-1), a1 .. a(NI-1)
-  auto read_one = [&](Frags& f, int stage, int q, int n) {
-    const int base = stage * F_STAGE + (((2 * q + half) ^ sw) << 4);
-    const bool is_a = n == 1 || n > F_NJ;
-    const int idx = n == 0 ? 0 : (n == 1 ? 0 : (n <= F_NJ ? n - 1 : n - F_NJ));
-    if (is_a)
-      f.a[idx] = *reinterpret_cast<const uint4*>(lds + base + offA0 + idx * 32 * F_SLAB);
+  const int quarter = lane >> 4;    // which 8 of a k-step's 32 elements
+  const int offA0 = (wv * 128 + (lane & 15)) * F_SLAB;
+  const int offB0 = (wr * 128 + (lane & 15)) * F_SLAB;
+  // fragment n of k-step q of the slab in a stage, counted in the order the MFMAs first need them: b0, a0, b1 .. b7,
+  // a1 .. a7
+  auto read_one = [&](Frags& f, int stage, int q, auto n_) __attribute__((always_inline)) {
+    constexpr int n = decltype(n_)::value;
+    constexpr bool is_a = n == 1 || n > F_N;
+    constexpr int idx = n <= 1 ? 0 : (n <= F_N ? n - 1 : n - F_N);
+    const int base = stage * F_STAGE + (((4 * q + quarter) ^ sw) << 4);
+    if constexpr (is_a)
+      f.a[idx] = *reinterpret_cast<const uint4*>(lds + base + offA0 + idx * 16 * F_SLAB);
     else
-      f.b[idx] = *reinterpret_cast<const uint4*>(lds + base + F_OPER + offB0 + idx * 32 * F_SLAB);
+      f.b[idx] = *reinterpret_cast<const uint4*>(lds + base + F_OPER + offB0 + idx * 16 * F_SLAB);
   };
 
-  f32x16 acc[F_NI][F_NJ];
-  auto zero_acc = [&]() {
-#pragma unroll
-    for (int i = 0; i < F_NI; ++i)
-#pragma unroll
-      for (int j = 0; j < F_NJ; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-  };
-  // pair i of the request in progress (switch: the LDS offset is an instruction literal)
-  auto issue_pair = [&](int i) {
-    switch (i) {
-      case 0: Z2Z_ISSUE_PAIR(0); break;
-      case 1: Z2Z_ISSUE_PAIR(1); break;
-      case 2: Z2Z_ISSUE_PAIR(2); break;
-#if F_WAVES == 4
-      case 3: Z2Z_ISSUE_PAIR(3); break;
-      case 4: Z2Z_ISSUE_PAIR(4); break;
-      case 5: Z2Z_ISSUE_PAIR(5); break;
-      case 6: Z2Z_ISSUE_PAIR(6); break;
-      default: Z2Z_ISSUE_PAIR(7); break;
-#else
-      default: Z2Z_ISSUE_PAIR(3); break;
-#endif
-    }
-  };
-  // The MFMAs of blocks [i_lo, i_hi) x [0, F_NJ); w0 = window index of the first one.  After an MFMA
-  // whose window index is 1 + i * F_SPREAD, request pair i is issued (fenced, so that it stays there: a
-  // burst of requests backs up the memory pipeline, and a wave that cannot issue its request cannot issue
-  // MFMAs either).
-  // the two requests of pair i on their own (F_SPLIT_PAIR: the hidden-row half goes out a few MFMAs after the other)
-  auto issue_a = [&](int i) {
-    switch (i) {
-      case 0: Z2Z_ISSUE_A(0); break;
-      case 1: Z2Z_ISSUE_A(1); break;
-      case 2: Z2Z_ISSUE_A(2); break;
-#if F_WAVES == 4
-      case 3: Z2Z_ISSUE_A(3); break;
-      case 4: Z2Z_ISSUE_A(4); break;
-      case 5: Z2Z_ISSUE_A(5); break;
-      case 6: Z2Z_ISSUE_A(6); break;
-      default: Z2Z_ISSUE_A(7); break;
-#else
-      default: Z2Z_ISSUE_A(3); break;
-#endif
-    }
-  };
-  // The MFMAs of blocks [i_lo, i_hi) x [0, F_NJ); w0 = window index of the first one.  After an MFMA
-  // whose window index is 1 + i * F_SPREAD, request pair i is issued (fenced, so that it stays there: a
-  // burst of requests backs up the memory pipeline, and a wave that cannot issue its request cannot issue
-  // MFMAs either).
-  auto issue_b = [&](int i) {
-    switch (i) {
-      case 0: Z2Z_ISSUE_B(0); break;
-      case 1: Z2Z_ISSUE_B(1); break;
-      case 2: Z2Z_ISSUE_B(2); break;
-#if F_WAVES == 4
-      case 3: Z2Z_ISSUE_B(3); break;
-      case 4: Z2Z_ISSUE_B(4); break;
-      case 5: Z2Z_ISSUE_B(5); break;
-      case 6: Z2Z_ISSUE_B(6); break;
-      default: Z2Z_ISSUE_B(7); break;
-#else
-      default: Z2Z_ISSUE_B(3); break;
-#endif
-    }
-  };
-  // The MFMAs of blocks [i_lo, i_hi) x [0, F_NJ); w0 = window index of the first one.  After an MFMA
-  // whose window index is 1 + i * F_SPREAD, request pair i is issued (fenced, so that it stays there: a
-  // burst of requests backs up the memory pipeline, and a wave that cannot issue its request cannot issue
-  // MFMAs either).
-  // `nf` (may be null): the fragments of the k-step (nstage, nq) are read into it, one read after every
-  // F_RD_EVERY-th MFMA starting at MFMA F_RD_FIRST of this call
-  auto mfma_rows = [&](const Frags& f, int i_lo, int i_hi, int w0, Frags* nf = nullptr, int nstage = 0, int nq = 0,
-                       int rd_first = F_RD_FIRST) {
-#pragma unroll
-    for (int i = i_lo; i < i_hi; ++i)
-#pragma unroll
-      for (int j = 0; j < F_NJ; ++j) {
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.a[i]),
-                                                            __builtin_bit_cast(bf16x8, f.b[j]), acc[i][j], 0, 0, 0);
-        const int local = (i - i_lo) * F_NJ + j;
-        if (F_LDS_SPREAD && nf != nullptr && local >= rd_first && (local - rd_first) % F_RD_EVERY == 0 &&
-            (local - rd_first) / F_RD_EVERY < F_NI + F_NJ) {
-          __builtin_amdgcn_sched_barrier(0);
-          read_one(*nf, nstage, nq, (local - rd_first) / F_RD_EVERY);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        const int w = w0 + (i - i_lo) * F_NJ + j;
-        if (!PROBE_NOREQ && F_SPLIT_PAIR == 0 && w >= 1 && (w - 1) % F_SPREAD == 0 && (w - 1) / F_SPREAD < F_PAIRS) {
-          __builtin_amdgcn_sched_barrier(0);
-          issue_pair((w - 1) / F_SPREAD);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        if (!PROBE_NOREQ && F_SPLIT_PAIR > 0 && w >= 1 && (w - 1) % F_SPREAD == 0 && (w - 1) / F_SPREAD < F_PAIRS) {
-          __builtin_amdgcn_sched_barrier(0);
-          issue_a((w - 1) / F_SPREAD);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        if (!PROBE_NOREQ && F_SPLIT_PAIR > 0 && w >= 1 + F_SPLIT_PAIR && (w - 1 - F_SPLIT_PAIR) % F_SPREAD == 0 &&
-            (w - 1 - F_SPLIT_PAIR) / F_SPREAD < F_PAIRS) {
-          __builtin_amdgcn_sched_barrier(0);
-          issue_b((w - 1 - F_SPLIT_PAIR) / F_SPREAD);
-          __builtin_amdgcn_sched_barrier(0);
-        }
+  Acc acc;
+  Frags f[2];                                        // the two k-steps of a slab
+  int g = 0;                                         // slabs behind
+  // one slab: 128 MFMAs, and what goes out between them; FIRST: nothing has been accumulated yet.  The hand-overs
+  // are the same for every slab, the last ones included: past the end of the stream the requests re-read the last slab
+  // into a stage nobody reads again.
+  auto slab_step = [&](auto first_) __attribute__((always_inline)) {
+    constexpr bool FIRST = decltype(first_)::value;
+    const int stage = g & 1;
+    static_for<F_SLOTS>([&](auto m_) __attribute__((always_inline)) {
+      constexpr int m = decltype(m_)::value;
+      constexpr int q = m / (F_N * F_N), i = m / F_N % F_N;
+      constexpr int j = i & 1 ? F_N - 1 - m % F_N : m % F_N;      // (to and fro: one operand stays from MFMA to MFMA)
+      if constexpr (m == kFree) {
+        __builtin_amdgcn_sched_barrier(0);
+        barrier_after_lds();
+        if (!PROBE_NOREQ) issue_begin(stage);
+        __builtin_amdgcn_sched_barrier(0);
       }
+      if constexpr (m == kLanded) {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(PROBE_NOREQ ? 0 : kOutAtLanded));
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      mfma<FIRST && q == 0>(acc[i][j], f[q].a[i], f[q].b[j]);
+      if constexpr (!PROBE_MFMA && m >= kRead2 && m < kRead2 + 16) {
+        __builtin_amdgcn_sched_barrier(0);
+        read_one(f[1], stage, 1, std::integral_constant<int, (m >= kRead2 && m < kRead2 + 16) ? m - kRead2 : 0>{});
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (!PROBE_MFMA && m >= kRead1 && m < kRead1 + 16) {
+        __builtin_amdgcn_sched_barrier(0);
+        read_one(f[0], stage ^ 1, 0, std::integral_constant<int, (m >= kRead1 && m < kRead1 + 16) ? m - kRead1 : 0>{});
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (!PROBE_NOREQ && m >= kRequest && (m - kRequest) % kRequestEvery == 0 && (m - kRequest) / kRequestEvery < 2 * F_PAIRS) {
+        __builtin_amdgcn_sched_barrier(0);
+        request(std::integral_constant<int, (m >= kRequest) ? (m - kRequest) / kRequestEvery : 0>{});
+        if constexpr ((m - kRequest) / kRequestEvery == 2 * F_PAIRS - 1) issue_end();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    });
+    ++g;
   };
 
   if (n_tiles > 0) {
-    zero_acc();
     set_tile(vt0);
-    // prologue: slab 0 requested in full, of slab 1 the pairs that a hand-over k-step issues (the rest
-    // follows during the first three k-steps, as for every later slab); slab 0 landed and visible, its
-    // first fragments on the way
+    // prologue: slabs 0 and 1 requested; slab 0 landed and visible, the fragments of its first k-step on the way
     issue_begin(0);
-#pragma unroll
-    for (int i = 0; i < F_PAIRS; ++i) issue_pair(i);
+    static_for<2 * F_PAIRS>(request);
     issue_end();
     issue_begin(1);
-#pragma unroll
-    for (int i = 0; i <= (PROBE_NOREQ ? F_PAIRS - 1 : F_LAST_IN_HANDOVER); ++i) issue_pair(i);
-    if (PROBE_NOREQ)
-      __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-    else
-      __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * (F_LAST_IN_HANDOVER + 1)));   // all of slab 0
-    __syncthreads();
-    Frags f0, f1;
-    read_frags(f0, 0, 0);
-    if (PROBE_MFMA) read_frags(f1, 0, 1);
-    int g = 0;
+    static_for<2 * F_PAIRS>(request);
+    issue_end();
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(PROBE_NOREQ ? 0 : 2 * F_PAIRS));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    static_for<16>([&](auto n) __attribute__((always_inline)) { read_one(f[0], 0, 0, n); });
+    if (PROBE_MFMA) static_for<16>([&](auto n) __attribute__((always_inline)) { read_one(f[1], 0, 1, n); });
     for (int vt = vt0; vt < vt_end; ++vt) {
-      for (int slab = 0; slab < n_slabs; ++slab, ++g) {
-        const int stage = g & 1;
-        if (F_LDS_SPREAD && !PROBE_MFMA) {
-          // the fragments of k-step q + 1 are read between the MFMAs of k-step q (as one burst per wave the four
-          // waves' reads arrive at the LDS together, right after a barrier, and the MFMAs wait behind them)
-          mfma_rows(f0, 0, F_NI, F_REST, &f1, stage, 1);
-          mfma_rows(f1, 0, F_NI, F_REST + F_KSTEP, &f0, stage, 2);
-          mfma_rows(f0, 0, F_NI, F_REST + 2 * F_KSTEP, &f1, stage, 3);
-        } else {
-          if (!PROBE_MFMA) read_frags(f1, stage, 1);
-          mfma_rows(f0, 0, F_NI, F_REST);
-          if (!PROBE_MFMA) read_frags(f0, stage, 2);
-          mfma_rows(f1, 0, F_NI, F_REST + F_KSTEP);
-          if (!PROBE_MFMA) read_frags(f1, stage, 3);
-          mfma_rows(f0, 0, F_NI, F_REST + 2 * F_KSTEP);
-        }
-        if (!PROBE_NOREQ) issue_end();          // the request for slab g+1 is out in full
-        // last k-step: a quarter of its MFMAs, then the slab hand-over.  It is the same for every slab,
-        // the last ones included (no test inside the loop): past the end of the stream the requests
-        // re-read the last slab into a stage nobody reads again.
-        mfma_rows(f1, 0, F_HO_ROWS, 1000);
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // slab g+1 (the only one in flight) has landed
-        __syncthreads();                            // slab g+1 visible to all; everyone has read slab g
-        if (!PROBE_NOREQ) issue_begin(stage);       // refill this stage with slab g+2
-        if (F_LDS_SPREAD && F_HANDOVER_SPREAD && !PROBE_MFMA) {
-          mfma_rows(f1, F_HO_ROWS, F_NI, 0, &f0, stage ^ 1, 0, F_HO_RD_FIRST);
-        } else {
-          if (!PROBE_MFMA) read_frags(f0, stage ^ 1, 0);
-          mfma_rows(f1, F_HO_ROWS, F_NI, 0);
-        }
-      }
-      // ---- this vocabulary tile is complete: fold its 128 x 128 logits into the running triples ------
-      const int v0 = vt * FT;
+      if (!PROBE_MFMA || vt == vt0)
+        slab_step(std::true_type{});
+      else
+        slab_step(std::false_type{});
+      for (int slab = 1; slab < n_slabs; ++slab) slab_step(std::false_type{});
+      if (PROBE_MFMA) continue;
+      wait_for_mfma();
+      // ---- this vocabulary tile is complete: fold its 128 x 128 logits into the running triples, or store it ------
+      int row_base = r0 + wr * 128, col_base = vt * FT + wv * 128 + quarter * 4;
+      asm volatile("" : "+v"(col_base), "+v"(row_base));   // (what follows from them is not worked out ahead of the K loop and kept)
       if (MODE == 2) {
         if (a.stream_f32)
-          store_tile_f32<F_NI, F_NJ>(acc, a, r0 + wr * (F_NJ * 32), r_end, v0 + wv * 128 + half * 4, n_valid);
+          store_tile16_f32(acc, a, row_base, r_end, col_base, n_valid);
         else
-          store_tile<F_NI, F_NJ>(acc, a, r0 + wr * (F_NJ * 32), r_end, v0 + wv * 128 + half * 4, n_valid);
+          store_tile16(acc, a, row_base, r_end, col_base, n_valid);
+      } else if (MODE == 5) {
+        store_partial16(acc, a.partial + (size_t)ks * a.rows * a.ldo, a.ldo, row_base, r_end, col_base, n_valid);
+      } else if (MODE == 3 || MODE == 4) {
+        store_prob16(acc, a, row_base, r_end, col_base, n_valid);
+      } else if (MODE == 6) {
+        fold_sample16(acc, run, draw, a, row_base, col_base, n_valid);
+      } else if (MODE == 7) {
+        fold_store16(acc, run, a, row_base, r_end, col_base, n_valid);
+      } else {
+        if ((vt + 1) * FT > n_valid) mask_tail16(acc, col_base, n_valid);
+        fold_tile16(acc, run, col_base, a.col0);
       }
-      else if (MODE == 5)
-        store_partial_tile<F_NI, F_NJ>(acc, a.partial + (size_t)ks * a.rows * a.ldo, a.ldo, r0 + wr * (F_NJ * 32), r_end,
-                                       v0 + wv * 128 + half * 4, n_valid);
-      else if (MODE == 3 || MODE == 4)
-        store_prob_tile<F_NI, F_NJ>(acc, a, r0 + wr * (F_NJ * 32), r_end, v0 + wv * 128 + half * 4, n_valid);
-      else if (MODE == 6)
-        fold_tile_sample<F_NI, F_NJ>(acc, run, draw, a, r0 + wr * (F_NJ * 32), v0 + wv * 128 + half * 4, n_valid);
-      else if (MODE == 7)
-        fold_tile_store<F_NI, F_NJ>(acc, run, a, r0 + wr * (F_NJ * 32), r_end, v0 + wv * 128 + half * 4, n_valid);
-      else if (!PROBE_MFMA)
-        fold_tile<F_NI, F_NJ>(acc, run, v0 + wv * 128 + half * 4, a.col0, n_valid, v0 + FT > n_valid);
-      if (!PROBE_MFMA) zero_acc();
     }
-    if (PROBE_MFMA) fold_tile_impl<F_NI, F_NJ, false>(acc, run, vt0 * FT + wv * 128 + half * 4, a.col0, n_valid);
+    if (PROBE_MFMA) {
+      wait_for_mfma();
+      fold_tile16(acc, run, vt0 * FT + wv * 128 + quarter * 4, a.col0);
+    }
   }
 
   if (MODE >= 2 && MODE <= 5) {
     __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0): the requests past the end of the stream land in LDS
     return;
   }
-  // ---- end of strip: lanes l and l+32 hold the same hidden row; then the two vocabulary halves ------
+  // ---- end of strip: the four quarter-waves hold the same hidden rows; then the two vocabulary halves ------
 #pragma unroll
-  for (int j = 0; j < F_NJ; ++j) {
-    Triple o;
-    o.m = __shfl_xor(run[j].m, 32);
-    o.s = __shfl_xor(run[j].s, 32);
-    o.i = __shfl_xor(run[j].i, 32);
-    merge_triple(run[j], o);
-    if (MODE == 6) {
-      Draw od;
-      od.v = __shfl_xor(draw[j].v, 32);
-      od.l = __shfl_xor(draw[j].l, 32);
-      od.i = __shfl_xor(draw[j].i, 32);
-      merge_draw(draw[j], od);
+  for (int j = 0; j < F_N; ++j) {
+#pragma unroll
+    for (int off = 16; off <= 32; off <<= 1) {
+      Triple o;
+      o.m = __shfl_xor(run[j].m, off);
+      o.s = __shfl_xor(run[j].s, off);
+      o.i = __shfl_xor(run[j].i, off);
+      merge_triple(run[j], o);
+      if (MODE == 6) {
+        Draw od;
+        od.v = __shfl_xor(draw[j].v, off);
+        od.l = __shfl_xor(draw[j].l, off);
+        od.i = __shfl_xor(draw[j].i, off);
+        merge_draw(draw[j], od);
+      }
     }
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): the requests past the end of the stream too
   __syncthreads();                                 // every wave is done with the operand stages
   Triple* xch = reinterpret_cast<Triple*>(lds);    // [256 hidden rows of the tile]
   Draw* xdr = reinterpret_cast<Draw*>(xch + FT);
-  const int hrow0 = wr * (F_NJ * 32);
-  if (wv == 1 && lane < 32) {
+  const int hrow0 = wr * 128;
+  if (wv == 1 && lane < 16) {
 #pragma unroll
-    for (int j = 0; j < F_NJ; ++j) {
-      xch[hrow0 + j * 32 + lane] = run[j];
-      if (MODE == 6) xdr[hrow0 + j * 32 + lane] = draw[j];
+    for (int j = 0; j < F_N; ++j) {
+      xch[hrow0 + j * 16 + lane] = run[j];
+      if (MODE == 6) xdr[hrow0 + j * 16 + lane] = draw[j];
     }
   }
   __syncthreads();
-  if (wv == 0 && lane < 32) {
+  if (wv == 0 && lane < 16) {
 #pragma unroll
-    for (int j = 0; j < F_NJ; ++j) {
-      merge_triple(run[j], xch[hrow0 + j * 32 + lane]);
-      const int hrow = r0 + hrow0 + j * 32 + lane;
+    for (int j = 0; j < F_N; ++j) {
+      merge_triple(run[j], xch[hrow0 + j * 16 + lane]);
+      const int hrow = r0 + hrow0 + j * 16 + lane;
       if (hrow < r_end) {
         const size_t p = (size_t)hrow * a.n_parts + a.part0 + st;
         a.part_m[p] = run[j].m;
         a.part_s[p] = run[j].s;
         if (MODE == 6) {
-          merge_draw(draw[j], xdr[hrow0 + j * 32 + lane]);
+          merge_draw(draw[j], xdr[hrow0 + j * 16 + lane]);
           a.part_v[p] = draw[j].v;
           a.part_l[p] = draw[j].l;
           a.part_i[p] = draw[j].i;
@@ -591,7 +837,7 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
 }  // namespace
 
 int z2z_launch_logits_fast(int mode, const LogitsArgs& a, unsigned grid, hipStream_t s) {
-  const bool rot = F_ROTATE_FEW && a.row_tiles == 1;
+  const bool rot = a.row_tiles == 1;
   if (rot && mode == 0)
     hipLaunchKernelGGL((logits_fast_kernel<0, true>), dim3(grid), dim3(F_THREADS), F_LDS, s, a);
   else if (rot && mode == 6)
