@@ -376,10 +376,11 @@ enum {
   Z2Z_OPT_LZW_KERNEL = 3,      /* 0 = automatic, >0 = force a variant (2: table in global memory, 3: one
                                   code per step in the decoder, 4: one wave per sequence) */
   Z2Z_OPT_DECODE_KERNEL = 4,   /* 0 = automatic, >0 = force a variant                               */
-  Z2Z_OPT_LOGITS_MAP = 6,      /* workgroup -> tile order of the bf16 MFMA kernel's base part, packed
+  Z2Z_OPT_LOGITS_MAP = 6,      /* order of the bf16 MFMA kernel's base part over its output tiles, packed
                                   lr | ls << 8 | xr << 16 | xs << 24: each of the 8 XCDs walks blocks of
-                                  lr row tiles x ls strips, the XCDs' blocks lie xr x xs (xr * xs = 8)
-                                  inside one super block; 0 = automatic                              */
+                                  lr row tiles and, inside a block, its strips; the row blocks are dealt
+                                  out to the XCDs xr ways, the strips xs ways (xr * xs = 8; ls, at least
+                                  1, has no effect); 0 = automatic                                    */
   Z2Z_OPT_SAMPLE_KERNEL = 7,   /* filtered sampling: 0 = automatic, 1 = always select the kept prefix by
                                   passes over the whole row (no short list from the largest parts)   */
   Z2Z_OPT_BACKWARD_CHUNK = 8,  /* z2z_extended_nll_backward: at most this many sequences per pass, 0 = as many as

@@ -243,11 +243,8 @@ int z2z_launch_linear(z2z_ctx* c, const void* A, const void* W, const float* bia
   a.w_rows = N;
   a.n_vtiles = (N + 255) / 256;
   a.row_tiles = (R + 255) / 256;
-  // one tile per workgroup when the row count is only known on the device: the launch cannot be shaped to
-  // it, and the finer the grain, the less of the last round of workgroups is wasted
-  a.strip = (!rows_dev && (long long)a.row_tiles * a.n_vtiles >= 2048) ? 4 : 1;
-  a.n_strips = (a.n_vtiles + a.strip - 1) / a.strip;
-  a.n_work = a.row_tiles * a.n_strips;
+  a.strip = 1;
+  a.n_strips = a.n_vtiles;
   a.out = out;
   a.bias = bias;
   a.residual = residual;
@@ -256,72 +253,8 @@ int z2z_launch_linear(z2z_ctx* c, const void* A, const void* W, const float* bia
   a.ldh = pitch ? pitch->a : 0;
   a.ldw = pitch ? pitch->w : 0;
   a.stream_f32 = stream_f32 ? 1 : 0;
-  a.rows_dev = nullptr;
-  a.k_dev = k_dev;
-  if (rows_dev && a.row_tiles >= 16) {
-    // the real row count is on the device: what an XCD owns is settled there (see map_rows_dev)
-    a.rows_dev = rows_dev;
-    a.map_lr = 4;
-    unsigned grid;
-    if (a.n_strips % 8 == 0) {
-      // every XCD takes an eighth of the weight tiles and all row tiles
-      const int strips_per_xcd = a.n_strips / 8;
-      a.map_xs = 8;
-      a.map_xr = 1;
-      a.map_ls = strips_per_xcd >= 8 ? 8 : (strips_per_xcd >= 4 ? 4 : (strips_per_xcd >= 2 ? 2 : 1));
-      a.strip_blocks = (strips_per_xcd + a.map_ls - 1) / a.map_ls;
-      const int row_blocks = (a.row_tiles + a.map_lr - 1) / a.map_lr;
-      grid = 8u * (unsigned)(a.map_lr * a.map_ls) * (unsigned)row_blocks * (unsigned)a.strip_blocks;
-    } else {
-      a.map_xs = 1;
-      a.map_xr = 8;
-      a.map_ls = a.n_strips >= 8 ? 8 : (a.n_strips >= 4 ? 4 : (a.n_strips >= 2 ? 2 : 1));
-      a.strip_blocks = (a.n_strips + a.map_ls - 1) / a.map_ls;
-      const int tiles_per_xcd = (a.row_tiles + 7) / 8;
-      const int row_blocks = (tiles_per_xcd + a.map_lr - 1) / a.map_lr;
-      grid = 8u * (unsigned)(a.map_lr * a.map_ls) * (unsigned)row_blocks * (unsigned)a.strip_blocks;
-    }
-    return z2z_launch_logits_fast(2, a, grid, s);
-  }
-  // (fewer row tiles than that: the tiles beyond the real rows only exit early)
-  // Workgroup ids go round-robin over the 8 XCDs and the mapping gives XCD (xr_i, xs_i) the row tiles whose
-  // block index is xr_i mod map_xr and the strips whose block index is xs_i mod map_xs: an XCD's share is the
-  // product of the two counts.  Take the mapping with the smallest largest share (nobody waits for one XCD),
-  // and among equals the one with the largest blocks (what runs together shares operand tiles through L2).
-  {
-    long long best_load = -1;
-    int best_area = 0;
-    const int xrs[4] = {8, 4, 2, 1};
-    for (int xi = 0; xi < 4; ++xi)
-      for (int lr = 4; lr >= 1; lr >>= 1)
-        for (int ls = 8; ls >= 1; ls >>= 1) {
-          const int xr = xrs[xi], xs = 8 / xr;
-          long long worst = 0;
-          for (int i = 0; i < xr; ++i) {
-            long long rows_i = 0;
-            for (int blk = i; blk * lr < a.row_tiles; blk += xr) rows_i += (blk + 1) * lr <= a.row_tiles ? lr : a.row_tiles - blk * lr;
-            for (int j = 0; j < xs; ++j) {
-              long long strips_j = 0;
-              for (int blk = j; blk * ls < a.n_strips; blk += xs) strips_j += (blk + 1) * ls <= a.n_strips ? ls : a.n_strips - blk * ls;
-              if (rows_i * strips_j > worst) worst = rows_i * strips_j;
-            }
-          }
-          const int area = lr * ls;
-          if (best_load < 0 || worst < best_load || (worst == best_load && area > best_area)) {
-            best_load = worst;
-            best_area = area;
-            a.map_lr = lr;
-            a.map_ls = ls;
-            a.map_xr = xr;
-            a.map_xs = xs;
-          }
-        }
-  }
-  const int sb_rows = a.map_xr * a.map_lr, sb_strips = a.map_xs * a.map_ls;
-  a.map_sb_r = (a.row_tiles + sb_rows - 1) / sb_rows;
-  const int sb_s = (a.n_strips + sb_strips - 1) / sb_strips;
-  const unsigned grid = 8u * (unsigned)(a.map_lr * a.map_ls) * (unsigned)a.map_sb_r * (unsigned)sb_s;
   a.rows_dev = rows_dev;
+  a.k_dev = k_dev;
+  const unsigned grid = z2z_logits_fast_order(a, 0);
   return z2z_launch_logits_fast(2, a, grid, s);
 }
-

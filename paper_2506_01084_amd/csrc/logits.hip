@@ -302,38 +302,7 @@ int z2z_launch_logits_part(z2z_ctx* c, bool hyper, LogitsArgs a, const void* W, 
             rows_per_seq);
   *n_strips_out = a.n_strips;
   unsigned grid = (unsigned)a.n_work;
-  if (!hyper) {
-    const int m = c->opt_logits_map;
-    a.map_lr = m ? (m & 0xFF) : 4;
-    a.map_ls = m ? ((m >> 8) & 0xFF) : 8;
-    a.map_xr = m ? ((m >> 16) & 0xFF) : 4;
-    a.map_xs = m ? ((m >> 24) & 0xFF) : 2;
-    if (!m && a.row_tiles < 16) {
-      // few row tiles: the XCDs share out the strips alone (split over row tiles, most of them would idle)
-      a.map_xr = 1;
-      a.map_xs = 8;
-      a.map_lr = a.row_tiles >= 4 ? 4 : (a.row_tiles >= 2 ? 2 : 1);
-    }
-    const int tail = !m && a.row_tiles >= 16 ? a.row_tiles & 15 : 0;     // row tiles behind the last whole block of 16
-    const int sb_rows = a.map_xr * a.map_lr, sb_strips = a.map_xs * a.map_ls;
-    a.map_sb_r = (a.row_tiles - tail + sb_rows - 1) / sb_rows;
-    const int sb_s = (a.n_strips + sb_strips - 1) / sb_strips;
-    unsigned per_xcd = (unsigned)(a.map_lr * a.map_ls) * (unsigned)a.map_sb_r * (unsigned)sb_s;
-    // Dealt out four ways along the rows, 8 row tiles behind the whole blocks would be two XCD pairs' work and none
-    // for the others (104 row tiles: 28 for half of the XCDs, 24 for the rest).  They go as blocks of 8, 4 and the
-    // last 1-3, split 2 x 4 and 1 x 8 ways, where every XCD has a share of the strips.  (Those splits for all row
-    // tiles balance as well, but read more operand tiles at a time from beyond the L2s: 32768 rows x 128256 columns,
-    // d = 4096: 28.1 and 28.8 ms against 25.0.)
-    int at = 0;
-    for (int part : {tail & 8, tail & 4, tail & 3}) {
-      if (!part) continue;
-      const int xs = part == 8 ? 4 : 8;
-      a.map_tail_j[at] = (int32_t)per_xcd;
-      a.map_tail_rows[at++] = part;
-      per_xcd += (unsigned)((part == 8 ? 4 : part) * a.map_ls) * (unsigned)((a.n_strips + xs * a.map_ls - 1) / (xs * a.map_ls));
-    }
-    grid = 8u * per_xcd;
-  }
+  if (!hyper) grid = z2z_logits_fast_order(a, c->opt_logits_map);
   c->n_launch[hyper ? Z2Z_KERNEL_TILE_HYPER : Z2Z_KERNEL_TILE_BASE]++;
   if (timed) Z2Z_HIP_TRY(hipEventRecord(c->ev_start[c->n_timed], s));
   // (measurement probes of the base part: see logits_fast_kernel, modes 8 and 9)
@@ -472,7 +441,6 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
   a.logits = logits;
   a.ld = V + cap;
   a.n_parts = n_parts;
-  a.map_lr = a.map_ls = a.map_xr = a.map_xs = a.map_sb_r = 1;
 
   if (!fast) {
     // both parts in one launch of the general kernel
@@ -564,8 +532,7 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     a.part_v = c->part_v;
     a.part_l = c->part_l;
     a.n_parts = n_parts;
-    a.map_lr = a.map_ls = a.map_xr = a.map_xs = a.map_sb_r = 1;
-    a.sample = 1;
+      a.sample = 1;
     a.inv_temperature = 1.0f / temperature;
     a.key0 = (uint32_t)seed;
     a.key1 = (uint32_t)(seed >> 32);
@@ -638,8 +605,7 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     a.part_s = c->part_s;
     a.part_i = c->part_i;
     a.n_parts = n_parts;
-    a.map_lr = a.map_ls = a.map_xr = a.map_xs = a.map_sb_r = 1;
-    a.sample = 2;
+      a.sample = 2;
     a.inv_temperature = 1.0f / temperature;
     a.logits = c->sample_logits;
     a.ld = c->cfg.V + c->cfg.cap;

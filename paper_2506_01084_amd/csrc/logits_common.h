@@ -201,15 +201,9 @@ struct LogitsArgs {
   int32_t n_parts;        // partials per hidden row (row stride of the part arrays)
   int32_t row_tiles;      // base: tiles over all rows; hyper: tiles per sequence
   int32_t n_work;         // workgroups with work: row tiles (x sequences) x strips
-  // workgroup -> (row tile, strip) mapping of the base part: workgroup ids go round-robin over the 8
-  // XCDs; each XCD walks blocks of map_lr x map_ls (row tiles x strips), and the 8 XCDs' blocks sit
-  // side by side as map_xr x map_xs inside one super block, so that what runs at the same time shares
-  // W strips and hidden-row tiles through the XCD's L2 and the memory-side cache.
-  int32_t map_lr, map_ls, map_xr, map_xs, map_sb_r;
-  // row tiles behind the map_sb_r blocks along the rows, in up to three pieces of their own: piece k begins with an
-  // XCD's workgroup map_tail_j[k] and holds map_tail_rows[k] row tiles (8: 2 x 4 XCDs, each 4 row tiles; at most
-  // 4: 1 x 8); 0 rows: no piece
-  int32_t map_tail_j[3], map_tail_rows[3];
+  // order of the tile kernel's base part and dense layers over (row tiles, strips), see locate_base: the side walked in
+  // blocks (map_p_rows: row tiles), the block, and how many ways either side is dealt out to the 8 XCDs (xp * xq = 8)
+  int32_t map_p_rows, map_lp, map_xp, map_xq;
   float* part_m;          // [rows, n_parts]
   float* part_s;
   int32_t* part_i;
@@ -229,7 +223,6 @@ struct LogitsArgs {
   const float* row_grad;  // [rows] g: the upstream gradient, 0 for rows without a usable target
   const int32_t* targets; // [rows]
   const int32_t* rows_dev;  // nullptr, or the number of rows that exist (<= rows), known on the device only
-  int32_t strip_blocks;     // > 0: linear mode with the XCD-per-row-tile mapping, = ceil(n_strips / map_ls)
   // linear mode with K split over ksplit workgroups per tile (few rows: too few tiles to fill the machine):
   // part ks covers K slabs [ks * slabs_per_part, ...) and leaves its fp32 tile in partial[ks][row][col]
   int32_t ksplit, slabs_per_part;
@@ -388,6 +381,9 @@ int z2z_launch_logits_general(bool bf16, const z2z_logits::LogitsArgs& base, con
 // 3 base part, 4 hyper part storing the gradient with respect to the logits, 5 dense layer with K split
 // (fp32 partial tiles)
 int z2z_launch_logits_fast(int mode, const z2z_logits::LogitsArgs& a, unsigned grid, hipStream_t s);
+// order and grid of a base part or dense layer (modes 0, 2, 3, 6 - 9): a.row_tiles, n_vtiles and n_strips are set; `forced`:
+// Z2Z_OPT_LOGITS_MAP, 0 for the automatic order
+unsigned z2z_logits_fast_order(z2z_logits::LogitsArgs& a, int forced);
 // out[R, N] = act(A[R, K] . W[N, K]^T + bias) + residual, all matrices bf16 (bias float), on the bf16 MFMA kernel
 // (R rows are laid out; with rows_dev only the first *rows_dev of them exist: the others are neither read nor
 // written).  stream_f32: residual and out are fp32 instead (a residual stream that is not rounded between layers).

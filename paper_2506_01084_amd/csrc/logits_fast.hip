@@ -43,7 +43,8 @@ constexpr int FT = 256;                   // tile edge, vocabulary and hidden ro
 constexpr int F_SLAB = 128;               // bytes per row per K slab (64 bf16)
 constexpr int F_OPER = FT * F_SLAB;       // one operand tile of one slab: 32 KiB
 constexpr int F_STAGE = 2 * F_OPER;       // A + B
-constexpr int F_LDS = 2 * F_STAGE;        // 128 KiB
+constexpr int F_LDS_STAGES = 2 * F_STAGE; // 128 KiB
+constexpr int F_LDS = F_LDS_STAGES + FT * (int)(sizeof(Triple) + sizeof(Draw));     // + what the waves exchange at the end of a strip
 constexpr int F_THREADS = 256;
 constexpr int F_N = 8;                    // MFMA blocks of a wave along either side (128 x 128)
 constexpr int F_PAIRS = 8;                // request pairs (8 rows of A + 8 rows of B) per wave and slab
@@ -114,58 +115,35 @@ __device__ __forceinline__ uint32_t lds_offset_of(const void* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
 }
 
-// Workgroup id -> (row tile, strip) for the base part; returns false when the id maps to no work.
-__device__ __forceinline__ bool map_base(const LogitsArgs& a, int bid, int* rt, int* st) {
-  const int xcd = bid & 7;
-  int j = bid >> 3;
-  int n_lr = a.map_lr, n_xr = a.map_xr, n_xs = a.map_xs, n_sb_r = a.map_sb_r, row0 = 0;
-  if (a.map_tail_rows[0] && j >= a.map_tail_j[0]) {     // a piece of the row tiles behind the whole blocks
-    const int k = a.map_tail_rows[2] && j >= a.map_tail_j[2] ? 2 : (a.map_tail_rows[1] && j >= a.map_tail_j[1] ? 1 : 0);
-    row0 = n_sb_r * n_xr * n_lr + (k > 0 ? a.map_tail_rows[0] : 0) + (k > 1 ? a.map_tail_rows[1] : 0);
-    j -= a.map_tail_j[k];
-    n_xr = a.map_tail_rows[k] == 8 ? 2 : 1;
-    n_lr = a.map_tail_rows[k] == 8 ? 4 : a.map_tail_rows[k];
-    n_xs = 8 / n_xr;
-    n_sb_r = 1;
-  }
-  const int per = n_lr * a.map_ls;
-  const int g = j / per;
-  const int within = j - g * per;
-  const int lr = within % n_lr;
-  const int ls = within / n_lr;
-  const int xr = xcd % n_xr;
-  const int xs = xcd / n_xr;
-  const int sb_r = g % n_sb_r;
-  const int sb_s = g / n_sb_r;
-  *rt = row0 + (sb_r * n_xr + xr) * n_lr + lr;
-  *st = (sb_s * n_xs + xs) * a.map_ls + ls;
-  return *rt < a.row_tiles && *st < a.n_strips;
-}
-
-// Linear mode when the number of rows is known on the device only.  Workgroup ids go round-robin over the 8
-// XCDs; an XCD walks blocks of map_lr row tiles x map_ls weight tiles ("strips" of one tile), the weight
-// tiles of a row block before the next row block.  What an XCD owns is decided here, on the device, from the
-// row count: if the weight tiles divide evenly among the XCDs (map_xs = 8), XCD x owns the weight tiles
-// x, x + 8, ... and every row tile -- equal shares whatever the count is; otherwise row tile t belongs to XCD
-// t mod 8 (shares differ by one row tile at most).  The grid is sized for the rows laid out.
-__device__ __forceinline__ bool map_rows_dev(const LogitsArgs& a, int bid, int row_tiles_now, int* rt, int* st) {
-  const int xcd = bid & 7;
-  const int j = bid >> 3;
-  const int per = a.map_lr * a.map_ls;
-  const int blk = j / per;
-  const int within = j - blk * per;
-  const int lr = within % a.map_lr;
-  const int ls = within / a.map_lr;
-  const int sblk = blk % a.strip_blocks;
-  const int rblk = blk / a.strip_blocks;
-  if (a.map_xs == 8) {
-    *rt = rblk * a.map_lr + lr;
-    *st = (sblk * a.map_ls + ls) * 8 + xcd;
+// Position j of XCD xcd's list of work -> (row tile, strip) for the base part and dense layers; false behind its end.
+// Workgroup ids go round-robin over the 8 XCDs, and the 32 workgroups of one take consecutive positions, so what is
+// consecutive shares operand tiles through the XCD's L2.  One side of the output, P tiles (map_p_rows: the row tiles,
+// otherwise the strips), is walked in blocks of map_lp, dealt out map_xp ways; inside a block all Q of the other side's that are this XCD's
+// (q mod map_xq) follow: 32 workgroups work on map_lp x 32 / map_lp outputs, and all of them on 16 x 16 (the memory-side cache
+// serves an operand tile to several XCDs).  The P tiles behind whole blocks of map_lp * map_xp go, with all of Q, in eight
+// equal runs, so that the XCDs' lists differ by a run's rounding.  Lists without holes, in sizes that the device works
+// out itself: the row count may be known there only.
+__device__ __forceinline__ bool locate_base(const LogitsArgs& a, int row_tiles, int xcd, int j, int* rt, int* st) {
+  const int P = a.map_p_rows ? row_tiles : a.n_strips, Q = a.map_p_rows ? a.n_strips : row_tiles;
+  const int xpi = xcd % a.map_xp, xqi = xcd / a.map_xp;
+  const int blocks = P / (a.map_lp * a.map_xp);                    // whole blocks of each XCD along P
+  const int own_q = (Q - xqi + a.map_xq - 1) / a.map_xq;
+  const int main_items = blocks * a.map_lp * own_q;
+  int pi, qi;
+  if (j < main_items) {
+    const int w = j / a.map_lp, blk = w / own_q;
+    pi = (blk * a.map_xp + xpi) * a.map_lp + (j - w * a.map_lp);
+    qi = (w - blk * own_q) * a.map_xq + xqi;
   } else {
-    *rt = (rblk * a.map_lr + lr) * 8 + xcd;
-    *st = sblk * a.map_ls + ls;
+    const int p0 = blocks * a.map_lp * a.map_xp, T = P - p0, total = T * Q;
+    const int t = j - main_items + (int)((long long)total * xcd / 8);
+    if (t >= (int)((long long)total * (xcd + 1) / 8)) return false;
+    qi = t / T;
+    pi = p0 + (t - qi * T);
   }
-  return *rt < row_tiles_now && *st < a.n_strips;
+  *rt = a.map_p_rows ? pi : qi;
+  *st = a.map_p_rows ? qi : pi;
+  return true;
 }
 
 struct Frags {
@@ -528,10 +506,17 @@ __device__ __forceinline__ void store_prob16(const Acc& acc, const LogitsArgs& a
 // same few memory channels.  (With many row tiles the workgroups that share operands through L2 and the
 // memory-side cache must stay in step: there the rotation costs 1-2 %, and so does its arithmetic alone; with two
 // row tiles it is level or 1 % slower.  A decode step of 256 sequences: 646 -> 634 us, with a filtered draw 704 -> 675.)
+//
+// A workgroup walks its XCD's list (locate_base) from its own position on, in steps of the workgroups an XCD has: the
+// operand stream runs on from one output tile to the next, and a tile's epilogue finds the next one's first two slabs on the
+// way.  With a workgroup per tile instead, a launch and the first slabs' round trip stood before every tile and a
+// store queue behind it: a training step of 8 x 4096 tokens (kernels only) 172.8 -> 168.9 ms, of it the order below 2.5.
+// The hyper parts and K-split layers (modes 1, 4, 5) have a workgroup per item: what exists of them is known on the device.
 template <int MODE, bool ROT = false>
 __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
   constexpr bool PROBE_NOREQ = MODE == 8 || MODE == 9;
   constexpr bool PROBE_MFMA = MODE == 9;
+  constexpr bool LIST = MODE != 1 && MODE != 4 && MODE != 5;
   extern __shared__ __align__(1024) unsigned char lds[];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -539,103 +524,104 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
   const int wv = wave & 1;    // which 128 vocabulary rows of the tile
   const int wr = wave >> 1;   // which 128 hidden rows of the tile
 
-  int rt, st;
-  int r0, r_end, n_valid;
+  // ---- the work: positions first, first + step, ... of a list; item(j) gives its row tile and strip ----------------
+  const int first = LIST ? (int)(blockIdx.x >> 3) : 0, step = LIST ? (int)(gridDim.x >> 3) : 1;
   const unsigned char* Wp = reinterpret_cast<const unsigned char*>(a.W);
+  const unsigned char* Hm = reinterpret_cast<const unsigned char*>(a.H);
   const size_t row_bytes = (size_t)a.d * 2;
   // (pitches of their own: dense layers only)
   const size_t pitch_h = MODE == 2 && a.ldh ? (size_t)a.ldh * 2 : row_bytes;
   const size_t pitch_w = MODE == 2 && a.ldw ? (size_t)a.ldw * 2 : row_bytes;
+  int r_end = a.rows;                                // one past the last row of the matrix, or of the sequence
+  if ((MODE == 2 || MODE == 5) && a.rows_dev) r_end = min(r_end, *a.rows_dev);
+  const int row_tiles_now = (r_end + FT - 1) / FT;
+  int n_valid = a.w_rows;
+  int one_rt = 0, one_st = 0, one_r0 = 0, ks = 0;    // modes 1, 4, 5: the one item
   if (MODE == 1 || MODE == 4) {
     if ((int)blockIdx.x >= a.n_work) return;
-    rt = blockIdx.x / a.n_strips;
+    one_rt = blockIdx.x / a.n_strips;
     // workgroup ids go round-robin over the 8 XCDs, and the strips beyond a sequence's C_b are empty: with the
     // strip taken straight from the id, the XCDs that own the low strips would do all the work (config 5: 9 of 16
     // strips exist, XCD 0 owned two of them, the others one).  Rotating by the row tile deals them out evenly.
-    st = (int)((blockIdx.x + (unsigned)rt) % (unsigned)a.n_strips);
-    const int b = rt / a.row_tiles;
-    r0 = b * a.rows_per_seq + (rt % a.row_tiles) * FT;
+    one_st = (int)((blockIdx.x + (unsigned)one_rt) % (unsigned)a.n_strips);
+    const int b = one_rt / a.row_tiles;
+    one_r0 = b * a.rows_per_seq + (one_rt % a.row_tiles) * FT;
     r_end = (b + 1) * a.rows_per_seq;
     n_valid = min(max(a.size[b], 0), a.w_rows);
     Wp += (size_t)b * a.w_rows * row_bytes;
   } else if (MODE == 5) {
     // few tiles, K split: workgroup -> (K part, row tile, weight tile)
-    r_end = a.rows_dev ? min(a.rows, *a.rows_dev) : a.rows;
     const int t = blockIdx.x / a.ksplit;
-    rt = t % a.row_tiles;
-    st = t / a.row_tiles;
-    if (st >= a.n_strips) return;
-    r0 = rt * FT;
-    if (r0 >= r_end) return;
-    n_valid = a.w_rows;
-  } else {
-    r_end = a.rows;
-    if (MODE == 2 && a.rows_dev) r_end = min(r_end, *a.rows_dev);
-    if (MODE == 2 && a.strip_blocks > 0) {
-      if (!map_rows_dev(a, blockIdx.x, (r_end + FT - 1) / FT, &rt, &st)) return;
-    } else {
-      if (!map_base(a, blockIdx.x, &rt, &st)) return;
+    ks = (int)(blockIdx.x % a.ksplit);
+    one_rt = t % a.row_tiles;
+    one_st = t / a.row_tiles;
+    if (one_st >= a.n_strips) return;
+    one_r0 = one_rt * FT;
+    if (one_r0 >= r_end) return;                     // a tile beyond the rows that exist
+    Wp += (size_t)ks * a.slabs_per_part * F_SLAB;    // this part's slabs start here in every row
+    Hm += (size_t)ks * a.slabs_per_part * F_SLAB;
+  }
+  auto item = [&](int j, int* r0, int* st) -> bool {
+    if (!LIST) {
+      *r0 = one_r0;
+      *st = one_st;
+      return j == 0;
     }
-    r0 = rt * FT;
-    if (r0 >= r_end) return;                       // a tile beyond the rows that exist
-    n_valid = a.w_rows;
-  }
-  const unsigned char* Hp = reinterpret_cast<const unsigned char*>(a.H) + (size_t)r0 * pitch_h;
-  const int ks = MODE == 5 ? (int)(blockIdx.x % a.ksplit) : 0;
-  if (MODE == 5) {                                   // this part's slabs start here in every row
-    Wp += (size_t)ks * a.slabs_per_part * F_SLAB;
-    Hp += (size_t)ks * a.slabs_per_part * F_SLAB;
-  }
-  const int vt0 = st * a.strip;
-  const int vt_end = min(min(vt0 + a.strip, a.n_vtiles), (n_valid + FT - 1) / FT);
-  const int n_tiles = vt_end - vt0;          // vocabulary tiles this workgroup sweeps (may be <= 0)
+    int rt;
+    if (!locate_base(a, row_tiles_now, (int)(blockIdx.x & 7), j, &rt, st)) return false;
+    *r0 = rt * FT;
+    return true;
+  };
+  const int n_vt = min(a.n_vtiles, (n_valid + FT - 1) / FT);
   int n_slabs = MODE == 5 ? min(a.slabs_per_part, (int)(row_bytes / F_SLAB) - ks * a.slabs_per_part)
                           : (int)(row_bytes / F_SLAB);
   if (MODE == 2 && a.k_dev) n_slabs = max(1, min(n_slabs, (*a.k_dev * 2 + F_SLAB - 1) / F_SLAB));
-
-  Triple run[F_N];
-  Draw draw[F_N];                                   // MODE 6 only
-#pragma unroll
-  for (int j = 0; j < F_N; ++j) {
-    run[j] = empty_triple();
-    draw[j] = empty_draw();
-  }
 
   // ---- loader: lane l of wave w, instruction i moves the chunk that lands at LDS byte
   //      ((w * F_PAIRS + i) * 8 + (l >> 3)) * 128 + (l & 7) * 16 of the operand tile; offsets are relative to
   //      the first row of the tile, rows past the last valid one are clamped onto it ------------------
   const uint32_t lds_base = lds_offset_of(lds);
   const int ld_row = lane >> 3;                                  // row inside the 8-row group
-  const int limB = r_end - 1 - r0;                               // last valid hidden row of the tile
-  const unsigned char* Wtile = Wp;
-  int limA = 0;                                                  // last valid vocabulary row of the tile
   // per-lane global byte offsets of the 8 row groups a wave requests (swizzled chunk folded in); rows
-  // past the last valid one are clamped onto it.  B's never change, A's change with the tile.
+  // past the last valid one are clamped onto it.  B's change with the item, A's with the tile.
   auto row_offset = [&](int i, int lim, size_t pitch) -> uint32_t {
     const int row = (wave * F_PAIRS + i) * 8 + ld_row;
     const int chunk16 = ((lane & 7) ^ ((row >> 1) & 7)) * 16;
     return (uint32_t)(min(row, lim) * (int)pitch + chunk16);
   };
   uint32_t voffA[F_PAIRS], voffB[F_PAIRS];
-#pragma unroll
-  for (int i = 0; i < F_PAIRS; ++i) voffB[i] = row_offset(i, limB, pitch_h);
+  const unsigned char* Wtile = Wp;
+  const unsigned char* Hp = Hm;
+  // ---- the cursor of the operand stream: slab lslab of weight tile lvt of the item at position lj (none: !live) ----------
+  int lj = first, lslab = 0, lvt = 0, lvt_end = 0, rot = 0;
+  bool live = true;
   auto set_tile = [&](int vt) {
     Wtile = Wp + (size_t)vt * FT * pitch_w;
-    limA = n_valid - 1 - vt * FT;
 #pragma unroll
-    for (int i = 0; i < F_PAIRS; ++i) voffA[i] = row_offset(i, limA, pitch_w);
+    for (int i = 0; i < F_PAIRS; ++i) voffA[i] = row_offset(i, n_valid - 1 - vt * FT, pitch_w);
   };
-  // request the slab that follows (lslab, lvt) in the stream, if any, and advance the cursor.  A request
-  // is 16 instructions per wave; issue_rows<i>() issues the pair for row group i so that the caller can
-  // place the pairs between MFMAs.
-  int lslab = 0, lvt = vt0;
+  auto open_item = [&]() {
+    int r0, st;
+    live = item(lj, &r0, &st);
+    if (!live) return;
+    lvt = st * a.strip;
+    lvt_end = min(lvt + a.strip, n_vt);
+    live = lvt < lvt_end;
+    if (!live) return;
+    Hp = Hm + (size_t)r0 * pitch_h;
+#pragma unroll
+    for (int i = 0; i < F_PAIRS; ++i) voffB[i] = row_offset(i, r_end - 1 - r0, pitch_h);
+    if (ROT) rot = st % n_slabs;
+    set_tile(lvt);
+  };
+  // request the slab that follows in the stream, if any, and advance the cursor.  A request is 16 instructions per
+  // wave, so that the caller can place them between MFMAs.
   uint32_t isA = 0;                          // LDS destination (operand A) of the slab being requested
   const unsigned char* is_ga = Wp;
-  const unsigned char* is_gb = Hp;
-  const int rot = ROT ? st % n_slabs : 0;
+  const unsigned char* is_gb = Hm;
   auto issue_begin = [&](int stage) {
-    isA = lds_base + stage * F_STAGE + wave * (F_PAIRS * 1024);
-    if (lvt < vt_end) {                      // else: keep the last valid source
+    isA = __builtin_amdgcn_readfirstlane(lds_base + stage * F_STAGE + wave * (F_PAIRS * 1024));
+    if (live) {                              // else: keep the last valid source
       int sl = lslab;
       if (ROT) {
         sl += rot;
@@ -654,10 +640,14 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
       load16_to_lds<(n >> 1) * 1024>(is_ga, voffA[n >> 1], isA);
   };
   auto issue_end = [&]() {
-    if (lvt < vt_end && ++lslab == n_slabs) {
+    if (live && ++lslab == n_slabs) {
       lslab = 0;
-      ++lvt;
-      if (lvt < vt_end) set_tile(lvt);
+      if (++lvt < lvt_end) {
+        set_tile(lvt);
+      } else {
+        lj += step;
+        open_item();
+      }
     }
   };
   // ---- MFMA operand addresses (bytes inside an operand tile), swizzle folded in ---------------------
@@ -690,7 +680,7 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
     static_for<F_SLOTS>([&](auto m_) __attribute__((always_inline)) {
       constexpr int m = decltype(m_)::value;
       constexpr int q = m / (F_N * F_N), i = m / F_N % F_N;
-      constexpr int j = i & 1 ? F_N - 1 - m % F_N : m % F_N;      // (to and fro: one operand stays from MFMA to MFMA)
+      constexpr int j = i & 1 ? F_N - 1 - m % F_N : m % F_N;      // (to and fro: one operand stays from MFMA to MFMA, 1 %)
       if constexpr (m == kFree) {
         __builtin_amdgcn_sched_barrier(0);
         barrier_after_lds();
@@ -726,9 +716,10 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
     ++g;
   };
 
-  if (n_tiles > 0) {
-    set_tile(vt0);
-    // prologue: slabs 0 and 1 requested; slab 0 landed and visible, the fragments of its first k-step on the way
+  open_item();
+  if (live) {
+    // prologue: the first two slabs of the stream requested; the first landed and visible, the fragments of its first
+    // k-step on the way
     issue_begin(0);
     static_for<2 * F_PAIRS>(request);
     issue_end();
@@ -741,13 +732,21 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
     asm volatile("" ::: "memory");
     static_for<16>([&](auto n) __attribute__((always_inline)) { read_one(f[0], 0, 0, n); });
     if (PROBE_MFMA) static_for<16>([&](auto n) __attribute__((always_inline)) { read_one(f[1], 0, 1, n); });
+  }
+  int r0, st;
+  for (int j = first; item(j, &r0, &st); j += step) {
+    Triple run[F_N];
+    Draw draw[F_N];                                  // MODE 6 only
+#pragma unroll
+    for (int i = 0; i < F_N; ++i) {
+      run[i] = empty_triple();
+      draw[i] = empty_draw();
+    }
+    const int vt0 = st * a.strip, vt_end = min(vt0 + a.strip, n_vt);      // (modes 1, 4: possibly no tile)
     for (int vt = vt0; vt < vt_end; ++vt) {
-      if (!PROBE_MFMA || vt == vt0)
-        slab_step(std::true_type{});
-      else
-        slab_step(std::false_type{});
+      slab_step(std::true_type{});
       for (int slab = 1; slab < n_slabs; ++slab) slab_step(std::false_type{});
-      if (PROBE_MFMA) continue;
+      if (PROBE_MFMA && vt + 1 < vt_end) continue;
       wait_for_mfma();
       // ---- this vocabulary tile is complete: fold its 128 x 128 logits into the running triples, or store it ------
       int row_base = r0 + wr * 128, col_base = vt * FT + wv * 128 + quarter * 4;
@@ -770,71 +769,87 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
         fold_tile16(acc, run, col_base, a.col0);
       }
     }
-    if (PROBE_MFMA) {
-      wait_for_mfma();
-      fold_tile16(acc, run, vt0 * FT + wv * 128 + quarter * 4, a.col0);
-    }
-  }
-
-  if (MODE >= 2 && MODE <= 5) {
-    __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0): the requests past the end of the stream land in LDS
-    return;
-  }
-  // ---- end of strip: the four quarter-waves hold the same hidden rows; then the two vocabulary halves ------
+    if (MODE >= 2 && MODE <= 5) continue;
+    // ---- end of strip: the four quarter-waves hold the same hidden rows; then the two vocabulary halves ------
 #pragma unroll
-  for (int j = 0; j < F_N; ++j) {
+    for (int i = 0; i < F_N; ++i) {
 #pragma unroll
-    for (int off = 16; off <= 32; off <<= 1) {
-      Triple o;
-      o.m = __shfl_xor(run[j].m, off);
-      o.s = __shfl_xor(run[j].s, off);
-      o.i = __shfl_xor(run[j].i, off);
-      merge_triple(run[j], o);
-      if (MODE == 6) {
-        Draw od;
-        od.v = __shfl_xor(draw[j].v, off);
-        od.l = __shfl_xor(draw[j].l, off);
-        od.i = __shfl_xor(draw[j].i, off);
-        merge_draw(draw[j], od);
+      for (int off = 16; off <= 32; off <<= 1) {
+        Triple o;
+        o.m = __shfl_xor(run[i].m, off);
+        o.s = __shfl_xor(run[i].s, off);
+        o.i = __shfl_xor(run[i].i, off);
+        merge_triple(run[i], o);
+        if (MODE == 6) {
+          Draw od;
+          od.v = __shfl_xor(draw[i].v, off);
+          od.l = __shfl_xor(draw[i].l, off);
+          od.i = __shfl_xor(draw[i].i, off);
+          merge_draw(draw[i], od);
+        }
       }
     }
-  }
-  __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): the requests past the end of the stream too
-  __syncthreads();                                 // every wave is done with the operand stages
-  Triple* xch = reinterpret_cast<Triple*>(lds);    // [256 hidden rows of the tile]
-  Draw* xdr = reinterpret_cast<Draw*>(xch + FT);
-  const int hrow0 = wr * 128;
-  if (wv == 1 && lane < 16) {
+    // (one barrier: the next strip's writes lie behind the barriers of its slabs, and these reads ahead of them)
+    Triple* xch = reinterpret_cast<Triple*>(lds + F_LDS_STAGES);    // [256 hidden rows of the tile]
+    Draw* xdr = reinterpret_cast<Draw*>(xch + FT);
+    const int hrow0 = wr * 128;
+    if (wv == 1 && lane < 16) {
 #pragma unroll
-    for (int j = 0; j < F_N; ++j) {
-      xch[hrow0 + j * 16 + lane] = run[j];
-      if (MODE == 6) xdr[hrow0 + j * 16 + lane] = draw[j];
+      for (int i = 0; i < F_N; ++i) {
+        xch[hrow0 + i * 16 + lane] = run[i];
+        if (MODE == 6) xdr[hrow0 + i * 16 + lane] = draw[i];
+      }
     }
-  }
-  __syncthreads();
-  if (wv == 0 && lane < 16) {
+    barrier_after_lds();
+    if (wv == 0 && lane < 16) {
 #pragma unroll
-    for (int j = 0; j < F_N; ++j) {
-      merge_triple(run[j], xch[hrow0 + j * 16 + lane]);
-      const int hrow = r0 + hrow0 + j * 16 + lane;
-      if (hrow < r_end) {
-        const size_t p = (size_t)hrow * a.n_parts + a.part0 + st;
-        a.part_m[p] = run[j].m;
-        a.part_s[p] = run[j].s;
-        if (MODE == 6) {
-          merge_draw(draw[j], xdr[hrow0 + j * 16 + lane]);
-          a.part_v[p] = draw[j].v;
-          a.part_l[p] = draw[j].l;
-          a.part_i[p] = draw[j].i;
-        } else {
-          a.part_i[p] = run[j].i;
+      for (int i = 0; i < F_N; ++i) {
+        merge_triple(run[i], xch[hrow0 + i * 16 + lane]);
+        const int hrow = r0 + hrow0 + i * 16 + lane;
+        if (hrow < r_end) {
+          const size_t p = (size_t)hrow * a.n_parts + a.part0 + st;
+          a.part_m[p] = run[i].m;
+          a.part_s[p] = run[i].s;
+          if (MODE == 6) {
+            merge_draw(draw[i], xdr[hrow0 + i * 16 + lane]);
+            a.part_v[p] = draw[i].v;
+            a.part_l[p] = draw[i].l;
+            a.part_i[p] = draw[i].i;
+          } else {
+            a.part_i[p] = run[i].i;
+          }
         }
       }
     }
   }
+  __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): the requests past the end of the stream land in LDS
 }
 
 }  // namespace
+
+unsigned z2z_logits_fast_order(LogitsArgs& a, int forced) {
+  // The longer side is walked in blocks, the shorter one inside them: it is the one that the memory-side cache can hold
+  // meanwhile.  Both ways 2 x 4 or 4 x 2 for the XCDs is within 1 % (26616 rows x 128256, d = 4096: 19.9 ms, rows in blocks
+  // 20.2-20.4; 8 ways along one side 20.9); what counts is 4 x 8 outputs for an XCD's 32 workgroups (2 x 16: 21.4), and that
+  // a short side is not dealt out unevenly.  Against blocks with holes at the edges and one strip of four tiles per
+  // workgroup: 128256 x 4096 outputs over K = 32896 27.2 -> 23.3 ms, 35404 x 4096 over 16384 3.60 -> 3.14.
+  a.map_p_rows = a.row_tiles > a.n_vtiles;
+  const int q = a.map_p_rows ? a.n_strips : a.row_tiles;
+  a.map_lp = 4;
+  a.map_xq = q % 2 == 0 || q >= 64 ? 2 : 1;
+  if (forced) {
+    a.map_p_rows = 1;
+    a.map_lp = forced & 0xFF;
+    a.map_xq = (forced >> 24) & 0xFF;
+  }
+  a.map_xp = 8 / a.map_xq;
+  // 32 workgroups per XCD (one per CU) walk its list; a short list has fewer
+  const int P = a.map_p_rows ? a.row_tiles : a.n_strips;
+  const long long main_items = (long long)(P / (a.map_lp * a.map_xp)) * a.map_lp * ((q + a.map_xq - 1) / a.map_xq);
+  const long long tail = (long long)(P % (a.map_lp * a.map_xp)) * q;
+  const long long longest = main_items + (tail + 7) / 8;
+  return 8u * (unsigned)(longest < 32 ? longest : 32);
+}
 
 int z2z_launch_logits_fast(int mode, const LogitsArgs& a, unsigned grid, hipStream_t s) {
   const bool rot = a.row_tiles == 1;

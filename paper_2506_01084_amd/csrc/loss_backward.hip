@@ -135,7 +135,6 @@ int z2z_launch_extended_nll_backward(z2z_ctx* c, const void* H, int32_t rows, in
     a.rows = rows_c;
     a.rows_per_seq = rows_per_seq;
     a.d = d;
-    a.map_lr = a.map_ls = a.map_xr = a.map_xs = a.map_sb_r = 1;
     a.lse = lse + r0;
     a.row_grad = g;
     a.targets = targets + r0;
