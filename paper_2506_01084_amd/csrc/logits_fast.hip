@@ -831,12 +831,13 @@ unsigned z2z_logits_fast_order(LogitsArgs& a, int forced) {
   // The longer side is walked in blocks, the shorter one inside them: it is the one that the memory-side cache can hold
   // meanwhile.  Both ways 2 x 4 or 4 x 2 for the XCDs is within 1 % (26616 rows x 128256, d = 4096: 19.9 ms, rows in blocks
   // 20.2-20.4; 8 ways along one side 20.9); what counts is 4 x 8 outputs for an XCD's 32 workgroups (2 x 16: 21.4), and that
-  // a short side is not dealt out unevenly.  Against blocks with holes at the edges and one strip of four tiles per
+  // a short side is not dealt out unevenly.  (Up to 4 row tiles meet a weight tile on one XCD, which fetches it once: 300 rows 482 -> 471
+  // us, 800 rows 850 -> 839; 6 and 14 row tiles lose 1.5 % that way.)  Against blocks with holes at the edges and one strip of four tiles per
   // workgroup: 128256 x 4096 outputs over K = 32896 27.2 -> 23.3 ms, 35404 x 4096 over 16384 3.60 -> 3.14.
   a.map_p_rows = a.row_tiles > a.n_vtiles;
   const int q = a.map_p_rows ? a.n_strips : a.row_tiles;
   a.map_lp = 4;
-  a.map_xq = q % 2 == 0 || q >= 64 ? 2 : 1;
+  a.map_xq = q > 4 && (q % 2 == 0 || q >= 64) ? 2 : 1;
   if (forced) {
     a.map_p_rows = 1;
     a.map_lp = forced & 0xFF;
