@@ -153,7 +153,7 @@ int ensure_partial(z2z_ctx* c, size_t need, hipStream_t s) {
 }  // namespace
 
 int z2z_launch_linear_parts(z2z_ctx* c, const void* A, const void* W, int R, const int32_t* rows_dev, int N, int K,
-                            bool k_on_device, const float** partial, int* ksplit_out, hipStream_t s) {
+                            bool k_on_device, const float** partial, int* ksplit_out, hipStream_t s, bool once) {
   *ksplit_out = 0;
   // up to 128 rows (a decode step's new entries through the learned encoder at a small batch): bound by the weight
   // bytes; the weight-streaming kernel with K split over workgroups, its fp32 partial tiles summed with the layer's
@@ -165,7 +165,7 @@ int z2z_launch_linear_parts(z2z_ctx* c, const void* A, const void* W, int R, con
     int rc = ensure_partial(c, (size_t)ksplit * R * N * sizeof(float), s);
     if (rc != Z2Z_OK) return rc;
     *partial = reinterpret_cast<const float*>(c->skinny_partial);
-    return z2z_launch_linear_mid(c, A, W, R, rows_dev, N, K, reinterpret_cast<float*>(c->skinny_partial),
+    return z2z_launch_linear_mid(c, A, W, R, rows_dev, N, K, once, reinterpret_cast<float*>(c->skinny_partial),
                                  c->skinny_partial_bytes / sizeof(float), ksplit_out, s);
   }
   // more rows than the 64 the decode-step kernel serves per pass over the weights, but fewer 256 x 256 output
@@ -215,11 +215,11 @@ bool z2z_linear_takes_pitch(const z2z_ctx* c, int R, int N, int K) {
 
 int z2z_launch_linear(z2z_ctx* c, const void* A, const void* W, const float* bias, const void* residual, int act,
                       void* out, int R, const int32_t* rows_dev, int N, int K, hipStream_t s, const int32_t* k_dev,
-                      bool stream_f32, const z2z_linear_pitch* pitch) {
+                      bool stream_f32, const z2z_linear_pitch* pitch, bool once) {
   if (pitch && !z2z_linear_takes_pitch(c, R, N, K)) return Z2Z_EUNSUPPORTED;
   const float* partial = nullptr;
   int ksplit = 0;
-  int rc = z2z_launch_linear_parts(c, A, W, R, rows_dev, N, K, k_dev != nullptr, &partial, &ksplit, s);
+  int rc = z2z_launch_linear_parts(c, A, W, R, rows_dev, N, K, k_dev != nullptr, &partial, &ksplit, s, once);
   if (rc != Z2Z_OK) return rc;
   if (ksplit > 0) {
     const long long n_threads = (long long)R * (N / 4);

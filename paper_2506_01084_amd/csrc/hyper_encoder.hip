@@ -809,6 +809,8 @@ int z2z_launch_hyper_encode(z2z_ctx* c, const void* E, const z2z_encoder* enc, v
   const bool incremental = first || max_new > 0;
   const int units = incremental ? (max_new < 1 ? cap : (max_new < cap ? max_new : cap)) : cap;
   const int dff = enc->attention_only ? 0 : enc->d_ff;
+  // (few rows: does anything of the weights stay in the memory-side cache until the next call?)
+  const bool once = (size_t)enc->n_layers * ((size_t)4 * d + (size_t)2 * dff) * d * sizeof(uint16_t) > z2z_logits::kKeepBytes;
   // rows per pass: all sequences, u_step entries each, M slots per entry
   long long u_step = 65536 / ((long long)B * M);
   if (u_step < 1) u_step = 1;
@@ -877,10 +879,10 @@ int z2z_launch_hyper_encode(z2z_ctx* c, const void* E, const z2z_encoder* enc, v
       // (with more rows -- K is split there too in a narrow encoder -- a wave per row is the better LayerNorm: 6144 rows,
       // d = 256: the pass 275 us fused, 267 in launches of their own)
       if (!padded && R <= E_FEW_ROWS)
-        ret = z2z_launch_linear_parts(c, in, w, R, rows_dev, d, K, false, &parts.partial, &parts.ksplit, s);
+        ret = z2z_launch_linear_parts(c, in, w, R, rows_dev, d, K, false, &parts.partial, &parts.ksplit, s, once);
       if (ret != Z2Z_OK) return ret;
       if (parts.ksplit == 0)
-        return z2z_launch_linear(c, in, w, bias, residual, 0, out, R, rows_dev, d, K, s, nullptr, true, padded ? &pitch : nullptr);
+        return z2z_launch_linear(c, in, w, bias, residual, 0, out, R, rows_dev, d, K, s, nullptr, true, padded ? &pitch : nullptr, once);
       parts.R = R;
       parts.bias = bias;
       parts.residual = residual;
@@ -908,7 +910,7 @@ int z2z_launch_hyper_encode(z2z_ctx* c, const void* E, const z2z_encoder* enc, v
         hipLaunchKernelGGL(enc_norm_kernel<false>, dim3(row_blocks), dim3(256), 0, s, m, nullptr, nullptr, x,
                            reinterpret_cast<uint4*>(A), lay.ln1_g, lay.ln1_b, n_units);
       }
-      rc = z2z_launch_linear(c, A, lay.w_qkv, lay.b_qkv, nullptr, 0, QKV, R, rows_dev, 3 * d, d, s);
+      rc = z2z_launch_linear(c, A, lay.w_qkv, lay.b_qkv, nullptr, 0, QKV, R, rows_dev, 3 * d, d, s, nullptr, false, nullptr, once);
       if (rc != Z2Z_OK) return rc;
       const long long att_waves = (long long)n_units * groups;
       hipLaunchKernelGGL(enc_attention_kernel, dim3((unsigned)((att_waves + 3) / 4)), dim3(256), 0, s, m,
@@ -929,7 +931,7 @@ int z2z_launch_hyper_encode(z2z_ctx* c, const void* E, const z2z_encoder* enc, v
                              reinterpret_cast<uint4*>(A), lay.ln2_g, lay.ln2_b, n_units);
         const z2z_linear_pitch to_wide = {d, d, dffp};
         rc = z2z_launch_linear(c, A, lay.w_1, lay.b_1, nullptr, 1, F, R, rows_dev, dff, d, s, nullptr, false,
-                               dffp != dff ? &to_wide : nullptr);
+                               dffp != dff ? &to_wide : nullptr, once);
         if (rc != Z2Z_OK) return rc;
         rc = layer_out(F, lay.w_2, lay.b_2, y, x, dff, next ? next->ln1_g : nullptr, next ? next->ln1_b : nullptr, &fused);
         if (rc != Z2Z_OK) return rc;

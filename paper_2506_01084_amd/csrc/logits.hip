@@ -331,23 +331,24 @@ static int pick_strip_for(const z2z_ctx* c, long long row_tiles, int n_vt, int w
 // A decode step of 5..64 sequences whose base vocabulary goes to the weight-streaming kernel, with the hyper units in a
 // launch of their own, instead of the decode kernel's base and hyper units in one.  Either kernel has one tile of 256 weight
 // rows per CU, so a last round of tiles that leaves CUs idle costs as much as a full one -- but in the decode kernel the
-// hyper units run there.  Greedy, d = 4096, hyper units of 1000 entries, cap = 1024, us, one launch -> split:
-//   tiles (of the rounds')   8 sequences     24             40             64
-//   384 (of 512)             195 -> 188      209 -> 208     230 -> 229     230 -> 260
-//   448 (of 512)             210 -> 193      236 -> 214     286 -> 235     298 -> 266
-//   501 (V = 128256)         280 -> 203      287 -> 223     294 -> 243     300 -> 272
-//   594 (of 768, V = 151936) 289 -> 276      297 -> 297     308 -> 319     322 -> 350
-// Hence: up to 16 sequences, or a last round at least 7/8 full over all rounds, or hyper units that would open another
-// round in one launch (with short histories most of them are empty: 64 sequences with 100 entries over 594 tiles 297 -> 289).
-// At most 256 tiles stay (V = 32064, 40 sequences, 203 -> 217), and so does a draw, whose generator would run in the
-// streaming kernel's epilogue with nothing beside it (V = 128256, 64 sequences: 338 -> 375).
+// hyper units run there.  d = 4096 (V = 151936: 3584), hyper units of 1000 entries, cap = 1024, us, one launch -> split:
+//   tiles (of the rounds')            8 sequences   24           40           64
+//   256 (V = 65536)         draw      205 -> 113    213 -> 131   220 -> 156   220 -> 183
+//   501 (of 512, 128256)    greedy    280 -> 180    287 -> 200   294 -> 217   300 -> 246
+//                           draw      315 -> 205    321 -> 224   325 -> 254   329 -> 284
+//                           filtered  305 -> 253    318 -> 266   327 -> 276   339 -> 285
+//   594 (of 768, 151936)    greedy    289 -> 207    270 -> 226   279 -> 243   299 -> 270
+//                           draw      292 -> 242    300 -> 262   307 -> 297   324 -> 323
+//                           filtered  286 -> 278    299 -> 295   314 -> 306   336 -> 317
+// Hence: up to 16 sequences, or more than two rounds, or a last round at least 7/8 full over all rounds, or hyper units that
+// would open another round in one launch.  At most 256 tiles stay (V = 32064, 40 sequences, 203 -> 217 before the ring).
 static bool split_few(const z2z_ctx* c, int rows) {
   const long long tiles = z2z_logits_mid_tiles(c->cfg.V), slots = (tiles + 255) / 256 * 256;
   int base_columns, hyper_columns;
   z2z_logits_decode_units(&base_columns, &hyper_columns);
   const long long units = (long long)rows * ((c->cfg.cap + hyper_columns - 1) / hyper_columns);
   return rows > 4 && rows <= 64 && c->opt_decode_kernel == 0 && c->opt_logits_kernel == 0 && tiles >= 256 &&
-         (rows <= 16 || 8 * tiles >= 7 * slots || tiles + units > slots) && z2z_logits_mid_ok(c, rows);
+         (rows <= 16 || tiles > 512 || 8 * tiles >= 7 * slots || tiles + units > slots) && z2z_logits_mid_ok(c, rows);
 }
 
 // Parts per row that any kind of step may leave (hyper units of 64 rows): every step sizes the scratch for all of them,
@@ -504,12 +505,14 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
   sp.seed = seed;
   sp.step = step;
   const bool timed = c->opt_timing && c->n_timed < Z2Z_MAX_TIMED && c->ev_created;
-  // 65..192 rows: the base vocabulary goes to the weight-streaming kernel (with the tile kernel's sampling epilogues)
-  const bool mid_base = rows > 64 && c->opt_logits_kernel == 0 && z2z_logits_mid_ok(c, rows);
+  // 65..192 rows, and fewer by the rule of a greedy step: the base vocabulary goes to the weight-streaming kernel (with the
+  // tile kernel's sampling epilogues)
+  const bool mid_base = (rows > 64 || split_few(c, rows)) && c->opt_logits_kernel == 0 && z2z_logits_mid_ok(c, rows);
+  const bool timed_pair = timed && mid_base && rows <= 64;       // a split step's two launches are timed together
   if (top_k <= 0 && top_p >= 1.0f && (rows > 128 || mid_base) && c->cfg.d % 64 == 0 && c->fast_ready &&
       c->opt_logits_kernel != 1) {
     // no filter, more than two passes of the decode kernel's base units (the generator in the tile kernel's
-    // epilogue costs more than the second pass): as for the argmax, the tile kernel takes the base vocabulary
+    // epilogue costs more than the second pass), or the streaming kernel: as for the argmax, the tile kernel takes the base vocabulary
     // (with the draw folded into its epilogue) and the hyper units run alone
     const int base_vt = (c->cfg.V + 255) / 256;
     const int strip_b = mid_base ? 1 : pick_strip_for(c, (rows + 255) / 256, base_vt);
@@ -518,7 +521,8 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     n_parts = base_strips + (c->cfg.cap + unit - 1) / unit;
     rc = ensure_scratch(c, (size_t)n_parts * rows, s);
     if (rc != Z2Z_OK) return rc;
-    rc = ensure_sample_scratch(c, (size_t)n_parts * rows, s);
+    // (a step's scratch serves every kind of step, captured ones too)
+    rc = ensure_sample_scratch(c, std::max((size_t)n_parts, step_parts(c)) * rows, s);
     if (rc != Z2Z_OK) return rc;
     LogitsArgs a;
     memset(&a, 0, sizeof(a));
@@ -532,13 +536,14 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     a.part_v = c->part_v;
     a.part_l = c->part_l;
     a.n_parts = n_parts;
-      a.sample = 1;
+    a.sample = 1;
     a.inv_temperature = 1.0f / temperature;
     a.key0 = (uint32_t)seed;
     a.key1 = (uint32_t)(seed >> 32);
     a.ctr2 = (uint32_t)step;
     a.ctr3 = (uint32_t)(step >> 32);
     int ns = 0;
+    if (timed_pair) Z2Z_HIP_TRY(hipEventRecord(c->ev_start[c->n_timed], s));
     if (mid_base)
       rc = z2z_launch_logits_mid(c, a, W_base, c->cfg.V, 0, s);
     else
@@ -549,6 +554,7 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
       rc = z2z_launch_logits_decode(c, H, W_base, W_hyper, &np, false, &sp, nullptr, s, base_strips, nullptr, 1, unit);
       if (rc != Z2Z_OK) return rc;
     }
+    if (timed_pair) Z2Z_HIP_TRY(hipEventRecord(c->ev_stop[c->n_timed++], s));
     hipLaunchKernelGGL(sample_combine_kernel, dim3(rows), dim3(256), 0, s, c->part_m, c->part_s, c->part_v,
                        c->part_l, c->part_i, n_parts, rows, token, logprob);
     Z2Z_HIP_TRY(hipGetLastError());
@@ -583,8 +589,8 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     c->sample_logits_capacity = need;
   }
   int base_columns = 0;                              // of a base part: the decode kernel's unit unless set
-  if (rows > 64 && c->cfg.d % 64 == 0 && c->fast_ready && c->opt_logits_kernel != 1) {
-    // more than one pass of the decode kernel's base units: the tile kernel stores and folds the base
+  if ((rows > 64 || mid_base) && c->cfg.d % 64 == 0 && c->fast_ready && c->opt_logits_kernel != 1) {
+    // more than one pass of the decode kernel's base units, or a split step: the tile or the streaming kernel stores and folds the base
     // vocabulary's scaled logits, the hyper units run alone (strips of at most 2 tiles: the selection kernels'
     // short-list pass takes parts of up to 512 columns)
     const int base_vt = (c->cfg.V + 255) / 256;
@@ -605,11 +611,12 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     a.part_s = c->part_s;
     a.part_i = c->part_i;
     a.n_parts = n_parts;
-      a.sample = 2;
+    a.sample = 2;
     a.inv_temperature = 1.0f / temperature;
     a.logits = c->sample_logits;
     a.ld = c->cfg.V + c->cfg.cap;
     int ns = 0;
+    if (timed_pair) Z2Z_HIP_TRY(hipEventRecord(c->ev_start[c->n_timed], s));
     if (mid_base)
       rc = z2z_launch_logits_mid(c, a, W_base, c->cfg.V, 0, s);
     else
@@ -620,6 +627,7 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
       rc = z2z_launch_logits_decode(c, H, W_base, W_hyper, &np, false, &sp, c->sample_logits, s, base_strips);
       if (rc != Z2Z_OK) return rc;
     }
+    if (timed_pair) Z2Z_HIP_TRY(hipEventRecord(c->ev_stop[c->n_timed++], s));
   } else {
     rc = z2z_launch_logits_decode(c, H, W_base, W_hyper, &n_parts, timed, &sp, c->sample_logits, s);
     if (rc != Z2Z_OK) return rc;

@@ -240,7 +240,12 @@ struct LogitsArgs {
   // K beyond *k_dev, up to the next multiple of 64, holds zeros and the slabs after that are not read
   const int32_t* k_dev;
   int32_t ldh, ldw;         // row pitch of H and W in elements (dense layers; 0: d)
+  int32_t once;             // weight-streaming kernel: the weights are read past the caches
 };
+
+// Weights of up to this many bytes are read through the memory-side cache (256 MB), where the next step finds them; more
+// go past the caches (logits_decode.hip has the figures).
+constexpr size_t kKeepBytes = (size_t)128 << 20;
 
 // fold_tile for a filtered sampled pick: x = logit * inv_temperature enters the running triple and is stored,
 // fp32, at logits[row, col0 + column] (the selection kernels read the rows back); 16-byte stores where the four
@@ -251,6 +256,7 @@ __device__ __forceinline__ void fold_tile_store(const f32x16 (&acc)[NI][NJ], Tri
   const int lane31 = threadIdx.x & 31;
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
+    if (row_base + j * 32 >= r_end) break;           // (uniform)
     const int row = row_base + j * 32 + lane31;
     float* out = a.logits + (size_t)min(row, r_end - 1) * a.ld + a.col0;
 #pragma unroll
@@ -308,6 +314,7 @@ __device__ __forceinline__ void fold_tile_sample(const f32x16 (&acc)[NI][NJ], Tr
   const int lane31 = threadIdx.x & 31;
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
+    if (row_base + j * 32 >= a.rows) break;          // (uniform; 24 sequences over 128256 columns: 236 -> 224 us)
     const uint32_t row = (uint32_t)(row_base + j * 32 + lane31);
     Triple t = run[j];
     Draw dr = draw[j];
@@ -412,7 +419,8 @@ struct z2z_linear_pitch {
 };
 int z2z_launch_linear(z2z_ctx* c, const void* A, const void* W, const float* bias, const void* residual, int act,
                       void* out, int R, const int32_t* rows_dev, int N, int K, hipStream_t s, const int32_t* k_dev = nullptr,
-                      bool stream_f32 = false, const z2z_linear_pitch* pitch = nullptr);
+                      bool stream_f32 = false, const z2z_linear_pitch* pitch = nullptr,
+                      bool once = false);
 // Row pitch for n columns of an activation that is an operand of dense layers: n, or 64 more where n columns are a
 // multiple of 4 KiB -- the tile kernel's workgroups read the same slab of 256 rows at a time, and rows that far apart
 // on a power of two put it on a few memory channels (35400 rows x 4096 columns, K = 16384: 1.07 -> 1.18
@@ -426,7 +434,7 @@ bool z2z_linear_takes_pitch(const z2z_ctx* c, int R, int N, int K);
 // [*ksplit][R][N] at *partial, which the caller adds up in order before the next dense layer is launched; *ksplit = 0:
 // the layer is not split at this shape, nothing was launched.
 int z2z_launch_linear_parts(z2z_ctx* c, const void* A, const void* W, int R, const int32_t* rows_dev, int N, int K,
-                            bool k_on_device, const float** partial, int* ksplit, hipStream_t s);
+                            bool k_on_device, const float** partial, int* ksplit, hipStream_t s, bool once = false);
 int z2z_logits_fast_prepare(z2z_ctx* c);
 int z2z_launch_logits_part(z2z_ctx* c, bool hyper, z2z_logits::LogitsArgs a, const void* W, int w_rows, int col0,
                            int part0, int strip, int rows, int rows_per_seq, int* n_strips_out, bool timed,

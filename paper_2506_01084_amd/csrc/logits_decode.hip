@@ -61,7 +61,6 @@ constexpr int D_MAXQ = 8;              // hyper units: d <= 512 * D_MAXQ
 // (256 MB), and the first one is as fast.  One sequence, us in a row / with other weights each time, plain and streamed:
 // V = 32000, d = 1024 (68 MB) 33 / 41 and 41 / 41; V = 32064, d = 3072 (203 MB) 49 / 67 and 65 / 65 -- between two steps
 // of a model of that size its own layers pass through the cache; V = 128256, d = 4096 (1 GB) 199 / 199 and 184 / 184.
-constexpr size_t kKeepBytes = (size_t)128 << 20;
 template <bool ONCE>
 __device__ __forceinline__ uint4 load_weights(const uint4* p) {
   typedef __attribute__((__vector_size__(16))) uint32_t u32x4;

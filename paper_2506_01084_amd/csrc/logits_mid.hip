@@ -3,23 +3,26 @@
 // small batch, a short chunk; dense layers on up to 128 rows.  (zip2zip paper, section 2.3, steps 7-9.)
 //
 // With so few rows the part is bound by the bytes of W_base, like the one-row-per-sequence step.  That kernel's
-// base units hold 64 hidden rows in registers (one pass over W_base per 64 rows); the 256 x 256 tile kernel stages
-// both operands through two LDS stages and waits for memory once per slab (3.4-3.5 TB/s of weights at these row
-// counts).  Here the weights never touch LDS:
+// base units hold 64 hidden rows in registers (one pass over W_base per 64 rows); the 256 x 256 tile kernel shares
+// both operands between its waves, which meet at every slab (3.4-3.5 TB/s of weights at these row counts).  Here:
 //
 //   workgroup = 8 waves = one tile of 256 weight rows x all hidden rows; wave w owns weight rows 32 w .. 32 w + 31:
 //   2, 4 or 6 blocks of v_mfma_f32_32x32x16_bf16 (the kernel is built for up to 64, 128 and 192 rows).
-//   K advances in slabs of 64.  A wave loads its own weight fragments straight from global memory in MFMA operand
-//   layout (lane = row, 16 bytes of each 32-byte k-step; the four k-steps of a slab use up whole 128-byte lines),
-//   two slabs at a time (256 contiguous bytes per row: +5 % over single slabs), four to five slabs ahead of their
-//   use in six register buffers (two to three ahead in four with 6 blocks of accumulators).  The hidden rows of a
-//   slab (up to 192 x 128 bytes, shared by the 8 waves, served by
-//   L2) go straight from global memory into one of three LDS stages, two slabs ahead, in the tile kernel's
-//   swizzled layout (conflict-free operand reads); one barrier per slab.
+//   K advances in slabs of 64.  Up to 128 rows a wave moves its own weights straight from global memory into a ring of its
+//   own in LDS, four requests of 8 whole lines per slab, two or three slabs ahead, and reads its operands from there; nobody else
+//   touches the ring, so it needs no barrier.  (Loaded in operand layout, 32 rows and half a line each way, a
+//   request takes 64 pieces of 16 bytes: 1 GB of weights for 64 rows 190 us; through the ring 180; and since
+//   every request takes whole lines, the weights can go past the caches, which the halves of a line cannot: 162, 6.5 TB/s.)
+//   In the 192-row build the hidden rows leave no room for a ring: weights in operand layout in four register buffers,
+//   two to three slabs ahead, two slabs at a time (256 contiguous bytes per row: +5 % over single slabs).
+//   The hidden rows of a slab (up to 192 x 128 bytes, shared by the 8 waves, served by L2) go straight from global memory
+//   into one of three LDS stages, two slabs ahead, in the tile kernel's swizzled layout (conflict-free operand
+//   reads); one barrier per slab.
 //   The tiles start their walk over K at different slabs (+5-7 %: see below).
 //
-// Measured at V = 128256, d = 4096: 4.1-4.9 TB/s of W_base (the tile kernel: 3.4-3.5; the decode kernel's base
-// units in a launch of their own: 4.5 at up to 64 rows).  The fold of the finished tile into (max, sum-exp,
+// V = 128256, d = 4096, whole calls in us, operand-layout loads -> ring: 8 x 5 rows 207 -> 187, 24 x 5 258 -> 211, steps of
+// 16 / 64 / 100 / 128 sequences 213 -> 185, 272 -> 244, 340 -> 300, 365 -> 323; 192 rows stay at 4.1 TB/s of W_base.
+// The fold of the finished tile into (max, sum-exp,
 // argmax) triples is the tile kernel's; the 8 waves' triples of a hidden row are merged through LDS and leave one
 // part per (row, weight tile).
 #include "logits_mid.h"
@@ -39,14 +42,7 @@ constexpr int M_SLAB = 128;               // bytes per row per K slab (64 bf16)
 constexpr int M_STAGE = M_HT * M_SLAB;    // the hidden rows of one slab: 24 KiB
 constexpr int M_NSTAGE = 3;
 constexpr int M_LDS = M_NSTAGE * M_STAGE;
-constexpr int M_LDS_LEVELS = M_LDS + 32 * M_THREADS * 4;   // decode steps: the third level of their sums
-// weight register buffers per instance (what fits beside 16 NJV accumulators without spilling inside the K loop)
-#ifndef M_NBUF
-#define M_NBUF 6                          // up to 128 hidden rows
-#endif
-#ifndef M_NBUF_6
-#define M_NBUF_6 4                        // up to 192 (96 accumulator registers)
-#endif
+constexpr int M_NBUF_6 = 4;               // weight register buffers of the 192-row build (what fits beside 96 accumulators)
 // 1: the weights of two consecutive slabs are requested together, every other step: 256 contiguous bytes per row
 #ifndef M_PAIR
 #define M_PAIR 1
@@ -63,6 +59,14 @@ __device__ __forceinline__ void load16_to_lds(const unsigned char* base, uint32_
                : "memory");
 }
 
+// The same for bytes that nothing reads again before the caches have turned over: past them.
+__device__ __forceinline__ void load16_to_lds_once(const unsigned char* base, uint32_t lane_offset, uint32_t lds_dst) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
+               :
+               : "v"(lane_offset), "s"(base), "s"(lds_dst)
+               : "memory");
+}
+
 // Wait until at most N of this wave's loads are in flight.  Inline assembly with a memory clobber: the compiler
 // moves no load across it, so the number of requests that follow a given one is the number written below.
 template <int N>
@@ -74,18 +78,21 @@ __device__ __forceinline__ uint32_t lds_offset_of(const void* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
 }
 
-// NJV: blocks of 32 hidden rows the instance is built for (rows of the tile <= 32 NJV); NBUF: weight register
-// buffers (slabs in flight + the one in use); SMODE: 0 = fold the logits, 1 = fold logit / T and the Gumbel-max
+// NJV: blocks of 32 hidden rows the instance is built for (rows of the tile <= 32 NJV); RING: slabs of the waves' rings
+// (those in flight + the one in use), 0: register buffers; SMODE: 0 = fold the logits, 1 = fold logit / T and the Gumbel-max
 // draw (a.sample = 1: part_v, part_l, and the drawn column in part_i), 2 = store logit / T and fold it
 // (a.sample = 2) -- the tile kernel's epilogues for its modes 0, 6 and 7; 3 = a dense layer with K split over
-// gridDim.y workgroups per tile: the fp32 partial tile goes to a.partial[ks][row][col] (the tile kernel's mode 5).
-template <int NJV, int NBUF, int SMODE>
-__global__ void __launch_bounds__(M_THREADS) logits_mid_kernel(LogitsArgs a) {
-  extern __shared__ __align__(1024) unsigned char lds[];
+// gridDim.y workgroups per tile: the fp32 partial tile goes to a.partial[ks][row][col] (the tile kernel's mode 5);
+// 4, 5, 6 = 0, 1, 2 with the sums in levels, for a step of up to 64 sequences.
+template <int NJV, int RING, int SMODE>
+__device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int half = lane >> 5;
+  constexpr int NBUF = M_NBUF_6;
+  constexpr int STAGE = 32 * NJV * M_SLAB, STAGES = M_NSTAGE * STAGE;
+  constexpr int W_SLAB = 32 * M_SLAB;                      // a wave's weights of one slab
   const int vt = blockIdx.x;                               // weight tile
   const int r0 = 0;                                        // (one row tile: the call has at most M_HT rows)
   // SMODE 3 (a dense layer's partial sums): the rows that exist may be known on the device only, and blockIdx.y is
@@ -111,13 +118,33 @@ __global__ void __launch_bounds__(M_THREADS) logits_mid_kernel(LogitsArgs a) {
     const int x = min(s, n_slabs - 1) + rot;
     return slab0 + (x >= n_slabs ? x - n_slabs : x);
   };
-  // weights: this lane's row, clamped onto the last one that exists; 16 bytes at (2 q + half) * 16 of a slab
+  // weights into registers: this lane's row, clamped onto the last one that exists; 16 bytes at (2 q + half) * 16 of a slab
   const int wrow = min(v0 + wave * 32 + (lane & 31), n_valid - 1);
   const unsigned char* wp = reinterpret_cast<const unsigned char*>(a.W) + (size_t)wrow * row_bytes + half * 16;
   auto load_w = [&](uint4 (&w)[4], int slab) {
     const unsigned char* p = wp + (size_t)slab_at(slab) * M_SLAB;
 #pragma unroll
     for (int q = 0; q < 4; ++q) w[q] = *reinterpret_cast<const uint4*>(p + q * 32);
+  };
+  // weights through the wave's own ring: its 32 rows in four requests of 8 whole lines, laid out as the hidden rows are
+  const unsigned char* Wt = reinterpret_cast<const unsigned char*>(a.W) + (size_t)v0 * row_bytes;
+  uint32_t wsrc[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int row = wave * 32 + i * 8 + (lane >> 3);
+    wsrc[i] = (uint32_t)(min(row, n_valid - 1 - v0) * (int)row_bytes + (((lane & 7) ^ ((row >> 1) & 7)) << 4));
+  }
+  const uint32_t ring0 = lds_offset_of(lds) + (uint32_t)(STAGES + wave * (RING * W_SLAB));
+  auto issue_w = [&](int slab, int slot) {
+    const unsigned char* p = Wt + (size_t)slab_at(slab) * M_SLAB;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t to = ring0 + (uint32_t)(slot * W_SLAB + i * 1024);
+      if (a.once)
+        load16_to_lds_once(p, wsrc[i], to);
+      else
+        load16_to_lds(p, wsrc[i], to);
+    }
   };
   // hidden rows: the 4 NJV groups of 8 rows of a slab are dealt to the waves, group g = i * 8 + wave for the
   // wave's i-th request; lane l moves, for row g * 8 + (l >> 3), the chunk that lands at position l & 7 of the row's
@@ -136,7 +163,7 @@ __global__ void __launch_bounds__(M_THREADS) logits_mid_kernel(LogitsArgs a) {
     const unsigned char* p = Ht + (size_t)slab_at(slab) * M_SLAB;
 #pragma unroll
     for (int i = 0; i < HL; ++i)
-      load16_to_lds(p, hsrc[i], lds_base + (uint32_t)(stage * M_STAGE + (i * M_WAVES + wave) * 1024));
+      load16_to_lds(p, hsrc[i], lds_base + (uint32_t)(stage * STAGE + (i * M_WAVES + wave) * 1024));
   };
   // operand reads: block j, row lane & 31, logical chunk 2 q + half
   const int sw = (lane >> 1) & 7;
@@ -148,27 +175,25 @@ __global__ void __launch_bounds__(M_THREADS) logits_mid_kernel(LogitsArgs a) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[0][j][v] = 0.f;
 
-  // SMODE 4, a decode step of up to 64 sequences: the logits are added up in three levels: two slabs (8 MFMAs) in the accumulators, two rounds of the
-  // buffers in registers, those in LDS (each thread its own words).  One accumulator over all of K rounds every step at the
+  // A decode step of up to 64 sequences: the logits are added up in three levels: two slabs (8 MFMAs) in the accumulators,
+  // sixteen slabs, all.  One accumulator over all of K rounds every step at the
   // size of the whole sum: d = 4096, relative error of the maxima 2.7e-7 to 3.3e-7; in two levels 5.7e-8 to 8.0e-8, in
   // three 4.4e-8 to 5.2e-8; the decode kernel's base units, which such a step ran on before and which add up 128 elements at a
-  // time, 4.5e-8 to 4.9e-8.  (It costs 8 us of 216 in a call with a few rows per sequence, which keep the one accumulator.)
-  constexpr bool LEVELS = SMODE == 4;
-  float* lds_total = reinterpret_cast<float*>(lds + M_LDS) + tid;      // [16 NJV][M_THREADS]
-  f32x16 total[NJV];
+  // time, 4.5e-8 to 4.9e-8.  (Calls with a few rows per sequence keep the one accumulator.)
+  constexpr bool LEVELS = SMODE >= 4;
+  f32x16 total[NJV], top[NJV];
+  if (LEVELS) {
 #pragma unroll
-  for (int j = 0; j < NJV; ++j)
+    for (int j = 0; j < NJV; ++j)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      total[j][v] = 0.f;
-      if (LEVELS) lds_total[(j * 16 + v) * M_THREADS] = 0.f;
-    }
+      for (int v = 0; v < 16; ++v) total[j][v] = top[j][v] = 0.f;
+  }
   auto third_level = [&]() {
 #pragma unroll
     for (int j = 0; j < NJV; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        lds_total[(j * 16 + v) * M_THREADS] += total[j][v];
+        top[j][v] += total[j][v];
         total[j][v] = 0.f;
       }
   };
@@ -183,7 +208,7 @@ __global__ void __launch_bounds__(M_THREADS) logits_mid_kernel(LogitsArgs a) {
   };
 
   auto compute = [&](const uint4 (&w)[4], int stage) {
-    const unsigned char* Bs = lds + stage * M_STAGE + offB;
+    const unsigned char* Bs = lds + stage * STAGE + offB;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int pos = ((2 * q + half) ^ sw) << 4;
@@ -196,66 +221,113 @@ __global__ void __launch_bounds__(M_THREADS) logits_mid_kernel(LogitsArgs a) {
     }
   };
 
-  // One step = one slab.  On entry to step s: stage s % 3 holds the hidden rows of slab s, visible to all; those of
-  // slab s + 1 are on their way into stage (s + 1) % 3; buffer s % NBUF holds the weights of slab s, the weights of
-  // the next slabs are on their way.  Loads complete in the order of their requests.  Requested during step s, in
-  // this order: the hidden rows of slab s + 2 (HL requests; the stage's last readers, those of slab s - 1, passed
-  // the barrier of step s - 1), then weights: of slab s + NBUF - 1 (4 requests), or with M_PAIR of the slabs
-  // s + NBUF - 2 and s + NBUF - 1 before every other step (8 requests).  Before the barrier of step s the hidden
-  // rows of slab s + 1 must have landed: after them came the weight requests of step s - 1 and the HL + weight
-  // requests of step s, HL + 8 in all either way, which may stay in flight.
-  int stage = 0;                                           // s % 3
-  uint4 w[NBUF][4];
-  static_assert(!M_PAIR || NBUF % 2 == 0, "pairs of slabs");
-  auto requests = [&](int u, int s) {                      // u = s % NBUF, a constant where this is expanded
-    issue_h(s + 2, stage == 0 ? 2 : stage - 1);            // stage (s + 2) % 3
-    if (M_PAIR) {
-      if ((u & 1) == 0) {                                  // the two buffers used last
-        load_w(w[(u + NBUF - 2) % NBUF], s + NBUF - 2);
-        load_w(w[(u + NBUF - 1) % NBUF], s + NBUF - 1);
-      }
-    } else {
-      load_w(w[(u + NBUF - 1) % NBUF], s + NBUF - 1);
-    }
-  };
-  // (in_loop: the count above holds inside the loop, where every weight request feeds a later iteration.  In the
-  // steps after the loop the compiler drops the requests whose buffers no step reads any more, so there
-  // everything in flight is awaited: a handful of steps per tile.)
-  auto finish = [&](int u, bool in_loop) {
-    compute(w[u], stage);
-    if (LEVELS && (u & 1)) next_level();
-    if (in_loop)
-      wait_loads<HL + 8>();
+  if constexpr (RING > 0) {
+    // One step = one slab: on entry to step s the hidden rows of slab s are in stage s % 3 for all, and its weights in the
+    // wave's ring slot s % RING.  Requested during the step: the hidden rows of slab s + 2 (HL requests), then the weights of
+    // slab s + RING - 1 (4), into the slot that step s - 1 has read.  At its end slab s + 1 must have landed: behind the later
+    // of its two come HL + 4 (RING - 2) requests.  The last steps request nothing that does not exist, and wait for all.
+    int stage = 0, slot = 0;
+    auto step_compute = [&]() {
+      const unsigned char* As = lds + STAGES + wave * (RING * W_SLAB) + slot * W_SLAB + offB;
+      uint4 w[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) w[q] = *reinterpret_cast<const uint4*>(As + (((2 * q + half) ^ sw) << 4));
+      compute(w, stage);
+    };
+    auto next_step = [&]() {
+      __syncthreads();
+      stage = stage == 2 ? 0 : stage + 1;
+      slot = slot == RING - 1 ? 0 : slot + 1;
+    };
+    issue_h(0, 0);
+    issue_w(0, 0);
+    if (n_slabs > 1) issue_h(1, 1);
+#pragma unroll
+    for (int u = 1; u < RING - 1; ++u)
+      if (u < n_slabs) issue_w(u, u);
+    if (n_slabs >= RING - 1)
+      wait_loads<HL + 4 * (RING - 2)>();
     else
       wait_loads<0>();
     __syncthreads();
-    stage = stage == 2 ? 0 : stage + 1;
-  };
+    int s = 0;
+    for (; s + RING - 1 < n_slabs; ++s) {
+      issue_h(s + 2, stage == 0 ? 2 : stage - 1);
+      issue_w(s + RING - 1, slot == 0 ? RING - 1 : slot - 1);
+      step_compute();
+      if (LEVELS && (s & 1)) next_level();
+      if (LEVELS && (s & 15) == 15) third_level();
+      wait_loads<HL + 4 * (RING - 2)>();
+      next_step();
+    }
+    for (; s < n_slabs; ++s) {
+      if (s + 2 < n_slabs) issue_h(s + 2, stage == 0 ? 2 : stage - 1);
+      step_compute();
+      if (LEVELS && (s & 1)) next_level();
+      if (LEVELS && (s & 15) == 15) third_level();
+      wait_loads<0>();
+      next_step();
+    }
+  } else {
+    // One step = one slab.  On entry to step s: stage s % 3 holds the hidden rows of slab s, visible to all; those of
+    // slab s + 1 are on their way into stage (s + 1) % 3; buffer s % NBUF holds the weights of slab s, the weights of
+    // the next slabs are on their way.  Loads complete in the order of their requests.  Requested during step s, in
+    // this order: the hidden rows of slab s + 2 (HL requests; the stage's last readers, those of slab s - 1, passed
+    // the barrier of step s - 1), then weights: of slab s + NBUF - 1 (4 requests), or with M_PAIR of the slabs
+    // s + NBUF - 2 and s + NBUF - 1 before every other step (8 requests).  Before the barrier of step s the hidden
+    // rows of slab s + 1 must have landed: after them came the weight requests of step s - 1 and the HL + weight
+    // requests of step s, HL + 8 in all either way, which may stay in flight.
+    int stage = 0;                                           // s % 3
+    uint4 w[NBUF][4];
+    static_assert(!M_PAIR || NBUF % 2 == 0, "pairs of slabs");
+    auto requests = [&](int u, int s) {                      // u = s % NBUF, a constant where this is expanded
+      issue_h(s + 2, stage == 0 ? 2 : stage - 1);            // stage (s + 2) % 3
+      if (M_PAIR) {
+        if ((u & 1) == 0) {                                  // the two buffers used last
+          load_w(w[(u + NBUF - 2) % NBUF], s + NBUF - 2);
+          load_w(w[(u + NBUF - 1) % NBUF], s + NBUF - 1);
+        }
+      } else {
+        load_w(w[(u + NBUF - 1) % NBUF], s + NBUF - 1);
+      }
+    };
+    // (in_loop: the count above holds inside the loop, where every weight request feeds a later iteration.  In the
+    // steps after the loop the compiler drops the requests whose buffers no step reads any more, so there
+    // everything in flight is awaited: a handful of steps per tile.)
+    auto finish = [&](int u, bool in_loop) {
+      compute(w[u], stage);
+      if (in_loop)
+        wait_loads<HL + 8>();
+      else
+        wait_loads<0>();
+      __syncthreads();
+      stage = stage == 2 ? 0 : stage + 1;
+    };
 
-  issue_h(0, 0);
-  issue_h(1, 1);
-  constexpr int PRE = M_PAIR ? NBUF - 2 : NBUF - 1;        // slabs whose weights are requested ahead of the loop
+    issue_h(0, 0);
+    issue_h(1, 1);
+    constexpr int PRE = M_PAIR ? NBUF - 2 : NBUF - 1;        // slabs whose weights are requested ahead of the loop
 #pragma unroll
-  for (int u = 0; u < PRE; ++u) load_w(w[u], u);
-  wait_loads<HL + 4 * PRE>();                              // slab 0's hidden rows; what followed may be in flight
-  __syncthreads();
-  // whole rounds of the buffers without a test inside (a loop the register allocator keeps the buffers fixed in),
-  // then the rest
-  int s0 = 0;
-  for (; s0 + NBUF <= n_slabs; s0 += NBUF) {
+    for (int u = 0; u < PRE; ++u) load_w(w[u], u);
+    wait_loads<HL + 4 * PRE>();                              // slab 0's hidden rows; what followed may be in flight
+    __syncthreads();
+    // whole rounds of the buffers without a test inside (a loop the register allocator keeps the buffers fixed in),
+    // then the rest
+    int s0 = 0;
+    for (; s0 + NBUF <= n_slabs; s0 += NBUF) {
 #pragma unroll
-    for (int u = 0; u < NBUF; ++u) {
-      requests(u, s0 + u);
-      finish(u, true);
+      for (int u = 0; u < NBUF; ++u) {
+        requests(u, s0 + u);
+        finish(u, true);
+      }
     }
-    if (LEVELS && ((s0 / NBUF) & 1)) third_level();
+#pragma unroll
+    for (int u = 0; u < NBUF - 1; ++u)
+      if (s0 + u < n_slabs) {                                // (uniform)
+        requests(u, s0 + u);
+        finish(u, false);
+      }
   }
-#pragma unroll
-  for (int u = 0; u < NBUF - 1; ++u)
-    if (s0 + u < n_slabs) {                                // (uniform)
-      requests(u, s0 + u);
-      finish(u, false);
-    }
   // the requests past the end of the stream (slabs clamped onto the last one) must land before the stages are reused
   wait_loads<0>();
   __syncthreads();
@@ -264,9 +336,7 @@ __global__ void __launch_bounds__(M_THREADS) logits_mid_kernel(LogitsArgs a) {
     next_level();
     third_level();
 #pragma unroll
-    for (int j = 0; j < NJV; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[0][j][v] = lds_total[(j * 16 + v) * M_THREADS];
+    for (int j = 0; j < NJV; ++j) acc[0][j] = top[j];
   }
 
   // ---- fold the tile, then one triple (and draw) per hidden row --------------------------------------------
@@ -283,9 +353,9 @@ __global__ void __launch_bounds__(M_THREADS) logits_mid_kernel(LogitsArgs a) {
     store_partial_tile<1, NJV>(acc, a.partial + (size_t)ks * a.rows * a.ldo, a.ldo, r0, r_end, col_base, n_valid);
     return;
   }
-  if (SMODE == 1)
+  if (SMODE == 1 || SMODE == 5)
     fold_tile_sample<1, NJV>(acc, run, draw, a, r0, col_base, n_valid);
-  else if (SMODE == 2)
+  else if (SMODE == 2 || SMODE == 6)
     fold_tile_store<1, NJV>(acc, run, a, r0, r_end, col_base, n_valid);
   else
     fold_tile<1, NJV>(acc, run, col_base, a.col0, n_valid, v0 + M_WT > n_valid);
@@ -296,7 +366,7 @@ __global__ void __launch_bounds__(M_THREADS) logits_mid_kernel(LogitsArgs a) {
     o.s = __shfl_xor(run[j].s, 32);
     o.i = __shfl_xor(run[j].i, 32);
     merge_triple(run[j], o);
-    if (SMODE == 1) {
+    if (SMODE == 1 || SMODE == 5) {
       Draw od;
       od.v = __shfl_xor(draw[j].v, 32);
       od.l = __shfl_xor(draw[j].l, 32);
@@ -310,7 +380,7 @@ __global__ void __launch_bounds__(M_THREADS) logits_mid_kernel(LogitsArgs a) {
 #pragma unroll
     for (int j = 0; j < NJV; ++j) {
       xch[wave * M_HT + j * 32 + lane] = run[j];
-      if (SMODE == 1) xdr[wave * M_HT + j * 32 + lane] = draw[j];
+      if (SMODE == 1 || SMODE == 5) xdr[wave * M_HT + j * 32 + lane] = draw[j];
     }
   }
   __syncthreads();
@@ -321,7 +391,7 @@ __global__ void __launch_bounds__(M_THREADS) logits_mid_kernel(LogitsArgs a) {
     const size_t p = (size_t)(r0 + tid) * a.n_parts + a.part0 + vt;
     a.part_m[p] = t.m;
     a.part_s[p] = t.s;
-    if (SMODE == 1) {
+    if (SMODE == 1 || SMODE == 5) {
       Draw dw = xdr[tid];
 #pragma unroll
       for (int w = 1; w < M_WAVES; ++w) merge_draw(dw, xdr[w * M_HT + tid]);
@@ -331,6 +401,26 @@ __global__ void __launch_bounds__(M_THREADS) logits_mid_kernel(LogitsArgs a) {
     } else {
       a.part_i[p] = t.i;
     }
+  }
+}
+
+// Ring slots per build: what fits beside three stages of hidden rows (0: weights in registers).
+constexpr int mid_ring(int njv) { return njv == 2 ? 4 : (njv == 4 ? 3 : 0); }
+constexpr int mid_lds(int njv) { return M_NSTAGE * 32 * njv * M_SLAB + M_WAVES * 32 * M_SLAB * mid_ring(njv); }
+constexpr int M_LDS_MAX = mid_lds(2) > mid_lds(4) ? mid_lds(2) : mid_lds(4);
+static_assert(M_LDS_MAX <= 160 * 1024 && mid_lds(2) >= M_LDS && mid_lds(4) >= M_LDS && mid_lds(6) == M_LDS, "");
+
+template <int NJV, int SMODE>
+__global__ void __launch_bounds__(M_THREADS) logits_mid_kernel(LogitsArgs a) {
+  extern __shared__ __align__(1024) unsigned char lds[];
+  if constexpr (SMODE == 3 && NJV == 4) {
+    // (the rows that exist may be half of those laid out: known here only)
+    if ((a.rows_dev ? min(a.rows, *a.rows_dev) : a.rows) <= 64)
+      mid_tile<2, mid_ring(2), SMODE>(a, lds);
+    else
+      mid_tile<4, mid_ring(4), SMODE>(a, lds);
+  } else {
+    mid_tile<NJV, mid_ring(NJV), SMODE>(a, lds);
   }
 }
 
@@ -349,6 +439,7 @@ int z2z_launch_logits_mid(z2z_ctx* c, LogitsArgs a, const void* W, int w_rows, i
   a.w_rows = w_rows;
   a.col0 = col0;
   a.n_vtiles = (w_rows + M_WT - 1) / M_WT;
+  a.once = (size_t)w_rows * a.d * sizeof(uint16_t) > kKeepBytes;
   c->n_launch[Z2Z_KERNEL_MID]++;
   // (two workgroups of the 64-row build per weight tile for 65..128 rows, sharing the tile's weights through an
   // XCD's L2, measured slower than one of the 128-row build: 383 against 293 us at config 2's shape)
@@ -358,24 +449,28 @@ int z2z_launch_logits_mid(z2z_ctx* c, LogitsArgs a, const void* W, int w_rows, i
   // tile kernel: 650 against 645 us for a decode step of 256 sequences.)
   const int blocks = a.rows <= 64 ? 2 : (a.rows <= 128 ? 4 : 6);
   if (a.sample == 1) {
-    if (blocks <= 4)
-      hipLaunchKernelGGL((logits_mid_kernel<4, M_NBUF, 1>), grid, block, M_LDS, s, a);
+    if (blocks == 2)
+      hipLaunchKernelGGL((logits_mid_kernel<2, 5>), grid, block, mid_lds(2), s, a);
+    else if (blocks == 4)
+      hipLaunchKernelGGL((logits_mid_kernel<4, 1>), grid, block, mid_lds(4), s, a);
     else
-      hipLaunchKernelGGL((logits_mid_kernel<6, M_NBUF_6, 1>), grid, block, M_LDS, s, a);
+      hipLaunchKernelGGL((logits_mid_kernel<6, 1>), grid, block, mid_lds(6), s, a);
   } else if (a.sample == 2) {
-    if (blocks <= 4)
-      hipLaunchKernelGGL((logits_mid_kernel<4, M_NBUF, 2>), grid, block, M_LDS, s, a);
+    if (blocks == 2)
+      hipLaunchKernelGGL((logits_mid_kernel<2, 6>), grid, block, mid_lds(2), s, a);
+    else if (blocks == 4)
+      hipLaunchKernelGGL((logits_mid_kernel<4, 2>), grid, block, mid_lds(4), s, a);
     else
-      hipLaunchKernelGGL((logits_mid_kernel<6, M_NBUF_6, 2>), grid, block, M_LDS, s, a);
+      hipLaunchKernelGGL((logits_mid_kernel<6, 2>), grid, block, mid_lds(6), s, a);
   } else {
     if (blocks == 2 && a.rows_per_seq == 1)
-      hipLaunchKernelGGL((logits_mid_kernel<2, M_NBUF, 4>), grid, block, M_LDS_LEVELS, s, a);
+      hipLaunchKernelGGL((logits_mid_kernel<2, 4>), grid, block, mid_lds(2), s, a);
     else if (blocks == 2)
-      hipLaunchKernelGGL((logits_mid_kernel<2, M_NBUF, 0>), grid, block, M_LDS, s, a);
+      hipLaunchKernelGGL((logits_mid_kernel<2, 0>), grid, block, mid_lds(2), s, a);
     else if (blocks == 4)
-      hipLaunchKernelGGL((logits_mid_kernel<4, M_NBUF, 0>), grid, block, M_LDS, s, a);
+      hipLaunchKernelGGL((logits_mid_kernel<4, 0>), grid, block, mid_lds(4), s, a);
     else
-      hipLaunchKernelGGL((logits_mid_kernel<6, M_NBUF_6, 0>), grid, block, M_LDS, s, a);
+      hipLaunchKernelGGL((logits_mid_kernel<6, 0>), grid, block, mid_lds(6), s, a);
   }
   Z2Z_HIP_TRY(hipGetLastError());
   return Z2Z_OK;
@@ -404,7 +499,7 @@ int z2z_linear_mid_ksplit(int N, int K) {
 // leaves ksplit fp32 partial tiles per weight tile in `partial` ([ksplit][R][N]); the caller sums them
 // (linear_sum_kernel in dense.hip).  Returns the ksplit chosen through *ksplit_out.
 int z2z_launch_linear_mid(z2z_ctx* c, const void* A, const void* W, int R, const int32_t* rows_dev, int N, int K,
-                          float* partial, size_t partial_floats, int* ksplit_out, hipStream_t s) {
+                          bool once, float* partial, size_t partial_floats, int* ksplit_out, hipStream_t s) {
   if (!z2z_logits_mid_ok(c, R) || R > 128 || K % 64 != 0 || N < 1) return Z2Z_EUNSUPPORTED;
   const int n_vt = (N + M_WT - 1) / M_WT, n_slabs = K / 64;
   const int ksplit = z2z_linear_mid_ksplit(N, K);
@@ -423,13 +518,14 @@ int z2z_launch_linear_mid(z2z_ctx* c, const void* A, const void* W, int R, const
   a.ksplit = ksplit;
   a.slabs_per_part = per;
   a.partial = partial;
+  a.once = once ? 1 : 0;
   *ksplit_out = ksplit;
   c->n_launch[Z2Z_KERNEL_MID]++;
   const dim3 grid((unsigned)n_vt, (unsigned)ksplit), block(M_THREADS);
   if (R <= 64)
-    hipLaunchKernelGGL((logits_mid_kernel<2, M_NBUF, 3>), grid, block, M_LDS, s, a);
+    hipLaunchKernelGGL((logits_mid_kernel<2, 3>), grid, block, mid_lds(2), s, a);
   else
-    hipLaunchKernelGGL((logits_mid_kernel<4, M_NBUF, 3>), grid, block, M_LDS, s, a);
+    hipLaunchKernelGGL((logits_mid_kernel<4, 3>), grid, block, M_LDS_MAX, s, a);
   Z2Z_HIP_TRY(hipGetLastError());
   return Z2Z_OK;
 }
@@ -437,18 +533,20 @@ int z2z_launch_linear_mid(z2z_ctx* c, const void* A, const void* W, int R, const
 int z2z_logits_mid_tiles(int w_rows) { return (w_rows + M_WT - 1) / M_WT; }
 
 int z2z_logits_mid_prepare(z2z_ctx* c) {
-  if (c->lds_limit < M_LDS_LEVELS) return Z2Z_EUNSUPPORTED;
-  const void* kernels[10] = {reinterpret_cast<const void*>(logits_mid_kernel<2, M_NBUF, 4>),
-                            reinterpret_cast<const void*>(logits_mid_kernel<2, M_NBUF, 3>),
-                            reinterpret_cast<const void*>(logits_mid_kernel<4, M_NBUF, 3>),
-                            reinterpret_cast<const void*>(logits_mid_kernel<2, M_NBUF, 0>),
-                            reinterpret_cast<const void*>(logits_mid_kernel<4, M_NBUF, 0>),
-                            reinterpret_cast<const void*>(logits_mid_kernel<4, M_NBUF, 1>),
-                            reinterpret_cast<const void*>(logits_mid_kernel<4, M_NBUF, 2>),
-                            reinterpret_cast<const void*>(logits_mid_kernel<6, M_NBUF_6, 0>),
-                            reinterpret_cast<const void*>(logits_mid_kernel<6, M_NBUF_6, 1>),
-                            reinterpret_cast<const void*>(logits_mid_kernel<6, M_NBUF_6, 2>)};
-  for (int k = 0; k < 10; ++k)
-    Z2Z_HIP_TRY(hipFuncSetAttribute(kernels[k], hipFuncAttributeMaxDynamicSharedMemorySize, M_LDS_LEVELS));
+  if (c->lds_limit < M_LDS_MAX) return Z2Z_EUNSUPPORTED;
+  const void* kernels[12] = {reinterpret_cast<const void*>(logits_mid_kernel<2, 6>),
+                            reinterpret_cast<const void*>(logits_mid_kernel<2, 5>),
+                            reinterpret_cast<const void*>(logits_mid_kernel<2, 4>),
+                            reinterpret_cast<const void*>(logits_mid_kernel<2, 3>),
+                            reinterpret_cast<const void*>(logits_mid_kernel<4, 3>),
+                            reinterpret_cast<const void*>(logits_mid_kernel<2, 0>),
+                            reinterpret_cast<const void*>(logits_mid_kernel<4, 0>),
+                            reinterpret_cast<const void*>(logits_mid_kernel<4, 1>),
+                            reinterpret_cast<const void*>(logits_mid_kernel<4, 2>),
+                            reinterpret_cast<const void*>(logits_mid_kernel<6, 0>),
+                            reinterpret_cast<const void*>(logits_mid_kernel<6, 1>),
+                            reinterpret_cast<const void*>(logits_mid_kernel<6, 2>)};
+  for (int k = 0; k < 12; ++k)
+    Z2Z_HIP_TRY(hipFuncSetAttribute(kernels[k], hipFuncAttributeMaxDynamicSharedMemorySize, M_LDS_MAX));
   return Z2Z_OK;
 }

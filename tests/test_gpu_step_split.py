@@ -67,6 +67,46 @@ def test_split_step(B, V, d, cap, split):
     ctx.close()
 
 
+@pytest.mark.parametrize("B,V,d,cap,top_k,top_p", [
+    (5, 65281, 128, 40, 0, 1.0),        # two slabs, fewer than the ring's slots; a last tile of one column
+    (33, 65500, 1664, 100, 0, 1.0),     # weights past the caches; a second block of rows with one row
+    (64, 65500, 384, 520, 0, 1.0),      # six slabs: half of the steps behind the loop
+    (9, 65290, 768, 700, 50, 0.9),
+    (32, 65281, 1152, 40, 50, 0.9),     # (one block of rows: the second is left out)
+    (64, 65500, 256, 100, 0, 0.8),
+])
+def test_split_draws_match_one_launch(B, V, d, cap, top_k, top_p):
+    """Draws of a split step against those of the decode kernel in one launch (both oracle-tested on smaller vocabularies):
+    the same numbers perturb logits that differ by fp32 rounding, at most 1e-5 of a size below 10: picks agree unless two
+    perturbed values are that close, and log-probabilities to 1e-4."""
+    import torch
+
+    from paper_2506_01084_amd import api
+
+    print(f"[case] draws of {B} sequences, V={V} d={d} cap={cap} top_k={top_k} top_p={top_p}", flush=True)
+    ctx = api.Context(B=B, V=V, M=3, cap=cap, d=d, dtype="bf16", pool="mean")
+    gen = torch.Generator(device="cuda").manual_seed(V + B)
+    tokens = torch.randint(0, V, (B, 300), generator=gen, device="cuda").to(torch.int32)
+    codes, n, st = torch.empty_like(tokens), *(torch.empty(B, dtype=torch.int32, device="cuda") for _ in range(2))
+    ctx.lzw_encode(tokens, None, codes, n, st, api.RESET)
+    E = (torch.randn((V, d), generator=gen, device="cuda") * d ** -0.5).bfloat16()
+    W = (torch.randn((B, cap, d), generator=gen, device="cuda") * d ** -0.5).bfloat16()
+    H = torch.randn((B, d), generator=gen, device="cuda").bfloat16()
+    got = {}
+    for kernel in (0, 4):               # automatic; not the streaming kernel
+        ctx.set_option(api.OPT_LOGITS_KERNEL, kernel)
+        token, lp = torch.full((B,), -5, dtype=torch.int32, device="cuda"), torch.full((B,), 777.0, device="cuda")
+        before = ctx.read_launches()["mid"]
+        ctx.extended_sample(H, 1, E, W, 0.8, 77, 5, token, lp, top_k=top_k, top_p=top_p)
+        torch.cuda.synchronize()
+        assert ctx.read_launches()["mid"] - before == (1 if kernel == 0 else 0)
+        got[kernel] = token, lp
+    same = got[0][0] == got[4][0]
+    assert int((~same).sum()) <= 1
+    assert torch.allclose(got[0][1][same], got[4][1][same], atol=1e-4, rtol=0)
+    ctx.close()
+
+
 def test_greedy_step_is_captured_behind_an_eager_draw():
     """(the draw's kernels leave fewer parts per row; every kind of step sizes the scratch for all of them)"""
     import torch
