@@ -276,13 +276,13 @@ bool static_parts(const z2z_ctx* c, z2z_parts* out) {
 }  // namespace
 
 // The shape-dependent fields of one part's arguments (tiles of `tile` rows, strips); B: sequences of a hyper part.
-static void fill_part(LogitsArgs& a, const int32_t* size, int tile, int B, const void* W, int w_rows, int col0, int part0,
+static void fill_part(LogitsArgs& a, const int32_t* size, int tile, int tile_v, int B, const void* W, int w_rows, int col0, int part0,
                       int strip, int rows, int rows_per_seq) {
   a.W = W;
   a.size = size;
   a.w_rows = w_rows;
   a.col0 = col0;
-  a.n_vtiles = (w_rows + tile - 1) / tile;
+  a.n_vtiles = (w_rows + tile_v - 1) / tile_v;
   a.strip = strip;
   a.n_strips = (a.n_vtiles + strip - 1) / strip;
   a.part0 = part0;
@@ -298,7 +298,7 @@ int z2z_launch_logits_part(z2z_ctx* c, bool hyper, LogitsArgs a, const void* W, 
                            hipStream_t s, bool prob, int seq0, int n_seq) {
   // (seq0, n_seq: the hyper part of a sub-range of the sequences -- the caller passes that range's rows and
   // its W_hyper; n_seq = 0 means all of them)
-  fill_part(a, hyper ? c->st.size + seq0 : nullptr, 256, n_seq > 0 ? n_seq : c->cfg.B, W, w_rows, col0, part0, strip, rows,
+  fill_part(a, hyper ? c->st.size + seq0 : nullptr, 256, 256, n_seq > 0 ? n_seq : c->cfg.B, W, w_rows, col0, part0, strip, rows,
             rows_per_seq);
   *n_strips_out = a.n_strips;
   unsigned grid = (unsigned)a.n_work;
@@ -318,8 +318,8 @@ int z2z_launch_logits_part(z2z_ctx* c, bool hyper, LogitsArgs a, const void* W, 
 
 // A workgroup sweeps a strip of 4 weight tiles with its rows' tile resident; with few row tiles that leaves CUs
 // idle, so the strips shorten until there are `want` workgroups (or one tile per workgroup): two per CU for the
-// bf16 tile kernel, four for the general kernel, of which two run on a CU at a time (fp32, 600 rows x 32000
-// columns, d = 256: 124 us with two, 115 with four; 1024 rows: 184 and 182).
+// bf16 tile kernel, four for the general kernel (tiles of 64 columns), of which three run on a CU at a time (fp32, d = 256,
+// 32000 columns, strips of 1 / 2 / 4 tiles: 1024 rows 159 / 156 / 179 us, 2048 rows 299 / 291 / 314).
 static int pick_strip_for(const z2z_ctx* c, long long row_tiles, int n_vt, int want = 512) {
   if (c->opt_logits_strip > 0) return c->opt_logits_strip;
   int st = 4;
@@ -403,16 +403,30 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
   const bool fast = fast_ok && c->opt_logits_kernel != 1;
 
   // number of parts (strips of both launches), then the scratch for them
-  const int tile = fast ? 256 : 128;
-  const int base_vt = (V + tile - 1) / tile, hyp_vt = (cap + tile - 1) / tile;
-  auto pick_strip = [&](long long row_tiles, int n_vt) { return pick_strip_for(c, row_tiles, n_vt, fast ? 512 : 1024); };
+  const int tile = fast ? 256 : 128, tile_v = fast ? 256 : 64;
+  const int base_vt = (V + tile_v - 1) / tile_v, hyp_vt = (cap + tile_v - 1) / tile_v;
   // few hidden rows in all (several per sequence, or 65..192 sequences): the base part is bound by the bytes of
   // W_base and goes to the kernel that streams the weights past all rows at once, one part per 256 weight rows
   // (measured against the decode kernel's base units in a launch of their own at up to 64 rows: 260 against 305 us
   // for the call at config 2's shape; two or three passes of those units for more rows cost more still)
   const bool mid_base = fast && c->opt_logits_kernel == 0 && z2z_logits_mid_ok(c, rows);
-  const int strip_b = mid_base ? 1 : pick_strip((rows + tile - 1) / tile, base_vt);
-  const int strip_h = pick_strip((long long)c->cfg.B * ((rows_per_seq + tile - 1) / tile), hyp_vt);
+  const long long tiles_b = (rows + tile - 1) / tile, tiles_h = (long long)c->cfg.B * ((rows_per_seq + tile - 1) / tile);
+  int strip_b = 1, strip_h = 1;
+  if (fast) {
+    if (!mid_base) strip_b = pick_strip_for(c, tiles_b, base_vt);
+    strip_h = pick_strip_for(c, tiles_h, hyp_vt);
+  } else {
+    // (strips asked for, and those where the static array could not hold the parts of shorter ones, count in 128 columns;
+    // the other entry point cuts the same way)
+    const bool pairs = c->opt_logits_strip > 0;
+    const int vt2_b = (base_vt + 1) / 2, vt2_h = (hyp_vt + 1) / 2;
+    strip_b = pairs ? 2 * c->opt_logits_strip : pick_strip_for(c, tiles_b, base_vt, 1024);
+    strip_h = pairs ? 2 * c->opt_logits_strip : pick_strip_for(c, tiles_h, hyp_vt, 1024);
+    if (!pairs && (size_t)((base_vt + strip_b - 1) / strip_b + (hyp_vt + strip_h - 1) / strip_h) * rows > Z2Z_STATIC_PARTS) {
+      strip_b = 2 * pick_strip_for(c, tiles_b, vt2_b, 1024);
+      strip_h = 2 * pick_strip_for(c, tiles_h, vt2_h, 1024);
+    }
+  }
   const int base_strips = (base_vt + strip_b - 1) / strip_b;
   int hyp_strips = cap > 0 ? (hyp_vt + strip_h - 1) / strip_h : 0;
   int seq_unit = 0;
@@ -446,8 +460,8 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
   if (!fast) {
     // both parts in one launch of the general kernel
     LogitsArgs h = a;
-    fill_part(a, nullptr, tile, 1, W_base, V, 0, 0, strip_b, rows, rows_per_seq);
-    if (cap > 0) fill_part(h, c->st.size, tile, c->cfg.B, W_hyper, cap, V, base_strips, strip_h, rows, rows_per_seq);
+    fill_part(a, nullptr, tile, tile_v, 1, W_base, V, 0, 0, strip_b, rows, rows_per_seq);
+    if (cap > 0) fill_part(h, c->st.size, tile, tile_v, c->cfg.B, W_hyper, cap, V, base_strips, strip_h, rows, rows_per_seq);
     c->n_launch[Z2Z_KERNEL_GENERAL]++;
     if (timed) Z2Z_HIP_TRY(hipEventRecord(c->ev_start[c->n_timed], s));
     rc = z2z_launch_logits_general(c->cfg.dtype == Z2Z_BF16, a, cap > 0 ? &h : nullptr, s);

@@ -7,15 +7,16 @@
 // per strip.  A workgroup owns one tile of hidden rows and sweeps a strip of vocabulary tiles.
 // This is the fp32 path, and the fallback for shapes the fast bf16 kernel does not take.
 //
-// fp32 is bound by the matrix cores (v_mfma_f32_32x32x2_f32: 256 flop per CU and clock, 157 TFLOP/s): a wave issues
-// 64 of them (4096 cycles) per slab, so two waves per SIMD -- two workgroups per CU -- cover the loads, the barriers
-// and each other's folds, provided nothing of the K loop spills.  The instance that stores the logits is a kernel of
-// its own for that reason (its store addresses and column tests cost the plain one 200 registers, scratch traffic
-// in the loop and the second workgroup), and operand rows are 32-bit offsets from one base address per tile.
+// fp32 is bound by the matrix cores (v_mfma_f32_32x32x2_f32: 256 flop per CU and clock, 157 TFLOP/s).  A workgroup's loads,
+// barriers and folds are covered by the others on its CU, so its tile is as small as keeps three of them there (48 KiB of LDS,
+// at most 168 registers): 64 columns x 128 rows, whose LDS reads still take a fifth of the matrix instructions' time.  Smaller
+// tiles also fill the last round of a CU better.  With 128 x 128, two per CU, two waves per SIMD kept the matrix cores 62 % busy.
+// The instance that stores the logits is a kernel of its own (its store addresses and column tests cost the plain one
+// registers), and operand rows are 32-bit offsets from one base address per tile.
 // Both parts share a launch, the hyper part's few tiles first; an XCD walks consecutive row tiles of consecutive
 // strips, so its L2 reads a weight strip once for all of them.
-// Measured, fp32, 1024 rows x 32000 columns and two codebooks, d = 256 (17.6 GFLOP): 421 us in two launches ->
-// 182 us (97 TFLOP/s); 2048 rows: 319 us (111 TFLOP/s).
+// Whole calls, fp32, 32000 columns and two codebooks, d = 256, 128 x 128 -> 64 x 128: 512 rows 106 -> 100 us, 1024 rows
+// 170 -> 156 (17.6 GFLOP), 2048 rows 306 -> 291, 4096 rows 578 -> 563 (119 TFLOP/s).
 #include "logits_common.h"
 
 namespace {
@@ -23,15 +24,17 @@ namespace {
 using namespace z2z_logits;
 
 // ------------------------------------------------------------------------------------------------
-// Tile kernel, 128 (vocabulary) x 128 (hidden rows) per workgroup, 4 waves of 64 x 64, K slabs of
-// 128 bytes per row.  LDS holds two buffers of (128 + 128) rows x 128 B; the 16-byte chunk c of row
+// Tile kernel, 64 (vocabulary) x 128 (hidden rows) per workgroup, 4 waves of 32 x 64, K slabs of
+// 128 bytes per row.  LDS holds two buffers of (64 + 128) rows x 128 B; the 16-byte chunk c of row
 // r sits at chunk (c ^ ((r >> 1) & 7)) so that the 16 rows a quarter-wave reads hit all 64 banks.
 // T = bf16 bits (uint16_t) or float.
 // ------------------------------------------------------------------------------------------------
-constexpr int TV = 128;
+constexpr int TV = 64;
 constexpr int TR = 128;
 constexpr int SLAB_BYTES = 128;
-constexpr int TILE_BYTES = TV * SLAB_BYTES;   // one operand tile in LDS (16 KiB)
+constexpr int A_BYTES = TV * SLAB_BYTES;      // the weight tile of one slab in LDS (8 KiB)
+constexpr int B_BYTES = TR * SLAB_BYTES;      // the hidden rows (16 KiB)
+constexpr int NI = TV / 64, NA = TV / 32;     // MFMA blocks of a wave along the vocabulary; rows a thread stages
 constexpr int ROW_BLOCK = 8;                  // row tiles that an XCD walks together per strip
 
 struct GeneralArgs {
@@ -39,14 +42,14 @@ struct GeneralArgs {
   int32_t hyper_grid;   // workgroups of the hyper part (the first ones), a multiple of 8
 };
 
-// The wave's four 32 x 32 blocks advance by one 16-byte chunk of K per lane.
+// The wave's two 32 x 32 blocks advance by one 16-byte chunk of K per lane.
 template <typename T>
-__device__ __forceinline__ void mfma_block(const f32x4 (&fa)[2], const f32x4 (&fb)[2], f32x16 (&acc)[2][2]);
+__device__ __forceinline__ void mfma_block(const f32x4 (&fa)[NI], const f32x4 (&fb)[2], f32x16 (&acc)[NI][2]);
 
 template <>
-__device__ __forceinline__ void mfma_block<uint16_t>(const f32x4 (&fa)[2], const f32x4 (&fb)[2], f32x16 (&acc)[2][2]) {
+__device__ __forceinline__ void mfma_block<uint16_t>(const f32x4 (&fa)[NI], const f32x4 (&fb)[2], f32x16 (&acc)[NI][2]) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < NI; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
       acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[i]), __builtin_bit_cast(bf16x8, fb[j]),
@@ -54,29 +57,36 @@ __device__ __forceinline__ void mfma_block<uint16_t>(const f32x4 (&fa)[2], const
 }
 
 template <>
-__device__ __forceinline__ void mfma_block<float>(const f32x4 (&fa)[2], const f32x4 (&fb)[2], f32x16 (&acc)[2][2]) {
+__device__ __forceinline__ void mfma_block<float>(const f32x4 (&fa)[NI], const f32x4 (&fb)[2], f32x16 (&acc)[NI][2]) {
   // a 16-byte chunk holds 4 consecutive k; lanes 0-31 and 32-63 hold different chunks, and the
   // pairing of k between the two operands is the same, so any order of the 4 steps is a valid sum
 #pragma unroll
   for (int e = 0; e < 4; ++e)
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][e], fb[j][e],
                                                          acc[i][j], 0, 0, 0);
 }
 
-// Fold the wave's 64 x 64 logits into the running triples (and store them).  TAIL: the tile has columns that do not exist.
+// Waves of the workgroup meet.  (Not __syncthreads, which would wait for the next slab's loads as well.)
+__device__ __forceinline__ void meet() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// Fold the wave's 32 x 64 logits into the running triples (and store them).  TAIL: the tile has columns that do not exist.
 template <bool STORE, bool TAIL>
-__device__ __forceinline__ void fold_general(const f32x16 (&acc)[2][2], Triple (&run)[2], const LogitsArgs& a, int row0,
+__device__ __forceinline__ void fold_general(const f32x16 (&acc)[NI][2], Triple (&run)[2], const LogitsArgs& a, int row0,
                                              int r_end, int col_base, int n_valid) {
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int hrow = row0 + j * 32;
     float* out = STORE ? a.logits + (size_t)min(hrow, r_end - 1) * a.ld + a.col0 : nullptr;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < NI; ++i) {
       float x[16];
       float gmax = kNegInf;
       int targ = 0;
@@ -107,12 +117,12 @@ __device__ __forceinline__ void fold_general(const f32x16 (&acc)[2][2], Triple (
 }
 
 template <typename T, bool STORE>
-__global__ void __launch_bounds__(256, 2) logits_general_kernel(GeneralArgs g) {
-  __shared__ __align__(16) unsigned char lds[4 * TILE_BYTES];   // [buf][A|B][TILE_BYTES]
+__global__ void __launch_bounds__(256, 3) logits_general_kernel(GeneralArgs g) {
+  __shared__ __align__(16) unsigned char lds[2 * (A_BYTES + B_BYTES)];   // [buf][A|B]
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int wv = wave & 1;    // which 64 vocabulary rows of the tile
+  const int wv = wave & 1;    // which 32 vocabulary rows of the tile
   const int wr = wave >> 1;   // which 64 hidden rows of the tile
 
   // ---- which part, rows, W, strip -----------------------------------------------------------------
@@ -152,7 +162,7 @@ __global__ void __launch_bounds__(256, 2) logits_general_kernel(GeneralArgs g) {
 #pragma unroll
   for (int j = 0; j < 2; ++j) run[j] = empty_triple();
 
-  // global -> LDS staging: thread t moves chunk t & 7 of rows (t >> 3) + 32 i, i < 4, of each operand tile
+  // global -> LDS staging: thread t moves chunk t & 7 of rows (t >> 3) + 32 i of each operand tile
   const int n_slabs = (int)((row_bytes + SLAB_BYTES - 1) / SLAB_BYTES);
   const uint32_t my_k = (uint32_t)(tid & 7) * 16;
   uint32_t off_b[4];
@@ -160,74 +170,89 @@ __global__ void __launch_bounds__(256, 2) logits_general_kernel(GeneralArgs g) {
   for (int i = 0; i < 4; ++i) off_b[i] = (uint32_t)min((tid >> 3) + 32 * i, r_end - 1 - r0) * row_bytes + my_k;
   // (the swizzle of row + 32 i is the row's own)
   const int lds_at = (tid >> 3) * SLAB_BYTES + (((tid & 7) ^ ((tid >> 4) & 7)) << 4);
-  // operand reads: row = 64 w + 32 i + (lane & 31), chunk 2 q + (lane >> 5)
-  const int rd_a = (wv * 64 + (lane & 31)) * SLAB_BYTES;
-  const int rd_b = TILE_BYTES + (wr * 64 + (lane & 31)) * SLAB_BYTES;
+  // operand reads: row = 32 wv (weights) or 64 wr (hidden rows) + 32 i + (lane & 31), chunk 2 q + (lane >> 5)
+  const int rd_a = (wv * (TV / 2) + (lane & 31)) * SLAB_BYTES;
+  const int rd_b = A_BYTES + (wr * 64 + (lane & 31)) * SLAB_BYTES;
   const int swz = (lane >> 1) & 7;
 
   for (int vt = vt0; vt < vt1; ++vt) {
     const int v0 = vt * TV;
     if (v0 >= n_valid) break;
     const unsigned char* Wt = Wp + (size_t)v0 * row_bytes;
-    uint32_t off_a[4];
+    uint32_t off_a[NA];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) off_a[i] = (uint32_t)min((tid >> 3) + 32 * i, n_valid - 1 - v0) * row_bytes + my_k;
+    for (int i = 0; i < NA; ++i) off_a[i] = (uint32_t)min((tid >> 3) + 32 * i, n_valid - 1 - v0) * row_bytes + my_k;
 
-    f32x16 acc[2][2];
+    f32x16 acc[NI][2];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-    f32x4 stage_a[4], stage_b[4];
+    f32x4 stage_a[NA], stage_b[4];
     auto fetch = [&](int slab) {
       const uint32_t kb = (uint32_t)slab * SLAB_BYTES;
       const bool in_k = kb + my_k < row_bytes;       // (past the end of a row: zeros add nothing)
       const f32x4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        stage_a[i] = in_k ? *reinterpret_cast<const f32x4*>(Wt + (off_a[i] + kb)) : z;
+        if (i < NA) stage_a[i] = in_k ? *reinterpret_cast<const f32x4*>(Wt + (off_a[i] + kb)) : z;
         stage_b[i] = in_k ? *reinterpret_cast<const f32x4*>(Hp + (off_b[i] + kb)) : z;
       }
     };
     auto stash = [&](int buf) {
-      unsigned char* A = lds + buf * 2 * TILE_BYTES + lds_at;
+      unsigned char* A = lds + buf * (A_BYTES + B_BYTES) + lds_at;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        *reinterpret_cast<f32x4*>(A + i * 32 * SLAB_BYTES) = stage_a[i];
-        *reinterpret_cast<f32x4*>(A + TILE_BYTES + i * 32 * SLAB_BYTES) = stage_b[i];
+        if (i < NA) *reinterpret_cast<f32x4*>(A + i * 32 * SLAB_BYTES) = stage_a[i];
+        *reinterpret_cast<f32x4*>(A + A_BYTES + i * 32 * SLAB_BYTES) = stage_b[i];
       }
     };
 
+    // Fragments are read a quarter slab ahead; a slab's successor is written to LDS under its second quarter and its own last
+    // fragments are read ahead of the barrier, so that what stands between two slabs is the barrier alone.
+    f32x4 fa[2][NI], fb[2][2];
+    auto read = [&](f32x4 (&ra)[NI], f32x4 (&rb)[2], int buf, int q) {
+      const unsigned char* L = lds + buf * (A_BYTES + B_BYTES) + (((2 * q + (lane >> 5)) ^ swz) << 4);
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        ra[i] = *reinterpret_cast<const f32x4*>(L + rd_a + i * 32 * SLAB_BYTES);
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        rb[i] = *reinterpret_cast<const f32x4*>(L + rd_b + i * 32 * SLAB_BYTES);
+      }
+    };
     fetch(0);
     __syncthreads();          // the previous tile's readers are done with buffer 0
     stash(0);
-    __syncthreads();
+    if (n_slabs > 1) fetch(1);
+    meet();
+    read(fa[0], fb[0], 0, 0);
     for (int slab = 0; slab < n_slabs; ++slab) {
       const int buf = slab & 1;
-      if (slab + 1 < n_slabs) fetch(slab + 1);
-      const unsigned char* L = lds + buf * 2 * TILE_BYTES;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int o = ((2 * q + (lane >> 5)) ^ swz) << 4;
-        f32x4 fa[2], fb[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          fa[i] = *reinterpret_cast<const f32x4*>(L + rd_a + i * 32 * SLAB_BYTES + o);
-          fb[i] = *reinterpret_cast<const f32x4*>(L + rd_b + i * 32 * SLAB_BYTES + o);
-        }
-        mfma_block<T>(fa, fb, acc);
+      const bool more = slab + 1 < n_slabs;
+      read(fa[1], fb[1], buf, 1);
+      mfma_block<T>(fa[0], fb[0], acc);
+      read(fa[0], fb[0], buf, 2);
+      if (more) {
+        stash(buf ^ 1);       // (its last readers had their fragments ahead of the barrier before)
+        if (slab + 2 < n_slabs) fetch(slab + 2);
       }
-      if (slab + 1 < n_slabs) {
-        stash(buf ^ 1);       // buffer buf^1 was last read two slabs ago, behind the barrier below
-        __syncthreads();
+      mfma_block<T>(fa[1], fb[1], acc);
+      read(fa[1], fb[1], buf, 3);
+      mfma_block<T>(fa[0], fb[0], acc);
+      if (more) {
+        meet();
+        read(fa[0], fb[0], buf ^ 1, 0);
       }
+      mfma_block<T>(fa[1], fb[1], acc);
     }
 
-    // ---- epilogue of this tile: fold the 128 x 128 logits into the running triples -------------
-    const int col_base = v0 + wv * 64 + (lane >> 5) * 4;
+    // ---- epilogue of this tile: fold the 64 x 128 logits into the running triples -------------
+    const int col_base = v0 + wv * (TV / 2) + (lane >> 5) * 4;
     const int row0 = r0 + wr * 64 + (lane & 31);
     if (v0 + TV <= n_valid)
       fold_general<STORE, false>(acc, run, a, row0, r_end, col_base, n_valid);

@@ -21,6 +21,8 @@ pytestmark = pytest.mark.gpu
     ("f32", 3, 128, 2049, 64, 0),       # no hyper part; whole slabs
     ("bf16", 2, 200, 700, 72, 150),     # d no multiple of 64
     ("bf16", 1, 1, 50, 8, 5),           # a single row
+    ("f32", 2, 130, 65, 68, 66),        # tiles with one and two columns behind a whole one; two K slabs and a chunk
+    ("f32", 1, 300, 6400, 32, 64),      # one slab: nothing is fetched ahead; strips of one tile
 ])
 def test_general_kernel(dtype, B, rows_per_seq, V, d, cap):
     import torch
@@ -69,4 +71,32 @@ def test_general_kernel(dtype, B, rows_per_seq, V, d, cap):
         sl = slice(b * rows_per_seq, (b + 1) * rows_per_seq)
         want = oracle.extended_logits(H[sl], E, Wr, len(ref[b][1]), dtype)
         check_logits_rows(want, am[sl], mx[sl], lse[sl], logits[sl])
+    ctx.close()
+
+
+def test_strips_lengthen_where_the_static_array_would_not_hold_the_parts():
+    """32768 rows x 32769 columns: strips of 4 x 64 columns would leave 129 parts a row, more than 2^22 in all; every row against
+    float64 products (four terms each: 1e-6 of the largest logit)."""
+    import torch
+
+    from paper_2506_01084_amd import api
+
+    rows, V, d = 32768, 32769, 4
+    ctx = api.Context(B=1, V=V, M=3, cap=0, d=d, dtype="f32", pool="mean")
+    ctx.reset()
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    W, H = torch.randn((V, d), generator=gen, device="cuda"), torch.randn((rows, d), generator=gen, device="cuda")
+    W[-1] = 9.0                                   # the column of a tile of its own decides many rows
+    am = torch.full((rows,), -5, dtype=torch.int32, device="cuda")
+    mx, lse = torch.zeros(rows, device="cuda"), torch.zeros(rows, device="cuda")
+    ctx.extended_logits(H, rows, W, torch.zeros((1, 0, d), device="cuda"), am, mx, lse)
+    torch.cuda.synchronize()
+    for r in range(0, rows, 4096):
+        z = H[r:r + 4096].double() @ W.double().t()
+        top = z.topk(2, dim=1)
+        sl = slice(r, r + 4096)
+        assert torch.allclose(mx[sl].double(), top.values[:, 0], rtol=1e-6, atol=1e-6)
+        assert torch.allclose(lse[sl].double(), z.logsumexp(1), rtol=1e-5, atol=1e-5)
+        clear = top.values[:, 0] - top.values[:, 1] > 1e-4
+        assert torch.equal(am[sl][clear].long(), top.indices[:, 0][clear])
     ctx.close()
