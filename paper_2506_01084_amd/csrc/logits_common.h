@@ -314,7 +314,7 @@ __device__ __forceinline__ void fold_tile_sample(const f32x16 (&acc)[NI][NJ], Tr
   const int lane31 = threadIdx.x & 31;
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
-    if (row_base + j * 32 >= a.rows) break;          // (uniform; 24 sequences over 128256 columns: 236 -> 224 us)
+    if (row_base + j * 32 >= a.rows) break;          // (uniform; 24 sequences over 128256 columns: 236 -> 224 us, before the scratch memory went)
     const uint32_t row = (uint32_t)(row_base + j * 32 + lane31);
     Triple t = run[j];
     Draw dr = draw[j];
@@ -328,26 +328,30 @@ __device__ __forceinline__ void fold_tile_sample(const f32x16 (&acc)[NI][NJ], Tr
         const int c0 = a.col0 + col_base + i * 32 + q * 8;
         const uint4 w = philox4x32_10(uint4{(uint32_t)(c0 >> 2), row, a.ctr2, a.ctr3}, a.key0, a.key1);
         const uint32_t word[4] = {w.x, w.y, w.z, w.w};
+        float z[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-          const float xv = q == 0 ? x[k] : (q == 1 ? x[4 + k] : (q == 2 ? x[8 + k] : x[12 + k]));
           // (columns past the last valid one: -inf never enters the triple or wins the draw)
-          const bool ok = c0 - a.col0 + k < n_valid;
-          const float z = ok ? xv * a.inv_temperature : kNegInf;
-          if (z > t.m) {
-            t.s = (t.m == kNegInf) ? 1.f : t.s * __expf(t.m - z) + 1.f;
-            t.m = z;
-            t.i = c0 + k;
-          } else if (ok) {
-            t.s += __expf(z - t.m);
-          }
-          const float pv = z + gumbel_from_word(word[k]);
+          z[k] = c0 - a.col0 + k < n_valid ? x[k] * a.inv_temperature : kNegInf;
+          const float pv = z[k] + gumbel_from_word(word[k]);
           if (pv > dr.v) {
             dr.v = pv;
-            dr.l = z;
+            dr.l = z[k];
             dr.i = c0 + k;
           }
         }
+        const float m4 = fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]));
+        if (m4 > t.m) {
+          t.s = (t.m == kNegInf) ? 0.f : t.s * __expf(t.m - m4);
+          t.m = m4;
+          t.i = c0 + (z[0] == m4 ? 0 : (z[1] == m4 ? 1 : (z[2] == m4 ? 2 : 3)));
+        }
+        if (t.m != kNegInf)
+          t.s += (__expf(z[0] - t.m) + __expf(z[1] - t.m)) + (__expf(z[2] - t.m) + __expf(z[3] - t.m));
+        // (the next four move up: picked by q, the values go through scratch memory -- draws of 24 sequences over 128256
+        // columns 224 -> 208 us, 64: 284 -> 267)
+#pragma unroll
+        for (int v = 0; v < 12; ++v) x[v] = x[v + 4];
       }
     }
     run[j] = t;
