@@ -43,3 +43,40 @@ def test_pieces_behind_the_whole_blocks(row_tiles):
     for x, y in zip(*got):
         assert np.array_equal(x, y)
     ctx.close()
+
+
+@pytest.mark.parametrize("row_tiles,V", [
+    (2, 17921),         # 71 weight tiles, walked in blocks along the vocabulary; the last with one column
+    (5, 9300),          # five row tiles: an odd short side, dealt out whole
+    (6, 8192),          # an even one, two ways
+    (33, 300),          # more row tiles than weight tiles: blocks along the rows, one behind whole blocks of 32
+    (9, 513),           # three weight tiles under nine row tiles
+])
+def test_lists_hold_every_tile_once(row_tiles, V):
+    """The automatic order along either side against single row tiles dealt out eight ways: the same bits."""
+    import torch
+
+    from paper_2506_01084_amd import api
+
+    rows, d = row_tiles * 256 - 5, 64
+    print(f"[case] {row_tiles} row tiles x {V} columns", flush=True)
+    ctx = api.Context(B=1, V=V, M=3, cap=0, d=d, dtype="bf16", pool="mean")
+    ctx.reset()
+    gen = torch.Generator(device="cuda").manual_seed(V)
+    W, H = (torch.randn((n, d), generator=gen, device="cuda").bfloat16() for n in (V, rows))
+    none = torch.zeros((1, 0, d), dtype=torch.bfloat16, device="cuda")
+    got = []
+    for mapping in (0, 1 | 1 << 8 | 8 << 16 | 1 << 24):
+        ctx.set_option(api.OPT_LOGITS_MAP, mapping)
+        am = torch.full((rows,), -5, dtype=torch.int32, device="cuda")
+        mx, lse = torch.full((rows,), 777.0, device="cuda"), torch.full((rows,), 777.0, device="cuda")
+        ctx.extended_logits(H, rows, W, none, am, mx, lse)
+        torch.cuda.synchronize()
+        got.append((am, mx, lse))
+        # the parts of the next call start from other values
+        ctx.extended_logits(torch.zeros_like(H), rows, W, none, am.clone(), mx.clone(), lse.clone())
+    for x, y in zip(*got):
+        assert torch.equal(x, y)
+    want = (H.float() @ W.float().t()).max(1).values          # 64 products of bf16 values in fp32: 1e-5 of the size
+    assert torch.allclose(got[0][1], want, rtol=1e-5, atol=1e-4)
+    ctx.close()
