@@ -8,20 +8,19 @@
 //
 //   workgroup = 8 waves = one tile of 256 weight rows x all hidden rows; wave w owns weight rows 32 w .. 32 w + 31:
 //   2, 4 or 6 blocks of v_mfma_f32_32x32x16_bf16 (the kernel is built for up to 64, 128 and 192 rows).
-//   K advances in slabs of 64.  Up to 128 rows a wave moves its own weights straight from global memory into a ring of its
+//   K advances in slabs of 64.  A wave moves its own weights straight from global memory into a ring of its
 //   own in LDS, four requests of 8 whole lines per slab, two or three slabs ahead, and reads its operands from there; nobody else
 //   touches the ring, so it needs no barrier.  (Loaded in operand layout, 32 rows and half a line each way, a
 //   request takes 64 pieces of 16 bytes: 1 GB of weights for 64 rows 190 us; through the ring 180; and since
 //   every request takes whole lines, the weights can go past the caches, which the halves of a line cannot: 162, 6.5 TB/s.)
-//   In the 192-row build the hidden rows leave no room for a ring: weights in operand layout in four register buffers,
-//   two to three slabs ahead, two slabs at a time (256 contiguous bytes per row: +5 % over single slabs).
 //   The hidden rows of a slab (up to 192 x 128 bytes, shared by the 8 waves, served by L2) go straight from global memory
-//   into one of three LDS stages, two slabs ahead, in the tile kernel's swizzled layout (conflict-free operand
-//   reads); one barrier per slab.
+//   into LDS stages, two slabs ahead (one in the 192-row build, which has room for two stages beside three ring slots), in the
+//   tile kernel's swizzled layout (conflict-free operand reads); one barrier per slab.
 //   The tiles start their walk over K at different slabs (+5-7 %: see below).
 //
 // V = 128256, d = 4096, whole calls in us, operand-layout loads -> ring: 8 x 5 rows 207 -> 187, 24 x 5 258 -> 211, steps of
-// 16 / 64 / 100 / 128 sequences 213 -> 185, 272 -> 244, 340 -> 300, 365 -> 323; 192 rows stay at 4.1 TB/s of W_base.
+// 16 / 64 / 100 / 128 sequences 213 -> 185, 272 -> 244, 340 -> 300, 365 -> 323,
+// 160 / 192 438 -> 390, 480 -> 423.
 // The fold of the finished tile into (max, sum-exp,
 // argmax) triples is the tile kernel's; the 8 waves' triples of a hidden row are merged through LDS and leave one
 // part per (row, weight tile).
@@ -39,15 +38,13 @@ constexpr int M_WT = 32 * M_WAVES;        // weight rows of a workgroup's tile
 constexpr int M_HT = 192;                 // hidden rows of a call at most (the builds below: 2, 4 or 6 blocks of 32)
 constexpr int M_MAX_ROWS = M_HT;
 constexpr int M_SLAB = 128;               // bytes per row per K slab (64 bf16)
-constexpr int M_STAGE = M_HT * M_SLAB;    // the hidden rows of one slab: 24 KiB
-constexpr int M_NSTAGE = 3;
-constexpr int M_LDS = M_NSTAGE * M_STAGE;
-constexpr int M_NBUF_6 = 4;               // weight register buffers of the 192-row build (what fits beside 96 accumulators)
-// 1: the weights of two consecutive slabs are requested together, every other step: 256 contiguous bytes per row
-#ifndef M_PAIR
-#define M_PAIR 1
-#endif
-static_assert(M_WAVES * M_HT * (int)(sizeof(Triple) + sizeof(Draw)) <= M_LDS, "the waves' triples are merged in the idle stages");
+// LDS per build (blocks of 32 hidden rows): stages of a slab's hidden rows, and the waves' rings with what is left.
+constexpr int mid_stages(int njv) { return njv == 6 ? 2 : 3; }
+constexpr int mid_ring(int njv) { return njv == 2 ? 4 : 3; }
+constexpr int mid_lds(int njv) { return mid_stages(njv) * 32 * njv * M_SLAB + M_WAVES * 32 * M_SLAB * mid_ring(njv); }
+constexpr int M_LDS_MAX = mid_lds(2) > mid_lds(4) ? mid_lds(2) : mid_lds(4);
+static_assert(M_LDS_MAX <= 160 * 1024 && mid_lds(6) <= M_LDS_MAX, "");
+static_assert(M_WAVES * M_HT * (int)(sizeof(Triple) + sizeof(Draw)) <= mid_lds(6), "the waves' triples are merged in the idle stages and rings");
 
 // 16 bytes per lane, global -> LDS without passing through registers (as in the tile kernel): address = 64-bit
 // scalar base + 32-bit per-lane offset; the LDS address is the wave-uniform byte offset in M0 plus 16 * lane.
@@ -78,20 +75,19 @@ __device__ __forceinline__ uint32_t lds_offset_of(const void* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
 }
 
-// NJV: blocks of 32 hidden rows the instance is built for (rows of the tile <= 32 NJV); RING: slabs of the waves' rings
-// (those in flight + the one in use), 0: register buffers; SMODE: 0 = fold the logits, 1 = fold logit / T and the Gumbel-max
+// NJV: blocks of 32 hidden rows the instance is built for (rows of the tile <= 32 NJV); SMODE: 0 = fold the logits, 1 = fold logit / T and the Gumbel-max
 // draw (a.sample = 1: part_v, part_l, and the drawn column in part_i), 2 = store logit / T and fold it
 // (a.sample = 2) -- the tile kernel's epilogues for its modes 0, 6 and 7; 3 = a dense layer with K split over
 // gridDim.y workgroups per tile: the fp32 partial tile goes to a.partial[ks][row][col] (the tile kernel's mode 5);
 // 4, 5, 6 = 0, 1, 2 with the sums in levels, for a step of up to 64 sequences.
-template <int NJV, int RING, int SMODE>
+template <int NJV, int SMODE>
 __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int half = lane >> 5;
-  constexpr int NBUF = M_NBUF_6;
-  constexpr int STAGE = 32 * NJV * M_SLAB, STAGES = M_NSTAGE * STAGE;
+  constexpr int STAGES = mid_stages(NJV), RING = mid_ring(NJV);
+  constexpr int STAGE = 32 * NJV * M_SLAB, STAGE_BYTES = STAGES * STAGE;
   constexpr int W_SLAB = 32 * M_SLAB;                      // a wave's weights of one slab
   const int vt = blockIdx.x;                               // weight tile
   const int r0 = 0;                                        // (one row tile: the call has at most M_HT rows)
@@ -118,14 +114,6 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
     const int x = min(s, n_slabs - 1) + rot;
     return slab0 + (x >= n_slabs ? x - n_slabs : x);
   };
-  // weights into registers: this lane's row, clamped onto the last one that exists; 16 bytes at (2 q + half) * 16 of a slab
-  const int wrow = min(v0 + wave * 32 + (lane & 31), n_valid - 1);
-  const unsigned char* wp = reinterpret_cast<const unsigned char*>(a.W) + (size_t)wrow * row_bytes + half * 16;
-  auto load_w = [&](uint4 (&w)[4], int slab) {
-    const unsigned char* p = wp + (size_t)slab_at(slab) * M_SLAB;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) w[q] = *reinterpret_cast<const uint4*>(p + q * 32);
-  };
   // weights through the wave's own ring: its 32 rows in four requests of 8 whole lines, laid out as the hidden rows are
   const unsigned char* Wt = reinterpret_cast<const unsigned char*>(a.W) + (size_t)v0 * row_bytes;
   uint32_t wsrc[4];
@@ -134,7 +122,7 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
     const int row = wave * 32 + i * 8 + (lane >> 3);
     wsrc[i] = (uint32_t)(min(row, n_valid - 1 - v0) * (int)row_bytes + (((lane & 7) ^ ((row >> 1) & 7)) << 4));
   }
-  const uint32_t ring0 = lds_offset_of(lds) + (uint32_t)(STAGES + wave * (RING * W_SLAB));
+  const uint32_t ring0 = lds_offset_of(lds) + (uint32_t)(STAGE_BYTES + wave * (RING * W_SLAB));
   auto issue_w = [&](int slab, int slot) {
     const unsigned char* p = Wt + (size_t)slab_at(slab) * M_SLAB;
 #pragma unroll
@@ -221,112 +209,52 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
     }
   };
 
-  if constexpr (RING > 0) {
-    // One step = one slab: on entry to step s the hidden rows of slab s are in stage s % 3 for all, and its weights in the
-    // wave's ring slot s % RING.  Requested during the step: the hidden rows of slab s + 2 (HL requests), then the weights of
-    // slab s + RING - 1 (4), into the slot that step s - 1 has read.  At its end slab s + 1 must have landed: behind the later
-    // of its two come HL + 4 (RING - 2) requests.  The last steps request nothing that does not exist, and wait for all.
-    int stage = 0, slot = 0;
-    auto step_compute = [&]() {
-      const unsigned char* As = lds + STAGES + wave * (RING * W_SLAB) + slot * W_SLAB + offB;
-      uint4 w[4];
+  // One step = one slab: on entry to step s the hidden rows of slab s are in stage s % STAGES for all, and its weights in the
+  // wave's ring slot s % RING.  Requested during the step: the hidden rows of slab s + STAGES - 1 (HL requests), then the
+  // weights of slab s + RING - 1 (4), both into what step s - 1 has read.  At its end slab s + 1 must have landed: KEEP
+  // requests come behind the later of its two.  The last steps request nothing that does not exist, and wait for all.
+  constexpr int KEEP = STAGES == 3 ? HL + 4 * (RING - 2) : 4;
+  int stage = 0, slot = 0;
+  auto step_compute = [&]() {
+    const unsigned char* As = lds + STAGE_BYTES + wave * (RING * W_SLAB) + slot * W_SLAB + offB;
+    uint4 w[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) w[q] = *reinterpret_cast<const uint4*>(As + (((2 * q + half) ^ sw) << 4));
-      compute(w, stage);
-    };
-    auto next_step = [&]() {
-      __syncthreads();
-      stage = stage == 2 ? 0 : stage + 1;
-      slot = slot == RING - 1 ? 0 : slot + 1;
-    };
-    issue_h(0, 0);
-    issue_w(0, 0);
-    if (n_slabs > 1) issue_h(1, 1);
-#pragma unroll
-    for (int u = 1; u < RING - 1; ++u)
-      if (u < n_slabs) issue_w(u, u);
-    if (n_slabs >= RING - 1)
-      wait_loads<HL + 4 * (RING - 2)>();
-    else
-      wait_loads<0>();
+    for (int q = 0; q < 4; ++q) w[q] = *reinterpret_cast<const uint4*>(As + (((2 * q + half) ^ sw) << 4));
+    compute(w, stage);
+  };
+  auto next_step = [&]() {
     __syncthreads();
-    int s = 0;
-    for (; s + RING - 1 < n_slabs; ++s) {
-      issue_h(s + 2, stage == 0 ? 2 : stage - 1);
-      issue_w(s + RING - 1, slot == 0 ? RING - 1 : slot - 1);
-      step_compute();
-      if (LEVELS && (s & 1)) next_level();
-      if (LEVELS && (s & 15) == 15) third_level();
-      wait_loads<HL + 4 * (RING - 2)>();
-      next_step();
-    }
-    for (; s < n_slabs; ++s) {
-      if (s + 2 < n_slabs) issue_h(s + 2, stage == 0 ? 2 : stage - 1);
-      step_compute();
-      if (LEVELS && (s & 1)) next_level();
-      if (LEVELS && (s & 15) == 15) third_level();
-      wait_loads<0>();
-      next_step();
-    }
-  } else {
-    // One step = one slab.  On entry to step s: stage s % 3 holds the hidden rows of slab s, visible to all; those of
-    // slab s + 1 are on their way into stage (s + 1) % 3; buffer s % NBUF holds the weights of slab s, the weights of
-    // the next slabs are on their way.  Loads complete in the order of their requests.  Requested during step s, in
-    // this order: the hidden rows of slab s + 2 (HL requests; the stage's last readers, those of slab s - 1, passed
-    // the barrier of step s - 1), then weights: of slab s + NBUF - 1 (4 requests), or with M_PAIR of the slabs
-    // s + NBUF - 2 and s + NBUF - 1 before every other step (8 requests).  Before the barrier of step s the hidden
-    // rows of slab s + 1 must have landed: after them came the weight requests of step s - 1 and the HL + weight
-    // requests of step s, HL + 8 in all either way, which may stay in flight.
-    int stage = 0;                                           // s % 3
-    uint4 w[NBUF][4];
-    static_assert(!M_PAIR || NBUF % 2 == 0, "pairs of slabs");
-    auto requests = [&](int u, int s) {                      // u = s % NBUF, a constant where this is expanded
-      issue_h(s + 2, stage == 0 ? 2 : stage - 1);            // stage (s + 2) % 3
-      if (M_PAIR) {
-        if ((u & 1) == 0) {                                  // the two buffers used last
-          load_w(w[(u + NBUF - 2) % NBUF], s + NBUF - 2);
-          load_w(w[(u + NBUF - 1) % NBUF], s + NBUF - 1);
-        }
-      } else {
-        load_w(w[(u + NBUF - 1) % NBUF], s + NBUF - 1);
-      }
-    };
-    // (in_loop: the count above holds inside the loop, where every weight request feeds a later iteration.  In the
-    // steps after the loop the compiler drops the requests whose buffers no step reads any more, so there
-    // everything in flight is awaited: a handful of steps per tile.)
-    auto finish = [&](int u, bool in_loop) {
-      compute(w[u], stage);
-      if (in_loop)
-        wait_loads<HL + 8>();
-      else
-        wait_loads<0>();
-      __syncthreads();
-      stage = stage == 2 ? 0 : stage + 1;
-    };
-
-    issue_h(0, 0);
-    issue_h(1, 1);
-    constexpr int PRE = M_PAIR ? NBUF - 2 : NBUF - 1;        // slabs whose weights are requested ahead of the loop
+    stage = stage == STAGES - 1 ? 0 : stage + 1;
+    slot = slot == RING - 1 ? 0 : slot + 1;
+  };
+  issue_h(0, 0);
+  issue_w(0, 0);
+  if (STAGES == 3 && n_slabs > 1) issue_h(1, 1);
 #pragma unroll
-    for (int u = 0; u < PRE; ++u) load_w(w[u], u);
-    wait_loads<HL + 4 * PRE>();                              // slab 0's hidden rows; what followed may be in flight
-    __syncthreads();
-    // whole rounds of the buffers without a test inside (a loop the register allocator keeps the buffers fixed in),
-    // then the rest
-    int s0 = 0;
-    for (; s0 + NBUF <= n_slabs; s0 += NBUF) {
-#pragma unroll
-      for (int u = 0; u < NBUF; ++u) {
-        requests(u, s0 + u);
-        finish(u, true);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < NBUF - 1; ++u)
-      if (s0 + u < n_slabs) {                                // (uniform)
-        requests(u, s0 + u);
-        finish(u, false);
-      }
+  for (int u = 1; u < RING - 1; ++u)
+    if (u < n_slabs) issue_w(u, u);
+  if (n_slabs >= RING - 1)
+    wait_loads<(STAGES - 2) * HL + 4 * (RING - 2)>();
+  else
+    wait_loads<0>();
+  __syncthreads();
+  int s = 0;
+  for (; s + RING - 1 < n_slabs; ++s) {
+    issue_h(s + STAGES - 1, stage == 0 ? STAGES - 1 : stage - 1);
+    issue_w(s + RING - 1, slot == 0 ? RING - 1 : slot - 1);
+    step_compute();
+    if (LEVELS && (s & 1)) next_level();
+    if (LEVELS && (s & 15) == 15) third_level();
+    wait_loads<KEEP>();
+    next_step();
+  }
+  for (; s < n_slabs; ++s) {
+    if (s + STAGES - 1 < n_slabs) issue_h(s + STAGES - 1, stage == 0 ? STAGES - 1 : stage - 1);
+    step_compute();
+    if (LEVELS && (s & 1)) next_level();
+    if (LEVELS && (s & 15) == 15) third_level();
+    wait_loads<0>();
+    next_step();
   }
   // the requests past the end of the stream (slabs clamped onto the last one) must land before the stages are reused
   wait_loads<0>();
@@ -404,23 +332,17 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
   }
 }
 
-// Ring slots per build: what fits beside three stages of hidden rows (0: weights in registers).
-constexpr int mid_ring(int njv) { return njv == 2 ? 4 : (njv == 4 ? 3 : 0); }
-constexpr int mid_lds(int njv) { return M_NSTAGE * 32 * njv * M_SLAB + M_WAVES * 32 * M_SLAB * mid_ring(njv); }
-constexpr int M_LDS_MAX = mid_lds(2) > mid_lds(4) ? mid_lds(2) : mid_lds(4);
-static_assert(M_LDS_MAX <= 160 * 1024 && mid_lds(2) >= M_LDS && mid_lds(4) >= M_LDS && mid_lds(6) == M_LDS, "");
-
 template <int NJV, int SMODE>
 __global__ void __launch_bounds__(M_THREADS) logits_mid_kernel(LogitsArgs a) {
   extern __shared__ __align__(1024) unsigned char lds[];
   if constexpr (SMODE == 3 && NJV == 4) {
     // (the rows that exist may be half of those laid out: known here only)
     if ((a.rows_dev ? min(a.rows, *a.rows_dev) : a.rows) <= 64)
-      mid_tile<2, mid_ring(2), SMODE>(a, lds);
+      mid_tile<2, SMODE>(a, lds);
     else
-      mid_tile<4, mid_ring(4), SMODE>(a, lds);
+      mid_tile<4, SMODE>(a, lds);
   } else {
-    mid_tile<NJV, mid_ring(NJV), SMODE>(a, lds);
+    mid_tile<NJV, SMODE>(a, lds);
   }
 }
 
