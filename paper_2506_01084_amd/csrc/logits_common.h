@@ -346,8 +346,8 @@ __device__ __forceinline__ void fold_tile_sample(const f32x16 (&acc)[NI][NJ], Tr
           t.m = m4;
           t.i = c0 + (z[0] == m4 ? 0 : (z[1] == m4 ? 1 : (z[2] == m4 ? 2 : 3)));
         }
-        if (t.m != kNegInf)
-          t.s += (__expf(z[0] - t.m) + __expf(z[1] - t.m)) + (__expf(z[2] - t.m) + __expf(z[3] - t.m));
+        const float m = t.m == kNegInf ? 0.f : t.m;  // (columns that do not exist add 0, a hidden row's NaN stay NaN)
+        t.s += (__expf(z[0] - m) + __expf(z[1] - m)) + (__expf(z[2] - m) + __expf(z[3] - m));
         // (the next four move up: picked by q, the values go through scratch memory -- draws of 24 sequences over 128256
         // columns 224 -> 208 us, 64: 284 -> 267)
 #pragma unroll

@@ -179,7 +179,7 @@ __device__ __forceinline__ void mask_tail16(Acc& acc, int col_base, int n_valid)
 // Fold one finished tile into the running triples, 16 values of a row at a time, in increasing column order per lane, so
 // strict comparisons keep the lowest column among equal maxima.  The running sum is kept against the running maximum in
 // base-2 units: exp(x - m) is one multiply-add and one hardware exponential.
-__device__ __forceinline__ void fold_tile16(const Acc& acc, Triple (&run)[F_N], int col_base, int col0) {
+__device__ __forceinline__ void fold_tile16(const Acc& acc, Triple (&run)[F_N], int col_base, int col0, int n_valid) {
   constexpr float kLog2e = 1.4426950408889634f;
 #pragma unroll
   for (int j = 0; j < F_N; ++j) {
@@ -200,8 +200,10 @@ __device__ __forceinline__ void fold_tile16(const Acc& acc, Triple (&run)[F_N], 
         run[j].m = gmax;
         run[j].i = col0 + col_base + h * 64 + (targ >> 2) * 16 + (targ & 3);
       }
-      if (run[j].m != kNegInf) {
-        const float m2 = -run[j].m * kLog2e;
+      if (col_base + h * 64 < n_valid) {
+        // (where nothing has been above -inf yet, columns that do not exist add 0 and a hidden row's NaN stay NaN.  The branch keeps
+        // the groups apart: without it they are scheduled together and spill 48 bytes a lane.)
+        const float m2 = run[j].m == kNegInf ? 0.f : -run[j].m * kLog2e;
         float add0 = 0.f, add1 = 0.f;
 #pragma unroll
         for (int v = 0; v < 16; v += 2) {
@@ -309,8 +311,8 @@ __device__ __forceinline__ void fold_sample16(const Acc& acc, Triple (&run)[F_N]
           t.m = m4;
           t.i = c0 + (z[0] == m4 ? 0 : (z[1] == m4 ? 1 : (z[2] == m4 ? 2 : 3)));
         }
-        if (t.m != kNegInf)
-          t.s += (__expf(z[0] - t.m) + __expf(z[1] - t.m)) + (__expf(z[2] - t.m) + __expf(z[3] - t.m));
+        const float m = t.m == kNegInf ? 0.f : t.m;  // (a hidden row's NaN stay NaN, as in fold_tile16)
+        t.s += (__expf(z[0] - m) + __expf(z[1] - m)) + (__expf(z[2] - m) + __expf(z[3] - m));
         // (the next four move up: picked by q, the values go through scratch memory -- draws of 256 sequences over 128256
         // columns 735 -> 644 us, 300: 1136 -> 949; the plain picks' kernel gains 27 and 22 of that as well)
 #pragma unroll
@@ -770,7 +772,7 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
         fold_store16(acc, run, a, row_base, r_end, col_base, n_valid);
       } else {
         if ((vt + 1) * FT > n_valid) mask_tail16(acc, col_base, n_valid);
-        fold_tile16(acc, run, col_base, a.col0);
+        fold_tile16(acc, run, col_base, a.col0, n_valid);
       }
     }
     if (MODE >= 2 && MODE <= 5) continue;
