@@ -318,7 +318,7 @@ int z2z_launch_logits_part(z2z_ctx* c, bool hyper, LogitsArgs a, const void* W, 
 
 // A workgroup sweeps a strip of 4 weight tiles with its rows' tile resident; with few row tiles that leaves CUs
 // idle, so the strips shorten until there are `want` workgroups (or one tile per workgroup): two per CU for the
-// bf16 tile kernel, four for the general kernel (tiles of 64 columns), of which three run on a CU at a time (fp32, d = 256,
+// bf16 tile kernel, four for the general kernel, of which two (tiles of 128 columns) or three (64) run on a CU at a time (fp32, 64, d = 256,
 // 32000 columns, strips of 1 / 2 / 4 tiles: 1024 rows 159 / 156 / 179 us, 2048 rows 299 / 291 / 314).
 static int pick_strip_for(const z2z_ctx* c, long long row_tiles, int n_vt, int want = 512) {
   if (c->opt_logits_strip > 0) return c->opt_logits_strip;
@@ -403,14 +403,15 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
   const bool fast = fast_ok && c->opt_logits_kernel != 1;
 
   // number of parts (strips of both launches), then the scratch for them
-  const int tile = fast ? 256 : 128, tile_v = fast ? 256 : 64;
+  const int tile = fast ? 256 : 128;
+  const long long tiles_b = (rows + tile - 1) / tile, tiles_h = (long long)c->cfg.B * ((rows_per_seq + tile - 1) / tile);
+  const int tile_v = fast ? 256 : z2z_logits_general_columns(c->cfg.dtype == Z2Z_BF16, tiles_b * ((V + 63) / 64) + tiles_h * ((cap + 63) / 64));
   const int base_vt = (V + tile_v - 1) / tile_v, hyp_vt = (cap + tile_v - 1) / tile_v;
   // few hidden rows in all (several per sequence, or 65..192 sequences): the base part is bound by the bytes of
   // W_base and goes to the kernel that streams the weights past all rows at once, one part per 256 weight rows
   // (measured against the decode kernel's base units in a launch of their own at up to 64 rows: 260 against 305 us
   // for the call at config 2's shape; two or three passes of those units for more rows cost more still)
   const bool mid_base = fast && c->opt_logits_kernel == 0 && z2z_logits_mid_ok(c, rows);
-  const long long tiles_b = (rows + tile - 1) / tile, tiles_h = (long long)c->cfg.B * ((rows_per_seq + tile - 1) / tile);
   int strip_b = 1, strip_h = 1;
   if (fast) {
     if (!mid_base) strip_b = pick_strip_for(c, tiles_b, base_vt);
@@ -418,13 +419,14 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
   } else {
     // (strips asked for, and those where the static array could not hold the parts of shorter ones, count in 128 columns;
     // the other entry point cuts the same way)
-    const bool pairs = c->opt_logits_strip > 0;
-    const int vt2_b = (base_vt + 1) / 2, vt2_h = (hyp_vt + 1) / 2;
-    strip_b = pairs ? 2 * c->opt_logits_strip : pick_strip_for(c, tiles_b, base_vt, 1024);
-    strip_h = pairs ? 2 * c->opt_logits_strip : pick_strip_for(c, tiles_h, hyp_vt, 1024);
-    if (!pairs && (size_t)((base_vt + strip_b - 1) / strip_b + (hyp_vt + strip_h - 1) / strip_h) * rows > Z2Z_STATIC_PARTS) {
-      strip_b = 2 * pick_strip_for(c, tiles_b, vt2_b, 1024);
-      strip_h = 2 * pick_strip_for(c, tiles_h, vt2_h, 1024);
+    const bool asked = c->opt_logits_strip > 0;
+    const int unit = 128 / tile_v;
+    const int units_b = (base_vt + unit - 1) / unit, units_h = (hyp_vt + unit - 1) / unit;
+    strip_b = asked ? unit * c->opt_logits_strip : pick_strip_for(c, tiles_b, base_vt, 1024);
+    strip_h = asked ? unit * c->opt_logits_strip : pick_strip_for(c, tiles_h, hyp_vt, 1024);
+    if (!asked && (size_t)((base_vt + strip_b - 1) / strip_b + (hyp_vt + strip_h - 1) / strip_h) * rows > Z2Z_STATIC_PARTS) {
+      strip_b = unit * pick_strip_for(c, tiles_b, units_b, 1024);
+      strip_h = unit * pick_strip_for(c, tiles_h, units_h, 1024);
     }
   }
   const int base_strips = (base_vt + strip_b - 1) / strip_b;
@@ -464,7 +466,7 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     if (cap > 0) fill_part(h, c->st.size, tile, tile_v, c->cfg.B, W_hyper, cap, V, base_strips, strip_h, rows, rows_per_seq);
     c->n_launch[Z2Z_KERNEL_GENERAL]++;
     if (timed) Z2Z_HIP_TRY(hipEventRecord(c->ev_start[c->n_timed], s));
-    rc = z2z_launch_logits_general(c->cfg.dtype == Z2Z_BF16, a, cap > 0 ? &h : nullptr, s);
+    rc = z2z_launch_logits_general(c->cfg.dtype == Z2Z_BF16, tile_v, a, cap > 0 ? &h : nullptr, s);
     if (rc != Z2Z_OK) return rc;
     if (timed) {
       Z2Z_HIP_TRY(hipEventRecord(c->ev_stop[c->n_timed], s));

@@ -387,7 +387,8 @@ __device__ __forceinline__ void store_partial_tile(const f32x16 (&acc)[NI][NJ], 
 }  // namespace z2z_logits
 
 // kernel launchers, one per translation unit
-int z2z_launch_logits_general(bool bf16, const z2z_logits::LogitsArgs& base, const z2z_logits::LogitsArgs* hyper, hipStream_t s);
+int z2z_logits_general_columns(bool bf16, long long tiles_of_64);
+int z2z_launch_logits_general(bool bf16, int columns, const z2z_logits::LogitsArgs& base, const z2z_logits::LogitsArgs* hyper, hipStream_t s);
 // mode: 0 base part, 1 hyper part (both fold the joint softmax), 2 dense layer (stores the tile),
 // 3 base part, 4 hyper part storing the gradient with respect to the logits, 5 dense layer with K split
 // (fp32 partial tiles)

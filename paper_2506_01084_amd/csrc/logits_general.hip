@@ -11,6 +11,7 @@
 // barriers and folds are covered by the others on its CU, so its tile is as small as keeps three of them there (48 KiB of LDS,
 // at most 168 registers): 64 columns x 128 rows, whose LDS reads still take a fifth of the matrix instructions' time.  Smaller
 // tiles also fill the last round of a CU better.  With 128 x 128, two per CU, two waves per SIMD kept the matrix cores 62 % busy.
+// bf16 takes 128 x 128 but for the smallest calls (z2z_logits_general_columns).
 // The instance that stores the logits is a kernel of its own (its store addresses and column tests cost the plain one
 // registers), and operand rows are 32-bit offsets from one base address per tile.
 // Both parts share a launch, the hyper part's few tiles first; an XCD walks consecutive row tiles of consecutive
@@ -24,50 +25,49 @@ namespace {
 using namespace z2z_logits;
 
 // ------------------------------------------------------------------------------------------------
-// Tile kernel, 64 (vocabulary) x 128 (hidden rows) per workgroup, 4 waves of 32 x 64, K slabs of
-// 128 bytes per row.  LDS holds two buffers of (64 + 128) rows x 128 B; the 16-byte chunk c of row
+// Tile kernel, TV = 64 or 128 (vocabulary) x 128 (hidden rows) per workgroup, 4 waves of TV / 2 x 64, K slabs of
+// 128 bytes per row.  LDS holds two buffers of (TV + 128) rows x 128 B; the 16-byte chunk c of row
 // r sits at chunk (c ^ ((r >> 1) & 7)) so that the 16 rows a quarter-wave reads hit all 64 banks.
 // T = bf16 bits (uint16_t) or float.
 // ------------------------------------------------------------------------------------------------
-constexpr int TV = 64;
 constexpr int TR = 128;
 constexpr int SLAB_BYTES = 128;
-constexpr int A_BYTES = TV * SLAB_BYTES;      // the weight tile of one slab in LDS (8 KiB)
-constexpr int B_BYTES = TR * SLAB_BYTES;      // the hidden rows (16 KiB)
-constexpr int NI = TV / 64, NA = TV / 32;     // MFMA blocks of a wave along the vocabulary; rows a thread stages
+constexpr int B_BYTES = TR * SLAB_BYTES;      // the hidden rows of one slab in LDS (16 KiB)
 constexpr int ROW_BLOCK = 8;                  // row tiles that an XCD walks together per strip
+
+// per build (TV = 64 or 128 columns):
+constexpr int weight_bytes(int tv) { return tv * SLAB_BYTES; }     // a tile's weight rows of one slab in LDS
+constexpr int blocks_v(int tv) { return tv / 64; }                 // MFMA blocks of a wave along the vocabulary
+constexpr int stage_rows(int tv) { return tv / 32; }               // weight rows that a thread stages
+constexpr int per_cu(int tv) { return tv == 64 ? 3 : 2; }          // workgroups that a CU's LDS and registers hold
 
 struct GeneralArgs {
   LogitsArgs base, hyper;
   int32_t hyper_grid;   // workgroups of the hyper part (the first ones), a multiple of 8
 };
 
-// The wave's two 32 x 32 blocks advance by one 16-byte chunk of K per lane.
-template <typename T>
-__device__ __forceinline__ void mfma_block(const f32x4 (&fa)[NI], const f32x4 (&fb)[2], f32x16 (&acc)[NI][2]);
-
-template <>
-__device__ __forceinline__ void mfma_block<uint16_t>(const f32x4 (&fa)[NI], const f32x4 (&fb)[2], f32x16 (&acc)[NI][2]) {
-#pragma unroll
-  for (int i = 0; i < NI; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[i]), __builtin_bit_cast(bf16x8, fb[j]),
-                                                          acc[i][j], 0, 0, 0);
-}
-
-template <>
-__device__ __forceinline__ void mfma_block<float>(const f32x4 (&fa)[NI], const f32x4 (&fb)[2], f32x16 (&acc)[NI][2]) {
-  // a 16-byte chunk holds 4 consecutive k; lanes 0-31 and 32-63 hold different chunks, and the
-  // pairing of k between the two operands is the same, so any order of the 4 steps is a valid sum
-#pragma unroll
-  for (int e = 0; e < 4; ++e)
+// The wave's NI x 2 blocks of 32 x 32 advance by one 16-byte chunk of K per lane.
+template <typename T, int NI>
+__device__ __forceinline__ void mfma_block(const f32x4 (&fa)[NI], const f32x4 (&fb)[2], f32x16 (&acc)[NI][2]) {
+  if constexpr (sizeof(T) == 2) {
 #pragma unroll
     for (int i = 0; i < NI; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][e], fb[j][e],
-                                                         acc[i][j], 0, 0, 0);
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[i]), __builtin_bit_cast(bf16x8, fb[j]),
+                                                            acc[i][j], 0, 0, 0);
+  } else {
+    // a 16-byte chunk holds 4 consecutive k; lanes 0-31 and 32-63 hold different chunks, and the
+    // pairing of k between the two operands is the same, so any order of the 4 steps is a valid sum
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][e], fb[j][e],
+                                                           acc[i][j], 0, 0, 0);
+  }
 }
 
 // Waves of the workgroup meet.  (Not __syncthreads, which would wait for the next slab's loads as well.)
@@ -77,8 +77,8 @@ __device__ __forceinline__ void meet() {
   asm volatile("" ::: "memory");
 }
 
-// Fold the wave's 32 x 64 logits into the running triples (and store them).  TAIL: the tile has columns that do not exist.
-template <bool STORE, bool TAIL>
+// Fold the wave's 32 NI x 64 logits into the running triples (and store them).  TAIL: the tile has columns that do not exist.
+template <bool STORE, bool TAIL, int NI>
 __device__ __forceinline__ void fold_general(const f32x16 (&acc)[NI][2], Triple (&run)[2], const LogitsArgs& a, int row0,
                                              int r_end, int col_base, int n_valid) {
 #pragma unroll
@@ -116,13 +116,14 @@ __device__ __forceinline__ void fold_general(const f32x16 (&acc)[NI][2], Triple 
   }
 }
 
-template <typename T, bool STORE>
-__global__ void __launch_bounds__(256, 3) logits_general_kernel(GeneralArgs g) {
+template <typename T, int TV, bool STORE>
+__global__ void __launch_bounds__(256, per_cu(TV)) logits_general_kernel(GeneralArgs g) {
+  constexpr int A_BYTES = weight_bytes(TV), NI = blocks_v(TV), NA = stage_rows(TV);
   __shared__ __align__(16) unsigned char lds[2 * (A_BYTES + B_BYTES)];   // [buf][A|B]
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int wv = wave & 1;    // which 32 vocabulary rows of the tile
+  const int wv = wave & 1;    // which half of the tile's vocabulary rows
   const int wr = wave >> 1;   // which 64 hidden rows of the tile
 
   // ---- which part, rows, W, strip -----------------------------------------------------------------
@@ -170,7 +171,7 @@ __global__ void __launch_bounds__(256, 3) logits_general_kernel(GeneralArgs g) {
   for (int i = 0; i < 4; ++i) off_b[i] = (uint32_t)min((tid >> 3) + 32 * i, r_end - 1 - r0) * row_bytes + my_k;
   // (the swizzle of row + 32 i is the row's own)
   const int lds_at = (tid >> 3) * SLAB_BYTES + (((tid & 7) ^ ((tid >> 4) & 7)) << 4);
-  // operand reads: row = 32 wv (weights) or 64 wr (hidden rows) + 32 i + (lane & 31), chunk 2 q + (lane >> 5)
+  // operand reads: row = TV / 2 wv (weights) or 64 wr (hidden rows) + 32 i + (lane & 31), chunk 2 q + (lane >> 5)
   const int rd_a = (wv * (TV / 2) + (lane & 31)) * SLAB_BYTES;
   const int rd_b = A_BYTES + (wr * 64 + (lane & 31)) * SLAB_BYTES;
   const int swz = (lane >> 1) & 7;
@@ -235,23 +236,23 @@ __global__ void __launch_bounds__(256, 3) logits_general_kernel(GeneralArgs g) {
       const int buf = slab & 1;
       const bool more = slab + 1 < n_slabs;
       read(fa[1], fb[1], buf, 1);
-      mfma_block<T>(fa[0], fb[0], acc);
+      mfma_block<T, NI>(fa[0], fb[0], acc);
       read(fa[0], fb[0], buf, 2);
       if (more) {
         stash(buf ^ 1);       // (its last readers had their fragments ahead of the barrier before)
         if (slab + 2 < n_slabs) fetch(slab + 2);
       }
-      mfma_block<T>(fa[1], fb[1], acc);
+      mfma_block<T, NI>(fa[1], fb[1], acc);
       read(fa[1], fb[1], buf, 3);
-      mfma_block<T>(fa[0], fb[0], acc);
+      mfma_block<T, NI>(fa[0], fb[0], acc);
       if (more) {
         meet();
         read(fa[0], fb[0], buf ^ 1, 0);
       }
-      mfma_block<T>(fa[1], fb[1], acc);
+      mfma_block<T, NI>(fa[1], fb[1], acc);
     }
 
-    // ---- epilogue of this tile: fold the 64 x 128 logits into the running triples -------------
+    // ---- epilogue of this tile: fold its logits into the running triples ----------------------
     const int col_base = v0 + wv * (TV / 2) + (lane >> 5) * 4;
     const int row0 = r0 + wr * 64 + (lane & 31);
     if (v0 + TV <= n_valid)
@@ -293,22 +294,33 @@ __global__ void __launch_bounds__(256, 3) logits_general_kernel(GeneralArgs g) {
 
 }  // namespace
 
-// One launch for both parts; hyper == nullptr: no hyper vocabulary.
-int z2z_launch_logits_general(bool bf16, const LogitsArgs& base, const LogitsArgs* hyper, hipStream_t s) {
+// Columns of a tile, by the workgroups that tiles of 64 columns would make (128 rows each, base and hyper).  fp32: 64.  bf16 is bound
+// by LDS reads and epilogues more than by its matrix instructions: 128, whose fragments serve twice the products, unless tiles of
+// 64 fill no more than one round of the CUs' three.  Whole calls in us, bf16, 64 / 128 columns: with the logits stored 256 rows x
+// 128256, d = 4096 526 / 451; 700 x 151936, d = 3584 1480 / 1290; 128 x 50257, d = 768 52.0 / 46.8 (786 tiles); 64 x 32000, d = 1024
+// 34.6 / 37.3 (500); picks alone, d = 1000, 2048 x 32000 236 / 196, 300 rows 56.0 / 51.3, 64 rows 27.7 / 29.8; d = 520, 100 x 5000 14.0 / 16.4.
+int z2z_logits_general_columns(bool bf16, long long tiles_of_64) { return bf16 && tiles_of_64 > 3 * 256 ? 128 : 64; }
+
+// One launch for both parts, tiles of `columns` columns; hyper == nullptr: no hyper vocabulary.
+int z2z_launch_logits_general(bool bf16, int columns, const LogitsArgs& base, const LogitsArgs* hyper, hipStream_t s) {
   GeneralArgs g;
   g.base = base;
   g.hyper = hyper ? *hyper : base;
   g.hyper_grid = hyper ? (hyper->n_work + 7) / 8 * 8 : 0;
   const dim3 grid((unsigned)g.hyper_grid + (unsigned)((base.n_work + 7) / 8 * 8)), block(256);
   const bool store = base.logits != nullptr;
-  if (bf16 && store)
-    hipLaunchKernelGGL((logits_general_kernel<uint16_t, true>), grid, block, 0, s, g);
+  if (bf16 && columns == 128 && store)
+    hipLaunchKernelGGL((logits_general_kernel<uint16_t, 128, true>), grid, block, 0, s, g);
+  else if (bf16 && columns == 128)
+    hipLaunchKernelGGL((logits_general_kernel<uint16_t, 128, false>), grid, block, 0, s, g);
+  else if (bf16 && store)
+    hipLaunchKernelGGL((logits_general_kernel<uint16_t, 64, true>), grid, block, 0, s, g);
   else if (bf16)
-    hipLaunchKernelGGL((logits_general_kernel<uint16_t, false>), grid, block, 0, s, g);
+    hipLaunchKernelGGL((logits_general_kernel<uint16_t, 64, false>), grid, block, 0, s, g);
   else if (store)
-    hipLaunchKernelGGL((logits_general_kernel<float, true>), grid, block, 0, s, g);
+    hipLaunchKernelGGL((logits_general_kernel<float, 64, true>), grid, block, 0, s, g);
   else
-    hipLaunchKernelGGL((logits_general_kernel<float, false>), grid, block, 0, s, g);
+    hipLaunchKernelGGL((logits_general_kernel<float, 64, false>), grid, block, 0, s, g);
   Z2Z_HIP_TRY(hipGetLastError());
   return Z2Z_OK;
 }

@@ -1,7 +1,7 @@
 """GPU parity of the general tile kernel of extended_logits (fp32, and bf16 shapes the other kernels do not take), with
 and without the full-logits output: section 2.3, steps 7-9.
 
-Shapes sit at the edges of its tiles (128 x 128), of its blocks of eight row tiles, of a K slab (32 floats or 64
+Shapes sit at the edges of its tiles (128 rows x 64 columns, 128 columns in bf16 where those of 64 would be more than 768), of its blocks of eight row tiles, of a K slab (32 floats or 64
 bf16) and of a vocabulary tile; both instances must leave the same picks and maxima."""
 import numpy as np
 import pytest
@@ -21,6 +21,9 @@ pytestmark = pytest.mark.gpu
     ("f32", 3, 128, 2049, 64, 0),       # no hyper part; whole slabs
     ("bf16", 2, 200, 700, 72, 150),     # d no multiple of 64
     ("bf16", 1, 1, 50, 8, 5),           # a single row
+    ("bf16", 2, 700, 4353, 200, 300),   # 759 tiles of 64 columns, 819 with the hyper part: 128 columns, one in the last tile; a part of a slab
+    ("bf16", 1, 129, 24512, 64, 0),     # 766: the most (an even number) that stay at 64; a second row tile with one row
+    ("bf16", 1, 129, 24577, 64, 0),     # 770; one slab; strips of one tile
     ("f32", 2, 130, 65, 68, 66),        # tiles with one and two columns behind a whole one; two K slabs and a chunk
     ("f32", 1, 300, 6400, 32, 64),      # one slab: nothing is fetched ahead; strips of one tile
 ])
