@@ -116,9 +116,10 @@ __device__ __forceinline__ void fold_tile_impl(const f32x16 (&acc)[NI][NJ], Trip
         run[j].m = gmax;
         run[j].i = col0 + col_base + i * 32 + (targ >> 2) * 8 + (targ & 3);
       }
-      if (!TAIL || run[j].m != kNegInf) {
-        // (without a tail every logit is finite, so the running maximum is finite from the first block on)
-        const float m2 = -run[j].m * kLog2e;
+      if (!TAIL || col_base + i * 32 < n_valid) {
+        // (where nothing has been above -inf yet, columns that do not exist add 0 and a hidden row's NaN stay NaN; without a tail
+        // every logit is finite or NaN, and so is the sum)
+        const float m2 = TAIL && run[j].m == kNegInf ? 0.f : -run[j].m * kLog2e;
         float add0 = 0.f, add1 = 0.f;
 #pragma unroll
         for (int v = 0; v < 16; v += 2) {

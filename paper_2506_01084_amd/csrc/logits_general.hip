@@ -106,10 +106,12 @@ __device__ __forceinline__ void fold_general(const f32x16 (&acc)[NI][2], Triple 
         run[j].m = gmax;
         run[j].i = a.col0 + col_base + i * 32 + (targ >> 2) * 8 + (targ & 3);
       }
-      if (run[j].m != kNegInf) {
+      if (col_base + i * 32 < n_valid) {
+        // (where nothing has been above -inf yet, columns that do not exist add 0 and a hidden row's NaN stay NaN)
+        const float m = run[j].m == kNegInf ? 0.f : run[j].m;
         float add = 0.f;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) add += __expf(x[v] - run[j].m);
+        for (int v = 0; v < 16; ++v) add += __expf(x[v] - m);
         run[j].s += add;
       }
     }

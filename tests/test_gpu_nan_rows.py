@@ -45,6 +45,10 @@ def _check(H, run):
     ("bf16", 1, 300, 600, 64, 300, True),       # ... for both parts; a last tile that is partly there
     ("bf16", 2, 150, 5, 64, 3, True),           # ... and nothing but partial groups of columns
     ("bf16", 2, 20, 600, 64, 40, False),        # weight-streaming kernel
+    ("bf16", 2, 20, 5, 64, 40, False),          # ... a partial group of columns
+    ("f32", 2, 20, 600, 36, 40, False),         # general kernel
+    ("f32", 2, 20, 3, 36, 40, True),            # ... partial groups of columns
+    ("bf16", 2, 400, 9000, 72, 40, False),      # ... tiles of 128 columns
 ])
 def test_log_sum_exp(dtype, B, rows_per_seq, V, d, cap, fill):
     import torch
