@@ -658,7 +658,8 @@ __device__ __forceinline__ void truncated_row(const TruncArgs& a, const float* p
   best = block_best(best, misc + 8);
   if (tid == 0) {
     a.token[r] = best.i;
-    if (a.logprob) a.logprob[r] = (best.z - m * inv_t) - logf(st->kept_mass);
+    // (nothing drawn: a row of NaN, whose maximum and masses read as those of a row without columns)
+    if (a.logprob) a.logprob[r] = best.i == kNoColumn ? NAN : (best.z - m * inv_t) - logf(st->kept_mass);
   }
 }
 

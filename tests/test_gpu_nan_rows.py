@@ -67,22 +67,24 @@ def test_log_sum_exp(dtype, B, rows_per_seq, V, d, cap, fill):
     ctx.close()
 
 
-@pytest.mark.parametrize("B,V,d", [
-    (2, 600, 128),          # decode kernel
-    (5, 65281, 128),        # weight-streaming kernel, sums in levels; a last tile of one column
-    (70, 600, 128),         # weight-streaming kernel
-    (200, 600, 128),        # tile kernel
-    (200, 3, 128),          # ... one partial group of columns
+@pytest.mark.parametrize("B,V,d,top_k,top_p", [
+    (2, 600, 128, 0, 1.0),          # decode kernel
+    (5, 65281, 128, 0, 1.0),        # weight-streaming kernel, sums in levels; a last tile of one column
+    (70, 600, 128, 0, 1.0),         # weight-streaming kernel
+    (200, 600, 128, 0, 1.0),        # tile kernel
+    (200, 3, 128, 0, 1.0),          # ... one partial group of columns
+    (2, 600, 128, 50, 0.9),         # filtered: a short list, then the row's passes in the same launch
+    (5, 65281, 128, 0, 0.9),        # ... the passes in launches of their own
 ])
-def test_log_probability(B, V, d):
+def test_log_probability(B, V, d, top_k, top_p):
     import torch
 
-    print(f"[case] draws of {B} sequences, V={V} d={d}", flush=True)
+    print(f"[case] draws of {B} sequences, V={V} d={d} top_k={top_k} top_p={top_p}", flush=True)
     ctx, E, W, H = _setup(B, 1, V, d, 40, "bf16")
 
     def run(h):
         token, lp = torch.full((B,), -5, dtype=torch.int32, device="cuda"), torch.zeros(B, device="cuda")
-        ctx.extended_sample(h, 1, E, W, 0.8, 77, 5, token, lp)
+        ctx.extended_sample(h, 1, E, W, 0.8, 77, 5, token, lp, top_k=top_k, top_p=top_p)
         torch.cuda.synchronize()
         return token, lp
 
