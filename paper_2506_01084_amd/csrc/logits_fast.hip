@@ -502,6 +502,42 @@ __device__ __forceinline__ void store_prob16(const Acc& acc, const LogitsArgs& a
   }
 }
 
+// Lanes that hold the same rows, 16 or 32 apart, exchange halves: of a[k] and a[k + N] the lower lane of a pair keeps row k
+// and the upper one row k + N, each with both lanes' values.
+struct Swap16 {
+  __device__ __forceinline__ void operator()(uint32_t& x, uint32_t& y) const {
+    const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    x = r[0];
+    y = r[1];
+  }
+};
+struct Swap32 {
+  __device__ __forceinline__ void operator()(uint32_t& x, uint32_t& y) const {
+    const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+    x = r[0];
+    y = r[1];
+  }
+};
+__device__ __forceinline__ void merge(Triple& a, const Triple& b) { merge_triple(a, b); }
+__device__ __forceinline__ void merge(Draw& a, const Draw& b) { merge_draw(a, b); }
+
+template <int N, typename R, typename S>
+__device__ __forceinline__ void merge_rows(R (&a)[F_N], S swap) {
+  static_assert(sizeof(R) == 12, "three words");
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    uint32_t x[3], y[3];
+    __builtin_memcpy(x, &a[k], 12);
+    __builtin_memcpy(y, &a[k + N], 12);
+#pragma unroll
+    for (int w = 0; w < 3; ++w) swap(x[w], y[w]);
+    R other;
+    __builtin_memcpy(&a[k], x, 12);
+    __builtin_memcpy(&other, y, 12);
+    merge(a[k], other);
+  }
+}
+
 // MODE 8 and 9 are measurement probes of the base part (their results are NOT the logits' reduction): 8 stops
 // requesting operands after the first two slabs (the matrix cores, the LDS reads and the fold run as usual on
 // those two slabs' values), 9 also stops reading LDS and folds once per strip -- the MFMA stream alone.  They
@@ -777,52 +813,44 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
     }
     if (MODE >= 2 && MODE <= 5) continue;
     // ---- end of strip: the four quarter-waves hold the same hidden rows; then the two vocabulary halves ------
-#pragma unroll
-    for (int i = 0; i < F_N; ++i) {
-#pragma unroll
-      for (int off = 16; off <= 32; off <<= 1) {
-        Triple o;
-        o.m = __shfl_xor(run[i].m, off);
-        o.s = __shfl_xor(run[i].s, off);
-        o.i = __shfl_xor(run[i].i, off);
-        merge_triple(run[i], o);
-        if (MODE == 6) {
-          Draw od;
-          od.v = __shfl_xor(draw[i].v, off);
-          od.l = __shfl_xor(draw[i].l, off);
-          od.i = __shfl_xor(draw[i].i, off);
-          merge_draw(draw[i], od);
-        }
-      }
+    // (each exchange halves a lane's rows: 6 merges and no shuffles, where every row merged in all lanes took 16 and 48 and three
+    // lanes in four idled behind them.  32000 columns, 300 / 3500 rows, d = 64 33.1 -> 28.2, 92.4 -> 80.1 us, d = 1024 66.0 -> 61.4,
+    // 246.9 -> 232.4)
+    merge_rows<4>(run, Swap16{});
+    merge_rows<2>(run, Swap32{});
+    if (MODE == 6) {
+      merge_rows<4>(draw, Swap16{});
+      merge_rows<2>(draw, Swap32{});
     }
+    // (now lane l holds rows (l & 15) + 16 (4 (bit 4 of l) + 2 (bit 5) + e), e = 0, 1)
+    const int hrow0 = wr * 128 + (lane & 15) + 16 * (4 * ((lane >> 4) & 1) + 2 * (lane >> 5));
     // (one barrier: the next strip's writes lie behind the barriers of its slabs, and these reads ahead of them)
     Triple* xch = reinterpret_cast<Triple*>(lds + F_LDS_STAGES);    // [256 hidden rows of the tile]
     Draw* xdr = reinterpret_cast<Draw*>(xch + FT);
-    const int hrow0 = wr * 128;
-    if (wv == 1 && lane < 16) {
+    if (wv == 1) {
 #pragma unroll
-      for (int i = 0; i < F_N; ++i) {
-        xch[hrow0 + i * 16 + lane] = run[i];
-        if (MODE == 6) xdr[hrow0 + i * 16 + lane] = draw[i];
+      for (int e = 0; e < 2; ++e) {
+        xch[hrow0 + e * 16] = run[e];
+        if (MODE == 6) xdr[hrow0 + e * 16] = draw[e];
       }
     }
     barrier_after_lds();
-    if (wv == 0 && lane < 16) {
+    if (wv == 0) {
 #pragma unroll
-      for (int i = 0; i < F_N; ++i) {
-        merge_triple(run[i], xch[hrow0 + i * 16 + lane]);
-        const int hrow = r0 + hrow0 + i * 16 + lane;
+      for (int e = 0; e < 2; ++e) {
+        merge_triple(run[e], xch[hrow0 + e * 16]);
+        const int hrow = r0 + hrow0 + e * 16;
         if (hrow < r_end) {
           const size_t p = (size_t)hrow * a.n_parts + a.part0 + st;
-          a.part_m[p] = run[i].m;
-          a.part_s[p] = run[i].s;
+          a.part_m[p] = run[e].m;
+          a.part_s[p] = run[e].s;
           if (MODE == 6) {
-            merge_draw(draw[i], xdr[hrow0 + i * 16 + lane]);
-            a.part_v[p] = draw[i].v;
-            a.part_l[p] = draw[i].l;
-            a.part_i[p] = draw[i].i;
+            merge_draw(draw[e], xdr[hrow0 + e * 16]);
+            a.part_v[p] = draw[e].v;
+            a.part_l[p] = draw[e].l;
+            a.part_i[p] = draw[e].i;
           } else {
-            a.part_i[p] = run[i].i;
+            a.part_i[p] = run[e].i;
           }
         }
       }
