@@ -1,5 +1,5 @@
 // extended_logits, base-vocabulary part for up to 192 hidden rows in all (gfx950, bf16, d a multiple of 64): a
-// decode step of 65..192 sequences, a greedy one of 5..64 where the tiles fill the CUs, a few rows per sequence at a
+// decode step of 65..192 sequences, one of 5..64 where the tiles fill the CUs (greedy or a draw), a few rows per sequence at a
 // small batch, a short chunk; dense layers on up to 128 rows.  (zip2zip paper, section 2.3, steps 7-9.)
 //
 // With so few rows the part is bound by the bytes of W_base, like the one-row-per-sequence step.  That kernel's
@@ -89,13 +89,12 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
   constexpr int STAGES = mid_stages(NJV), RING = mid_ring(NJV);
   constexpr int STAGE = 32 * NJV * M_SLAB, STAGE_BYTES = STAGES * STAGE;
   constexpr int W_SLAB = 32 * M_SLAB;                      // a wave's weights of one slab
-  const int vt = blockIdx.x;                               // weight tile
-  const int r0 = 0;                                        // (one row tile: the call has at most M_HT rows)
+  const int vt = blockIdx.x;                               // weight tile (and one row tile: a call has at most M_HT rows)
   // SMODE 3 (a dense layer's partial sums): the rows that exist may be known on the device only, and blockIdx.y is
   // the part of K this workgroup takes (slabs [ks * slabs_per_part, ...))
   const int r_end = (SMODE == 3 && a.rows_dev) ? min(a.rows, *a.rows_dev) : a.rows;
-  if (r_end <= r0) return;                                 // (the whole workgroup)
-  const int nr = min(32 * NJV, r_end - r0);                // valid hidden rows
+  if (r_end <= 0) return;                                  // (the whole workgroup)
+  const int nr = min(32 * NJV, r_end);                     // valid hidden rows
   const int n_valid = a.w_rows;
   const int v0 = vt * M_WT;
   const size_t row_bytes = (size_t)a.d * 2;
@@ -106,12 +105,9 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
   // The tiles walk K in the same order but start at different slabs (tile t at slab t mod n_slabs, wrapping round):
   // at any moment the workgroups in flight ask for different 128-byte columns of their weight rows, not all for
   // the same one, which would keep landing on the same few memory channels (rows are a power of two apart).
-#ifndef M_ROTATE
-#define M_ROTATE 1
-#endif
-  const int rot = M_ROTATE ? vt % n_slabs : 0;
-  auto slab_at = [&](int s) {                              // step -> slab (steps past the end repeat the last one)
-    const int x = min(s, n_slabs - 1) + rot;
+  const int rot = vt % n_slabs;
+  auto slab_at = [&](int s) {                              // step -> slab
+    const int x = s + rot;
     return slab0 + (x >= n_slabs ? x - n_slabs : x);
   };
   // weights through the wave's own ring: its 32 rows in four requests of 8 whole lines, laid out as the hidden rows are
@@ -139,7 +135,7 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
   // 128 LDS bytes: chunk (l & 7) ^ ((row >> 1) & 7).  Rows past the last valid one read the last valid one.
   constexpr int HL = (4 * NJV) / M_WAVES;                  // requests per wave and slab
   static_assert(HL * M_WAVES == 4 * NJV, "whole groups per wave");
-  const unsigned char* Ht = reinterpret_cast<const unsigned char*>(a.H) + (size_t)r0 * row_bytes;
+  const unsigned char* Ht = reinterpret_cast<const unsigned char*>(a.H);
   const uint32_t lds_base = lds_offset_of(lds);
   uint32_t hsrc[HL];
 #pragma unroll
@@ -256,10 +252,7 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
     wait_loads<0>();
     next_step();
   }
-  // the requests past the end of the stream (slabs clamped onto the last one) must land before the stages are reused
-  wait_loads<0>();
-  __syncthreads();
-
+  // (the last step ended with a wait for all requests and a barrier: the stages and rings are free)
   if (LEVELS) {
     next_level();
     third_level();
@@ -278,13 +271,13 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
   const int col_base = v0 + wave * 32 + half * 4;
   if (SMODE == 3) {
     // a dense layer's K part: the fp32 tile as it is; linear_sum_kernel adds the parts and runs the layer's epilogue
-    store_partial_tile<1, NJV>(acc, a.partial + (size_t)ks * a.rows * a.ldo, a.ldo, r0, r_end, col_base, n_valid);
+    store_partial_tile<1, NJV>(acc, a.partial + (size_t)ks * a.rows * a.ldo, a.ldo, 0, r_end, col_base, n_valid);
     return;
   }
   if (SMODE == 1 || SMODE == 5)
-    fold_tile_sample<1, NJV>(acc, run, draw, a, r0, col_base, n_valid);
+    fold_tile_sample<1, NJV>(acc, run, draw, a, 0, col_base, n_valid);
   else if (SMODE == 2 || SMODE == 6)
-    fold_tile_store<1, NJV>(acc, run, a, r0, r_end, col_base, n_valid);
+    fold_tile_store<1, NJV>(acc, run, a, 0, r_end, col_base, n_valid);
   else
     fold_tile<1, NJV>(acc, run, col_base, a.col0, n_valid, v0 + M_WT > n_valid);
 #pragma unroll
@@ -316,7 +309,7 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
     Triple t = xch[tid];
 #pragma unroll
     for (int w = 1; w < M_WAVES; ++w) merge_triple(t, xch[w * M_HT + tid]);
-    const size_t p = (size_t)(r0 + tid) * a.n_parts + a.part0 + vt;
+    const size_t p = (size_t)tid * a.n_parts + a.part0 + vt;
     a.part_m[p] = t.m;
     a.part_s[p] = t.s;
     if (SMODE == 1 || SMODE == 5) {
@@ -366,9 +359,9 @@ int z2z_launch_logits_mid(z2z_ctx* c, LogitsArgs a, const void* W, int w_rows, i
   // (two workgroups of the 64-row build per weight tile for 65..128 rows, sharing the tile's weights through an
   // XCD's L2, measured slower than one of the 128-row build: 383 against 293 us at config 2's shape)
   const dim3 grid((unsigned)a.n_vtiles), block(M_THREADS);
-  // builds: 2, 4 or 6 blocks of 32 hidden rows; the sampling calls come with one row per sequence and more than 64
-  // of them.  (8 blocks, up to 256 rows, leave the registers for four buffers at most and measured level with the
-  // tile kernel: 650 against 645 us for a decode step of 256 sequences.)
+  // builds: 2, 4 or 6 blocks of 32 hidden rows; the sampling calls come with one row per sequence.  (8 blocks, up to 256
+  // rows, measured level with the tile kernel when weights still went through registers: 650 against 645 us for a decode step of
+  // 256 sequences.)
   const int blocks = a.rows <= 64 ? 2 : (a.rows <= 128 ? 4 : 6);
   if (a.sample == 1) {
     if (blocks == 2)
