@@ -78,8 +78,9 @@ def test_general_kernel(dtype, B, rows_per_seq, V, d, cap):
 
 
 def test_strips_lengthen_where_the_static_array_would_not_hold_the_parts():
-    """32768 rows x 32769 columns: strips of 4 x 64 columns would leave 129 parts a row, more than 2^22 in all; every row against
-    float64 products (four terms each: 1e-6 of the largest logit)."""
+    """32768 rows x 32769 columns: strips of 4 x 64 columns would leave 129 parts a row, more than the static array's 2^22 in all
+    (Z2Z_ELIMIT).  Through the allocation-free entry point, every row against float64 products (four terms each: 1e-6 of the largest
+    logit); the allocating one cuts the same way: the same bits."""
     import torch
 
     from paper_2506_01084_amd import api
@@ -92,8 +93,13 @@ def test_strips_lengthen_where_the_static_array_would_not_hold_the_parts():
     W[-1] = 9.0                                   # the column of a tile of its own decides many rows
     am = torch.full((rows,), -5, dtype=torch.int32, device="cuda")
     mx, lse = torch.zeros(rows, device="cuda"), torch.zeros(rows, device="cuda")
-    ctx.extended_logits(H, rows, W, torch.zeros((1, 0, d), device="cuda"), am, mx, lse)
+    none = torch.zeros((1, 0, d), device="cuda")
+    ctx.extended_logits_static(H, rows, W, none, am, mx, lse)
+    grown = torch.full_like(am, -5), torch.zeros_like(mx), torch.zeros_like(lse)
+    ctx.extended_logits(H, rows, W, none, *grown)
     torch.cuda.synchronize()
+    for a, b in zip((am, mx, lse), grown):
+        assert torch.equal(a, b)
     for r in range(0, rows, 4096):
         z = H[r:r + 4096].double() @ W.double().t()
         top = z.topk(2, dim=1)

@@ -6,9 +6,9 @@ base and hyper vocabulary, the pick: section 2.3, steps 7-9.
 A call lands there when the context is bf16, d is a multiple of 64, no full-logits output is asked for and the
 call is not a decode step of at most 64 sequences; each test checks the library's launch counters.  Shapes span
 the three builds of the kernel (up to 64, 128 and 192 rows), a last weight tile with a single row, fewer K slabs than
-weight buffers, slab counts that are no multiple of the buffer count, more weight tiles than K slabs (the tiles
-start their walk over K at different slabs), and both ways of the hyper part (the decode kernel's units, the
-MFMA tile kernel).
+the weight rings have slots (four in the 64-row build, otherwise three), more weight tiles than K slabs (the tiles
+start their walk over K at different slabs), weights read past the caches (more than 128 MiB), and both ways of the
+hyper part (the decode kernel's units, the MFMA tile kernel).
 
 Bars as for the other logits tests: max and lse within 2e-2 * max(1, |ref|), argmax identical wherever the
 oracle's two largest logits differ by more than 1e-2 (elsewhere it must name a logit within that gap).
@@ -51,20 +51,22 @@ def _call(ctx, d_H, rows_per_seq, d_Wb, d_Wh):
 @pytest.mark.parametrize("B,rows_per_seq,V,d,M,cap,pool", [
     (65, 1, 1000, 128, 3, 300, "mean"),          # a decode step of 65 sequences: 128-row build, hyper on the decode units
     (128, 1, 777, 192, 3, 0, "mean"),            # 128 rows, no hyper vocabulary: three K slabs
-    (3, 2, 300, 64, 4, 40, "mean"),              # 6 rows, one K slab: 64-row build, fewer slabs than buffers
+    (3, 2, 300, 64, 4, 40, "mean"),              # 6 rows, one K slab: 64-row build, fewer slabs than ring slots
     (1, 100, 2500, 320, 4, 100, "weighted"),     # 100 rows of one sequence: five slabs, hyper on the tile kernel
     (4, 24, 513, 576, 3, 70, "mean"),            # 96 rows; nine slabs; V one row past two weight tiles
     (9, 7, 1300, 4096, 3, 257, "mean"),          # 63 rows, d = 4096: 64 slabs, 6 weight tiles
     (5, 3, 700, 448, 3, 100, "mean"),            # 15 rows, 7 slabs
     (2, 5, 5200, 256, 3, 30, "mean"),            # 10 rows, 4 slabs, 21 weight tiles: every starting slab several times
-    (1, 64, 255, 192, 3, 0, "mean"),             # 64 rows, 3 slabs: every step is one of those after the buffer loop
-    (1, 64, 700, 320, 3, 0, "mean"),             # 64 rows, 5 slabs (one fewer than buffers); three weight tiles
-    (2, 60, 300, 704, 3, 20, "mean"),            # 120 rows, 11 slabs: one round of the buffers and five steps after
+    (1, 64, 255, 192, 3, 0, "mean"),             # 64 rows, 3 slabs: every step is one of those behind the loop
+    (1, 64, 700, 320, 3, 0, "mean"),             # 64 rows, 5 slabs: two steps in the loop, three behind it; three weight tiles
+    (2, 60, 300, 704, 3, 20, "mean"),            # 120 rows, 11 slabs: three rounds of the ring in the loop, two steps behind it
     (64, 2, 20000, 4096, 3, 64, "mean"),         # 128 rows at the benchmark's width: 79 workgroups of 64 slabs
-    (130, 1, 777, 256, 3, 300, "mean"),          # a decode step of 130 sequences: 192-row build, four slabs (one round of its buffers)
-    (3, 60, 1500, 448, 4, 100, "weighted"),      # 180 rows, seven slabs: a round and three steps after
+    (130, 1, 777, 256, 3, 300, "mean"),          # a decode step of 130 sequences: 192-row build, two steps in the loop, two behind it
+    (3, 60, 1500, 448, 4, 100, "weighted"),      # 180 rows, seven slabs
     (192, 1, 513, 192, 3, 0, "mean"),            # 192 rows, three slabs: every row of the 192-row build valid
     (6, 30, 9000, 4096, 3, 40, "mean"),          # 180 rows at the benchmark's width
+    (6, 30, 16500, 4096, 3, 40, "mean"),         # 135 MB of weights: past the caches, in the 192-row build
+    (5, 20, 16500, 4096, 3, 40, "mean"),         # ... in the 128-row build
 ])
 def test_streaming_kernel_every_row_ragged(B, rows_per_seq, V, d, M, cap, pool):
     import torch

@@ -1,7 +1,7 @@
-"""GPU parity of greedy decode steps of 5..64 sequences over a vocabulary of at least 65281 columns (256 tiles; with more
-than 16 sequences only where the rounds of 256 tiles are 7/8 full, or hyper units would open another): the base part on
-the weight-streaming kernel (sums in three levels), the hyper units alone, in units of 64..512 rows.  Section 2.3, steps
-7-9.
+"""GPU parity of decode steps of 5..64 sequences over a vocabulary of at least 65281 columns (256 tiles; with more
+than 16 sequences only where there are more than 512 tiles, or the rounds of 256 tiles are 7/8 full, or hyper units would
+open another): the base part on the weight-streaming kernel (sums in three levels), the hyper units alone, in units of
+64..512 rows.  Section 2.3, steps 7-9.
 
 Bound of the largest logit: fp32 sums of d products, 8 at most in one run of the accumulators: 1e-5 of its size."""
 import numpy as np
@@ -16,9 +16,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("B,V,d,cap,split", [
-    (5, 65281, 128, 40, 1),       # two slabs: fewer than buffers; one unit per sequence
-    (9, 65290, 768, 700, 1),      # twelve slabs: two rounds of the buffers, one flush of the second level
-    (33, 65500, 1664, 100, 1),    # 26 slabs: four rounds and two steps
+    (5, 65281, 128, 40, 1),       # two slabs: fewer than the ring's slots; one unit per sequence
+    (9, 65290, 768, 700, 1),      # twelve slabs: the second level is flushed at the end alone
+    (33, 65500, 1664, 100, 1),    # 26 slabs: the second level is flushed after 16 and at the end
     (64, 65281, 256, 520, 1),     # every row valid; nine units of 64 per sequence
     (4, 65281, 128, 40, 0),       # (four sequences stay on the dot-product units)
     (4, 65500, 1152, 40, 0),      # (... past the caches with more than 128 MB of weights)
@@ -27,6 +27,7 @@ pytestmark = pytest.mark.gpu
     (17, 66000, 128, 40, 0),
     (17, 114433, 128, 40, 1),     # 448 tiles of 512
     (17, 114432, 128, 40, 0),     # 447
+    (17, 131073, 128, 40, 1),     # 513: a third round, nearly empty
     (32, 66000, 128, 4000, 1),    # 258 tiles and 256 hyper units
 ])
 def test_split_step(B, V, d, cap, split):
@@ -74,6 +75,8 @@ def test_split_step(B, V, d, cap, split):
     (9, 65290, 768, 700, 50, 0.9),
     (32, 65281, 1152, 40, 50, 0.9),     # (one block of rows: the second is left out)
     (64, 65500, 256, 100, 0, 0.8),
+    (17, 131073, 128, 40, 0, 1.0),      # 513 tiles
+    (33, 131073, 128, 40, 50, 0.9),
 ])
 def test_split_draws_match_one_launch(B, V, d, cap, top_k, top_p):
     """Draws of a split step against those of the decode kernel in one launch (both oracle-tested on smaller vocabularies):
