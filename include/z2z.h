@@ -372,7 +372,8 @@ enum {
                                   3 = the MFMA stream alone (no requests, no LDS reads, one fold per strip);
                                   4 = the bf16 MFMA tile kernel also for the base part of calls with at most
                                   192 hidden rows, which otherwise goes to the weight-streaming kernel */
-  Z2Z_OPT_LOGITS_STRIP = 2,    /* vocabulary tiles swept per workgroup, 0 = automatic               */
+  Z2Z_OPT_LOGITS_STRIP = 2,    /* vocabulary swept per workgroup, in units of 256 columns (bf16 MFMA tile
+                                  kernel) or 128 (general kernel, whatever its tile); 0 = automatic  */
   Z2Z_OPT_LZW_KERNEL = 3,      /* 0 = automatic, >0 = force a variant (2: table in global memory, 3: one
                                   code per step in the decoder, 4: one wave per sequence) */
   Z2Z_OPT_DECODE_KERNEL = 4,   /* 0 = automatic, >0 = force a variant                               */

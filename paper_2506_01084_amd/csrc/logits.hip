@@ -331,17 +331,32 @@ static int pick_strip_for(const z2z_ctx* c, long long row_tiles, int n_vt, int w
 // A decode step of 5..64 sequences whose base vocabulary goes to the weight-streaming kernel, with the hyper units in a
 // launch of their own, instead of the decode kernel's base and hyper units in one.  Either kernel has one tile of 256 weight
 // rows per CU, so a last round of tiles that leaves CUs idle costs as much as a full one -- but in the decode kernel the
-// hyper units run there.  d = 4096 (V = 151936: 3584), hyper units of 1000 entries, cap = 1024, us, one launch -> split:
+// hyper units run there.  d = 4096 (V = 151936: 3584), cap = 1024, codebooks half full, us, one launch -> split, calls in a row:
 //   tiles (of the rounds')            8 sequences   24           40           64
-//   256 (V = 65536)         draw      205 -> 113    213 -> 131   220 -> 156   220 -> 183
-//   501 (of 512, 128256)    greedy    280 -> 180    287 -> 200   294 -> 217   300 -> 246
-//                           draw      315 -> 205    321 -> 224   325 -> 254   329 -> 284
-//                           filtered  305 -> 253    318 -> 266   327 -> 276   339 -> 285
-//   594 (of 768, 151936)    greedy    289 -> 207    270 -> 226   279 -> 243   299 -> 270
-//                           draw      292 -> 242    300 -> 262   307 -> 297   324 -> 323
-//                           filtered  286 -> 278    299 -> 295   314 -> 306   336 -> 317
+//   256 (V = 65536)         greedy    191 -> 103    201 -> 124   204 -> 142   203 -> 169
+//                           draw      211 -> 112    220 -> 130   224 -> 153   223 -> 180
+//                           filtered  208 -> 177    219 -> 183   228 -> 189   230 -> 198
+//   313 (of 512, 80000)     greedy    193 -> 154    207 -> 174   209 -> 193   224 -> 222
+//                           draw      214 -> 164    226 -> 186   228 -> 211   231 -> 240
+//                           filtered  212 -> 229    226 -> 235   234 -> 244   249 -> 253
+//   384 (of 512, 98304)     greedy    198 -> 159    216 -> 178   238 -> 197   238 -> 224
+//                           draw      218 -> 169    232 -> 187   245 -> 214   241 -> 244
+//                           filtered  217 -> 230    233 -> 243   259 -> 254   263 -> 264
+//   448 (of 512, 114688)    greedy    214 -> 162    242 -> 182   290 -> 202   303 -> 230
+//                           draw      233 -> 174    254 -> 192   320 -> 220   327 -> 251
+//                           filtered  235 -> 235    263 -> 251   319 -> 265   335 -> 276
+//   501 (of 512, 128256)    greedy    282 -> 180    289 -> 198   298 -> 217   307 -> 247
+//                           draw      316 -> 189    321 -> 209   326 -> 238   332 -> 270
+//                           filtered  305 -> 254    316 -> 268   326 -> 277   342 -> 288
+//   594 (of 768, 151936)    greedy    262 -> 208    270 -> 227   283 -> 246   305 -> 271
+//                           draw      294 -> 222    302 -> 243   310 -> 274   331 -> 303
+//                           filtered  288 -> 281    301 -> 297   316 -> 309   341 -> 319
+// Behind other work that has turned the caches over the one launch is 40-60 us slower and the split 2-5.
 // Hence: up to 16 sequences, or more than two rounds, or a last round at least 7/8 full over all rounds, or hyper units that
-// would open another round in one launch.  At most 256 tiles stay (V = 32064, 40 sequences, 203 -> 217 before the ring).
+// would open another round in one launch.  Fewer than 256 tiles stay in one launch.  (That line, and the 7/8 for greedy steps, are
+// from before the ring; now the split side has the smaller figures down to about 196 tiles -- V = 50176, greedy 124 -> 84,
+// 134 -> 102, 193 -> 122, 200 -> 152 -- and at 126, V = 32064, d = 3072, where the caches are cold: in a row 66 -> 65, 70 -> 80,
+// 78 -> 94, 93 -> 117, cold 99 -> 68, 111 -> 83, 128 -> 97, 150 -> 120.)
 static bool split_few(const z2z_ctx* c, int rows) {
   const long long tiles = z2z_logits_mid_tiles(c->cfg.V), slots = (tiles + 255) / 256 * 256;
   int base_columns, hyper_columns;
