@@ -331,7 +331,7 @@ static int pick_strip_for(const z2z_ctx* c, long long row_tiles, int n_vt, int w
 // A decode step of 5..64 sequences whose base vocabulary goes to the weight-streaming kernel, with the hyper units in a
 // launch of their own, instead of the decode kernel's base and hyper units in one.  Either kernel has one tile of 256 weight
 // rows per CU, so a last round of tiles that leaves CUs idle costs as much as a full one -- but in the decode kernel the
-// hyper units run there.  d = 4096 (V = 151936: 3584), cap = 1024, codebooks half full, us, one launch -> split, calls in a row:
+// hyper units run there.  d = 4096 (V = 151936: 3584), cap = 1024, codebooks full, us, one launch -> split, calls in a row:
 //   tiles (of the rounds')            8 sequences   24           40           64
 //   256 (V = 65536)         greedy    191 -> 103    201 -> 124   204 -> 142   203 -> 169
 //                           draw      211 -> 112    220 -> 130   224 -> 153   223 -> 180
