@@ -19,6 +19,8 @@
 // entry there when it fits.  Tokens and codes are staged in LDS a window ahead.
 #include "hyper_embed_common.h"
 
+#include <algorithm>
+
 #include <string.h>
 
 namespace {
@@ -38,6 +40,7 @@ struct LzwArgs {
   int32_t out_stride;
   int32_t* status;         // [B]
   int32_t lds_ef;          // decode, LDS variant: 1 = (length, first token) of the entries live in LDS too
+  int32_t by_length;       // window kernels: workgroups take the sequences longest first
   int32_t in_step;         // one-code-at-a-time decoder only: > 0 = row distance of `in` (else `stride`)
 };
 
@@ -319,6 +322,59 @@ __device__ __forceinline__ int call_length(const LzwArgs& a, int b) {
   return a.in_len ? min(max(__builtin_amdgcn_readfirstlane(a.in_len[b]), 0), a.stride) : a.stride;
 }
 
+// The sequence workgroup r of a window kernel works on.  With a few rounds of workgroups on every CU the last ones to
+// start decide when a call with ragged lengths ends, so they should be the shortest: the r-th in the order of 16 classes
+// of length, longest first, and inside a class in the order (wave, turn, lane) of the threads that look at the lengths.
+// Every workgroup finds its own (about 1 us of the 50 and more that a document takes; as a launch of its own it would be 5).
+// 2048 documents of 1024 to 4096 tokens, cap 2048: @@ -> @@ us.
+constexpr int kLengthBins = 16;
+struct BlockOrder {
+  int32_t bin[kLengthBins];
+  int32_t count[16];                           // of each wave, in the class that holds r
+  int32_t seq;
+};
+template <int NW>
+__device__ __forceinline__ int sequence_of_block(const LzwArgs& a, BlockOrder& sh) {
+  if (!a.by_length) return blockIdx.x;
+  constexpr int THREADS = NW * kWave;
+  const int B = gridDim.x, tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const float scale = (float)kLengthBins / ((float)a.stride + 1.0f);
+  auto bin_of = [&](int i) -> int {            // -1 past the end
+    if (i >= B) return -1;
+    const int len = min(max(a.in_len[i], 0), a.stride);
+    return kLengthBins - 1 - min((int)((float)len * scale), kLengthBins - 1);
+  };
+  if (tid < kLengthBins) sh.bin[tid] = 0;
+  __syncthreads();
+  for (int i = tid; i < B; i += THREADS) atomicAdd(&sh.bin[bin_of(i)], 1);
+  __syncthreads();
+  int mine = 0, rank = blockIdx.x;
+  while (mine < kLengthBins - 1 && rank >= sh.bin[mine]) rank -= sh.bin[mine++];
+  mine = __builtin_amdgcn_readfirstlane(mine);
+  rank = __builtin_amdgcn_readfirstlane(rank);
+  int count = 0;
+  for (int base = 0; base < B; base += THREADS) count += (int)__popcll(__ballot(bin_of(base + tid) == mine));
+  if (lane == 0) sh.count[w] = count;
+  __syncthreads();
+  for (int j = 0; j < w; ++j) rank -= sh.count[j];
+  if (rank >= 0 && rank < count) {
+    for (int base = 0; base < B; base += THREADS) {
+      const unsigned long long m = __ballot(bin_of(base + tid) == mine);
+      const int c = (int)__popcll(m);
+      if (rank < c) {
+        if (bin_of(base + tid) == mine && (int)__popcll(m & ((1ull << lane) - 1)) == rank) sh.seq = base + tid;
+        break;
+      }
+      rank -= c;
+    }
+  }
+  __syncthreads();
+  const int b = __builtin_amdgcn_readfirstlane(sh.seq);
+  __syncthreads();                             // (the kernel's own shared memory may lie over this)
+  return b;
+}
+
 // The skip function of one position or of a run of positions: byte s = state after it, for state s before it.
 struct SkipFn {
   uint32_t lo, hi;
@@ -422,11 +478,11 @@ struct RoundSet {
 };
 
 constexpr int kMaxWaves = 16;
-template <int NW>
+template <int NW, int SETS>
 struct EncShared {
   static constexpr int W = NW * kWave;       // positions of a window
   static constexpr int kSet = 4 * W;
-  uint32_t set[2][kSet];                     // edges proposed in an even / odd iteration
+  uint32_t set[SETS][kSet];                  // edges proposed (two sets: in an even / odd iteration)
   u64 key[W];
   u64 skip[kMaxWaves];                       // skip function of each wave's positions
   int32_t tok[2 * W];                        // ring of token classes: position p at p & (2 W - 1)
@@ -438,15 +494,15 @@ struct EncShared {
   int32_t last_code, last_len, last_end;     // the last phrase of the window
   uint16_t rank[W];                          // of the proposing starts
 };
-constexpr int kParseStaticLds = (int)sizeof(EncShared<kMaxWaves>) + 256;    // + alignment slack
 
-template <int NW, bool LDS, bool M4>
-__device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, EncShared<NW>& sh) {
+constexpr int kParseStaticLds = (int)sizeof(EncShared<kMaxWaves, 2>) + 256;    // + alignment slack
+
+template <int NW, int SETS, bool LDS, bool M4>
+__device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, int b, EncShared<NW, SETS>& sh) {
   constexpr int W = NW * kWave;
-  constexpr int kSet = EncShared<NW>::kSet, kRing = 2 * W;
+  constexpr int kSet = EncShared<NW, SETS>::kSet, kRing = 2 * W;
   typedef RoundSet<kSet> Set;
   const LzwState& st = a.st;
-  const int b = blockIdx.x;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -465,7 +521,7 @@ __device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, EncShared<N
 
   Table<LDS> t;
   table_open_all<LDS, W>(a, b, tid, reset, &t);
-  for (int i = tid; i < 2 * kSet; i += W) sh.set[0][i] = kRoundEmpty;
+  for (int i = tid; i < SETS * kSet; i += W) sh.set[0][i] = kRoundEmpty;
   // tokens: the ring holds [fill - kRing, fill); the next W of them wait in a register
   auto classify = [&](int32_t v) -> int32_t { return (v >= 0 && v < V) ? v : -2; };
   int fill = kRing;
@@ -573,8 +629,12 @@ __device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, EncShared<N
       if (lane == 0) sh.count[w] = (uint32_t)__popcll(start_mask) | ((uint32_t)__popcll(cand_mask) << 16);
       if (room <= 0) break;
       // ---- 3. proposals -------------------------------------------------------------------------------
-      uint32_t* set = sh.set[it & 1];
-      if (own >= 0) sh.set[(it + 1) & 1][own] = kRoundEmpty;     // the previous iteration's
+      uint32_t* set = sh.set[it & (SETS - 1)];
+      if (SETS == 1) {
+        if (it > 0) __syncthreads();                             // (emptied at the end of the previous iteration)
+      } else {
+        if (own >= 0) sh.set[(it + 1) & 1][own] = kRoundEmpty;   // the previous iteration's
+      }
       own = -1;
       if (cand) {
         own = Set::insert(set, sh.key, h, round_key(code, nxt), tid);
@@ -612,8 +672,9 @@ __device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, EncShared<N
       if (__ballot(ch) != 0 && lane == 0) sh.changed[it & 1] = 1;
       skip_functions();
       __syncthreads();
-      if (sh.changed[it & 1] == 0) {
-        if (own >= 0) set[own] = kRoundEmpty;
+      const bool settled = sh.changed[it & 1] == 0;
+      if (own >= 0 && (SETS == 1 || settled)) set[own] = kRoundEmpty;
+      if (settled) {
         break;
       }
     }
@@ -734,16 +795,17 @@ __device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, EncShared<N
 // A short appended call touches a handful of slots: probing the table where it lives, in global memory,
 // is cheaper than staging all of it in LDS and writing it back (the length is known only on the device,
 // so the LDS kernels take this decision per sequence).
-template <int NW, bool LDS>
+template <int NW, bool LDS, int SETS = 2>
 __global__ void __launch_bounds__(NW * kWave) lzw_encode_kernel(LzwArgs a) {
-  __shared__ EncShared<NW> sh;
-  const bool short_append = !(a.flags & Z2Z_RESET) && call_length(a, blockIdx.x) <= kShortAppend;
+  __shared__ EncShared<NW, SETS> sh;
+  const int b = sequence_of_block<NW>(a, reinterpret_cast<BlockOrder&>(sh));
+  const bool short_append = !(a.flags & Z2Z_RESET) && call_length(a, b) <= kShortAppend;
   if (LDS && short_append) {
-    lzw_encode_windows<NW, false, false>(a, sh);
+    lzw_encode_windows<NW, SETS, false, false>(a, b, sh);
   } else if (a.st.M <= 4) {
-    lzw_encode_windows<NW, LDS, true>(a, sh);
+    lzw_encode_windows<NW, SETS, LDS, true>(a, b, sh);
   } else {
-    lzw_encode_windows<NW, LDS, false>(a, sh);
+    lzw_encode_windows<NW, SETS, LDS, false>(a, b, sh);
   }
 }
 
@@ -977,17 +1039,16 @@ struct DecShared {
   int32_t last_code, last_len, last_tokens, last_made;
   uint16_t maker[W];                         // position of the code that makes entry `rank` of the round
 };
-static_assert(sizeof(DecShared<kMaxWaves>) <= sizeof(EncShared<kMaxWaves>), "one LDS budget for both directions");
+static_assert(sizeof(DecShared<kMaxWaves>) <= sizeof(EncShared<kMaxWaves, 2>), "one LDS budget for both directions");
 
 template <int NW, bool LDS, bool M4>
-__device__ __forceinline__ void lzw_decode_windows(const LzwArgs& a, DecShared<NW>& sh) {
+__device__ __forceinline__ void lzw_decode_windows(const LzwArgs& a, int b, DecShared<NW>& sh) {
   constexpr int W = NW * kWave;
   constexpr int kSet = DecShared<NW>::kSet, kRing = 2 * W;
   constexpr int kTok = M4 ? 4 : Z2Z_MAX_M;
   constexpr int32_t kFirst = 0x0FFFFFFF;
   typedef RoundSet<kSet> Set;
   const LzwState& st = a.st;
-  const int b = blockIdx.x;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1248,13 +1309,14 @@ __device__ __forceinline__ void lzw_decode_windows(const LzwArgs& a, DecShared<N
 template <int NW, bool LDS>
 __global__ void __launch_bounds__(NW * kWave) lzw_decode_kernel(LzwArgs a) {
   __shared__ DecShared<NW> sh;
-  const bool short_append = !(a.flags & Z2Z_RESET) && call_length(a, blockIdx.x) <= kShortAppend;
+  const int b = sequence_of_block<NW>(a, reinterpret_cast<BlockOrder&>(sh));
+  const bool short_append = !(a.flags & Z2Z_RESET) && call_length(a, b) <= kShortAppend;
   if (LDS && short_append) {
-    lzw_decode_windows<NW, false, false>(a, sh);
+    lzw_decode_windows<NW, false, false>(a, b, sh);
   } else if (a.st.M <= 4) {
-    lzw_decode_windows<NW, LDS, true>(a, sh);
+    lzw_decode_windows<NW, LDS, true>(a, b, sh);
   } else {
-    lzw_decode_windows<NW, LDS, false>(a, sh);
+    lzw_decode_windows<NW, LDS, false>(a, b, sh);
   }
 }
 
@@ -1292,6 +1354,7 @@ __global__ void lzw_clear_entries_kernel(LzwState st) {
 struct ParsePlan {
   bool lds;
   int nw;
+  int sets;                // encoder: RoundSets that the iterations of a window use in turn
   size_t smem;
 };
 ParsePlan plan(const z2z_ctx* c, int32_t stride, int32_t flags, bool decode, LzwArgs* a) {
@@ -1300,8 +1363,8 @@ ParsePlan plan(const z2z_ctx* c, int32_t stride, int32_t flags, bool decode, Lzw
   p.lds = c->st.slots_fit_lds && !tiny_append && c->opt_lzw_kernel != 2;
   p.nw = tiny_append || c->opt_lzw_kernel == 4 ? 1 : stride <= 512 ? 8 : 16;
   p.smem = p.lds ? (size_t)c->st.nslots * sizeof(u64) : 0;
-  const size_t all = (size_t)c->lds_limit, fixed8 = decode ? sizeof(DecShared<8>) : sizeof(EncShared<8>),
-               fixed4 = decode ? sizeof(DecShared<4>) : sizeof(EncShared<4>);
+  const size_t all = (size_t)c->lds_limit, fixed8 = decode ? sizeof(DecShared<8>) : sizeof(EncShared<8, 2>),
+               fixed4 = decode ? sizeof(DecShared<4>) : sizeof(EncShared<4, 2>);
   size_t ef = decode && p.lds ? (size_t)c->st.cap * sizeof(uint32_t) : 0;
   if (p.smem + ef + kParseStaticLds > all) ef = 0;
   if (c->cfg.B > c->num_cu && p.nw > 1) {
@@ -1312,6 +1375,15 @@ ParsePlan plan(const z2z_ctx* c, int32_t stride, int32_t flags, bool decode, Lzw
     }
   }
   a->lds_ef = ef != 0;
+  p.sets = 2;
+  if (!decode && c->cfg.B > c->num_cu && p.nw > 1) {
+    // workgroups that a CU holds, by its LDS and by 28 waves of registers, no more than there are
+    auto held = [&](size_t fixed) {
+      return std::min({all / (p.smem + fixed), (size_t)(28 / p.nw), (size_t)((c->cfg.B + c->num_cu - 1) / c->num_cu)});
+    };
+    if (p.nw == 4 ? held(sizeof(EncShared<4, 1>)) > held(fixed4) : held(sizeof(EncShared<8, 1>)) > held(fixed8)) p.sets = 1;
+  }
+  a->by_length = a->in_len != nullptr && c->cfg.B > 2 * c->num_cu;
   p.smem += ef;
   return p;
 }
@@ -1512,11 +1584,21 @@ int z2z_launch_codebook_prefill(z2z_ctx* c, const int32_t* phrases, const int32_
 }
 
 template <bool LDS>
-static void launch_encode(const LzwArgs& a, int B, int nw, size_t smem, hipStream_t s) {
+static void launch_encode(const LzwArgs& a, int B, int nw, int sets, size_t smem, hipStream_t s) {
   switch (nw) {
     case 1: hipLaunchKernelGGL((lzw_encode_kernel<1, LDS>), dim3(B), dim3(64), smem, s, a); break;
-    case 4: hipLaunchKernelGGL((lzw_encode_kernel<4, LDS>), dim3(B), dim3(256), smem, s, a); break;
-    case 8: hipLaunchKernelGGL((lzw_encode_kernel<8, LDS>), dim3(B), dim3(512), smem, s, a); break;
+    case 4:
+      if (sets == 1)
+        hipLaunchKernelGGL((lzw_encode_kernel<4, LDS, 1>), dim3(B), dim3(256), smem, s, a);
+      else
+        hipLaunchKernelGGL((lzw_encode_kernel<4, LDS>), dim3(B), dim3(256), smem, s, a);
+      break;
+    case 8:
+      if (sets == 1)
+        hipLaunchKernelGGL((lzw_encode_kernel<8, LDS, 1>), dim3(B), dim3(512), smem, s, a);
+      else
+        hipLaunchKernelGGL((lzw_encode_kernel<8, LDS>), dim3(B), dim3(512), smem, s, a);
+      break;
     default: hipLaunchKernelGGL((lzw_encode_kernel<16, LDS>), dim3(B), dim3(1024), smem, s, a); break;
   }
 }
@@ -1546,9 +1628,9 @@ int z2z_launch_lzw_encode(z2z_ctx* c, const int32_t* tokens, const int32_t* lens
   a.status = status;
   const ParsePlan p = plan(c, stride, flags, false, &a);
   if (p.lds)
-    launch_encode<true>(a, c->cfg.B, p.nw, p.smem, s);
+    launch_encode<true>(a, c->cfg.B, p.nw, p.sets, p.smem, s);
   else
-    launch_encode<false>(a, c->cfg.B, p.nw, 0, s);
+    launch_encode<false>(a, c->cfg.B, p.nw, p.sets, 0, s);
   Z2Z_HIP_TRY(hipGetLastError());
   return Z2Z_OK;
 }
@@ -1641,6 +1723,8 @@ int z2z_lzw_prepare(z2z_ctx* c) {
   st.nslots &= ~1;                                     // whole buckets
   const void* parse[] = {reinterpret_cast<const void*>(lzw_encode_kernel<1, true>),
                          reinterpret_cast<const void*>(lzw_encode_kernel<4, true>),
+                         reinterpret_cast<const void*>(lzw_encode_kernel<4, true, 1>),
+                         reinterpret_cast<const void*>(lzw_encode_kernel<8, true, 1>),
                          reinterpret_cast<const void*>(lzw_encode_kernel<8, true>),
                          reinterpret_cast<const void*>(lzw_encode_kernel<16, true>),
                          reinterpret_cast<const void*>(lzw_decode_kernel<1, true>),
