@@ -10,7 +10,7 @@
 // Measured, kernel time encode; decode (before: rounds of 256 elements, four waves, cut at the first element that depends
 // on an entry of the round): 8 sequences of 4096 tokens, M = 3, cap 2048: 110 -> 44 us; 89 -> 32 us.  4 of 32768,
 // M = 4, cap 8192: 691 -> 211; 391 -> 125.  16 of 16384, M = 5, cap 16384 (table in memory): 657 -> 284; 449 -> 157.
-// 2048 of 4096: 470 -> 258; 395 -> 187.  1 of 512: 24 -> 11.5; 22 -> 10.
+// 2048 of 4096: 470 -> 258 -> 180; 395 -> 187 -> 150 (up to four workgroups on a CU).  1 of 512: 24 -> 11.5; 22 -> 10.
 //
 // The codebook is a trie stored as a hash table over its edges: one 64-bit slot = parent code (24 bits)
 // | token (24 bits) | entry index (16 bits), two slots per bucket, two buckets per probe step (Table).  The
@@ -326,7 +326,7 @@ __device__ __forceinline__ int call_length(const LzwArgs& a, int b) {
 // start decide when a call with ragged lengths ends, so they should be the shortest: the r-th in the order of 16 classes
 // of length, longest first, and inside a class in the order (wave, turn, lane) of the threads that look at the lengths.
 // Every workgroup finds its own (about 1 us of the 50 and more that a document takes; as a launch of its own it would be 5).
-// 2048 documents of 1024 to 4096 tokens, cap 2048: @@ -> @@ us.
+// 2048 documents of 1024 to 4096 tokens, cap 2048, three workgroups per CU: 199 -> 181 us.
 constexpr int kLengthBins = 16;
 struct BlockOrder {
   int32_t bin[kLengthBins];
@@ -796,7 +796,7 @@ __device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, int b, EncS
 // is cheaper than staging all of it in LDS and writing it back (the length is known only on the device,
 // so the LDS kernels take this decision per sequence).
 template <int NW, bool LDS, int SETS = 2>
-__global__ void __launch_bounds__(NW * kWave) lzw_encode_kernel(LzwArgs a) {
+__global__ void __launch_bounds__(NW * kWave, SETS == 1 ? 8 : 1) lzw_encode_kernel(LzwArgs a) {
   __shared__ EncShared<NW, SETS> sh;
   const int b = sequence_of_block<NW>(a, reinterpret_cast<BlockOrder&>(sh));
   const bool short_append = !(a.flags & Z2Z_RESET) && call_length(a, b) <= kShortAppend;
@@ -1348,9 +1348,11 @@ __global__ void lzw_clear_entries_kernel(LzwState st) {
 //   - A short appended call (a decode step) touches a handful of slots: one wave, the table where it is.
 //   - While every sequence has a CU to itself, the widest window is the fastest (4096 tokens, 8 sequences: 44 us
 //     with 16 waves, 54 with 8); up to 512 elements a call is a single window of 8 waves.
-//   - With more sequences than CUs, two workgroups per CU hide each other's latencies: 8 waves each when the LDS
-//     allows (2048 sequences of 4096 tokens, cap 2048: 260 us; 16 waves 576), else 4 (cap 4096: 397 us; one workgroup of 8
-//     waves 501), the decoder then without its (length, first token) copy; else one workgroup of 8.
+//   - With more sequences than CUs, workgroups of a CU hide each other's latencies: 8 waves each where two fit its LDS
+//     (2048 sequences of 4096 tokens, cap 2048: 260 us; 16 waves 576), else 4 (the decoder then without its (length, first
+//     token) copy), else one of 8.  Up to four fit (z2z_lzw_prepare); the encoder's iterations then share one RoundSet
+//     where two would keep one workgroup from fitting (2048 documents of 1024 to 4096 tokens, cap 2048: two workgroups 200
+//     us, three 162); where they would not, two sets are faster, by a barrier an iteration (500 sequences: 73, one set 82).
 struct ParsePlan {
   bool lds;
   int nw;
@@ -1363,8 +1365,8 @@ ParsePlan plan(const z2z_ctx* c, int32_t stride, int32_t flags, bool decode, Lzw
   p.lds = c->st.slots_fit_lds && !tiny_append && c->opt_lzw_kernel != 2;
   p.nw = tiny_append || c->opt_lzw_kernel == 4 ? 1 : stride <= 512 ? 8 : 16;
   p.smem = p.lds ? (size_t)c->st.nslots * sizeof(u64) : 0;
-  const size_t all = (size_t)c->lds_limit, fixed8 = decode ? sizeof(DecShared<8>) : sizeof(EncShared<8, 2>),
-               fixed4 = decode ? sizeof(DecShared<4>) : sizeof(EncShared<4, 2>);
+  const size_t all = (size_t)c->lds_limit, fixed8 = decode ? sizeof(DecShared<8>) : sizeof(EncShared<8, 1>),
+               fixed4 = decode ? sizeof(DecShared<4>) : sizeof(EncShared<4, 1>);
   size_t ef = decode && p.lds ? (size_t)c->st.cap * sizeof(uint32_t) : 0;
   if (p.smem + ef + kParseStaticLds > all) ef = 0;
   if (c->cfg.B > c->num_cu && p.nw > 1) {
@@ -1377,11 +1379,12 @@ ParsePlan plan(const z2z_ctx* c, int32_t stride, int32_t flags, bool decode, Lzw
   a->lds_ef = ef != 0;
   p.sets = 2;
   if (!decode && c->cfg.B > c->num_cu && p.nw > 1) {
-    // workgroups that a CU holds, by its LDS and by 28 waves of registers, no more than there are
-    auto held = [&](size_t fixed) {
-      return std::min({all / (p.smem + fixed), (size_t)(28 / p.nw), (size_t)((c->cfg.B + c->num_cu - 1) / c->num_cu)});
+    // workgroups that a CU holds, by its LDS and by 32 (two sets: 28) waves of registers, no more than there are
+    auto held = [&](size_t fixed, int waves) {
+      return std::min({all / (p.smem + fixed), (size_t)(waves / p.nw), (size_t)((c->cfg.B + c->num_cu - 1) / c->num_cu)});
     };
-    if (p.nw == 4 ? held(sizeof(EncShared<4, 1>)) > held(fixed4) : held(sizeof(EncShared<8, 1>)) > held(fixed8)) p.sets = 1;
+    const int one = p.nw == 4 ? (int)sizeof(EncShared<4, 1>) : (int)sizeof(EncShared<8, 1>);
+    if (held(one, 32) > held(p.nw == 4 ? sizeof(EncShared<4, 2>) : sizeof(EncShared<8, 2>), 28)) p.sets = 1;
   }
   a->by_length = a->in_len != nullptr && c->cfg.B > 2 * c->num_cu;
   p.smem += ef;
@@ -1707,7 +1710,23 @@ int z2z_lzw_prepare(z2z_ctx* c) {
   // With fewer sequences than CUs a workgroup has its CU to itself and the roomier table (shorter probe
   // sequences) is free; with many, LDS decides how many sequences a CU works on at once.
   const bool roomy = c->cfg.B < 256;
-  if (roomy && want4 + cap / 2 <= lds_slots) {        // room left for the decoder's entry info
+  // A CU holds up to four workgroups of 8 waves (32 waves of 64 registers): as many as there are sequences for it, the
+  // tables as large as that leaves room for.  Another workgroup hides more than the longer probes cost: 2048 documents of
+  // 1024 to 4096 tokens, encode (decode), cap 2048: 4096 slots, three per CU 162 us (152), 2906 slots, four 149 (125); cap
+  // 3000: 6000 slots, two 237 (177), 4440 slots, three 171 (163).  More than there are sequences for only costs: 600 of 4096
+  // tokens, cap 2048: 4096 slots 67 us, 2561 slots 81 (four workgroups on one CU, fewer on another).
+  int shared = 0;
+  if (c->cfg.B > c->num_cu) {
+    for (int k = std::min(4, (c->cfg.B + c->num_cu - 1) / c->num_cu); k >= 2 && shared == 0; --k) {
+      const int share = c->lds_limit / k & ~2047;      // (LDS is handed out in pieces of 1280 bytes)
+      const int slots = std::min(want, (share - (int)sizeof(EncShared<8, 1>)) / (int)sizeof(u64));
+      if (slots >= std::max(floor125, 64)) shared = slots;
+    }
+  }
+  if (shared > 0) {
+    st.nslots = shared;
+    st.slots_fit_lds = 1;
+  } else if (roomy && want4 + cap / 2 <= lds_slots) {        // room left for the decoder's entry info
     st.nslots = want4;
     st.slots_fit_lds = 1;
   } else if (want <= lds_slots) {
