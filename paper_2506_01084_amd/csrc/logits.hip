@@ -353,17 +353,23 @@ static int pick_strip_for(const z2z_ctx* c, long long row_tiles, int n_vt, int w
 //                           filtered  288 -> 281    301 -> 297   316 -> 309   341 -> 319
 // Behind other work that has turned the caches over the one launch is 40-60 us slower and the split 2-5.
 // Hence: up to 16 sequences, or more than two rounds, or a last round at least 7/8 full over all rounds, or hyper units that
-// would open another round in one launch.  Fewer than 256 tiles stay in one launch.  (That line, and the 7/8 for greedy steps, are
-// from before the ring; now the split side has the smaller figures down to about 196 tiles -- V = 50176, greedy 124 -> 84,
-// 134 -> 102, 193 -> 122, 200 -> 152 -- and at 126, V = 32064, d = 3072, where the caches are cold: in a row 66 -> 65, 70 -> 80,
-// 78 -> 94, 93 -> 117, cold 99 -> 68, 111 -> 83, 128 -> 97, 150 -> 120.)
+// would open another round in one launch.
+// 112 to 255 tiles leave so many CUs to the hyper units that only the last of these counts.  V = 32064, d = 3072 (126 tiles),
+// tiles + hyper units, one launch -> split, on fresh inputs:
+//   above 256   greedy    17 x 4096 (262) 148 -> 104   34 x 2048 (262) 155 -> 132   40 x 2048 160 -> 136   64 x 4096 288 -> 242
+//               draw      17 x 4096 166 -> 113         34 x 2048 174 -> 144         50 x 2048 191 -> 175   64 x 4096 304 -> 260
+//               filtered  17 x 4096 168 -> 139         34 x 2048 177 -> 151         24 x 4096 179 -> 145   64 x 2048 219 -> 200
+//   up to 256   greedy    24 x 1024 (174) 83 -> 82     draw 24 x 2048 (222) 100 -> 109, 64 x 1024 (254) 111 -> 132
+//               filtered  12 x 2048 (174) 99 -> 132    40 x 1024 (206) 109 -> 141
+// (Units count whole however few entries they have: at least 64 of them, so that they are what opens the round.)
 static bool split_few(const z2z_ctx* c, int rows) {
   const long long tiles = z2z_logits_mid_tiles(c->cfg.V), slots = (tiles + 255) / 256 * 256;
   int base_columns, hyper_columns;
   z2z_logits_decode_units(&base_columns, &hyper_columns);
   const long long units = (long long)rows * ((c->cfg.cap + hyper_columns - 1) / hyper_columns);
-  return rows > 4 && rows <= 64 && c->opt_decode_kernel == 0 && c->opt_logits_kernel == 0 && tiles >= 256 &&
-         (rows <= 16 || tiles > 512 || 8 * tiles >= 7 * slots || tiles + units > slots) && z2z_logits_mid_ok(c, rows);
+  const bool pays = tiles >= 256 ? rows <= 16 || tiles > 512 || 8 * tiles >= 7 * slots || tiles + units > slots
+                                 : tiles >= 112 && units >= 64 && tiles + units > slots;
+  return rows > 4 && rows <= 64 && c->opt_decode_kernel == 0 && c->opt_logits_kernel == 0 && pays && z2z_logits_mid_ok(c, rows);
 }
 
 // Parts per row that any kind of step may leave (hyper units of 64 rows): every step sizes the scratch for all of them,

@@ -29,6 +29,12 @@ pytestmark = pytest.mark.gpu
     (17, 114432, 128, 40, 0),     # 447
     (17, 131073, 128, 40, 1),     # 513: a third round, nearly empty
     (32, 66000, 128, 4000, 1),    # 258 tiles and 256 hyper units
+    (37, 28432, 128, 2000, 1),    # 112 tiles, 148 hyper units: above 256 in all
+    (36, 28432, 128, 2000, 0),    # 256
+    (37, 28416, 256, 2000, 0),    # 111 tiles
+    (64, 49200, 128, 100, 1),     # 193 tiles and 64 units: 257
+    (63, 49500, 128, 100, 0),     # 194 tiles, 63 units
+    (9, 50000, 256, 3600, 1),     # 196 tiles, 72 units, the last of a sequence nearly empty
 ])
 def test_split_step(B, V, d, cap, split):
     import torch
