@@ -41,6 +41,7 @@ struct LzwArgs {
   int32_t* status;         // [B]
   int32_t lds_ef;          // decode, LDS variant: 1 = (length, first token) of the entries live in LDS too
   int32_t by_length;       // window kernels: workgroups take the sequences longest first
+  int32_t tail_min;        // decode: codes left behind a full codebook that lzw_decode_tail_kernel takes over
   int32_t in_step;         // one-code-at-a-time decoder only: > 0 = row distance of `in` (else `stride`)
 };
 
@@ -1023,6 +1024,9 @@ __global__ void __launch_bounds__(kStepWaves * kWave) lzw_step_update_kernel(Lzw
 //      with the next code's first token behind them, to the row of the entry the next code makes.
 // A chain of entries of this round is at most M long, so two to four iterations are usual.
 // ------------------------------------------------------------------------------------------------
+// Codes that the decoder leaves to the kernel behind it, which takes a launch (5 us) where a window of 1024 takes 2.6.
+constexpr int kTailMin = 3072;
+
 template <int NW>
 struct DecShared {
   static constexpr int W = NW * kWave;
@@ -1286,6 +1290,7 @@ __device__ __forceinline__ void lzw_decode_windows(const LzwArgs& a, int b, DecS
       n_out += sh.last_tokens;
       C += sh.last_made;
       cpos += limit - 1;
+      if (C >= cap && n - cpos >= a.tail_min) break;
     } else {
       stop = true;
     }
@@ -1303,6 +1308,8 @@ __device__ __forceinline__ void lzw_decode_windows(const LzwArgs& a, int b, DecS
     st.rounds[b] = n_rounds;
     a.out_n[b] = n_out;
     a.status[b] = status;
+    st.tail[2 * b] = stop ? n : cpos;
+    st.tail[2 * b + 1] = n_out;
   }
 }
 
@@ -1317,6 +1324,119 @@ __global__ void __launch_bounds__(NW * kWave) lzw_decode_kernel(LzwArgs a) {
     lzw_decode_windows<NW, LDS, true>(a, b, sh);
   } else {
     lzw_decode_windows<NW, LDS, false>(a, b, sh);
+  }
+}
+
+// The codes behind a full codebook: nothing is made any more, so lengths are a table look-up, offsets a prefix sum, and
+// all CUs can take part.  grid = (parts, B); a part of a sequence adds up the lengths of the codes before its own by
+// itself (a chain of parts, each waiting for the one before, would be as long as the window kernel's).
+//
+// What bounds it: the launch, two dependent trips to L2 per 1024 codes before the part.  4 sequences of 22300 codes, of which
+// 13700 lie behind the 8192 entries of a full codebook: 35 us in the window kernel, 10 here; 27400 behind 1024: 84 -> 32 in all.
+__global__ void __launch_bounds__(1024) lzw_decode_tail_kernel(LzwArgs a) {
+  constexpr int W = 1024, NW = W / kWave;
+  struct Shared {
+    uint32_t count[NW];
+    int32_t bad;                               // a code before this part that names nothing
+    int32_t end;                               // first element of a turn that is not taken
+  };
+  __shared__ Shared sh;
+  const LzwState& st = a.st;
+  const int b = blockIdx.y;
+  const int from = __builtin_amdgcn_readfirstlane(st.tail[2 * b]), n = call_length(a, b);
+  const int share = (n - from + (int)gridDim.x - 1) / (int)gridDim.x;
+  const int span = (share + W - 1) / W * W;
+  const int lo = from + (int)blockIdx.x * span;
+  if (from >= n || lo >= n) return;
+  const int hi = min(n, lo + span);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int V = st.V, M = st.M, cap = st.cap;
+  const int C = min(max(__builtin_amdgcn_readfirstlane(st.size[b]), 0), cap);
+  const int32_t* in = a.in + (size_t)b * a.stride;
+  int32_t* out = a.out ? a.out + (size_t)b * a.out_stride : nullptr;
+  const int32_t* ent_tokens = st.ent_tokens + (size_t)b * cap * M;
+  const int32_t* ent_len = st.ent_len + (size_t)b * cap;
+  auto length = [&](int32_t k) -> int {        // 0: names nothing
+    if (k < 0) return 0;
+    if (k < V) return 1;
+    return k - V < C ? ent_len[k - V] : 0;
+  };
+
+  if (tid == 0) sh.bad = 0;
+  __syncthreads();
+  int sum = 0;
+  bool bad = false;
+#pragma unroll 4
+  for (int i = from + tid; i < lo; i += W) {
+    const int len = length(in[i]);
+    bad |= len == 0;
+    sum += len;
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
+  if (lane == 0) sh.count[w] = (uint32_t)sum;
+  if (__ballot(bad) != 0 && lane == 0) sh.bad = 1;
+  __syncthreads();
+  int base = st.tail[2 * b + 1];               // tokens of the codes before
+  for (int j = 0; j < NW; ++j) base += (int)sh.count[j];
+  // the sequence ended in an earlier part
+  if (sh.bad || (out != nullptr && base > a.out_stride)) return;
+
+  const u64 lanes_below = (1ull << lane) - 1;
+  for (int pos = lo; pos < hi; pos += W) {
+    const int i = pos + tid;
+    const bool present = i < hi;
+    const int32_t k = present ? in[i] : -1;
+    const int len = present ? length(k) : 0;
+    int incl = 0;                              // tokens of the codes of this turn up to this one
+#pragma unroll
+    for (int bit = 0; bit < 4; ++bit) {
+      const u64 m = __ballot((len >> bit) & 1);
+      incl += (__popcll(m & lanes_below) + ((len >> bit) & 1)) << bit;
+    }
+    __syncthreads();                           // (the previous turn's counts have been read)
+    if (tid == 0) sh.end = W;
+    if (lane == kWave - 1) sh.count[w] = (uint32_t)incl;
+    __syncthreads();
+    const uint32_t counts = row_scan_add(lane < NW ? sh.count[lane] : 0u);
+    incl += w == 0 ? 0 : __builtin_amdgcn_readlane((int)counts, w == 0 ? 0 : w - 1);
+    const int total = __builtin_amdgcn_readlane((int)counts, NW - 1);
+    const u64 ends = __ballot(present && (len == 0 || (out != nullptr && base + incl > a.out_stride)));
+    if (ends != 0 && lane == 0) atomicMin(&sh.end, w * kWave + (int)__builtin_ctzll(ends));
+    __syncthreads();
+    const int end = sh.end;
+    if (present && tid < end && out != nullptr) {
+      int32_t* dst = out + base + incl - len;
+      if (k < V) {
+        dst[0] = k;
+      } else {
+        const int32_t* row = ent_tokens + (size_t)(k - V) * M;
+        int32_t T[Z2Z_MAX_M];
+#pragma unroll
+        for (int j = 0; j < Z2Z_MAX_M; ++j) T[j] = j < M ? row[j] : -1;
+#pragma unroll
+        for (int j = 0; j < Z2Z_MAX_M; ++j)
+          if (j < len) dst[j] = T[j];
+      }
+    }
+    if (end < W) {                             // uniform
+      if (tid == end) {
+        a.status[b] = len == 0 ? Z2Z_ST_BAD_CODE : Z2Z_ST_OVERFLOW;
+        a.out_n[b] = base + incl - len;
+        if (i > from) {
+          st.prev_code[b] = in[i - 1];
+          st.prev_len[b] = length(in[i - 1]);
+        }
+      }
+      return;
+    }
+    if (i == n - 1) {
+      a.out_n[b] = base + incl;
+      st.prev_code[b] = k;
+      st.prev_len[b] = len;
+    }
+    base += total;
   }
 }
 
@@ -1654,6 +1774,13 @@ int z2z_launch_lzw_decode(z2z_ctx* c, const int32_t* codes, const int32_t* n_cod
   a.status = status;
   const ParsePlan p = plan(c, stride, flags, true, &a);
   const bool serial = stride <= 8 || c->opt_lzw_kernel == 3;
+  // Long rows of few sequences: a second launch over all CUs takes the codes behind a full codebook.  A codebook that starts
+  // empty is full after cap codes at the earliest; how many follow only the device knows, and the first launch goes on
+  // by itself when they are fewer than kTailMin.  (16 sequences of 9700 codes, 8192 entries, nothing
+  // left for it: 95 -> 98 us.)
+  const bool tail = !serial && p.nw > 1 && 2 * c->cfg.B <= c->num_cu &&
+                    stride >= ((flags & Z2Z_RESET) ? (int64_t)c->cfg.cap : 0) + 2 * kTailMin;
+  a.tail_min = tail ? kTailMin : INT32_MAX;
   // (the window kernels clear the rows behind the new codebook themselves)
   if (serial && (flags & Z2Z_RESET)) hipLaunchKernelGGL(lzw_clear_entries_kernel, dim3(c->cfg.B), dim3(256), 0, s, c->st);
   if (serial && p.lds)
@@ -1664,6 +1791,10 @@ int z2z_launch_lzw_decode(z2z_ctx* c, const int32_t* codes, const int32_t* n_cod
     launch_decode<true>(a, c->cfg.B, p.nw, p.smem, s);
   else
     launch_decode<false>(a, c->cfg.B, p.nw, 0, s);
+  if (tail) {
+    const int parts = std::min(64, c->num_cu / c->cfg.B);
+    hipLaunchKernelGGL(lzw_decode_tail_kernel, dim3(parts, c->cfg.B), dim3(1024), 0, s, a);
+  }
   Z2Z_HIP_TRY(hipGetLastError());
   return Z2Z_OK;
 }

@@ -141,6 +141,58 @@ def test_decode_of_arbitrary_codes(M, cap):
         ctx.close()
 
 
+@pytest.mark.parametrize("M,cap", [(3, 400), (5, 40), (8, 1500), (2, 0)])
+def test_codes_behind_a_full_codebook(M, cap):
+    """Rows so long that the codes behind a full codebook go to a launch of their own, in parts: ragged rows (one too short for
+    it), no output, a code that names nothing and an output row that ends in any part, appended calls behind it."""
+    from paper_2506_01084_amd import api
+
+    V, n = 25, 12000
+    rng = np.random.default_rng(M + cap)
+    streams = []
+    for b in range(4):
+        head = oracle.lzw_encode(rng.integers(0, V, 4 * cap + 64).tolist(), V, M, cap)
+        assert len(head[1]) == cap
+        streams.append(head[0] + rng.integers(0, V + cap, n - len(head[0])).tolist())
+    rows = np.asarray(streams, dtype=np.int32)
+    cnt = np.array([n, n - 1, 2500, 9217], dtype=np.int32)
+    B = len(cnt)
+    ref = [oracle.lzw_decode(streams[b][:cnt[b]], V, M, cap) for b in range(B)]
+    longest = max(len(r[0]) for r in ref)
+    ctx = _ctx(B, V, M, cap)
+    toks, n_tok, st = gpu_decode(ctx, rows, cnt, out_stride=longest)
+    assert (st == 0).all()
+    for b in range(B):
+        assert toks[b, :n_tok[b]].tolist() == ref[b][0] and (toks[b, n_tok[b]:] == -7).all()
+    assert_codebook_equal(ctx, [r[1] for r in ref], M, cap)
+    # appended: all codes of the second call stand behind a full codebook; then a few, then a tokenized chunk
+    s = [oracle.LZWStream(V, M, cap) for _ in range(B)]
+    for b in range(B):
+        s[b].decode_chunk(streams[b][:cnt[b]])
+    more = rng.integers(0, V + cap, (B, 7000)).astype(np.int32)
+    for chunk, width in ((more, M * 7000), (more[:, :5], 0)):
+        toks, n_tok, st = gpu_decode(ctx, chunk, None, out_stride=width, flags=api.APPEND)
+        for b in range(B):
+            want, rst = s[b].decode_chunk(chunk[b].tolist())
+            assert int(st[b]) == rst == 0 and int(n_tok[b]) == len(want)
+            assert toks is None or toks[b, :n_tok[b]].tolist() == want
+    _, n_tok, st = gpu_decode(ctx, rows, cnt, out_stride=0)
+    assert (st == 0).all() and n_tok.tolist() == [len(r[0]) for r in ref]
+    for at in (0, 3000, 6143, 6144, 7168, 9215, 9216, n - 1):
+        bad = rows.copy()
+        bad[:, at] = (V + cap, -1, V + cap + 7, -2**31)
+        toks, n_tok, st = gpu_decode(ctx, bad, cnt, out_stride=longest)
+        for b in range(B):
+            rt, _, rst = oracle.lzw_decode(bad[b, :cnt[b]].tolist(), V, M, cap)
+            assert int(st[b]) == rst and toks[b, :n_tok[b]].tolist() == rt and (toks[b, n_tok[b]:] == -7).all()
+    for room in (longest - 1, longest - 1500, len(ref[3][0]), len(ref[3][0]) - 1, 5000):
+        toks, n_tok, st = gpu_decode(ctx, rows, cnt, out_stride=room)
+        for b in range(B):
+            rt, _, rst = oracle.lzw_decode(streams[b][:cnt[b]], V, M, cap, max_tokens=room)
+            assert int(st[b]) == rst and toks[b, :n_tok[b]].tolist() == rt and (toks[b, n_tok[b]:] == -7).all()
+    ctx.close()
+
+
 def _crowded_pairs(V, bits):
     """Pairs of tokens, the most found, whose edges share both of their groups of the round's set (2^bits groups of four):
     beyond eight of them in a window the rest find no slot.  (The hash is the kernel's.)"""
