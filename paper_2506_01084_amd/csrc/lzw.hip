@@ -9,7 +9,7 @@
 //
 // Measured, kernel time encode; decode (before: rounds of 256 elements, four waves, cut at the first element that depends
 // on an entry of the round): 8 sequences of 4096 tokens, M = 3, cap 2048: 110 -> 44 us; 89 -> 32 us.  4 of 32768,
-// M = 4, cap 8192: 691 -> 211; 391 -> 125.  16 of 16384, M = 5, cap 16384 (table in memory): 657 -> 284; 449 -> 157.
+// M = 4, cap 8192: 691 -> 211; 391 -> 125 -> 98.  16 of 16384, M = 5, cap 16384 (table in memory, its tags in LDS): 657 -> 284 -> 185; 449 -> 157 -> 100.
 // 2048 of 4096: 470 -> 258 -> 180; 395 -> 187 -> 150 (up to four workgroups on a CU).  1 of 512: 24 -> 11.5; 22 -> 10.
 //
 // The codebook is a trie stored as a hash table over its edges: one 64-bit slot = parent code (24 bits)
@@ -56,14 +56,36 @@ __device__ __forceinline__ u64 edge_bits(int32_t parent, int32_t tok) {
   return ((u64)(uint32_t)parent << 40) | ((u64)(uint32_t)tok << 16);
 }
 
-extern __shared__ __align__(16) u64 lds_slots[];   // LDS variant: the sequence's hash table (+ entry info)
+extern __shared__ __align__(16) u64 lds_slots[];   // the sequence's hash table (+ entry info), or its tags
 
-// The hash table of one sequence, in LDS (LDS = true; indexes the shared array directly so that probes
-// are ds_read_b64) or in global memory (huge capacities, and short appends that touch a few slots).
-template <bool LDS>
+// The hash table of one sequence: in LDS for the length of a call (indexes the shared array directly so that probes
+// are ds_read_b128), in global memory (huge capacities, and short appends that touch a few slots), or in global memory
+// with a tag of every slot in LDS: 16 bits of the edge's hash | entry index.  What a probe in memory costs is requests, two
+// of 16 bytes, hit or miss; with the tags a miss is a matter of LDS and a hit one request of 8 bytes, the slot itself.
+// 16 sequences of 16384 tokens, cap 16384, M = 5: encode 272 -> 185 us, decode 156 -> 100; 100 of 8192, cap 12000, M = 3: 134
+// -> 89; 109 -> 69.
+enum { kMem, kLds, kTag };
+template <int WHERE>
 struct Table {
+  static constexpr bool LDS = WHERE == kLds;
   u64* g;           // global slots of this sequence
   uint32_t n;       // number of slots
+
+  static __device__ __forceinline__ uint32_t* tags() { return reinterpret_cast<uint32_t*>(lds_slots); }
+  static __device__ __forceinline__ uint32_t tag_of(uint32_t h) {           // (all ones: no entry has it)
+    return min((h >> 2) & 0xFFFFu, 0xFFFEu) << 16;
+  }
+  // The tags of two buckets, and which of them agree with an edge's (bit i: slot i of the four).
+  struct Tags {
+    uint2 a, b;
+  };
+  __device__ __forceinline__ Tags load_tags(uint32_t b0, uint32_t b1) const {
+    return {*reinterpret_cast<const uint2*>(tags() + 2 * b0), *reinterpret_cast<const uint2*>(tags() + 2 * b1)};
+  }
+  static __device__ __forceinline__ uint32_t agree(const Tags& t, uint32_t tag) {
+    return ((t.a.x ^ tag) < 0x10000u ? 1u : 0u) | ((t.a.y ^ tag) < 0x10000u ? 2u : 0u) | ((t.b.x ^ tag) < 0x10000u ? 4u : 0u) |
+           ((t.b.y ^ tag) < 0x10000u ? 8u : 0u);
+  }
 
   // Two slots are a bucket (n is even): one 16-byte read.  A probe step looks at two buckets at once, and a new
   // edge goes into the emptier one (slot 0 of a bucket first), so hardly any look-up needs a second step: with the
@@ -114,7 +136,10 @@ struct Table {
     b->y = ((u64)y[3] << 32) | y[2];
   }
   __device__ __forceinline__ void store(uint32_t pos, u64 v) const {
-    if (LDS)
+    if (WHERE == kTag) {
+      tags()[pos] = tag_of(edge_hash((int32_t)(v >> 40), (int32_t)((v >> 16) & 0xFFFFFFu))) | (uint32_t)(v & 0xFFFFu);
+      g[pos] = v;
+    } else if (LDS)
       lds_slots[pos] = v;
     else
       __hip_atomic_store(&g[pos], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -125,6 +150,22 @@ struct Table {
     if (b.x == kEmpty) return (int)(2 * p.b1);
     if (a.y == kEmpty) return (int)(2 * p.b0 + 1);
     if (b.y == kEmpty) return (int)(2 * p.b1 + 1);
+    return -1;
+  }
+  static __device__ __forceinline__ int free_slot(const Probe& p, const Tags& t) {
+    if (t.a.x == ~0u) return (int)(2 * p.b0);
+    if (t.b.x == ~0u) return (int)(2 * p.b1);
+    if (t.a.y == ~0u) return (int)(2 * p.b0 + 1);
+    if (t.b.y == ~0u) return (int)(2 * p.b1 + 1);
+    return -1;
+  }
+  // The entry of an edge whose tag some slots of a probe have, or -1: the slots themselves decide.
+  __device__ __forceinline__ int confirm(const Probe& p, uint32_t which, u64 key) const {
+    for (; which != 0; which &= which - 1) {
+      const int i = __builtin_ctz(which);
+      const u64 slot = g[2 * (i < 2 ? p.b0 : p.b1) + (i & 1)];
+      if (holds(slot, key)) return (int)((uint32_t)slot & 0xFFFFu);
+    }
     return -1;
   }
   static __device__ __forceinline__ bool holds(u64 slot, u64 key) {
@@ -150,6 +191,14 @@ struct Table {
     const u64 key = edge_bits(parent, tok);
     Probe p = probe_init(edge_hash(parent, tok));
     do {
+      if (WHERE == kTag) {
+        const Tags t = load_tags(p.b0, p.b1);
+        const int idx = __builtin_amdgcn_readfirstlane(confirm(p, agree(t, tag_of(edge_hash(parent, tok))), key));
+        if (idx >= 0) return idx;
+        *free_pos = __builtin_amdgcn_readfirstlane(free_slot(p, t));
+        if (*free_pos >= 0) return -1;
+        continue;
+      }
       ulonglong2 a, b;
       load(p, &a, &b);
       a.x = uniform(a.x);
@@ -168,6 +217,16 @@ struct Table {
     const u64 key = edge_bits(parent, tok);
     Probe p = probe_init(h);
     do {
+      if (WHERE == kTag) {
+        const Tags t = load_tags(p.b0, p.b1);
+        const uint32_t which = agree(t, tag_of(h));
+        if (which != 0) {
+          const int idx = confirm(p, which, key);
+          if (idx >= 0) return idx;
+        }
+        if (t.a.y == ~0u || t.b.y == ~0u) return -1;
+        continue;
+      }
       ulonglong2 a, b;
       load(p, &a, &b);
       const int idx = match(a, b, key);
@@ -183,9 +242,19 @@ struct Table {
   // compare-and-swap, and the buckets are looked at again when it was lost).
   __device__ __forceinline__ void insert_lane(int32_t parent, int32_t tok, int idx) const {
     const u64 val = edge_bits(parent, tok) | (u64)(uint32_t)idx;
-    Probe p = probe_init(edge_hash(parent, tok));
+    const uint32_t h = edge_hash(parent, tok);
+    Probe p = probe_init(h);
     do {
       for (int tries = 0; tries < 5; ++tries) {     // (a lost slot has filled: at most four times)
+        if (WHERE == kTag) {
+          const int at = free_slot(p, load_tags(p.b0, p.b1));
+          if (at < 0) break;
+          if (atomicCAS(&tags()[at], ~0u, tag_of(h) | (uint32_t)idx) == ~0u) {
+            g[at] = val;
+            return;
+          }
+          continue;
+        }
         ulonglong2 a, b;
         load(p, &a, &b);
         const int at = free_slot(p, a, b);
@@ -216,7 +285,7 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-template <bool LDS>
+template <int LDS>
 __device__ __forceinline__ void table_open(const LzwArgs& a, int b, int lane, bool reset, Table<LDS>* t) {
   const LzwState& st = a.st;
   t->g = st.slots + (size_t)b * st.nslots;
@@ -237,30 +306,42 @@ __device__ __forceinline__ void table_open(const LzwArgs& a, int b, int lane, bo
 }
 
 // The same by all THREADS threads of a workgroup; no barrier inside.
-template <bool LDS, int THREADS>
-__device__ __forceinline__ void table_open_all(const LzwArgs& a, int b, int tid, bool reset, Table<LDS>* t) {
+template <int WHERE, int THREADS>
+__device__ __forceinline__ void table_open_all(const LzwArgs& a, int b, int tid, bool reset, Table<WHERE>* t) {
   t->g = a.st.slots + (size_t)b * a.st.nslots;
   t->n = (uint32_t)a.st.nslots;
   ulonglong2* g2 = reinterpret_cast<ulonglong2*>(t->g);             // (nslots is even, the rows 16-byte aligned)
   ulonglong2* l2 = reinterpret_cast<ulonglong2*>(lds_slots);
   const int pairs = a.st.nslots >> 1;
   const ulonglong2 empty = {kEmpty, kEmpty};
-  if (LDS) {
+  if (WHERE == kLds) {
     for (int i = tid; i < pairs; i += THREADS) l2[i] = reset ? empty : g2[i];
   } else if (reset) {
     for (int i = tid; i < pairs; i += THREADS) g2[i] = empty;
   }
+  if (WHERE == kTag) {
+    uint2* tags = reinterpret_cast<uint2*>(t->tags());
+    if (reset) {                               // (chosen per element, the compiler got `reset` the wrong way round further on)
+      for (int i = tid; i < pairs; i += THREADS) tags[i] = {~0u, ~0u};
+    } else {
+      auto tag = [&](u64 v) -> uint32_t {
+        if (v == kEmpty) return ~0u;
+        return t->tag_of(edge_hash((int32_t)(v >> 40), (int32_t)((v >> 16) & 0xFFFFFFu))) | (uint32_t)(v & 0xFFFFu);
+      };
+      for (int i = tid; i < pairs; i += THREADS) tags[i] = {tag(g2[i].x), tag(g2[i].y)};
+    }
+  }
 }
-template <bool LDS, int THREADS>
-__device__ __forceinline__ void table_close_all(int tid, const Table<LDS>& t) {
-  if (LDS) {
+template <int WHERE, int THREADS>
+__device__ __forceinline__ void table_close_all(int tid, const Table<WHERE>& t) {
+  if (WHERE == kLds) {
     ulonglong2* g2 = reinterpret_cast<ulonglong2*>(t.g);
     const ulonglong2* l2 = reinterpret_cast<const ulonglong2*>(lds_slots);
     for (int i = tid; i < (int)(t.n >> 1); i += THREADS) g2[i] = l2[i];
   }
 }
 
-template <bool LDS>
+template <int LDS>
 __device__ __forceinline__ void table_close(const LzwArgs& a, int lane, const Table<LDS>& t) {
   if (LDS) {
     wave_sync();
@@ -270,7 +351,7 @@ __device__ __forceinline__ void table_close(const LzwArgs& a, int lane, const Ta
 
 // Add the edge (parent, tok) as entry C.  `ph` holds, in lane j, token j of the parent phrase (plen
 // tokens); the new entry's flattened row is that phrase followed by tok.
-template <bool LDS>
+template <int LDS>
 __device__ __forceinline__ void table_insert(const LzwArgs& a, int b, int lane, const Table<LDS>& t, int free_pos,
                                              int C, int32_t parent, int32_t tok, int32_t ph, int plen) {
   const LzwState& st = a.st;
@@ -498,7 +579,7 @@ struct EncShared {
 
 constexpr int kParseStaticLds = (int)sizeof(EncShared<kMaxWaves, 2>) + 256;    // + alignment slack
 
-template <int NW, int SETS, bool LDS, bool M4>
+template <int NW, int SETS, int WHERE, bool M4>
 __device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, int b, EncShared<NW, SETS>& sh) {
   constexpr int W = NW * kWave;
   constexpr int kSet = EncShared<NW, SETS>::kSet, kRing = 2 * W;
@@ -520,8 +601,8 @@ __device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, int b, EncS
   int32_t* ent_tokens = st.ent_tokens + (size_t)b * cap * M;
   int32_t* ent_len = st.ent_len + (size_t)b * cap;
 
-  Table<LDS> t;
-  table_open_all<LDS, W>(a, b, tid, reset, &t);
+  Table<WHERE> t;
+  table_open_all<WHERE, W>(a, b, tid, reset, &t);
   for (int i = tid; i < SETS * kSet; i += W) sh.set[0][i] = kRoundEmpty;
   // tokens: the ring holds [fill - kRing, fill); the next W of them wait in a register
   auto classify = [&](int32_t v) -> int32_t { return (v >= 0 && v < V) ? v : -2; };
@@ -550,7 +631,7 @@ __device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, int b, EncS
           } else if (lane < M) {
             ph = ent_tokens[(size_t)(prev - V) * M + lane];
           }
-          table_insert<LDS>(a, b, lane, t, free_pos, C, prev, c, ph, prev_len);
+          table_insert<WHERE>(a, b, lane, t, free_pos, C, prev, c, ph, prev_len);
         }
         ++C;
       }
@@ -665,7 +746,7 @@ __device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, int b, EncS
         }
       }
       // (which edges found no slot depends on timing; positions from the first of them on are cut off this window)
-      const bool ch = start && (L2 != L || code2 != code) && tid < *(volatile int32_t*)&sh.spill_pos;
+      const bool ch = start && (L2 != L || code2 != code) && tid < sh.spill_pos;
       L = L2;
       code = code2;
       nxt = nxt2;
@@ -778,7 +859,7 @@ __device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, int b, EncS
     }
   }
 
-  table_close_all<LDS, W>(tid, t);
+  table_close_all<WHERE, W>(tid, t);
   if (reset) {                                  // rows of the codebook that was there before
     for (int i = C + tid; i < size0; i += W) ent_len[i] = 0;
     for (int i = C * M + tid; i < size0 * M; i += W) ent_tokens[i] = -1;
@@ -796,17 +877,17 @@ __device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, int b, EncS
 // A short appended call touches a handful of slots: probing the table where it lives, in global memory,
 // is cheaper than staging all of it in LDS and writing it back (the length is known only on the device,
 // so the LDS kernels take this decision per sequence).
-template <int NW, bool LDS, int SETS = 2>
+template <int NW, int WHERE, int SETS = 2>
 __global__ void __launch_bounds__(NW * kWave, SETS == 1 ? 8 : 1) lzw_encode_kernel(LzwArgs a) {
   __shared__ EncShared<NW, SETS> sh;
   const int b = sequence_of_block<NW>(a, reinterpret_cast<BlockOrder&>(sh));
   const bool short_append = !(a.flags & Z2Z_RESET) && call_length(a, b) <= kShortAppend;
-  if (LDS && short_append) {
-    lzw_encode_windows<NW, SETS, false, false>(a, b, sh);
+  if (WHERE != kMem && short_append) {
+    lzw_encode_windows<NW, SETS, kMem, false>(a, b, sh);
   } else if (a.st.M <= 4) {
-    lzw_encode_windows<NW, SETS, LDS, true>(a, b, sh);
+    lzw_encode_windows<NW, SETS, WHERE, true>(a, b, sh);
   } else {
-    lzw_encode_windows<NW, SETS, LDS, false>(a, b, sh);
+    lzw_encode_windows<NW, SETS, WHERE, false>(a, b, sh);
   }
 }
 
@@ -1045,7 +1126,7 @@ struct DecShared {
 };
 static_assert(sizeof(DecShared<kMaxWaves>) <= sizeof(EncShared<kMaxWaves, 2>), "one LDS budget for both directions");
 
-template <int NW, bool LDS, bool M4>
+template <int NW, int WHERE, bool M4>
 __device__ __forceinline__ void lzw_decode_windows(const LzwArgs& a, int b, DecShared<NW>& sh) {
   constexpr int W = NW * kWave;
   constexpr int kSet = DecShared<NW>::kSet, kRing = 2 * W;
@@ -1058,7 +1139,7 @@ __device__ __forceinline__ void lzw_decode_windows(const LzwArgs& a, int b, DecS
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int V = st.V, M = st.M, cap = st.cap;
   const bool reset = (a.flags & Z2Z_RESET) != 0;
-  const bool ef_lds = LDS && a.lds_ef;
+  const bool ef_lds = WHERE == kLds && a.lds_ef;
   uint32_t* ef = reinterpret_cast<uint32_t*>(lds_slots + st.nslots);   // [cap], valid when ef_lds
 
   const int size0 = __builtin_amdgcn_readfirstlane(st.size[b]);
@@ -1071,8 +1152,8 @@ __device__ __forceinline__ void lzw_decode_windows(const LzwArgs& a, int b, DecS
   int32_t* ent_tokens = st.ent_tokens + (size_t)b * cap * M;
   int32_t* ent_len = st.ent_len + (size_t)b * cap;
 
-  Table<LDS> t;
-  table_open_all<LDS, W>(a, b, tid, reset, &t);
+  Table<WHERE> t;
+  table_open_all<WHERE, W>(a, b, tid, reset, &t);
   if (ef_lds && !reset) {
     for (int i = tid; i < C; i += W) ef[i] = pack_ef(ent_len[i], ent_tokens[(size_t)i * M]);
   }
@@ -1296,7 +1377,7 @@ __device__ __forceinline__ void lzw_decode_windows(const LzwArgs& a, int b, DecS
     }
   }
 
-  table_close_all<LDS, W>(tid, t);
+  table_close_all<WHERE, W>(tid, t);
   if (reset) {                                  // rows of the codebook that was there before
     for (int i = C + tid; i < size0; i += W) ent_len[i] = 0;
     for (int i = C * M + tid; i < size0 * M; i += W) ent_tokens[i] = -1;
@@ -1313,17 +1394,17 @@ __device__ __forceinline__ void lzw_decode_windows(const LzwArgs& a, int b, DecS
   }
 }
 
-template <int NW, bool LDS>
+template <int NW, int WHERE>
 __global__ void __launch_bounds__(NW * kWave) lzw_decode_kernel(LzwArgs a) {
   __shared__ DecShared<NW> sh;
   const int b = sequence_of_block<NW>(a, reinterpret_cast<BlockOrder&>(sh));
   const bool short_append = !(a.flags & Z2Z_RESET) && call_length(a, b) <= kShortAppend;
-  if (LDS && short_append) {
-    lzw_decode_windows<NW, false, false>(a, b, sh);
+  if (WHERE != kMem && short_append) {
+    lzw_decode_windows<NW, kMem, false>(a, b, sh);
   } else if (a.st.M <= 4) {
-    lzw_decode_windows<NW, LDS, true>(a, b, sh);
+    lzw_decode_windows<NW, WHERE, true>(a, b, sh);
   } else {
-    lzw_decode_windows<NW, LDS, false>(a, b, sh);
+    lzw_decode_windows<NW, WHERE, false>(a, b, sh);
   }
 }
 
@@ -1474,7 +1555,7 @@ __global__ void lzw_clear_entries_kernel(LzwState st) {
 //     where two would keep one workgroup from fitting (2048 documents of 1024 to 4096 tokens, cap 2048: two workgroups 200
 //     us, three 162); where they would not, two sets are faster, by a barrier an iteration (500 sequences: 73, one set 82).
 struct ParsePlan {
-  bool lds;
+  bool lds, tags;
   int nw;
   int sets;                // encoder: RoundSets that the iterations of a window use in turn
   size_t smem;
@@ -1485,6 +1566,8 @@ ParsePlan plan(const z2z_ctx* c, int32_t stride, int32_t flags, bool decode, Lzw
   p.lds = c->st.slots_fit_lds && !tiny_append && c->opt_lzw_kernel != 2;
   p.nw = tiny_append || c->opt_lzw_kernel == 4 ? 1 : stride <= 512 ? 8 : 16;
   p.smem = p.lds ? (size_t)c->st.nslots * sizeof(u64) : 0;
+  p.tags = c->st.tags_fit_lds && p.nw == 16 && c->opt_lzw_kernel != 2;
+  if (p.tags) p.smem = (size_t)c->st.nslots * sizeof(uint32_t);
   const size_t all = (size_t)c->lds_limit, fixed8 = decode ? sizeof(DecShared<8>) : sizeof(EncShared<8, 1>),
                fixed4 = decode ? sizeof(DecShared<4>) : sizeof(EncShared<4, 1>);
   size_t ef = decode && p.lds ? (size_t)c->st.cap * sizeof(uint32_t) : 0;
@@ -1706,32 +1789,32 @@ int z2z_launch_codebook_prefill(z2z_ctx* c, const int32_t* phrases, const int32_
   return Z2Z_OK;
 }
 
-template <bool LDS>
+template <int WHERE>
 static void launch_encode(const LzwArgs& a, int B, int nw, int sets, size_t smem, hipStream_t s) {
   switch (nw) {
-    case 1: hipLaunchKernelGGL((lzw_encode_kernel<1, LDS>), dim3(B), dim3(64), smem, s, a); break;
+    case 1: hipLaunchKernelGGL((lzw_encode_kernel<1, WHERE>), dim3(B), dim3(64), smem, s, a); break;
     case 4:
       if (sets == 1)
-        hipLaunchKernelGGL((lzw_encode_kernel<4, LDS, 1>), dim3(B), dim3(256), smem, s, a);
+        hipLaunchKernelGGL((lzw_encode_kernel<4, WHERE, 1>), dim3(B), dim3(256), smem, s, a);
       else
-        hipLaunchKernelGGL((lzw_encode_kernel<4, LDS>), dim3(B), dim3(256), smem, s, a);
+        hipLaunchKernelGGL((lzw_encode_kernel<4, WHERE>), dim3(B), dim3(256), smem, s, a);
       break;
     case 8:
       if (sets == 1)
-        hipLaunchKernelGGL((lzw_encode_kernel<8, LDS, 1>), dim3(B), dim3(512), smem, s, a);
+        hipLaunchKernelGGL((lzw_encode_kernel<8, WHERE, 1>), dim3(B), dim3(512), smem, s, a);
       else
-        hipLaunchKernelGGL((lzw_encode_kernel<8, LDS>), dim3(B), dim3(512), smem, s, a);
+        hipLaunchKernelGGL((lzw_encode_kernel<8, WHERE>), dim3(B), dim3(512), smem, s, a);
       break;
-    default: hipLaunchKernelGGL((lzw_encode_kernel<16, LDS>), dim3(B), dim3(1024), smem, s, a); break;
+    default: hipLaunchKernelGGL((lzw_encode_kernel<16, WHERE>), dim3(B), dim3(1024), smem, s, a); break;
   }
 }
-template <bool LDS>
+template <int WHERE>
 static void launch_decode(const LzwArgs& a, int B, int nw, size_t smem, hipStream_t s) {
   switch (nw) {
-    case 1: hipLaunchKernelGGL((lzw_decode_kernel<1, LDS>), dim3(B), dim3(64), smem, s, a); break;
-    case 4: hipLaunchKernelGGL((lzw_decode_kernel<4, LDS>), dim3(B), dim3(256), smem, s, a); break;
-    case 8: hipLaunchKernelGGL((lzw_decode_kernel<8, LDS>), dim3(B), dim3(512), smem, s, a); break;
-    default: hipLaunchKernelGGL((lzw_decode_kernel<16, LDS>), dim3(B), dim3(1024), smem, s, a); break;
+    case 1: hipLaunchKernelGGL((lzw_decode_kernel<1, WHERE>), dim3(B), dim3(64), smem, s, a); break;
+    case 4: hipLaunchKernelGGL((lzw_decode_kernel<4, WHERE>), dim3(B), dim3(256), smem, s, a); break;
+    case 8: hipLaunchKernelGGL((lzw_decode_kernel<8, WHERE>), dim3(B), dim3(512), smem, s, a); break;
+    default: hipLaunchKernelGGL((lzw_decode_kernel<16, WHERE>), dim3(B), dim3(1024), smem, s, a); break;
   }
 }
 
@@ -1750,10 +1833,12 @@ int z2z_launch_lzw_encode(z2z_ctx* c, const int32_t* tokens, const int32_t* lens
   a.out_stride = out_stride;
   a.status = status;
   const ParsePlan p = plan(c, stride, flags, false, &a);
-  if (p.lds)
-    launch_encode<true>(a, c->cfg.B, p.nw, p.sets, p.smem, s);
+  if (p.tags)
+    hipLaunchKernelGGL((lzw_encode_kernel<16, kTag>), dim3(c->cfg.B), dim3(1024), p.smem, s, a);
+  else if (p.lds)
+    launch_encode<kLds>(a, c->cfg.B, p.nw, p.sets, p.smem, s);
   else
-    launch_encode<false>(a, c->cfg.B, p.nw, p.sets, 0, s);
+    launch_encode<kMem>(a, c->cfg.B, p.nw, p.sets, 0, s);
   Z2Z_HIP_TRY(hipGetLastError());
   return Z2Z_OK;
 }
@@ -1787,10 +1872,12 @@ int z2z_launch_lzw_decode(z2z_ctx* c, const int32_t* codes, const int32_t* n_cod
     hipLaunchKernelGGL(lzw_decode_serial_kernel<true>, dim3(c->cfg.B), dim3(kWave), p.smem, s, a);
   else if (serial)
     hipLaunchKernelGGL(lzw_decode_serial_kernel<false>, dim3(c->cfg.B), dim3(kWave), 0, s, a);
+  else if (p.tags)
+    hipLaunchKernelGGL((lzw_decode_kernel<16, kTag>), dim3(c->cfg.B), dim3(1024), p.smem, s, a);
   else if (p.lds)
-    launch_decode<true>(a, c->cfg.B, p.nw, p.smem, s);
+    launch_decode<kLds>(a, c->cfg.B, p.nw, p.smem, s);
   else
-    launch_decode<false>(a, c->cfg.B, p.nw, 0, s);
+    launch_decode<kMem>(a, c->cfg.B, p.nw, 0, s);
   if (tail) {
     const int parts = std::min(64, c->num_cu / c->cfg.B);
     hipLaunchKernelGGL(lzw_decode_tail_kernel, dim3(parts, c->cfg.B), dim3(1024), 0, s, a);
@@ -1867,20 +1954,26 @@ int z2z_lzw_prepare(z2z_ctx* c) {
     st.nslots = lds_slots;
     st.slots_fit_lds = 1;
   } else {
-    st.nslots = want;
+    // A table in memory: its tags in LDS, while a sequence has a CU to itself (several on a CU hide the latency of tables in
+    // memory, and the tags would keep them from it).
+    const int tags = (c->lds_limit - kParseStaticLds) / (int)sizeof(uint32_t);
+    st.tags_fit_lds = c->cfg.B <= c->num_cu && floor125 <= tags;
+    st.nslots = st.tags_fit_lds ? std::min(want, tags) : want;
     st.slots_fit_lds = 0;
   }
   st.nslots &= ~1;                                     // whole buckets
-  const void* parse[] = {reinterpret_cast<const void*>(lzw_encode_kernel<1, true>),
-                         reinterpret_cast<const void*>(lzw_encode_kernel<4, true>),
-                         reinterpret_cast<const void*>(lzw_encode_kernel<4, true, 1>),
-                         reinterpret_cast<const void*>(lzw_encode_kernel<8, true, 1>),
-                         reinterpret_cast<const void*>(lzw_encode_kernel<8, true>),
-                         reinterpret_cast<const void*>(lzw_encode_kernel<16, true>),
-                         reinterpret_cast<const void*>(lzw_decode_kernel<1, true>),
-                         reinterpret_cast<const void*>(lzw_decode_kernel<4, true>),
-                         reinterpret_cast<const void*>(lzw_decode_kernel<8, true>),
-                         reinterpret_cast<const void*>(lzw_decode_kernel<16, true>),
+  const void* parse[] = {reinterpret_cast<const void*>(lzw_encode_kernel<1, kLds>),
+                         reinterpret_cast<const void*>(lzw_encode_kernel<4, kLds>),
+                         reinterpret_cast<const void*>(lzw_encode_kernel<4, kLds, 1>),
+                         reinterpret_cast<const void*>(lzw_encode_kernel<8, kLds, 1>),
+                         reinterpret_cast<const void*>(lzw_encode_kernel<8, kLds>),
+                         reinterpret_cast<const void*>(lzw_encode_kernel<16, kLds>),
+                         reinterpret_cast<const void*>(lzw_decode_kernel<1, kLds>),
+                         reinterpret_cast<const void*>(lzw_decode_kernel<4, kLds>),
+                         reinterpret_cast<const void*>(lzw_decode_kernel<8, kLds>),
+                         reinterpret_cast<const void*>(lzw_decode_kernel<16, kLds>),
+                         reinterpret_cast<const void*>(lzw_encode_kernel<16, kTag>),
+                         reinterpret_cast<const void*>(lzw_decode_kernel<16, kTag>),
                          reinterpret_cast<const void*>(lzw_decode_serial_kernel<true>)};
   for (const void* f : parse)
     Z2Z_HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_limit - kParseStaticLds));

@@ -28,6 +28,7 @@ struct LzwState {
   unsigned long long* slots;
   int32_t V, M, cap, nslots;
   int32_t slots_fit_lds;     // the table of one sequence fits the LDS of a CU
+  int32_t tags_fit_lds;      // it does not, but a tag of every slot does
 };
 
 // Where the tile kernels leave their partial (max, sum-exp, argmax) triples: three arrays of `capacity`

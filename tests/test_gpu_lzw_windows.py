@@ -193,6 +193,34 @@ def test_codes_behind_a_full_codebook(M, cap):
     ctx.close()
 
 
+@pytest.mark.parametrize("M,cap,kernel", [(3, 12000, 0), (5, 20000, 0), (8, 23000, 0), (5, 3000, 0), (5, 3000, 2)])
+def test_calls_on_one_codebook(M, cap, kernel):
+    """A codebook emptied twice, then appended to by long, short and single-element calls in both directions: tables in LDS,
+    in memory with their tags in LDS (more than 11000 entries), in memory alone (more than 22400, or as an option)."""
+    from paper_2506_01084_amd import api
+
+    V, B = 3000, 3
+    rng = np.random.default_rng(cap + M)
+    draw = lambda n: np.where(rng.random((B, n)) < 0.3, rng.integers(0, 6, (B, n)), np.minimum(rng.zipf(1.2, (B, n)) - 1, V - 1)).astype(np.int32)
+    enc, dec = _ctx(B, V, M, cap, kernel), _ctx(B, V, M, cap, kernel)
+    s = d = None
+    for n, flags in ((2500, api.RESET), (3100, api.RESET), (2048, api.APPEND), (40, api.APPEND), (1, api.APPEND), (700, api.APPEND)):
+        if flags == api.RESET:
+            s, d = ([oracle.LZWStream(V, M, cap) for _ in range(B)] for _ in range(2))
+        tokens = draw(n)
+        codes, n_codes, st = gpu_encode(enc, tokens, None, flags=flags)
+        toks, n_tok, st2 = gpu_decode(dec, codes, n_codes, out_stride=n, flags=flags)
+        for b in range(B):
+            want, rst = s[b].encode_chunk(tokens[b].tolist())
+            assert int(st[b]) == rst == 0 and codes[b, :n_codes[b]].tolist() == want, (n, flags, b)
+            assert d[b].decode_chunk(want) == (tokens[b].tolist(), 0)
+            assert int(st2[b]) == 0 and toks[b, :n_tok[b]].tolist() == tokens[b].tolist(), (n, flags, b)
+        assert_codebook_equal(enc, [x.entries for x in s], M, cap)
+        assert_codebook_equal(dec, [x.entries for x in d], M, cap)
+    enc.close()
+    dec.close()
+
+
 def _crowded_pairs(V, bits):
     """Pairs of tokens, the most found, whose edges share both of their groups of the round's set (2^bits groups of four):
     beyond eight of them in a window the rest find no slot.  (The hash is the kernel's.)"""
