@@ -8,9 +8,9 @@
 // give the argument why the result is that of the one-element-at-a-time loop.
 //
 // Measured, kernel time encode; decode (before: rounds of 256 elements, four waves, cut at the first element that depends
-// on an entry of the round): 8 sequences of 4096 tokens, M = 3, cap 2048: 110 -> 44 us; 89 -> 32 us.  4 of 32768,
-// M = 4, cap 8192: 691 -> 211; 391 -> 125 -> 98.  16 of 16384, M = 5, cap 16384 (table in memory, its tags in LDS): 657 -> 284 -> 185; 449 -> 157 -> 100.
-// 2048 of 4096: 470 -> 258 -> 180; 395 -> 187 -> 150 (up to four workgroups on a CU).  1 of 512: 24 -> 11.5; 22 -> 10.
+// on an entry of the round): 8 sequences of 4096 tokens, M = 3, cap 2048: 110 -> 44 us; 89 -> 32 -> 28 us.  4 of 32768,
+// M = 4, cap 8192: 691 -> 211; 391 -> 125 -> 84.  16 of 16384, M = 5, cap 16384 (table in memory, its tags in LDS): 657 -> 284 -> 185; 449 -> 157 -> 75.
+// 2048 of 4096: 470 -> 258 -> 180; 395 -> 187 -> 135 (up to four workgroups on a CU).  1 of 512: 24 -> 11.5; 22 -> 10.
 //
 // The codebook is a trie stored as a hash table over its edges: one 64-bit slot = parent code (24 bits)
 // | token (24 bits) | entry index (16 bits), two slots per bucket, two buckets per probe step (Table).  The
@@ -62,8 +62,8 @@ extern __shared__ __align__(16) u64 lds_slots[];   // the sequence's hash table 
 // are ds_read_b128), in global memory (huge capacities, and short appends that touch a few slots), or in global memory
 // with a tag of every slot in LDS: 16 bits of the edge's hash | entry index.  What a probe in memory costs is requests, two
 // of 16 bytes, hit or miss; with the tags a miss is a matter of LDS and a hit one request of 8 bytes, the slot itself.
-// 16 sequences of 16384 tokens, cap 16384, M = 5: encode 272 -> 185 us, decode 156 -> 100; 100 of 8192, cap 12000, M = 3: 134
-// -> 89; 109 -> 69.
+// 16 sequences of 16384 tokens, cap 16384, M = 5: encode 272 -> 185 us, decode 156 -> 100; 100 of 8192, cap 12000, M = 3:
+// 134 -> 89; 109 -> 69.
 enum { kMem, kLds, kTag };
 template <int WHERE>
 struct Table {
@@ -237,6 +237,48 @@ struct Table {
   }
   __device__ __forceinline__ int find_lane(int32_t parent, int32_t tok) const {
     return find_lane(parent, tok, edge_hash(parent, tok));
+  }
+  // Per-lane insertion of an edge that may be there, or be inserted by another lane at the same time: of several lanes with
+  // one edge, one claims a slot (returned) and the others find it (-1; with tags also, now and then, where it is not so: the
+  // slot of a tag claimed in this phase may not be readable yet).  -2: no empty slot, which cannot happen while n > cap.
+  __device__ __forceinline__ int insert_new(int32_t parent, int32_t tok, int idx) const {
+    const u64 key = edge_bits(parent, tok), val = key | (u64)(uint32_t)idx;
+    const uint32_t h = edge_hash(parent, tok);
+    Probe p = probe_init(h);
+    do {
+      for (int tries = 0; tries < 5; ++tries) {     // (a lost slot has filled: at most four times)
+        int at;
+        if (WHERE == kTag) {
+          const Tags t = load_tags(p.b0, p.b1);
+          for (uint32_t which = agree(t, tag_of(h)); which != 0; which &= which - 1) {
+            const int i = __builtin_ctz(which);
+            const u64 slot = g[2 * (i < 2 ? p.b0 : p.b1) + (i & 1)];
+            if (slot == kEmpty || holds(slot, key)) return -1;
+          }
+          at = free_slot(p, t);
+          if (at < 0) break;
+          if (atomicCAS(&tags()[at], ~0u, tag_of(h) | (uint32_t)idx) == ~0u) {
+            g[at] = val;
+            return at;
+          }
+        } else {
+          ulonglong2 a, b;
+          load(p, &a, &b);
+          if (match(a, b, key) >= 0) return -1;
+          at = free_slot(p, a, b);
+          if (at < 0) break;
+          if (atomicCAS(LDS ? &lds_slots[at] : &g[at], kEmpty, val) == kEmpty) return at;
+        }
+      }
+    } while (probe_next(&p));
+    return -2;
+  }
+  __device__ __forceinline__ void remove(int at) const {
+    if (WHERE == kTag) tags()[at] = ~0u;
+    if (LDS)
+      lds_slots[at] = kEmpty;
+    else
+      __hip_atomic_store(&g[at], kEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   // Per-lane insertion of an edge known to be absent (several lanes insert at once: a slot is claimed with a
   // compare-and-swap, and the buckets are looked at again when it was lost).
@@ -1093,17 +1135,22 @@ __global__ void __launch_bounds__(kStepWaves * kWave) lzw_step_update_kernel(Lzw
 // for an entry of this round, from the code before its maker.  Again a recurrence over lower positions, solved by
 // iteration:
 //   1. codes that are base tokens or old entries have their (length, first token); edges between those are looked
-//      up in the table at once.  Codes that name entries of this round start from a guess.
+//      up in the table at once.  Codes that name entries of this round start from a guess of their length.
 //   2. who makes an entry follows from the lengths; the makers' ranks are a prefix count, maker[rank] = position.
 //   3. a code that names entry `rank` of this round takes (length + 1, first token) from the position before its
 //      maker, or is invalid if that entry is made after it.  When nothing changes the values are exact.
-//   4. what 1-3 assume about edges that involve this round's entries (that they are new) is checked: edges a late
-//      look-up finds in the table, and edges proposed twice in the window (the encoder's round set); the window is cut at
-//      the first such position, which the next round meets as its first code, where everything is known.  Streams
-//      of a greedy parse have none.
+//   4. the makers' edges go into the table.  What 1-3 assume about edges that involve this round's entries -- that they are
+//      new -- shows there: if an edge is in the table, or proposed twice in the window, the window's insertions are taken
+//      back, the encoder's round set and late look-ups say where the first such position is, and the window is cut there;
+//      the next round meets it as its first code, where everything is known.  Streams of a greedy parse have none.
 //   5. publish: token offsets are prefix sums of the lengths; a thread writes its code's tokens to the output and,
 //      with the next code's first token behind them, to the row of the entry the next code makes.
-// A chain of entries of this round is at most M long, so two to four iterations are usual.
+// Three to five iterations are usual: who is as long as M, and so makes nothing, moves the ranks behind it.
+//
+// What bounds it: those iterations, two barriers each.  A thread owns what its code does as the FIRST half of an entry, so that
+// an iteration needs no exchange of lengths with the neighbour; the insertion into the table is itself the check of 4.
+// Before (three barriers, a set for the edges of every window), us: 8 sequences of 4096 tokens, M = 3, cap 4096 38 -> 32; 4 of 32768,
+// M = 4, cap 8192 97 -> 84; 16 of 16384, M = 5, cap 16384 100 -> 75; 2048 of up to 4096, M = 3, cap 2048 125 -> 113.
 // ------------------------------------------------------------------------------------------------
 // Codes that the decoder leaves to the kernel behind it, which takes a launch (5 us) where a window of 1024 takes 2.6.
 constexpr int kTailMin = 3072;
@@ -1114,15 +1161,15 @@ struct DecShared {
   static constexpr int kSet = 4 * W;
   uint32_t set[kSet];
   u64 key[W];
-  u64 makes[kMaxWaves];                      // codes that make an entry, a mask per wave
   int32_t ring[2 * W];                       // codes: code p at p & (2 W - 1)
   int32_t code[W];                           // of the window
   uint32_t info[W];                          // pack_ef(length, first token)
-  uint32_t count[kMaxWaves];                 // entries made | tokens << 16 of each wave
-  int32_t changed[2];
+  uint32_t count[kMaxWaves];                 // entries made by each wave; above them whether its makers changed and need others
+  uint32_t tokens[kMaxWaves];                // of each wave's codes
+  int32_t clash;                             // an edge of the window was in the table or proposed twice
   int32_t bad_pos, ovf_pos, cut;             // where the window ends early
   int32_t last_code, last_len, last_tokens, last_made;
-  uint16_t maker[W];                         // position of the code that makes entry `rank` of the round
+  uint16_t parent[W];                        // position of the code before the one that makes entry `rank` of the round
 };
 static_assert(sizeof(DecShared<kMaxWaves>) <= sizeof(EncShared<kMaxWaves, 2>), "one LDS budget for both directions");
 
@@ -1161,7 +1208,6 @@ __device__ __forceinline__ void lzw_decode_windows(const LzwArgs& a, int b, DecS
   int fill = kRing;
   for (int i = tid; i < kRing; i += W) sh.ring[i] = i < n ? in[i] : -1;
   int32_t ahead = fill + tid < n ? in[fill + tid] : -1;
-  if (tid == 0) sh.changed[0] = sh.changed[1] = 0;
   sync_after_global_stores();        // (a table cleared in global memory is read past the L1)
 
   const u64 lanes_below = (1ull << lane) - 1;
@@ -1206,126 +1252,128 @@ __device__ __forceinline__ void lzw_decode_windows(const LzwArgs& a, int b, DecS
     sh.info[tid] = pack_ef(len, first);
     if (tid == 0) sh.bad_pos = sh.ovf_pos = sh.cut = W;
     __syncthreads();
-    const int32_t pk = tid > 0 ? sh.code[tid - 1] : -1;
-    uint32_t pinfo = tid > 0 ? sh.info[tid - 1] : 0u;
+    // this position's part in the entry that the code behind it makes: this code and the first token of that one
+    const int next = tid + 1;
+    const int32_t nk = next < W ? sh.code[next] : -1;
+    const bool next_present = next < W && ci + 1 < n;
+    const bool next_new = next_present && nk >= V + C;
     const int room = cap - C;
-    const bool may_add = tid > 0 && present && pk >= 0 && room > 0;
-    const bool old_parent = pk < V + C;
+    const bool may_add = present && k >= 0 && next_present && room > 0;
     bool taken = false;               // the edge is an entry already
     // (the first code of the window may name the entry it makes itself: its first token is then the previous code's)
-    const int32_t first_guess = tid == 1 && new_entry ? (int32_t)(pinfo & kFirst) : first;
-    if (may_add && old_parent && (!new_entry || tid == 1) && (int)(pinfo >> 28) < M)
-      taken = t.find_lane(pk, first_guess) >= 0;
+    if (may_add && !new_entry && (!next_new || next == 1) && len < M)
+      taken = t.find_lane(k, next_new ? first : (int32_t)(sh.info[next] & kFirst)) >= 0;
 
     // ---- 2., 3. lengths and makers -----------------------------------------------------------------------
     bool makes = false;
-    int rank = 0, incl = 0, n_made = 0, n_tokens = 0;
+    int rank = 0, n_made = 0;
+    const bool has_new = __ballot(new_entry) != 0;
+    bool stepped = true;              // a length of this wave changed in the iteration before
     for (int it = 0; it <= W; ++it) {           // (a position becomes final with every iteration: the bound is never met)
       ++n_rounds;
-      makes = may_add && !taken && (int)(pinfo >> 28) < M;
+      makes = may_add && !taken && len < M;
       const u64 makes_mask = __ballot(makes);
-      const int mylen = tid > 0 ? len : 0;
-      incl = 0;                                 // tokens of the codes up to this one
-#pragma unroll
-      for (int bit = 0; bit < 4; ++bit) {
-        const u64 m = __ballot((mylen >> bit) & 1);
-        incl += (__popcll(m & lanes_below) + ((mylen >> bit) & 1)) << bit;
-      }
-      if (lane == kWave - 1) {
-        sh.makes[w] = makes_mask;
-        sh.count[w] = (uint32_t)__popcll(makes_mask) | ((uint32_t)incl << 16);
-      }
+      if (lane == kWave - 1)
+        sh.count[w] = (uint32_t)__popcll(makes_mask) | (stepped ? 0x80000000u : 0u) | (has_new ? 0x40000000u : 0u);
       __syncthreads();
-      const uint32_t counts = row_scan_add(lane < NW ? sh.count[lane] : 0u);
-      const uint32_t below = w == 0 ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)counts, w == 0 ? 0 : w - 1);
-      const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)counts, NW - 1);
-      rank = (int)(below & 0xFFFFu) + __popcll(makes_mask & lanes_below);
-      incl += (int)(below >> 16);
-      n_made = min((int)(total & 0xFFFFu), room);
-      n_tokens = (int)(total >> 16);
-      if (makes && rank < room) sh.maker[rank] = (uint16_t)tid;
-      if (tid == 0) sh.changed[(it + 1) & 1] = 0;
+      const uint32_t word = lane < NW ? sh.count[lane] : 0u;
+      if (__ballot((word & 0x80000000u) != 0) == 0) break;        // (rank and n_made stand)
+      const uint32_t counts = row_scan_add(word & 0xFFFFu);
+      rank = (w == 0 ? 0 : __builtin_amdgcn_readlane((int)counts, w == 0 ? 0 : w - 1)) + __popcll(makes_mask & lanes_below);
+      n_made = min(__builtin_amdgcn_readlane((int)counts, NW - 1), room);
+      if (__ballot((word & 0x40000000u) != 0) == 0) break;        // no code of the window depends on an entry of it
+      if (makes && rank < room) sh.parent[rank] = (uint16_t)tid;
       __syncthreads();
       bool ch = false;
       if (new_entry) {
         const int e = k - V - C;
-        int len2 = 0;                           // (invalid)
-        int32_t first2 = 0;
-        if (e < n_made) {
-          const int p = sh.maker[e];
-          if (p <= tid) {
-            const uint32_t pi = sh.info[p - 1];
-            len2 = min((int)(pi >> 28) + 1, M);
-            first2 = (int32_t)(pi & kFirst);
-          }
-        }
+        const int p = e < n_made ? (int)sh.parent[e] : W;
+        const uint32_t base = p < tid ? sh.info[p] : 0u;            // (of this iteration or the one before, as it comes)
+        const int len2 = (base >> 28) != 0 ? min((int)(base >> 28) + 1, M) : 0;
+        const int32_t first2 = (int32_t)(base & kFirst);
         ch = len2 != len || first2 != first;
         len = len2;
         first = first2;
         sh.info[tid] = pack_ef(len, first);
       }
-      if (__ballot(ch) != 0 && lane == 0) sh.changed[it & 1] = 1;
-      __syncthreads();
-      if (sh.changed[it & 1] == 0) break;
-      if (tid > 0) pinfo = sh.info[tid - 1];
+      stepped = __ballot(ch) != 0;
     }
 
     // ---- 4. limits of the window --------------------------------------------------------------------------
-    const bool makes_it = makes && rank < room;
-    if (n_made > 1) {
-      const uint32_t h = edge_hash(pk, first);
-      int own = -1;
-      bool clash = false;
-      if (makes_it) {
-        own = Set::insert(sh.set, sh.key, h, round_key(pk, first), tid);
-        if (own == -2) atomicMin(&sh.cut, tid + 1);              // later positions cannot see this edge
-        if (new_entry && tid > 1 && old_parent) clash = t.find_lane(pk, first, h) >= 0;
-      }
-      __syncthreads();
-      if (makes_it && !clash) clash = Set::find(sh.set, sh.key, h, round_key(pk, first), tid) >= 0;
-      if (clash) atomicMin(&sh.cut, tid);
-      if (tid > 0 && present && len == 0) atomicMin(&sh.bad_pos, tid);
-      __syncthreads();
-      if (own >= 0) sh.set[own] = kRoundEmpty;
-    } else {
-      if (makes_it && new_entry && tid > 1 && old_parent && t.find_lane(pk, first) >= 0) atomicMin(&sh.cut, tid);
-      if (tid > 0 && present && len == 0) atomicMin(&sh.bad_pos, tid);
-      __syncthreads();
+    const bool makes_it = makes && rank < room;      // with the code at `next`
+    const int mylen = tid > 0 ? len : 0;
+    int incl = 0;                               // tokens of the codes up to this one
+#pragma unroll
+    for (int bit = 0; bit < 4; ++bit) {
+      const u64 m = __ballot((mylen >> bit) & 1);
+      incl += (__popcll(m & lanes_below) + ((mylen >> bit) & 1)) << bit;
     }
+    if (lane == kWave - 1) sh.tokens[w] = (uint32_t)incl;
+    const u64 bad_mask = __ballot(tid > 0 && present && len == 0);
+    if (bad_mask != 0 && lane == 0) atomicMin(&sh.bad_pos, w * kWave + (int)__builtin_ctzll(bad_mask));
+    if (tid == 0) sh.clash = 0;
+    __syncthreads();
+    const uint32_t tokens = row_scan_add(lane < NW ? sh.tokens[lane] : 0u);
+    incl += w == 0 ? 0 : __builtin_amdgcn_readlane((int)tokens, w == 0 ? 0 : w - 1);
+    const int n_tokens = __builtin_amdgcn_readlane((int)tokens, NW - 1);
     const int bad_pos = sh.bad_pos;
-    int limit = min(min(W, n - cpos + 1), min(bad_pos, sh.cut));    // codes 1 .. limit-1 of the window are taken
+    int limit = min(min(W, n - cpos + 1), bad_pos);                 // codes 1 .. limit-1 of the window are taken
+    int ovf_pos = W;
     if (out != nullptr && n_out + n_tokens > a.out_stride) {        // uniform
       const u64 ovf_mask = __ballot(tid > 0 && present && len > 0 && n_out + incl > a.out_stride);
       if (ovf_mask && lane == 0) atomicMin(&sh.ovf_pos, w * kWave + (int)__builtin_ctzll(ovf_mask));
       __syncthreads();
-      limit = min(limit, sh.ovf_pos);
-      if (sh.ovf_pos < W && limit == sh.ovf_pos) {
-        status |= Z2Z_ST_OVERFLOW;
-        stop = true;
+      ovf_pos = sh.ovf_pos;
+      limit = min(limit, ovf_pos);
+    }
+    if (n_made > 0) {
+      int slot = -2;
+      const int32_t tok = makes_it ? (int32_t)(sh.info[next] & kFirst) : 0;
+      const bool inserts = makes_it && next < limit;
+      if (inserts) slot = t.insert_new(k, tok, C + rank);
+      if (__ballot(inserts && slot < 0) != 0 && lane == 0) sh.clash = 1;
+      __syncthreads();
+      if (sh.clash) {                           // (rare: codes that no greedy parse made)
+        if (slot >= 0) t.remove(slot);
+        sync_after_global_stores();
+        const uint32_t h = edge_hash(k, tok);
+        int own = -1;
+        bool clash = false;
+        if (makes_it) {
+          own = Set::insert(sh.set, sh.key, h, round_key(k, tok), next);
+          if (own == -2) atomicMin(&sh.cut, next + 1);            // later positions cannot see this edge
+          if (next_new && next > 1 && !new_entry) clash = t.find_lane(k, tok, h) >= 0;
+        }
+        __syncthreads();
+        if (makes_it && !clash) clash = Set::find(sh.set, sh.key, h, round_key(k, tok), next) >= 0;
+        if (clash) atomicMin(&sh.cut, next);
+        __syncthreads();
+        if (own >= 0) sh.set[own] = kRoundEmpty;
+        limit = min(limit, sh.cut);
+        if (makes_it && next < limit) t.insert_lane(k, tok, C + rank);
       }
     }
-    if (!stop && bad_pos < W && limit == bad_pos) {
+    if (ovf_pos < W && limit == ovf_pos) {
+      status |= Z2Z_ST_OVERFLOW;
+      stop = true;
+    } else if (bad_pos < W && limit == bad_pos) {
       status |= Z2Z_ST_BAD_CODE;
       stop = true;
     }
 
     // ---- 5. publish ---------------------------------------------------------------------------------------
-    if (makes_it && tid < limit) t.insert_lane(pk, first, C + rank);
-    const int next = tid + 1;
-    const int next_rank = rank + (makes ? 1 : 0);
-    const bool next_makes = next < limit && ((sh.makes[next >> 6] >> (next & 63)) & 1) != 0 && next_rank < room;
-    int32_t* dst = tid > 0 && tid < limit && out != nullptr ? out + n_out + incl - len : nullptr;
-    int32_t* row = next_makes ? ent_tokens + (size_t)(C + next_rank) * M : nullptr;
-    if (dst != nullptr || row != nullptr) {
+    const bool next_makes = makes_it && next < limit;
+    const bool writes = tid > 0 && tid < limit && out != nullptr;
+    if (writes || next_makes) {
       int l = len;
       int32_t kk = k;
       while (kk >= V + C) {                     // entries of this round: last token first (at most M - 1 steps)
-        const int p = sh.maker[kk - V - C];
-        const int32_t tok = (int32_t)(sh.info[p] & kFirst);
+        const int p = sh.parent[kk - V - C];
+        const int32_t tok = (int32_t)(sh.info[p + 1] & kFirst);
         --l;
-        if (dst != nullptr) dst[l] = tok;
-        if (row != nullptr) row[l] = tok;
-        kk = sh.code[p - 1];
+#pragma unroll
+        for (int j = 0; j < kTok; ++j) T[j] = j == l ? tok : T[j];
+        kk = sh.code[p];
       }
       if (kk != k) {
         if (kk < V) {
@@ -1337,25 +1385,29 @@ __device__ __forceinline__ void lzw_decode_windows(const LzwArgs& a, int b, DecS
             if (j < l) T[j] = src[j];
         }
       }
+      if (writes) {
+        int32_t* dst = out + n_out + incl - len;
 #pragma unroll
-      for (int j = 0; j < kTok; ++j) {
-        if (j < l && dst != nullptr) dst[j] = T[j];
-        if (j < l && row != nullptr) row[j] = T[j];
+        for (int j = 0; j < kTok; ++j)
+          if (j < len) dst[j] = T[j];
       }
-      if (row != nullptr) {
+      if (next_makes) {
         const int32_t tok = (int32_t)(sh.info[next] & kFirst);
 #pragma unroll
-        for (int j = 1; j < kTok; ++j)
-          if (j >= len && j < M) row[j] = j == len ? tok : -1;
-        ent_len[C + next_rank] = len + 1;
-        if (ef_lds) ef[C + next_rank] = pack_ef(len + 1, first);
+        for (int j = 0; j < kTok; ++j) T[j] = j < len ? T[j] : j == len ? tok : -1;
+        int32_t* row = ent_tokens + (size_t)(C + rank) * M;
+#pragma unroll
+        for (int j = 0; j < kTok; ++j)
+          if (j < M) row[j] = T[j];
+        ent_len[C + rank] = len + 1;
+        if (ef_lds) ef[C + rank] = pack_ef(len + 1, first);
       }
     }
     if (limit >= 2 && tid == limit - 1) {
       sh.last_code = k;
       sh.last_len = len;
       sh.last_tokens = incl;
-      sh.last_made = min(next_rank, room);
+      sh.last_made = min(rank, room);
     }
     if (fill < n) {                             // the ring takes the next codes in place of those behind the window
       const int cnt = min(W, cpos + limit - 1 + kRing - fill);

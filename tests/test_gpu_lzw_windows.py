@@ -103,7 +103,7 @@ def _random_codes(rng, V, M, cap, n, hot):
     return codes
 
 
-@pytest.mark.parametrize("M,cap", [(3, 5000), (5, 400)])
+@pytest.mark.parametrize("M,cap", [(3, 5000), (5, 400), (4, 12000)])
 def test_decode_of_arbitrary_codes(M, cap):
     """Windows whose codes repeat edges, meet edges of the table and name the window's own entries: cut where they
     must be; then a code that names nothing, and an output row that ends, at places in different windows."""
