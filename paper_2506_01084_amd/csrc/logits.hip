@@ -354,28 +354,35 @@ static int pick_strip_for(const z2z_ctx* c, long long row_tiles, int n_vt, int w
 // Behind other work that has turned the caches over the one launch is 40-60 us slower and the split 2-5.
 // Hence: up to 16 sequences, or more than two rounds, or a last round at least 7/8 full over all rounds, or hyper units that
 // would open another round in one launch.
-// 112 to 255 tiles leave so many CUs to the hyper units that only the last of these counts.  V = 32064, d = 3072 (126 tiles),
-// tiles + hyper units, one launch -> split, on fresh inputs:
-//   above 256   greedy    17 x 4096 (262) 148 -> 104   34 x 2048 (262) 155 -> 132   40 x 2048 160 -> 136   64 x 4096 288 -> 242
+// 112 to 255 tiles leave so many CUs to the hyper units that the last of these decides, on fresh inputs.  V = 32064, d = 3072 (126
+// tiles, which the streaming kernel halves), tiles + hyper units, one launch -> split:
+//   above 256   greedy    17 x 4096 (262) 151 -> 105   34 x 2048 (262) 155 -> 132   40 x 2048 160 -> 136   64 x 4096 288 -> 242
 //               draw      17 x 4096 166 -> 113         34 x 2048 174 -> 144         50 x 2048 191 -> 175   64 x 4096 304 -> 260
-//               filtered  17 x 4096 168 -> 139         34 x 2048 177 -> 151         24 x 4096 179 -> 145   64 x 2048 219 -> 200
-//   up to 256   greedy    24 x 1024 (174) 83 -> 82     draw 24 x 2048 (222) 100 -> 109, 64 x 1024 (254) 111 -> 132
-//               filtered  12 x 2048 (174) 99 -> 132    40 x 1024 (206) 109 -> 141
-// (Units count whole however few entries they have: at least 64 of them, so that they are what opens the round.)
-static bool split_few(const z2z_ctx* c, int rows) {
+//               filtered  17 x 4096 168 -> 139         34 x 2048 183 -> 151         24 x 4096 179 -> 145   64 x 2048 219 -> 200
+//   up to 256   greedy    30 x 2048 (246) 110 -> 113   50 x 1024 (226) 106 -> 109   64 x 1024 (254) 106 -> 117
+//               draw      30 x 2048 115 -> 119         50 x 1024 110 -> 117         64 x 1024 120 -> 128
+//   up to 208   greedy    5 x 1024 (136) 93 -> 64      24 x 1024 (174) 93 -> 80     40 x 1024 (206) 101 -> 97   60 x 256 90 -> 71
+//               draw      12 x 1024 (150) 101 -> 71    8 x 4096 (190) 103 -> 86     40 x 1024 106 -> 104        60 x 256 100 -> 78
+//               filtered  5 x 1024 104 -> 124          16 x 1024 108 -> 126         40 x 1024 119 -> 147 (never there)
+// (Units count whole however few entries they have: above 256 at least 64 of them, so that they are what opens the round.  The
+// figures of 34 x 2048, 40 x 2048 and above and of draws with them are from tiles of 256.)
+static bool split_few(const z2z_ctx* c, int rows, bool filtered) {
   const long long tiles = z2z_logits_mid_tiles(c->cfg.V), slots = (tiles + 255) / 256 * 256;
   int base_columns, hyper_columns;
   z2z_logits_decode_units(&base_columns, &hyper_columns);
   const long long units = (long long)rows * ((c->cfg.cap + hyper_columns - 1) / hyper_columns);
+  const bool full = units >= 64 && tiles + units > slots;
+  const bool halves = !filtered && z2z_logits_mid_columns(c, c->cfg.V) < 256 && 16 * (tiles + units) <= 13 * slots;
   const bool pays = tiles >= 256 ? rows <= 16 || tiles > 512 || 8 * tiles >= 7 * slots || tiles + units > slots
-                                 : tiles >= 112 && units >= 64 && tiles + units > slots;
+                                 : tiles >= 112 && (full || halves);
   return rows > 4 && rows <= 64 && c->opt_decode_kernel == 0 && c->opt_logits_kernel == 0 && pays && z2z_logits_mid_ok(c, rows);
 }
 
 // Parts per row that any kind of step may leave (hyper units of 64 rows): every step sizes the scratch for all of them,
 // so that a greedy one can be captured behind an eager draw at the same shape and the other way round.
 static size_t step_parts(const z2z_ctx* c) {
-  return (size_t)(c->cfg.V + 255) / 256 + (size_t)(c->cfg.cap + 63) / 64;
+  const int columns = z2z_logits_mid_columns(c, c->cfg.V);
+  return (size_t)(c->cfg.V + columns - 1) / columns + (size_t)(c->cfg.cap + 63) / 64;
 }
 
 int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t rows_per_seq, const void* W_base,
@@ -400,7 +407,7 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
   // Its base units serve 64 rows per pass over W_base, each pass at about the cost of the first; from the second
   // pass on the tile kernel takes the base vocabulary (all rows at once) and only the hyper units run here
   const bool decode_step = rows_per_seq == 1 && c->decode_ready && c->opt_decode_kernel != 1;
-  const bool decode_split = decode_step && fast_ok && (rows > 64 || split_few(c, rows)) && c->opt_logits_kernel != 1;
+  const bool decode_split = decode_step && fast_ok && (rows > 64 || split_few(c, rows, false)) && c->opt_logits_kernel != 1;
   // a few rows per sequence (2..64: a verification step over drafted codes, a short chunk): every sequence's
   // W_hyper meets only its own rows, so the hyper part is bandwidth-bound like the decode step's; it goes to
   // that kernel's matrix-core units (one pass over each W_hyper), the base vocabulary to the tile kernel
@@ -450,7 +457,8 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
       strip_h = unit * pick_strip_for(c, tiles_h, units_h, 1024);
     }
   }
-  const int base_strips = (base_vt + strip_b - 1) / strip_b;
+  const int mid_columns = z2z_logits_mid_columns(c, V);
+  const int base_strips = mid_base ? (V + mid_columns - 1) / mid_columns : (base_vt + strip_b - 1) / strip_b;
   int hyp_strips = cap > 0 ? (hyp_vt + strip_h - 1) / strip_h : 0;
   int seq_unit = 0;
   if (decode_split || seq_split) {
@@ -544,7 +552,7 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
   const bool timed = c->opt_timing && c->n_timed < Z2Z_MAX_TIMED && c->ev_created;
   // 65..192 rows, and fewer by the rule of a greedy step: the base vocabulary goes to the weight-streaming kernel (with the
   // tile kernel's sampling epilogues)
-  const bool mid_base = (rows > 64 || split_few(c, rows)) && c->opt_logits_kernel == 0 && z2z_logits_mid_ok(c, rows);
+  const bool mid_base = (rows > 64 || split_few(c, rows, top_k > 0 || top_p < 1.0f)) && c->opt_logits_kernel == 0 && z2z_logits_mid_ok(c, rows);
   const bool timed_pair = timed && mid_base && rows <= 64;       // a split step's two launches are timed together
   if (top_k <= 0 && top_p >= 1.0f && (rows > 128 || mid_base) && c->cfg.d % 64 == 0 && c->fast_ready &&
       c->opt_logits_kernel != 1) {
@@ -553,7 +561,8 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     // (with the draw folded into its epilogue) and the hyper units run alone
     const int base_vt = (c->cfg.V + 255) / 256;
     const int strip_b = mid_base ? 1 : pick_strip_for(c, (rows + 255) / 256, base_vt);
-    const int base_strips = (base_vt + strip_b - 1) / strip_b;
+    const int mid_columns = z2z_logits_mid_columns(c, c->cfg.V);
+    const int base_strips = mid_base ? (c->cfg.V + mid_columns - 1) / mid_columns : (base_vt + strip_b - 1) / strip_b;
     const int unit = z2z_logits_decode_hyper_unit(c);
     n_parts = base_strips + (c->cfg.cap + unit - 1) / unit;
     rc = ensure_scratch(c, (size_t)n_parts * rows, s);
@@ -633,11 +642,12 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     const int base_vt = (c->cfg.V + 255) / 256;
     int strip_b = mid_base ? 1 : pick_strip_for(c, (rows + 255) / 256, base_vt);
     if (strip_b > 2) strip_b = 2;
-    const int base_strips = (base_vt + strip_b - 1) / strip_b;
+    const int mid_columns = z2z_logits_mid_columns(c, c->cfg.V);
+    const int base_strips = mid_base ? (c->cfg.V + mid_columns - 1) / mid_columns : (base_vt + strip_b - 1) / strip_b;
     int unit_base, unit_hyper;
     z2z_logits_decode_units(&unit_base, &unit_hyper);
     n_parts = base_strips + (c->cfg.cap + unit_hyper - 1) / unit_hyper;
-    base_columns = strip_b * 256;
+    base_columns = mid_base ? mid_columns : strip_b * 256;
     LogitsArgs a;
     memset(&a, 0, sizeof(a));
     a.H = H;

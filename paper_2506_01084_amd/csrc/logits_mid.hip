@@ -32,19 +32,22 @@ namespace {
 
 using namespace z2z_logits;
 
-constexpr int M_WAVES = 8;
-constexpr int M_THREADS = 64 * M_WAVES;
+constexpr int M_WAVES = 8;                // of a workgroup; four where tiles of 256 weight rows are too few for the CUs
 constexpr int M_WT = 32 * M_WAVES;        // weight rows of a workgroup's tile
 constexpr int M_HT = 192;                 // hidden rows of a call at most (the builds below: 2, 4 or 6 blocks of 32)
 constexpr int M_MAX_ROWS = M_HT;
 constexpr int M_SLAB = 128;               // bytes per row per K slab (64 bf16)
-// LDS per build (blocks of 32 hidden rows): stages of a slab's hidden rows, and the waves' rings with what is left.
-constexpr int mid_stages(int njv) { return njv == 6 ? 2 : 3; }
-constexpr int mid_ring(int njv) { return njv == 2 ? 4 : 3; }
-constexpr int mid_lds(int njv) { return mid_stages(njv) * 32 * njv * M_SLAB + M_WAVES * 32 * M_SLAB * mid_ring(njv); }
-constexpr int M_LDS_MAX = mid_lds(2) > mid_lds(4) ? mid_lds(2) : mid_lds(4);
-static_assert(M_LDS_MAX <= 160 * 1024 && mid_lds(6) <= M_LDS_MAX, "");
-static_assert(M_WAVES * M_HT * (int)(sizeof(Triple) + sizeof(Draw)) <= mid_lds(6), "the waves' triples are merged in the idle stages and rings");
+// LDS per build (blocks of 32 hidden rows, waves): stages of a slab's hidden rows, and slots of the waves' rings.  Four waves
+// have the CU to themselves and ask for both up to five slabs ahead.
+constexpr int mid_stages(int njv, int waves) { return waves == 4 ? (njv == 2 ? 6 : njv == 4 ? 5 : 4) : njv == 6 ? 2 : 3; }
+constexpr int mid_ring(int njv, int waves) { return waves == 4 ? mid_stages(njv, 4) : njv == 2 ? 4 : 3; }
+constexpr int mid_lds(int njv, int waves) {
+  return mid_stages(njv, waves) * 32 * njv * M_SLAB + waves * 32 * M_SLAB * mid_ring(njv, waves);
+}
+constexpr int M_LDS_MAX = 160 * 1024;
+static_assert(mid_lds(2, 8) <= M_LDS_MAX && mid_lds(4, 8) <= M_LDS_MAX && mid_lds(6, 8) <= M_LDS_MAX, "");
+static_assert(mid_lds(2, 4) <= M_LDS_MAX && mid_lds(4, 4) <= M_LDS_MAX && mid_lds(6, 4) <= M_LDS_MAX, "");
+static_assert(M_WAVES * M_HT * (int)(sizeof(Triple) + sizeof(Draw)) <= mid_lds(6, 8), "the waves' triples are merged in the idle stages and rings");
 
 // 16 bytes per lane, global -> LDS without passing through registers (as in the tile kernel): address = 64-bit
 // scalar base + 32-bit per-lane offset; the LDS address is the wave-uniform byte offset in M0 plus 16 * lane.
@@ -80,13 +83,13 @@ __device__ __forceinline__ uint32_t lds_offset_of(const void* p) {
 // (a.sample = 2) -- the tile kernel's epilogues for its modes 0, 6 and 7; 3 = a dense layer with K split over
 // gridDim.y workgroups per tile: the fp32 partial tile goes to a.partial[ks][row][col] (the tile kernel's mode 5);
 // 4, 5, 6 = 0, 1, 2 with the sums in levels, for a step of up to 64 sequences.
-template <int NJV, int SMODE>
+template <int NJV, int SMODE, int WAVES>
 __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int half = lane >> 5;
-  constexpr int STAGES = mid_stages(NJV), RING = mid_ring(NJV);
+  constexpr int STAGES = mid_stages(NJV, WAVES), RING = mid_ring(NJV, WAVES), TILE = 32 * WAVES;
   constexpr int STAGE = 32 * NJV * M_SLAB, STAGE_BYTES = STAGES * STAGE;
   constexpr int W_SLAB = 32 * M_SLAB;                      // a wave's weights of one slab
   const int vt = blockIdx.x;                               // weight tile (and one row tile: a call has at most M_HT rows)
@@ -96,7 +99,7 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
   if (r_end <= 0) return;                                  // (the whole workgroup)
   const int nr = min(32 * NJV, r_end);                     // valid hidden rows
   const int n_valid = a.w_rows;
-  const int v0 = vt * M_WT;
+  const int v0 = vt * TILE;
   const size_t row_bytes = (size_t)a.d * 2;
   const int ks = SMODE == 3 ? (int)blockIdx.y : 0;
   const int slab0 = SMODE == 3 ? ks * a.slabs_per_part : 0;
@@ -133,21 +136,21 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
   // hidden rows: the 4 NJV groups of 8 rows of a slab are dealt to the waves, group g = i * 8 + wave for the
   // wave's i-th request; lane l moves, for row g * 8 + (l >> 3), the chunk that lands at position l & 7 of the row's
   // 128 LDS bytes: chunk (l & 7) ^ ((row >> 1) & 7).  Rows past the last valid one read the last valid one.
-  constexpr int HL = (4 * NJV) / M_WAVES;                  // requests per wave and slab
-  static_assert(HL * M_WAVES == 4 * NJV, "whole groups per wave");
+  constexpr int HL = (4 * NJV) / WAVES;                  // requests per wave and slab
+  static_assert(HL * WAVES == 4 * NJV, "whole groups per wave");
   const unsigned char* Ht = reinterpret_cast<const unsigned char*>(a.H);
   const uint32_t lds_base = lds_offset_of(lds);
   uint32_t hsrc[HL];
 #pragma unroll
   for (int i = 0; i < HL; ++i) {
-    const int row = (i * M_WAVES + wave) * 8 + (lane >> 3);
+    const int row = (i * WAVES + wave) * 8 + (lane >> 3);
     hsrc[i] = (uint32_t)(min(row, nr - 1) * (int)row_bytes + (((lane & 7) ^ ((row >> 1) & 7)) << 4));
   }
   auto issue_h = [&](int slab, int stage) {
     const unsigned char* p = Ht + (size_t)slab_at(slab) * M_SLAB;
 #pragma unroll
     for (int i = 0; i < HL; ++i)
-      load16_to_lds(p, hsrc[i], lds_base + (uint32_t)(stage * STAGE + (i * M_WAVES + wave) * 1024));
+      load16_to_lds(p, hsrc[i], lds_base + (uint32_t)(stage * STAGE + (i * WAVES + wave) * 1024));
   };
   // operand reads: block j, row lane & 31, logical chunk 2 q + half
   const int sw = (lane >> 1) & 7;
@@ -209,7 +212,9 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
   // wave's ring slot s % RING.  Requested during the step: the hidden rows of slab s + STAGES - 1 (HL requests), then the
   // weights of slab s + RING - 1 (4), both into what step s - 1 has read.  At its end slab s + 1 must have landed: KEEP
   // requests come behind the later of its two.  The last steps request nothing that does not exist, and wait for all.
-  constexpr int KEEP = STAGES == 3 ? HL + 4 * (RING - 2) : 4;
+  constexpr int BEHIND_H = 4 + (STAGES - 2) * (HL + 4), BEHIND_W = (RING - 2) * (HL + 4);
+  constexpr int KEEP = BEHIND_H < BEHIND_W ? BEHIND_H : BEHIND_W;
+  static_assert(KEEP < 64, "");
   int stage = 0, slot = 0;
   auto step_compute = [&]() {
     const unsigned char* As = lds + STAGE_BYTES + wave * (RING * W_SLAB) + slot * W_SLAB + offB;
@@ -223,12 +228,11 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
     stage = stage == STAGES - 1 ? 0 : stage + 1;
     slot = slot == RING - 1 ? 0 : slot + 1;
   };
-  issue_h(0, 0);
-  issue_w(0, 0);
-  if (STAGES == 3 && n_slabs > 1) issue_h(1, 1);
 #pragma unroll
-  for (int u = 1; u < RING - 1; ++u)
-    if (u < n_slabs) issue_w(u, u);
+  for (int u = 0; u < (RING > STAGES ? RING : STAGES) - 1; ++u) {
+    if (u < STAGES - 1 && u < n_slabs) issue_h(u, u);
+    if (u < RING - 1 && u < n_slabs) issue_w(u, u);
+  }
   if (n_slabs >= RING - 1)
     wait_loads<(STAGES - 2) * HL + 4 * (RING - 2)>();
   else
@@ -279,7 +283,7 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
   else if (SMODE == 2 || SMODE == 6)
     fold_tile_store<1, NJV>(acc, run, a, 0, r_end, col_base, n_valid);
   else
-    fold_tile<1, NJV>(acc, run, col_base, a.col0, n_valid, v0 + M_WT > n_valid);
+    fold_tile<1, NJV>(acc, run, col_base, a.col0, n_valid, v0 + TILE > n_valid);
 #pragma unroll
   for (int j = 0; j < NJV; ++j) {                          // lanes l and l + 32 hold the same hidden row
     Triple o;
@@ -296,7 +300,7 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
     }
   }
   Triple* xch = reinterpret_cast<Triple*>(lds);            // [wave][hidden row of the tile]
-  Draw* xdr = reinterpret_cast<Draw*>(xch + M_WAVES * M_HT);
+  Draw* xdr = reinterpret_cast<Draw*>(xch + WAVES * M_HT);
   if (lane < 32) {
 #pragma unroll
     for (int j = 0; j < NJV; ++j) {
@@ -308,14 +312,14 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
   if (tid < nr) {
     Triple t = xch[tid];
 #pragma unroll
-    for (int w = 1; w < M_WAVES; ++w) merge_triple(t, xch[w * M_HT + tid]);
+    for (int w = 1; w < WAVES; ++w) merge_triple(t, xch[w * M_HT + tid]);
     const size_t p = (size_t)tid * a.n_parts + a.part0 + vt;
     a.part_m[p] = t.m;
     a.part_s[p] = t.s;
     if (SMODE == 1 || SMODE == 5) {
       Draw dw = xdr[tid];
 #pragma unroll
-      for (int w = 1; w < M_WAVES; ++w) merge_draw(dw, xdr[w * M_HT + tid]);
+      for (int w = 1; w < WAVES; ++w) merge_draw(dw, xdr[w * M_HT + tid]);
       a.part_v[p] = dw.v;
       a.part_l[p] = dw.l;
       a.part_i[p] = dw.i;
@@ -325,17 +329,17 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
   }
 }
 
-template <int NJV, int SMODE>
-__global__ void __launch_bounds__(M_THREADS) logits_mid_kernel(LogitsArgs a) {
+template <int NJV, int SMODE, int WAVES = M_WAVES>
+__global__ void __launch_bounds__(64 * WAVES) logits_mid_kernel(LogitsArgs a) {
   extern __shared__ __align__(1024) unsigned char lds[];
   if constexpr (SMODE == 3 && NJV == 4) {
     // (the rows that exist may be half of those laid out: known here only)
     if ((a.rows_dev ? min(a.rows, *a.rows_dev) : a.rows) <= 64)
-      mid_tile<2, SMODE>(a, lds);
+      mid_tile<2, SMODE, WAVES>(a, lds);
     else
-      mid_tile<4, SMODE>(a, lds);
+      mid_tile<4, SMODE, WAVES>(a, lds);
   } else {
-    mid_tile<NJV, SMODE>(a, lds);
+    mid_tile<NJV, SMODE, WAVES>(a, lds);
   }
 }
 
@@ -345,7 +349,44 @@ bool z2z_logits_mid_ok(const z2z_ctx* c, int rows) {
   return c->mid_ready && c->cfg.dtype == Z2Z_BF16 && c->cfg.d % 64 == 0 && rows >= 1 && rows <= M_MAX_ROWS;
 }
 
-// The base part of a call: one part per tile of 256 weight rows.  a: H, rows, d, the part arrays, n_parts, part0
+// Columns of a part: 256, or 128 (workgroups of four waves) where that gives every tile a CU of its own and 256 would leave
+// half of the CUs without one.  V = 32064, d = 3072 (126 tiles of 256), whole calls in us, 256 -> 128: 2 x 5 rows 88 -> 71, 8 x 8 82
+// -> 63, 3 x 36 91 -> 74, 180 131 -> 117; steps of 17 sequences, 4096 entries each, 118 -> 105, 90 162 -> 146, a draw of 150 264 -> 247.
+int z2z_logits_mid_columns(const z2z_ctx* c, int w_rows) {
+  return (w_rows + M_WT - 1) / M_WT * 2 <= c->num_cu ? M_WT / 2 : M_WT;
+}
+
+template <int WAVES>
+static void launch_mid(const LogitsArgs& a, hipStream_t s) {
+  const dim3 grid((unsigned)a.n_vtiles), block(64 * WAVES);
+  const int blocks = a.rows <= 64 ? 2 : (a.rows <= 128 ? 4 : 6);
+  if (a.sample == 1) {
+    if (blocks == 2)
+      hipLaunchKernelGGL((logits_mid_kernel<2, 5, WAVES>), grid, block, mid_lds(2, WAVES), s, a);
+    else if (blocks == 4)
+      hipLaunchKernelGGL((logits_mid_kernel<4, 1, WAVES>), grid, block, mid_lds(4, WAVES), s, a);
+    else
+      hipLaunchKernelGGL((logits_mid_kernel<6, 1, WAVES>), grid, block, mid_lds(6, WAVES), s, a);
+  } else if (a.sample == 2) {
+    if (blocks == 2)
+      hipLaunchKernelGGL((logits_mid_kernel<2, 6, WAVES>), grid, block, mid_lds(2, WAVES), s, a);
+    else if (blocks == 4)
+      hipLaunchKernelGGL((logits_mid_kernel<4, 2, WAVES>), grid, block, mid_lds(4, WAVES), s, a);
+    else
+      hipLaunchKernelGGL((logits_mid_kernel<6, 2, WAVES>), grid, block, mid_lds(6, WAVES), s, a);
+  } else {
+    if (blocks == 2 && a.rows_per_seq == 1)
+      hipLaunchKernelGGL((logits_mid_kernel<2, 4, WAVES>), grid, block, mid_lds(2, WAVES), s, a);
+    else if (blocks == 2)
+      hipLaunchKernelGGL((logits_mid_kernel<2, 0, WAVES>), grid, block, mid_lds(2, WAVES), s, a);
+    else if (blocks == 4)
+      hipLaunchKernelGGL((logits_mid_kernel<4, 0, WAVES>), grid, block, mid_lds(4, WAVES), s, a);
+    else
+      hipLaunchKernelGGL((logits_mid_kernel<6, 0, WAVES>), grid, block, mid_lds(6, WAVES), s, a);
+  }
+}
+
+// The base part of a call: one part per tile of z2z_logits_mid_columns weight rows.  a: H, rows, d, the part arrays, n_parts, part0
 // filled by the caller; with a.sample = 1 or 2 also the generator words, inv_temperature and part_v / part_l or
 // logits / ld, as for the tile kernel's sampling modes.
 int z2z_launch_logits_mid(z2z_ctx* c, LogitsArgs a, const void* W, int w_rows, int col0, hipStream_t s) {
@@ -353,40 +394,19 @@ int z2z_launch_logits_mid(z2z_ctx* c, LogitsArgs a, const void* W, int w_rows, i
   a.W = W;
   a.w_rows = w_rows;
   a.col0 = col0;
-  a.n_vtiles = (w_rows + M_WT - 1) / M_WT;
+  const int columns = z2z_logits_mid_columns(c, w_rows);
+  a.n_vtiles = (w_rows + columns - 1) / columns;
   a.once = (size_t)w_rows * a.d * sizeof(uint16_t) > kKeepBytes;
   c->n_launch[Z2Z_KERNEL_MID]++;
   // (two workgroups of the 64-row build per weight tile for 65..128 rows, sharing the tile's weights through an
   // XCD's L2, measured slower than one of the 128-row build: 383 against 293 us at config 2's shape)
-  const dim3 grid((unsigned)a.n_vtiles), block(M_THREADS);
   // builds: 2, 4 or 6 blocks of 32 hidden rows; the sampling calls come with one row per sequence.  (8 blocks, up to 256
   // rows, measured level with the tile kernel when weights still went through registers: 650 against 645 us for a decode step of
   // 256 sequences.)
-  const int blocks = a.rows <= 64 ? 2 : (a.rows <= 128 ? 4 : 6);
-  if (a.sample == 1) {
-    if (blocks == 2)
-      hipLaunchKernelGGL((logits_mid_kernel<2, 5>), grid, block, mid_lds(2), s, a);
-    else if (blocks == 4)
-      hipLaunchKernelGGL((logits_mid_kernel<4, 1>), grid, block, mid_lds(4), s, a);
-    else
-      hipLaunchKernelGGL((logits_mid_kernel<6, 1>), grid, block, mid_lds(6), s, a);
-  } else if (a.sample == 2) {
-    if (blocks == 2)
-      hipLaunchKernelGGL((logits_mid_kernel<2, 6>), grid, block, mid_lds(2), s, a);
-    else if (blocks == 4)
-      hipLaunchKernelGGL((logits_mid_kernel<4, 2>), grid, block, mid_lds(4), s, a);
-    else
-      hipLaunchKernelGGL((logits_mid_kernel<6, 2>), grid, block, mid_lds(6), s, a);
-  } else {
-    if (blocks == 2 && a.rows_per_seq == 1)
-      hipLaunchKernelGGL((logits_mid_kernel<2, 4>), grid, block, mid_lds(2), s, a);
-    else if (blocks == 2)
-      hipLaunchKernelGGL((logits_mid_kernel<2, 0>), grid, block, mid_lds(2), s, a);
-    else if (blocks == 4)
-      hipLaunchKernelGGL((logits_mid_kernel<4, 0>), grid, block, mid_lds(4), s, a);
-    else
-      hipLaunchKernelGGL((logits_mid_kernel<6, 0>), grid, block, mid_lds(6), s, a);
-  }
+  if (columns == M_WT)
+    launch_mid<M_WAVES>(a, s);
+  else
+    launch_mid<M_WAVES / 2>(a, s);
   Z2Z_HIP_TRY(hipGetLastError());
   return Z2Z_OK;
 }
@@ -436,11 +456,11 @@ int z2z_launch_linear_mid(z2z_ctx* c, const void* A, const void* W, int R, const
   a.once = once ? 1 : 0;
   *ksplit_out = ksplit;
   c->n_launch[Z2Z_KERNEL_MID]++;
-  const dim3 grid((unsigned)n_vt, (unsigned)ksplit), block(M_THREADS);
+  const dim3 grid((unsigned)n_vt, (unsigned)ksplit), block(64 * M_WAVES);
   if (R <= 64)
-    hipLaunchKernelGGL((logits_mid_kernel<2, 3>), grid, block, mid_lds(2), s, a);
+    hipLaunchKernelGGL((logits_mid_kernel<2, 3>), grid, block, mid_lds(2, M_WAVES), s, a);
   else
-    hipLaunchKernelGGL((logits_mid_kernel<4, 3>), grid, block, M_LDS_MAX, s, a);
+    hipLaunchKernelGGL((logits_mid_kernel<4, 3>), grid, block, mid_lds(2, M_WAVES) > mid_lds(4, M_WAVES) ? mid_lds(2, M_WAVES) : mid_lds(4, M_WAVES), s, a);
   Z2Z_HIP_TRY(hipGetLastError());
   return Z2Z_OK;
 }
@@ -449,19 +469,29 @@ int z2z_logits_mid_tiles(int w_rows) { return (w_rows + M_WT - 1) / M_WT; }
 
 int z2z_logits_mid_prepare(z2z_ctx* c) {
   if (c->lds_limit < M_LDS_MAX) return Z2Z_EUNSUPPORTED;
-  const void* kernels[12] = {reinterpret_cast<const void*>(logits_mid_kernel<2, 6>),
-                            reinterpret_cast<const void*>(logits_mid_kernel<2, 5>),
-                            reinterpret_cast<const void*>(logits_mid_kernel<2, 4>),
-                            reinterpret_cast<const void*>(logits_mid_kernel<2, 3>),
-                            reinterpret_cast<const void*>(logits_mid_kernel<4, 3>),
-                            reinterpret_cast<const void*>(logits_mid_kernel<2, 0>),
-                            reinterpret_cast<const void*>(logits_mid_kernel<4, 0>),
-                            reinterpret_cast<const void*>(logits_mid_kernel<4, 1>),
-                            reinterpret_cast<const void*>(logits_mid_kernel<4, 2>),
-                            reinterpret_cast<const void*>(logits_mid_kernel<6, 0>),
-                            reinterpret_cast<const void*>(logits_mid_kernel<6, 1>),
-                            reinterpret_cast<const void*>(logits_mid_kernel<6, 2>)};
-  for (int k = 0; k < 12; ++k)
-    Z2Z_HIP_TRY(hipFuncSetAttribute(kernels[k], hipFuncAttributeMaxDynamicSharedMemorySize, M_LDS_MAX));
+  const void* kernels[] = {reinterpret_cast<const void*>(logits_mid_kernel<2, 3>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<4, 3>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<2, 0, M_WAVES>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<2, 4, M_WAVES>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<2, 5, M_WAVES>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<2, 6, M_WAVES>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<4, 0, M_WAVES>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<4, 1, M_WAVES>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<4, 2, M_WAVES>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<6, 0, M_WAVES>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<6, 1, M_WAVES>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<6, 2, M_WAVES>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<2, 0, M_WAVES / 2>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<2, 4, M_WAVES / 2>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<2, 5, M_WAVES / 2>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<2, 6, M_WAVES / 2>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<4, 0, M_WAVES / 2>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<4, 1, M_WAVES / 2>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<4, 2, M_WAVES / 2>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<6, 0, M_WAVES / 2>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<6, 1, M_WAVES / 2>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<6, 2, M_WAVES / 2>)};
+  for (const void* k : kernels)
+    Z2Z_HIP_TRY(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, M_LDS_MAX));
   return Z2Z_OK;
 }

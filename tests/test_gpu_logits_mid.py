@@ -67,6 +67,17 @@ def _call(ctx, d_H, rows_per_seq, d_Wb, d_Wh):
     (6, 30, 9000, 4096, 3, 40, "mean"),          # 180 rows at the benchmark's width
     (6, 30, 16500, 4096, 3, 40, "mean"),         # 135 MB of weights: past the caches, in the 192-row build
     (5, 20, 16500, 4096, 3, 40, "mean"),         # ... in the 128-row build
+    # (up to 128 tiles of 256 the tiles have 128 columns; above: every build, around the slots of its ring)
+    (2, 5, 33000, 256, 3, 30, "mean"),
+    (1, 64, 32800, 320, 3, 0, "mean"),
+    (65, 1, 32769, 192, 3, 300, "mean"),
+    (2, 60, 33000, 704, 3, 20, "mean"),
+    (192, 1, 32900, 192, 3, 0, "mean"),
+    (3, 60, 33300, 448, 4, 100, "weighted"),
+    (1, 64, 32768, 256, 3, 0, "mean"),           # 128 tiles: halved
+    (3, 50, 300, 256, 3, 40, "mean"),            # four slabs in the 192-row build of half tiles: its ring exactly
+    (3, 40, 400, 320, 3, 40, "mean"),            # five in the 128-row build
+    (1, 60, 400, 448, 3, 40, "mean"),            # seven in the 64-row build
 ])
 def test_streaming_kernel_every_row_ragged(B, rows_per_seq, V, d, M, cap, pool):
     import torch

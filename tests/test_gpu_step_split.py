@@ -35,6 +35,10 @@ pytestmark = pytest.mark.gpu
     (64, 49200, 128, 100, 1),     # 193 tiles and 64 units: 257
     (63, 49500, 128, 100, 0),     # 194 tiles, 63 units
     (9, 50000, 256, 3600, 1),     # 196 tiles, 72 units, the last of a sequence nearly empty
+    (20, 32700, 384, 500, 1),     # 128 tiles, halved; 20 units: 148
+    (40, 28500, 1664, 700, 1),    # 112 tiles, halved, 80 units: 192
+    (41, 32768, 256, 700, 0),     # 128 tiles and 82 units: 210
+    (8, 32769, 128, 40, 0),       # 129 tiles
 ])
 def test_split_step(B, V, d, cap, split):
     import torch
@@ -83,6 +87,8 @@ def test_split_step(B, V, d, cap, split):
     (64, 65500, 256, 100, 0, 0.8),
     (17, 131073, 128, 40, 0, 1.0),      # 513 tiles
     (33, 131073, 128, 40, 50, 0.9),
+    (20, 32700, 384, 500, 0, 1.0),      # tiles of 128 columns
+    (33, 32768, 256, 2000, 50, 0.9),    # ... whose parts the filters' kernels read
 ])
 def test_split_draws_match_one_launch(B, V, d, cap, top_k, top_p):
     """Draws of a split step against those of the decode kernel in one launch (both oracle-tested on smaller vocabularies):
