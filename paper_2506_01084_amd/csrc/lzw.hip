@@ -602,10 +602,10 @@ struct RoundSet {
 };
 
 constexpr int kMaxWaves = 16;
-template <int NW, int SETS>
+template <int NW, int SETS, int PER = 4>
 struct EncShared {
   static constexpr int W = NW * kWave;       // positions of a window
-  static constexpr int kSet = 4 * W;
+  static constexpr int kSet = PER * W;       // slots of a set
   uint32_t set[SETS][kSet];                  // edges proposed (two sets: in an even / odd iteration)
   u64 key[W];
   u64 skip[kMaxWaves];                       // skip function of each wave's positions
@@ -621,10 +621,10 @@ struct EncShared {
 
 constexpr int kParseStaticLds = (int)sizeof(EncShared<kMaxWaves, 2>) + 256;    // + alignment slack
 
-template <int NW, int SETS, int WHERE, bool M4>
-__device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, int b, EncShared<NW, SETS>& sh) {
+template <int NW, int SETS, int PER, int WHERE, bool M4>
+__device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, int b, EncShared<NW, SETS, PER>& sh) {
   constexpr int W = NW * kWave;
-  constexpr int kSet = EncShared<NW, SETS>::kSet, kRing = 2 * W;
+  constexpr int kSet = EncShared<NW, SETS, PER>::kSet, kRing = 2 * W;
   typedef RoundSet<kSet> Set;
   const LzwState& st = a.st;
   const int tid = threadIdx.x;
@@ -919,17 +919,17 @@ __device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, int b, EncS
 // A short appended call touches a handful of slots: probing the table where it lives, in global memory,
 // is cheaper than staging all of it in LDS and writing it back (the length is known only on the device,
 // so the LDS kernels take this decision per sequence).
-template <int NW, int WHERE, int SETS = 2>
+template <int NW, int WHERE, int SETS = 2, int PER = 4>
 __global__ void __launch_bounds__(NW * kWave, SETS == 1 ? 8 : 1) lzw_encode_kernel(LzwArgs a) {
-  __shared__ EncShared<NW, SETS> sh;
+  __shared__ EncShared<NW, SETS, PER> sh;
   const int b = sequence_of_block<NW>(a, reinterpret_cast<BlockOrder&>(sh));
   const bool short_append = !(a.flags & Z2Z_RESET) && call_length(a, b) <= kShortAppend;
   if (WHERE != kMem && short_append) {
-    lzw_encode_windows<NW, SETS, kMem, false>(a, b, sh);
+    lzw_encode_windows<NW, SETS, PER, kMem, false>(a, b, sh);
   } else if (a.st.M <= 4) {
-    lzw_encode_windows<NW, SETS, WHERE, true>(a, b, sh);
+    lzw_encode_windows<NW, SETS, PER, WHERE, true>(a, b, sh);
   } else {
-    lzw_encode_windows<NW, SETS, WHERE, false>(a, b, sh);
+    lzw_encode_windows<NW, SETS, PER, WHERE, false>(a, b, sh);
   }
 }
 
@@ -1609,7 +1609,8 @@ __global__ void lzw_clear_entries_kernel(LzwState st) {
 struct ParsePlan {
   bool lds, tags;
   int nw;
-  int sets;                // encoder: RoundSets that the iterations of a window use in turn
+  int sets;                // encoder: RoundSets that the iterations of a window use in turn ...
+  int per;                 // ... and their slots per position
   size_t smem;
 };
 ParsePlan plan(const z2z_ctx* c, int32_t stride, int32_t flags, bool decode, LzwArgs* a) {
@@ -1633,6 +1634,10 @@ ParsePlan plan(const z2z_ctx* c, int32_t stride, int32_t flags, bool decode, Lzw
   }
   a->lds_ef = ef != 0;
   p.sets = 2;
+  p.per = 4;
+  if (!decode && c->cfg.B <= c->num_cu && p.lds && p.nw >= 8 &&
+      p.smem + (p.nw == 16 ? sizeof(EncShared<16, 2, 8>) : sizeof(EncShared<8, 2, 8>)) <= all)
+    p.per = 8;
   if (!decode && c->cfg.B > c->num_cu && p.nw > 1) {
     // workgroups that a CU holds, by its LDS and by 32 (two sets: 28) waves of registers, no more than there are
     auto held = [&](size_t fixed, int waves) {
@@ -1887,6 +1892,10 @@ int z2z_launch_lzw_encode(z2z_ctx* c, const int32_t* tokens, const int32_t* lens
   const ParsePlan p = plan(c, stride, flags, false, &a);
   if (p.tags)
     hipLaunchKernelGGL((lzw_encode_kernel<16, kTag>), dim3(c->cfg.B), dim3(1024), p.smem, s, a);
+  else if (p.per == 8 && p.nw == 16)
+    hipLaunchKernelGGL((lzw_encode_kernel<16, kLds, 2, 8>), dim3(c->cfg.B), dim3(1024), p.smem, s, a);
+  else if (p.per == 8)
+    hipLaunchKernelGGL((lzw_encode_kernel<8, kLds, 2, 8>), dim3(c->cfg.B), dim3(512), p.smem, s, a);
   else if (p.lds)
     launch_encode<kLds>(a, c->cfg.B, p.nw, p.sets, p.smem, s);
   else
@@ -1980,6 +1989,8 @@ int z2z_lzw_prepare(z2z_ctx* c) {
   // With fewer sequences than CUs a workgroup has its CU to itself and the roomier table (shorter probe
   // sequences) is free; with many, LDS decides how many sequences a CU works on at once.
   const bool roomy = c->cfg.B < 256;
+  // ... but not where it keeps the encoder from sets of eight slots per position, which gain more than the probes it shortens.
+  const int beside_large_sets = (c->lds_limit - (int)sizeof(EncShared<kMaxWaves, 2, 8>) - 256) / (int)sizeof(u64);
   // A CU holds up to four workgroups of 8 waves (32 waves of 64 registers): as many as there are sequences for it, the
   // tables as large as that leaves room for.  Another workgroup hides more than the longer probes cost: 2048 documents of
   // 1024 to 4096 tokens, encode (decode), cap 2048: 4096 slots, three per CU 162 us (152), 2906 slots, four 149 (125); cap
@@ -1997,7 +2008,7 @@ int z2z_lzw_prepare(z2z_ctx* c) {
     st.nslots = shared;
     st.slots_fit_lds = 1;
   } else if (roomy && want4 + cap / 2 <= lds_slots) {        // room left for the decoder's entry info
-    st.nslots = want4;
+    st.nslots = want <= beside_large_sets ? std::min(want4, beside_large_sets) : want4;
     st.slots_fit_lds = 1;
   } else if (want <= lds_slots) {
     st.nslots = want;
@@ -2029,5 +2040,8 @@ int z2z_lzw_prepare(z2z_ctx* c) {
                          reinterpret_cast<const void*>(lzw_decode_serial_kernel<true>)};
   for (const void* f : parse)
     Z2Z_HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_limit - kParseStaticLds));
+  for (const void* f : {reinterpret_cast<const void*>(lzw_encode_kernel<16, kLds, 2, 8>), reinterpret_cast<const void*>(lzw_encode_kernel<8, kLds, 2, 8>)})
+    Z2Z_HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    c->lds_limit - (int)sizeof(EncShared<kMaxWaves, 2, 8>) - 256));
   return Z2Z_OK;
 }
