@@ -138,7 +138,8 @@ int z2z_step_update(z2z_ctx* ctx, const int32_t* d_codes, int32_t stride, const 
  * z2z_lzw_decode call took for each sequence.  The parse kernels (section 2.1's sequential loop, restructured)
  * take the elements of a sequence in windows of up to 1024 and iterate on a window until every element's match agrees
  * with the entries made before it; the serial chain of a call is its iterations (what is counted here), so kernel
- * time / rounds is the latency the parse is bound by.  Valid until z2z_destroy. */
+ * time / rounds is the latency the parse is bound by.  (Codes behind a full codebook that z2z_lzw_decode leaves to its second
+ * launch are not counted.)  Valid until z2z_destroy. */
 int z2z_lzw_rounds(z2z_ctx* ctx, const int32_t** d_rounds);
 
 /* Codebook prefilling (the paper's discussion, "Codebook Management Strategy", item 2: seeding the codebook

@@ -8,9 +8,9 @@
 // give the argument why the result is that of the one-element-at-a-time loop.
 //
 // Measured, kernel time encode; decode (before: rounds of 256 elements, four waves, cut at the first element that depends
-// on an entry of the round): 8 sequences of 4096 tokens, M = 3, cap 2048: 110 -> 44 us; 89 -> 32 -> 28 us.  4 of 32768,
+// on an entry of the round): 8 sequences of 4096 tokens, M = 3, cap 2048: 110 -> 44 -> 42 us; 89 -> 32 -> 28 us.  4 of 32768,
 // M = 4, cap 8192: 691 -> 211; 391 -> 125 -> 84.  16 of 16384, M = 5, cap 16384 (table in memory, its tags in LDS): 657 -> 284 -> 185; 449 -> 157 -> 75.
-// 2048 of 4096: 470 -> 258 -> 180; 395 -> 187 -> 135 (up to four workgroups on a CU).  1 of 512: 24 -> 11.5; 22 -> 10.
+// 2048 of 1024 to 4096, cap 2048: 224 -> 149; 163 -> 113 (up to four workgroups on a CU).  1 of 512: 24 -> 11.5; 22 -> 9.
 //
 // The codebook is a trie stored as a hash table over its edges: one 64-bit slot = parent code (24 bits)
 // | token (24 bits) | entry index (16 bits), two slots per bucket, two buckets per probe step (Table).  The
@@ -449,7 +449,9 @@ __device__ __forceinline__ int call_length(const LzwArgs& a, int b) {
 // The sequence workgroup r of a window kernel works on.  With a few rounds of workgroups on every CU the last ones to
 // start decide when a call with ragged lengths ends, so they should be the shortest: the r-th in the order of 16 classes
 // of length, longest first, and inside a class in the order (wave, turn, lane) of the threads that look at the lengths.
-// Every workgroup finds its own (about 1 us of the 50 and more that a document takes; as a launch of its own it would be 5).
+// Every workgroup finds its own (about 2 us of the 50 and more that a long document takes; as a launch of its own it would be 5).
+// Short rows end together and only pay for it: 2048 rows of up to 400 tokens, as they come -> in order, 38 -> 41 us, of 700 52 -> 51, of
+// 1000 63 -> 59; decode of 1000 46 -> 49.
 // 2048 documents of 1024 to 4096 tokens, cap 2048, three workgroups per CU: 199 -> 181 us.
 constexpr int kLengthBins = 16;
 struct BlockOrder {
@@ -1606,6 +1608,9 @@ __global__ void lzw_clear_entries_kernel(LzwState st) {
 //     token) copy), else one of 8.  Up to four fit (z2z_lzw_prepare); the encoder's iterations then share one RoundSet
 //     where two would keep one workgroup from fitting (2048 documents of 1024 to 4096 tokens, cap 2048: two workgroups 200
 //     us, three 162); where they would not, two sets are faster, by a barrier an iteration (500 sequences: 73, one set 82).
+//   - While every sequence has a CU, the encoder's sets have eight slots per position where the table leaves the LDS for it: a
+//     wave inserts with as many compare-and-swaps as its unluckiest lane needs (8 sequences of 4096 tokens, four slots -> eight,
+//     cap 2048: 46 -> 42 us; cap 4096: 51 -> 47; 8 of 8192, cap 2900: 67 -> 57; 200 of 2000: 38 -> 34; 1 of 512: 12.1 -> 11.5).
 struct ParsePlan {
   bool lds, tags;
   int nw;
@@ -1646,7 +1651,7 @@ ParsePlan plan(const z2z_ctx* c, int32_t stride, int32_t flags, bool decode, Lzw
     const int one = p.nw == 4 ? (int)sizeof(EncShared<4, 1>) : (int)sizeof(EncShared<8, 1>);
     if (held(one, 32) > held(p.nw == 4 ? sizeof(EncShared<4, 2>) : sizeof(EncShared<8, 2>), 28)) p.sets = 1;
   }
-  a->by_length = a->in_len != nullptr && c->cfg.B > 2 * c->num_cu;
+  a->by_length = a->in_len != nullptr && c->cfg.B > 2 * c->num_cu && p.nw >= 4 && stride >= (decode ? 2048 : 640);
   p.smem += ef;
   return p;
 }
