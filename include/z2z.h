@@ -109,6 +109,8 @@ int z2z_lzw_encode(z2z_ctx* ctx, const int32_t* d_tokens, const int32_t* d_lens,
  *   d_tokens  [B, out_stride] int32 out (may be NULL with out_stride 0: only update the codebook;
  *             nothing is written and OVERFLOW is not raised); d_n_tokens [B] out (tokens produced)
  *   d_status  [B] out; BAD_CODE / OVERFLOW end the sequence before the offending code
+ * One [B] buffer may serve as d_n_codes and as d_n_tokens or d_status: a sequence's length is read before its counts
+ * are written.
  */
 int z2z_lzw_decode(z2z_ctx* ctx, const int32_t* d_codes, const int32_t* d_n_codes, int32_t stride,
                    int32_t flags, int32_t* d_tokens, int32_t* d_n_tokens, int32_t out_stride,

@@ -1443,8 +1443,9 @@ __device__ __forceinline__ void lzw_decode_windows(const LzwArgs& a, int b, DecS
     st.rounds[b] = n_rounds;
     a.out_n[b] = n_out;
     a.status[b] = status;
-    st.tail[2 * b] = stop ? n : cpos;
-    st.tail[2 * b + 1] = n_out;
+    st.tail[3 * b] = stop ? n : cpos;
+    st.tail[3 * b + 1] = n_out;
+    st.tail[3 * b + 2] = n;
   }
 }
 
@@ -1478,7 +1479,8 @@ __global__ void __launch_bounds__(1024) lzw_decode_tail_kernel(LzwArgs a) {
   __shared__ Shared sh;
   const LzwState& st = a.st;
   const int b = blockIdx.y;
-  const int from = __builtin_amdgcn_readfirstlane(st.tail[2 * b]), n = call_length(a, b);
+  // (the length as well: where the caller has counts and lengths in one buffer, in_len holds token counts by now)
+  const int from = __builtin_amdgcn_readfirstlane(st.tail[3 * b]), n = __builtin_amdgcn_readfirstlane(st.tail[3 * b + 2]);
   const int share = (n - from + (int)gridDim.x - 1) / (int)gridDim.x;
   const int span = (share + W - 1) / W * W;
   const int lo = from + (int)blockIdx.x * span;
@@ -1513,7 +1515,7 @@ __global__ void __launch_bounds__(1024) lzw_decode_tail_kernel(LzwArgs a) {
   if (lane == 0) sh.count[w] = (uint32_t)sum;
   if (__ballot(bad) != 0 && lane == 0) sh.bad = 1;
   __syncthreads();
-  int base = st.tail[2 * b + 1];               // tokens of the codes before
+  int base = st.tail[3 * b + 1];               // tokens of the codes before
   for (int j = 0; j < NW; ++j) base += (int)sh.count[j];
   // the sequence ended in an earlier part
   if (sh.bad || (out != nullptr && base > a.out_stride)) return;

@@ -100,7 +100,7 @@ Z2Z_API int z2z_create(z2z_ctx** out, const z2z_config* cfg) {
   ok = ok && hipMalloc(&st.prev_code, B * sizeof(int32_t)) == hipSuccess;
   ok = ok && hipMalloc(&st.prev_len, B * sizeof(int32_t)) == hipSuccess;
   ok = ok && hipMalloc(&st.rounds, B * sizeof(int32_t)) == hipSuccess;
-  ok = ok && hipMalloc(&st.tail, 2 * B * sizeof(int32_t)) == hipSuccess;
+  ok = ok && hipMalloc(&st.tail, 3 * B * sizeof(int32_t)) == hipSuccess;
   ok = ok && hipMemset(st.rounds, 0, B * sizeof(int32_t)) == hipSuccess;
   ok = ok && hipMalloc(&st.ent_tokens, B * capn * cfg->M * sizeof(int32_t)) == hipSuccess;
   ok = ok && hipMalloc(&st.ent_len, B * capn * sizeof(int32_t)) == hipSuccess;

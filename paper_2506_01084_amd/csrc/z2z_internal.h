@@ -22,7 +22,7 @@ struct LzwState {
   int32_t* prev_code;
   int32_t* prev_len;
   int32_t* rounds;           // [B] rounds the latest parse kernel took for the sequence (instrumentation)
-  int32_t* tail;             // [B, 2] codes and tokens up to where the latest decode call left the window kernel
+  int32_t* tail;             // [B, 3] codes and tokens up to where the latest decode call left the window kernel, codes in all
   int32_t* ent_tokens;
   int32_t* ent_len;
   unsigned long long* slots;

@@ -193,6 +193,37 @@ def test_codes_behind_a_full_codebook(M, cap):
     ctx.close()
 
 
+def test_lengths_overwritten_by_the_counts_of_a_long_decode():
+    """One tensor for the lengths and the token counts of a decode call in two launches: the second takes the lengths that
+    the first one read (expanding codes, so that the counts are larger; one row ends behind its full codebook, one before)."""
+    import torch
+
+    from paper_2506_01084_amd import api
+
+    V, M, cap, n = 25, 3, 400, 9000
+    rng = np.random.default_rng(11)
+    streams = []
+    for b in range(3):
+        head = oracle.lzw_encode(rng.integers(0, V, 4 * cap + 64).tolist(), V, M, cap)[0]
+        streams.append(head + rng.integers(V, V + cap, n - len(head)).tolist())
+    cnt = [n - 2000, n, 300]
+    ref = [oracle.lzw_decode(streams[b][:cnt[b]], V, M, cap) for b in range(3)]
+    assert max(len(r[0]) for r in ref) > n
+    ctx = _ctx(3, V, M, cap)
+    codes = torch.tensor(streams, dtype=torch.int32, device="cuda")
+    for counts_first in (True, False):
+        tokens = torch.full((3, M * n), -7, dtype=torch.int32, device="cuda")
+        shared = torch.tensor(cnt, dtype=torch.int32, device="cuda")
+        other = torch.empty_like(shared)
+        ctx.lzw_decode(codes, shared, tokens, *((shared, other) if counts_first else (other, shared)), api.RESET)
+        n_tok, st = (shared, other) if counts_first else (other, shared)
+        assert st.tolist() == [0, 0, 0] and n_tok.tolist() == [len(r[0]) for r in ref]
+        got = tokens.cpu().numpy()
+        for b in range(3):
+            assert got[b, :len(ref[b][0])].tolist() == ref[b][0] and (got[b, len(ref[b][0]):] == -7).all()
+    ctx.close()
+
+
 @pytest.mark.parametrize("M,cap,kernel", [(3, 12000, 0), (5, 20000, 0), (8, 23000, 0), (5, 3000, 0), (5, 3000, 2)])
 def test_calls_on_one_codebook(M, cap, kernel):
     """A codebook emptied twice, then appended to by long, short and single-element calls in both directions: tables in LDS,
