@@ -94,6 +94,8 @@ int z2z_reset(z2z_ctx* ctx, void* stream);
  *   d_tokens  [B, stride] int32, row b holds d_lens[b] valid IDs (d_lens NULL: every row has `stride`)
  *   d_codes   [B, out_stride] int32 out; d_n_codes [B] int32 out (number of codes written)
  *   d_status  [B] int32 out (Z2Z_ST_* bits); BAD_TOKEN ends the sequence just before that token
+ * One [B] buffer may serve as d_lens and as d_n_codes or d_status: a sequence's length is read before its counts are
+ * written.
  */
 int z2z_lzw_encode(z2z_ctx* ctx, const int32_t* d_tokens, const int32_t* d_lens, int32_t stride,
                    int32_t flags, int32_t* d_codes, int32_t* d_n_codes, int32_t out_stride,

@@ -472,6 +472,7 @@ __device__ __forceinline__ int sequence_of_block(const LzwArgs& a, BlockOrder& s
     return kLengthBins - 1 - min((int)((float)len * scale), kLengthBins - 1);
   };
   if (tid < kLengthBins) sh.bin[tid] = 0;
+  if (tid == 0) sh.seq = blockIdx.x;           // (found below as long as nobody writes to the lengths meanwhile: see plan)
   __syncthreads();
   for (int i = tid; i < B; i += THREADS) atomicAdd(&sh.bin[bin_of(i)], 1);
   __syncthreads();
@@ -1620,6 +1621,16 @@ struct ParsePlan {
   int per;                 // ... and their slots per position
   size_t smem;
 };
+// Lengths that a call overwrites (one buffer for lengths and counts): every workgroup reads its own before it writes, but in
+// order of length the late ones would look at the counts of those that have ended.
+bool writes_lengths(const LzwArgs& a, size_t B) {
+  const uintptr_t lo = reinterpret_cast<uintptr_t>(a.in_len), hi = lo + B * sizeof(int32_t);
+  auto meets = [&](const int32_t* p, size_t n) {
+    const uintptr_t at = reinterpret_cast<uintptr_t>(p);
+    return p != nullptr && at < hi && lo < at + n * sizeof(int32_t);
+  };
+  return meets(a.out_n, B) || meets(a.status, B) || meets(a.out, B * (size_t)a.out_stride);
+}
 ParsePlan plan(const z2z_ctx* c, int32_t stride, int32_t flags, bool decode, LzwArgs* a) {
   ParsePlan p;
   const bool tiny_append = !(flags & Z2Z_RESET) && stride <= kShortAppend;
@@ -1653,7 +1664,8 @@ ParsePlan plan(const z2z_ctx* c, int32_t stride, int32_t flags, bool decode, Lzw
     const int one = p.nw == 4 ? (int)sizeof(EncShared<4, 1>) : (int)sizeof(EncShared<8, 1>);
     if (held(one, 32) > held(p.nw == 4 ? sizeof(EncShared<4, 2>) : sizeof(EncShared<8, 2>), 28)) p.sets = 1;
   }
-  a->by_length = a->in_len != nullptr && c->cfg.B > 2 * c->num_cu && p.nw >= 4 && stride >= (decode ? 2048 : 640);
+  a->by_length = a->in_len != nullptr && c->cfg.B > 2 * c->num_cu && p.nw >= 4 && stride >= (decode ? 2048 : 640) &&
+                 !writes_lengths(*a, (size_t)c->cfg.B);
   p.smem += ef;
   return p;
 }

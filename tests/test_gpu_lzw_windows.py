@@ -224,6 +224,43 @@ def test_lengths_overwritten_by_the_counts_of_a_long_decode():
     ctx.close()
 
 
+@pytest.mark.parametrize("shared_with", ["counts", "status", "neither"])
+def test_lengths_overwritten_by_many_sequences(shared_with):
+    """One tensor for the lengths and the counts (or the status words) of a call that has more sequences than run at once and
+    would take them in order of length, in both directions."""
+    import torch
+
+    from paper_2506_01084_amd import api
+
+    B, N, V, M, cap = 1300, 2100, 100, 3, 300
+    rng = np.random.default_rng(17)
+    lens = rng.integers(1, 200, B).astype(np.int32)
+    lens[rng.integers(0, B, 12)] = N
+    tokens = np.minimum(rng.zipf(1.3, (B, N)) - 1, V - 1).astype(np.int32)
+    ref = oracle_encode_batch(tokens, lens, V, M, cap)
+    n_ref = [len(r[0]) for r in ref]
+    ctx = _ctx(B, V, M, cap)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    outputs = lambda n: dict(counts=(n, torch.empty_like(n)), status=(torch.empty_like(n), n),
+                             neither=(torch.empty_like(n), torch.empty_like(n)))[shared_with]
+    d_tok, d_codes, d_back = t(tokens), t(np.full((B, N), -7, np.int32)), t(np.full((B, N), -7, np.int32))
+    d_len = t(lens)
+    n_codes, st = outputs(d_len)
+    ctx.lzw_encode(d_tok, d_len, d_codes, n_codes, st, api.RESET)
+    assert (st == 0).all() and n_codes.tolist() == n_ref
+    codes = d_codes.cpu().numpy()
+    for b in range(B):
+        assert codes[b, :n_ref[b]].tolist() == ref[b][0]
+    assert_codebook_equal(ctx, [r[1] for r in ref], M, cap)
+    d_n = t(np.asarray(n_ref, np.int32))
+    n_tok, st = outputs(d_n)
+    ctx.lzw_decode(d_codes, d_n, d_back, n_tok, st, api.RESET)
+    assert (st == 0).all() and n_tok.tolist() == lens.tolist()
+    back = d_back.cpu().numpy()
+    assert all((back[b, :lens[b]] == tokens[b, :lens[b]]).all() and (back[b, lens[b]:] == -7).all() for b in range(B))
+    ctx.close()
+
+
 @pytest.mark.parametrize("M,cap,kernel", [(3, 12000, 0), (5, 20000, 0), (8, 23000, 0), (5, 3000, 0), (5, 3000, 2)])
 def test_calls_on_one_codebook(M, cap, kernel):
     """A codebook emptied twice, then appended to by long, short and single-element calls in both directions: tables in LDS,
