@@ -453,6 +453,14 @@ __device__ __forceinline__ int call_length(const LzwArgs& a, int b) {
 // Short rows end together and only pay for it: 2048 rows of up to 400 tokens, as they come -> in order, 38 -> 41 us, of 700 52 -> 51, of
 // 1000 63 -> 59; decode of 1000 46 -> 49.
 // 2048 documents of 1024 to 4096 tokens, cap 2048, three workgroups per CU: 199 -> 181 us.
+// Every workgroup looks at all lengths, so that the cost of a call grows with B squared, where the gain is a share of the last
+// round of workgroups.  Lengths from 0 to N, as they come -> in order, us:
+//   encode  N = 700   B = 2048 54 -> 52    3072 71 -> 72    16384 294 -> 503    32768 561 -> 1422
+//           N = 2100      2048 99 -> 85    4096 162 -> 155  16384 508 -> 707 (from N / 4 on)
+//           N = 4096      2048 164 -> 127  4096 265 -> 232
+//   decode  N = 2100      2048 72 -> 67    3072 94 -> 97    16384 371 -> 668
+//           N = 4096      2048 121 -> 98   3072 160 -> 145  4096 200 -> 192 (from N / 4 on: 234 -> 237)
+// Hence up to eight (decode: four) sequences per CU and half the row's length more, sixteen per CU at most.
 constexpr int kLengthBins = 16;
 struct BlockOrder {
   int32_t bin[kLengthBins];
@@ -1664,7 +1672,8 @@ ParsePlan plan(const z2z_ctx* c, int32_t stride, int32_t flags, bool decode, Lzw
     const int one = p.nw == 4 ? (int)sizeof(EncShared<4, 1>) : (int)sizeof(EncShared<8, 1>);
     if (held(one, 32) > held(p.nw == 4 ? sizeof(EncShared<4, 2>) : sizeof(EncShared<8, 2>), 28)) p.sets = 1;
   }
-  a->by_length = a->in_len != nullptr && c->cfg.B > 2 * c->num_cu && p.nw >= 4 && stride >= (decode ? 2048 : 640) &&
+  const int most = std::min(16 * c->num_cu, (decode ? 4 : 8) * c->num_cu + stride / 2);
+  a->by_length = a->in_len != nullptr && c->cfg.B > 2 * c->num_cu && c->cfg.B <= most && p.nw >= 4 && stride >= (decode ? 2048 : 640) &&
                  !writes_lengths(*a, (size_t)c->cfg.B);
   p.smem += ef;
   return p;

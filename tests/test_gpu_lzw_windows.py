@@ -63,12 +63,13 @@ def test_more_sequences_than_compute_units(B, cap):
     _round_trip(tokens, lens, 200, 3, cap)
 
 
-@pytest.mark.parametrize("B,M,cap", [(520, 3, 2048), (1100, 4, 1500), (800, 5, 3000), (1030, 8, 40)])
+@pytest.mark.parametrize("B,M,cap", [(520, 3, 2048), (1100, 4, 1500), (800, 5, 3000), (1030, 8, 40), (2700, 3, 200)])
 def test_several_workgroups_of_a_compute_unit(B, M, cap):
     """More than two sequences per CU: three or four workgroups on one, tables cut to what that leaves of the LDS, one round
-    set for all iterations of a window, sequences taken longest first (lengths of 0, of all of a row, all alike, of every class)."""
+    set for all iterations of a window, sequences taken longest first (lengths of 0, of all of a row, all alike, of every class),
+    or as they come where there are too many of them for their length."""
     rng = np.random.default_rng(B + cap)
-    N = {520: 2100, 1100: 700}.get(B, 300)              # (in order of length from 640 tokens, 2048 codes on)
+    N = {520: 2100, 1100: 700, 2700: 700}.get(B, 300)   # (in order of length from 640 tokens, 2048 codes on; 2700: as they come)
     tokens = np.where(rng.random((B, 1)) < 0.5, rng.integers(0, 4, (B, N)), np.minimum(rng.zipf(1.3, (B, N)) - 1, 99)).astype(np.int32)
     lens = rng.integers(0, N + 1, B).astype(np.int32)
     lens[rng.integers(0, B, 40)] = 0
