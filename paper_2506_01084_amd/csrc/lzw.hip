@@ -60,8 +60,10 @@ extern __shared__ __align__(16) u64 lds_slots[];   // the sequence's hash table 
 
 // The hash table of one sequence: in LDS for the length of a call (indexes the shared array directly so that probes
 // are ds_read_b128), in global memory (huge capacities, and short appends that touch a few slots), or in global memory
-// with a tag of every slot in LDS: 16 bits of the edge's hash | entry index.  What a probe in memory costs is requests, two
+// with a tag of every slot in LDS: 16 bits of the edge's hash.  What a probe in memory costs is requests, two
 // of 16 bytes, hit or miss; with the tags a miss is a matter of LDS and a hit one request of 8 bytes, the slot itself.
+// (Tags of 32 bits, with the entry's index, left LDS for 28100 slots only, and calls that go to the table in memory all the
+// same met it fuller: 2000 tokens appended to a full codebook of 22000 entries, 16 sequences, 44000 -> 28100 slots 13 -> 20 us.)
 // 16 sequences of 16384 tokens, cap 16384, M = 5: encode 272 -> 185 us, decode 156 -> 100; 100 of 8192, cap 12000, M = 3:
 // 134 -> 89; 109 -> 69.
 enum { kMem, kLds, kTag };
@@ -71,20 +73,26 @@ struct Table {
   u64* g;           // global slots of this sequence
   uint32_t n;       // number of slots
 
-  static __device__ __forceinline__ uint32_t* tags() { return reinterpret_cast<uint32_t*>(lds_slots); }
-  static __device__ __forceinline__ uint32_t tag_of(uint32_t h) {           // (all ones: no entry has it)
-    return min((h >> 2) & 0xFFFFu, 0xFFFEu) << 16;
-  }
-  // The tags of two buckets, and which of them agree with an edge's (bit i: slot i of the four).
-  struct Tags {
-    uint2 a, b;
+  struct Probe {
+    uint32_t b0, b1, step, i;
   };
-  __device__ __forceinline__ Tags load_tags(uint32_t b0, uint32_t b1) const {
-    return {*reinterpret_cast<const uint2*>(tags() + 2 * b0), *reinterpret_cast<const uint2*>(tags() + 2 * b1)};
+  static __device__ __forceinline__ uint32_t* tags() { return reinterpret_cast<uint32_t*>(lds_slots); }   // a word per bucket
+  static __device__ __forceinline__ uint32_t tag_of(uint32_t h) {           // (all ones: no entry has it)
+    return min((h >> 2) & 0xFFFFu, 0xFFFEu);
   }
+  // The tags of two buckets (slot 0 of a bucket in the low half), and which of them agree with an edge's (bit i: slot i of the four).
+  struct Tags {
+    uint32_t a, b;
+  };
+  __device__ __forceinline__ Tags load_tags(uint32_t b0, uint32_t b1) const { return {tags()[b0], tags()[b1]}; }
   static __device__ __forceinline__ uint32_t agree(const Tags& t, uint32_t tag) {
-    return ((t.a.x ^ tag) < 0x10000u ? 1u : 0u) | ((t.a.y ^ tag) < 0x10000u ? 2u : 0u) | ((t.b.x ^ tag) < 0x10000u ? 4u : 0u) |
-           ((t.b.y ^ tag) < 0x10000u ? 8u : 0u);
+    const uint32_t x = t.a ^ (tag * 0x10001u), y = t.b ^ (tag * 0x10001u);
+    return ((x & 0xFFFFu) == 0 ? 1u : 0u) | (x < 0x10000u ? 2u : 0u) | ((y & 0xFFFFu) == 0 ? 4u : 0u) | (y < 0x10000u ? 8u : 0u);
+  }
+  // Claims slot `at`, empty in the tags read: fails when another lane has claimed a slot of the bucket since.
+  static __device__ __forceinline__ bool claim(const Probe& p, const Tags& t, int at, uint32_t tag) {
+    const uint32_t old = (uint32_t)(at >> 1) == p.b0 ? t.a : t.b, shift = (at & 1) * 16;
+    return atomicCAS(&tags()[at >> 1], old, old ^ ((tag ^ 0xFFFFu) << shift)) == old;
   }
 
   // Two slots are a bucket (n is even): one 16-byte read.  A probe step looks at two buckets at once, and a new
@@ -93,9 +101,6 @@ struct Table {
   // first kJumps buckets of a sequence are `step` (a second hash) apart, the rest follow one by one, which reaches
   // every bucket whatever n is.  A look-up ends at the first step with an empty slot.
   static constexpr uint32_t kJumps = 8;
-  struct Probe {
-    uint32_t b0, b1, step, i;
-  };
   __device__ __forceinline__ uint32_t hop(uint32_t bucket, uint32_t by) const {
     bucket += by;
     return min(bucket, bucket - (n >> 1));          // (unsigned: the subtraction wraps unless bucket is past the end)
@@ -137,7 +142,7 @@ struct Table {
   }
   __device__ __forceinline__ void store(uint32_t pos, u64 v) const {
     if (WHERE == kTag) {
-      tags()[pos] = tag_of(edge_hash((int32_t)(v >> 40), (int32_t)((v >> 16) & 0xFFFFFFu))) | (uint32_t)(v & 0xFFFFu);
+      reinterpret_cast<uint16_t*>(tags())[pos] = (uint16_t)tag_of(edge_hash((int32_t)(v >> 40), (int32_t)((v >> 16) & 0xFFFFFFu)));
       g[pos] = v;
     } else if (LDS)
       lds_slots[pos] = v;
@@ -153,10 +158,10 @@ struct Table {
     return -1;
   }
   static __device__ __forceinline__ int free_slot(const Probe& p, const Tags& t) {
-    if (t.a.x == ~0u) return (int)(2 * p.b0);
-    if (t.b.x == ~0u) return (int)(2 * p.b1);
-    if (t.a.y == ~0u) return (int)(2 * p.b0 + 1);
-    if (t.b.y == ~0u) return (int)(2 * p.b1 + 1);
+    if ((t.a & 0xFFFFu) == 0xFFFFu) return (int)(2 * p.b0);
+    if ((t.b & 0xFFFFu) == 0xFFFFu) return (int)(2 * p.b1);
+    if (t.a >= 0xFFFF0000u) return (int)(2 * p.b0 + 1);
+    if (t.b >= 0xFFFF0000u) return (int)(2 * p.b1 + 1);
     return -1;
   }
   // The entry of an edge whose tag some slots of a probe have, or -1: the slots themselves decide.
@@ -224,7 +229,7 @@ struct Table {
           const int idx = confirm(p, which, key);
           if (idx >= 0) return idx;
         }
-        if (t.a.y == ~0u || t.b.y == ~0u) return -1;
+        if (t.a >= 0xFFFF0000u || t.b >= 0xFFFF0000u) return -1;
         continue;
       }
       ulonglong2 a, b;
@@ -246,7 +251,7 @@ struct Table {
     const uint32_t h = edge_hash(parent, tok);
     Probe p = probe_init(h);
     do {
-      for (int tries = 0; tries < 5; ++tries) {     // (a lost slot has filled: at most four times)
+      for (int tries = 0; tries < 5; ++tries) {     // (a claim is lost when one of the four slots has filled: at most four times)
         int at;
         if (WHERE == kTag) {
           const Tags t = load_tags(p.b0, p.b1);
@@ -257,7 +262,7 @@ struct Table {
           }
           at = free_slot(p, t);
           if (at < 0) break;
-          if (atomicCAS(&tags()[at], ~0u, tag_of(h) | (uint32_t)idx) == ~0u) {
+          if (claim(p, t, at, tag_of(h))) {
             g[at] = val;
             return at;
           }
@@ -274,7 +279,7 @@ struct Table {
     return -2;
   }
   __device__ __forceinline__ void remove(int at) const {
-    if (WHERE == kTag) tags()[at] = ~0u;
+    if (WHERE == kTag) atomicOr(&tags()[at >> 1], 0xFFFFu << ((at & 1) * 16));
     if (LDS)
       lds_slots[at] = kEmpty;
     else
@@ -287,11 +292,12 @@ struct Table {
     const uint32_t h = edge_hash(parent, tok);
     Probe p = probe_init(h);
     do {
-      for (int tries = 0; tries < 5; ++tries) {     // (a lost slot has filled: at most four times)
+      for (int tries = 0; tries < 5; ++tries) {     // (a claim is lost when one of the four slots has filled: at most four times)
         if (WHERE == kTag) {
-          const int at = free_slot(p, load_tags(p.b0, p.b1));
+          const Tags t = load_tags(p.b0, p.b1);
+          const int at = free_slot(p, t);
           if (at < 0) break;
-          if (atomicCAS(&tags()[at], ~0u, tag_of(h) | (uint32_t)idx) == ~0u) {
+          if (claim(p, t, at, tag_of(h))) {
             g[at] = val;
             return;
           }
@@ -362,15 +368,14 @@ __device__ __forceinline__ void table_open_all(const LzwArgs& a, int b, int tid,
     for (int i = tid; i < pairs; i += THREADS) g2[i] = empty;
   }
   if (WHERE == kTag) {
-    uint2* tags = reinterpret_cast<uint2*>(t->tags());
+    uint32_t* tags = t->tags();
     if (reset) {                               // (chosen per element, the compiler got `reset` the wrong way round further on)
-      for (int i = tid; i < pairs; i += THREADS) tags[i] = {~0u, ~0u};
+      for (int i = tid; i < pairs; i += THREADS) tags[i] = ~0u;
     } else {
       auto tag = [&](u64 v) -> uint32_t {
-        if (v == kEmpty) return ~0u;
-        return t->tag_of(edge_hash((int32_t)(v >> 40), (int32_t)((v >> 16) & 0xFFFFFFu))) | (uint32_t)(v & 0xFFFFu);
+        return v == kEmpty ? 0xFFFFu : t->tag_of(edge_hash((int32_t)(v >> 40), (int32_t)((v >> 16) & 0xFFFFFFu)));
       };
-      for (int i = tid; i < pairs; i += THREADS) tags[i] = {tag(g2[i].x), tag(g2[i].y)};
+      for (int i = tid; i < pairs; i += THREADS) tags[i] = tag(g2[i].x) | tag(g2[i].y) << 16;
     }
   }
 }
@@ -1646,7 +1651,7 @@ ParsePlan plan(const z2z_ctx* c, int32_t stride, int32_t flags, bool decode, Lzw
   p.nw = tiny_append || c->opt_lzw_kernel == 4 ? 1 : stride <= 512 ? 8 : 16;
   p.smem = p.lds ? (size_t)c->st.nslots * sizeof(u64) : 0;
   p.tags = c->st.tags_fit_lds && p.nw == 16 && c->opt_lzw_kernel != 2;
-  if (p.tags) p.smem = (size_t)c->st.nslots * sizeof(uint32_t);
+  if (p.tags) p.smem = (size_t)c->st.nslots * sizeof(uint16_t);
   const size_t all = (size_t)c->lds_limit, fixed8 = decode ? sizeof(DecShared<8>) : sizeof(EncShared<8, 1>),
                fixed4 = decode ? sizeof(DecShared<4>) : sizeof(EncShared<4, 1>);
   size_t ef = decode && p.lds ? (size_t)c->st.cap * sizeof(uint32_t) : 0;
@@ -2047,9 +2052,8 @@ int z2z_lzw_prepare(z2z_ctx* c) {
   } else {
     // A table in memory: its tags in LDS, while a sequence has a CU to itself (several on a CU hide the latency of tables in
     // memory, and the tags would keep them from it).
-    const int tags = (c->lds_limit - kParseStaticLds) / (int)sizeof(uint32_t);
-    st.tags_fit_lds = c->cfg.B <= c->num_cu && floor125 <= tags;
-    st.nslots = st.tags_fit_lds ? std::min(want, tags) : want;
+    st.tags_fit_lds = c->cfg.B <= c->num_cu && want <= (c->lds_limit - kParseStaticLds) / (int)sizeof(uint16_t);
+    st.nslots = want;
     st.slots_fit_lds = 0;
   }
   st.nslots &= ~1;                                     // whole buckets

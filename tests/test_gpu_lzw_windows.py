@@ -262,10 +262,10 @@ def test_lengths_overwritten_by_many_sequences(shared_with):
     ctx.close()
 
 
-@pytest.mark.parametrize("M,cap,kernel", [(3, 12000, 0), (5, 20000, 0), (8, 23000, 0), (5, 3000, 0), (5, 3000, 2)])
+@pytest.mark.parametrize("M,cap,kernel", [(3, 12000, 0), (5, 20000, 0), (8, 23000, 0), (8, 28136, 0), (4, 28137, 0), (5, 3000, 0), (5, 3000, 2)])
 def test_calls_on_one_codebook(M, cap, kernel):
     """A codebook emptied twice, then appended to by long, short and single-element calls in both directions: tables in LDS,
-    in memory with their tags in LDS (more than 11000 entries), in memory alone (more than 22400, or as an option)."""
+    in memory with their tags in LDS (more than 11000 entries), in memory alone (more than 28136, or as an option)."""
     from paper_2506_01084_amd import api
 
     V, B = 3000, 3
