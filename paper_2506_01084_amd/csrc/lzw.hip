@@ -445,6 +445,15 @@ __device__ __forceinline__ void table_insert(const LzwArgs& a, int b, int lane, 
 // first repeat, but 5 windows of 1024 with 13 iterations in all.
 // ------------------------------------------------------------------------------------------------
 constexpr int kShortAppend = 64;
+// Tags of a table in memory have to be made from all of its slots when a call continues a codebook (256 KB for a CU to
+// read at cap 16384), which only entries to come make up for: an appended call has them made from kTagAppendTokens tokens
+// (kTagAppendCodes codes) on, and where the codebook has room for so many codes' entries.  Table in memory -> tags, us:
+//   room   200 sequences, cap 16384: encode 513 tokens 20 -> 26, 1024 27 -> 32, 1500 37 -> 39, 2048 44 -> 42, 4096 75 -> 64; decode of their
+//          codes (280, 560, 830, 1130, 2260) 14 -> 21, 19 -> 23, 27 -> 24, 33 -> 29, 52 -> 37
+//          16 sequences, cap 22000: encode 1024 22 -> 23, 1500 31 -> 30, 2048 35 -> 32; decode 16 -> 18, 17 -> 18, 24 -> 22
+//   full   16 sequences, cap 12000: encode 1024 tokens 11 -> 14, 4096 27 -> 31, 16384 88 -> 93; decode 8 -> 12, 14 -> 17
+// (An emptied codebook has its tags for nothing: 513 tokens 42 -> 37 and 30 -> 24.)
+constexpr int kTagAppendTokens = 2048, kTagAppendCodes = 1024;
 
 // Number of elements of sequence b in this call.
 __device__ __forceinline__ int call_length(const LzwArgs& a, int b) {
@@ -934,13 +943,17 @@ __device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, int b, EncS
 
 // A short appended call touches a handful of slots: probing the table where it lives, in global memory,
 // is cheaper than staging all of it in LDS and writing it back (the length is known only on the device,
-// so the LDS kernels take this decision per sequence).
+// so the LDS kernels take this decision per sequence; for the tags the line lies at kTagAppendTokens).
 template <int NW, int WHERE, int SETS = 2, int PER = 4>
 __global__ void __launch_bounds__(NW * kWave, SETS == 1 ? 8 : 1) lzw_encode_kernel(LzwArgs a) {
   __shared__ EncShared<NW, SETS, PER> sh;
   const int b = sequence_of_block<NW>(a, reinterpret_cast<BlockOrder&>(sh));
-  const bool short_append = !(a.flags & Z2Z_RESET) && call_length(a, b) <= kShortAppend;
-  if (WHERE != kMem && short_append) {
+  bool short_append = !(a.flags & Z2Z_RESET) && call_length(a, b) <= kShortAppend;
+  if (WHERE == kTag && !(a.flags & Z2Z_RESET))
+    short_append = min(call_length(a, b), 2 * (a.st.cap - a.st.size[b])) < kTagAppendTokens;
+  if (WHERE == kTag && short_append && a.st.M <= 4) {
+    lzw_encode_windows<NW, SETS, PER, kMem, true>(a, b, sh);
+  } else if (WHERE != kMem && short_append) {
     lzw_encode_windows<NW, SETS, PER, kMem, false>(a, b, sh);
   } else if (a.st.M <= 4) {
     lzw_encode_windows<NW, SETS, PER, WHERE, true>(a, b, sh);
@@ -1467,8 +1480,11 @@ template <int NW, int WHERE>
 __global__ void __launch_bounds__(NW * kWave) lzw_decode_kernel(LzwArgs a) {
   __shared__ DecShared<NW> sh;
   const int b = sequence_of_block<NW>(a, reinterpret_cast<BlockOrder&>(sh));
-  const bool short_append = !(a.flags & Z2Z_RESET) && call_length(a, b) <= kShortAppend;
-  if (WHERE != kMem && short_append) {
+  bool short_append = !(a.flags & Z2Z_RESET) && call_length(a, b) <= kShortAppend;
+  if (WHERE == kTag && !(a.flags & Z2Z_RESET)) short_append = min(call_length(a, b), a.st.cap - a.st.size[b]) < kTagAppendCodes;
+  if (WHERE == kTag && short_append && a.st.M <= 4) {
+    lzw_decode_windows<NW, kMem, true>(a, b, sh);
+  } else if (WHERE != kMem && short_append) {
     lzw_decode_windows<NW, kMem, false>(a, b, sh);
   } else if (a.st.M <= 4) {
     lzw_decode_windows<NW, WHERE, true>(a, b, sh);
@@ -1650,7 +1666,8 @@ ParsePlan plan(const z2z_ctx* c, int32_t stride, int32_t flags, bool decode, Lzw
   p.lds = c->st.slots_fit_lds && !tiny_append && c->opt_lzw_kernel != 2;
   p.nw = tiny_append || c->opt_lzw_kernel == 4 ? 1 : stride <= 512 ? 8 : 16;
   p.smem = p.lds ? (size_t)c->st.nslots * sizeof(u64) : 0;
-  p.tags = c->st.tags_fit_lds && p.nw == 16 && c->opt_lzw_kernel != 2;
+  p.tags = c->st.tags_fit_lds && p.nw == 16 && c->opt_lzw_kernel != 2 &&
+           ((flags & Z2Z_RESET) || stride >= (decode ? kTagAppendCodes : kTagAppendTokens));
   if (p.tags) p.smem = (size_t)c->st.nslots * sizeof(uint16_t);
   const size_t all = (size_t)c->lds_limit, fixed8 = decode ? sizeof(DecShared<8>) : sizeof(EncShared<8, 1>),
                fixed4 = decode ? sizeof(DecShared<4>) : sizeof(EncShared<4, 1>);

@@ -290,6 +290,39 @@ def test_calls_on_one_codebook(M, cap, kernel):
     dec.close()
 
 
+@pytest.mark.parametrize("M", [3, 6])
+def test_ragged_appends_to_a_table_in_memory(M):
+    """Appended rows of one call on both sides of the length, and of the room, from which the tags of a table in memory are
+    made for it."""
+    from paper_2506_01084_amd import api
+
+    V, cap, N = 500, 12000, 2100
+    lens = np.array([N, 2048, 2047, 700, 65, 64, 0], dtype=np.int32)
+    B, rng = len(lens), np.random.default_rng(M)
+    enc, dec = _ctx(B, V, M, cap), _ctx(B, V, M, cap)
+    s = [oracle.LZWStream(V, M, cap) for _ in range(B)]
+    for flags in (api.RESET, api.APPEND, api.APPEND, "room", api.APPEND, api.APPEND):
+        if flags == "room":                                  # room for 500 to 1900 entries
+            N, flags = 12000, api.RESET
+            lens = (10300 + 250 * np.arange(B)).astype(np.int32)
+            s = [oracle.LZWStream(V, M, cap) for _ in range(B)]
+            tokens = rng.integers(0, V, (B, N)).astype(np.int32)
+        else:
+            N = 2100
+            tokens = np.minimum(rng.zipf(1.2, (B, N)) - 1, V - 1).astype(np.int32)
+        codes, n_codes, st = gpu_encode(enc, tokens, lens, flags=flags)
+        toks, n_tok, st2 = gpu_decode(dec, codes, n_codes, out_stride=N, flags=flags)
+        for b in range(B):
+            want, rst = s[b].encode_chunk(tokens[b, :lens[b]].tolist())
+            assert int(st[b]) == int(st2[b]) == rst == 0 and codes[b, :n_codes[b]].tolist() == want
+            assert int(n_tok[b]) == lens[b] and (toks[b, :lens[b]] == tokens[b, :lens[b]]).all()
+        lens = lens[::-1].copy() if N == 2100 else np.full(B, 2100, dtype=np.int32)
+    assert_codebook_equal(enc, [x.entries for x in s], M, cap)
+    assert_codebook_equal(dec, [x.entries for x in s], M, cap)
+    enc.close()
+    dec.close()
+
+
 def _crowded_pairs(V, bits):
     """Pairs of tokens, the most found, whose edges share both of their groups of the round's set (2^bits groups of four):
     beyond eight of them in a window the rest find no slot.  (The hash is the kernel's.)"""
