@@ -353,9 +353,9 @@ __device__ __forceinline__ void table_open(const LzwArgs& a, int b, int lane, bo
   }
 }
 
-// The same by all THREADS threads of a workgroup; no barrier inside.
+// The same by all THREADS threads of a workgroup; no barrier inside.  (probed: whether a look-up can come)
 template <int WHERE, int THREADS>
-__device__ __forceinline__ void table_open_all(const LzwArgs& a, int b, int tid, bool reset, Table<WHERE>* t) {
+__device__ __forceinline__ void table_open_all(const LzwArgs& a, int b, int tid, bool reset, Table<WHERE>* t, bool probed = true) {
   t->g = a.st.slots + (size_t)b * a.st.nslots;
   t->n = (uint32_t)a.st.nslots;
   ulonglong2* g2 = reinterpret_cast<ulonglong2*>(t->g);             // (nslots is even, the rows 16-byte aligned)
@@ -367,7 +367,7 @@ __device__ __forceinline__ void table_open_all(const LzwArgs& a, int b, int tid,
   } else if (reset) {
     for (int i = tid; i < pairs; i += THREADS) g2[i] = empty;
   }
-  if (WHERE == kTag) {
+  if (WHERE == kTag && probed) {
     uint32_t* tags = t->tags();
     if (reset) {                               // (chosen per element, the compiler got `reset` the wrong way round further on)
       for (int i = tid; i < pairs; i += THREADS) tags[i] = ~0u;
@@ -451,7 +451,8 @@ constexpr int kShortAppend = 64;
 //   room   200 sequences, cap 16384: encode 513 tokens 20 -> 26, 1024 27 -> 32, 1500 37 -> 39, 2048 44 -> 42, 4096 75 -> 64; decode of their
 //          codes (280, 560, 830, 1130, 2260) 14 -> 21, 19 -> 23, 27 -> 24, 33 -> 29, 52 -> 37
 //          16 sequences, cap 22000: encode 1024 22 -> 23, 1500 31 -> 30, 2048 35 -> 32; decode 16 -> 18, 17 -> 18, 24 -> 22
-//   full   16 sequences, cap 12000: encode 1024 tokens 11 -> 14, 4096 27 -> 31, 16384 88 -> 93; decode 8 -> 12, 14 -> 17
+//   full   16 sequences, cap 12000: encode 1024 tokens 11 -> 14, 4096 27 -> 31, 16384 88 -> 93; decode 8 -> 12, 14 -> 17 (nothing is
+//          looked up there: the tag kernel without tags, 8 and 13)
 // (An emptied codebook has its tags for nothing: 513 tokens 42 -> 37 and 30 -> 24.)
 constexpr int kTagAppendTokens = 2048, kTagAppendCodes = 1024;
 
@@ -1229,7 +1230,7 @@ __device__ __forceinline__ void lzw_decode_windows(const LzwArgs& a, int b, DecS
   int32_t* ent_len = st.ent_len + (size_t)b * cap;
 
   Table<WHERE> t;
-  table_open_all<WHERE, W>(a, b, tid, reset, &t);
+  table_open_all<WHERE, W>(a, b, tid, reset, &t, C < cap);
   if (ef_lds && !reset) {
     for (int i = tid; i < C; i += W) ef[i] = pack_ef(ent_len[i], ent_tokens[(size_t)i * M]);
   }
@@ -1481,7 +1482,10 @@ __global__ void __launch_bounds__(NW * kWave) lzw_decode_kernel(LzwArgs a) {
   __shared__ DecShared<NW> sh;
   const int b = sequence_of_block<NW>(a, reinterpret_cast<BlockOrder&>(sh));
   bool short_append = !(a.flags & Z2Z_RESET) && call_length(a, b) <= kShortAppend;
-  if (WHERE == kTag && !(a.flags & Z2Z_RESET)) short_append = min(call_length(a, b), a.st.cap - a.st.size[b]) < kTagAppendCodes;
+  if (WHERE == kTag && !(a.flags & Z2Z_RESET)) {
+    const int room = a.st.cap - a.st.size[b];                 // (full: nothing is looked up, the tags are not made)
+    short_append = room > 0 && min(call_length(a, b), room) < kTagAppendCodes;
+  }
   if (WHERE == kTag && short_append && a.st.M <= 4) {
     lzw_decode_windows<NW, kMem, true>(a, b, sh);
   } else if (WHERE != kMem && short_append) {
