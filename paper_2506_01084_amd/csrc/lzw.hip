@@ -1644,6 +1644,8 @@ __global__ void lzw_clear_entries_kernel(LzwState st) {
 //     token) copy), else one of 8.  Up to four fit (z2z_lzw_prepare); the encoder's iterations then share one RoundSet
 //     where two would keep one workgroup from fitting (2048 documents of 1024 to 4096 tokens, cap 2048: two workgroups 200
 //     us, three 162); where they would not, two sets are faster, by a barrier an iteration (500 sequences: 73, one set 82).
+//     With tables in memory the fourth workgroup's 64 registers are not enough: two sets -> one, cap 12000, 2048 of 1024
+//     tokens 243 -> 259, of 4096 595 -> 607 (1024 of 4096 319 -> 303).
 //   - While every sequence has a CU, the encoder's sets have eight slots per position where the table leaves the LDS for it: a
 //     wave inserts with as many compare-and-swaps as its unluckiest lane needs (8 sequences of 4096 tokens, four slots -> eight,
 //     cap 2048: 46 -> 42 us; cap 4096: 51 -> 47; 8 of 8192, cap 2900: 67 -> 57; 200 of 2000: 38 -> 34; 1 of 512: 12.1 -> 11.5).
@@ -1690,7 +1692,7 @@ ParsePlan plan(const z2z_ctx* c, int32_t stride, int32_t flags, bool decode, Lzw
   if (!decode && c->cfg.B <= c->num_cu && p.lds && p.nw >= 8 &&
       p.smem + (p.nw == 16 ? sizeof(EncShared<16, 2, 8>) : sizeof(EncShared<8, 2, 8>)) <= all)
     p.per = 8;
-  if (!decode && c->cfg.B > c->num_cu && p.nw > 1) {
+  if (!decode && c->cfg.B > c->num_cu && p.nw > 1 && p.lds) {
     // workgroups that a CU holds, by its LDS and by 32 (two sets: 28) waves of registers, no more than there are
     auto held = [&](size_t fixed, int waves) {
       return std::min({all / (p.smem + fixed), (size_t)(waves / p.nw), (size_t)((c->cfg.B + c->num_cu - 1) / c->num_cu)});
@@ -1902,20 +1904,20 @@ int z2z_launch_codebook_prefill(z2z_ctx* c, const int32_t* phrases, const int32_
 
 template <int WHERE>
 static void launch_encode(const LzwArgs& a, int B, int nw, int sets, size_t smem, hipStream_t s) {
+  if constexpr (WHERE == kLds) {
+    if (sets == 1 && nw == 4) {
+      hipLaunchKernelGGL((lzw_encode_kernel<4, WHERE, 1>), dim3(B), dim3(256), smem, s, a);
+      return;
+    }
+    if (sets == 1 && nw == 8) {
+      hipLaunchKernelGGL((lzw_encode_kernel<8, WHERE, 1>), dim3(B), dim3(512), smem, s, a);
+      return;
+    }
+  }
   switch (nw) {
     case 1: hipLaunchKernelGGL((lzw_encode_kernel<1, WHERE>), dim3(B), dim3(64), smem, s, a); break;
-    case 4:
-      if (sets == 1)
-        hipLaunchKernelGGL((lzw_encode_kernel<4, WHERE, 1>), dim3(B), dim3(256), smem, s, a);
-      else
-        hipLaunchKernelGGL((lzw_encode_kernel<4, WHERE>), dim3(B), dim3(256), smem, s, a);
-      break;
-    case 8:
-      if (sets == 1)
-        hipLaunchKernelGGL((lzw_encode_kernel<8, WHERE, 1>), dim3(B), dim3(512), smem, s, a);
-      else
-        hipLaunchKernelGGL((lzw_encode_kernel<8, WHERE>), dim3(B), dim3(512), smem, s, a);
-      break;
+    case 4: hipLaunchKernelGGL((lzw_encode_kernel<4, WHERE>), dim3(B), dim3(256), smem, s, a); break;
+    case 8: hipLaunchKernelGGL((lzw_encode_kernel<8, WHERE>), dim3(B), dim3(512), smem, s, a); break;
     default: hipLaunchKernelGGL((lzw_encode_kernel<16, WHERE>), dim3(B), dim3(1024), smem, s, a); break;
   }
 }
