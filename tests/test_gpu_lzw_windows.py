@@ -142,6 +142,40 @@ def test_decode_of_arbitrary_codes(M, cap):
         ctx.close()
 
 
+@pytest.mark.parametrize("M,cap,kernel", [(3, 9000, 0), (5, 9000, 2), (4, 12000, 0), (3, 9000, 4)])
+def test_windows_behind_a_cut_window(M, cap, kernel):
+    """Stretches of a parse's codes, of arbitrary ones and of a parse's with one in sixty replaced, longer and shorter than a
+    window, in turn: windows that are inserted at once, taken back, looked through first, and inserted at once again."""
+    V = 200
+    rng = np.random.default_rng(M)
+    streams = []
+    for b in range(3):
+        s, codes = oracle.LZWStream(V, M, cap), []
+        for part, n in enumerate((1500, 700, 2600, 300, 1100, 60, 1500)):
+            if (part + b) % 3 == 0:                          # pairs that repeat all the time
+                chunk = rng.integers(0, 12, n).tolist()
+            else:                                            # what a parse of these tokens gives, as the codebook stands
+                t = oracle.LZWStream(V, M, cap)
+                t.decode_chunk(codes)
+                chunk = t.encode_chunk(np.minimum(rng.zipf(1.3, n) - 1, V - 1).tolist())[0]
+                if (part + b) % 3 == 2:
+                    chunk = [int(rng.integers(0, 12)) if rng.random() < 1 / 60 else c for c in chunk]
+            for c in chunk:
+                if c < V + len(s.entries):                   # (a replaced code moves the entries behind it)
+                    assert s.decode_chunk([c])[1] == 0
+                    codes.append(c)
+        streams.append(codes)
+    n = min(len(c) for c in streams)
+    rows = np.asarray([c[:n] for c in streams], dtype=np.int32)
+    ref = [oracle.lzw_decode(r.tolist(), V, M, cap) for r in rows]
+    ctx = _ctx(len(rows), V, M, cap, kernel)
+    toks, n_tok, st = gpu_decode(ctx, rows, None, out_stride=M * n)
+    for b in range(len(rows)):
+        assert int(st[b]) == ref[b][2] == 0 and toks[b, :n_tok[b]].tolist() == ref[b][0]
+    assert_codebook_equal(ctx, [r[1] for r in ref], M, cap)
+    ctx.close()
+
+
 @pytest.mark.parametrize("M,cap", [(3, 400), (5, 40), (8, 1500), (2, 0)])
 def test_codes_behind_a_full_codebook(M, cap):
     """Rows so long that the codes behind a full codebook go to a launch of their own, in parts: ragged rows (one too short for
