@@ -645,7 +645,10 @@ struct EncShared {
   uint16_t rank[W];                          // of the proposing starts
 };
 
-constexpr int kParseStaticLds = (int)sizeof(EncShared<kMaxWaves, 2>) + 256;    // + alignment slack
+// What a kernel has of its own in LDS, for the room it leaves to a table: the size of its shared structure, and alignment.
+constexpr int own_lds(size_t shared) { return (int)shared + 256; }
+constexpr int kParseStaticLds = own_lds(sizeof(EncShared<kMaxWaves, 2>));
+constexpr int kWideSets16 = own_lds(sizeof(EncShared<16, 2, 8>)), kWideSets8 = own_lds(sizeof(EncShared<8, 2, 8>));
 
 template <int NW, int SETS, int PER, int WHERE, bool M4>
 __device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, int b, EncShared<NW, SETS, PER>& sh) {
@@ -1699,9 +1702,7 @@ ParsePlan plan(const z2z_ctx* c, int32_t stride, int32_t flags, bool decode, Lzw
   a->lds_ef = ef != 0;
   p.sets = 2;
   p.per = 4;
-  if (!decode && c->cfg.B <= c->num_cu && p.lds && p.nw >= 8 &&
-      p.smem + (p.nw == 16 ? sizeof(EncShared<16, 2, 8>) : sizeof(EncShared<8, 2, 8>)) <= all)
-    p.per = 8;
+  if (!decode && c->cfg.B <= c->num_cu && p.lds && p.nw >= 8 && p.smem + (p.nw == 16 ? kWideSets16 : kWideSets8) <= all) p.per = 8;
   if (!decode && c->cfg.B > c->num_cu && p.nw > 1 && p.lds) {
     // workgroups that a CU holds, by its LDS and by 32 (two sets: 28) waves of registers, no more than there are
     auto held = [&](size_t fixed, int waves) {
@@ -1715,6 +1716,11 @@ ParsePlan plan(const z2z_ctx* c, int32_t stride, int32_t flags, bool decode, Lzw
                  !writes_lengths(*a, (size_t)c->cfg.B);
   p.smem += ef;
   return p;
+}
+// A launch asks for no more dynamic LDS than z2z_lzw_prepare has declared for its kernel.
+bool fits(const z2z_ctx* c, const ParsePlan& p) {
+  const int own = p.per == 8 ? (p.nw == 16 ? kWideSets16 : kWideSets8) : kParseStaticLds;
+  return p.smem + own <= (size_t)c->lds_limit;
 }
 
 // How often each entry is named by a code stream: usage[b][e] += number of codes equal to V + e (codes of base
@@ -1956,6 +1962,7 @@ int z2z_launch_lzw_encode(z2z_ctx* c, const int32_t* tokens, const int32_t* lens
   a.out_stride = out_stride;
   a.status = status;
   const ParsePlan p = plan(c, stride, flags, false, &a);
+  if (!fits(c, p)) return Z2Z_EUNSUPPORTED;
   if (p.tags)
     hipLaunchKernelGGL((lzw_encode_kernel<16, kTag>), dim3(c->cfg.B), dim3(1024), p.smem, s, a);
   else if (p.per == 8 && p.nw == 16)
@@ -1985,6 +1992,7 @@ int z2z_launch_lzw_decode(z2z_ctx* c, const int32_t* codes, const int32_t* n_cod
   a.out_stride = out_stride;
   a.status = status;
   const ParsePlan p = plan(c, stride, flags, true, &a);
+  if (!fits(c, p)) return Z2Z_EUNSUPPORTED;
   const bool serial = stride <= 8 || c->opt_lzw_kernel == 3;
   // Long rows of few sequences: a second launch over all CUs takes the codes behind a full codebook.  A codebook that starts
   // empty is full after cap codes at the earliest; how many follow only the device knows, and the first launch goes on
@@ -2056,7 +2064,7 @@ int z2z_lzw_prepare(z2z_ctx* c) {
   // sequences) is free; with many, LDS decides how many sequences a CU works on at once.
   const bool roomy = c->cfg.B < 256;
   // ... but not where it keeps the encoder from sets of eight slots per position, which gain more than the probes it shortens.
-  const int beside_large_sets = (c->lds_limit - (int)sizeof(EncShared<kMaxWaves, 2, 8>) - 256) / (int)sizeof(u64);
+  const int beside_large_sets = (c->lds_limit - kWideSets16) / (int)sizeof(u64);
   // A CU holds up to four workgroups of 8 waves (32 waves of 64 registers): as many as there are sequences for it, the
   // tables as large as that leaves room for.  Another workgroup hides more than the longer probes cost: 2048 documents of
   // 1024 to 4096 tokens, encode (decode), cap 2048: 4096 slots, three per CU 162 us (152), 2906 slots, four 149 (125); cap
@@ -2105,8 +2113,9 @@ int z2z_lzw_prepare(z2z_ctx* c) {
                          reinterpret_cast<const void*>(lzw_decode_serial_kernel<true>)};
   for (const void* f : parse)
     Z2Z_HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_limit - kParseStaticLds));
-  for (const void* f : {reinterpret_cast<const void*>(lzw_encode_kernel<16, kLds, 2, 8>), reinterpret_cast<const void*>(lzw_encode_kernel<8, kLds, 2, 8>)})
-    Z2Z_HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    c->lds_limit - (int)sizeof(EncShared<kMaxWaves, 2, 8>) - 256));
+  Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(lzw_encode_kernel<16, kLds, 2, 8>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_limit - kWideSets16));
+  Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(lzw_encode_kernel<8, kLds, 2, 8>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_limit - kWideSets8));
   return Z2Z_OK;
 }

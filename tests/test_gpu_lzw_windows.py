@@ -63,6 +63,16 @@ def test_more_sequences_than_compute_units(B, cap):
     _round_trip(tokens, lens, 200, 3, cap)
 
 
+@pytest.mark.parametrize("B,N,cap", [(3, 300, 5000), (3, 300, 8192), (3, 300, 11208), (3, 300, 11209), (256, 600, 4957),
+                                     (256, 600, 4965), (3, 700, 2478), (3, 700, 2479)])
+def test_tables_beside_wide_round_sets(B, N, cap):
+    """Tables of the sizes up to which LDS has room for them beside the encoder's sets of eight slots per position (one window
+    of eight waves, or windows of sixteen), and beside any of its sets: a launch must not ask for more than is declared."""
+    rng = np.random.default_rng(N + cap)
+    tokens = np.minimum(rng.zipf(1.2, (B, N)) - 1, 199).astype(np.int32)
+    _round_trip(tokens, np.full(B, N, np.int32), 200, 3, cap)
+
+
 @pytest.mark.parametrize("B,M,cap", [(520, 3, 2048), (1100, 4, 1500), (800, 5, 3000), (1030, 8, 40), (2700, 3, 200)])
 def test_several_workgroups_of_a_compute_unit(B, M, cap):
     """More than two sequences per CU: three or four workgroups on one, tables cut to what that leaves of the LDS, one round
