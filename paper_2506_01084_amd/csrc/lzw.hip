@@ -34,6 +34,9 @@ struct LzwArgs {
   const int32_t* in;       // tokens (encode) or codes (decode), [B, stride]
   const int32_t* in_len;   // [B] or nullptr
   int32_t stride;
+  // APPEND or RESET, compared whole, never masked: the compiler (clang 22 for gfx950) turns `x & 1` that is asked for != 0 and
+  // for == 0 in one basic block into one s_bitcmp0_b32 that both answers are read from, so that one of them is inverted (seen
+  // in the tag kernels, which then cleared a table that a call continued and kept one that it emptied)
   int32_t flags;
   int32_t* out;            // codes (encode) or tokens (decode), [B, out_stride]
   int32_t* out_n;          // [B]
@@ -369,7 +372,7 @@ __device__ __forceinline__ void table_open_all(const LzwArgs& a, int b, int tid,
   }
   if (WHERE == kTag && probed) {
     uint32_t* tags = t->tags();
-    if (reset) {                               // (chosen per element, the compiler got `reset` the wrong way round further on)
+    if (reset) {
       for (int i = tid; i < pairs; i += THREADS) tags[i] = ~0u;
     } else {
       auto tag = [&](u64 v) -> uint32_t {
@@ -660,7 +663,7 @@ __device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, int b, EncS
   const int lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int V = st.V, M = st.M, cap = st.cap;
-  const bool reset = (a.flags & Z2Z_RESET) != 0;
+  const bool reset = a.flags == Z2Z_RESET;
 
   const int size0 = __builtin_amdgcn_readfirstlane(st.size[b]);
   int C = reset ? 0 : size0;
@@ -952,8 +955,8 @@ template <int NW, int WHERE, int SETS = 2, int PER = 4>
 __global__ void __launch_bounds__(NW * kWave, SETS == 1 ? 8 : 1) lzw_encode_kernel(LzwArgs a) {
   __shared__ EncShared<NW, SETS, PER> sh;
   const int b = sequence_of_block<NW>(a, reinterpret_cast<BlockOrder&>(sh));
-  bool short_append = !(a.flags & Z2Z_RESET) && call_length(a, b) <= kShortAppend;
-  if (WHERE == kTag && !(a.flags & Z2Z_RESET))
+  bool short_append = a.flags != Z2Z_RESET && call_length(a, b) <= kShortAppend;
+  if (WHERE == kTag && a.flags != Z2Z_RESET)
     short_append = min(call_length(a, b), 2 * (a.st.cap - a.st.size[b])) < kTagAppendTokens;
   if (WHERE == kTag && short_append && a.st.M <= 4) {
     lzw_encode_windows<NW, SETS, PER, kMem, true>(a, b, sh);
@@ -983,7 +986,7 @@ template <bool LDS>
 __device__ __forceinline__ void lzw_decode_serial_body(const LzwArgs& a, int b, int lane) {
   const LzwState& st = a.st;
   const int V = st.V, M = st.M, cap = st.cap;
-  const bool reset = (a.flags & Z2Z_RESET) != 0;
+  const bool reset = a.flags == Z2Z_RESET;
   const bool ef_lds = LDS && a.lds_ef;
   uint32_t* ef = reinterpret_cast<uint32_t*>(lds_slots + st.nslots);   // [cap], valid when ef_lds
   int32_t* ent_tokens = st.ent_tokens + (size_t)b * cap * M;
@@ -1221,7 +1224,7 @@ __device__ __forceinline__ void lzw_decode_windows(const LzwArgs& a, int b, DecS
   const int lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int V = st.V, M = st.M, cap = st.cap;
-  const bool reset = (a.flags & Z2Z_RESET) != 0;
+  const bool reset = a.flags == Z2Z_RESET;
   const bool ef_lds = WHERE == kLds && a.lds_ef;
   uint32_t* ef = reinterpret_cast<uint32_t*>(lds_slots + st.nslots);   // [cap], valid when ef_lds
 
@@ -1494,8 +1497,8 @@ template <int NW, int WHERE>
 __global__ void __launch_bounds__(NW * kWave) lzw_decode_kernel(LzwArgs a) {
   __shared__ DecShared<NW> sh;
   const int b = sequence_of_block<NW>(a, reinterpret_cast<BlockOrder&>(sh));
-  bool short_append = !(a.flags & Z2Z_RESET) && call_length(a, b) <= kShortAppend;
-  if (WHERE == kTag && !(a.flags & Z2Z_RESET)) {
+  bool short_append = a.flags != Z2Z_RESET && call_length(a, b) <= kShortAppend;
+  if (WHERE == kTag && a.flags != Z2Z_RESET) {
     const int room = a.st.cap - a.st.size[b];                 // (full: nothing is looked up, the tags are not made)
     short_append = room > 0 && min(call_length(a, b), room) < kTagAppendCodes;
   }
@@ -1817,7 +1820,7 @@ __global__ void __launch_bounds__(kWave) lzw_prefill_kernel(LzwArgs a) {
   const int b = blockIdx.x;
   const int lane = threadIdx.x;
   const int V = st.V, M = st.M, cap = st.cap;
-  const bool reset = (a.flags & Z2Z_RESET) != 0;
+  const bool reset = a.flags == Z2Z_RESET;
   int C = reset ? 0 : __builtin_amdgcn_readfirstlane(st.size[b]);
   Table<false> t;
   table_open<false>(a, b, lane, reset, &t);

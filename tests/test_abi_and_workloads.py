@@ -156,3 +156,12 @@ def test_bench_refuses_more_than_one_gpu():
                        timeout=120)
     assert r.returncode != 0
     assert "single-GPU" in (r.stdout + r.stderr)
+
+
+def test_kernels_compare_the_flags_whole():
+    """The flags of a parse call are one of two values and are compared, not masked: of a masked bit that is asked for both
+    ways in one block the compiler has made one test with one of the answers inverted (lzw.hip, LzwArgs)."""
+    with open(os.path.join(ROOT, "paper_2506_01084_amd", "csrc", "lzw.hip")) as f:
+        source = f.read()
+    assert "a.flags == Z2Z_RESET" in source
+    assert not re.findall(r"\ba\.flags\s*&(?!&)", source)
