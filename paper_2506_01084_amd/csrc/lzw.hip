@@ -1656,7 +1656,7 @@ __global__ void lzw_clear_entries_kernel(LzwState st) {
 //   - While every sequence has a CU to itself, the widest window is the fastest (4096 tokens, 8 sequences: 44 us
 //     with 16 waves, 54 with 8); up to 512 elements a call is a single window of 8 waves.
 //   - With more sequences than CUs, workgroups of a CU hide each other's latencies: 8 waves each where two fit its LDS
-//     (2048 sequences of 4096 tokens, cap 2048: 260 us; 16 waves 576), else 4 (the decoder then without its (length, first
+//     (2048 sequences of 4096 tokens, cap 2048: 260 us; 16 waves 576), else for the decoder 4 (without its (length, first
 //     token) copy), else one of 8.  Up to four fit (z2z_lzw_prepare); the encoder's iterations then share one RoundSet
 //     where two would keep one workgroup from fitting (2048 documents of 1024 to 4096 tokens, cap 2048: two workgroups 200
 //     us, three 162); where they would not, two sets are faster, by a barrier an iteration (500 sequences: 73, one set 82).
@@ -1691,13 +1691,12 @@ ParsePlan plan(const z2z_ctx* c, int32_t stride, int32_t flags, bool decode, Lzw
   p.tags = c->st.tags_fit_lds && p.nw == 16 && c->opt_lzw_kernel != 2 &&
            ((flags & Z2Z_RESET) || stride >= (decode ? kTagAppendCodes : kTagAppendTokens));
   if (p.tags) p.smem = (size_t)c->st.nslots * sizeof(uint16_t);
-  const size_t all = (size_t)c->lds_limit, fixed8 = decode ? sizeof(DecShared<8>) : sizeof(EncShared<8, 1>),
-               fixed4 = decode ? sizeof(DecShared<4>) : sizeof(EncShared<4, 1>);
+  const size_t all = (size_t)c->lds_limit, fixed8 = sizeof(DecShared<8>), fixed4 = sizeof(DecShared<4>);
   size_t ef = decode && p.lds ? (size_t)c->st.cap * sizeof(uint32_t) : 0;
   if (p.smem + ef + kParseStaticLds > all) ef = 0;
   if (c->cfg.B > c->num_cu && p.nw > 1) {
     p.nw = 8;
-    if (p.lds && 2 * (p.smem + ef + fixed8) > all && 2 * (p.smem + fixed4) <= all) {
+    if (decode && p.lds && 2 * (p.smem + ef + fixed8) > all && 2 * (p.smem + fixed4) <= all) {
       p.nw = 4;
       if (2 * (p.smem + ef + fixed4) > all) ef = 0;
     }
@@ -1711,8 +1710,7 @@ ParsePlan plan(const z2z_ctx* c, int32_t stride, int32_t flags, bool decode, Lzw
     auto held = [&](size_t fixed, int waves) {
       return std::min({all / (p.smem + fixed), (size_t)(waves / p.nw), (size_t)((c->cfg.B + c->num_cu - 1) / c->num_cu)});
     };
-    const int one = p.nw == 4 ? (int)sizeof(EncShared<4, 1>) : (int)sizeof(EncShared<8, 1>);
-    if (held(one, 32) > held(p.nw == 4 ? sizeof(EncShared<4, 2>) : sizeof(EncShared<8, 2>), 28)) p.sets = 1;
+    if (held(sizeof(EncShared<8, 1>), 32) > held(sizeof(EncShared<8, 2>), 28)) p.sets = 1;
   }
   const int most = std::min(16 * c->num_cu, (decode ? 4 : 8) * c->num_cu + stride / 2);
   a->by_length = a->in_len != nullptr && c->cfg.B > 2 * c->num_cu && c->cfg.B <= most && p.nw >= 4 && stride >= (decode ? 2048 : 640) &&
@@ -1924,10 +1922,6 @@ int z2z_launch_codebook_prefill(z2z_ctx* c, const int32_t* phrases, const int32_
 template <int WHERE>
 static void launch_encode(const LzwArgs& a, int B, int nw, int sets, size_t smem, hipStream_t s) {
   if constexpr (WHERE == kLds) {
-    if (sets == 1 && nw == 4) {
-      hipLaunchKernelGGL((lzw_encode_kernel<4, WHERE, 1>), dim3(B), dim3(256), smem, s, a);
-      return;
-    }
     if (sets == 1 && nw == 8) {
       hipLaunchKernelGGL((lzw_encode_kernel<8, WHERE, 1>), dim3(B), dim3(512), smem, s, a);
       return;
@@ -1935,16 +1929,20 @@ static void launch_encode(const LzwArgs& a, int B, int nw, int sets, size_t smem
   }
   switch (nw) {
     case 1: hipLaunchKernelGGL((lzw_encode_kernel<1, WHERE>), dim3(B), dim3(64), smem, s, a); break;
-    case 4: hipLaunchKernelGGL((lzw_encode_kernel<4, WHERE>), dim3(B), dim3(256), smem, s, a); break;
     case 8: hipLaunchKernelGGL((lzw_encode_kernel<8, WHERE>), dim3(B), dim3(512), smem, s, a); break;
     default: hipLaunchKernelGGL((lzw_encode_kernel<16, WHERE>), dim3(B), dim3(1024), smem, s, a); break;
   }
 }
 template <int WHERE>
 static void launch_decode(const LzwArgs& a, int B, int nw, size_t smem, hipStream_t s) {
+  if constexpr (WHERE == kLds) {
+    if (nw == 4) {
+      hipLaunchKernelGGL((lzw_decode_kernel<4, WHERE>), dim3(B), dim3(256), smem, s, a);
+      return;
+    }
+  }
   switch (nw) {
     case 1: hipLaunchKernelGGL((lzw_decode_kernel<1, WHERE>), dim3(B), dim3(64), smem, s, a); break;
-    case 4: hipLaunchKernelGGL((lzw_decode_kernel<4, WHERE>), dim3(B), dim3(256), smem, s, a); break;
     case 8: hipLaunchKernelGGL((lzw_decode_kernel<8, WHERE>), dim3(B), dim3(512), smem, s, a); break;
     default: hipLaunchKernelGGL((lzw_decode_kernel<16, WHERE>), dim3(B), dim3(1024), smem, s, a); break;
   }
@@ -2102,8 +2100,6 @@ int z2z_lzw_prepare(z2z_ctx* c) {
   }
   st.nslots &= ~1;                                     // whole buckets
   const void* parse[] = {reinterpret_cast<const void*>(lzw_encode_kernel<1, kLds>),
-                         reinterpret_cast<const void*>(lzw_encode_kernel<4, kLds>),
-                         reinterpret_cast<const void*>(lzw_encode_kernel<4, kLds, 1>),
                          reinterpret_cast<const void*>(lzw_encode_kernel<8, kLds, 1>),
                          reinterpret_cast<const void*>(lzw_encode_kernel<8, kLds>),
                          reinterpret_cast<const void*>(lzw_encode_kernel<16, kLds>),
