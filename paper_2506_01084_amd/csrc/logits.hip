@@ -378,6 +378,12 @@ static bool split_few(const z2z_ctx* c, int rows, bool filtered) {
   return rows > 4 && rows <= 64 && c->opt_decode_kernel == 0 && c->opt_logits_kernel == 0 && pays && z2z_logits_mid_ok(c, rows);
 }
 
+// Whether such a step reads its base vocabulary past the caches: by all of its weights, like the decode kernel that it leaves.
+static bool split_few_once(const z2z_ctx* c, int rows) {
+  return rows <= 64 && z2z_logits_mid_tiles(c->cfg.V) < 256 &&
+         ((size_t)c->cfg.V + (size_t)c->cfg.B * c->cfg.cap) * c->cfg.d * sizeof(uint16_t) > kKeepBytes;
+}
+
 // Parts per row that any kind of step may leave (hyper units of 64 rows): every step sizes the scratch for all of them,
 // so that a greedy one can be captured behind an eager draw at the same shape and the other way round.
 static size_t step_parts(const z2z_ctx* c) {
@@ -436,7 +442,7 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
   const int tile_v = fast ? 256 : z2z_logits_general_columns(c->cfg.dtype == Z2Z_BF16, tiles_b * ((V + 63) / 64) + tiles_h * ((cap + 63) / 64));
   const int base_vt = (V + tile_v - 1) / tile_v, hyp_vt = (cap + tile_v - 1) / tile_v;
   // few hidden rows in all (several per sequence, or 65..192 sequences): the base part is bound by the bytes of
-  // W_base and goes to the kernel that streams the weights past all rows at once, one part per 256 weight rows
+  // W_base and goes to the kernel that streams the weights past all rows at once, one part per 256 weight rows (or 128)
   // (measured against the decode kernel's base units in a launch of their own at up to 64 rows: 260 against 305 us
   // for the call at config 2's shape; two or three passes of those units for more rows cost more still)
   const bool mid_base = fast && c->opt_logits_kernel == 0 && z2z_logits_mid_ok(c, rows);
@@ -512,6 +518,7 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
   int ns = 0;
   if (mid_base) {
     if (timed) Z2Z_HIP_TRY(hipEventRecord(c->ev_start[c->n_timed], s));
+    a.once = decode_split && split_few_once(c, rows);
     rc = z2z_launch_logits_mid(c, a, W_base, V, 0, s);
     if (timed && !decode_split) {
       Z2Z_HIP_TRY(hipEventRecord(c->ev_stop[c->n_timed], s));
@@ -590,6 +597,7 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     a.ctr3 = (uint32_t)(step >> 32);
     int ns = 0;
     if (timed_pair) Z2Z_HIP_TRY(hipEventRecord(c->ev_start[c->n_timed], s));
+    a.once = mid_base && split_few_once(c, rows);
     if (mid_base)
       rc = z2z_launch_logits_mid(c, a, W_base, c->cfg.V, 0, s);
     else
@@ -664,6 +672,7 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     a.ld = c->cfg.V + c->cfg.cap;
     int ns = 0;
     if (timed_pair) Z2Z_HIP_TRY(hipEventRecord(c->ev_start[c->n_timed], s));
+    a.once = mid_base && split_few_once(c, rows);
     if (mid_base)
       rc = z2z_launch_logits_mid(c, a, W_base, c->cfg.V, 0, s);
     else

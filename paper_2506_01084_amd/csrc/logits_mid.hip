@@ -388,7 +388,7 @@ static void launch_mid(const LogitsArgs& a, hipStream_t s) {
 
 // The base part of a call: one part per tile of z2z_logits_mid_columns weight rows.  a: H, rows, d, the part arrays, n_parts, part0
 // filled by the caller; with a.sample = 1 or 2 also the generator words, inv_temperature and part_v / part_l or
-// logits / ld, as for the tile kernel's sampling modes.
+// logits / ld, as for the tile kernel's sampling modes; a.once where the caller knows of more weights that the call reads.
 int z2z_launch_logits_mid(z2z_ctx* c, LogitsArgs a, const void* W, int w_rows, int col0, hipStream_t s) {
   if (!z2z_logits_mid_ok(c, a.rows) || w_rows < 1) return Z2Z_EUNSUPPORTED;
   a.W = W;
@@ -396,7 +396,7 @@ int z2z_launch_logits_mid(z2z_ctx* c, LogitsArgs a, const void* W, int w_rows, i
   a.col0 = col0;
   const int columns = z2z_logits_mid_columns(c, w_rows);
   a.n_vtiles = (w_rows + columns - 1) / columns;
-  a.once = (size_t)w_rows * a.d * sizeof(uint16_t) > kKeepBytes;
+  a.once = a.once || (size_t)w_rows * a.d * sizeof(uint16_t) > kKeepBytes;
   c->n_launch[Z2Z_KERNEL_MID]++;
   // (two workgroups of the 64-row build per weight tile for 65..128 rows, sharing the tile's weights through an
   // XCD's L2, measured slower than one of the 128-row build: 383 against 293 us at config 2's shape)

@@ -89,6 +89,7 @@ def test_split_step(B, V, d, cap, split):
     (33, 131073, 128, 40, 50, 0.9),
     (20, 32700, 384, 500, 0, 1.0),      # tiles of 128 columns
     (33, 32768, 256, 2000, 50, 0.9),    # ... whose parts the filters' kernels read
+    (64, 33000, 1024, 700, 0, 1.0),     # weights past the caches by those of the codebooks
 ])
 def test_split_draws_match_one_launch(B, V, d, cap, top_k, top_p):
     """Draws of a split step against those of the decode kernel in one launch (both oracle-tested on smaller vocabularies):
