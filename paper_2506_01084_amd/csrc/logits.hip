@@ -354,24 +354,27 @@ static int pick_strip_for(const z2z_ctx* c, long long row_tiles, int n_vt, int w
 // Behind other work that has turned the caches over the one launch is 40-60 us slower and the split 2-5.
 // Hence: up to 16 sequences, or more than two rounds, or a last round at least 7/8 full over all rounds, or hyper units that
 // would open another round in one launch.
-// 112 to 255 tiles leave so many CUs to the hyper units that the last of these decides, on fresh inputs.  V = 32064, d = 3072 (126
-// tiles, which the streaming kernel halves), tiles + hyper units, one launch -> split:
-//   above 256   greedy    17 x 4096 (262) 151 -> 105   34 x 2048 (262) 155 -> 132   40 x 2048 160 -> 136   64 x 4096 288 -> 242
-//               draw      17 x 4096 166 -> 113         34 x 2048 174 -> 144         50 x 2048 191 -> 175   64 x 4096 304 -> 260
-//               filtered  17 x 4096 168 -> 139         34 x 2048 183 -> 151         24 x 4096 179 -> 145   64 x 2048 219 -> 200
-//   up to 256   greedy    30 x 2048 (246) 110 -> 113   50 x 1024 (226) 106 -> 109   64 x 1024 (254) 106 -> 117
-//               draw      30 x 2048 115 -> 119         50 x 1024 110 -> 117         64 x 1024 120 -> 128
-//   up to 208   greedy    5 x 1024 (136) 93 -> 64      24 x 1024 (174) 93 -> 80     40 x 1024 (206) 101 -> 97   60 x 256 90 -> 71
-//               draw      12 x 1024 (150) 101 -> 71    8 x 4096 (190) 103 -> 86     40 x 1024 106 -> 104        60 x 256 100 -> 78
-//               filtered  5 x 1024 104 -> 124          16 x 1024 108 -> 126         40 x 1024 119 -> 147 (never there)
-// (Units count whole however few entries they have: above 256 at least 64 of them, so that they are what opens the round.  The
-// figures of 34 x 2048, 40 x 2048 and above and of draws with them are from tiles of 256.)
+// 112 to 255 tiles leave so many CUs to the hyper units that the last of these decides.  Tiles + hyper units, one launch -> split, three
+// sets of weights in turn; in brackets behind 600 MB of other writes:
+//   d = 3072, greedy      112 tiles: 5 x 1024 73 -> 58 (96 -> 58), 24 x 2048 91 -> 92 (131 -> 94), 50 x 2048 (of 312) 177 -> 149 (234 -> 151)
+//                         126: 24 x 1024 79 -> 72 (113 -> 73), 40 x 1024 86 -> 86 (130 -> 87), 17 x 4096 (of 262) 149 -> 118 (198 -> 119)
+//                         160: 17 x 4096 151 -> 131 (205 -> 131)   197: 40 x 1024 149 -> 103 (205 -> 103)   254: 8 x 4096 143 -> 103 (196 -> 103)
+//             draw        112: 5 x 1024 85 -> 65, 24 x 2048 95 -> 96    126: 40 x 1024 93 -> 95, 17 x 4096 168 -> 126    254: 8 x 4096 163 -> 111
+//             filtered    126: 17 x 4096 169 -> 138    197: 40 x 1024 173 -> 148    254: 8 x 4096 164 -> 150, 64 x 4096 349 -> 332
+//   d = 1024, greedy      112: 40 x 1024 46 -> 42 (58 -> 42)   126: 17 x 4096 58 -> 55 (77 -> 55)   197: 40 x 1024 64 -> 48 (83 -> 50)
+//             draw        112: 40 x 1024 71 -> 52    126: 17 x 4096 78 -> 65    254: 40 x 1024 86 -> 67
+//   d = 4096, greedy      126: 8 x 4096 106 -> 99 (148 -> 100)   160: 64 x 1024 197 -> 149 (242 -> 150)   254: 40 x 1024 204 -> 146 (263 -> 144)
+// (d = 512, 768, 1536, 2048 alike; 24 x 2048 over 112 tiles at d = 2048 62 -> 67 in a row, 85 -> 67 behind other writes.)  The split needs
+// halved tiles (up to 128) as long as all fits one round, and up to 208 tiles and units; above a round it needs 64 units, which
+// count whole however few entries they have, so that they are what opens it.  Filtered steps, which store their logits, stay in one launch
+// where all fits one round (5 x 1024 104 -> 124), and for short rows (d <= 1024) until the units fill half of another (d = 1024, 197 tiles: 40 x
+// 1024 86 -> 92, 64 x 1024 91 -> 97; 254: 8 x 4096 81 -> 92; d = 512, 126: 17 x 4096 79 -> 70, 50 x 2048 over 112 89 -> 72).
 static bool split_few(const z2z_ctx* c, int rows, bool filtered) {
   const long long tiles = z2z_logits_mid_tiles(c->cfg.V), slots = (tiles + 255) / 256 * 256;
   int base_columns, hyper_columns;
   z2z_logits_decode_units(&base_columns, &hyper_columns);
   const long long units = (long long)rows * ((c->cfg.cap + hyper_columns - 1) / hyper_columns);
-  const bool full = units >= 64 && tiles + units > slots;
+  const bool full = tiles + units > slots && (filtered && c->cfg.d <= 1024 ? units > 128 : units >= 64);
   const bool halves = !filtered && z2z_logits_mid_columns(c, c->cfg.V) < 256 && 16 * (tiles + units) <= 13 * slots;
   const bool pays = tiles >= 256 ? rows <= 16 || tiles > 512 || 8 * tiles >= 7 * slots || tiles + units > slots
                                  : tiles >= 112 && (full || halves);

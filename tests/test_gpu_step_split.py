@@ -90,6 +90,8 @@ def test_split_step(B, V, d, cap, split):
     (20, 32700, 384, 500, 0, 1.0),      # tiles of 128 columns
     (33, 32768, 256, 2000, 50, 0.9),    # ... whose parts the filters' kernels read
     (64, 33000, 1024, 700, 0, 1.0),     # weights past the caches by those of the codebooks
+    (32, 50000, 1152, 1000, 50, 0.9),   # 196 tiles, 64 units
+    (43, 50000, 1024, 1100, 50, 0.9),   # ... 129, rows of 2 KB
 ])
 def test_split_draws_match_one_launch(B, V, d, cap, top_k, top_p):
     """Draws of a split step against those of the decode kernel in one launch (both oracle-tested on smaller vocabularies):
@@ -179,4 +181,29 @@ def test_sums_keep_the_decode_kernels_precision():
     rms = float(torch.cat(err).square().mean().sqrt())
     print(f"[case] largest logits of 64 rows: relative error {rms:.2e}", flush=True)
     assert rms <= 1.2e-7
+    ctx.close()
+
+
+@pytest.mark.parametrize("B,V,d,cap", [(32, 50000, 1024, 1000), (64, 50000, 256, 1000), (20, 32700, 384, 500)])
+def test_filtered_steps_in_one_launch(B, V, d, cap):
+    """Filtered steps that a draw splits and they do not: rows of up to 2 KB until the hyper units fill half of another round, and
+    whatever fits one round."""
+    import torch
+
+    from paper_2506_01084_amd import api
+
+    ctx = api.Context(B=B, V=V, M=3, cap=cap, d=d, dtype="bf16", pool="mean")
+    ctx.reset()
+    gen = torch.Generator(device="cuda").manual_seed(V + B)
+    E = (torch.randn((V, d), generator=gen, device="cuda") * d ** -0.5).bfloat16()
+    W = torch.zeros((B, cap, d), dtype=torch.bfloat16, device="cuda")
+    H = torch.randn((B, d), generator=gen, device="cuda").bfloat16()
+    token, lp = torch.full((B,), -5, dtype=torch.int32, device="cuda"), torch.full((B,), 777.0, device="cuda")
+    for filters, split in ((dict(top_k=1), 0), (dict(), 1)):
+        before = ctx.read_launches()["mid"]
+        ctx.extended_sample(H, 1, E, W, 0.8, 77, 5, token, lp, **filters)
+        torch.cuda.synchronize()
+        assert ctx.read_launches()["mid"] - before == split
+        if filters:                     # one column is kept: the largest logit, whose log-probability is 0
+            assert torch.equal(token.long(), (H.float() @ E.float().t()).argmax(1)) and (lp == 0).all()
     ctx.close()
