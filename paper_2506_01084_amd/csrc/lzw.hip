@@ -677,7 +677,9 @@ __device__ __forceinline__ void lzw_encode_windows(const LzwArgs& a, int b, EncS
 
   Table<WHERE> t;
   table_open_all<WHERE, W>(a, b, tid, reset, &t);
-  for (int i = tid; i < SETS * kSet; i += W) sh.set[0][i] = kRoundEmpty;
+  if (C < cap) {                      // (behind a full codebook nothing is proposed)
+    for (int i = tid; i < SETS * kSet; i += W) sh.set[0][i] = kRoundEmpty;
+  }
   // tokens: the ring holds [fill - kRing, fill); the next W of them wait in a register
   auto classify = [&](int32_t v) -> int32_t { return (v >= 0 && v < V) ? v : -2; };
   int fill = kRing;
