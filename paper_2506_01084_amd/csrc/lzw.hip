@@ -2068,11 +2068,15 @@ int z2z_lzw_prepare(z2z_ctx* c) {
   const bool roomy = c->cfg.B < 256;
   // ... but not where it keeps the encoder from sets of eight slots per position, which gain more than the probes it shortens.
   const int beside_large_sets = (c->lds_limit - kWideSets16) / (int)sizeof(u64);
-  // A CU holds up to four workgroups of 8 waves (32 waves of 64 registers): as many as there are sequences for it, the
-  // tables as large as that leaves room for.  Another workgroup hides more than the longer probes cost: 2048 documents of
+  // A CU holds up to four workgroups of 8 waves (32 waves of 64 registers; the decoder's, with 67, three): as many as there are
+  // sequences for it, the tables as large as that leaves room for.  Another workgroup hides more than the longer probes cost: 2048 documents of
   // 1024 to 4096 tokens, encode (decode), cap 2048: 4096 slots, three per CU 162 us (152), 2906 slots, four 149 (125); cap
   // 3000: 6000 slots, two 237 (177), 4440 slots, three 171 (163).  More than there are sequences for only costs: 600 of 4096
-  // tokens, cap 2048: 4096 slots 67 us, 2561 slots 81 (four workgroups on one CU, fewer on another).
+  // tokens, cap 2048: 4096 slots 67 us, 2561 slots 81 (four workgroups on one CU, fewer on another).  That holds down to 1.25
+  // slots per entry (2048 documents, encode (decode): cap 2150 170 us (145) -> 156 (119), cap 3500 210 (207) -> 172 (151)).  What
+  // it costs are short calls on the tables where they are, nearly full ones above all: 1024 sequences, cap 2048, 97 % full, 4096
+  // -> 2906 slots: an appended token 9.6 -> 10.8 us, a step update 11.8 -> 12.6, 16 appended codes 11.9 -> 14.  (Two steps of a probe at
+  // once there gave back half of it, but its registers took a workgroup off the CU: decode of 768 of 400 codes 15.8 -> 20.2.)
   int shared = 0;
   if (c->cfg.B > c->num_cu) {
     for (int k = std::min(4, (c->cfg.B + c->num_cu - 1) / c->num_cu); k >= 2 && shared == 0; --k) {
