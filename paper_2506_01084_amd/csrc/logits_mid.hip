@@ -17,6 +17,8 @@
 //   into LDS stages, two slabs ahead (one in the 192-row build, which has room for two stages beside three ring slots), in the
 //   tile kernel's swizzled layout (conflict-free operand reads); one barrier per slab.
 //   The tiles start their walk over K at different slabs (+5-7 %: see below).
+//   Where tiles of 256 would leave half of the CUs without one, a workgroup is four waves and 128 weight rows, and has the LDS
+//   for both operands up to five slabs ahead (z2z_logits_mid_columns).
 //
 // V = 128256, d = 4096, whole calls in us, operand-layout loads -> ring: 8 x 5 rows 207 -> 187, 24 x 5 258 -> 211, steps of
 // 16 / 64 / 100 / 128 sequences 213 -> 185, 272 -> 244, 340 -> 300, 365 -> 323,
@@ -133,10 +135,10 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
         load16_to_lds(p, wsrc[i], to);
     }
   };
-  // hidden rows: the 4 NJV groups of 8 rows of a slab are dealt to the waves, group g = i * 8 + wave for the
+  // hidden rows: the 4 NJV groups of 8 rows of a slab are dealt to the waves, group g = i * WAVES + wave for the
   // wave's i-th request; lane l moves, for row g * 8 + (l >> 3), the chunk that lands at position l & 7 of the row's
   // 128 LDS bytes: chunk (l & 7) ^ ((row >> 1) & 7).  Rows past the last valid one read the last valid one.
-  constexpr int HL = (4 * NJV) / WAVES;                  // requests per wave and slab
+  constexpr int HL = (4 * NJV) / WAVES;                    // requests per wave and slab
   static_assert(HL * WAVES == 4 * NJV, "whole groups per wave");
   const unsigned char* Ht = reinterpret_cast<const unsigned char*>(a.H);
   const uint32_t lds_base = lds_offset_of(lds);
