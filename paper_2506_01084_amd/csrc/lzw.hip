@@ -8,9 +8,10 @@
 // give the argument why the result is that of the one-element-at-a-time loop.
 //
 // Measured, kernel time encode; decode (before: rounds of 256 elements, four waves, cut at the first element that depends
-// on an entry of the round): 8 sequences of 4096 tokens, M = 3, cap 2048: 110 -> 44 -> 42 us; 89 -> 32 -> 28 us.  4 of 32768,
-// M = 4, cap 8192: 691 -> 211; 391 -> 125 -> 84.  16 of 16384, M = 5, cap 16384 (table in memory, its tags in LDS): 657 -> 284 -> 185; 449 -> 157 -> 75.
-// 2048 of 1024 to 4096, cap 2048: 224 -> 149; 163 -> 113 (up to four workgroups on a CU).  1 of 512: 24 -> 11.5; 22 -> 9.
+// on an entry of the round; inputs in the caches): 8 sequences of 4096 tokens, M = 3, cap 2048: 110 -> 44 -> 40 us; 89 -> 32 -> 28 us.
+// 4 of 32768, M = 4, cap 8192: 691 -> 211 -> 210; 391 -> 125 -> 85.  16 of 16384, M = 5, cap 16384 (table in memory, its tags in LDS):
+// 657 -> 284 -> 187; 449 -> 157 -> 76.  2048 of 1024 to 4096, cap 2048: 224 -> 149 (up to four workgroups on a CU); 163 -> 113 (three).
+// 1 of 512: 24 -> 11; 22 -> 8.3.
 //
 // The codebook is a trie stored as a hash table over its edges: one 64-bit slot = parent code (24 bits)
 // | token (24 bits) | entry index (16 bits), two slots per bucket, two buckets per probe step (Table).  The
@@ -67,8 +68,8 @@ extern __shared__ __align__(16) u64 lds_slots[];   // the sequence's hash table 
 // of 16 bytes, hit or miss; with the tags a miss is a matter of LDS and a hit one request of 8 bytes, the slot itself.
 // (Tags of 32 bits, with the entry's index, left LDS for 28100 slots only, and calls that go to the table in memory all the
 // same met it fuller: 2000 tokens appended to a full codebook of 22000 entries, 16 sequences, 44000 -> 28100 slots 13 -> 20 us.)
-// 16 sequences of 16384 tokens, cap 16384, M = 5: encode 272 -> 185 us, decode 156 -> 100; 100 of 8192, cap 12000, M = 3:
-// 134 -> 89; 109 -> 69.
+// 16 sequences of 16384 tokens, cap 16384, M = 5: encode 272 -> 187 us, decode 156 -> 100 (76 by now); 100 of 8192, cap 12000,
+// M = 3: 134 -> 91; 109 -> 69 (54).
 enum { kMem, kLds, kTag };
 template <int WHERE>
 struct Table {
@@ -1520,7 +1521,7 @@ __global__ void __launch_bounds__(NW * kWave) lzw_decode_kernel(LzwArgs a) {
 // itself (a chain of parts, each waiting for the one before, would be as long as the window kernel's).
 //
 // What bounds it: the launch, two dependent trips to L2 per 1024 codes before the part.  4 sequences of 22300 codes, of which
-// 13700 lie behind the 8192 entries of a full codebook: 35 us in the window kernel, 10 here; 27400 behind 1024: 84 -> 32 in all.
+// 13700 lie behind the 8192 entries of a full codebook: 35 us in the window kernel, 10 here; 27400 behind 1024: 84 -> 33 in all.
 __global__ void __launch_bounds__(1024) lzw_decode_tail_kernel(LzwArgs a) {
   constexpr int W = 1024, NW = W / kWave;
   struct Shared {
