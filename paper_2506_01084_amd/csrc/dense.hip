@@ -207,6 +207,15 @@ int z2z_launch_linear_parts(z2z_ctx* c, const void* A, const void* W, int R, con
   return Z2Z_OK;
 }
 
+namespace {
+constexpr size_t kSplitBytes = (size_t)256 * 256 * 256 * sizeof(float);      // LogitsArgs::split
+// Contractions from this many slabs on may be cut: half of them saved is worth the launch of the sum (5 us where nothing was cut:
+// 0.1 ms of a training step's 171).  Learned encoder over codebooks with room for 2048 entries, a whole prompt: 2 x 148 tokens, d = 3584
+// 1054 -> 694 us, 2 x 354, d = 3072 1019 -> 742, 8 x 847, d = 4096 8.59 -> 8.21 ms; a training step with it, 1 x 67 tokens, d = 4096 6.50 ->
+// 5.24 ms; where the host knows the rows, 4 x 1347 without it, V = 151936 21.3 -> 19.3 ms (84 tiles: four parts were two rounds, three are one).
+constexpr int kSplitSlabs = 32;
+}  // namespace
+
 bool z2z_linear_takes_pitch(const z2z_ctx* c, int R, int N, int K) {
   // (more rows than the few-row kernels take, and not split over K by z2z_launch_linear_parts)
   const long long tiles = (long long)((R + 255) / 256) * ((N + 255) / 256);
@@ -217,9 +226,12 @@ int z2z_launch_linear(z2z_ctx* c, const void* A, const void* W, const float* bia
                       void* out, int R, const int32_t* rows_dev, int N, int K, hipStream_t s, const int32_t* k_dev,
                       bool stream_f32, const z2z_linear_pitch* pitch, bool once) {
   if (pitch && !z2z_linear_takes_pitch(c, R, N, K)) return Z2Z_EUNSUPPORTED;
+  // (more rows than one tile's: how many there are, and with them whether a cut along K pays, may be known on the device only)
+  const bool tile_parts = R > 256 && K / 64 >= kSplitSlabs && c->fast_ready && K % 64 == 0 && N % 8 == 0 && c->opt_logits_kernel != 1;
   const float* partial = nullptr;
   int ksplit = 0;
-  int rc = z2z_launch_linear_parts(c, A, W, R, rows_dev, N, K, k_dev != nullptr, &partial, &ksplit, s, once);
+  int rc = Z2Z_OK;
+  if (!tile_parts) rc = z2z_launch_linear_parts(c, A, W, R, rows_dev, N, K, k_dev != nullptr, &partial, &ksplit, s, once);
   if (rc != Z2Z_OK) return rc;
   if (ksplit > 0) {
     const long long n_threads = (long long)R * (N / 4);
@@ -230,7 +242,7 @@ int z2z_launch_linear(z2z_ctx* c, const void* A, const void* W, const float* bia
   }
   // few rows: bound by the weight bytes, which the decode-step kernel streams at HBM rate (it re-reads them
   // once per 64 rows, so it loses to the tile kernel beyond a few hundred rows)
-  if (R <= 512 && c->skinny_ready && K % 128 == 0 && N % 2 == 0 && c->opt_logits_kernel != 2)
+  if (!tile_parts && R <= 512 && c->skinny_ready && K % 128 == 0 && N % 2 == 0 && c->opt_logits_kernel != 2)
     return z2z_launch_linear_skinny(c, A, W, bias, residual, act, out, R, rows_dev, N, K, s, stream_f32);
   if (!c->fast_ready || K % 64 != 0 || N % 8 != 0 || R < 1) return Z2Z_EUNSUPPORTED;
   LogitsArgs a;
@@ -255,6 +267,12 @@ int z2z_launch_linear(z2z_ctx* c, const void* A, const void* W, const float* bia
   a.stream_f32 = stream_f32 ? 1 : 0;
   a.rows_dev = rows_dev;
   a.k_dev = k_dev;
-  const unsigned grid = z2z_logits_fast_order(a, 0);
-  return z2z_launch_logits_fast(2, a, grid, s);
+  unsigned grid = z2z_logits_fast_order(a, 0);
+  // (without room for the parts, under capture for instance, the tiles stay whole)
+  if (tile_parts && ensure_partial(c, kSplitBytes, s) == Z2Z_OK) {
+    a.split = reinterpret_cast<float*>(c->skinny_partial);
+    grid = 256;
+  }
+  rc = z2z_launch_logits_fast(2, a, grid, s);
+  return rc == Z2Z_OK && a.split ? z2z_launch_tile_sum(a, s) : rc;
 }

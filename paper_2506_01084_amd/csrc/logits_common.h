@@ -228,6 +228,8 @@ struct LogitsArgs {
   // part ks covers K slabs [ks * slabs_per_part, ...) and leaves its fp32 tile in partial[ks][row][col]
   int32_t ksplit, slabs_per_part;
   float* partial;           // [ksplit][rows][ldo]
+  // dense layer whose last round of tiles may be cut along K, as the device sees fit: 256 tile buffers of 256 x 256; nullptr: never
+  float* split;
   // sampling fold (base part of a sampled decode step with many rows): the triples are taken over
   // logit * inv_temperature, and next to them the largest perturbed value (part_v), the scaled logit there
   // (part_l) and its column (part_i, instead of the maximum's); generator key and counter words as in the
@@ -394,6 +396,8 @@ int z2z_launch_logits_general(bool bf16, int columns, const z2z_logits::LogitsAr
 // 3 base part, 4 hyper part storing the gradient with respect to the logits, 5 dense layer with K split
 // (fp32 partial tiles)
 int z2z_launch_logits_fast(int mode, const z2z_logits::LogitsArgs& a, unsigned grid, hipStream_t s);
+// behind a dense layer launched with LogitsArgs::split, on 256 workgroups: the sums of the tiles that the device has cut along K
+int z2z_launch_tile_sum(const z2z_logits::LogitsArgs& a, hipStream_t s);
 // order and grid of a base part or dense layer (modes 0, 2, 3, 6 - 9): a.row_tiles, n_vtiles and n_strips are set; `forced`:
 // Z2Z_OPT_LOGITS_MAP, 0 for the automatic order
 unsigned z2z_logits_fast_order(z2z_logits::LogitsArgs& a, int forced);

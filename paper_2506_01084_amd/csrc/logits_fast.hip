@@ -146,6 +146,50 @@ __device__ __forceinline__ bool locate_base(const LogitsArgs& a, int row_tiles, 
   return true;
 }
 
+// Length of that list.
+__device__ __forceinline__ int list_length(const LogitsArgs& a, int row_tiles, int xcd) {
+  const int P = a.map_p_rows ? row_tiles : a.n_strips, Q = a.map_p_rows ? a.n_strips : row_tiles;
+  const int blocks = P / (a.map_lp * a.map_xp);
+  const int own_q = (Q - xcd / a.map_xp + a.map_xq - 1) / a.map_xq;
+  const long long total = (long long)(P - blocks * a.map_lp * a.map_xp) * Q;
+  return blocks * a.map_lp * own_q + (int)(total * (xcd + 1) / 8) - (int)(total * xcd / 8);
+}
+
+// A dense layer's last round.  The 32 workgroups of an XCD take 32 output tiles of its list at a time; the `rem` tiles that are
+// left may be too few for them, and then every one of those is cut along K into `ways` parts of `per` slabs: position
+// full + part * rem + t is part `part` of tile full + t, its fp32 sums go to tile buffer xcd * 32 + part * rem + t, and
+// tile_sum_kernel adds the parts up, in order, with the layer's epilogue.  Decided here, where the row count is known: the host lays
+// out rows for codebooks that are full.  A part is worth it from 16 slabs saved on (17-20 us; the sum reads at most 64 MB, about 10).
+struct LastRound {
+  int full, rem, ways, per;
+};
+constexpr int F_XCD_WGS = 32;                // workgroups of an XCD that a dense layer is launched with where it may be cut
+constexpr int F_MIN_SAVED = 16;              // slabs
+constexpr int F_MIN_PART = 4;
+__device__ __forceinline__ LastRound last_round(const LogitsArgs& a, int row_tiles, int xcd, int n_slabs) {
+  const int len = list_length(a, row_tiles, xcd);
+  LastRound r;
+  r.full = len & ~(F_XCD_WGS - 1);
+  r.rem = len - r.full;
+  r.ways = 1;
+  r.per = n_slabs;
+  if (r.rem > 0 && r.rem <= F_XCD_WGS / 2) {
+    const int ways = min(F_XCD_WGS / r.rem, max(n_slabs / F_MIN_PART, 1));
+    const int per = (n_slabs + ways - 1) / ways;
+    if (n_slabs - per >= F_MIN_SAVED) {
+      r.ways = (n_slabs + per - 1) / per;    // no empty parts
+      r.per = per;
+    }
+  }
+  return r;
+}
+
+// Slabs of a dense layer's contraction (k_dev: its length is known on the device only).
+__device__ __forceinline__ int dense_slabs(const LogitsArgs& a) {
+  const int n = (a.d * 2) / F_SLAB;
+  return a.k_dev ? max(1, min(n, (*a.k_dev * 2 + F_SLAB - 1) / F_SLAB)) : n;
+}
+
 struct Frags {
   uint4 a[F_N];
   uint4 b[F_N];
@@ -603,21 +647,35 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
     Wp += (size_t)ks * a.slabs_per_part * F_SLAB;    // this part's slabs start here in every row
     Hm += (size_t)ks * a.slabs_per_part * F_SLAB;
   }
-  auto item = [&](int j, int* r0, int* st) -> bool {
+  const int n_vt = min(a.n_vtiles, (n_valid + FT - 1) / FT);
+  int n_slabs = MODE == 5 ? min(a.slabs_per_part, (int)(row_bytes / F_SLAB) - ks * a.slabs_per_part)
+                          : (int)(row_bytes / F_SLAB);
+  if (MODE == 2) n_slabs = dense_slabs(a);
+  // the item's slabs [s0, s0 + sn) and, where it is a part of a tile, the buffer of its sums (else -1)
+  const LastRound last = MODE == 2 && a.split ? last_round(a, row_tiles_now, (int)(blockIdx.x & 7), n_slabs) : LastRound{0, 0, 1, n_slabs};
+
+  auto item = [&](int j, int* r0, int* st, int* s0, int* sn, int* part) -> bool {
+    *s0 = 0;
+    *sn = n_slabs;
+    *part = -1;
     if (!LIST) {
       *r0 = one_r0;
       *st = one_st;
       return j == 0;
+    }
+    if (MODE == 2 && last.ways > 1 && j >= last.full) {
+      const int p = j - last.full, ks = p / last.rem;
+      if (ks >= last.ways) return false;
+      j = last.full + p - ks * last.rem;
+      *s0 = ks * last.per;
+      *sn = min(last.per, n_slabs - *s0);
+      *part = (int)(blockIdx.x & 7) * F_XCD_WGS + p;
     }
     int rt;
     if (!locate_base(a, row_tiles_now, (int)(blockIdx.x & 7), j, &rt, st)) return false;
     *r0 = rt * FT;
     return true;
   };
-  const int n_vt = min(a.n_vtiles, (n_valid + FT - 1) / FT);
-  int n_slabs = MODE == 5 ? min(a.slabs_per_part, (int)(row_bytes / F_SLAB) - ks * a.slabs_per_part)
-                          : (int)(row_bytes / F_SLAB);
-  if (MODE == 2 && a.k_dev) n_slabs = max(1, min(n_slabs, (*a.k_dev * 2 + F_SLAB - 1) / F_SLAB));
 
   // ---- loader: lane l of wave w, instruction i moves the chunk that lands at LDS byte
   //      ((w * F_PAIRS + i) * 8 + (l >> 3)) * 128 + (l & 7) * 16 of the operand tile; offsets are relative to
@@ -635,7 +693,7 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
   const unsigned char* Wtile = Wp;
   const unsigned char* Hp = Hm;
   // ---- the cursor of the operand stream: slab lslab of weight tile lvt of the item at position lj (none: !live) ----------
-  int lj = first, lslab = 0, lvt = 0, lvt_end = 0, rot = 0;
+  int lj = first, lslab = 0, lslab_end = n_slabs, lvt = 0, lvt_end = 0, rot = 0;
   bool live = true;
   auto set_tile = [&](int vt) {
     Wtile = Wp + (size_t)vt * FT * pitch_w;
@@ -643,9 +701,11 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
     for (int i = 0; i < F_PAIRS; ++i) voffA[i] = row_offset(i, n_valid - 1 - vt * FT, pitch_w);
   };
   auto open_item = [&]() {
-    int r0, st;
-    live = item(lj, &r0, &st);
+    int r0, st, s0, sn, part;
+    live = item(lj, &r0, &st, &s0, &sn, &part);
     if (!live) return;
+    lslab = s0;
+    lslab_end = s0 + sn;
     lvt = st * a.strip;
     lvt_end = min(lvt + a.strip, n_vt);
     live = lvt < lvt_end;
@@ -682,8 +742,8 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
       load16_to_lds<(n >> 1) * 1024>(is_ga, voffA[n >> 1], isA);
   };
   auto issue_end = [&]() {
-    if (live && ++lslab == n_slabs) {
-      lslab = 0;
+    if (live && ++lslab == lslab_end) {
+      lslab = 0;                               // (a strip of several tiles is never a part)
       if (++lvt < lvt_end) {
         set_tile(lvt);
       } else {
@@ -775,8 +835,8 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
     static_for<16>([&](auto n) __attribute__((always_inline)) { read_one(f[0], 0, 0, n); });
     if (PROBE_MFMA) static_for<16>([&](auto n) __attribute__((always_inline)) { read_one(f[1], 0, 1, n); });
   }
-  int r0, st;
-  for (int j = first; item(j, &r0, &st); j += step) {
+  int r0, st, s0, sn, part;
+  for (int j = first; item(j, &r0, &st, &s0, &sn, &part); j += step) {
     Triple run[F_N];
     Draw draw[F_N];                                  // MODE 6 only
 #pragma unroll
@@ -787,14 +847,16 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
     const int vt0 = st * a.strip, vt_end = min(vt0 + a.strip, n_vt);      // (modes 1, 4: possibly no tile)
     for (int vt = vt0; vt < vt_end; ++vt) {
       slab_step(std::true_type{});
-      for (int slab = 1; slab < n_slabs; ++slab) slab_step(std::false_type{});
+      for (int slab = 1; slab < sn; ++slab) slab_step(std::false_type{});
       if (PROBE_MFMA && vt + 1 < vt_end) continue;
       wait_for_mfma();
       // ---- this vocabulary tile is complete: fold its 128 x 128 logits into the running triples, or store it ------
       int row_base = r0 + wr * 128, col_base = vt * FT + wv * 128 + quarter * 4;
       asm volatile("" : "+v"(col_base), "+v"(row_base));   // (what follows from them is not worked out ahead of the K loop and kept)
       if (MODE == 2) {
-        if (a.stream_f32)
+        if (part >= 0)
+          store_partial16(acc, a.split + (ptrdiff_t)part * (FT * FT) - ((ptrdiff_t)r0 * FT + vt * FT), FT, row_base, r_end, col_base, n_valid);
+        else if (a.stream_f32)
           store_tile16_f32(acc, a, row_base, r_end, col_base, n_valid);
         else
           store_tile16(acc, a, row_base, r_end, col_base, n_valid);
@@ -859,6 +921,71 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
   __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): the requests past the end of the stream land in LDS
 }
 
+// A dense layer's epilogue on 4 columns of a row.
+__device__ __forceinline__ void finish_linear(const LogitsArgs& a, int row, int col, float4 x, const float4& bias) {
+  const size_t at = (size_t)row * a.ldo + col;
+  x.x += bias.x;
+  x.y += bias.y;
+  x.z += bias.z;
+  x.w += bias.w;
+  if (a.act == 1) {
+    x.x = gelu_erf(x.x);
+    x.y = gelu_erf(x.y);
+    x.z = gelu_erf(x.z);
+    x.w = gelu_erf(x.w);
+  }
+  if (a.stream_f32) {                                // fp32 residual and output: no rounding
+    if (a.residual) {
+      const float4 rv = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(a.residual) + at);
+      x.x += rv.x;
+      x.y += rv.y;
+      x.z += rv.z;
+      x.w += rv.w;
+    }
+    *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.out) + at) = x;
+    return;
+  }
+  if (a.residual) {
+    const uint2 rv = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(a.residual) + at);
+    x.x += __uint_as_float(rv.x << 16);
+    x.y += __uint_as_float(rv.x & 0xFFFF0000u);
+    x.z += __uint_as_float(rv.y << 16);
+    x.w += __uint_as_float(rv.y & 0xFFFF0000u);
+  }
+  *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.out) + at) = uint2{pack_bf16(x.x, x.y), pack_bf16(x.z, x.w)};
+}
+
+// The tiles of a dense layer's last round that were cut along K (last_round): out = act(sum of the parts + bias) + residual.  Grid
+// (8 XCDs x 16 tiles, 8 runs of 32 rows); a thread has 4 columns of 8 rows.  Bound by the parts' bytes: 60 MB in 14 us.
+__global__ void __launch_bounds__(256) tile_sum_kernel(LogitsArgs a) {
+  const int xcd = blockIdx.x & 7, t = blockIdx.x >> 3;
+  const int r_end = a.rows_dev ? min(a.rows, *a.rows_dev) : a.rows;
+  const int row_tiles = (r_end + FT - 1) / FT;
+  const LastRound last = last_round(a, row_tiles, xcd, dense_slabs(a));
+  int rt, st;
+  if (last.ways < 2 || t >= last.rem || !locate_base(a, row_tiles, xcd, last.full + t, &rt, &st)) return;
+  const int tcol = 4 * (int)(threadIdx.x & 63), col = st * FT + tcol;
+  if (col >= a.w_rows) return;
+  const float4 bias = a.bias ? *reinterpret_cast<const float4*>(a.bias + col) : float4{0.f, 0.f, 0.f, 0.f};
+  const size_t part_step = (size_t)last.rem * (FT * FT);
+#pragma unroll 2
+  for (int i = 0; i < 8; ++i) {
+    const int trow = (int)blockIdx.y * 32 + i * 4 + (int)(threadIdx.x >> 6), row = rt * FT + trow;
+    if (row >= r_end) return;
+    const float* from = a.split + (size_t)(xcd * F_XCD_WGS + t) * (FT * FT) + trow * FT + tcol;
+    float4 x = *reinterpret_cast<const float4*>(from);
+#pragma unroll 4
+    for (int k = 1; k < last.ways; ++k) {
+      const float4 y = *reinterpret_cast<const float4*>(from + (size_t)k * part_step);
+      x.x += y.x;
+      x.y += y.y;
+      x.z += y.z;
+      x.w += y.w;
+    }
+    finish_linear(a, row, col, x, bias);
+  }
+}
+
 }  // namespace
 
 unsigned z2z_logits_fast_order(LogitsArgs& a, int forced) {
@@ -914,6 +1041,12 @@ int z2z_launch_logits_fast(int mode, const LogitsArgs& a, unsigned grid, hipStre
     hipLaunchKernelGGL(logits_fast_kernel<1>, dim3(grid), dim3(F_THREADS), F_LDS, s, a);
   else
     hipLaunchKernelGGL(logits_fast_kernel<0>, dim3(grid), dim3(F_THREADS), F_LDS, s, a);
+  Z2Z_HIP_TRY(hipGetLastError());
+  return Z2Z_OK;
+}
+
+int z2z_launch_tile_sum(const LogitsArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(tile_sum_kernel, dim3(8 * F_XCD_WGS / 2, FT / 32), dim3(256), 0, s, a);
   Z2Z_HIP_TRY(hipGetLastError());
   return Z2Z_OK;
 }
