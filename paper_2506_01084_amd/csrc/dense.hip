@@ -68,75 +68,6 @@ __global__ void __launch_bounds__(256) linear_sum_kernel(const float* partial, i
   *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(out) + at) = o;
 }
 
-// out[b][c][r] = in[b][r][c] (bf16) for r < R (and r < *rows_dev when given), c < C; columns up to ld_out of out
-// beyond that are zero (they pad the contraction of a product over rows).  64 x 64 tiles through LDS, 256
-// threads, 16 bytes per lane on both sides (ld_in and ld_out are multiples of 8, the bases 16-byte aligned); grid
-// (ceil(ld_out / 64), ceil(C / 64), batch).  A copy that is more than the memory-side cache holds goes PAST the caches on
-// both sides (whole lines, each once): the 30 copies of a training step over 8 x 4096 tokens, 46 GB moved, 9.5 -> 8.3 ms.
-// A smaller one is read by the next launch, and so is what it was made from; with few rows those wait for it: 5 x 107
-// tokens, d = 3584, the four products over transposed weights of a layer 1264 us, 1526 when the copies went past the caches.
-typedef __attribute__((__vector_size__(16))) uint32_t u32x4;
-constexpr size_t kPastCaches = (size_t)256 << 20;
-template <bool PAST>
-__global__ void __launch_bounds__(256) transpose_bf16_kernel(const uint16_t* in, uint16_t* out, int R, const int32_t* rows_dev,
-                                                             int C, int ld_in, int ld_out, size_t in_batch,
-                                                             size_t out_batch) {
-  __shared__ uint16_t t[64][72];                     // [column of the tile][row of the tile], rows padded
-  if (rows_dev) R = min(R, *rows_dev);
-  const uint16_t* src = in + (size_t)blockIdx.z * in_batch;
-  uint16_t* dst = out + (size_t)blockIdx.z * out_batch;
-  const int r0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
-  const int chunk = threadIdx.x & 7, line = threadIdx.x >> 3;       // 8 chunks of 8 elements per line, 32 lines
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int i = line + 32 * h;                     // row of the tile
-    const int r = r0 + i, c = c0 + chunk * 8;
-    uint4 v = {0u, 0u, 0u, 0u};
-    if (r < R && c < ld_in) {
-      const u32x4* from = reinterpret_cast<const u32x4*>(src + (size_t)r * ld_in + c);
-      v = __builtin_bit_cast(uint4, PAST ? __builtin_nontemporal_load(from) : *from);
-    }
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      t[chunk * 8 + 2 * e][i] = (uint16_t)(w[e] & 0xFFFFu);
-      t[chunk * 8 + 2 * e + 1][i] = (uint16_t)(w[e] >> 16);
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int i = line + 32 * h;                     // column of the tile = row of the output
-    const int c = c0 + i, r = r0 + chunk * 8;
-    if (c < C && r < ld_out) {
-      const u32x4 v = *reinterpret_cast<const u32x4*>(&t[i][chunk * 8]);
-      u32x4* to = reinterpret_cast<u32x4*>(dst + (size_t)c * ld_out + r);
-      if (PAST)
-        __builtin_nontemporal_store(v, to);
-      else
-        *to = v;
-    }
-  }
-}
-
-}  // namespace
-
-int z2z_launch_transpose(const void* in, void* out, int R, const int32_t* rows_dev, int C, int ld_in, int ld_out,
-                         int batch, size_t in_batch, size_t out_batch, hipStream_t s) {
-  if (R < 1 || C < 1 || batch < 1) return Z2Z_OK;
-  const dim3 grid((ld_out + 63) / 64, (C + 63) / 64, batch), block(256);
-  const uint16_t* from = reinterpret_cast<const uint16_t*>(in);
-  uint16_t* to = reinterpret_cast<uint16_t*>(out);
-  if ((size_t)batch * C * ld_out * sizeof(uint16_t) > kPastCaches)
-    hipLaunchKernelGGL(transpose_bf16_kernel<true>, grid, block, 0, s, from, to, R, rows_dev, C, ld_in, ld_out, in_batch, out_batch);
-  else
-    hipLaunchKernelGGL(transpose_bf16_kernel<false>, grid, block, 0, s, from, to, R, rows_dev, C, ld_in, ld_out, in_batch, out_batch);
-  Z2Z_HIP_TRY(hipGetLastError());
-  return Z2Z_OK;
-}
-
-namespace {
-
 // The partial tiles' buffer, at least `need` bytes of it.
 int ensure_partial(z2z_ctx* c, size_t need, hipStream_t s) {
   if (need <= c->skinny_partial_bytes) return Z2Z_OK;
@@ -153,14 +84,14 @@ int ensure_partial(z2z_ctx* c, size_t need, hipStream_t s) {
 }  // namespace
 
 int z2z_launch_linear_parts(z2z_ctx* c, const void* A, const void* W, int R, const int32_t* rows_dev, int N, int K,
-                            bool k_on_device, const float** partial, int* ksplit_out, hipStream_t s, bool once) {
+                            const float** partial, int* ksplit_out, hipStream_t s, bool once) {
   *ksplit_out = 0;
   // up to 128 rows (a decode step's new entries through the learned encoder at a small batch): bound by the weight
   // bytes; the weight-streaming kernel with K split over workgroups, its fp32 partial tiles summed with the layer's
   // epilogue.  (The encoder's newest-entry pass at d = 4096, d_ff = 4 d: 347 -> 302 us for 8 sequences, 401 -> 374
   // for 40; with the 192-row build for 129..192 rows laid out the tile kernel's K split below is faster, 432
   // against 459 us for 64 sequences.)
-  if (R <= 128 && !k_on_device && K % 64 == 0 && N % 4 == 0 && c->opt_logits_kernel == 0 && z2z_logits_mid_ok(c, R)) {
+  if (R <= 128 && K % 64 == 0 && N % 4 == 0 && c->opt_logits_kernel == 0 && z2z_logits_mid_ok(c, R)) {
     const int ksplit = z2z_linear_mid_ksplit(N, K);
     int rc = ensure_partial(c, (size_t)ksplit * R * N * sizeof(float), s);
     if (rc != Z2Z_OK) return rc;
@@ -214,6 +145,15 @@ constexpr size_t kSplitBytes = (size_t)256 * 256 * 256 * sizeof(float);      // 
 // 1054 -> 694 us, 2 x 354, d = 3072 1019 -> 742, 8 x 847, d = 4096 8.59 -> 8.21 ms; a training step with it, 1 x 67 tokens, d = 4096 6.50 ->
 // 5.24 ms; where the host knows the rows, 4 x 1347 without it, V = 151936 21.3 -> 19.3 ms (84 tiles: four parts were two rounds, three are one).
 constexpr int kSplitSlabs = 32;
+
+// Order and grid of a dense layer on the tile kernel; parts: its last round may be cut (without room for the parts, under capture for
+// instance, the tiles stay whole).
+unsigned order_dense(z2z_ctx* c, LogitsArgs& a, bool parts, hipStream_t s) {
+  const unsigned grid = z2z_logits_fast_order(a, 0);
+  if (!parts || ensure_partial(c, kSplitBytes, s) != Z2Z_OK) return grid;
+  a.split = reinterpret_cast<float*>(c->skinny_partial);
+  return 256;
+}
 }  // namespace
 
 bool z2z_linear_takes_pitch(const z2z_ctx* c, int R, int N, int K) {
@@ -223,15 +163,14 @@ bool z2z_linear_takes_pitch(const z2z_ctx* c, int R, int N, int K) {
 }
 
 int z2z_launch_linear(z2z_ctx* c, const void* A, const void* W, const float* bias, const void* residual, int act,
-                      void* out, int R, const int32_t* rows_dev, int N, int K, hipStream_t s, const int32_t* k_dev,
-                      bool stream_f32, const z2z_linear_pitch* pitch, bool once) {
+                      void* out, int R, const int32_t* rows_dev, int N, int K, hipStream_t s, bool stream_f32, const z2z_linear_pitch* pitch, bool once) {
   if (pitch && !z2z_linear_takes_pitch(c, R, N, K)) return Z2Z_EUNSUPPORTED;
   // (more rows than one tile's: how many there are, and with them whether a cut along K pays, may be known on the device only)
   const bool tile_parts = R > 256 && K / 64 >= kSplitSlabs && c->fast_ready && K % 64 == 0 && N % 8 == 0 && c->opt_logits_kernel != 1;
   const float* partial = nullptr;
   int ksplit = 0;
   int rc = Z2Z_OK;
-  if (!tile_parts) rc = z2z_launch_linear_parts(c, A, W, R, rows_dev, N, K, k_dev != nullptr, &partial, &ksplit, s, once);
+  if (!tile_parts) rc = z2z_launch_linear_parts(c, A, W, R, rows_dev, N, K, &partial, &ksplit, s, once);
   if (rc != Z2Z_OK) return rc;
   if (ksplit > 0) {
     const long long n_threads = (long long)R * (N / 4);
@@ -266,13 +205,55 @@ int z2z_launch_linear(z2z_ctx* c, const void* A, const void* W, const float* bia
   a.ldw = pitch ? pitch->w : 0;
   a.stream_f32 = stream_f32 ? 1 : 0;
   a.rows_dev = rows_dev;
-  a.k_dev = k_dev;
-  unsigned grid = z2z_logits_fast_order(a, 0);
-  // (without room for the parts, under capture for instance, the tiles stay whole)
-  if (tile_parts && ensure_partial(c, kSplitBytes, s) == Z2Z_OK) {
-    a.split = reinterpret_cast<float*>(c->skinny_partial);
-    grid = 256;
-  }
+  const unsigned grid = order_dense(c, a, tile_parts, s);
   rc = z2z_launch_logits_fast(2, a, grid, s);
   return rc == Z2Z_OK && a.split ? z2z_launch_tile_sum(a, s) : rc;
+}
+
+namespace {
+
+int launch_kmajor(z2z_ctx* c, LogitsArgs& a, bool rows_too, const void* A, int lda, const void* W, int ldw, int k_rows, const void* residual,
+                  void* out, int ldo, int R, int N, z2z_linear_batch batch, hipStream_t s) {
+  if (!c->fast_ready || a.d % 64 != 0 || N % 8 != 0 || lda % 8 != 0 || ldw % 8 != 0 || R < 1 || N < 1 || batch.n < 1) return Z2Z_EUNSUPPORTED;
+  a.H = A;
+  a.W = W;
+  a.ldh = lda;
+  a.ldw = ldw;
+  a.k_rows = k_rows;
+  a.residual = residual;
+  a.out = out;
+  a.ldo = ldo;
+  a.rows = R;
+  a.rows_per_seq = R;
+  a.w_rows = N;
+  a.batch = batch.n;
+  a.batch_h = batch.a;
+  a.batch_w = batch.w;
+  a.n_vtiles = (N + 255) / 256;
+  a.row_tiles = batch.n * ((R + 255) / 256);
+  a.strip = 1;
+  a.n_strips = a.n_vtiles;
+  const unsigned grid = order_dense(c, a, a.d / 64 >= kSplitSlabs, s);
+  const int rc = z2z_launch_linear_kmajor(a, rows_too, grid, s);
+  return rc == Z2Z_OK && a.split ? z2z_launch_tile_sum(a, s) : rc;
+}
+
+}  // namespace
+
+int z2z_launch_linear_input(z2z_ctx* c, const void* A, int lda, const void* W, int ldw, int k_rows, const void* residual, void* out, int ldo,
+                            int R, const int32_t* rows_dev, int N, int K, hipStream_t s, z2z_linear_batch batch) {
+  LogitsArgs a;
+  memset(&a, 0, sizeof(a));
+  a.d = K;
+  a.rows_dev = rows_dev;
+  return launch_kmajor(c, a, false, A, lda, W, ldw, k_rows, residual, out, ldo, R, N, batch, s);
+}
+
+int z2z_launch_linear_weight(z2z_ctx* c, const void* A, int lda, const void* W, int ldw, int k_rows, const int32_t* k_dev,
+                             const void* residual, void* out, int R, int N, hipStream_t s, z2z_linear_batch batch) {
+  LogitsArgs a;
+  memset(&a, 0, sizeof(a));
+  a.d = (k_rows + 63) / 64 * 64;
+  a.k_dev = k_dev;
+  return launch_kmajor(c, a, true, A, lda, W, ldw, k_rows, residual, out, N, R, N, batch, s);
 }

@@ -436,7 +436,7 @@ __global__ void __launch_bounds__(256) enc_pool_kernel(RowMap m, const float* Z,
 // ---------------------------------------------------------------------------------------------------------
 // Backward pass (training f_phi: the loss reaches the encoder through every hypertoken vector, section 2.4).
 // Reverse mode over the forward steps above.  Every product with a weight matrix, and every weight gradient
-// (a product over the rows of the pass), runs on the same MFMA kernels from transposed bf16 copies; the kernels
+// (a product over the rows of the pass), runs on the same MFMA kernel, which reads the operands as they are; the kernels
 // below are the bandwidth-bound rest.  Gradients between kernels are bf16, sums fp32.
 // ---------------------------------------------------------------------------------------------------------
 
@@ -891,10 +891,10 @@ int z2z_launch_hyper_encode(z2z_ctx* c, const void* E, const z2z_encoder* enc, v
       // (with more rows -- K is split there too in a narrow encoder -- a wave per row is the better LayerNorm: 6144 rows,
       // d = 256: the pass 275 us fused, 267 in launches of their own)
       if (!padded && R <= E_FEW_ROWS)
-        ret = z2z_launch_linear_parts(c, in, w, R, rows_dev, d, K, false, &parts.partial, &parts.ksplit, s, once);
+        ret = z2z_launch_linear_parts(c, in, w, R, rows_dev, d, K, &parts.partial, &parts.ksplit, s, once);
       if (ret != Z2Z_OK) return ret;
       if (parts.ksplit == 0)
-        return z2z_launch_linear(c, in, w, bias, residual, 0, out, R, rows_dev, d, K, s, nullptr, true, padded ? &pitch : nullptr, once);
+        return z2z_launch_linear(c, in, w, bias, residual, 0, out, R, rows_dev, d, K, s, true, padded ? &pitch : nullptr, once);
       parts.R = R;
       parts.bias = bias;
       parts.residual = residual;
@@ -922,7 +922,7 @@ int z2z_launch_hyper_encode(z2z_ctx* c, const void* E, const z2z_encoder* enc, v
         hipLaunchKernelGGL(enc_norm_kernel<false>, dim3(row_blocks), dim3(256), 0, s, m, nullptr, nullptr, x,
                            reinterpret_cast<uint4*>(A), lay.ln1_g, lay.ln1_b, n_units);
       }
-      rc = z2z_launch_linear(c, A, lay.w_qkv, lay.b_qkv, nullptr, 0, QKV, R, rows_dev, 3 * d, d, s, nullptr, false, nullptr, once);
+      rc = z2z_launch_linear(c, A, lay.w_qkv, lay.b_qkv, nullptr, 0, QKV, R, rows_dev, 3 * d, d, s, false, nullptr, once);
       if (rc != Z2Z_OK) return rc;
       const long long att_waves = (long long)n_units * groups;
       hipLaunchKernelGGL(M <= 4 ? enc_attention_kernel<4> : enc_attention_kernel<Z2Z_MAX_M>, dim3((unsigned)((att_waves + 3) / 4)), dim3(256), 0, s, m,
@@ -942,7 +942,7 @@ int z2z_launch_hyper_encode(z2z_ctx* c, const void* E, const z2z_encoder* enc, v
           hipLaunchKernelGGL(enc_norm_kernel<false>, dim3(row_blocks), dim3(256), 0, s, m, nullptr, nullptr, y,
                              reinterpret_cast<uint4*>(A), lay.ln2_g, lay.ln2_b, n_units);
         const z2z_linear_pitch to_wide = {d, d, dffp};
-        rc = z2z_launch_linear(c, A, lay.w_1, lay.b_1, nullptr, 1, F, R, rows_dev, dff, d, s, nullptr, false,
+        rc = z2z_launch_linear(c, A, lay.w_1, lay.b_1, nullptr, 1, F, R, rows_dev, dff, d, s, false,
                                dffp != dff ? &to_wide : nullptr, once);
         if (rc != Z2Z_OK) return rc;
         rc = layer_out(F, lay.w_2, lay.b_2, y, x, dff, next ? next->ln1_g : nullptr, next ? next->ln1_b : nullptr, &fused);
@@ -965,10 +965,6 @@ struct LayerSave {                   // what the training pass keeps of one laye
   float *Xin, *Y;                    // the operands of the matrix products [rows, .] bf16
   uint16_t *A, *QKV, *O, *N2, *U, *F;
 };
-
-int transpose_to(const void* in, void* out, int R, const int32_t* rows_dev, int C, int ld_in, int ld_out, hipStream_t s) {
-  return z2z_launch_transpose(in, out, R, rows_dev, C, ld_in, ld_out, 1, 0, 0, s);
-}
 
 void colsum_to(const void* G, int N, int ld, const int32_t* rows_dev, float* out, hipStream_t s) {
   hipLaunchKernelGGL(enc_colsum_kernel, dim3((N / 8 + 63) / 64, E_CS_STRIPES), dim3(256), 0, s,
@@ -998,17 +994,13 @@ int z2z_launch_hyper_encode_train(z2z_ctx* c, int mode, const void* E, const z2z
   if (u_step > cap) u_step = cap;
   const size_t R_max = (size_t)B * (size_t)u_step * M;
   const int dffp = ffn_pitch(c, B, M, cap, (int)u_step, d, dff);
-  const int wide = 3 * d > dffp ? 3 * d : dffp;                 // widest activation
-  const size_t Rp = z2z_contraction_pitch(R_max, 128);          // contraction length of the weight-gradient products
   const size_t n_units_max = (size_t)B * (size_t)u_step;
   const size_t index_bytes = ((n_units_max + 1 + R_max) * sizeof(int32_t) + 255) & ~(size_t)255;
   const size_t pos_bytes = ((size_t)Z2Z_MAX_M * d * sizeof(float) + 255) & ~(size_t)255;
   // in units of bf16 elements (an fp32 element counts as two): per layer what LayerSave names (Xin and Y fp32);
-  // the last layer's output (fp32); the running gradients dX dY dN dO (d each), dQKV (3d), dF (d_ff); two
-  // transposed operands [wide, Rp]; one transposed weight
+  // the last layer's output (fp32); the running gradients dX dY dN dO (d each), dQKV (3d), dF (d_ff)
   const size_t per_layer = R_max * ((size_t)10 * d + (size_t)2 * dffp);
-  const size_t elems = (size_t)nl * per_layer + R_max * ((size_t)7 * d + dffp) + R_max * 2 * d + 2 * (size_t)wide * Rp +
-                       (size_t)wide * d;
+  const size_t elems = (size_t)nl * per_layer + R_max * ((size_t)7 * d + dffp) + R_max * 2 * d;
   const size_t nb_bytes = (R_max * sizeof(float2) + 255) & ~(size_t)255;   // mean and rstd of every row of a LayerNorm
   const size_t need = index_bytes + pos_bytes + nb_bytes + elems * 2;
   if (need > ((size_t)200 << 30)) return Z2Z_ENOMEM;
@@ -1052,9 +1044,6 @@ int z2z_launch_hyper_encode_train(z2z_ctx* c, int mode, const void* E, const z2z
   uint16_t* dO = take(R_max * d);
   uint16_t* dQKV = take(R_max * 3 * d);
   uint16_t* dF = take(R_max * (size_t)dffp);
-  uint16_t* TA = take((size_t)wide * Rp);
-  uint16_t* TB = take((size_t)wide * Rp);
-  uint16_t* WT = take((size_t)wide * d);
 
   RowMap m;
   m.size = c->st.size;
@@ -1099,17 +1088,15 @@ int z2z_launch_hyper_encode_train(z2z_ctx* c, int mode, const void* E, const z2z
     if (rc != Z2Z_OK) return rc; \
   } while (0)
 
-  // pitches of the products into and out of the feed-forward width (the last with a transposed weight of that pitch)
-  const z2z_linear_pitch into = {d, d, dffp}, out_of = {dffp, dff, d}, out_of_t = {dffp, dffp, d};
-  const z2z_linear_pitch *to_wide = dffp != dff ? &into : nullptr, *from_wide = dffp != dff ? &out_of : nullptr,
-                         *from_wide_t = dffp != dff ? &out_of_t : nullptr;
+  // pitches of the products into and out of the feed-forward width
+  const z2z_linear_pitch into = {d, d, dffp}, out_of = {dffp, dff, d};
+  const z2z_linear_pitch *to_wide = dffp != dff ? &into : nullptr, *from_wide = dffp != dff ? &out_of : nullptr;
   int pass = 0;
   for (int u0 = 0; u0 < cap; u0 += (int)u_step, ++pass) {
     m.u0 = u0;
     m.un = (int)(u0 + u_step <= cap ? u_step : cap - u0);
     const int n_units = B * m.un;
     const int R = n_units * M;                       // upper bound; the real count is on the device
-    const int Rk = (int)z2z_contraction_pitch(R, 128);   // contraction length of this pass's weight-gradient products
     const int32_t* rows_dev = m.row0 + n_units;
     const unsigned row_blocks = (unsigned)((R + 3) / 4);
     if (mode != 2) hipLaunchKernelGGL(enc_rows_kernel, dim3(1), dim3(1024), 0, s, m, n_units);
@@ -1132,14 +1119,14 @@ int z2z_launch_hyper_encode_train(z2z_ctx* c, int mode, const void* E, const z2z
                          reinterpret_cast<const uint4*>(v.QKV), reinterpret_cast<uint4*>(v.O), dh / 8, scale, groups,
                          n_units);
       float* y = ffn ? v.Y : next;
-      Z2Z_TRY_RC(z2z_launch_linear(c, v.O, lay.w_o, lay.b_o, v.Xin, 0, y, R, rows_dev, d, d, s, nullptr, true));
+      Z2Z_TRY_RC(z2z_launch_linear(c, v.O, lay.w_o, lay.b_o, v.Xin, 0, y, R, rows_dev, d, d, s, true));
       if (ffn) {
         hipLaunchKernelGGL(enc_norm_kernel<false>, dim3(row_blocks), dim3(256), 0, s, m, nullptr, nullptr, v.Y,
                            reinterpret_cast<uint4*>(v.N2), lay.ln2_g, lay.ln2_b, n_units);
-        Z2Z_TRY_RC(z2z_launch_linear(c, v.N2, lay.w_1, lay.b_1, nullptr, 0, v.U, R, rows_dev, dff, d, s, nullptr, false, to_wide));
+        Z2Z_TRY_RC(z2z_launch_linear(c, v.N2, lay.w_1, lay.b_1, nullptr, 0, v.U, R, rows_dev, dff, d, s, false, to_wide));
         hipLaunchKernelGGL(enc_gelu_kernel, dim3(flat_grid((size_t)R * dffp / 8)), dim3(256), 0, s,
                            reinterpret_cast<const uint4*>(v.U), reinterpret_cast<uint4*>(v.F), dffp / 8, rows_dev);
-        Z2Z_TRY_RC(z2z_launch_linear(c, v.F, lay.w_2, lay.b_2, v.Y, 0, next, R, rows_dev, d, dff, s, nullptr, true, from_wide));
+        Z2Z_TRY_RC(z2z_launch_linear(c, v.F, lay.w_2, lay.b_2, v.Y, 0, next, R, rows_dev, d, dff, s, true, from_wide));
       }
     }
 
@@ -1169,31 +1156,22 @@ int z2z_launch_hyper_encode_train(z2z_ctx* c, int mode, const void* E, const z2z
       uint16_t* dy = dX;                             // gradient at Y (attention layers: the layer's output)
       if (ffn) {
         colsum_to(dX, d, d, rows_dev, const_cast<float*>(g.b_2), s);
-        Z2Z_TRY_RC(transpose_to(lay.w_2, WT, d, nullptr, dff, dff, d, s));                        // [dff, d]
-        Z2Z_TRY_RC(z2z_launch_linear(c, dX, WT, nullptr, nullptr, 0, dF, R, rows_dev, dff, d, s, nullptr, false, to_wide));
-        Z2Z_TRY_RC(transpose_to(dX, TA, R, rows_dev, d, d, Rk, s));
-        Z2Z_TRY_RC(transpose_to(v.F, TB, R, rows_dev, dff, dffp, Rk, s));
+        Z2Z_TRY_RC(z2z_launch_linear_input(c, dX, d, lay.w_2, dff, d, nullptr, dF, dffp, R, rows_dev, dff, d, s));
         acc = pass > 0 ? g.w_2 : nullptr;
-        Z2Z_TRY_RC(z2z_launch_linear(c, TA, TB, nullptr, acc, 0, const_cast<void*>(g.w_2), d, nullptr, dff, Rk, s, rows_dev));
+        Z2Z_TRY_RC(z2z_launch_linear_weight(c, dX, d, v.F, dffp, R, rows_dev, acc, const_cast<void*>(g.w_2), d, dff, s));
         hipLaunchKernelGGL(enc_gelu_backward_kernel, dim3(flat_grid((size_t)R * dffp / 8)), dim3(256), 0, s,
                            reinterpret_cast<uint4*>(dF), reinterpret_cast<const uint4*>(v.U), dffp / 8, rows_dev);
         colsum_to(dF, dff, dffp, rows_dev, const_cast<float*>(g.b_1), s);
-        Z2Z_TRY_RC(transpose_to(dF, TA, R, rows_dev, dff, dffp, Rk, s));
-        Z2Z_TRY_RC(transpose_to(v.N2, TB, R, rows_dev, d, d, Rk, s));
         acc = pass > 0 ? g.w_1 : nullptr;
-        Z2Z_TRY_RC(z2z_launch_linear(c, TA, TB, nullptr, acc, 0, const_cast<void*>(g.w_1), dff, nullptr, d, Rk, s, rows_dev));
-        Z2Z_TRY_RC(transpose_to(lay.w_1, WT, dff, nullptr, d, d, dffp, s));                       // [d, dffp]
-        Z2Z_TRY_RC(z2z_launch_linear(c, dF, WT, nullptr, nullptr, 0, dN, R, rows_dev, d, dff, s, nullptr, false, from_wide_t));
+        Z2Z_TRY_RC(z2z_launch_linear_weight(c, dF, dffp, v.N2, d, R, rows_dev, acc, const_cast<void*>(g.w_1), dff, d, s));
+        Z2Z_TRY_RC(z2z_launch_linear_input(c, dF, dffp, lay.w_1, d, dff, nullptr, dN, d, R, rows_dev, d, dff, s));
         norm_backward(dN, v.Y, lay.ln2_g, dX, dY, g.ln2_g, g.ln2_b);
         dy = dY;
       }
       colsum_to(dy, d, d, rows_dev, const_cast<float*>(g.b_o), s);
-      Z2Z_TRY_RC(transpose_to(lay.w_o, WT, d, nullptr, d, d, d, s));
-      Z2Z_TRY_RC(z2z_launch_linear(c, dy, WT, nullptr, nullptr, 0, dO, R, rows_dev, d, d, s));
-      Z2Z_TRY_RC(transpose_to(dy, TA, R, rows_dev, d, d, Rk, s));
-      Z2Z_TRY_RC(transpose_to(v.O, TB, R, rows_dev, d, d, Rk, s));
+      Z2Z_TRY_RC(z2z_launch_linear_input(c, dy, d, lay.w_o, d, d, nullptr, dO, d, R, rows_dev, d, d, s));
       acc = pass > 0 ? g.w_o : nullptr;
-      Z2Z_TRY_RC(z2z_launch_linear(c, TA, TB, nullptr, acc, 0, const_cast<void*>(g.w_o), d, nullptr, d, Rk, s, rows_dev));
+      Z2Z_TRY_RC(z2z_launch_linear_weight(c, dy, d, v.O, d, R, rows_dev, acc, const_cast<void*>(g.w_o), d, d, s));
       const long long att_waves = (long long)n_units * groups;
       if (M <= 4)
         hipLaunchKernelGGL(enc_attention_backward_kernel<4>, dim3((unsigned)((att_waves + 3) / 4)), dim3(256), 0, s, m,
@@ -1204,12 +1182,9 @@ int z2z_launch_hyper_encode_train(z2z_ctx* c, int mode, const void* E, const z2z
                            s, m, reinterpret_cast<const uint4*>(v.QKV), reinterpret_cast<const uint4*>(dO),
                            reinterpret_cast<uint4*>(dQKV), dh / 8, scale, groups, n_units);
       colsum_to(dQKV, 3 * d, 3 * d, rows_dev, const_cast<float*>(g.b_qkv), s);
-      Z2Z_TRY_RC(transpose_to(dQKV, TA, R, rows_dev, 3 * d, 3 * d, Rk, s));
-      Z2Z_TRY_RC(transpose_to(v.A, TB, R, rows_dev, d, d, Rk, s));
       acc = pass > 0 ? g.w_qkv : nullptr;
-      Z2Z_TRY_RC(z2z_launch_linear(c, TA, TB, nullptr, acc, 0, const_cast<void*>(g.w_qkv), 3 * d, nullptr, d, Rk, s, rows_dev));
-      Z2Z_TRY_RC(transpose_to(lay.w_qkv, WT, 3 * d, nullptr, d, d, 3 * d, s));                    // [d, 3d]
-      Z2Z_TRY_RC(z2z_launch_linear(c, dQKV, WT, nullptr, nullptr, 0, dN, R, rows_dev, d, 3 * d, s));
+      Z2Z_TRY_RC(z2z_launch_linear_weight(c, dQKV, 3 * d, v.A, d, R, rows_dev, acc, const_cast<void*>(g.w_qkv), 3 * d, d, s));
+      Z2Z_TRY_RC(z2z_launch_linear_input(c, dQKV, 3 * d, lay.w_qkv, d, 3 * d, nullptr, dN, d, R, rows_dev, d, 3 * d, s));
       norm_backward(dN, v.Xin, lay.ln1_g, dy, dX, g.ln1_g, g.ln1_b);
     }
     hipLaunchKernelGGL(enc_input_backward_kernel, dim3((d + 511) / 512, (R + 255) / 256), dim3(256), 0, s, m, dX, dE,

@@ -243,6 +243,9 @@ struct LogitsArgs {
   // K beyond *k_dev, up to the next multiple of 64, holds zeros and the slabs after that are not read
   const int32_t* k_dev;
   int32_t ldh, ldw;         // row pitch of H and W in elements (dense layers; 0: d)
+  int32_t k_rows;           // rows of the K-major operands (dense layers whose contraction runs over them; at most *k_dev)
+  int32_t batch;            // products with K-major operands in one launch (0, 1: one); the operands' steps in elements
+  size_t batch_h, batch_w;
   int32_t once;             // weight-streaming kernel: the weights are read past the caches
 };
 
@@ -396,6 +399,8 @@ int z2z_launch_logits_general(bool bf16, int columns, const z2z_logits::LogitsAr
 // 3 base part, 4 hyper part storing the gradient with respect to the logits, 5 dense layer with K split
 // (fp32 partial tiles)
 int z2z_launch_logits_fast(int mode, const z2z_logits::LogitsArgs& a, unsigned grid, hipStream_t s);
+// mode 2 with W K-major, and H too (rows_too)
+int z2z_launch_linear_kmajor(const z2z_logits::LogitsArgs& a, bool rows_too, unsigned grid, hipStream_t s);
 // behind a dense layer launched with LogitsArgs::split, on 256 workgroups: the sums of the tiles that the device has cut along K
 int z2z_launch_tile_sum(const z2z_logits::LogitsArgs& a, hipStream_t s);
 // order and grid of a base part or dense layer (modes 0, 2, 3, 6 - 9): a.row_tiles, n_vtiles and n_strips are set; `forced`:
@@ -404,37 +409,30 @@ unsigned z2z_logits_fast_order(z2z_logits::LogitsArgs& a, int forced);
 // out[R, N] = act(A[R, K] . W[N, K]^T + bias) + residual, all matrices bf16 (bias float), on the bf16 MFMA kernel
 // (R rows are laid out; with rows_dev only the first *rows_dev of them exist: the others are neither read nor
 // written).  stream_f32: residual and out are fp32 instead (a residual stream that is not rounded between layers).
-// bf16 transpose with zero padding of the output rows (see dense.hip)
-int z2z_launch_transpose(const void* in, void* out, int R, const int32_t* rows_dev, int C, int ld_in, int ld_out,
-                         int batch, size_t in_batch, size_t out_batch, hipStream_t s);
-// Row pitch (and contraction length, the padding holds zeros) of transposed operands whose contraction runs over n
-// rows: a multiple of `align`, and no multiple of 4 KiB -- rows a power of two apart put the slabs that all
-// workgroups read at one time on a few memory channels.  It never falls as n grows: a buffer laid out for the largest n
-// of a call holds every smaller one (a pass's last and shortest chunk).  (128 elements beyond: with 64, 32064 x 3072 outputs
-// over 8192 rows took 1503 us instead of 1380.)
-constexpr size_t z2z_contraction_pitch(size_t n, size_t align) {
-  const size_t p = (n + align - 1) / align * align;
-  return p >= 2048 && p % 2048 < 128 ? p - p % 2048 + 128 : p;
-}
-constexpr bool z2z_contraction_pitch_grows(size_t align) {
-  for (size_t n = 1; n < 3 * 2048; ++n) {            // (what happens about one multiple of 2048 happens about all)
-    const size_t p = z2z_contraction_pitch(n, align);
-    if (p < n || p % align || p % 2048 == 0 || p > z2z_contraction_pitch(n + 1, align)) return false;
-  }
-  return true;
-}
-static_assert(z2z_contraction_pitch_grows(64) && z2z_contraction_pitch_grows(128), "a shorter chunk would not fit");
 struct z2z_linear_pitch {
   int a, w, out;           // row pitches of A, W and the output (a residual has the output's)
 };
 int z2z_launch_linear(z2z_ctx* c, const void* A, const void* W, const float* bias, const void* residual, int act,
-                      void* out, int R, const int32_t* rows_dev, int N, int K, hipStream_t s, const int32_t* k_dev = nullptr,
+                      void* out, int R, const int32_t* rows_dev, int N, int K, hipStream_t s,
                       bool stream_f32 = false, const z2z_linear_pitch* pitch = nullptr,
                       bool once = false);
+// The two products of a dense layer's backward pass, bf16, operands as the forward pass has them (nothing is transposed or padded;
+// widths and pitches are multiples of 8, see logits_fast.hip).  All are row-major with pitches ld..:
+//   z2z_launch_linear_input    out[R, N] = A[R, K] . W[k_rows, N] + residual;  A's columns from k_rows to K (K: a multiple of 64) are finite
+//   z2z_launch_linear_weight   out[R, N] = A[k_rows, R]^T . W[k_rows, N] + residual;  with k_dev only the first *k_dev rows exist
+// A batch of them: outputs of R rows below each other, W (and the second's A) batch_w (batch_a) elements apart.
+struct z2z_linear_batch {
+  int n;
+  size_t a, w;
+};
+int z2z_launch_linear_input(z2z_ctx* c, const void* A, int lda, const void* W, int ldw, int k_rows, const void* residual, void* out, int ldo,
+                            int R, const int32_t* rows_dev, int N, int K, hipStream_t s, z2z_linear_batch batch = {1, 0, 0});
+int z2z_launch_linear_weight(z2z_ctx* c, const void* A, int lda, const void* W, int ldw, int k_rows, const int32_t* k_dev,
+                             const void* residual, void* out, int R, int N, hipStream_t s, z2z_linear_batch batch = {1, 0, 0});
 // Row pitch for n columns of an activation that is an operand of dense layers: n, or 64 more where n columns are a
 // multiple of 4 KiB -- the tile kernel's workgroups read the same slab of 256 rows at a time, and rows that far apart
 // on a power of two put it on a few memory channels (35400 rows x 4096 columns, K = 16384: 1.07 -> 1.18
-// PFLOP/s, with a padded transposed weight 1.04 -> 1.19; whole passes at n = 4096 2 % faster, n = 12288 level).  Odd
+// PFLOP/s; whole passes at n = 4096 2 % faster, n = 12288 level).  Odd
 // multiples of 16 KiB stay: with 64 more columns the product at n = 8192 (29000 rows x 2048) takes 1061 us instead of
 // 970.  (128 more gain nothing at 8192 and lose the gain at 16384.)
 inline int z2z_activation_pitch(int n) { return n % 2048 || n % 16384 == 8192 ? n : n + 64; }
@@ -444,7 +442,7 @@ bool z2z_linear_takes_pitch(const z2z_ctx* c, int R, int N, int K);
 // [*ksplit][R][N] at *partial, which the caller adds up in order before the next dense layer is launched; *ksplit = 0:
 // the layer is not split at this shape, nothing was launched.
 int z2z_launch_linear_parts(z2z_ctx* c, const void* A, const void* W, int R, const int32_t* rows_dev, int N, int K,
-                            bool k_on_device, const float** partial, int* ksplit, hipStream_t s, bool once = false);
+                            const float** partial, int* ksplit, hipStream_t s, bool once = false);
 int z2z_logits_fast_prepare(z2z_ctx* c);
 int z2z_launch_logits_part(z2z_ctx* c, bool hyper, z2z_logits::LogitsArgs a, const void* W, int w_rows, int col0,
                            int part0, int strip, int rows, int rows_per_seq, int* n_strips_out, bool timed,

@@ -12,7 +12,7 @@
 // kernel: 14-22 TB/s against 12-15 TB/s out of L2).  Both operand tiles of a slab (2 x 32 KiB) go straight
 // from global memory into LDS (16-byte global_load ... lds), two stages.  With one wave per SIMD all overlap is
 // inside the instruction stream.  A slab's 128 MFMAs are slots, and between them go, each at a slot of its own
-// (kRead2 ... below):
+// (Schedule below):
 //   - the 16 fragment reads of the second k-step, then a barrier (everybody holds the rest of slab s in registers:
 //     its stage is free) and the 16 requests for slab s+2, six MFMAs apart;
 //   - late in the second k-step a wait for slab s+1 and a second barrier (it has landed for everybody), then the 16
@@ -27,6 +27,16 @@
 // c ^ ((r >> 1) & 7).  The LDS has 64 four-byte banks and serves a 16-byte-per-lane read 16 lanes at a
 // time; an MFMA operand read has 16 consecutive lanes on 16 consecutive rows at one logical chunk, whose
 // bank group is (r & 1) * 8 + position -- all 16 distinct with this swizzle.
+//
+// Gradient products contract over what their operands have as rows (dW = dY^T X, dX = dY W): such an operand is read as it
+// is, K-major.  A slab is then 64 rows of 512 bytes (the tile's 256 columns), two whole rows a request, and a fragment
+// comes out of LDS by transposing reads (ds_read_b64_tr_b16: 16 lanes read 4 rows x 16 columns, a lane gets 4 rows of one column), two
+// for one plain read and the same bytes.  The 32-byte piece b of row k is stored at b ^ f(k), f = 3 low bits out of k's bits
+// 0, 1 and 3: the 8 pieces that 32 lanes read at a time are on different banks.  Rows behind the last one read as zeros by the buffer
+// descriptor's range, so that nothing is copied or padded.  One read per MFMA, its address in a register of its own (two per MFMA with an
+// addition each: dW 20 % slower, dX 8 %).  32768 x 4096 over 128256 and 128256 x 4096 over 32768: 22.0 and 23.3 ms, against 22.4 and 22.2 on
+// transposed copies that took 3.6 ms to make; a training step of 8 x 4096 tokens 169.3 -> 164.6 ms, 1 x 65 tokens, d = 3072 4.2 -> 2.4 (with the cut
+// along K).
 //
 // In the 16 x 16 result block a lane holds 4 vocabulary entries of one hidden row (of 8 rows and 32 entries each in the
 // whole tile), so the running (max, sum-exp, argmax) of the joint softmax (zip2zip paper, section 2.3, step 8) lives in
@@ -49,18 +59,39 @@ constexpr int F_THREADS = 256;
 constexpr int F_N = 8;                    // MFMA blocks of a wave along either side (128 x 128)
 constexpr int F_PAIRS = 8;                // request pairs (8 rows of A + 8 rows of B) per wave and slab
 constexpr int F_SLOTS = 2 * F_N * F_N;    // MFMAs of a wave per slab
+constexpr int F_KROW = 2 * FT;            // bytes of a row of a K-major operand's tile
+
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
+typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4;
 
 // What goes out after which MFMA of a slab (barriers: ahead of it).
-constexpr int kRead2 = 0;                 // 16 fragment reads of the second k-step, one per MFMA
-constexpr int kFree = 24;                 // barrier: slab s is in registers
-constexpr int kRequest = 26;              // 16 requests for slab s+2 ...
-constexpr int kRequestEvery = 6;          // ... this far apart
-constexpr int kLanded = 110;              // wait + barrier: slab s+1 is there
-constexpr int kRead1 = 110;               // 16 fragment reads of its first k-step, one per MFMA
-constexpr int kOutAtLanded = (kLanded - kRequest + kRequestEvery - 1) / kRequestEvery;     // requests out ahead of that wait
-static_assert(kFree > kRead2 + 15 && kRequest >= kFree && kRequest + 15 * kRequestEvery < F_SLOTS, "stage s is refilled after its last read");
-static_assert(kRead1 >= kLanded && kRead1 + 15 < F_SLOTS && kLanded > F_SLOTS / 2, "slab s+1 is read after it landed, into registers that are free");
-static_assert(kOutAtLanded <= 2 * F_PAIRS, "");
+template <bool TW, bool TH>
+struct Schedule {
+  static constexpr int reads = F_N * (1 + TW) + F_N * (1 + TH);      // of a k-step: 16 fragments, those of a K-major operand in two
+  static constexpr bool long_reads = reads > 16;
+  static constexpr int read2 = 0;                              // the second k-step's reads, one per MFMA
+  static constexpr int free_ = read2 + reads + 8;              // barrier: slab s is in registers
+  static constexpr int request = free_ + 2;                    // 16 requests for slab s+2 ...
+  static constexpr int request_every = long_reads ? 5 : 6;     // ... this far apart
+  static constexpr int landed = F_SLOTS - reads - 2;           // wait + barrier: slab s+1 is there
+  static constexpr int read1 = landed;                         // its first k-step's reads, one per MFMA
+  static constexpr int out_at_landed = (landed - request + request_every - 1) / request_every;     // requests out ahead of that wait
+  static_assert(request + 15 * request_every < F_SLOTS && read1 + reads <= F_SLOTS && landed > F_SLOTS / 2 && out_at_landed <= 2 * F_PAIRS, "");
+  // read e: fragment (in the order the MFMAs first need them: b0, a0, b1 .. b7, a1 .. a7) and half
+  static constexpr bool is_a(int n) { return n == 1 || n > F_N; }
+  static constexpr int parts(int n) { return 1 + (is_a(n) ? TW : TH); }
+  static constexpr int fragment(int e) {
+    int n = 0;
+    while (e >= parts(n)) e -= parts(n++);
+    return n;
+  }
+  static constexpr int half(int e) {
+    int n = 0;
+    while (e >= parts(n)) e -= parts(n++);
+    return e;
+  }
+};
+static_assert(Schedule<false, false>::free_ == 24 && Schedule<false, false>::request == 26 && Schedule<false, false>::landed == 110, "");
 
 // f(0) ... f(N - 1) with the index a constant.
 template <typename F, int... I>
@@ -94,6 +125,29 @@ __device__ __forceinline__ void barrier_after_lds() {
   asm volatile("" ::: "memory");
 }
 
+// Half of a fragment out of a K-major operand: four rows of a column.
+template <int OFFSET, int HALF>
+__device__ __forceinline__ void read_transposed(uint4& f, uint32_t at) {
+  typedef __attribute__((address_space(3))) s16x4* lds_ptr;
+  const uint2 v = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(uintptr_t)(at + OFFSET)));
+  if (HALF == 0) {
+    f.x = v.x;
+    f.y = v.y;
+  } else {
+    f.z = v.x;
+    f.w = v.y;
+  }
+}
+
+// Descriptor of the rows from p on, of which `rows` exist (none: an empty range); p is `col` bytes into its row.
+__device__ __forceinline__ u32x4 k_rows_rsrc(const unsigned char* p, int rows, size_t pitch, int col) {
+  const int n = min(max(rows, 0), 64);
+  const uint32_t range = n > 0 ? (uint32_t)n * (uint32_t)pitch - (uint32_t)col : 0u;
+  const uint64_t at = (uint64_t)p;
+  return u32x4{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at), (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(at >> 32) & 0xFFFFu)),
+               (uint32_t)__builtin_amdgcn_readfirstlane((int)range), 0x00020000u};
+}
+
 constexpr int vmcnt_imm(int n) { return (n & 0xF) | ((n >> 4) << 14) | 0x0F70; }
 
 // 16 bytes per lane, global -> LDS without passing through registers: address = 64-bit scalar base +
@@ -109,6 +163,15 @@ __device__ __forceinline__ void load16_to_lds(const unsigned char* base, uint32_
                :
                : "v"(lane_offset), "s"(base), "s"(lds_stage_base), "n"(LDS_IMM)
                : "memory", "scc");   // M0 is reserved: the compiler keeps nothing in it across statements
+}
+
+// The same through a buffer descriptor: lanes at or beyond its range put zeros into LDS.
+template <int LDS_IMM>
+__device__ __forceinline__ void load16_to_lds(const u32x4& rsrc, uint32_t lane_offset, uint32_t lds_stage_base) {
+  asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
+               :
+               : "v"(lane_offset), "s"(rsrc), "s"(lds_stage_base), "n"(LDS_IMM)
+               : "memory", "scc");
 }
 
 __device__ __forceinline__ uint32_t lds_offset_of(const void* p) {
@@ -187,7 +250,7 @@ __device__ __forceinline__ LastRound last_round(const LogitsArgs& a, int row_til
 // Slabs of a dense layer's contraction (k_dev: its length is known on the device only).
 __device__ __forceinline__ int dense_slabs(const LogitsArgs& a) {
   const int n = (a.d * 2) / F_SLAB;
-  return a.k_dev ? max(1, min(n, (*a.k_dev * 2 + F_SLAB - 1) / F_SLAB)) : n;
+  return a.k_dev ? max(1, min(n, (__builtin_amdgcn_readfirstlane(*a.k_dev) * 2 + F_SLAB - 1) / F_SLAB)) : n;
 }
 
 struct Frags {
@@ -598,8 +661,11 @@ __device__ __forceinline__ void merge_rows(R (&a)[F_N], S swap) {
 // way.  With a workgroup per tile instead, a launch and the first slabs' round trip stood before every tile and a
 // store queue behind it: a training step of 8 x 4096 tokens (kernels only) 172.8 -> 168.9 ms, of it the order below 2.5.
 // The hyper parts and K-split layers (modes 1, 4, 5) have a workgroup per item: what exists of them is known on the device.
-template <int MODE, bool ROT = false>
+// TW, TH (mode 2): the operand of that side is K-major, W [k_rows, ldw] and H [k_rows, ldh]; there may be a batch of such products,
+// of a.rows output rows each, one below the other.
+template <int MODE, bool ROT = false, bool TW = false, bool TH = false>
 __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
+  static_assert(MODE == 2 || (!TW && !TH), "dense layers only");
   constexpr bool PROBE_NOREQ = MODE == 8 || MODE == 9;
   constexpr bool PROBE_MFMA = MODE == 9;
   constexpr bool LIST = MODE != 1 && MODE != 4 && MODE != 5;
@@ -619,8 +685,8 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
   const size_t pitch_h = MODE == 2 && a.ldh ? (size_t)a.ldh * 2 : row_bytes;
   const size_t pitch_w = MODE == 2 && a.ldw ? (size_t)a.ldw * 2 : row_bytes;
   int r_end = a.rows;                                // one past the last row of the matrix, or of the sequence
-  if ((MODE == 2 || MODE == 5) && a.rows_dev) r_end = min(r_end, *a.rows_dev);
-  const int row_tiles_now = (r_end + FT - 1) / FT;
+  if ((MODE == 2 || MODE == 5) && a.rows_dev) r_end = min(r_end, __builtin_amdgcn_readfirstlane(*a.rows_dev));
+  const int tiles_each = (r_end + FT - 1) / FT, row_tiles_now = TW && a.batch > 1 ? a.batch * tiles_each : tiles_each;
   int n_valid = a.w_rows;
   int one_rt = 0, one_st = 0, one_r0 = 0, ks = 0;    // modes 1, 4, 5: the one item
   if (MODE == 1 || MODE == 4) {
@@ -652,28 +718,38 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
                           : (int)(row_bytes / F_SLAB);
   if (MODE == 2) n_slabs = dense_slabs(a);
   // the item's slabs [s0, s0 + sn) and, where it is a part of a tile, the buffer of its sums (else -1)
+  const int k_rows = (TW || TH) && a.k_dev ? min(a.k_rows, max(__builtin_amdgcn_readfirstlane(*a.k_dev), 0)) : a.k_rows;     // of the K-major operands
   const LastRound last = MODE == 2 && a.split ? last_round(a, row_tiles_now, (int)(blockIdx.x & 7), n_slabs) : LastRound{0, 0, 1, n_slabs};
 
-  auto item = [&](int j, int* r0, int* st, int* s0, int* sn, int* part) -> bool {
-    *s0 = 0;
-    *sn = n_slabs;
-    *part = -1;
+  struct Item {
+    int r0, st, s0, sn, part;    // first row, strip, slabs, buffer
+    int b;                       // product of a batch
+  };
+  auto item = [&](int j, Item* it) -> bool {
+    it->s0 = 0;
+    it->sn = n_slabs;
+    it->part = -1;
+    it->b = 0;
     if (!LIST) {
-      *r0 = one_r0;
-      *st = one_st;
+      it->r0 = one_r0;
+      it->st = one_st;
       return j == 0;
     }
     if (MODE == 2 && last.ways > 1 && j >= last.full) {
       const int p = j - last.full, ks = p / last.rem;
       if (ks >= last.ways) return false;
       j = last.full + p - ks * last.rem;
-      *s0 = ks * last.per;
-      *sn = min(last.per, n_slabs - *s0);
-      *part = (int)(blockIdx.x & 7) * F_XCD_WGS + p;
+      it->s0 = ks * last.per;
+      it->sn = min(last.per, n_slabs - it->s0);
+      it->part = (int)(blockIdx.x & 7) * F_XCD_WGS + p;
     }
     int rt;
-    if (!locate_base(a, row_tiles_now, (int)(blockIdx.x & 7), j, &rt, st)) return false;
-    *r0 = rt * FT;
+    if (!locate_base(a, row_tiles_now, (int)(blockIdx.x & 7), j, &rt, &it->st)) return false;
+    it->r0 = rt * FT;
+    if (TW && a.batch > 1) {
+      it->b = rt / tiles_each;
+      it->r0 = it->b * a.rows + (rt - it->b * tiles_each) * FT;
+    }
     return true;
   };
 
@@ -689,30 +765,46 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
     const int chunk16 = ((lane & 7) ^ ((row >> 1) & 7)) * 16;
     return (uint32_t)(min(row, lim) * (int)pitch + chunk16);
   };
+  // (K-major: two rows of the slab a request, a lane's 16 bytes of its row's 512; columns past the last whole chunk of the matrix row are
+  // clamped onto it)
+  auto krow_offset = [&](int i, int chunks, size_t pitch) -> uint32_t {
+    const int k = (wave * F_PAIRS + i) * 2 + (lane >> 5);
+    const int chunk = (lane & 31) ^ (((k & 3) | ((k >> 3) & 1) << 2) << 1);
+    return (uint32_t)(k * (int)pitch + min(chunk, chunks - 1) * 16);
+  };
   uint32_t voffA[F_PAIRS], voffB[F_PAIRS];
-  const unsigned char* Wtile = Wp;
+  const unsigned char *Wtile = Wp, *Wb = Wp;
   const unsigned char* Hp = Hm;
   // ---- the cursor of the operand stream: slab lslab of weight tile lvt of the item at position lj (none: !live) ----------
   int lj = first, lslab = 0, lslab_end = n_slabs, lvt = 0, lvt_end = 0, rot = 0;
+  int w_col = 0, h_col = 0;                  // K-major: byte of the tile's first column in a row
   bool live = true;
   auto set_tile = [&](int vt) {
-    Wtile = Wp + (size_t)vt * FT * pitch_w;
+    if (TW) w_col = vt * F_KROW;
+    Wtile = TW ? Wb + w_col : Wp + (size_t)vt * FT * pitch_w;
 #pragma unroll
-    for (int i = 0; i < F_PAIRS; ++i) voffA[i] = row_offset(i, n_valid - 1 - vt * FT, pitch_w);
+    for (int i = 0; i < F_PAIRS; ++i)
+      voffA[i] = TW ? krow_offset(i, ((int)pitch_w - w_col) >> 4, pitch_w) : row_offset(i, n_valid - 1 - vt * FT, pitch_w);
   };
   auto open_item = [&]() {
-    int r0, st, s0, sn, part;
-    live = item(lj, &r0, &st, &s0, &sn, &part);
+    Item it;
+    live = item(lj, &it);
     if (!live) return;
-    lslab = s0;
-    lslab_end = s0 + sn;
+    const int r0 = it.r0, st = it.st;
+    lslab = it.s0;
+    lslab_end = it.s0 + it.sn;
     lvt = st * a.strip;
     lvt_end = min(lvt + a.strip, n_vt);
     live = lvt < lvt_end;
     if (!live) return;
-    Hp = Hm + (size_t)r0 * pitch_h;
+    if (TH) h_col = (r0 - it.b * a.rows) * 2;
+    Hp = Hm + (TH ? (size_t)h_col : (size_t)r0 * pitch_h);
+    if (TH) Hp += (size_t)it.b * a.batch_h * 2;
+    if (TW) Wb = Wp + (size_t)it.b * a.batch_w * 2;
 #pragma unroll
-    for (int i = 0; i < F_PAIRS; ++i) voffB[i] = row_offset(i, r_end - 1 - r0, pitch_h);
+    for (int i = 0; i < F_PAIRS; ++i)
+      voffB[i] = TH ? krow_offset(i, ((int)pitch_h - h_col) >> 4, pitch_h)
+                    : row_offset(i, (TW && a.batch > 1 ? (it.b + 1) * a.rows : r_end) - 1 - r0, pitch_h);
     if (ROT) rot = st % n_slabs;
     set_tile(lvt);
   };
@@ -721,6 +813,8 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
   uint32_t isA = 0;                          // LDS destination (operand A) of the slab being requested
   const unsigned char* is_ga = Wp;
   const unsigned char* is_gb = Hm;
+  int is_rows = 0, is_col_a = 0, is_col_b = 0;
+  u32x4 is_ra, is_rb;                        // their descriptors where they are K-major
   auto issue_begin = [&](int stage) {
     isA = __builtin_amdgcn_readfirstlane(lds_base + stage * F_STAGE + wave * (F_PAIRS * 1024));
     if (live) {                              // else: keep the last valid source
@@ -729,17 +823,30 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
         sl += rot;
         if (sl >= n_slabs) sl -= n_slabs;
       }
-      is_ga = Wtile + (size_t)sl * F_SLAB;
-      is_gb = Hp + (size_t)sl * F_SLAB;
+      is_ga = Wtile + (size_t)sl * (TW ? 64 * pitch_w : F_SLAB);
+      is_gb = Hp + (size_t)sl * (TH ? 64 * pitch_h : F_SLAB);
+      is_col_a = w_col;
+      is_col_b = h_col;
+      is_rows = k_rows - sl * 64;
     }
+    // (a descriptor's range ends with the matrix's last row)
+    if (TW) is_ra = k_rows_rsrc(is_ga, is_rows, pitch_w, is_col_a);
+    if (TH) is_rb = k_rows_rsrc(is_gb, is_rows, pitch_h, is_col_b);
   };
   // request n of the 16 of a slab: 8 rows of the vocabulary tile (n even) or of the hidden rows' (n odd)
   auto request = [&](auto n_) __attribute__((always_inline)) {
     constexpr int n = decltype(n_)::value;
-    if constexpr (n & 1)
-      load16_to_lds<F_OPER + (n >> 1) * 1024>(is_gb, voffB[n >> 1], isA);
-    else
-      load16_to_lds<(n >> 1) * 1024>(is_ga, voffA[n >> 1], isA);
+    if constexpr (n & 1) {
+      if constexpr (TH)
+        load16_to_lds<F_OPER + (n >> 1) * 1024>(is_rb, voffB[n >> 1], isA);
+      else
+        load16_to_lds<F_OPER + (n >> 1) * 1024>(is_gb, voffB[n >> 1], isA);
+    } else {
+      if constexpr (TW)
+        load16_to_lds<(n >> 1) * 1024>(is_ra, voffA[n >> 1], isA);
+      else
+        load16_to_lds<(n >> 1) * 1024>(is_ga, voffA[n >> 1], isA);
+    }
   };
   auto issue_end = [&]() {
     if (live && ++lslab == lslab_end) {
@@ -757,19 +864,43 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
   const int quarter = lane >> 4;    // which 8 of a k-step's 32 elements
   const int offA0 = (wv * 128 + (lane & 15)) * F_SLAB;
   const int offB0 = (wr * 128 + (lane & 15)) * F_SLAB;
-  // fragment n of k-step q of the slab in a stage, counted in the order the MFMAs first need them: b0, a0, b1 .. b7,
-  // a1 .. a7
-  auto read_one = [&](Frags& f, int stage, int q, auto n_) __attribute__((always_inline)) {
-    constexpr int n = decltype(n_)::value;
-    constexpr bool is_a = n == 1 || n > F_N;
+  // (K-major: lane l reads 8 bytes of row k = 8 quarter + ((l & 15) >> 2) of the k-step, and of row k + 4, in the piece of block idx of its
+  // wave's 8; idx only meets the low 3 bits of the piece)
+  const uint32_t tr0 = (uint32_t)((8 * quarter + ((lane & 15) >> 2)) * F_KROW + ((((lane & 15) >> 2) | (quarter & 1) << 2) * 32) + (lane & 3) * 8);
+  // (addresses of the eight blocks in the stage that is read: everything else is an instruction's own offset)
+  uint32_t trA[F_N], trB[F_N];
+#pragma unroll
+  for (int i = 0; i < F_N; ++i) {
+    trA[i] = lds_base + ((tr0 + wv * 256) ^ (i * 32));
+    trB[i] = lds_base + ((tr0 + wr * 256) ^ (i * 32));
+  }
+  // read e (Schedule) of k-step q of the slab in a stage
+  using Sched = Schedule<TW, TH>;
+  auto read_one = [&](Frags& f, int stage, auto q_, auto e_, auto next_) __attribute__((always_inline)) {
+    constexpr bool next = decltype(next_)::value;
+    constexpr int q = decltype(q_)::value, e = decltype(e_)::value, n = Sched::fragment(e), half = Sched::half(e);
+    constexpr bool is_a = Sched::is_a(n);
     constexpr int idx = n <= 1 ? 0 : (n <= F_N ? n - 1 : n - F_N);
     const int base = stage * F_STAGE + (((4 * q + quarter) ^ sw) << 4);
-    if constexpr (is_a)
+    // (the first k-step's reads go over to the other stage)
+    if constexpr (next && half == 0 && (is_a ? TW : TH)) {
+      if constexpr (is_a)
+        asm volatile("v_add_u32 %0, %1, %0" : "+v"(trA[idx]) : "s"(stage ? (uint32_t)F_STAGE : 0u - (uint32_t)F_STAGE));
+      else
+        asm volatile("v_add_u32 %0, %1, %0" : "+v"(trB[idx]) : "s"(stage ? (uint32_t)F_STAGE : 0u - (uint32_t)F_STAGE));
+    }
+    if constexpr (is_a && TW)
+      read_transposed<q * 32 * F_KROW + half * 4 * F_KROW, half>(f.a[idx], trA[idx]);
+    else if constexpr (!is_a && TH)
+      read_transposed<F_OPER + q * 32 * F_KROW + half * 4 * F_KROW, half>(f.b[idx], trB[idx]);
+    else if constexpr (is_a)
       f.a[idx] = *reinterpret_cast<const uint4*>(lds + base + offA0 + idx * 16 * F_SLAB);
     else
       f.b[idx] = *reinterpret_cast<const uint4*>(lds + base + F_OPER + offB0 + idx * 16 * F_SLAB);
   };
 
+  constexpr std::integral_constant<int, 0> kZero{};
+  constexpr std::integral_constant<int, 1> kOne{};
   Acc acc;
   Frags f[2];                                        // the two k-steps of a slab
   int g = 0;                                         // slabs behind
@@ -783,35 +914,36 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
       constexpr int m = decltype(m_)::value;
       constexpr int q = m / (F_N * F_N), i = m / F_N % F_N;
       constexpr int j = i & 1 ? F_N - 1 - m % F_N : m % F_N;      // (to and fro: one operand stays from MFMA to MFMA, 1 %)
-      if constexpr (m == kFree) {
+      if constexpr (m == Sched::free_) {
         __builtin_amdgcn_sched_barrier(0);
         barrier_after_lds();
         if (!PROBE_NOREQ) issue_begin(stage);
         __builtin_amdgcn_sched_barrier(0);
       }
-      if constexpr (m == kLanded) {
+      if constexpr (m == Sched::landed) {
         __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(PROBE_NOREQ ? 0 : kOutAtLanded));
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(PROBE_NOREQ ? 0 : Sched::out_at_landed));
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
       }
       mfma<FIRST && q == 0>(acc[i][j], f[q].a[i], f[q].b[j]);
-      if constexpr (!PROBE_MFMA && m >= kRead2 && m < kRead2 + 16) {
+      if constexpr (!PROBE_MFMA && m >= Sched::read2 && m < Sched::read2 + Sched::reads) {
         __builtin_amdgcn_sched_barrier(0);
-        read_one(f[1], stage, 1, std::integral_constant<int, (m >= kRead2 && m < kRead2 + 16) ? m - kRead2 : 0>{});
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      if constexpr (!PROBE_MFMA && m >= kRead1 && m < kRead1 + 16) {
-        __builtin_amdgcn_sched_barrier(0);
-        read_one(f[0], stage ^ 1, 0, std::integral_constant<int, (m >= kRead1 && m < kRead1 + 16) ? m - kRead1 : 0>{});
+        read_one(f[1], stage, kOne, std::integral_constant<int, m - Sched::read2>{}, std::false_type{});
         __builtin_amdgcn_sched_barrier(0);
       }
-      if constexpr (!PROBE_NOREQ && m >= kRequest && (m - kRequest) % kRequestEvery == 0 && (m - kRequest) / kRequestEvery < 2 * F_PAIRS) {
+      if constexpr (!PROBE_MFMA && m >= Sched::read1 && m < Sched::read1 + Sched::reads) {
         __builtin_amdgcn_sched_barrier(0);
-        request(std::integral_constant<int, (m >= kRequest) ? (m - kRequest) / kRequestEvery : 0>{});
-        if constexpr ((m - kRequest) / kRequestEvery == 2 * F_PAIRS - 1) issue_end();
+        read_one(f[0], stage ^ 1, kZero, std::integral_constant<int, m - Sched::read1>{}, std::true_type{});
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      constexpr int rq = m - Sched::request;
+      if constexpr (!PROBE_NOREQ && rq >= 0 && rq % Sched::request_every == 0 && rq / Sched::request_every < 2 * F_PAIRS) {
+        __builtin_amdgcn_sched_barrier(0);
+        request(std::integral_constant<int, rq / Sched::request_every>{});
+        if constexpr (rq / Sched::request_every == 2 * F_PAIRS - 1) issue_end();
         __builtin_amdgcn_sched_barrier(0);
       }
     });
@@ -832,11 +964,13 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    static_for<16>([&](auto n) __attribute__((always_inline)) { read_one(f[0], 0, 0, n); });
-    if (PROBE_MFMA) static_for<16>([&](auto n) __attribute__((always_inline)) { read_one(f[1], 0, 1, n); });
+    static_for<Sched::reads>([&](auto e) __attribute__((always_inline)) { read_one(f[0], 0, kZero, e, std::false_type{}); });
+    if (PROBE_MFMA) static_for<Sched::reads>([&](auto e) __attribute__((always_inline)) { read_one(f[1], 0, kOne, e, std::false_type{}); });
   }
-  int r0, st, s0, sn, part;
-  for (int j = first; item(j, &r0, &st, &s0, &sn, &part); j += step) {
+  Item it;
+  for (int j = first; item(j, &it); j += step) {
+    const int r0 = it.r0, st = it.st;
+    if (TW && a.batch > 1) r_end = (it.b + 1) * a.rows;
     Triple run[F_N];
     Draw draw[F_N];                                  // MODE 6 only
 #pragma unroll
@@ -847,15 +981,15 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
     const int vt0 = st * a.strip, vt_end = min(vt0 + a.strip, n_vt);      // (modes 1, 4: possibly no tile)
     for (int vt = vt0; vt < vt_end; ++vt) {
       slab_step(std::true_type{});
-      for (int slab = 1; slab < sn; ++slab) slab_step(std::false_type{});
+      for (int slab = 1; slab < it.sn; ++slab) slab_step(std::false_type{});
       if (PROBE_MFMA && vt + 1 < vt_end) continue;
       wait_for_mfma();
       // ---- this vocabulary tile is complete: fold its 128 x 128 logits into the running triples, or store it ------
       int row_base = r0 + wr * 128, col_base = vt * FT + wv * 128 + quarter * 4;
       asm volatile("" : "+v"(col_base), "+v"(row_base));   // (what follows from them is not worked out ahead of the K loop and kept)
       if (MODE == 2) {
-        if (part >= 0)
-          store_partial16(acc, a.split + (ptrdiff_t)part * (FT * FT) - ((ptrdiff_t)r0 * FT + vt * FT), FT, row_base, r_end, col_base, n_valid);
+        if (it.part >= 0)
+          store_partial16(acc, a.split + (ptrdiff_t)it.part * (FT * FT) - ((ptrdiff_t)r0 * FT + vt * FT), FT, row_base, r_end, col_base, n_valid);
         else if (a.stream_f32)
           store_tile16_f32(acc, a, row_base, r_end, col_base, n_valid);
         else
@@ -959,18 +1093,19 @@ __device__ __forceinline__ void finish_linear(const LogitsArgs& a, int row, int 
 // (8 XCDs x 16 tiles, 8 runs of 32 rows); a thread has 4 columns of 8 rows.  Bound by the parts' bytes: 60 MB in 14 us.
 __global__ void __launch_bounds__(256) tile_sum_kernel(LogitsArgs a) {
   const int xcd = blockIdx.x & 7, t = blockIdx.x >> 3;
-  const int r_end = a.rows_dev ? min(a.rows, *a.rows_dev) : a.rows;
-  const int row_tiles = (r_end + FT - 1) / FT;
+  const int rows = a.rows_dev ? min(a.rows, *a.rows_dev) : a.rows;
+  const int tiles_each = (rows + FT - 1) / FT, row_tiles = max(a.batch, 1) * tiles_each;
   const LastRound last = last_round(a, row_tiles, xcd, dense_slabs(a));
   int rt, st;
   if (last.ways < 2 || t >= last.rem || !locate_base(a, row_tiles, xcd, last.full + t, &rt, &st)) return;
+  const int b = rt / tiles_each, r0 = b * rows + (rt - b * tiles_each) * FT, r_end = (b + 1) * rows;
   const int tcol = 4 * (int)(threadIdx.x & 63), col = st * FT + tcol;
   if (col >= a.w_rows) return;
   const float4 bias = a.bias ? *reinterpret_cast<const float4*>(a.bias + col) : float4{0.f, 0.f, 0.f, 0.f};
   const size_t part_step = (size_t)last.rem * (FT * FT);
 #pragma unroll 2
   for (int i = 0; i < 8; ++i) {
-    const int trow = (int)blockIdx.y * 32 + i * 4 + (int)(threadIdx.x >> 6), row = rt * FT + trow;
+    const int trow = (int)blockIdx.y * 32 + i * 4 + (int)(threadIdx.x >> 6), row = r0 + trow;
     if (row >= r_end) return;
     const float* from = a.split + (size_t)(xcd * F_XCD_WGS + t) * (FT * FT) + trow * FT + tcol;
     float4 x = *reinterpret_cast<const float4*>(from);
@@ -1011,6 +1146,15 @@ unsigned z2z_logits_fast_order(LogitsArgs& a, int forced) {
   const long long tail = (long long)(P % (a.map_lp * a.map_xp)) * q;
   const long long longest = main_items + (tail + 7) / 8;
   return 8u * (unsigned)(longest < 32 ? longest : 32);
+}
+
+int z2z_launch_linear_kmajor(const LogitsArgs& a, bool rows_too, unsigned grid, hipStream_t s) {
+  if (rows_too)
+    hipLaunchKernelGGL((logits_fast_kernel<2, false, true, true>), dim3(grid), dim3(F_THREADS), F_LDS, s, a);
+  else
+    hipLaunchKernelGGL((logits_fast_kernel<2, false, true, false>), dim3(grid), dim3(F_THREADS), F_LDS, s, a);
+  Z2Z_HIP_TRY(hipGetLastError());
+  return Z2Z_OK;
 }
 
 int z2z_launch_logits_fast(int mode, const LogitsArgs& a, unsigned grid, hipStream_t s) {
@@ -1072,6 +1216,10 @@ int z2z_logits_fast_prepare(z2z_ctx* c) {
   Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(logits_fast_kernel<8>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, F_LDS));
   Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(logits_fast_kernel<9>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, F_LDS));
+  Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(logits_fast_kernel<2, false, true, false>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, F_LDS));
+  Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(logits_fast_kernel<2, false, true, true>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, F_LDS));
   Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(logits_fast_kernel<0, true>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, F_LDS));

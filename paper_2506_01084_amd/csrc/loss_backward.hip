@@ -68,33 +68,27 @@ int z2z_launch_hyper_embed_backward(z2z_ctx* c, const void* dW_hyper, float* dE,
 // the logits, dZ = g * (softmax - onehot), is written out once in bf16 (the logits are recomputed by the
 // forward kernel with another epilogue, using the forward pass's lse), then
 //   dH = dZ_base W_base + dZ_hyper[b] W_hyper[b],   dW_base = dZ_base^T H,   dW_hyper[b] = dZ_hyper[b]^T H[b]
-// are four dense products on the same MFMA kernel, which wants both operands contiguous along the contraction:
-// hence one transposed copy of each operand (weights, hidden rows, dZ), made by a bandwidth-bound kernel.
+// are four dense products on the same MFMA kernel (the last and the second term, one per sequence, in a launch each), which reads
+// every operand as it is.
 int z2z_launch_extended_nll_backward(z2z_ctx* c, const void* H, int32_t rows, int32_t rows_per_seq, const void* W_base,
                                      const void* W_hyper, const int32_t* targets, const float* lse,
                                      const float* grad_nll, void* dH, void* dW_base, void* dW_hyper, hipStream_t s) {
   const int B = c->cfg.B, V = c->cfg.V, cap = c->cfg.cap, d = c->cfg.d;
   if (c->cfg.dtype != Z2Z_BF16 || d % 64 != 0 || !c->fast_ready) return Z2Z_EUNSUPPORTED;
-  const size_t Vp = round_up(V, 64), capp = round_up(cap, 64), Np = round_up(rows_per_seq, 64);
+  const size_t Vp = round_up(V, 64), capp = round_up(cap, 64);
   // The sequences go in chunks of n_seq, as many as the work-space limit allows (all of them at the sizes of
   // the benchmark configurations): dH and dW_hyper of a chunk are its own, dW_base of a later chunk adds to the
   // bf16 result of the earlier ones (one more rounding per chunk).
   // work space (bf16 unless noted), 256-byte aligned pieces
   size_t off = 0;
-  size_t o_g, o_Pb, o_PbT, o_Ph, o_PhT, o_WbT, o_WhT, o_HT, o_HTs;
+  size_t o_g, o_Pb, o_Ph;
   auto take = [&](size_t bytes) { const size_t at = off; off += round_up(bytes, 256); return at; };
   auto layout = [&](int n_seq) {
-    const size_t rc = (size_t)n_seq * rows_per_seq, rcp = z2z_contraction_pitch(rc, 64);
+    const size_t rc = (size_t)n_seq * rows_per_seq;
     off = 0;
     o_g = take(rc * 4);                              // float g[rows of the chunk]
     o_Pb = take(rc * Vp * 2);                        // dZ, base columns      [rows, Vp]
-    o_PbT = take((size_t)V * rcp * 2);               // its transpose         [V, rows_p]
     o_Ph = take(rc * capp * 2);                      // dZ, hyper columns     [rows, capp]
-    o_PhT = take((size_t)n_seq * cap * Np * 2);      // per sequence          [n_seq][cap, Np]
-    o_WbT = take((size_t)d * Vp * 2);                // W_base^T              [d, Vp]
-    o_WhT = take((size_t)n_seq * d * capp * 2);      // W_hyper[b]^T          [n_seq][d, capp]
-    o_HT = take((size_t)d * rcp * 2);                // H^T                   [d, rows_p]
-    o_HTs = take((size_t)n_seq * d * Np * 2);        // H[b]^T                [n_seq][d, Np]
     return off;
   };
   const size_t limit = (size_t)200 << 30;
@@ -112,8 +106,7 @@ int z2z_launch_extended_nll_backward(z2z_ctx* c, const void* H, int32_t rows, in
   }
   unsigned char* ws = reinterpret_cast<unsigned char*>(c->bwd_ws);
   float* g = reinterpret_cast<float*>(ws + o_g);
-  void *Pb = ws + o_Pb, *PbT = ws + o_PbT, *Ph = ws + o_Ph, *PhT = ws + o_PhT, *WbT = ws + o_WbT, *WhT = ws + o_WhT,
-       *HT = ws + o_HT, *HTs = ws + o_HTs;
+  void *Pb = ws + o_Pb, *Ph = ws + o_Ph;
   // (nothing is folded over a strip here, and a workgroup's operand stream runs on from tile to tile anyway.  Tiles one by one, against
   // strips of four: base part of 1448 rows, V = 151936 1332 -> 1238 us, 109, V = 32064 237 -> 66, 32768, V = 128256 24.55 -> 24.39 ms;
   // hyper part of 2 x 724 rows 217 -> 77 us.)
@@ -121,12 +114,10 @@ int z2z_launch_extended_nll_backward(z2z_ctx* c, const void* H, int32_t rows, in
   const uint16_t* H16 = reinterpret_cast<const uint16_t*>(H);
   const uint16_t* Wh16 = reinterpret_cast<const uint16_t*>(W_hyper);
 
-  int rc = z2z_launch_transpose(W_base, WbT, V, nullptr, d, d, (int)Vp, 1, 0, 0, s);
-  if (rc != Z2Z_OK) return rc;
+  int rc;
   for (int b0 = 0; b0 < B; b0 += n_seq) {
     const int nb = b0 + n_seq <= B ? n_seq : B - b0;
     const int r0 = b0 * rows_per_seq, rows_c = nb * rows_per_seq;
-    const size_t rows_p = z2z_contraction_pitch(rows_c, 64);
     const uint16_t* Hc = H16 + (size_t)r0 * d;
     const uint16_t* Whc = Wh16 + (size_t)b0 * cap * d;
     hipLaunchKernelGGL(row_grad_kernel, dim3((rows_c + 255) / 256), dim3(256), 0, s, targets + r0,
@@ -156,27 +147,20 @@ int z2z_launch_extended_nll_backward(z2z_ctx* c, const void* H, int32_t rows, in
                                   nb);
       if (rc != Z2Z_OK) return rc;
     }
-    // ---- transposed copies -----------------------------------------------------------------------------------
-    if ((rc = z2z_launch_transpose(Hc, HT, rows_c, nullptr, d, d, (int)rows_p, 1, 0, 0, s)) != Z2Z_OK) return rc;
-    if ((rc = z2z_launch_transpose(Pb, PbT, rows_c, nullptr, V, (int)Vp, (int)rows_p, 1, 0, 0, s)) != Z2Z_OK) return rc;
-    if (cap > 0) {
-      if ((rc = z2z_launch_transpose(Whc, WhT, cap, nullptr, d, d, (int)capp, nb, (size_t)cap * d, (size_t)d * capp, s)) != Z2Z_OK) return rc;
-      if ((rc = z2z_launch_transpose(Hc, HTs, rows_per_seq, nullptr, d, d, (int)Np, nb, (size_t)rows_per_seq * d, (size_t)d * Np, s)) != Z2Z_OK) return rc;
-      if ((rc = z2z_launch_transpose(Ph, PhT, rows_per_seq, nullptr, cap, (int)capp, (int)Np, nb, (size_t)rows_per_seq * capp, (size_t)cap * Np, s)) != Z2Z_OK) return rc;
-    }
     // ---- the products ------------------------------------------------------------------------------------------
     uint16_t* dHc = reinterpret_cast<uint16_t*>(dH) + (size_t)r0 * d;
-    if ((rc = z2z_launch_linear(c, Pb, WbT, nullptr, nullptr, 0, dHc, rows_c, nullptr, d, (int)Vp, s)) != Z2Z_OK) return rc;
-    if ((rc = z2z_launch_linear(c, PbT, HT, nullptr, b0 > 0 ? dW_base : nullptr, 0, dW_base, V, nullptr, d, (int)rows_p, s)) != Z2Z_OK) return rc;
-    for (int b = 0; b < nb && cap > 0; ++b) {
-      uint16_t* dH_b = dHc + (size_t)b * rows_per_seq * d;
-      const uint16_t* Ph_b = reinterpret_cast<const uint16_t*>(Ph) + (size_t)b * rows_per_seq * capp;
-      const uint16_t* WhT_b = reinterpret_cast<const uint16_t*>(WhT) + (size_t)b * d * capp;
-      if ((rc = z2z_launch_linear(c, Ph_b, WhT_b, nullptr, dH_b, 0, dH_b, rows_per_seq, nullptr, d, (int)capp, s)) != Z2Z_OK) return rc;
-      const uint16_t* PhT_b = reinterpret_cast<const uint16_t*>(PhT) + (size_t)b * cap * Np;
-      const uint16_t* HTs_b = reinterpret_cast<const uint16_t*>(HTs) + (size_t)b * d * Np;
-      uint16_t* dWh_b = reinterpret_cast<uint16_t*>(dW_hyper) + (size_t)(b0 + b) * cap * d;
-      if ((rc = z2z_launch_linear(c, PhT_b, HTs_b, nullptr, nullptr, 0, dWh_b, cap, nullptr, d, (int)Np, s)) != Z2Z_OK) return rc;
+    rc = z2z_launch_linear_input(c, Pb, (int)Vp, W_base, d, V, nullptr, dHc, d, rows_c, nullptr, d, (int)Vp, s);
+    if (rc != Z2Z_OK) return rc;
+    rc = z2z_launch_linear_weight(c, Pb, (int)Vp, Hc, d, rows_c, nullptr, b0 > 0 ? dW_base : nullptr, dW_base, V, d, s);
+    if (rc != Z2Z_OK) return rc;
+    if (cap > 0) {                                   // one product per sequence
+      uint16_t* dWh = reinterpret_cast<uint16_t*>(dW_hyper) + (size_t)b0 * cap * d;
+      rc = z2z_launch_linear_input(c, Ph, (int)capp, Whc, d, cap, dHc, dHc, d, rows_per_seq, nullptr, d, (int)capp, s,
+                                   {nb, 0, (size_t)cap * d});
+      if (rc != Z2Z_OK) return rc;
+      rc = z2z_launch_linear_weight(c, Ph, (int)capp, Hc, d, rows_per_seq, nullptr, nullptr, dWh, cap, d, s,
+                                    {nb, (size_t)rows_per_seq * capp, (size_t)rows_per_seq * d});
+      if (rc != Z2Z_OK) return rc;
     }
   }
   return Z2Z_OK;
