@@ -27,23 +27,31 @@ __global__ void __launch_bounds__(256) fill_zero_kernel(uint4* p, size_t n16) {
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += (size_t)gridDim.x * 256) p[i] = z;
 }
 
-// dE[t_j] += a_j * dW_hyper[b, e] for the tokens of every existing entry: one wave per entry, float atomics
-// (tokens recur across entries and sequences).
+// dE[t_j] += a_j * dW_hyper[b, e] for the tokens of every existing entry, float atomics (tokens recur across entries and
+// sequences): a wave per entry and 512 features, lane l those at l + 64 t, so that an instruction adds to 256 bytes in a row; the entry's row
+// is read once.  (A wave per entry, the row once per token: 8 x 1024 entries, d = 4096 442 us, 350 entries, d = 3072 83.)
 __global__ void __launch_bounds__(256) pool_backward_kernel(const uint16_t* dW, float* dE, const int32_t* size,
                                                             const int32_t* ent_tokens, const int32_t* ent_len, int B,
-                                                            int V, int M, int cap, int d, int mean,
+                                                            int V, int M, int cap, int d, int groups, int mean,
                                                             const float* coef /* [Z2Z_MAX_M + 1][Z2Z_MAX_M] */) {
   const int lane = threadIdx.x & 63;
-  const long long row = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const long long wid = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const long long row = wid / groups;
   if (row >= (long long)B * cap) return;
   const int b = (int)(row / cap), e = (int)(row % cap);
   if (e >= min(max(size[b], 0), cap)) return;
+  const int f0 = (int)(wid % groups) * 512 + lane;
+  float g[8];
+#pragma unroll
+  for (int t = 0; t < 8; ++t) g[t] = f0 + 64 * t < d ? __uint_as_float((uint32_t)dW[row * d + f0 + 64 * t] << 16) : 0.f;
   const int L = min(max(ent_len[row], 1), M);
   for (int j = 0; j < L; ++j) {
     const int tok = min(max(ent_tokens[row * M + j], 0), V - 1);
     const float a = mean ? 1.0f / (float)L : coef[L * Z2Z_MAX_M + j];
-    for (int c = lane; c < d; c += 64)
-      atomicAdd(dE + (size_t)tok * d + c, a * __uint_as_float((uint32_t)dW[row * d + c] << 16));
+    float* to = dE + (size_t)tok * d + f0;
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+      if (f0 + 64 * t < d) atomicAdd(to + 64 * t, a * g[t]);
   }
 }
 
@@ -56,9 +64,10 @@ int z2z_launch_hyper_embed_backward(z2z_ctx* c, const void* dW_hyper, float* dE,
   if (cap == 0) return Z2Z_OK;
   if (!c->coef_dev) return Z2Z_EHIP;       // (allocated and filled by z2z_create)
   const long long rows = (long long)B * cap;
-  hipLaunchKernelGGL(pool_backward_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s,
+  const int groups = (c->cfg.d + 511) / 512;
+  hipLaunchKernelGGL(pool_backward_kernel, dim3((unsigned)((rows * groups + 3) / 4)), dim3(256), 0, s,
                      reinterpret_cast<const uint16_t*>(dW_hyper), dE, c->st.size, c->st.ent_tokens, c->st.ent_len, B,
-                     c->cfg.V, c->cfg.M, cap, c->cfg.d, c->cfg.pool == Z2Z_POOL_MEAN ? 1 : 0,
+                     c->cfg.V, c->cfg.M, cap, c->cfg.d, groups, c->cfg.pool == Z2Z_POOL_MEAN ? 1 : 0,
                      reinterpret_cast<const float*>(c->coef_dev));
   Z2Z_HIP_TRY(hipGetLastError());
   return Z2Z_OK;
