@@ -440,8 +440,17 @@ __global__ void __launch_bounds__(256) enc_pool_kernel(RowMap m, const float* Z,
 // below are the bandwidth-bound rest.  Gradients between kernels are bf16, sums fp32.
 // ---------------------------------------------------------------------------------------------------------
 
-__global__ void __launch_bounds__(256) enc_fill_kernel(float* p, size_t n) {
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) p[i] = 0.f;
+// The vector gradients, cleared in one launch (17 of them took 77 us): grid (64, pieces).
+struct Pieces {
+  static constexpr int kMax = 8 * Z2Z_MAX_ENCODER_LAYERS + 1;
+  int n;
+  float* p[kMax];
+  int32_t len[kMax];
+};
+__global__ void __launch_bounds__(256) enc_fill_kernel(Pieces z) {
+  float* p = z.p[blockIdx.y];
+  const int n = z.len[blockIdx.y];
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += 64 * 256) p[i] = 0.f;
 }
 
 // dX[r] = dW_hyper[b, e] / L for the L rows of every entry (h = mean of the real slots); one wave per entry.
@@ -470,17 +479,34 @@ __global__ void __launch_bounds__(256) enc_pool_backward_kernel(RowMap m, const 
 
 // (Float sums that several workgroups add to go through the hardware's float atomic add: every target here is
 // ordinary device memory.)
-// out[n] += sum over the pass's rows of G[r, n] (bias gradients).  A thread owns 8 columns and the rows
-// stripe + E_CS_STRIPES * (lane group + 4 i); grid (ceil(N / 512), E_CS_STRIPES): few adds per address.
-constexpr int E_CS_STRIPES = 32;
+// Column sums over the pass's rows: a thread owns the 8 columns of its lane's chunk and, of the stripe's rows, those of its wave
+// (every fourth); the waves' sums meet in LDS, and a stripe adds once to every column, lane by lane.  Grid (ceil(N / 512), stripes); as
+// many stripes work as have 8 rows a wave.  (Four adds a column and stripe, 32 bytes between lanes: 240 rows x 3072 27 us, 35404 x 4096 110.)
+constexpr int E_CS_STRIPES = 64;
+__device__ __forceinline__ int cs_stripes(int rows) { return min(max((rows + 31) / 32, 1), E_CS_STRIPES); }
+
+// acc: this thread's sums; out[512 blockIdx.x + column] += all waves'.  xch: 4 x 512 floats.  (The whole workgroup calls.)
+__device__ __forceinline__ void cs_add(const float (&acc)[8], float* xch, float* out, int n) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  store8(xch + wave * 512 + lane * 8, acc);
+  __syncthreads();
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int t = threadIdx.x + 256 * h, col = blockIdx.x * 512 + t;
+    if (col < n) unsafeAtomicAdd(out + col, (xch[t] + xch[512 + t]) + (xch[1024 + t] + xch[1536 + t]));
+  }
+}
+
+// out[n] += sum over the pass's rows of G[r, n] (bias gradients).
 __global__ void __launch_bounds__(256) enc_colsum_kernel(const uint4* G, int n_chunks, int pitch,
                                                          const int32_t* rows_dev, float* out) {
+  __shared__ __align__(16) float xch[4 * 512];
   const int c = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int rows = *rows_dev;
-  if (c >= n_chunks) return;
+  const int rows = *rows_dev, stripes = cs_stripes(rows);
+  if ((int)blockIdx.y >= stripes) return;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  const int step = 4 * E_CS_STRIPES;
-  for (int r = blockIdx.y + E_CS_STRIPES * (threadIdx.x >> 6); r < rows; r += 4 * step) {   // four loads in flight
+  const int step = 4 * stripes;
+  for (int r = blockIdx.y * 4 + (threadIdx.x >> 6); c < n_chunks && r < rows; r += 4 * step) {   // four loads in flight
     const uint4 q0 = G[(size_t)r * pitch + c];
     const uint4 q1 = load_if(r + step < rows, G + (size_t)(r + step) * pitch + c);
     const uint4 q2 = load_if(r + 2 * step < rows, G + (size_t)(r + 2 * step) * pitch + c);
@@ -499,8 +525,7 @@ __global__ void __launch_bounds__(256) enc_colsum_kernel(const uint4* G, int n_c
 #pragma unroll
     for (int t = 0; t < 8; ++t) acc[t] += g[t];
   }
-#pragma unroll
-  for (int t = 0; t < 8; ++t) unsafeAtomicAdd(out + (size_t)c * 8 + t, acc[t]);
+  cs_add(acc, xch, out, n_chunks * 8);
 }
 
 __device__ __forceinline__ float gelu_exact(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
@@ -520,18 +545,44 @@ __global__ void __launch_bounds__(256) enc_gelu_kernel(const uint4* U, uint4* F,
   }
 }
 
-// dU = dF * GELU'(U), in place over dF.
-__global__ void __launch_bounds__(256) enc_gelu_backward_kernel(uint4* dF, const uint4* U, int n_chunks,
-                                                                const int32_t* rows_dev) {
-  const size_t n = (size_t)*rows_dev * n_chunks;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
+// dU = dF * GELU'(U), in place over dF, and its column sums (the bias gradient) on the way: the stripes of enc_colsum_kernel, two rows at
+// a time.
+__global__ void __launch_bounds__(256) enc_gelu_backward_kernel(uint4* dF, const uint4* U, int n_chunks, int pitch,
+                                                                const int32_t* rows_dev, float* out) {
+  __shared__ __align__(16) float xch[4 * 512];
+  const int c = blockIdx.x * 64 + (threadIdx.x & 63);
+  const int rows = *rows_dev, stripes = cs_stripes(rows);
+  if ((int)blockIdx.y >= stripes) return;
+  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  const int step = 4 * stripes;
+  for (int r = blockIdx.y * 4 + (threadIdx.x >> 6); c < n_chunks && r < rows; r += 2 * step) {
+    const bool two = r + step < rows;
+    const size_t at = (size_t)r * pitch + c, at2 = at + (size_t)step * pitch;
+    const uint4 u0 = U[at], g0 = dF[at];
+    const uint4 u1 = load_if(two, U + at2), g1 = load_if(two, dF + at2);
     float u[8], g[8];
-    unpack8(U[i], u);
-    unpack8(dF[i], g);
+    unpack8(u0, u);
+    unpack8(g0, g);
 #pragma unroll
     for (int t = 0; t < 8; ++t) g[t] *= gelu_slope(u[t]);
-    dF[i] = pack8(g);
+    uint4 o = pack8(g);
+    dF[at] = o;
+    unpack8(o, g);                                   // (what the products read is what is summed)
+#pragma unroll
+    for (int t = 0; t < 8; ++t) acc[t] += g[t];
+    if (two) {
+      unpack8(u1, u);
+      unpack8(g1, g);
+#pragma unroll
+      for (int t = 0; t < 8; ++t) g[t] *= gelu_slope(u[t]);
+      o = pack8(g);
+      dF[at2] = o;
+      unpack8(o, g);
+#pragma unroll
+      for (int t = 0; t < 8; ++t) acc[t] += g[t];
+    }
   }
+  cs_add(acc, xch, out, n_chunks * 8);
 }
 
 // LayerNorm backward: N = (x - mean) * rstd * gamma + beta.  out[r] = dres[r] + dx[r] with
@@ -605,17 +656,18 @@ __global__ void __launch_bounds__(256) enc_norm_backward_kernel(const int32_t* r
   }
 }
 
-// dgamma[n] += sum_r dN[r, n] * xh[r, n],  dbeta[n] += sum_r dN[r, n],  xh = (X - mean[r]) * rstd[r]: column sums
-// in the shape of enc_colsum_kernel (a thread owns 8 columns and a strided set of rows).
+// dgamma[n] += sum_r dN[r, n] * xh[r, n],  dbeta[n] += sum_r dN[r, n],  xh = (X - mean[r]) * rstd[r]: column sums as in
+// enc_colsum_kernel.
 __global__ void __launch_bounds__(256) enc_norm_param_grad_kernel(const uint4* dN, const float* X, const float2* stats,
                                                                   int n_chunks, const int32_t* rows_dev, float* dgamma,
                                                                   float* dbeta) {
+  __shared__ __align__(16) float xch[2][4 * 512];
   const int c = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int rows = *rows_dev;
-  if (c >= n_chunks) return;
+  const int rows = *rows_dev, stripes = cs_stripes(rows);
+  if ((int)blockIdx.y >= stripes) return;
   float ag[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, ab[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  const int step = 4 * E_CS_STRIPES;
-  for (int r = blockIdx.y + E_CS_STRIPES * (threadIdx.x >> 6); r < rows; r += 2 * step) {   // two rows in flight
+  const int step = 4 * stripes;
+  for (int r = blockIdx.y * 4 + (threadIdx.x >> 6); c < n_chunks && r < rows; r += 2 * step) {   // two rows in flight
     const bool two = r + step < rows;
     const int r2 = two ? r + step : r;
     const uint4 qg0 = dN[(size_t)r * n_chunks + c], qg1 = dN[(size_t)r2 * n_chunks + c];
@@ -638,11 +690,8 @@ __global__ void __launch_bounds__(256) enc_norm_param_grad_kernel(const uint4* d
       }
     }
   }
-#pragma unroll
-  for (int t = 0; t < 8; ++t) {
-    unsafeAtomicAdd(dgamma + (size_t)c * 8 + t, ag[t]);
-    unsafeAtomicAdd(dbeta + (size_t)c * 8 + t, ab[t]);
-  }
+  cs_add(ag, xch[0], dgamma, n_chunks * 8);
+  cs_add(ab, xch[1], dbeta, n_chunks * 8);
 }
 
 // Attention backward for one entry and 512 features (same split as the forward kernel).  Per query row i the
@@ -740,14 +789,16 @@ __global__ void __launch_bounds__(256) enc_attention_backward_kernel(RowMap m, c
 }
 
 // The gradient at the encoder's input: dE[token of row r] += dX[r] (float atomics: tokens recur), and
-// dP[slot of row r] += dX[r], the latter summed per slot over a stripe of 256 rows in registers first.
-// Grid (ceil(d / 512), ceil(max rows / 256)); a thread owns features f0 + lane + 64 t (t < 8) of a block of 512,
+// dP[slot of row r] += dX[r], the latter summed per slot over a stripe of rows in registers first.
+// Grid (ceil(d / 512), input_stripes): 128 stripes of the rows that exist, or stripes of 16 or of 256 (240 rows x 3072: one stripe of 256
+// 149 us, 15 of 16 17; 35404 x 4096: 139 of 256 536 us, 192 of 185 659); a thread owns features f0 + lane + 64 t (t < 8) of a block of 512,
 // so that the 64 lanes of one atomic instruction cover 256 consecutive bytes, and every fourth row of the stripe.
 __global__ void __launch_bounds__(256) enc_input_backward_kernel(RowMap m, const uint16_t* dX, float* dE, float* dP,
                                                                  int n_units) {
   const int f0 = blockIdx.x * 512 + (threadIdx.x & 63);
   const int rows = m.row0[n_units];
-  const int r_begin = blockIdx.y * 256 + (threadIdx.x >> 6), r_end = min(rows, (int)(blockIdx.y + 1) * 256);
+  const int per = min(max((rows + 127) / 128, 16), 256);
+  const int r_begin = (int)blockIdx.y * per + (threadIdx.x >> 6), r_end = min(rows, (int)(blockIdx.y + 1) * per);
   if (r_begin >= r_end) return;
   float acc[Z2Z_MAX_M][8];
 #pragma unroll
@@ -971,6 +1022,11 @@ void colsum_to(const void* G, int N, int ld, const int32_t* rows_dev, float* out
                      reinterpret_cast<const uint4*>(G), N / 8, ld / 8, rows_dev, out);
 }
 
+unsigned input_stripes(int R) {
+  const int most = (R + 15) / 16, of256 = (R + 255) / 256;
+  return (unsigned)(of256 > 128 ? of256 : (most < 128 ? most : 128));
+}
+
 unsigned flat_grid(size_t n) {
   const size_t blocks = (n + 255) / 256;
   return (unsigned)(blocks < 1 ? 1 : (blocks > 65536 ? 65536 : blocks));
@@ -1063,14 +1119,16 @@ int z2z_launch_hyper_encode_train(z2z_ctx* c, int mode, const void* E, const z2z
   const float scale = 1.0f / sqrtf((float)dh);
 
   // vector gradients are sums over all passes: cleared once, added to by every pass
-  auto clear = [&](const float* q, size_t n) {
-    hipLaunchKernelGGL(enc_fill_kernel, dim3(flat_grid(n)), dim3(256), 0, s, const_cast<float*>(q), n);
+  Pieces zero = {};
+  auto clear = [&](const float* q, int n) {
+    zero.p[zero.n] = const_cast<float*>(q);
+    zero.len[zero.n++] = n;
   };
   for (int l = 0; l < nl && mode != 1; ++l) {
     const z2z_encoder_layer& g = grad->layers[l];
     clear(g.ln1_g, d);
     clear(g.ln1_b, d);
-    clear(g.b_qkv, (size_t)3 * d);
+    clear(g.b_qkv, 3 * d);
     clear(g.b_o, d);
     if (ffn) {
       clear(g.ln2_g, d);
@@ -1079,7 +1137,10 @@ int z2z_launch_hyper_encode_train(z2z_ctx* c, int mode, const void* E, const z2z
       clear(g.b_2, d);
     }
   }
-  if (mode != 1) clear(dP, (size_t)Z2Z_MAX_M * d);
+  if (mode != 1) {
+    clear(dP, Z2Z_MAX_M * d);
+    hipLaunchKernelGGL(enc_fill_kernel, dim3(64, (unsigned)zero.n), dim3(256), 0, s, zero);
+  }
 
   int rc;
 #define Z2Z_TRY_RC(expr)      \
@@ -1159,9 +1220,9 @@ int z2z_launch_hyper_encode_train(z2z_ctx* c, int mode, const void* E, const z2z
         Z2Z_TRY_RC(z2z_launch_linear_input(c, dX, d, lay.w_2, dff, d, nullptr, dF, dffp, R, rows_dev, dff, d, s));
         acc = pass > 0 ? g.w_2 : nullptr;
         Z2Z_TRY_RC(z2z_launch_linear_weight(c, dX, d, v.F, dffp, R, rows_dev, acc, const_cast<void*>(g.w_2), d, dff, s));
-        hipLaunchKernelGGL(enc_gelu_backward_kernel, dim3(flat_grid((size_t)R * dffp / 8)), dim3(256), 0, s,
-                           reinterpret_cast<uint4*>(dF), reinterpret_cast<const uint4*>(v.U), dffp / 8, rows_dev);
-        colsum_to(dF, dff, dffp, rows_dev, const_cast<float*>(g.b_1), s);
+        hipLaunchKernelGGL(enc_gelu_backward_kernel, dim3((dff / 8 + 63) / 64, E_CS_STRIPES), dim3(256), 0, s,
+                           reinterpret_cast<uint4*>(dF), reinterpret_cast<const uint4*>(v.U), dff / 8, dffp / 8, rows_dev,
+                           const_cast<float*>(g.b_1));
         acc = pass > 0 ? g.w_1 : nullptr;
         Z2Z_TRY_RC(z2z_launch_linear_weight(c, dF, dffp, v.N2, d, R, rows_dev, acc, const_cast<void*>(g.w_1), dff, d, s));
         Z2Z_TRY_RC(z2z_launch_linear_input(c, dF, dffp, lay.w_1, d, dff, nullptr, dN, d, R, rows_dev, d, dff, s));
@@ -1187,7 +1248,7 @@ int z2z_launch_hyper_encode_train(z2z_ctx* c, int mode, const void* E, const z2z
       Z2Z_TRY_RC(z2z_launch_linear_input(c, dQKV, 3 * d, lay.w_qkv, d, 3 * d, nullptr, dN, d, R, rows_dev, d, 3 * d, s));
       norm_backward(dN, v.Xin, lay.ln1_g, dy, dX, g.ln1_g, g.ln1_b);
     }
-    hipLaunchKernelGGL(enc_input_backward_kernel, dim3((d + 511) / 512, (R + 255) / 256), dim3(256), 0, s, m, dX, dE,
+    hipLaunchKernelGGL(enc_input_backward_kernel, dim3((d + 511) / 512, input_stripes(R)), dim3(256), 0, s, m, dX, dE,
                        enc->pos ? dP : nullptr, n_units);
   }
 #undef Z2Z_TRY_RC
