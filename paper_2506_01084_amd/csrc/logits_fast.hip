@@ -218,26 +218,40 @@ __device__ __forceinline__ int list_length(const LogitsArgs& a, int row_tiles, i
   return blocks * a.map_lp * own_q + (int)(total * (xcd + 1) / 8) - (int)(total * xcd / 8);
 }
 
+// Length of the longest of the 8 lists, or one more.
+__device__ __forceinline__ int longest_list(const LogitsArgs& a, int row_tiles) {
+  const int P = a.map_p_rows ? row_tiles : a.n_strips, Q = a.map_p_rows ? a.n_strips : row_tiles;
+  const int blocks = P / (a.map_lp * a.map_xp);
+  return blocks * a.map_lp * ((Q + a.map_xq - 1) / a.map_xq) + ((P - blocks * a.map_lp * a.map_xp) * Q + 7) / 8;
+}
+
 // A dense layer's last round.  The 32 workgroups of an XCD take 32 output tiles of its list at a time; the `rem` tiles that are
 // left may be too few for them, and then every one of those is cut along K into `ways` parts of `per` slabs: position
-// full + part * rem + t is part `part` of tile full + t, its fp32 sums go to tile buffer xcd * 32 + part * rem + t, and
+// full + part * rem + t is part `part` of tile full + t.  Where all tiles together are at most half a round and the XCD with the most of them
+// would keep the others from another part, they are cut over all workgroups instead (`whole`): position 0 of workgroup g, counted XCD by XCD,
+// is part g / tiles of tile g % tiles (84 tiles, 10 or 11 an XCD, K = 151936: three parts instead of two, 1698 -> 1118 us; with as many parts either
+// way the XCDs' own tiles are the better ones, 70 tiles, K = 14336 146 against 160 us: a weight tile is fetched by one XCD).  The fp32 sums of a part go to the tile buffer of its workgroup, and
 // tile_sum_kernel adds the parts up, in order, with the layer's epilogue.  Decided here, where the row count is known: the host lays
 // out rows for codebooks that are full.  A part is worth it from 16 slabs saved on (17-20 us; the sum reads at most 64 MB, about 10).
+// (Runs of slabs as long as each other, across tiles, keep every CU busy but not at one place of K: 1.10 times the time at 2644 rows.)
 struct LastRound {
-  int full, rem, ways, per;
+  int full, rem, ways, per, whole;
 };
 constexpr int F_XCD_WGS = 32;                // workgroups of an XCD that a dense layer is launched with where it may be cut
+constexpr int F_WGS = 8 * F_XCD_WGS;
 constexpr int F_MIN_SAVED = 16;              // slabs
 constexpr int F_MIN_PART = 4;
 __device__ __forceinline__ LastRound last_round(const LogitsArgs& a, int row_tiles, int xcd, int n_slabs) {
-  const int len = list_length(a, row_tiles, xcd);
+  const int tiles = row_tiles * a.n_strips, len = list_length(a, row_tiles, xcd);
   LastRound r;
-  r.full = len & ~(F_XCD_WGS - 1);
-  r.rem = len - r.full;
+  r.whole = tiles > 0 && tiles <= F_WGS / 2 && F_WGS / tiles > F_XCD_WGS / longest_list(a, row_tiles);
+  r.full = r.whole ? 0 : len & ~(F_XCD_WGS - 1);
+  r.rem = r.whole ? tiles : len - r.full;
   r.ways = 1;
   r.per = n_slabs;
-  if (r.rem > 0 && r.rem <= F_XCD_WGS / 2) {
-    const int ways = min(F_XCD_WGS / r.rem, max(n_slabs / F_MIN_PART, 1));
+  const int wgs = r.whole ? F_WGS : F_XCD_WGS;
+  if (r.rem > 0 && r.rem <= wgs / 2) {
+    const int ways = min(wgs / r.rem, max(n_slabs / F_MIN_PART, 1));
     const int per = (n_slabs + ways - 1) / ways;
     if (n_slabs - per >= F_MIN_SAVED) {
       r.ways = (n_slabs + per - 1) / per;    // no empty parts
@@ -245,6 +259,15 @@ __device__ __forceinline__ LastRound last_round(const LogitsArgs& a, int row_til
     }
   }
   return r;
+}
+
+// Tile t of a dense layer that is cut over all workgroups: the longer side in blocks of four, all of the other side inside.
+__device__ __forceinline__ void locate_whole(const LogitsArgs& a, int row_tiles, int t, int* rt, int* st) {
+  const int P = a.map_p_rows ? row_tiles : a.n_strips, Q = a.map_p_rows ? a.n_strips : row_tiles;
+  const int blk = t / (4 * Q), in = t - blk * 4 * Q, wide = min(4, P - blk * 4);
+  const int q = in / wide, p = blk * 4 + in - q * wide;
+  *rt = a.map_p_rows ? p : q;
+  *st = a.map_p_rows ? q : p;
 }
 
 // Slabs of a dense layer's contraction (k_dev: its length is known on the device only).
@@ -735,20 +758,28 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
       it->st = one_st;
       return j == 0;
     }
+    int rt;
+    const int xcd = (int)(blockIdx.x & 7);
     if (MODE == 2 && last.ways > 1 && j >= last.full) {
-      const int p = j - last.full, ks = p / last.rem;
-      if (ks >= last.ways) return false;
-      j = last.full + p - ks * last.rem;
+      const int g = last.whole ? xcd * F_XCD_WGS + j : j - last.full, ks = __builtin_amdgcn_readfirstlane(g / last.rem);
+      if (ks >= last.ways || (last.whole && j >= F_XCD_WGS)) return false;
       it->s0 = ks * last.per;
       it->sn = min(last.per, n_slabs - it->s0);
-      it->part = (int)(blockIdx.x & 7) * F_XCD_WGS + p;
+      it->part = last.whole ? g : xcd * F_XCD_WGS + g;
+      j = last.full + g - ks * last.rem;
     }
-    int rt;
-    if (!locate_base(a, row_tiles_now, (int)(blockIdx.x & 7), j, &rt, &it->st)) return false;
+    if (MODE == 2 && last.ways > 1 && last.whole)
+      locate_whole(a, row_tiles_now, j, &rt, &it->st);
+    else if (!locate_base(a, row_tiles_now, xcd, j, &rt, &it->st))
+      return false;
     it->r0 = rt * FT;
     if (TW && a.batch > 1) {
-      it->b = rt / tiles_each;
+      it->b = __builtin_amdgcn_readfirstlane(rt / tiles_each);
       it->r0 = it->b * a.rows + (rt - it->b * tiles_each) * FT;
+    }
+    if (MODE == 2) {                         // (quotients come out of vector instructions; addresses follow from these)
+      it->r0 = __builtin_amdgcn_readfirstlane(it->r0);
+      it->st = __builtin_amdgcn_readfirstlane(it->st);
     }
     return true;
   };
@@ -1090,35 +1121,37 @@ __device__ __forceinline__ void finish_linear(const LogitsArgs& a, int row, int 
 }
 
 // The tiles of a dense layer's last round that were cut along K (last_round): out = act(sum of the parts + bias) + residual.  Grid
-// (8 XCDs x 16 tiles, 8 runs of 32 rows); a thread has 4 columns of 8 rows.  Bound by the parts' bytes: 60 MB in 14 us.
+// (128 tiles -- of the whole layer, or 16 of each XCD --, 16 runs of 16 rows); a thread has 4 columns of 4 rows.  Bound by the parts' bytes.
 __global__ void __launch_bounds__(256) tile_sum_kernel(LogitsArgs a) {
-  const int xcd = blockIdx.x & 7, t = blockIdx.x >> 3;
   const int rows = a.rows_dev ? min(a.rows, *a.rows_dev) : a.rows;
   const int tiles_each = (rows + FT - 1) / FT, row_tiles = max(a.batch, 1) * tiles_each;
+  const int xcd = blockIdx.x & 7;
   const LastRound last = last_round(a, row_tiles, xcd, dense_slabs(a));
+  const int t = last.whole ? (int)blockIdx.x : (int)(blockIdx.x >> 3);
+  if (last.ways < 2 || t >= last.rem) return;
   int rt, st;
-  if (last.ways < 2 || t >= last.rem || !locate_base(a, row_tiles, xcd, last.full + t, &rt, &st)) return;
+  if (last.whole)
+    locate_whole(a, row_tiles, t, &rt, &st);
+  else if (!locate_base(a, row_tiles, xcd, last.full + t, &rt, &st))
+    return;
   const int b = rt / tiles_each, r0 = b * rows + (rt - b * tiles_each) * FT, r_end = (b + 1) * rows;
   const int tcol = 4 * (int)(threadIdx.x & 63), col = st * FT + tcol;
   if (col >= a.w_rows) return;
   const float4 bias = a.bias ? *reinterpret_cast<const float4*>(a.bias + col) : float4{0.f, 0.f, 0.f, 0.f};
-  const size_t part_step = (size_t)last.rem * (FT * FT);
-#pragma unroll 2
-  for (int i = 0; i < 8; ++i) {
-    const int trow = (int)blockIdx.y * 32 + i * 4 + (int)(threadIdx.x >> 6), row = r0 + trow;
-    if (row >= r_end) return;
-    const float* from = a.split + (size_t)(xcd * F_XCD_WGS + t) * (FT * FT) + trow * FT + tcol;
-    float4 x = *reinterpret_cast<const float4*>(from);
-#pragma unroll 4
-    for (int k = 1; k < last.ways; ++k) {
-      const float4 y = *reinterpret_cast<const float4*>(from + (size_t)k * part_step);
-      x.x += y.x;
-      x.y += y.y;
-      x.z += y.z;
-      x.w += y.w;
+  const int trow = (int)blockIdx.y * 16 + (int)(threadIdx.x >> 6);
+  const float* from = a.split + (size_t)((last.whole ? 0 : xcd * F_XCD_WGS) + t) * (FT * FT) + trow * FT + tcol;
+  float4 x[4];
+  for (int k = 0; k < last.ways; ++k, from += (size_t)last.rem * (FT * FT)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (r0 + trow + i * 4 >= r_end) break;         // (rows that do not exist were not stored)
+      const float4 y = *reinterpret_cast<const float4*>(from + i * 4 * FT);
+      x[i] = k == 0 ? y : float4{x[i].x + y.x, x[i].y + y.y, x[i].z + y.z, x[i].w + y.w};
     }
-    finish_linear(a, row, col, x, bias);
   }
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (r0 + trow + i * 4 < r_end) finish_linear(a, r0 + trow + i * 4, col, x[i], bias);
 }
 
 }  // namespace
@@ -1190,7 +1223,7 @@ int z2z_launch_logits_fast(int mode, const LogitsArgs& a, unsigned grid, hipStre
 }
 
 int z2z_launch_tile_sum(const LogitsArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(tile_sum_kernel, dim3(8 * F_XCD_WGS / 2, FT / 32), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(tile_sum_kernel, dim3(F_WGS / 2, FT / 16), dim3(256), 0, s, a);
   Z2Z_HIP_TRY(hipGetLastError());
   return Z2Z_OK;
 }
