@@ -875,7 +875,7 @@ int z2z_launch_hyper_encode(z2z_ctx* c, const void* E, const z2z_encoder* enc, v
   // (few rows: does anything of the weights stay in the memory-side cache until the next call?)
   const bool once = (size_t)enc->n_layers * ((size_t)4 * d + (size_t)2 * dff) * d * sizeof(uint16_t) > z2z_logits::kKeepBytes;
   // rows per pass: all sequences, u_step entries each, M slots per entry
-  long long u_step = 65536 / ((long long)B * M);
+  long long u_step = 131072 / ((long long)B * M);
   if (u_step < 1) u_step = 1;
   if (u_step > units) u_step = units;
   const size_t R_max = (size_t)B * (size_t)u_step * M;
