@@ -290,25 +290,32 @@ static void fill_part(LogitsArgs& a, const int32_t* size, int tile, int tile_v, 
   a.n_work = (size ? B : 1) * a.row_tiles * a.n_strips;
 }
 
-// One launch of the bf16 MFMA tile kernel over the base part (hyper = false) or the per-sequence hyper part: fills in
-// the shape-dependent fields of `a` (tiles, strips, workgroup mapping) and launches; prob = true selects the
-// epilogue that stores the gradient with respect to the logits (the backward pass of the loss).
+void z2z_add_hyper_part(const z2z_ctx* c, LogitsArgs& a, const void* W_hyper, int part0, int strip, int rows_per_seq, int seq0, int n_seq) {
+  LogitsArgs h;
+  fill_part(h, c->st.size + seq0, 256, 256, n_seq, W_hyper, c->cfg.cap, c->cfg.V, part0, strip, 0, rows_per_seq);
+  a.hyper.W = h.W;
+  a.hyper.size = h.size;
+  a.hyper.cap = h.w_rows;
+  a.hyper.col0 = h.col0;
+  a.hyper.strip = h.strip;
+  a.hyper.n_strips = h.n_strips;
+  a.hyper.part0 = h.part0;
+  a.hyper.row_tiles = h.row_tiles;
+  a.hyper.n_work = h.n_work;
+  a.hyper.n_seq = n_seq;
+}
+
 int z2z_launch_logits_part(z2z_ctx* c, bool hyper, LogitsArgs a, const void* W, int w_rows, int col0,
-                           int part0, int strip, int rows, int rows_per_seq, int* n_strips_out, bool timed,
-                           hipStream_t s, bool prob, int seq0, int n_seq) {
-  // (seq0, n_seq: the hyper part of a sub-range of the sequences -- the caller passes that range's rows and
-  // its W_hyper; n_seq = 0 means all of them)
-  fill_part(a, hyper ? c->st.size + seq0 : nullptr, 256, 256, n_seq > 0 ? n_seq : c->cfg.B, W, w_rows, col0, part0, strip, rows,
-            rows_per_seq);
-  *n_strips_out = a.n_strips;
+                           int part0, int strip, int rows, int rows_per_seq, bool timed, hipStream_t s, bool prob) {
+  fill_part(a, hyper ? c->st.size : nullptr, 256, 256, c->cfg.B, W, w_rows, col0, part0, strip, rows, rows_per_seq);
   unsigned grid = (unsigned)a.n_work;
   if (!hyper) grid = z2z_logits_fast_order(a, c->opt_logits_map);
   c->n_launch[hyper ? Z2Z_KERNEL_TILE_HYPER : Z2Z_KERNEL_TILE_BASE]++;
+  if (a.hyper.n_work > 0) c->n_launch[Z2Z_KERNEL_TILE_HYPER]++;
   if (timed) Z2Z_HIP_TRY(hipEventRecord(c->ev_start[c->n_timed], s));
   // (measurement probes of the base part: see logits_fast_kernel, modes 8 and 9)
   const int plain_base = c->opt_logits_kernel == 2 ? 8 : (c->opt_logits_kernel == 3 ? 9 : 0);
-  const int rc = z2z_launch_logits_fast(prob ? (hyper ? 4 : 3) : (a.sample && !hyper ? (a.sample == 2 ? 7 : 6) : (hyper ? 1 : plain_base)),
-                                        a, grid, s);
+  const int rc = z2z_launch_logits_fast(prob ? 3 : (a.sample && !hyper ? (a.sample == 2 ? 7 : 6) : (hyper ? 1 : plain_base)), a, grid, s);
   if (timed) {
     Z2Z_HIP_TRY(hipEventRecord(c->ev_stop[c->n_timed], s));
     c->n_timed++;
@@ -518,7 +525,9 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     return launch_combine(parts, n_parts, rows, argmax, mx, lse, s);
   }
 
-  int ns = 0;
+  // both parts in one launch of the tile kernel (the measurement probes run the base part alone)
+  const bool one_launch = !mid_base && cap > 0 && !decode_split && !seq_split && c->opt_logits_kernel != 2 && c->opt_logits_kernel != 3;
+  if (one_launch) z2z_add_hyper_part(c, a, W_hyper, base_strips, strip_h, rows_per_seq, 0, c->cfg.B);
   if (mid_base) {
     if (timed) Z2Z_HIP_TRY(hipEventRecord(c->ev_start[c->n_timed], s));
     a.once = decode_split && split_few_once(c, rows);
@@ -528,7 +537,7 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
       c->n_timed++;
     }
   } else {
-    rc = z2z_launch_logits_part(c, false, a, W_base, V, 0, 0, strip_b, rows, rows_per_seq, &ns, timed, s);
+    rc = z2z_launch_logits_part(c, false, a, W_base, V, 0, 0, strip_b, rows, rows_per_seq, timed, s);
   }
   if (rc != Z2Z_OK) return rc;
   if (cap > 0 && (decode_split || seq_split)) {
@@ -536,8 +545,8 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     rc = z2z_launch_logits_decode(c, H, W_base, W_hyper, &np, false, nullptr, nullptr, s, base_strips, &parts,
                                   seq_split ? rows_per_seq : 1, seq_unit);
     if (rc != Z2Z_OK) return rc;
-  } else if (cap > 0) {
-    rc = z2z_launch_logits_part(c, true, a, W_hyper, cap, V, base_strips, strip_h, rows, rows_per_seq, &ns, false, s);
+  } else if (cap > 0 && !one_launch) {
+    rc = z2z_launch_logits_part(c, true, a, W_hyper, cap, V, base_strips, strip_h, rows, rows_per_seq, false, s);
     if (rc != Z2Z_OK) return rc;
   }
   if (timed && mid_base && decode_split) {        // a step's two launches are timed together
@@ -598,13 +607,12 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     a.key1 = (uint32_t)(seed >> 32);
     a.ctr2 = (uint32_t)step;
     a.ctr3 = (uint32_t)(step >> 32);
-    int ns = 0;
     if (timed_pair) Z2Z_HIP_TRY(hipEventRecord(c->ev_start[c->n_timed], s));
     a.once = mid_base && split_few_once(c, rows);
     if (mid_base)
       rc = z2z_launch_logits_mid(c, a, W_base, c->cfg.V, 0, s);
     else
-      rc = z2z_launch_logits_part(c, false, a, W_base, c->cfg.V, 0, 0, strip_b, rows, 1, &ns, timed, s);
+      rc = z2z_launch_logits_part(c, false, a, W_base, c->cfg.V, 0, 0, strip_b, rows, 1, timed, s);
     if (rc != Z2Z_OK) return rc;
     if (c->cfg.cap > 0) {
       int np = 0;
@@ -673,13 +681,12 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     a.inv_temperature = 1.0f / temperature;
     a.logits = c->sample_logits;
     a.ld = c->cfg.V + c->cfg.cap;
-    int ns = 0;
     if (timed_pair) Z2Z_HIP_TRY(hipEventRecord(c->ev_start[c->n_timed], s));
     a.once = mid_base && split_few_once(c, rows);
     if (mid_base)
       rc = z2z_launch_logits_mid(c, a, W_base, c->cfg.V, 0, s);
     else
-      rc = z2z_launch_logits_part(c, false, a, W_base, c->cfg.V, 0, 0, strip_b, rows, 1, &ns, timed, s);
+      rc = z2z_launch_logits_part(c, false, a, W_base, c->cfg.V, 0, 0, strip_b, rows, 1, timed, s);
     if (rc != Z2Z_OK) return rc;
     if (c->cfg.cap > 0) {
       int np = 0;

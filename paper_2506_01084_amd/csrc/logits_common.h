@@ -247,6 +247,13 @@ struct LogitsArgs {
   int32_t batch;            // products with K-major operands in one launch (0, 1: one); the operands' steps in elements
   size_t batch_h, batch_w;
   int32_t once;             // weight-streaming kernel: the weights are read past the caches
+  // the hyper part in the base part's launch (n_work > 0; fields as above, `out` and `ldo` in probability mode)
+  struct {
+    const void* W;
+    const int32_t* size;
+    void* out;
+    int32_t ldo, cap, col0, strip, n_strips, part0, row_tiles, n_work, n_seq;
+  } hyper;
 };
 
 // Weights of up to this many bytes are read through the memory-side cache (256 MB), where the next step finds them; more
@@ -396,7 +403,7 @@ __device__ __forceinline__ void store_partial_tile(const f32x16 (&acc)[NI][NJ], 
 int z2z_logits_general_columns(bool bf16, long long tiles_of_64);
 int z2z_launch_logits_general(bool bf16, int columns, const z2z_logits::LogitsArgs& base, const z2z_logits::LogitsArgs* hyper, hipStream_t s);
 // mode: 0 base part, 1 hyper part (both fold the joint softmax), 2 dense layer (stores the tile),
-// 3 base part, 4 hyper part storing the gradient with respect to the logits, 5 dense layer with K split
+// 3 storing the gradient with respect to the logits, 5 dense layer with K split
 // (fp32 partial tiles)
 int z2z_launch_logits_fast(int mode, const z2z_logits::LogitsArgs& a, unsigned grid, hipStream_t s);
 // mode 2 with W K-major, and H too (rows_too)
@@ -444,9 +451,12 @@ bool z2z_linear_takes_pitch(const z2z_ctx* c, int R, int N, int K);
 int z2z_launch_linear_parts(z2z_ctx* c, const void* A, const void* W, int R, const int32_t* rows_dev, int N, int K,
                             const float** partial, int* ksplit, hipStream_t s, bool once = false);
 int z2z_logits_fast_prepare(z2z_ctx* c);
+// One launch of the bf16 MFMA tile kernel over the base part (hyper = false), over the hyper part of n_seq sequences, or over both
+// (z2z_add_hyper_part first)
 int z2z_launch_logits_part(z2z_ctx* c, bool hyper, z2z_logits::LogitsArgs a, const void* W, int w_rows, int col0,
-                           int part0, int strip, int rows, int rows_per_seq, int* n_strips_out, bool timed,
-                           hipStream_t s, bool prob = false, int seq0 = 0, int n_seq = 0);
+                           int part0, int strip, int rows, int rows_per_seq, bool timed, hipStream_t s, bool prob = false);
+// Fills in a.hyper: sequences [seq0, seq0 + n_seq) with their W_hyper, columns from V on, parts from part0 on.
+void z2z_add_hyper_part(const z2z_ctx* c, z2z_logits::LogitsArgs& a, const void* W_hyper, int part0, int strip, int rows_per_seq, int seq0, int n_seq);
 // temperature sampling (one-row-per-sequence kernel only): softmax(logit / temperature), generator key and
 // counter words from seed and step
 struct z2z_sample_params {

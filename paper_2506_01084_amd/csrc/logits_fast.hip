@@ -186,21 +186,27 @@ __device__ __forceinline__ uint32_t lds_offset_of(const void* p) {
 // serves an operand tile to several XCDs).  The P tiles behind whole blocks of map_lp * map_xp go, with all of Q, in eight
 // equal runs, so that the XCDs' lists differ by a run's rounding.  Lists without holes, in sizes that the device works
 // out itself: the row count may be known there only.
-__device__ __forceinline__ bool locate_base(const LogitsArgs& a, int row_tiles, int xcd, int j, int* rt, int* st) {
+// `more` items of another kind lie behind the P tiles' last and are dealt out with them: *extra is the index of one of those, else -1.
+__device__ __forceinline__ bool locate_base(const LogitsArgs& a, int row_tiles, int xcd, int j, int* rt, int* st, int more = 0, int* extra = nullptr) {
   const int P = a.map_p_rows ? row_tiles : a.n_strips, Q = a.map_p_rows ? a.n_strips : row_tiles;
   const int xpi = xcd % a.map_xp, xqi = xcd / a.map_xp;
   const int blocks = P / (a.map_lp * a.map_xp);                    // whole blocks of each XCD along P
   const int own_q = (Q - xqi + a.map_xq - 1) / a.map_xq;
   const int main_items = blocks * a.map_lp * own_q;
   int pi, qi;
+  if (extra) *extra = -1;
   if (j < main_items) {
     const int w = j / a.map_lp, blk = w / own_q;
     pi = (blk * a.map_xp + xpi) * a.map_lp + (j - w * a.map_lp);
     qi = (w - blk * own_q) * a.map_xq + xqi;
   } else {
-    const int p0 = blocks * a.map_lp * a.map_xp, T = P - p0, total = T * Q;
+    const int p0 = blocks * a.map_lp * a.map_xp, T = P - p0, total = T * Q + more;
     const int t = j - main_items + (int)((long long)total * xcd / 8);
     if (t >= (int)((long long)total * (xcd + 1) / 8)) return false;
+    if (extra) {
+      *extra = t < T * Q ? -1 : t - T * Q;
+      if (t >= T * Q) return true;
+    }
     qi = t / T;
     pi = p0 + (t - qi * T);
   }
@@ -617,8 +623,8 @@ __device__ __forceinline__ void store_partial16(const Acc& acc, float* part, int
 
 // Store one finished tile as the gradient of the loss with respect to the logits (see LogitsArgs, probability mode).
 // Columns come in fours; ldo is a multiple of 64.
-__device__ __forceinline__ void store_prob16(const Acc& acc, const LogitsArgs& a, int row_base, int r_end, int col_base,
-                                             int n_valid) {
+__device__ __forceinline__ void store_prob16(const Acc& acc, const LogitsArgs& a, void* out, int ldo, int col0, int row_base, int r_end,
+                                             int col_base, int n_valid) {
   const int lane15 = threadIdx.x & 15;
   float lse[F_N], g[F_N];
   int tgt[F_N];
@@ -628,12 +634,12 @@ __device__ __forceinline__ void store_prob16(const Acc& acc, const LogitsArgs& a
     const bool ok = row < r_end;
     lse[j] = ok ? a.lse[row] : 0.f;
     g[j] = ok ? a.row_grad[row] : 0.f;
-    tgt[j] = ok ? a.targets[row] - a.col0 : -1;
+    tgt[j] = ok ? a.targets[row] - col0 : -1;
   }
 #pragma unroll
   for (int j = 0; j < F_N; ++j) {
     const int row = row_base + j * 16 + lane15;
-    uint16_t* out_row = reinterpret_cast<uint16_t*>(a.out) + (size_t)row * a.ldo;
+    uint16_t* out_row = reinterpret_cast<uint16_t*>(out) + (size_t)row * ldo;
     uint2 o[F_N];
 #pragma unroll
     for (int i = 0; i < F_N; ++i) {
@@ -648,7 +654,7 @@ __device__ __forceinline__ void store_prob16(const Acc& acc, const LogitsArgs& a
       o[i] = uint2{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3])};
     }
 #pragma unroll
-    for (int i = 0; i < F_N; i += 2) store_two_blocks(out_row, row < r_end, col_base, i, o[i], o[i + 1], a.ldo);
+    for (int i = 0; i < F_N; i += 2) store_two_blocks(out_row, row < r_end, col_base, i, o[i], o[i + 1], ldo);
   }
 }
 
@@ -703,15 +709,19 @@ __device__ __forceinline__ void merge_rows(R (&a)[F_N], S swap) {
 // operand stream runs on from one output tile to the next, and a tile's epilogue finds the next one's first two slabs on the
 // way.  With a workgroup per tile instead, a launch and the first slabs' round trip stood before every tile and a
 // store queue behind it: a training step of 8 x 4096 tokens (kernels only) 172.8 -> 168.9 ms, of it the order below 2.5.
-// The hyper parts and K-split layers (modes 1, 4, 5) have a workgroup per item: what exists of them is known on the device.
+// The hyper part alone and K-split layers (modes 1, 5) have a workgroup per item: what exists of them is known on the device.
 // TW, TH (mode 2): the operand of that side is K-major, W [k_rows, ldw] and H [k_rows, ldh]; there may be a batch of such products,
 // of a.rows output rows each, one below the other.
-template <int MODE, bool ROT = false, bool TW = false, bool TH = false>
+// HYP (modes 0 and 3): the items of the per-sequence hyper part (a.hyper) that exist are dealt out with the base part's last tiles.  In a launch
+// of its own that part is one or two rounds of tiles on a few CUs (58 us at d = 3072): V = 32064, 8 x 86 rows 190 -> 146 us, 17 x 75 257 -> 204;
+// V = 128256, d = 4096, 3 x 176 654 -> 597, 2 x 577 1090 -> 1043; level from 5000 rows on (3 x 3577 7818 and 7826).
+template <int MODE, bool ROT = false, bool TW = false, bool TH = false, bool HYP = false>
 __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
   static_assert(MODE == 2 || (!TW && !TH), "dense layers only");
+  static_assert(!HYP || ((MODE == 0 || MODE == 3) && !ROT), "");
   constexpr bool PROBE_NOREQ = MODE == 8 || MODE == 9;
   constexpr bool PROBE_MFMA = MODE == 9;
-  constexpr bool LIST = MODE != 1 && MODE != 4 && MODE != 5;
+  constexpr bool LIST = MODE != 1 && MODE != 5;
   extern __shared__ __align__(1024) unsigned char lds[];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -731,8 +741,8 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
   if ((MODE == 2 || MODE == 5) && a.rows_dev) r_end = min(r_end, __builtin_amdgcn_readfirstlane(*a.rows_dev));
   const int tiles_each = (r_end + FT - 1) / FT, row_tiles_now = TW && a.batch > 1 ? a.batch * tiles_each : tiles_each;
   int n_valid = a.w_rows;
-  int one_rt = 0, one_st = 0, one_r0 = 0, ks = 0;    // modes 1, 4, 5: the one item
-  if (MODE == 1 || MODE == 4) {
+  int one_rt = 0, one_st = 0, one_r0 = 0, ks = 0;    // modes 1, 5: the one item
+  if (MODE == 1) {
     if ((int)blockIdx.x >= a.n_work) return;
     one_rt = blockIdx.x / a.n_strips;
     // workgroup ids go round-robin over the 8 XCDs, and the strips beyond a sequence's C_b are empty: with the
@@ -766,8 +776,20 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
 
   struct Item {
     int r0, st, s0, sn, part;    // first row, strip, slabs, buffer
-    int b;                       // product of a batch
+    int b;                       // product of a batch; sequence of an item of the hyper part, else (HYP) -1
   };
+  // (the hyper part: strips of sequence b, and the items of all)
+  auto hyper_strips = [&](int b) -> int {
+    const int n = min(max(__builtin_amdgcn_readfirstlane(a.hyper.size[b]), 0), a.hyper.cap);
+    return (n + FT * a.hyper.strip - 1) / (FT * a.hyper.strip);
+  };
+  int hyper_items = 0;
+  if (HYP)
+    for (int b = 0; b < a.hyper.n_seq; ++b) hyper_items += hyper_strips(b) * a.hyper.row_tiles;
+  // (where all strips are one tile the base part's last ones and the hyper items are dealt out as one; else every XCD goes on with every eighth
+  // of these behind its base list: the longer strips of the base part have to be dealt out evenly by themselves, 9 x 263 rows 1930 us, 2155 as one)
+  const bool together = HYP && a.strip == 1 && a.hyper.strip == 1;
+  const int base_items = HYP && !together ? list_length(a, row_tiles_now, (int)(blockIdx.x & 7)) : 0;
   auto item = [&](int j, Item* it) -> bool {
     it->s0 = 0;
     it->sn = n_slabs;
@@ -790,8 +812,23 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
     }
     if (MODE == 2 && last.ways > 1 && last.whole)
       locate_whole(a, row_tiles_now, j, &rt, &it->st);
-    else if (!locate_base(a, row_tiles_now, xcd, j, &rt, &it->st))
-      return false;
+    else if (!locate_base(a, row_tiles_now, xcd, j, &rt, &it->st, HYP && together ? hyper_items : 0, HYP ? &it->b : nullptr)) {
+      if (!HYP || together) return false;
+      it->b = (j - base_items) * 8 + xcd;
+      if (it->b >= hyper_items) return false;
+    }
+    if (HYP && it->b >= 0) {
+      int k = it->b, b = 0, n = hyper_strips(0);
+      while (k >= n * a.hyper.row_tiles) {
+        k -= n * a.hyper.row_tiles;
+        n = hyper_strips(++b);
+      }
+      rt = __builtin_amdgcn_readfirstlane(k / n);
+      it->st = k - rt * n;
+      it->b = b;
+      it->r0 = b * a.rows_per_seq + rt * FT;
+      return true;
+    }
     it->r0 = rt * FT;
     if (TW && a.batch > 1) {
       it->b = __builtin_amdgcn_readfirstlane(rt / tiles_each);
@@ -802,6 +839,20 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
       it->st = __builtin_amdgcn_readfirstlane(it->st);
     }
     return true;
+  };
+
+  // what an item's tiles are cut from
+  struct Part {
+    const unsigned char* W;
+    int n_valid, n_vt, r_end, strip;
+  };
+  auto part_of = [&](const Item& it) -> Part {
+    if (HYP && it.b >= 0) {
+      const int n = min(max(__builtin_amdgcn_readfirstlane(a.hyper.size[it.b]), 0), a.hyper.cap);
+      return Part{reinterpret_cast<const unsigned char*>(a.hyper.W) + (size_t)it.b * a.hyper.cap * row_bytes, n, (n + FT - 1) / FT,
+                  (it.b + 1) * a.rows_per_seq, a.hyper.strip};
+    }
+    return Part{TW ? Wp + (size_t)it.b * a.batch_w * 2 : Wp, n_valid, n_vt, TW && a.batch > 1 ? (it.b + 1) * a.rows : r_end, a.strip};
   };
 
   // ---- loader: lane l of wave w, instruction i moves the chunk that lands at LDS byte
@@ -824,7 +875,8 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
     return (uint32_t)(k * (int)pitch + min(chunk, chunks - 1) * 16);
   };
   uint32_t voffA[F_PAIRS], voffB[F_PAIRS];
-  const unsigned char *Wtile = Wp, *Wb = Wp;
+  const unsigned char* Wtile = Wp;
+  Part at = {Wp, 0, 0, 0, 1};
   const unsigned char* Hp = Hm;
   // ---- the cursor of the operand stream: slab lslab of weight tile lvt of the item at position lj (none: !live) ----------
   int lj = first, lslab = 0, lslab_end = n_slabs, lvt = 0, lvt_end = 0, rot = 0;
@@ -832,30 +884,31 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
   bool live = true;
   auto set_tile = [&](int vt) {
     if (TW) w_col = vt * F_KROW;
-    Wtile = TW ? Wb + w_col : Wp + (size_t)vt * FT * pitch_w;
+    Wtile = at.W + (TW ? (size_t)w_col : (size_t)vt * FT * pitch_w);
 #pragma unroll
     for (int i = 0; i < F_PAIRS; ++i)
-      voffA[i] = TW ? krow_offset(i, ((int)pitch_w - w_col) >> 4, pitch_w) : row_offset(i, n_valid - 1 - vt * FT, pitch_w);
+      voffA[i] = TW ? krow_offset(i, ((int)pitch_w - w_col) >> 4, pitch_w) : row_offset(i, at.n_valid - 1 - vt * FT, pitch_w);
   };
   auto open_item = [&]() {
+    if (HYP) asm volatile("" : "+s"(lj));       // (what is worked out here is not worked out for every slab)
     Item it;
     live = item(lj, &it);
     if (!live) return;
+    at = part_of(it);
+    lvt = it.st * at.strip;
+    lvt_end = min(lvt + at.strip, at.n_vt);
     const int r0 = it.r0, st = it.st;
     lslab = it.s0;
     lslab_end = it.s0 + it.sn;
-    lvt = st * a.strip;
-    lvt_end = min(lvt + a.strip, n_vt);
     live = lvt < lvt_end;
     if (!live) return;
     if (TH) h_col = (r0 - it.b * a.rows) * 2;
     Hp = Hm + (TH ? (size_t)h_col : (size_t)r0 * pitch_h);
     if (TH) Hp += (size_t)it.b * a.batch_h * 2;
-    if (TW) Wb = Wp + (size_t)it.b * a.batch_w * 2;
 #pragma unroll
     for (int i = 0; i < F_PAIRS; ++i)
       voffB[i] = TH ? krow_offset(i, ((int)pitch_h - h_col) >> 4, pitch_h)
-                    : row_offset(i, (TW && a.batch > 1 ? (it.b + 1) * a.rows : r_end) - 1 - r0, pitch_h);
+                    : row_offset(i, at.r_end - 1 - r0, pitch_h);
     if (ROT) rot = st % n_slabs;
     set_tile(lvt);
   };
@@ -1001,6 +1054,19 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
     ++g;
   };
 
+  if (HYP && MODE == 0) {
+    // strips of the hyper part that do not exist leave empty triples (ahead of the loop: divergent code in it, and the compiler keeps
+    // the loop's state in vector registers)
+    for (int h = blockIdx.x; h < a.hyper.n_work; h += gridDim.x) {
+      const int rt = h / a.hyper.n_strips, st = h % a.hyper.n_strips, b = rt / a.hyper.row_tiles;
+      const int row = b * a.rows_per_seq + (rt % a.hyper.row_tiles) * FT + tid;
+      if (st * a.hyper.strip * FT < a.hyper.size[b] || row >= (b + 1) * a.rows_per_seq) continue;
+      const size_t q = (size_t)row * a.n_parts + a.hyper.part0 + st;
+      a.part_m[q] = kNegInf;
+      a.part_s[q] = 0.f;
+      a.part_i[q] = kNoColumn;
+    }
+  }
   open_item();
   if (live) {
     // prologue: the first two slabs of the stream requested; the first landed and visible, the fragments of its first
@@ -1021,7 +1087,10 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
   Item it;
   for (int j = first; item(j, &it); j += step) {
     const int r0 = it.r0, st = it.st;
-    if (TW && a.batch > 1) r_end = (it.b + 1) * a.rows;
+    const Part p = part_of(it);
+    const bool hyper = HYP && it.b >= 0;
+    const int r_end = p.r_end, n_valid = p.n_valid;
+    const int vt0 = st * p.strip, vt_end = min(vt0 + p.strip, p.n_vt);      // (hyper part: possibly no tile)
     Triple run[F_N];
     Draw draw[F_N];                                  // MODE 6 only
 #pragma unroll
@@ -1029,7 +1098,6 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
       run[i] = empty_triple();
       draw[i] = empty_draw();
     }
-    const int vt0 = st * a.strip, vt_end = min(vt0 + a.strip, n_vt);      // (modes 1, 4: possibly no tile)
     for (int vt = vt0; vt < vt_end; ++vt) {
       slab_step(std::true_type{});
       for (int slab = 1; slab < it.sn; ++slab) slab_step(std::false_type{});
@@ -1049,15 +1117,16 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
           store_tile16(acc, a, row_base, r_end, col_base, n_valid);
       } else if (MODE == 5) {
         store_partial16(acc, a.partial + (size_t)ks * a.rows * a.ldo, a.ldo, row_base, r_end, col_base, n_valid);
-      } else if (MODE == 3 || MODE == 4) {
-        store_prob16(acc, a, row_base, r_end, col_base, n_valid);
+      } else if (MODE == 3) {
+        store_prob16(acc, a, hyper ? a.hyper.out : a.out, hyper ? a.hyper.ldo : a.ldo, hyper ? a.hyper.col0 : a.col0, row_base, r_end, col_base,
+                     n_valid);
       } else if (MODE == 6) {
         fold_sample16(acc, run, draw, a, row_base, col_base, n_valid);
       } else if (MODE == 7) {
         fold_store16(acc, run, a, row_base, r_end, col_base, n_valid);
       } else {
         if ((vt + 1) * FT > n_valid) mask_tail16(acc, col_base, n_valid);
-        fold_tile16(acc, run, col_base, a.col0, n_valid);
+        fold_tile16(acc, run, col_base, hyper ? a.hyper.col0 : a.col0, n_valid);
       }
     }
     if (MODE >= 2 && MODE <= 5) continue;
@@ -1090,16 +1159,16 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
         merge_triple(run[e], xch[hrow0 + e * 16]);
         const int hrow = r0 + hrow0 + e * 16;
         if (hrow < r_end) {
-          const size_t p = (size_t)hrow * a.n_parts + a.part0 + st;
-          a.part_m[p] = run[e].m;
-          a.part_s[p] = run[e].s;
+          const size_t q = (size_t)hrow * a.n_parts + (hyper ? a.hyper.part0 : a.part0) + st;
+          a.part_m[q] = run[e].m;
+          a.part_s[q] = run[e].s;
           if (MODE == 6) {
             merge_draw(draw[e], xdr[hrow0 + e * 16]);
-            a.part_v[p] = draw[e].v;
-            a.part_l[p] = draw[e].l;
-            a.part_i[p] = draw[e].i;
+            a.part_v[q] = draw[e].v;
+            a.part_l[q] = draw[e].l;
+            a.part_i[q] = draw[e].i;
           } else {
-            a.part_i[p] = run[e].i;
+            a.part_i[q] = run[e].i;
           }
         }
       }
@@ -1207,7 +1276,7 @@ unsigned z2z_logits_fast_order(LogitsArgs& a, int forced) {
   const int P = a.map_p_rows ? a.row_tiles : a.n_strips;
   const long long main_items = (long long)(P / (a.map_lp * a.map_xp)) * a.map_lp * ((q + a.map_xq - 1) / a.map_xq);
   const long long tail = (long long)(P % (a.map_lp * a.map_xp)) * q;
-  const long long longest = main_items + (tail + 7) / 8;
+  const long long longest = main_items + (tail + 7) / 8 + (a.hyper.n_work + 7) / 8;
   return 8u * (unsigned)(longest < 32 ? longest : 32);
 }
 
@@ -1222,6 +1291,16 @@ int z2z_launch_linear_kmajor(const LogitsArgs& a, bool rows_too, unsigned grid, 
 
 int z2z_launch_logits_fast(int mode, const LogitsArgs& a, unsigned grid, hipStream_t s) {
   const bool rot = a.row_tiles == 1;
+  if (a.hyper.n_work > 0) {
+    if (mode == 3)
+      hipLaunchKernelGGL((logits_fast_kernel<3, false, false, false, true>), dim3(grid), dim3(F_THREADS), F_LDS, s, a);
+    else if (mode != 0)
+      return Z2Z_EUNSUPPORTED;
+    else
+      hipLaunchKernelGGL((logits_fast_kernel<0, false, false, false, true>), dim3(grid), dim3(F_THREADS), F_LDS, s, a);
+    Z2Z_HIP_TRY(hipGetLastError());
+    return Z2Z_OK;
+  }
   if (rot && mode == 0)
     hipLaunchKernelGGL((logits_fast_kernel<0, true>), dim3(grid), dim3(F_THREADS), F_LDS, s, a);
   else if (rot && mode == 6)
@@ -1238,8 +1317,6 @@ int z2z_launch_logits_fast(int mode, const LogitsArgs& a, unsigned grid, hipStre
     hipLaunchKernelGGL(logits_fast_kernel<6>, dim3(grid), dim3(F_THREADS), F_LDS, s, a);
   else if (mode == 5)
     hipLaunchKernelGGL(logits_fast_kernel<5>, dim3(grid), dim3(F_THREADS), F_LDS, s, a);
-  else if (mode == 4)
-    hipLaunchKernelGGL(logits_fast_kernel<4>, dim3(grid), dim3(F_THREADS), F_LDS, s, a);
   else if (mode == 3)
     hipLaunchKernelGGL(logits_fast_kernel<3>, dim3(grid), dim3(F_THREADS), F_LDS, s, a);
   else if (mode == 2)
@@ -1268,7 +1345,9 @@ int z2z_logits_fast_prepare(z2z_ctx* c) {
                                   hipFuncAttributeMaxDynamicSharedMemorySize, F_LDS));
   Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(logits_fast_kernel<3>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, F_LDS));
-  Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(logits_fast_kernel<4>),
+  Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(logits_fast_kernel<0, false, false, false, true>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, F_LDS));
+  Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(logits_fast_kernel<3, false, false, false, true>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, F_LDS));
   Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(logits_fast_kernel<5>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, F_LDS));

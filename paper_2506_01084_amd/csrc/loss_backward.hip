@@ -141,21 +141,18 @@ int z2z_launch_extended_nll_backward(z2z_ctx* c, const void* H, int32_t rows, in
     a.lse = lse + r0;
     a.row_grad = g;
     a.targets = targets + r0;
-    int ns = 0;
     a.out = Pb;
     a.ldo = (int)Vp;
-    rc = z2z_launch_logits_part(c, false, a, W_base, V, 0, 0, strip, rows_c, rows_per_seq, &ns, false, s, true);
-    if (rc != Z2Z_OK) return rc;
     if (cap > 0) {
       const size_t n16 = (size_t)rows_c * capp * 2 / 16;
       hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)std::min<size_t>((n16 + 255) / 256, 4096)), dim3(256), 0, s,
                          reinterpret_cast<uint4*>(Ph), n16);
-      a.out = Ph;
-      a.ldo = (int)capp;
-      rc = z2z_launch_logits_part(c, true, a, Whc, cap, V, 0, strip, rows_c, rows_per_seq, &ns, false, s, true, b0,
-                                  nb);
-      if (rc != Z2Z_OK) return rc;
+      z2z_add_hyper_part(c, a, Whc, 0, strip, rows_per_seq, b0, nb);
+      a.hyper.out = Ph;
+      a.hyper.ldo = (int)capp;
     }
+    rc = z2z_launch_logits_part(c, false, a, W_base, V, 0, 0, strip, rows_c, rows_per_seq, false, s, true);
+    if (rc != Z2Z_OK) return rc;
     // ---- the products ------------------------------------------------------------------------------------------
     uint16_t* dHc = reinterpret_cast<uint16_t*>(dH) + (size_t)r0 * d;
     rc = z2z_launch_linear_input(c, Pb, (int)Vp, W_base, d, V, nullptr, dHc, d, rows_c, nullptr, d, (int)Vp, s);
