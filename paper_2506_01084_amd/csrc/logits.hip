@@ -653,7 +653,7 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
       return Z2Z_ENOMEM;
     c->sample_logits_capacity = need;
   }
-  int base_columns = 0;                              // of a base part: the decode kernel's unit unless set
+  int base_columns = 0, hyper_columns = 0;           // of a part: the decode kernel's units unless set
   if ((rows > 64 || mid_base) && c->cfg.d % 64 == 0 && c->fast_ready && c->opt_logits_kernel != 1) {
     // more than one pass of the decode kernel's base units, or a split step: the tile or the streaming kernel stores and folds the base
     // vocabulary's scaled logits, the hyper units run alone (strips of at most 2 tiles: the selection kernels'
@@ -663,9 +663,15 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     if (strip_b > 2) strip_b = 2;
     const int mid_columns = z2z_logits_mid_columns(c, c->cfg.V);
     const int base_strips = mid_base ? (c->cfg.V + mid_columns - 1) / mid_columns : (base_vt + strip_b - 1) / strip_b;
-    int unit_base, unit_hyper;
-    z2z_logits_decode_units(&unit_base, &unit_hyper);
-    n_parts = base_strips + (c->cfg.cap + unit_hyper - 1) / unit_hyper;
+    // (hyper units of 512 rows are too few for a small batch: smaller ones, while the short-list pass takes as many parts.  21 sequences of up to
+    // 4096 entries, V = 32064 121 -> 84 us, 20 x 1024, V = 128256 271 -> 213, 6 x 4096, V = 151936 291 -> 250.  From 200 of 512 rows on those
+    // are the better ones here: a unit's logits leave it row by row, 108 x 1024 356 us, 361 in 432 of 256; 56 x 2048 341 and 348, 32 x 4096 338
+    // and 349.  Below that, room for more than 2048 entries is seldom full and the units that exist are few of them: 21 x 730 of 4096 96 us in 336
+    // units, 84 in 672)
+    const bool roomy = c->cfg.cap > 2048 && (long long)rows * ((c->cfg.cap + 511) / 512) < 200;
+    hyper_columns = z2z_logits_decode_hyper_unit(c, roomy ? 512 : 200);
+    while (hyper_columns < 512 && base_strips + (c->cfg.cap + hyper_columns - 1) / hyper_columns > z2z_sample_list_parts()) hyper_columns *= 2;
+    n_parts = base_strips + (c->cfg.cap + hyper_columns - 1) / hyper_columns;
     base_columns = mid_base ? mid_columns : strip_b * 256;
     LogitsArgs a;
     memset(&a, 0, sizeof(a));
@@ -690,7 +696,7 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     if (rc != Z2Z_OK) return rc;
     if (c->cfg.cap > 0) {
       int np = 0;
-      rc = z2z_launch_logits_decode(c, H, W_base, W_hyper, &np, false, &sp, c->sample_logits, s, base_strips);
+      rc = z2z_launch_logits_decode(c, H, W_base, W_hyper, &np, false, &sp, c->sample_logits, s, base_strips, nullptr, 1, hyper_columns);
       if (rc != Z2Z_OK) return rc;
     }
     if (timed_pair) Z2Z_HIP_TRY(hipEventRecord(c->ev_stop[c->n_timed++], s));
@@ -698,12 +704,12 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     rc = z2z_launch_logits_decode(c, H, W_base, W_hyper, &n_parts, timed, &sp, c->sample_logits, s);
     if (rc != Z2Z_OK) return rc;
   }
-  if (!z2z_sample_truncated_merges_parts(c, n_parts, top_k, base_columns)) {
+  if (!z2z_sample_truncated_merges_parts(c, n_parts, top_k, base_columns, hyper_columns)) {
     rc = launch_combine(ctx_parts(c), n_parts, rows, nullptr, c->row_max, c->row_max + rows, s);
     if (rc != Z2Z_OK) return rc;
   }
   return z2z_launch_sample_truncated(c, c->sample_logits, c->row_max, rows, n_parts, c->row_max + 2 * (size_t)rows, &sp,
-                                     top_k, top_p, token, logprob, s, base_columns);
+                                     top_k, top_p, token, logprob, s, base_columns, hyper_columns);
 }
 
 int z2z_launch_extended_nll(z2z_ctx* c, const void* H, int32_t rows, int32_t rows_per_seq, const void* W_base,

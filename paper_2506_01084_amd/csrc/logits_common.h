@@ -471,7 +471,8 @@ int z2z_launch_logits_decode(z2z_ctx* c, const void* H, const void* W_base, cons
                              int hyper_only_base_parts = -1, const z2z_parts* parts = nullptr, int rows_per_seq = 1,
                              int seq_unit = 512);
 // (hyper_only_base_parts >= 0, one row per sequence: seq_unit weight rows per hyper unit, z2z_logits_decode_hyper_unit)
-int z2z_logits_decode_hyper_unit(const z2z_ctx* c);
+// (units halve until there are `enough`)
+int z2z_logits_decode_hyper_unit(const z2z_ctx* c, int enough = 512);
 // rows_per_seq in 2..64 (with hyper_only_base_parts >= 0): the hyper part alone, one workgroup per sequence and
 // seq_unit (64, 128 or 256) rows of its W_hyper; parts per row then: base parts + ceil(cap / seq_unit)
 int z2z_logits_decode_seq_unit(const z2z_ctx* c);
@@ -479,10 +480,11 @@ int z2z_logits_decode_seq_unit(const z2z_ctx* c);
 // log-sum-exps, of those values; `work` is scratch of z2z_sample_truncated_work_floats(rows) floats.
 // z2z_sample_truncated_merges_parts: true when the selection's first kernel merges the parts into `row_stat` itself
 // (the caller then launches no merge); otherwise `row_stat` must hold them when the call is made.
-bool z2z_sample_truncated_merges_parts(const z2z_ctx* c, int n_parts, int32_t top_k, int base_columns);
+bool z2z_sample_truncated_merges_parts(const z2z_ctx* c, int n_parts, int32_t top_k, int base_columns, int hyper_columns);
+int z2z_sample_list_parts();   // most parts per row that the short-list pass takes
 int z2z_launch_sample_truncated(z2z_ctx* c, const float* logits, float* row_stat, int32_t rows, int n_parts,
                                 float* work, const z2z_sample_params* sp, int32_t top_k, float top_p,
-                                int32_t* token, float* logprob, hipStream_t s, int base_columns = 0);
+                                int32_t* token, float* logprob, hipStream_t s, int base_columns, int hyper_columns);
 size_t z2z_sample_truncated_work_floats(int32_t rows);
 // the same layer on the bandwidth-bound kernel of the decode step (few rows: every weight byte is read once per
 // 64 rows); K a multiple of 128, N even

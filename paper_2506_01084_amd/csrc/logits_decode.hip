@@ -954,9 +954,9 @@ int z2z_logits_decode_seq_unit(const z2z_ctx* c) {
 }
 
 // The same for one hidden row per sequence where the hyper units run alone, two workgroups per CU.
-int z2z_logits_decode_hyper_unit(const z2z_ctx* c) {
+int z2z_logits_decode_hyper_unit(const z2z_ctx* c, int enough) {
   int unit = D_UNIT;
-  while (unit > 64 && (long long)c->cfg.B * ((c->cfg.cap + unit - 1) / unit) < 512) unit >>= 1;
+  while (unit > 64 && (long long)c->cfg.B * ((c->cfg.cap + unit - 1) / unit) < enough) unit >>= 1;
   return unit;
 }
 

@@ -664,7 +664,7 @@ __device__ __forceinline__ void truncated_row(const TruncArgs& a, const float* p
 }
 
 // The short way, for a prefix of at most a few hundred columns.  The decode kernel left the largest value of
-// every part of the row (256 base columns, 512 hyper columns).  Let L be the j-th largest of them: j different
+// every part of the row (256 base columns, up to 512 hyper columns).  Let L be the j-th largest of them: j different
 // columns reach L, so the j-th element of the order is >= L, and every element >= L lies in a part whose
 // largest value is >= L.  Only those parts are read again, their elements >= L collected, and the sorted list
 // is then a prefix of the row's order that is at least j long: a top-k cut with k <= j, or a nucleus that
@@ -920,20 +920,23 @@ __global__ void __launch_bounds__(T_THREADS) sample_list_then_row_kernel(TruncAr
 
 // Whether the selection starts with the short-list kernel (which then also merges the row's parts into the row
 // maxima and log-sum-exps: the caller launches no merge of its own).
-static bool list_first_for(const z2z_ctx* c, int n_parts, int32_t top_k, int base_columns) {
+static bool list_first_for(const z2z_ctx* c, int n_parts, int32_t top_k, int base_columns, int hyper_columns) {
   int unit_base, unit_hyper;
   z2z_logits_decode_units(&unit_base, &unit_hyper);
   if (base_columns > 0) unit_base = base_columns;
+  if (hyper_columns > 0) unit_hyper = hyper_columns;
   return c->opt_sample_kernel != 1 && n_parts <= L_PARTS && top_k <= L_DEPTH && unit_base <= 512 && unit_hyper <= 512;
 }
 
-bool z2z_sample_truncated_merges_parts(const z2z_ctx* c, int n_parts, int32_t top_k, int base_columns) {
-  return list_first_for(c, n_parts, top_k, base_columns);
+bool z2z_sample_truncated_merges_parts(const z2z_ctx* c, int n_parts, int32_t top_k, int base_columns, int hyper_columns) {
+  return list_first_for(c, n_parts, top_k, base_columns, hyper_columns);
 }
+
+int z2z_sample_list_parts() { return L_PARTS; }
 
 int z2z_launch_sample_truncated(z2z_ctx* c, const float* logits, float* row_stat, int32_t rows, int n_parts,
                                 float* work, const z2z_sample_params* sp, int32_t top_k, float top_p,
-                                int32_t* token, float* logprob, hipStream_t s, int base_columns) {
+                                int32_t* token, float* logprob, hipStream_t s, int base_columns, int hyper_columns) {
   (void)sp->temperature;                             // the stored values are scaled already
   TruncArgs a;
   memset(&a, 0, sizeof(a));
@@ -947,6 +950,7 @@ int z2z_launch_sample_truncated(z2z_ctx* c, const float* logits, float* row_stat
   a.n_parts = n_parts;
   z2z_logits_decode_units(&a.base_columns, &a.hyper_columns);
   if (base_columns > 0) a.base_columns = base_columns;   // the base parts came from another kernel's strips
+  if (hyper_columns > 0) a.hyper_columns = hyper_columns;
   a.n_base_parts = (c->cfg.V + a.base_columns - 1) / a.base_columns;
   a.V = c->cfg.V;
   a.cap = c->cfg.cap;
@@ -964,7 +968,7 @@ int z2z_launch_sample_truncated(z2z_ctx* c, const float* logits, float* row_stat
   a.list_depth = 0;
   float* partial = work + rows;                      // work: [rows] redo flags, then the first pass's bin totals
   // a short prefix first: rows it cannot settle are flagged, and only those take the passes over the whole row
-  const bool list_first = list_first_for(c, n_parts, top_k, base_columns);
+  const bool list_first = list_first_for(c, n_parts, top_k, base_columns, hyper_columns);
   if (list_first) {
     a.redo = reinterpret_cast<int32_t*>(work);
     a.list_depth = top_k > 0 ? top_k : L_DEPTH;
