@@ -474,8 +474,11 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     }
   }
   const int mid_columns = z2z_logits_mid_columns(c, V);
+  // the streaming kernel takes the hyper part of longer runs of rows along (up to 64 rows a sequence it has units of its own)
+  const bool mid_both = mid_base && cap > 0 && rows_per_seq > 64 &&
+                        (size_t)((V + mid_columns - 1) / mid_columns + (cap + mid_columns - 1) / mid_columns) * rows <= Z2Z_STATIC_PARTS;
   const int base_strips = mid_base ? (V + mid_columns - 1) / mid_columns : (base_vt + strip_b - 1) / strip_b;
-  int hyp_strips = cap > 0 ? (hyp_vt + strip_h - 1) / strip_h : 0;
+  int hyp_strips = mid_both ? (cap + mid_columns - 1) / mid_columns : cap > 0 ? (hyp_vt + strip_h - 1) / strip_h : 0;
   int seq_unit = 0;
   if (decode_split || seq_split) {
     seq_unit = seq_split ? z2z_logits_decode_seq_unit(c) : z2z_logits_decode_hyper_unit(c);
@@ -528,6 +531,10 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
   // both parts in one launch of the tile kernel (the measurement probes run the base part alone)
   const bool one_launch = !mid_base && cap > 0 && !decode_split && !seq_split && c->opt_logits_kernel != 2 && c->opt_logits_kernel != 3;
   if (one_launch) z2z_add_hyper_part(c, a, W_hyper, base_strips, strip_h, rows_per_seq, 0, c->cfg.B);
+  if (mid_both) {
+    z2z_add_hyper_part(c, a, W_hyper, base_strips, 1, rows_per_seq, 0, c->cfg.B);
+    a.hyper.n_work = c->cfg.B * hyp_strips;
+  }
   if (mid_base) {
     if (timed) Z2Z_HIP_TRY(hipEventRecord(c->ev_start[c->n_timed], s));
     a.once = decode_split && split_few_once(c, rows);
@@ -545,7 +552,7 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     rc = z2z_launch_logits_decode(c, H, W_base, W_hyper, &np, false, nullptr, nullptr, s, base_strips, &parts,
                                   seq_split ? rows_per_seq : 1, seq_unit);
     if (rc != Z2Z_OK) return rc;
-  } else if (cap > 0 && !one_launch) {
+  } else if (cap > 0 && !one_launch && !mid_both) {
     rc = z2z_launch_logits_part(c, true, a, W_hyper, cap, V, base_strips, strip_h, rows, rows_per_seq, false, s);
     if (rc != Z2Z_OK) return rc;
   }

@@ -38,6 +38,7 @@ constexpr int M_WAVES = 8;                // of a workgroup; four where tiles of
 constexpr int M_WT = 32 * M_WAVES;        // weight rows of a workgroup's tile
 constexpr int M_HT = 192;                 // hidden rows of a call at most (the builds below: 2, 4 or 6 blocks of 32)
 constexpr int M_MAX_ROWS = M_HT;
+static_assert(M_HT <= 64 * M_WAVES / 2, "a thread per row");
 constexpr int M_SLAB = 128;               // bytes per row per K slab (64 bf16)
 // LDS per build (blocks of 32 hidden rows, waves): stages of a slab's hidden rows, and slots of the waves' rings.  Four waves
 // have the CU to themselves and ask for both up to five slabs ahead.
@@ -85,8 +86,15 @@ __device__ __forceinline__ uint32_t lds_offset_of(const void* p) {
 // (a.sample = 2) -- the tile kernel's epilogues for its modes 0, 6 and 7; 3 = a dense layer with K split over
 // gridDim.y workgroups per tile: the fp32 partial tile goes to a.partial[ks][row][col] (the tile kernel's mode 5);
 // 4, 5, 6 = 0, 1, 2 with the sums in levels, for a step of up to 64 sequences.
+// What a workgroup's tile is cut from: weight tile vt of W (n_valid rows), all `rows` hidden rows at H, which are rows row0 ... of the call; its
+// columns start at col0, its part is `part`.
+struct MidTile {
+  const void *W, *H;
+  int vt, n_valid, rows, row0, col0, part;
+};
+
 template <int NJV, int SMODE, int WAVES>
-__device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds) {
+__device__ __forceinline__ void mid_tile(const LogitsArgs& a, const MidTile& t, unsigned char* lds) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -94,13 +102,13 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
   constexpr int STAGES = mid_stages(NJV, WAVES), RING = mid_ring(NJV, WAVES), TILE = 32 * WAVES;
   constexpr int STAGE = 32 * NJV * M_SLAB, STAGE_BYTES = STAGES * STAGE;
   constexpr int W_SLAB = 32 * M_SLAB;                      // a wave's weights of one slab
-  const int vt = blockIdx.x;                               // weight tile (and one row tile: a call has at most M_HT rows)
+  const int vt = t.vt;                                     // weight tile (and one row tile: a call has at most M_HT rows)
   // SMODE 3 (a dense layer's partial sums): the rows that exist may be known on the device only, and blockIdx.y is
   // the part of K this workgroup takes (slabs [ks * slabs_per_part, ...))
-  const int r_end = (SMODE == 3 && a.rows_dev) ? min(a.rows, *a.rows_dev) : a.rows;
+  const int r_end = (SMODE == 3 && a.rows_dev) ? min(t.rows, *a.rows_dev) : t.rows;
   if (r_end <= 0) return;                                  // (the whole workgroup)
   const int nr = min(32 * NJV, r_end);                     // valid hidden rows
-  const int n_valid = a.w_rows;
+  const int n_valid = t.n_valid;
   const int v0 = vt * TILE;
   const size_t row_bytes = (size_t)a.d * 2;
   const int ks = SMODE == 3 ? (int)blockIdx.y : 0;
@@ -116,7 +124,7 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
     return slab0 + (x >= n_slabs ? x - n_slabs : x);
   };
   // weights through the wave's own ring: its 32 rows in four requests of 8 whole lines, laid out as the hidden rows are
-  const unsigned char* Wt = reinterpret_cast<const unsigned char*>(a.W) + (size_t)v0 * row_bytes;
+  const unsigned char* Wt = reinterpret_cast<const unsigned char*>(t.W) + (size_t)v0 * row_bytes;
   uint32_t wsrc[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -140,7 +148,7 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
   // 128 LDS bytes: chunk (l & 7) ^ ((row >> 1) & 7).  Rows past the last valid one read the last valid one.
   constexpr int HL = (4 * NJV) / WAVES;                    // requests per wave and slab
   static_assert(HL * WAVES == 4 * NJV, "whole groups per wave");
-  const unsigned char* Ht = reinterpret_cast<const unsigned char*>(a.H);
+  const unsigned char* Ht = reinterpret_cast<const unsigned char*>(t.H);
   const uint32_t lds_base = lds_offset_of(lds);
   uint32_t hsrc[HL];
 #pragma unroll
@@ -285,7 +293,7 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
   else if (SMODE == 2 || SMODE == 6)
     fold_tile_store<1, NJV>(acc, run, a, 0, r_end, col_base, n_valid);
   else
-    fold_tile<1, NJV>(acc, run, col_base, a.col0, n_valid, v0 + TILE > n_valid);
+    fold_tile<1, NJV>(acc, run, col_base, t.col0, n_valid, v0 + TILE > n_valid);
 #pragma unroll
   for (int j = 0; j < NJV; ++j) {                          // lanes l and l + 32 hold the same hidden row
     Triple o;
@@ -312,12 +320,12 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
   }
   __syncthreads();
   if (tid < nr) {
-    Triple t = xch[tid];
+    Triple tr = xch[tid];
 #pragma unroll
-    for (int w = 1; w < WAVES; ++w) merge_triple(t, xch[w * M_HT + tid]);
-    const size_t p = (size_t)tid * a.n_parts + a.part0 + vt;
-    a.part_m[p] = t.m;
-    a.part_s[p] = t.s;
+    for (int w = 1; w < WAVES; ++w) merge_triple(tr, xch[w * M_HT + tid]);
+    const size_t p = (size_t)(t.row0 + tid) * a.n_parts + t.part;
+    a.part_m[p] = tr.m;
+    a.part_s[p] = tr.s;
     if (SMODE == 1 || SMODE == 5) {
       Draw dw = xdr[tid];
 #pragma unroll
@@ -326,7 +334,7 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
       a.part_l[p] = dw.l;
       a.part_i[p] = dw.i;
     } else {
-      a.part_i[p] = t.i;
+      a.part_i[p] = tr.i;
     }
   }
 }
@@ -334,14 +342,40 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, unsigned char* lds
 template <int NJV, int SMODE, int WAVES = M_WAVES>
 __global__ void __launch_bounds__(64 * WAVES) logits_mid_kernel(LogitsArgs a) {
   extern __shared__ __align__(1024) unsigned char lds[];
+  MidTile t = {a.W, a.H, (int)blockIdx.x, a.w_rows, a.rows, 0, a.col0, a.part0 + (int)blockIdx.x};
+  if constexpr (SMODE == 0) {
+    // Workgroups behind the base part's tiles take the hyper part's (a.hyper): tile u of sequence b against that sequence's rows alone, the first
+    // tile of every sequence first.  In a launch of its own on the tile kernel this part was one round of a few workgroups, 58-80
+    // us: V = 32064, 1 x 72 rows 99 -> 43 us; V = 128256, 1 x 80 242 -> 179, 2 x 79 275 -> 230; V = 151936, 1 x 103 277 -> 220.
+    if (a.hyper.n_work > 0 && (int)blockIdx.x >= a.n_vtiles) {
+      const int id = (int)blockIdx.x - a.n_vtiles, u = id / a.hyper.n_seq, b = id - u * a.hyper.n_seq;
+      t.W = reinterpret_cast<const unsigned char*>(a.hyper.W) + (size_t)b * a.hyper.cap * a.d * 2;
+      t.H = reinterpret_cast<const unsigned char*>(a.H) + (size_t)b * a.rows_per_seq * a.d * 2;
+      t.vt = u;
+      t.n_valid = min(max(a.hyper.size[b], 0), a.hyper.cap);
+      t.rows = a.rows_per_seq;
+      t.row0 = b * a.rows_per_seq;
+      t.col0 = a.hyper.col0;
+      t.part = a.hyper.part0 + u;
+      if (u * 32 * WAVES >= t.n_valid) {                   // entries that do not exist: empty triples
+        if ((int)threadIdx.x < t.rows) {                   // (a thread per row)
+          const size_t p = (size_t)(t.row0 + (int)threadIdx.x) * a.n_parts + t.part;
+          a.part_m[p] = kNegInf;
+          a.part_s[p] = 0.f;
+          a.part_i[p] = kNoColumn;
+        }
+        return;
+      }
+    }
+  }
   if constexpr (SMODE == 3 && NJV == 4) {
     // (the rows that exist may be half of those laid out: known here only)
     if ((a.rows_dev ? min(a.rows, *a.rows_dev) : a.rows) <= 64)
-      mid_tile<2, SMODE, WAVES>(a, lds);
+      mid_tile<2, SMODE, WAVES>(a, t, lds);
     else
-      mid_tile<4, SMODE, WAVES>(a, lds);
+      mid_tile<4, SMODE, WAVES>(a, t, lds);
   } else {
-    mid_tile<NJV, SMODE, WAVES>(a, lds);
+    mid_tile<NJV, SMODE, WAVES>(a, t, lds);
   }
 }
 
@@ -360,7 +394,7 @@ int z2z_logits_mid_columns(const z2z_ctx* c, int w_rows) {
 
 template <int WAVES>
 static void launch_mid(const LogitsArgs& a, hipStream_t s) {
-  const dim3 grid((unsigned)a.n_vtiles), block(64 * WAVES);
+  const dim3 grid((unsigned)(a.n_vtiles + a.hyper.n_work)), block(64 * WAVES);
   const int blocks = a.rows <= 64 ? 2 : (a.rows <= 128 ? 4 : 6);
   if (a.sample == 1) {
     if (blocks == 2)
@@ -400,6 +434,7 @@ int z2z_launch_logits_mid(z2z_ctx* c, LogitsArgs a, const void* W, int w_rows, i
   a.n_vtiles = (w_rows + columns - 1) / columns;
   a.once = a.once || (size_t)w_rows * a.d * sizeof(uint16_t) > kKeepBytes;
   c->n_launch[Z2Z_KERNEL_MID]++;
+  if (a.hyper.n_work > 0 && (a.sample != 0 || a.rows_per_seq <= 64)) return Z2Z_EUNSUPPORTED;
   // (two workgroups of the 64-row build per weight tile for 65..128 rows, sharing the tile's weights through an
   // XCD's L2, measured slower than one of the 128-row build: 383 against 293 us at config 2's shape)
   // builds: 2, 4 or 6 blocks of 32 hidden rows; the sampling calls come with one row per sequence.  (8 blocks, up to 256
