@@ -85,13 +85,44 @@ __device__ __forceinline__ uint32_t lds_offset_of(const void* p) {
 // draw (a.sample = 1: part_v, part_l, and the drawn column in part_i), 2 = store logit / T and fold it
 // (a.sample = 2) -- the tile kernel's epilogues for its modes 0, 6 and 7; 3 = a dense layer with K split over
 // gridDim.y workgroups per tile: the fp32 partial tile goes to a.partial[ks][row][col] (the tile kernel's mode 5);
-// 4, 5, 6 = 0, 1, 2 with the sums in levels, for a step of up to 64 sequences.
+// 4, 5, 6 = 0, 1, 2 with the sums in levels, for a step of up to 64 sequences; 7 = the gradient of the loss with respect to the logits (the
+// tile kernel's mode 3).
 // What a workgroup's tile is cut from: weight tile vt of W (n_valid rows), all `rows` hidden rows at H, which are rows row0 ... of the call; its
 // columns start at col0, its part is `part`.
 struct MidTile {
   const void *W, *H;
   int vt, n_valid, rows, row0, col0, part;
+  void* out;                               // SMODE 7
+  int ldo;
 };
+
+// The gradient of the loss with respect to the logits of one finished tile (LogitsArgs, probability mode): four columns of a row at a time.
+template <int NJV>
+__device__ __forceinline__ void store_prob_tile(const f32x16 (&acc)[1][NJV], const LogitsArgs& a, const MidTile& t, int col_base) {
+  const int lane31 = threadIdx.x & 31;
+#pragma unroll
+  for (int j = 0; j < NJV; ++j) {
+    const int r = j * 32 + lane31;
+    if (r >= t.rows) continue;
+    const int row = t.row0 + r;
+    const float lse = a.lse[row], g = a.row_grad[row];
+    const int tgt = a.targets[row] - t.col0;
+    uint16_t* out = reinterpret_cast<uint16_t*>(t.out) + (size_t)row * t.ldo;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int col = col_base + q * 8;
+      float x[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float p = __expf(read_acc(acc[0][j][q * 4 + e]) - lse) - (col + e == tgt ? 1.f : 0.f);
+        x[e] = col + e < t.n_valid ? g * p : 0.f;
+      }
+      if (col < t.ldo)                     // (a multiple of 64)
+        *reinterpret_cast<uint2*>(out + col) =
+            uint2{bf16_bits_rne(x[0]) | (bf16_bits_rne(x[1]) << 16), bf16_bits_rne(x[2]) | (bf16_bits_rne(x[3]) << 16)};
+    }
+  }
+}
 
 template <int NJV, int SMODE, int WAVES>
 __device__ __forceinline__ void mid_tile(const LogitsArgs& a, const MidTile& t, unsigned char* lds) {
@@ -177,7 +208,7 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, const MidTile& t, 
   // size of the whole sum: d = 4096, relative error of the maxima 2.7e-7 to 3.3e-7; in two levels 5.7e-8 to 8.0e-8, in
   // three 4.4e-8 to 5.2e-8; the decode kernel's base units, which such a step ran on before and which add up 128 elements at a
   // time, 4.5e-8 to 4.9e-8.  (Calls with a few rows per sequence keep the one accumulator.)
-  constexpr bool LEVELS = SMODE >= 4;
+  constexpr bool LEVELS = SMODE >= 4 && SMODE <= 6;
   f32x16 total[NJV], top[NJV];
   if (LEVELS) {
 #pragma unroll
@@ -288,6 +319,10 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, const MidTile& t, 
     store_partial_tile<1, NJV>(acc, a.partial + (size_t)ks * a.rows * a.ldo, a.ldo, 0, r_end, col_base, n_valid);
     return;
   }
+  if (SMODE == 7) {
+    store_prob_tile<NJV>(acc, a, t, col_base);
+    return;
+  }
   if (SMODE == 1 || SMODE == 5)
     fold_tile_sample<1, NJV>(acc, run, draw, a, 0, col_base, n_valid);
   else if (SMODE == 2 || SMODE == 6)
@@ -342,8 +377,8 @@ __device__ __forceinline__ void mid_tile(const LogitsArgs& a, const MidTile& t, 
 template <int NJV, int SMODE, int WAVES = M_WAVES>
 __global__ void __launch_bounds__(64 * WAVES) logits_mid_kernel(LogitsArgs a) {
   extern __shared__ __align__(1024) unsigned char lds[];
-  MidTile t = {a.W, a.H, (int)blockIdx.x, a.w_rows, a.rows, 0, a.col0, a.part0 + (int)blockIdx.x};
-  if constexpr (SMODE == 0) {
+  MidTile t = {a.W, a.H, (int)blockIdx.x, a.w_rows, a.rows, 0, a.col0, a.part0 + (int)blockIdx.x, a.out, a.ldo};
+  if constexpr (SMODE == 0 || SMODE == 7) {
     // Workgroups behind the base part's tiles take the hyper part's (a.hyper): tile u of sequence b against that sequence's rows alone, the first
     // tile of every sequence first.  In a launch of its own on the tile kernel this part was one round of a few workgroups, 58-80
     // us: V = 32064, 1 x 72 rows 99 -> 43 us; V = 128256, 1 x 80 242 -> 179, 2 x 79 275 -> 230; V = 151936, 1 x 103 277 -> 220.
@@ -357,8 +392,10 @@ __global__ void __launch_bounds__(64 * WAVES) logits_mid_kernel(LogitsArgs a) {
       t.row0 = b * a.rows_per_seq;
       t.col0 = a.hyper.col0;
       t.part = a.hyper.part0 + u;
+      t.out = a.hyper.out;
+      t.ldo = a.hyper.ldo;
       if (u * 32 * WAVES >= t.n_valid) {                   // entries that do not exist: empty triples
-        if ((int)threadIdx.x < t.rows) {                   // (a thread per row)
+        if (SMODE == 0 && (int)threadIdx.x < t.rows) {     // (a thread per row)
           const size_t p = (size_t)(t.row0 + (int)threadIdx.x) * a.n_parts + t.part;
           a.part_m[p] = kNegInf;
           a.part_s[p] = 0.f;
@@ -396,6 +433,15 @@ template <int WAVES>
 static void launch_mid(const LogitsArgs& a, hipStream_t s) {
   const dim3 grid((unsigned)(a.n_vtiles + a.hyper.n_work)), block(64 * WAVES);
   const int blocks = a.rows <= 64 ? 2 : (a.rows <= 128 ? 4 : 6);
+  if (a.row_grad) {
+    if (blocks == 2)
+      hipLaunchKernelGGL((logits_mid_kernel<2, 7, WAVES>), grid, block, mid_lds(2, WAVES), s, a);
+    else if (blocks == 4)
+      hipLaunchKernelGGL((logits_mid_kernel<4, 7, WAVES>), grid, block, mid_lds(4, WAVES), s, a);
+    else
+      hipLaunchKernelGGL((logits_mid_kernel<6, 7, WAVES>), grid, block, mid_lds(6, WAVES), s, a);
+    return;
+  }
   if (a.sample == 1) {
     if (blocks == 2)
       hipLaunchKernelGGL((logits_mid_kernel<2, 5, WAVES>), grid, block, mid_lds(2, WAVES), s, a);
@@ -434,7 +480,7 @@ int z2z_launch_logits_mid(z2z_ctx* c, LogitsArgs a, const void* W, int w_rows, i
   a.n_vtiles = (w_rows + columns - 1) / columns;
   a.once = a.once || (size_t)w_rows * a.d * sizeof(uint16_t) > kKeepBytes;
   c->n_launch[Z2Z_KERNEL_MID]++;
-  if (a.hyper.n_work > 0 && (a.sample != 0 || a.rows_per_seq <= 64)) return Z2Z_EUNSUPPORTED;
+  if (a.hyper.n_work > 0 && (a.sample != 0 || (a.rows_per_seq <= 64 && !a.row_grad))) return Z2Z_EUNSUPPORTED;
   // (two workgroups of the 64-row build per weight tile for 65..128 rows, sharing the tile's weights through an
   // XCD's L2, measured slower than one of the 128-row build: 383 against 293 us at config 2's shape)
   // builds: 2, 4 or 6 blocks of 32 hidden rows; the sampling calls come with one row per sequence.  (8 blocks, up to 256
@@ -508,6 +554,12 @@ int z2z_logits_mid_prepare(z2z_ctx* c) {
   if (c->lds_limit < M_LDS_MAX) return Z2Z_EUNSUPPORTED;
   const void* kernels[] = {reinterpret_cast<const void*>(logits_mid_kernel<2, 3>),
                            reinterpret_cast<const void*>(logits_mid_kernel<4, 3>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<2, 7, M_WAVES>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<4, 7, M_WAVES>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<6, 7, M_WAVES>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<2, 7, M_WAVES / 2>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<4, 7, M_WAVES / 2>),
+                           reinterpret_cast<const void*>(logits_mid_kernel<6, 7, M_WAVES / 2>),
                            reinterpret_cast<const void*>(logits_mid_kernel<2, 0, M_WAVES>),
                            reinterpret_cast<const void*>(logits_mid_kernel<2, 4, M_WAVES>),
                            reinterpret_cast<const void*>(logits_mid_kernel<2, 5, M_WAVES>),

@@ -2,6 +2,7 @@
 // compressed sequence): gradient into the hidden rows and both unembedding matrices, and through the pooling of
 // the averaging hyper-encoder.
 #include "logits_common.h"
+#include "logits_mid.h"
 
 #include <string.h>
 
@@ -132,6 +133,8 @@ int z2z_launch_extended_nll_backward(z2z_ctx* c, const void* H, int32_t rows, in
     hipLaunchKernelGGL(row_grad_kernel, dim3((rows_c + 255) / 256), dim3(256), 0, s, targets + r0,
                        grad_nll ? grad_nll + r0 : nullptr, c->st.size + b0, rows_c, rows_per_seq, V, cap, g);
     // ---- dZ: the forward kernel with the probability epilogue -------------------------------------------
+    // (up to 192 rows are bound by the weights' bytes, as in the forward pass: the streaming kernel)
+    const bool few = c->opt_logits_kernel == 0 && z2z_logits_mid_ok(c, rows_c);
     LogitsArgs a;
     memset(&a, 0, sizeof(a));
     a.H = Hc;
@@ -147,11 +150,17 @@ int z2z_launch_extended_nll_backward(z2z_ctx* c, const void* H, int32_t rows, in
       const size_t n16 = (size_t)rows_c * capp * 2 / 16;
       hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)std::min<size_t>((n16 + 255) / 256, 4096)), dim3(256), 0, s,
                          reinterpret_cast<uint4*>(Ph), n16);
-      z2z_add_hyper_part(c, a, Whc, 0, strip, rows_per_seq, b0, nb);
+      z2z_add_hyper_part(c, a, Whc, 0, few ? 1 : strip, rows_per_seq, b0, nb);
       a.hyper.out = Ph;
       a.hyper.ldo = (int)capp;
     }
-    rc = z2z_launch_logits_part(c, false, a, W_base, V, 0, 0, strip, rows_c, rows_per_seq, false, s, true);
+    if (few) {
+      const int columns = z2z_logits_mid_columns(c, V);
+      a.hyper.n_work = cap > 0 ? nb * ((cap + columns - 1) / columns) : 0;
+      rc = z2z_launch_logits_mid(c, a, W_base, V, 0, s);
+    } else {
+      rc = z2z_launch_logits_part(c, false, a, W_base, V, 0, 0, strip, rows_c, rows_per_seq, false, s, true);
+    }
     if (rc != Z2Z_OK) return rc;
     // ---- the products ------------------------------------------------------------------------------------------
     uint16_t* dHc = reinterpret_cast<uint16_t*>(dH) + (size_t)r0 * d;
