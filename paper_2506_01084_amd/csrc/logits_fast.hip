@@ -714,7 +714,7 @@ __device__ __forceinline__ void merge_rows(R (&a)[F_N], S swap) {
 // of a.rows output rows each, one below the other.
 // HYP (modes 0 and 3): the items of the per-sequence hyper part (a.hyper) that exist are dealt out with the base part's last tiles.  In a launch
 // of its own that part is one or two rounds of tiles on a few CUs (58 us at d = 3072): V = 32064, 8 x 86 rows 190 -> 146 us, 17 x 75 257 -> 204;
-// V = 128256, d = 4096, 3 x 176 654 -> 597, 2 x 577 1090 -> 1043; level from 5000 rows on (3 x 3577 7818 and 7826).
+// V = 128256, d = 4096, 3 x 176 654 -> 597, 2 x 577 1090 -> 1043; level about 10000 rows (3 x 3577 7818 and 7826).
 template <int MODE, bool ROT = false, bool TW = false, bool TH = false, bool HYP = false>
 __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
   static_assert(MODE == 2 || (!TW && !TH), "dense layers only");
