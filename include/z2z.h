@@ -353,8 +353,8 @@ int z2z_extended_nll(z2z_ctx* ctx, const void* d_H, int32_t rows, int32_t rows_p
  *   d_grad_nll [rows] float or NULL (= 1 for every row)
  *   d_dH [rows, d], d_dW_base [V, d], d_dW_hyper [B, cap, d]: out, bf16 (overwritten, not accumulated)
  * dZ is rounded to bf16 once and the four products accumulate in fp32.  bf16 contexts with d a multiple of 64;
- * anything else returns Z2Z_EUNSUPPORTED.  Work space: 2 * rows * (V + cap) bf16 for dZ and its transpose plus
- * one transposed copy of H, W_base and W_hyper, library scratch.  Beyond 200 GB the sequences go in chunks (halved
+ * anything else returns Z2Z_EUNSUPPORTED.  Work space: rows * (V + cap) bf16 for
+ * dZ (V and cap rounded up to multiples of 64), library scratch.  Beyond 200 GB the sequences go in chunks (halved
  * until a chunk fits; dW_base of a later chunk adds to the bf16 result of the earlier ones); Z2Z_ENOMEM if one
  * sequence alone does not fit. */
 int z2z_extended_nll_backward(z2z_ctx* ctx, const void* d_H, int32_t rows, int32_t rows_per_seq,

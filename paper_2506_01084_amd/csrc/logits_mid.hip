@@ -1,6 +1,7 @@
 // extended_logits, base-vocabulary part for up to 192 hidden rows in all (gfx950, bf16, d a multiple of 64): a
 // decode step of 65..192 sequences, one of 5..64 where the tiles fill the CUs (greedy or a draw), a few rows per sequence at a
-// small batch, a short chunk; dense layers on up to 128 rows.  (zip2zip paper, section 2.3, steps 7-9.)
+// small batch, a short chunk; dense layers on up to 128 rows.  With one or two sequences of more than 64 rows the launch takes the
+// tiles of W_hyper along, and the backward pass of the loss makes dZ here.  (zip2zip paper, section 2.3, steps 7-9.)
 //
 // With so few rows the part is bound by the bytes of W_base, like the one-row-per-sequence step.  That kernel's
 // base units hold 64 hidden rows in registers (one pass over W_base per 64 rows); the 256 x 256 tile kernel shares

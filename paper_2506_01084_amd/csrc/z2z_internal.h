@@ -64,13 +64,12 @@ struct z2z_ctx {
   // hyper_encode work space: the activations of one pass (bf16)
   void* enc_ws;
   size_t enc_ws_bytes;
-  // backward pass of the loss: dZ, the transposed operand copies (bf16), the row gradients
   void* enc_bwd_ws;        // saved activations and gradients of the learned encoder's backward pass
   size_t enc_bwd_ws_bytes;
   bool enc_kept;           // the work space holds the rows of a z2z_hyper_encode_keep call ...
   size_t enc_kept_need;    // ... laid out for this size ...
   const void* enc_kept_E;  // ... computed from this embedding matrix
-  void* bwd_ws;
+  void* bwd_ws;            // backward pass of the loss: dZ of both parts (bf16), the row gradients
   size_t bwd_ws_bytes;
   void* prune_prefix;      // codebook pruning: every entry's prefix entry (scratch, [B, cap] int32)
   void* coef_dev;          // the pooling coefficients on the device (pooling backward)
