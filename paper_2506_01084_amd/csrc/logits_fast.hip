@@ -717,7 +717,7 @@ __device__ __forceinline__ void merge_rows(R (&a)[F_N], S swap) {
 // V = 128256, d = 4096, 3 x 176 654 -> 597, 2 x 577 1090 -> 1043; level about 10000 rows (3 x 3577 7818 and 7826).
 template <int MODE, bool ROT = false, bool TW = false, bool TH = false, bool HYP = false>
 __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
-  static_assert(MODE == 2 || (!TW && !TH), "dense layers only");
+  static_assert((MODE == 2 || !TW) && (TW || !TH), "dense layers only, and H K-major only where W is");
   static_assert(!HYP || ((MODE == 0 || MODE == 3) && !ROT), "");
   constexpr bool PROBE_NOREQ = MODE == 8 || MODE == 9;
   constexpr bool PROBE_MFMA = MODE == 9;
@@ -936,6 +936,11 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
     // (a descriptor's range ends with the matrix's last row)
     if (TW) is_ra = k_rows_rsrc(is_ga, is_rows, pitch_w, is_col_a);
     if (TH) is_rb = k_rows_rsrc(is_gb, is_rows, pitch_h, is_col_b);
+    // (five wait states between v_readfirstlane and the load that reads its register: the compiler does not know that the requests are loads)
+    if (TW && TH)
+      asm volatile("s_nop 4" : "+s"(is_ra), "+s"(is_rb));
+    else if (TW)
+      asm volatile("s_nop 4" : "+s"(is_ra));
   };
   // request n of the 16 of a slab: 8 rows of the vocabulary tile (n even) or of the hidden rows' (n odd)
   auto request = [&](auto n_) __attribute__((always_inline)) {
