@@ -76,7 +76,7 @@ int ensure_partial(z2z_ctx* c, size_t need, hipStream_t s) {
   c->skinny_partial = nullptr;
   c->skinny_partial_bytes = 0;
   const size_t want = need > ((size_t)64 << 20) ? need : ((size_t)64 << 20);
-  if (hipMalloc(&c->skinny_partial, want) != hipSuccess) return Z2Z_ENOMEM;
+  if (!z2z_device_malloc(&c->skinny_partial, want)) return Z2Z_ENOMEM;
   c->skinny_partial_bytes = want;
   return Z2Z_OK;
 }

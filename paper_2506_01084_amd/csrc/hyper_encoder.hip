@@ -889,7 +889,7 @@ int z2z_launch_hyper_encode(z2z_ctx* c, const void* E, const z2z_encoder* enc, v
     if (c->enc_ws) (void)hipFree(c->enc_ws);
     c->enc_ws = nullptr;
     c->enc_ws_bytes = 0;
-    if (hipMalloc(&c->enc_ws, need) != hipSuccess) return Z2Z_ENOMEM;
+    if (!z2z_device_malloc(&c->enc_ws, need)) return Z2Z_ENOMEM;
     c->enc_ws_bytes = need;
   }
   int32_t* index = reinterpret_cast<int32_t*>(c->enc_ws);
@@ -1068,7 +1068,7 @@ int z2z_launch_hyper_encode_train(z2z_ctx* c, int mode, const void* E, const z2z
     if (c->enc_bwd_ws) (void)hipFree(c->enc_bwd_ws);
     c->enc_bwd_ws = nullptr;
     c->enc_bwd_ws_bytes = 0;
-    if (hipMalloc(&c->enc_bwd_ws, need) != hipSuccess) return Z2Z_ENOMEM;
+    if (!z2z_device_malloc(&c->enc_bwd_ws, need)) return Z2Z_ENOMEM;
     c->enc_bwd_ws_bytes = need;
   }
   unsigned char* base = reinterpret_cast<unsigned char*>(c->enc_bwd_ws);

@@ -203,8 +203,8 @@ int ensure_sample_scratch(z2z_ctx* c, size_t need, hipStream_t s) {
   c->part_v = nullptr;
   c->part_l = nullptr;
   c->part_vl_capacity = 0;
-  if (hipMalloc(&c->part_v, need * sizeof(float)) != hipSuccess) return Z2Z_ENOMEM;
-  if (hipMalloc(&c->part_l, need * sizeof(float)) != hipSuccess) return Z2Z_ENOMEM;
+  if (!z2z_device_malloc(&c->part_v, need * sizeof(float))) return Z2Z_ENOMEM;
+  if (!z2z_device_malloc(&c->part_l, need * sizeof(float))) return Z2Z_ENOMEM;
   c->part_vl_capacity = need;
   return Z2Z_OK;
 }
@@ -219,9 +219,9 @@ int ensure_scratch(z2z_ctx* c, size_t need, hipStream_t s) {
   c->part_s = nullptr;
   c->part_i = nullptr;
   c->part_capacity = 0;
-  if (hipMalloc(&c->part_m, need * sizeof(float)) != hipSuccess) return Z2Z_ENOMEM;
-  if (hipMalloc(&c->part_s, need * sizeof(float)) != hipSuccess) return Z2Z_ENOMEM;
-  if (hipMalloc(&c->part_i, need * sizeof(int32_t)) != hipSuccess) return Z2Z_ENOMEM;
+  if (!z2z_device_malloc(&c->part_m, need * sizeof(float))) return Z2Z_ENOMEM;
+  if (!z2z_device_malloc(&c->part_s, need * sizeof(float))) return Z2Z_ENOMEM;
+  if (!z2z_device_malloc(&c->part_i, need * sizeof(int32_t))) return Z2Z_ENOMEM;
   c->part_capacity = need;
   return Z2Z_OK;
 }
@@ -656,9 +656,9 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     c->sample_logits = nullptr;
     c->row_max = nullptr;
     c->sample_logits_capacity = 0;
-    if (hipMalloc(&c->sample_logits, need * sizeof(float)) != hipSuccess) return Z2Z_ENOMEM;
+    if (!z2z_device_malloc(&c->sample_logits, need * sizeof(float))) return Z2Z_ENOMEM;
     // the row maxima and log-sum-exps, followed by the selection kernels' scratch
-    if (hipMalloc(&c->row_max, (2 * (size_t)rows + z2z_sample_truncated_work_floats(rows)) * sizeof(float)) != hipSuccess)
+    if (!z2z_device_malloc(&c->row_max, (2 * (size_t)rows + z2z_sample_truncated_work_floats(rows)) * sizeof(float)))
       return Z2Z_ENOMEM;
     c->sample_logits_capacity = need;
   }

@@ -924,7 +924,7 @@ int z2z_launch_linear_skinny(z2z_ctx* c, const void* A, const void* W, const flo
       c->skinny_partial = nullptr;
       c->skinny_partial_bytes = 0;
       const size_t want_bytes = need > ((size_t)16 << 20) ? need : ((size_t)16 << 20);
-      if (hipMalloc(&c->skinny_partial, want_bytes) != hipSuccess) return Z2Z_ENOMEM;
+      if (!z2z_device_malloc(&c->skinny_partial, want_bytes)) return Z2Z_ENOMEM;
       c->skinny_partial_bytes = want_bytes;
     }
     a.partial = reinterpret_cast<float*>(c->skinny_partial);

@@ -111,7 +111,7 @@ int z2z_launch_extended_nll_backward(z2z_ctx* c, const void* H, int32_t rows, in
     if (c->bwd_ws) (void)hipFree(c->bwd_ws);
     c->bwd_ws = nullptr;
     c->bwd_ws_bytes = 0;
-    if (hipMalloc(&c->bwd_ws, off) != hipSuccess) return Z2Z_ENOMEM;
+    if (!z2z_device_malloc(&c->bwd_ws, off)) return Z2Z_ENOMEM;
     c->bwd_ws_bytes = off;
   }
   unsigned char* ws = reinterpret_cast<unsigned char*>(c->bwd_ws);

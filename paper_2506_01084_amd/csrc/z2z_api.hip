@@ -96,19 +96,19 @@ Z2Z_API int z2z_create(z2z_ctx** out, const z2z_config* cfg) {
   const size_t B = (size_t)cfg->B;
   const size_t capn = cfg->cap > 0 ? (size_t)cfg->cap : 1;
   bool ok = true;
-  ok = ok && hipMalloc(&st.size, B * sizeof(int32_t)) == hipSuccess;
-  ok = ok && hipMalloc(&st.prev_code, B * sizeof(int32_t)) == hipSuccess;
-  ok = ok && hipMalloc(&st.prev_len, B * sizeof(int32_t)) == hipSuccess;
-  ok = ok && hipMalloc(&st.rounds, B * sizeof(int32_t)) == hipSuccess;
-  ok = ok && hipMalloc(&st.tail, 3 * B * sizeof(int32_t)) == hipSuccess;
+  ok = ok && z2z_device_malloc(&st.size, B * sizeof(int32_t));
+  ok = ok && z2z_device_malloc(&st.prev_code, B * sizeof(int32_t));
+  ok = ok && z2z_device_malloc(&st.prev_len, B * sizeof(int32_t));
+  ok = ok && z2z_device_malloc(&st.rounds, B * sizeof(int32_t));
+  ok = ok && z2z_device_malloc(&st.tail, 3 * B * sizeof(int32_t));
   ok = ok && hipMemset(st.rounds, 0, B * sizeof(int32_t)) == hipSuccess;
-  ok = ok && hipMalloc(&st.ent_tokens, B * capn * cfg->M * sizeof(int32_t)) == hipSuccess;
-  ok = ok && hipMalloc(&st.ent_len, B * capn * sizeof(int32_t)) == hipSuccess;
-  ok = ok && hipMalloc(&st.slots, B * (size_t)st.nslots * sizeof(unsigned long long)) == hipSuccess;
+  ok = ok && z2z_device_malloc(&st.ent_tokens, B * capn * cfg->M * sizeof(int32_t));
+  ok = ok && z2z_device_malloc(&st.ent_len, B * capn * sizeof(int32_t));
+  ok = ok && z2z_device_malloc(&st.slots, B * (size_t)st.nslots * sizeof(unsigned long long));
   // fixed-size work buffers of calls that must not allocate on a stream: pruning's prefix map, and the pooling
   // coefficients on the device (the pooling's backward pass)
-  ok = ok && hipMalloc(&c->prune_prefix, B * capn * sizeof(int32_t)) == hipSuccess;
-  ok = ok && hipMalloc(&c->coef_dev, sizeof(c->coef)) == hipSuccess;
+  ok = ok && z2z_device_malloc(&c->prune_prefix, B * capn * sizeof(int32_t));
+  ok = ok && z2z_device_malloc(&c->coef_dev, sizeof(c->coef));
   ok = ok && hipMemcpy(c->coef_dev, c->coef, sizeof(c->coef), hipMemcpyHostToDevice) == hipSuccess;
   if (!ok) {
     free_ctx(c);

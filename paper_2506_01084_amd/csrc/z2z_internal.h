@@ -144,6 +144,16 @@ inline int z2z_can_allocate(hipStream_t s) {
     if (_g != Z2Z_OK) return _g;               \
   } while (0)
 
+// Device memory, or false.  A refusal is the call's to answer (another way, or Z2Z_ENOMEM): it does not stay behind as the runtime's last error,
+// which the next launch, the program's too, would report as its own.
+template <typename T>
+inline bool z2z_device_malloc(T** p, size_t bytes) {
+  if (hipMalloc(p, bytes) == hipSuccess) return true;
+  *p = nullptr;
+  (void)hipGetLastError();
+  return false;
+}
+
 #define Z2Z_HIP_TRY(expr)                      \
   do {                                         \
     hipError_t _e = (expr);                    \
