@@ -212,8 +212,8 @@ int z2z_hyper_embed(z2z_ctx* ctx, const void* d_E, void* d_W_hyper, const int32_
  *   [d_first[b], min(C_b, d_first[b] + max_new)) are computed (max_new <= 0: up to cap).
  * Requires a bf16 context, d a multiple of 64 and at most 4096, d / n_heads a power of two in [8, 512], d_ff a
  * multiple of 64, 1 <= n_layers <= Z2Z_MAX_ENCODER_LAYERS; anything else returns Z2Z_EUNSUPPORTED or
- * Z2Z_EINVAL.  Work space (activations of up to 131072 slot rows) is library scratch, allocated by the first
- * call at a size. */
+ * Z2Z_EINVAL.  Work space (activations of up to 131072 slot rows, of 65536 where the device has no room for as many) is library
+ * scratch, allocated by the first call at a size. */
 #define Z2Z_MAX_ENCODER_LAYERS 8
 typedef struct z2z_encoder_layer {
   const float* ln1_g;   /* [d]  */

@@ -875,23 +875,40 @@ int z2z_launch_hyper_encode(z2z_ctx* c, const void* E, const z2z_encoder* enc, v
   // (few rows: does anything of the weights stay in the memory-side cache until the next call?)
   const bool once = (size_t)enc->n_layers * ((size_t)4 * d + (size_t)2 * dff) * d * sizeof(uint16_t) > z2z_logits::kKeepBytes;
   // rows per pass: all sequences, u_step entries each, M slots per entry
-  long long u_step = 131072 / ((long long)B * M);
-  if (u_step < 1) u_step = 1;
-  if (u_step > units) u_step = units;
-  const size_t R_max = (size_t)B * (size_t)u_step * M;
-  const int dffp = ffn_pitch(c, B, M, units, (int)u_step, d, dff);
-  const size_t n_units_max = (size_t)B * (size_t)u_step;
-  const size_t index_bytes = ((n_units_max + 1 + R_max) * sizeof(int32_t) + 255) & ~(size_t)255;
-  // per row: the stream X and Y in fp32 (2 x 4 bytes x d), A, O (d), QKV (3d) and F (d_ff) in bf16
-  const size_t need = R_max * ((size_t)8 * d + ((size_t)2 * d + (size_t)3 * d + (size_t)dffp) * 2) + index_bytes;
-  if (need > c->enc_ws_bytes) {
+  long long u_step = 0;
+  size_t R_max = 0, n_units_max = 0, index_bytes = 0;
+  int dffp = 0;
+  auto layout = [&](long long rows) -> size_t {
+    u_step = rows / ((long long)B * M);
+    if (u_step < 1) u_step = 1;
+    if (u_step > units) u_step = units;
+    R_max = (size_t)B * (size_t)u_step * M;
+    dffp = ffn_pitch(c, B, M, units, (int)u_step, d, dff);
+    n_units_max = (size_t)B * (size_t)u_step;
+    index_bytes = ((n_units_max + 1 + R_max) * sizeof(int32_t) + 255) & ~(size_t)255;
+    // per row: the stream X and Y in fp32 (2 x 4 bytes x d), A, O (d), QKV (3d) and F (d_ff) in bf16
+    return R_max * ((size_t)8 * d + ((size_t)2 * d + (size_t)3 * d + (size_t)dffp) * 2) + index_bytes;
+  };
+  auto room = [&](size_t need) -> int {
+    if (need <= c->enc_ws_bytes) return Z2Z_OK;
     Z2Z_TRY_GROW(s);
     if (c->enc_ws) (void)hipFree(c->enc_ws);
     c->enc_ws = nullptr;
     c->enc_ws_bytes = 0;
     if (!z2z_device_malloc(&c->enc_ws, need)) return Z2Z_ENOMEM;
     c->enc_ws_bytes = need;
+    return Z2Z_OK;
+  };
+  // (where the buffer cannot grow that far, or not at all under capture, passes of half as many rows.  What the device has refused is not asked
+  // for again: every call would free the buffer that does)
+  size_t need = layout(131072);
+  int rc = c->enc_ws_refused && need >= c->enc_ws_refused && need > c->enc_ws_bytes ? Z2Z_ENOMEM : room(need);
+  if (rc != Z2Z_OK) {
+    if (rc == Z2Z_ENOMEM) c->enc_ws_refused = need;
+    need = layout(65536);
+    rc = room(need);
   }
+  if (rc != Z2Z_OK) return rc;
   int32_t* index = reinterpret_cast<int32_t*>(c->enc_ws);
   float* X = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(c->enc_ws) + index_bytes);
   float* Y = X + R_max * d;
@@ -928,7 +945,6 @@ int z2z_launch_hyper_encode(z2z_ctx* c, const void* E, const z2z_encoder* enc, v
     float* y = Y;
     bool normed = false;                            // A holds the layer's normalised input already
     bool pooled = false;
-    int rc;
     // A dense layer that adds to the residual stream: out = in A^T + bias + residual, then the LayerNorm that follows
     // (gamma, beta -> A) or, behind the last layer, the mean over an entry's rows.  Where K is split those
     // add up the partial tiles themselves; else *fused stays false and only `out` is written.

@@ -64,6 +64,7 @@ struct z2z_ctx {
   // hyper_encode work space: the activations of one pass (bf16)
   void* enc_ws;
   size_t enc_ws_bytes;
+  size_t enc_ws_refused;   // 0, or a size the device had no room for
   void* enc_bwd_ws;        // saved activations and gradients of the learned encoder's backward pass
   size_t enc_bwd_ws_bytes;
   bool enc_kept;           // the work space holds the rows of a z2z_hyper_encode_keep call ...

@@ -120,3 +120,39 @@ room(8)
 assert lib.z2z_create(ctypes.byref(h), ctypes.byref(cfg)) == api.E_NOMEM and not h
 clean()
 """)
+
+
+def test_the_encoder_takes_shorter_passes_where_long_ones_have_no_room(without_a_device):
+    """40 sequences of up to 600 entries of 3 slots: one pass of 72000 rows, or two (546 and 54 entries) of up to 65520."""
+    without_a_device("""
+enc = encoder(512)
+run = lambda h: lib.z2z_hyper_encode(h, P, ctypes.byref(enc), P, None, 0, None)
+row = 8 * 512 + 2 * (5 * 512 + 2048 + 64)                  # bytes of a slot row, and some more
+parts = 64 * MB
+h = context(B=40, V=512, M=3, cap=600, d=512)
+assert run(h) == 0 and len(named(launches(), "enc_rows")) == 1
+h = context(B=40, V=512, M=3, cap=600, d=512)
+room((65600 * row + parts) // MB)
+assert run(h) == 0
+clean()
+assert len(named(launches(), "enc_rows")) == 2
+stub.stub_most()
+stub.stub_capacity(1 << 40)
+assert run(h) == 0 and len(named(launches(), "enc_rows")) == 2          # (once refused, the buffer stays as it is)
+assert stub.stub_most() == stub.stub_used()
+
+# under capture nothing grows: the buffer of a call with 546 new entries holds the shorter passes of a whole one, not the long one
+h = context(B=40, V=512, M=3, cap=600, d=512)
+assert lib.z2z_hyper_encode(h, P, ctypes.byref(enc), P, None, 546, None) == 0
+launches()
+stub.stub_capturing(1)
+assert run(h) == 0 and len(named(launches(), "enc_rows")) == 2
+h2 = context(B=40, V=512, M=3, cap=600, d=512)
+assert run(h2) == api.E_CAPTURE
+stub.stub_capturing(0)
+
+h = context(B=40, V=512, M=3, cap=600, d=512)
+room(64000 * row // MB)
+assert run(h) == api.E_NOMEM
+clean()
+""")
