@@ -531,7 +531,7 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
   // Both parts in one launch of the tile kernel (the measurement probes run the base part alone), up to 32768 tiles: 14875 rows x 128256 (29559
   // tiles) 11.57 -> 11.45 ms, 32768 rows (64128) 23.42 -> 23.56, where the hyper part is a hundredth of the call and its launch full anyway.
   const bool one_launch = !mid_base && cap > 0 && !decode_split && !seq_split && c->opt_logits_kernel != 2 && c->opt_logits_kernel != 3 &&
-                          tiles_b * base_vt <= 32768;
+                          c->cfg.B <= z2z_logits_fast_sequences() && tiles_b * base_vt <= 32768;
   if (one_launch) z2z_add_hyper_part(c, a, W_hyper, base_strips, strip_h, rows_per_seq, 0, c->cfg.B);
   if (mid_both) {
     z2z_add_hyper_part(c, a, W_hyper, base_strips, 1, rows_per_seq, 0, c->cfg.B);

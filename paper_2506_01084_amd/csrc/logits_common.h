@@ -451,6 +451,7 @@ bool z2z_linear_takes_pitch(const z2z_ctx* c, int R, int N, int K);
 int z2z_launch_linear_parts(z2z_ctx* c, const void* A, const void* W, int R, const int32_t* rows_dev, int N, int K,
                             const float** partial, int* ksplit, hipStream_t s, bool once = false);
 int z2z_logits_fast_prepare(z2z_ctx* c);
+int z2z_logits_fast_sequences();   // most sequences whose hyper part a launch of the tile kernel takes along
 // One launch of the bf16 MFMA tile kernel over the base part (hyper = false), over the hyper part of n_seq sequences, or over both
 // (z2z_add_hyper_part first)
 int z2z_launch_logits_part(z2z_ctx* c, bool hyper, z2z_logits::LogitsArgs a, const void* W, int w_rows, int col0,

@@ -56,6 +56,10 @@ constexpr int F_STAGE = 2 * F_OPER;       // A + B
 constexpr int F_LDS_STAGES = 2 * F_STAGE; // 128 KiB
 constexpr int F_LDS = F_LDS_STAGES + FT * (int)(sizeof(Triple) + sizeof(Draw));     // + what the waves exchange at the end of a strip
 constexpr int F_THREADS = 256;
+// with the hyper part along: items ahead of every sequence's, and sizes (of up to F_HYP_SEQS of them), sums of the four waves
+constexpr int F_HYP_SEQS = 2048;
+constexpr int F_HYP_LDS = F_LDS + (2 * F_HYP_SEQS + 4) * (int)sizeof(int32_t);
+static_assert(F_HYP_LDS <= 160 * 1024 && F_HYP_SEQS <= 64 * 64 && F_LDS % 16 == 0, "");
 constexpr int F_N = 8;                    // MFMA blocks of a wave along either side (128 x 128)
 constexpr int F_PAIRS = 8;                // request pairs (8 rows of A + 8 rows of B) per wave and slab
 constexpr int F_SLOTS = 2 * F_N * F_N;    // MFMAs of a wave per slab
@@ -778,14 +782,50 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
     int r0, st, s0, sn, part;    // first row, strip, slabs, buffer
     int b;                       // product of a batch; sequence of an item of the hyper part, else (HYP) -1
   };
-  // (the hyper part: strips of sequence b, and the items of all)
-  auto hyper_strips = [&](int b) -> int {
-    const int n = min(max(__builtin_amdgcn_readfirstlane(a.hyper.size[b]), 0), a.hyper.cap);
-    return (n + FT * a.hyper.strip - 1) / (FT * a.hyper.strip);
-  };
+  // The hyper part's items lie sequence by sequence, those of one strip after strip.  How many each sequence has follows from its size, so a table of the
+  // items ahead of every sequence is made in LDS first; an item's sequence is found in it by two reads of the wave.  (Counted out from
+  // the first sequence on, a load and a wait for the whole operand stream a step: 2000 x 66 rows, V = 1024, d = 512 2419 us, 499 with the table,
+  // 546 with the hyper part in a launch of its own; 1024 x 66, V = 4096, d = 1024 1302, 771, 815; 64 x 70, V = 32064, d = 3072 893, 868, 910.)
+  int32_t* const items_before = reinterpret_cast<int32_t*>(lds + F_LDS);
+  int32_t* const sizes = items_before + F_HYP_SEQS;
   int hyper_items = 0;
-  if (HYP)
-    for (int b = 0; b < a.hyper.n_seq; ++b) hyper_items += hyper_strips(b) * a.hyper.row_tiles;
+  auto strips_of = [&](int size) -> int { return (size + FT * a.hyper.strip - 1) / (FT * a.hyper.strip); };
+  if (HYP) {
+    int32_t* const wave_items = sizes + F_HYP_SEQS;
+    const int each = (a.hyper.n_seq + F_THREADS - 1) / F_THREADS, b0 = tid * each, b1 = min(b0 + each, a.hyper.n_seq);
+    int own = 0;
+    for (int b = b0; b < b1; ++b) {
+      sizes[b] = min(max(a.hyper.size[b], 0), a.hyper.cap);
+      own += strips_of(sizes[b]) * a.hyper.row_tiles;
+    }
+    int upto = own;                                  // of this lane and those before it
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int x = __shfl_up(upto, o);
+      upto += lane >= o ? x : 0;
+    }
+    if (lane == 63) wave_items[wave] = upto;
+    __syncthreads();
+    int before = upto - own;
+    for (int w = 0; w < 4; ++w) {
+      before += w < wave ? wave_items[w] : 0;
+      hyper_items += wave_items[w];
+    }
+    hyper_items = __builtin_amdgcn_readfirstlane(hyper_items);
+    for (int b = b0; b < b1; ++b) {
+      items_before[b] = before;
+      before += strips_of(sizes[b]) * a.hyper.row_tiles;
+    }
+    __syncthreads();
+  }
+  // the last sequence with at most k items ahead of it (the one that has item k: those without items lie before it)
+  auto sequence_of = [&](int k) -> int {
+    const int each = (a.hyper.n_seq + 63) / 64;
+    const int block = lane * each;
+    const int c = __popcll(__ballot(block < a.hyper.n_seq && items_before[min(block, a.hyper.n_seq - 1)] <= k)) - 1;
+    const int b = c * each + lane;
+    return c * each + __popcll(__ballot(lane < each && b < a.hyper.n_seq && items_before[min(b, a.hyper.n_seq - 1)] <= k)) - 1;
+  };
   // (where all strips are one tile the base part's last ones and the hyper items are dealt out as one; else every XCD goes on with every eighth
   // of these behind its base list: the longer strips of the base part have to be dealt out evenly by themselves, 9 x 263 rows 1930 us, 2155 as one)
   const bool together = HYP && a.strip == 1 && a.hyper.strip == 1;
@@ -818,11 +858,8 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
       if (it->b >= hyper_items) return false;
     }
     if (HYP && it->b >= 0) {
-      int k = it->b, b = 0, n = hyper_strips(0);
-      while (k >= n * a.hyper.row_tiles) {
-        k -= n * a.hyper.row_tiles;
-        n = hyper_strips(++b);
-      }
+      const int b = sequence_of(it->b), k = it->b - __builtin_amdgcn_readfirstlane(items_before[b]);
+      const int n = strips_of(__builtin_amdgcn_readfirstlane(sizes[b]));
       rt = __builtin_amdgcn_readfirstlane(k / n);
       it->st = k - rt * n;
       it->b = b;
@@ -848,7 +885,7 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
   };
   auto part_of = [&](const Item& it) -> Part {
     if (HYP && it.b >= 0) {
-      const int n = min(max(__builtin_amdgcn_readfirstlane(a.hyper.size[it.b]), 0), a.hyper.cap);
+      const int n = __builtin_amdgcn_readfirstlane(sizes[it.b]);
       return Part{reinterpret_cast<const unsigned char*>(a.hyper.W) + (size_t)it.b * a.hyper.cap * row_bytes, n, (n + FT - 1) / FT,
                   (it.b + 1) * a.rows_per_seq, a.hyper.strip};
     }
@@ -1297,12 +1334,13 @@ int z2z_launch_linear_kmajor(const LogitsArgs& a, bool rows_too, unsigned grid, 
 int z2z_launch_logits_fast(int mode, const LogitsArgs& a, unsigned grid, hipStream_t s) {
   const bool rot = a.row_tiles == 1;
   if (a.hyper.n_work > 0) {
+    if (a.hyper.n_seq > F_HYP_SEQS) return Z2Z_EUNSUPPORTED;
     if (mode == 3)
-      hipLaunchKernelGGL((logits_fast_kernel<3, false, false, false, true>), dim3(grid), dim3(F_THREADS), F_LDS, s, a);
+      hipLaunchKernelGGL((logits_fast_kernel<3, false, false, false, true>), dim3(grid), dim3(F_THREADS), F_HYP_LDS, s, a);
     else if (mode != 0)
       return Z2Z_EUNSUPPORTED;
     else
-      hipLaunchKernelGGL((logits_fast_kernel<0, false, false, false, true>), dim3(grid), dim3(F_THREADS), F_LDS, s, a);
+      hipLaunchKernelGGL((logits_fast_kernel<0, false, false, false, true>), dim3(grid), dim3(F_THREADS), F_HYP_LDS, s, a);
     Z2Z_HIP_TRY(hipGetLastError());
     return Z2Z_OK;
   }
@@ -1340,8 +1378,10 @@ int z2z_launch_tile_sum(const LogitsArgs& a, hipStream_t s) {
   return Z2Z_OK;
 }
 
+int z2z_logits_fast_sequences() { return F_HYP_SEQS; }
+
 int z2z_logits_fast_prepare(z2z_ctx* c) {
-  if (c->lds_limit < F_LDS) return Z2Z_EUNSUPPORTED;
+  if (c->lds_limit < F_HYP_LDS) return Z2Z_EUNSUPPORTED;
   Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(logits_fast_kernel<0>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, F_LDS));
   Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(logits_fast_kernel<1>),
@@ -1351,9 +1391,9 @@ int z2z_logits_fast_prepare(z2z_ctx* c) {
   Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(logits_fast_kernel<3>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, F_LDS));
   Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(logits_fast_kernel<0, false, false, false, true>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, F_LDS));
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, F_HYP_LDS));
   Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(logits_fast_kernel<3, false, false, false, true>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, F_LDS));
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, F_HYP_LDS));
   Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(logits_fast_kernel<5>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, F_LDS));
   Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(logits_fast_kernel<6>),

@@ -135,33 +135,42 @@ int z2z_launch_extended_nll_backward(z2z_ctx* c, const void* H, int32_t rows, in
     // ---- dZ: the forward kernel with the probability epilogue -------------------------------------------
     // (up to 192 rows are bound by the weights' bytes, as in the forward pass: the streaming kernel)
     const bool few = c->opt_logits_kernel == 0 && z2z_logits_mid_ok(c, rows_c);
-    LogitsArgs a;
-    memset(&a, 0, sizeof(a));
-    a.H = Hc;
-    a.rows = rows_c;
-    a.rows_per_seq = rows_per_seq;
-    a.d = d;
-    a.lse = lse + r0;
-    a.row_grad = g;
-    a.targets = targets + r0;
-    a.out = Pb;
-    a.ldo = (int)Vp;
     if (cap > 0) {
       const size_t n16 = (size_t)rows_c * capp * 2 / 16;
       hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)std::min<size_t>((n16 + 255) / 256, 4096)), dim3(256), 0, s,
                          reinterpret_cast<uint4*>(Ph), n16);
-      z2z_add_hyper_part(c, a, Whc, 0, few ? 1 : strip, rows_per_seq, b0, nb);
-      a.hyper.out = Ph;
-      a.hyper.ldo = (int)capp;
     }
-    if (few) {
-      const int columns = z2z_logits_mid_columns(c, V);
-      a.hyper.n_work = cap > 0 ? nb * ((cap + columns - 1) / columns) : 0;
-      rc = z2z_launch_logits_mid(c, a, W_base, V, 0, s);
-    } else {
-      rc = z2z_launch_logits_part(c, false, a, W_base, V, 0, 0, strip, rows_c, rows_per_seq, false, s, true);
+    // (in one launch as many sequences as the tile kernel takes the hyper part of)
+    const int most = cap > 0 ? z2z_logits_fast_sequences() : nb;
+    for (int q0 = 0; q0 < nb; q0 += most) {
+      const int nq = q0 + most <= nb ? most : nb - q0;
+      const size_t row = (size_t)q0 * rows_per_seq;
+      const uint16_t* Whq = Whc + (size_t)q0 * cap * d;
+      LogitsArgs a;
+      memset(&a, 0, sizeof(a));
+      a.H = Hc + row * d;
+      a.rows = nq * rows_per_seq;
+      a.rows_per_seq = rows_per_seq;
+      a.d = d;
+      a.lse = lse + r0 + row;
+      a.row_grad = g + row;
+      a.targets = targets + r0 + row;
+      a.out = reinterpret_cast<uint16_t*>(Pb) + row * Vp;
+      a.ldo = (int)Vp;
+      if (cap > 0) {
+        z2z_add_hyper_part(c, a, Whq, 0, few ? 1 : strip, rows_per_seq, b0 + q0, nq);
+        a.hyper.out = reinterpret_cast<uint16_t*>(Ph) + row * capp;
+        a.hyper.ldo = (int)capp;
+      }
+      if (few) {
+        const int columns = z2z_logits_mid_columns(c, V);
+        a.hyper.n_work = cap > 0 ? nq * ((cap + columns - 1) / columns) : 0;
+        rc = z2z_launch_logits_mid(c, a, W_base, V, 0, s);
+      } else {
+        rc = z2z_launch_logits_part(c, false, a, W_base, V, 0, 0, strip, nq * rows_per_seq, rows_per_seq, false, s, true);
+      }
+      if (rc != Z2Z_OK) return rc;
     }
-    if (rc != Z2Z_OK) return rc;
     // ---- the products ------------------------------------------------------------------------------------------
     uint16_t* dHc = reinterpret_cast<uint16_t*>(dH) + (size_t)r0 * d;
     rc = z2z_launch_linear_input(c, Pb, (int)Vp, W_base, d, V, nullptr, dHc, d, rows_c, nullptr, d, (int)Vp, s);

@@ -16,6 +16,9 @@ pytestmark = pytest.mark.gpu
     (4, 257, 775, 448, 4, 129, "weighted", True),
     (2, 40, 5003, 128, 3, 30, "mean", True),                 # 79 slabs over the vocabulary, one row tile
     (1, 2100, 600, 64, 3, 300, "mean", True),                # 33 slabs over the rows
+    # more sequences than one launch takes the hyper part of (2048)
+    (2100, 66, 200, 64, 3, 30, "mean", True),
+    (300, 70, 300, 64, 3, 300, "mean", True),
 ])
 def test_gradients(B, N, V, d, M, cap, pool, use_grad):
     check(B, N, V, d, M, cap, pool, use_grad, 0)
