@@ -140,17 +140,17 @@ int z2z_launch_linear_parts(z2z_ctx* c, const void* A, const void* W, int R, con
 
 namespace {
 constexpr size_t kSplitBytes = (size_t)256 * 256 * 256 * sizeof(float);      // LogitsArgs::split
-// Contractions from this many slabs on may be cut: half of them saved is worth the launch of the sum (5 us where nothing was cut:
-// 0.1 ms of a training step's 171).  Learned encoder over codebooks with room for 2048 entries, a whole prompt: 2 x 148 tokens, d = 3584
+// Contractions from this many slabs on may be cut: half of them saved is worth the launch of the sum (5 us where nothing was cut;
+// where the host knows rows and contraction it sees that itself and launches none).  Learned encoder over codebooks with room for 2048 entries, a whole prompt: 2 x 148 tokens, d = 3584
 // 1054 -> 694 us, 2 x 354, d = 3072 1019 -> 742, 8 x 847, d = 4096 8.59 -> 8.21 ms; a training step with it, 1 x 67 tokens, d = 4096 6.50 ->
 // 5.24 ms; where the host knows the rows, 4 x 1347 without it, V = 151936 21.3 -> 19.3 ms (84 tiles: four parts were two rounds, three are one).
 constexpr int kSplitSlabs = 32;
 
-// Order and grid of a dense layer on the tile kernel; parts: its last round may be cut (without room for the parts, under capture for
-// instance, the tiles stay whole).
+// Order and grid of a dense layer on the tile kernel; parts: its last round may be cut, if the device finds that worth it (without room for the
+// parts, under capture for instance, the tiles stay whole).
 unsigned order_dense(z2z_ctx* c, LogitsArgs& a, bool parts, hipStream_t s) {
   const unsigned grid = z2z_logits_fast_order(a, 0);
-  if (!parts || ensure_partial(c, kSplitBytes, s) != Z2Z_OK) return grid;
+  if (!parts || !z2z_logits_fast_cuts(a) || ensure_partial(c, kSplitBytes, s) != Z2Z_OK) return grid;
   a.split = reinterpret_cast<float*>(c->skinny_partial);
   return 256;
 }

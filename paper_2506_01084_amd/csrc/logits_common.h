@@ -408,6 +408,9 @@ int z2z_launch_logits_general(bool bf16, int columns, const z2z_logits::LogitsAr
 int z2z_launch_logits_fast(int mode, const z2z_logits::LogitsArgs& a, unsigned grid, hipStream_t s);
 // mode 2 with W K-major, and H too (rows_too)
 int z2z_launch_linear_kmajor(const z2z_logits::LogitsArgs& a, bool rows_too, unsigned grid, hipStream_t s);
+// whether the device may cut the last round of a dense layer's tiles along K (LogitsArgs::split; z2z_logits_fast_order first): as far as
+// the host knows the rows and the contraction
+bool z2z_logits_fast_cuts(const z2z_logits::LogitsArgs& a);
 // behind a dense layer launched with LogitsArgs::split, on 256 workgroups: the sums of the tiles that the device has cut along K
 int z2z_launch_tile_sum(const z2z_logits::LogitsArgs& a, hipStream_t s);
 // order and grid of a base part or dense layer (modes 0, 2, 3, 6 - 9): a.row_tiles, n_vtiles and n_strips are set; `forced`:

@@ -220,7 +220,7 @@ __device__ __forceinline__ bool locate_base(const LogitsArgs& a, int row_tiles, 
 }
 
 // Length of that list.
-__device__ __forceinline__ int list_length(const LogitsArgs& a, int row_tiles, int xcd) {
+__host__ __device__ __forceinline__ int list_length(const LogitsArgs& a, int row_tiles, int xcd) {
   const int P = a.map_p_rows ? row_tiles : a.n_strips, Q = a.map_p_rows ? a.n_strips : row_tiles;
   const int blocks = P / (a.map_lp * a.map_xp);
   const int own_q = (Q - xcd / a.map_xp + a.map_xq - 1) / a.map_xq;
@@ -229,7 +229,7 @@ __device__ __forceinline__ int list_length(const LogitsArgs& a, int row_tiles, i
 }
 
 // Length of the longest of the 8 lists, or one more.
-__device__ __forceinline__ int longest_list(const LogitsArgs& a, int row_tiles) {
+__host__ __device__ __forceinline__ int longest_list(const LogitsArgs& a, int row_tiles) {
   const int P = a.map_p_rows ? row_tiles : a.n_strips, Q = a.map_p_rows ? a.n_strips : row_tiles;
   const int blocks = P / (a.map_lp * a.map_xp);
   return blocks * a.map_lp * ((Q + a.map_xq - 1) / a.map_xq) + ((P - blocks * a.map_lp * a.map_xp) * Q + 7) / 8;
@@ -251,7 +251,7 @@ constexpr int F_XCD_WGS = 32;                // workgroups of an XCD that a dens
 constexpr int F_WGS = 8 * F_XCD_WGS;
 constexpr int F_MIN_SAVED = 16;              // slabs
 constexpr int F_MIN_PART = 4;
-__device__ __forceinline__ LastRound last_round(const LogitsArgs& a, int row_tiles, int xcd, int n_slabs) {
+__host__ __device__ __forceinline__ LastRound last_round(const LogitsArgs& a, int row_tiles, int xcd, int n_slabs) {
   const int tiles = row_tiles * a.n_strips, len = list_length(a, row_tiles, xcd);
   LastRound r;
   r.whole = tiles > 0 && tiles <= F_WGS / 2 && F_WGS / tiles > F_XCD_WGS / longest_list(a, row_tiles);
@@ -1320,6 +1320,13 @@ unsigned z2z_logits_fast_order(LogitsArgs& a, int forced) {
   const long long tail = (long long)(P % (a.map_lp * a.map_xp)) * q;
   const long long longest = main_items + (tail + 7) / 8 + (a.hyper.n_work + 7) / 8;
   return 8u * (unsigned)(longest < 32 ? longest : 32);
+}
+
+bool z2z_logits_fast_cuts(const LogitsArgs& a) {
+  if (a.rows_dev || a.k_dev) return true;
+  for (int xcd = 0; xcd < 8; ++xcd)
+    if (last_round(a, a.row_tiles, xcd, a.d * 2 / F_SLAB).ways > 1) return true;
+  return false;
 }
 
 int z2z_launch_linear_kmajor(const LogitsArgs& a, bool rows_too, unsigned grid, hipStream_t s) {

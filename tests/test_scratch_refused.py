@@ -122,6 +122,21 @@ clean()
 """)
 
 
+@pytest.mark.parametrize("B,rows_per_seq,V,cap,d,cut", [
+    (8, 4096, 128256, 2048, 4096, 1),                    # tiles an XCD: dH 256, hyper 256, dW_hyper 128, whole rounds of 32; dW_base 1002, 10 left
+    (8, 3300, 32000, 2048, 1024, 0),                     # 52, 62 and 63, 52: more than half a round left; 32
+    (8, 3300, 32000, 2048, 4096, 2),                     # 208 (dH and its hyper part): 16 left; 250, 128
+    (1, 300, 4096, 100, 128, 1),                         # dH: 2 tiles, 64 slabs
+])
+def test_a_sum_is_launched_where_something_may_be_cut(without_a_device, B, rows_per_seq, V, cap, d, cut):
+    without_a_device(f"""
+h = context(B={B}, V={V}, M=3, cap={cap}, d={d})
+assert nll_backward(h, {B}, {rows_per_seq}) == 0
+log = launches()
+assert len(named(log, "logits_fast_kernel")) == 5 and len(named(log, "tile_sum")) == {cut}, log
+""")
+
+
 def test_the_encoder_takes_shorter_passes_where_long_ones_have_no_room(without_a_device):
     """40 sequences of up to 600 entries of 3 slots: one pass of 72000 rows, or two (546 and 54 entries) of up to 65520."""
     without_a_device("""
