@@ -259,8 +259,8 @@ int z2z_hyper_encode(z2z_ctx* ctx, const void* d_E, const z2z_encoder* encoder, 
  * Without the flag the call runs the forward pass again, keeping every layer's rows, then reverse mode over the
  * same steps; activations and gradients between kernels are bf16, sums fp32; passes of up to 65536 slot rows
  * (matrix gradients of later passes add to the bf16 result of the earlier ones).  Work space (about
- * 2 * (n_layers * (8 d + 2 d_ff) + 8 d + d_ff + 2 max(3 d, d_ff)) bytes per slot row) is library scratch,
- * Z2Z_ENOMEM beyond 200 GB.  Restrictions and errors as for z2z_hyper_encode. */
+ * 2 * (n_layers * (10 d + 2 d_ff) + 9 d + d_ff) bytes per slot row) is library scratch, Z2Z_ENOMEM beyond 200 GB.
+ * Restrictions and errors as for z2z_hyper_encode. */
 #define Z2Z_ENC_KEPT 1
 int z2z_hyper_encode_backward(z2z_ctx* ctx, const void* d_E, const z2z_encoder* encoder, const void* d_dW_hyper,
                               const z2z_encoder* grad, float* d_dE, int32_t flags, void* stream);
@@ -406,10 +406,12 @@ int z2z_read_timing(z2z_ctx* ctx, float* total_ms, int32_t* launches);
  * was created (host-side counters; nothing is read from the device).  Tests use it to make sure that a
  * call ran on the kernel they mean to check; a profile can be matched against it.
  *   counts[Z2Z_KERNEL_TILE_BASE]   bf16 MFMA tile kernel, base-vocabulary launches (any epilogue)
- *   counts[Z2Z_KERNEL_TILE_HYPER]  bf16 MFMA tile kernel, per-sequence hyper-vocabulary launches
+ *   counts[Z2Z_KERNEL_TILE_HYPER]  bf16 MFMA tile kernel, launches with the per-sequence hyper vocabulary: alone, or in a base-vocabulary
+ *                                  launch, which then counts as both
  *   counts[Z2Z_KERNEL_GENERAL]     the general tile kernel (fp32, d not a multiple of 64, full logits)
  *   counts[Z2Z_KERNEL_DECODE]      the one-row-per-sequence (bandwidth-bound) kernel
- *   counts[Z2Z_KERNEL_MID]         the weight-streaming kernel for the base part of calls with up to 192 hidden rows
+ *   counts[Z2Z_KERNEL_MID]         the weight-streaming kernel for the base part of calls with up to 192 hidden rows (and, with more than 64
+ *                                  rows per sequence, their hyper part)
  * `counts` is a host array of Z2Z_N_KERNEL_FAMILIES elements. */
 enum { Z2Z_KERNEL_TILE_BASE = 0, Z2Z_KERNEL_TILE_HYPER = 1, Z2Z_KERNEL_GENERAL = 2, Z2Z_KERNEL_DECODE = 3,
        Z2Z_KERNEL_MID = 4, Z2Z_N_KERNEL_FAMILIES = 5 };

@@ -34,7 +34,8 @@ def test_backward(B, N, V, d, M, cap, n_layers, n_heads, d_ff, attn_only, with_p
 
 
 def test_entries_in_two_passes():
-    """75 x 600 x 3 = 135000 slot rows, more than one pass takes (131072): passes of 582 and 18 entries per sequence."""
+    """75 x 600 x 3 = 135000 slot rows, more than one pass takes (131072): passes of 582 and 18 entries per sequence.  The second
+    feed-forward layer is cut in both: about 73000 rows, the 35 or 36 tiles of an XCD less a whole round of 32; about 1500, 7 tiles in all."""
     import torch
 
     B, N, V, d, M, cap = 75, 1500, 3000, 64, 3, 600
@@ -42,13 +43,15 @@ def test_entries_in_two_passes():
     print("[case] hyper_encode in two passes", flush=True)
     lens = wl.make_lens(cfg, ragged=True)
     ctx, ref, E, d_E = _setup(cfg, lens)
-    enc = wl.make_encoder(cfg, n_layers=1, n_heads=2, d_ff=128)
+    enc = wl.make_encoder(cfg, n_layers=1, n_heads=2, d_ff=2048)
     d_W = torch.full((B, cap, d), 3.0, dtype=torch.bfloat16, device="cuda")
     ctx.hyper_encode(d_E, encoder_to_device(enc, "bf16"), d_W)
     torch.cuda.synchronize()
     W = storage_to_host(d_W, "bf16")
     longest = int(np.argmax([len(r[1]) for r in ref]))
     assert len(ref[longest][1]) > 582, "the case must reach the second pass"
+    rows = [sum(len(e) for r in ref for e in part(r[1])) for part in (lambda e: e[:582], lambda e: e[582:])]
+    assert 8 <= (rows[0] + 255) // 256 - 256 <= 128 and 2 <= (rows[1] + 255) // 256 <= 128, rows
     for b in (0, longest, B - 1):
         entries = ref[b][1]
         want = oracle.hyper_encode(E, "bf16", entries, cap, enc, rounded=False)

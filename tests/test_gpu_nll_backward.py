@@ -205,8 +205,8 @@ def test_edge_cases_no_hypertokens_no_targets_and_odd_row_counts():
 
 @pytest.mark.parametrize("cap", [40, 0])
 def test_last_chunk_whose_rows_are_a_multiple_of_2048(cap):
-    """33 + 32 sequences of 64 rows: chunks of 2112 and of 2048 rows, the shorter one with the padded pitch, in a work
-    space that is laid out for the longer one."""
+    """33 + 32 sequences of 64 rows: chunks of 2112 and of 2048 rows, the shorter one in a work space that is laid out for the
+    longer one."""
     import torch
     from paper_2506_01084_amd import api
 
