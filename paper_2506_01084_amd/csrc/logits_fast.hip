@@ -707,7 +707,9 @@ __device__ __forceinline__ void merge_rows(R (&a)[F_N], S swap) {
 // slab every request in flight goes to the same 128-byte column of rows a power of two apart, and with it to the
 // same few memory channels.  (With many row tiles the workgroups that share operands through L2 and the
 // memory-side cache must stay in step: there the rotation costs 1-2 %, and so does its arithmetic alone; with two
-// row tiles it is level or 1 % slower.  A decode step of 256 sequences: 646 -> 634 us, with a filtered draw 704 -> 675.)
+// row tiles it is level or 1 % slower.  A decode step of 256 sequences: 646 -> 634 us, with a filtered draw 704 -> 675.  With the hyper part
+// along, V = 128256, d = 4096: 1 x 193 rows 250 us in step, 240 rotated; where its items open a third round, 3 x 65 with 2048 entries each,
+// 317, 293, and 292 in two launches.)
 //
 // A workgroup walks its XCD's list (locate_base) from its own position on, in steps of the workgroups an XCD has: the
 // operand stream runs on from one output tile to the next, and a tile's epilogue finds the next one's first two slabs on the
@@ -722,7 +724,7 @@ __device__ __forceinline__ void merge_rows(R (&a)[F_N], S swap) {
 template <int MODE, bool ROT = false, bool TW = false, bool TH = false, bool HYP = false>
 __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
   static_assert((MODE == 2 || !TW) && (TW || !TH), "dense layers only, and H K-major only where W is");
-  static_assert(!HYP || ((MODE == 0 || MODE == 3) && !ROT), "");
+  static_assert(!HYP || MODE == 0 || (MODE == 3 && !ROT), "");
   constexpr bool PROBE_NOREQ = MODE == 8 || MODE == 9;
   constexpr bool PROBE_MFMA = MODE == 9;
   constexpr bool LIST = MODE != 1 && MODE != 5;
@@ -946,7 +948,7 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
     for (int i = 0; i < F_PAIRS; ++i)
       voffB[i] = TH ? krow_offset(i, ((int)pitch_h - h_col) >> 4, pitch_h)
                     : row_offset(i, at.r_end - 1 - r0, pitch_h);
-    if (ROT) rot = st % n_slabs;
+    if (ROT) rot = __builtin_amdgcn_readfirstlane(st % n_slabs);
     set_tile(lvt);
   };
   // request the slab that follows in the stream, if any, and advance the cursor.  A request is 16 instructions per
@@ -1346,6 +1348,8 @@ int z2z_launch_logits_fast(int mode, const LogitsArgs& a, unsigned grid, hipStre
       hipLaunchKernelGGL((logits_fast_kernel<3, false, false, false, true>), dim3(grid), dim3(F_THREADS), F_HYP_LDS, s, a);
     else if (mode != 0)
       return Z2Z_EUNSUPPORTED;
+    else if (rot)
+      hipLaunchKernelGGL((logits_fast_kernel<0, true, false, false, true>), dim3(grid), dim3(F_THREADS), F_HYP_LDS, s, a);
     else
       hipLaunchKernelGGL((logits_fast_kernel<0, false, false, false, true>), dim3(grid), dim3(F_THREADS), F_HYP_LDS, s, a);
     Z2Z_HIP_TRY(hipGetLastError());
@@ -1398,6 +1402,8 @@ int z2z_logits_fast_prepare(z2z_ctx* c) {
   Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(logits_fast_kernel<3>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, F_LDS));
   Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(logits_fast_kernel<0, false, false, false, true>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, F_HYP_LDS));
+  Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(logits_fast_kernel<0, true, false, false, true>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, F_HYP_LDS));
   Z2Z_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(logits_fast_kernel<3, false, false, false, true>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, F_HYP_LDS));

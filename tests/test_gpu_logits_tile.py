@@ -73,6 +73,7 @@ def _run(ctx, d_H, rows_per_seq, d_Wb, d_Wh, strip, mapping):
     (9, 33, 300, 576, 3, 257, "mean"),          # nine slabs, 297 rows, cap one column past a tile
     (2, 100, 1300, 320, 3, 300, "mean"),        # 200 rows, a single row tile: the weight tiles walk K from different slabs
     (1, 250, 2100, 192, 3, 0, "mean"),          # the same with three slabs and nine weight tiles (every start, wrapping round)
+    (3, 80, 500, 128, 3, 515, "mean"),          # the same with more hyper tiles than slabs, the last of three columns
     (63, 66, 300, 64, 3, 130, "mean"),          # many sequences' hyper items: found with one look at the table, ...
     (65, 66, 300, 64, 3, 300, "mean"),          # ... with two, ...
     (300, 66, 200, 64, 3, 260, "mean"),         # ... several sequences a thread when it is made
