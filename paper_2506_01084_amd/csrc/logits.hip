@@ -675,10 +675,12 @@ int z2z_launch_extended_sample(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     // (hyper units of 512 rows are too few for a small batch: smaller ones, while the short-list pass takes as many parts.  21 sequences of up to
     // 4096 entries, V = 32064 121 -> 84 us, 20 x 1024, V = 128256 271 -> 213, 6 x 4096, V = 151936 291 -> 250.  From 200 of 512 rows on those
     // are the better ones here: a unit's logits leave it row by row, 108 x 1024 356 us, 361 in 432 of 256; 56 x 2048 341 and 348, 32 x 4096 338
-    // and 349.  Below that, room for more than 2048 entries is seldom full and the units that exist are few of them: 21 x 730 of 4096 96 us in 336
-    // units, 84 in 672)
-    const bool roomy = c->cfg.cap > 2048 && (long long)rows * ((c->cfg.cap + 511) / 512) < 200;
-    hyper_columns = z2z_logits_decode_hyper_unit(c, roomy ? 512 : 200);
+    // and 349.  Below that at least 512 where those of 256 would be more than a round (129 to 199 of 512; units of 512 / 256 / 128 rows, codebooks full:
+    // 33 x 2048, V = 128256 283 / 304 / 286 us, V = 32064 133 / 145 / 130, V = 151936 318 / 333 / 312; 96 x 1024 314 / 323 / 317, 150 / 156 / 150, 346 /
+    // 352 / 344; a third full 40 x 2048 271 / 237 / 227, 120 / 94 / 84, 301 / 271 / 260) and where room for more than 2048 entries is seldom full and the units
+    // that exist are few of them (21 x 730 of 4096 96 us in 336 units, 84 in 672; full 8 x 4096, V = 128256 260 -> 221))
+    const long long wide = (long long)rows * ((c->cfg.cap + 511) / 512);
+    hyper_columns = z2z_logits_decode_hyper_unit(c, wide < 200 && (c->cfg.cap > 2048 || wide > 128) ? 512 : 200);
     while (hyper_columns < 512 && base_strips + (c->cfg.cap + hyper_columns - 1) / hyper_columns > z2z_sample_list_parts()) hyper_columns *= 2;
     n_parts = base_strips + (c->cfg.cap + hyper_columns - 1) / hyper_columns;
     base_columns = mid_base ? mid_columns : strip_b * 256;

@@ -9,7 +9,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("B,cap,unit", [
     (66, 130, 64),        # three units of 64, the last of two rows
     (66, 330, 64),        # 198 units of 128 would be too few
-    (70, 600, 256),       # 140 units of 512
+    (110, 500, 256),      # 110 units of 512
+    (70, 600, 128),       # 140: those of 256 would be more than a round
     (110, 1000, 512),     # 220
     (70, 2100, 512),      # 350 units, roomy but enough of them
     (66, 64, 64),
