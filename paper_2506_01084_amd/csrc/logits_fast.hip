@@ -773,6 +773,7 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
     Hm += (size_t)ks * a.slabs_per_part * F_SLAB;
   }
   const int n_vt = min(a.n_vtiles, (n_valid + FT - 1) / FT);
+  const int strip = MODE == 2 ? 1 : a.strip;
   int n_slabs = MODE == 5 ? min(a.slabs_per_part, (int)(row_bytes / F_SLAB) - ks * a.slabs_per_part)
                           : (int)(row_bytes / F_SLAB);
   if (MODE == 2) n_slabs = dense_slabs(a);
@@ -830,7 +831,7 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
   };
   // (where all strips are one tile the base part's last ones and the hyper items are dealt out as one; else every XCD goes on with every eighth
   // of these behind its base list: the longer strips of the base part have to be dealt out evenly by themselves, 9 x 263 rows 1930 us, 2155 as one)
-  const bool together = HYP && a.strip == 1 && a.hyper.strip == 1;
+  const bool together = HYP && strip == 1 && a.hyper.strip == 1;
   const int base_items = HYP && !together ? list_length(a, row_tiles_now, (int)(blockIdx.x & 7)) : 0;
   auto item = [&](int j, Item* it) -> bool {
     it->s0 = 0;
@@ -891,7 +892,7 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
       return Part{reinterpret_cast<const unsigned char*>(a.hyper.W) + (size_t)it.b * a.hyper.cap * row_bytes, n, (n + FT - 1) / FT,
                   (it.b + 1) * a.rows_per_seq, a.hyper.strip};
     }
-    return Part{TW ? Wp + (size_t)it.b * a.batch_w * 2 : Wp, n_valid, n_vt, TW && a.batch > 1 ? (it.b + 1) * a.rows : r_end, a.strip};
+    return Part{TW ? Wp + (size_t)it.b * a.batch_w * 2 : Wp, n_valid, n_vt, TW && a.batch > 1 ? (it.b + 1) * a.rows : r_end, strip};
   };
 
   // ---- loader: lane l of wave w, instruction i moves the chunk that lands at LDS byte
@@ -915,7 +916,7 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
   };
   uint32_t voffA[F_PAIRS], voffB[F_PAIRS];
   const unsigned char* Wtile = Wp;
-  Part at = {Wp, 0, 0, 0, 1};
+  Part at = {Wp, n_valid, n_vt, r_end, strip};       // (one for all items but with the hyper part and in a batch)
   const unsigned char* Hp = Hm;
   // ---- the cursor of the operand stream: slab lslab of weight tile lvt of the item at position lj (none: !live) ----------
   int lj = first, lslab = 0, lslab_end = n_slabs, lvt = 0, lvt_end = 0, rot = 0;
@@ -933,13 +934,13 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
     Item it;
     live = item(lj, &it);
     if (!live) return;
-    at = part_of(it);
+    if (HYP || TW) at = part_of(it);
     lvt = it.st * at.strip;
     lvt_end = min(lvt + at.strip, at.n_vt);
     const int r0 = it.r0, st = it.st;
     lslab = it.s0;
     lslab_end = it.s0 + it.sn;
-    live = lvt < lvt_end;
+    if (MODE != 2) live = lvt < lvt_end;       // (a tile of a dense layer exists)
     if (!live) return;
     if (TH) h_col = (r0 - it.b * a.rows) * 2;
     Hp = Hm + (TH ? (size_t)h_col : (size_t)r0 * pitch_h);
@@ -999,7 +1000,7 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
   auto issue_end = [&]() {
     if (live && ++lslab == lslab_end) {
       lslab = 0;                               // (a strip of several tiles is never a part)
-      if (++lvt < lvt_end) {
+      if (MODE != 2 && ++lvt < lvt_end) {
         set_tile(lvt);
       } else {
         lj += step;
