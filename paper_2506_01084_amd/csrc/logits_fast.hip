@@ -833,7 +833,9 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
   // of these behind its base list: the longer strips of the base part have to be dealt out evenly by themselves, 9 x 263 rows 1930 us, 2155 as one)
   const bool together = HYP && strip == 1 && a.hyper.strip == 1;
   const int base_items = HYP && !together ? list_length(a, row_tiles_now, (int)(blockIdx.x & 7)) : 0;
-  auto item = [&](int j, Item* it) -> bool {
+  // (behind: j is not the workgroup's first position.  There are copies of this at every place where the operand stream may go on to another
+  // item, and what a whole cut needs is left out of most of them)
+  auto item = [&](int j, Item* it, bool behind) __attribute__((always_inline)) -> bool {
     it->s0 = 0;
     it->sn = n_slabs;
     it->part = -1;
@@ -845,6 +847,7 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
     }
     int rt;
     const int xcd = (int)(blockIdx.x & 7);
+    if (MODE == 2 && behind && last.whole && last.ways > 1) return false;
     if (MODE == 2 && last.ways > 1 && j >= last.full) {
       const int g = last.whole ? xcd * F_XCD_WGS + j : j - last.full, ks = __builtin_amdgcn_readfirstlane(g / last.rem);
       if (ks >= last.ways || (last.whole && j >= F_XCD_WGS)) return false;
@@ -853,7 +856,7 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
       it->part = last.whole ? g : xcd * F_XCD_WGS + g;
       j = last.full + g - ks * last.rem;
     }
-    if (MODE == 2 && last.ways > 1 && last.whole)
+    if (MODE == 2 && !behind && last.ways > 1 && last.whole)
       locate_whole(a, row_tiles_now, j, &rt, &it->st);
     else if (!locate_base(a, row_tiles_now, xcd, j, &rt, &it->st, HYP && together ? hyper_items : 0, HYP ? &it->b : nullptr)) {
       if (!HYP || together) return false;
@@ -929,10 +932,10 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
     for (int i = 0; i < F_PAIRS; ++i)
       voffA[i] = TW ? krow_offset(i, ((int)pitch_w - w_col) >> 4, pitch_w) : row_offset(i, at.n_valid - 1 - vt * FT, pitch_w);
   };
-  auto open_item = [&]() {
+  auto open_item = [&](bool behind) __attribute__((always_inline)) {
     if (HYP) asm volatile("" : "+s"(lj));       // (what is worked out here is not worked out for every slab)
     Item it;
-    live = item(lj, &it);
+    live = item(lj, &it, behind);
     if (!live) return;
     if (HYP || TW) at = part_of(it);
     lvt = it.st * at.strip;
@@ -1004,7 +1007,7 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
         set_tile(lvt);
       } else {
         lj += step;
-        open_item();
+        open_item(true);
       }
     }
   };
@@ -1112,7 +1115,7 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
       a.part_i[q] = kNoColumn;
     }
   }
-  open_item();
+  open_item(false);
   if (live) {
     // prologue: the first two slabs of the stream requested; the first landed and visible, the fragments of its first
     // k-step on the way
