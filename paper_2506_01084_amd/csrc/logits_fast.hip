@@ -228,11 +228,22 @@ __host__ __device__ __forceinline__ int list_length(const LogitsArgs& a, int row
   return blocks * a.map_lp * own_q + (int)(total * (xcd + 1) / 8) - (int)(total * xcd / 8);
 }
 
-// Length of the longest of the 8 lists, or one more.
-__host__ __device__ __forceinline__ int longest_list(const LogitsArgs& a, int row_tiles) {
-  const int P = a.map_p_rows ? row_tiles : a.n_strips, Q = a.map_p_rows ? a.n_strips : row_tiles;
-  const int blocks = P / (a.map_lp * a.map_xp);
-  return blocks * a.map_lp * ((Q + a.map_xq - 1) / a.map_xq) + ((P - blocks * a.map_lp * a.map_xp) * Q + 7) / 8;
+// The lengths of an XCD's list and of the longest.  (On the device every lane works out one of them: the whole wave calls.)
+__host__ __device__ __forceinline__ void list_lengths(const LogitsArgs& a, int row_tiles, int xcd, int* own, int* longest) {
+#ifdef __HIP_DEVICE_COMPILE__
+  int len = list_length(a, row_tiles, (int)(threadIdx.x & 7));
+  *own = __builtin_amdgcn_readlane(len, xcd);
+#pragma unroll
+  for (int o = 1; o < 8; o <<= 1) len = max(len, __shfl_xor(len, o));
+  *longest = __builtin_amdgcn_readfirstlane(len);
+#else
+  *own = list_length(a, row_tiles, xcd);
+  *longest = 0;
+  for (int x = 0; x < 8; ++x) {
+    const int len = list_length(a, row_tiles, x);
+    *longest = *longest < len ? len : *longest;
+  }
+#endif
 }
 
 // A dense layer's last round.  The 32 workgroups of an XCD take 32 output tiles of its list at a time; the `rem` tiles that are
@@ -242,7 +253,9 @@ __host__ __device__ __forceinline__ int longest_list(const LogitsArgs& a, int ro
 // is part g / tiles of tile g % tiles (84 tiles, 10 or 11 an XCD, K = 151936: three parts instead of two, 1698 -> 1118 us; with as many parts either
 // way the XCDs' own tiles are the better ones, 70 tiles, K = 14336 146 against 160 us: a weight tile is fetched by one XCD).  The fp32 sums of a part go to the tile buffer of its workgroup, and
 // tile_sum_kernel adds the parts up, in order, with the layer's epilogue.  Decided here, where the row count is known: the host lays
-// out rows for codebooks that are full.  A part is worth it from 16 slabs saved on (17-20 us; the sum reads at most 64 MB, about 10).
+// out rows for codebooks that are full.  A part is worth it from 16 slabs saved on (17-20 us; the sum reads at most 64 MB, about 10), in the XCD
+// with the most tiles: the launch ends with that one.  (132 tiles, 16 or 17 an XCD, 48 slabs: whole 78 us, 102 with the sum where those of
+// 16 were cut; 144 tiles of 64 slabs 87 and 106, 704, the last round half full on some, 310 and 330.)
 // (Runs of slabs as long as each other, across tiles, keep every CU busy but not at one place of K: 1.10 times the time at 2644 rows.)
 struct LastRound {
   int full, rem, ways, per, whole;
@@ -251,22 +264,26 @@ constexpr int F_XCD_WGS = 32;                // workgroups of an XCD that a dens
 constexpr int F_WGS = 8 * F_XCD_WGS;
 constexpr int F_MIN_SAVED = 16;              // slabs
 constexpr int F_MIN_PART = 4;
+// Slabs of a part where `tiles` tiles of n_slabs share `wgs` workgroups.
+__host__ __device__ __forceinline__ int part_slabs(int wgs, int tiles, int n_slabs) {
+  const int most = n_slabs / F_MIN_PART > 1 ? n_slabs / F_MIN_PART : 1, ways = wgs / tiles < most ? wgs / tiles : most;
+  return (n_slabs + ways - 1) / ways;
+}
 __host__ __device__ __forceinline__ LastRound last_round(const LogitsArgs& a, int row_tiles, int xcd, int n_slabs) {
-  const int tiles = row_tiles * a.n_strips, len = list_length(a, row_tiles, xcd);
+  const int tiles = row_tiles * a.n_strips;
+  int len, longest;
+  list_lengths(a, row_tiles, xcd, &len, &longest);
   LastRound r;
-  r.whole = tiles > 0 && tiles <= F_WGS / 2 && F_WGS / tiles > F_XCD_WGS / longest_list(a, row_tiles);
+  r.whole = tiles > 0 && tiles <= F_WGS / 2 && F_WGS / tiles > F_XCD_WGS / longest;
   r.full = r.whole ? 0 : len & ~(F_XCD_WGS - 1);
   r.rem = r.whole ? tiles : len - r.full;
   r.ways = 1;
   r.per = n_slabs;
-  const int wgs = r.whole ? F_WGS : F_XCD_WGS;
-  if (r.rem > 0 && r.rem <= wgs / 2) {
-    const int ways = min(wgs / r.rem, max(n_slabs / F_MIN_PART, 1));
-    const int per = (n_slabs + ways - 1) / ways;
-    if (n_slabs - per >= F_MIN_SAVED) {
-      r.ways = (n_slabs + per - 1) / per;    // no empty parts
-      r.per = per;
-    }
+  // (what the XCD with the most tiles left gains decides: the launch ends with that one)
+  const int wgs = r.whole ? F_WGS : F_XCD_WGS, most = r.whole ? tiles : longest - r.full;
+  if (r.rem > 0 && most <= wgs / 2 && n_slabs - part_slabs(wgs, most, n_slabs) >= F_MIN_SAVED) {
+    r.per = part_slabs(wgs, r.rem, n_slabs);
+    r.ways = (n_slabs + r.per - 1) / r.per;    // no empty parts
   }
   return r;
 }
@@ -1133,7 +1150,7 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
     if (PROBE_MFMA) static_for<Sched::reads>([&](auto e) __attribute__((always_inline)) { read_one(f[1], 0, kOne, e, std::false_type{}); });
   }
   Item it;
-  for (int j = first; item(j, &it); j += step) {
+  for (int j = first; item(j, &it, false); j += step) {
     const int r0 = it.r0, st = it.st;
     const Part p = part_of(it);
     const bool hyper = HYP && it.b >= 0;

@@ -127,6 +127,7 @@ clean()
     (8, 3300, 32000, 2048, 1024, 0),                     # 52, 62 and 63, 52: more than half a round left; 32
     (8, 3300, 32000, 2048, 4096, 2),                     # 208 (dH and its hyper part): 16 left; 250, 128
     (1, 300, 4096, 100, 128, 1),                         # dH: 2 tiles, 64 slabs
+    (1, 2816, 4096, 100, 3072, 1),                       # dH: 16 tiles, 17 on some: whole; dW_base 24; dW_hyper 12 tiles in all, 44 slabs
 ])
 def test_a_sum_is_launched_where_something_may_be_cut(without_a_device, B, rows_per_seq, V, cap, d, cut):
     without_a_device(f"""
