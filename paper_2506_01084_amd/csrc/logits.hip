@@ -342,22 +342,22 @@ static int pick_strip_for(const z2z_ctx* c, long long row_tiles, int n_vt, int w
 //   tiles (of the rounds')            8 sequences   24           40           64
 //   256 (V = 65536)         greedy    191 -> 103    201 -> 124   204 -> 142   203 -> 169
 //                           draw      211 -> 112    220 -> 130   224 -> 153   223 -> 180
-//                           filtered  208 -> 177    219 -> 183   228 -> 189   230 -> 198
+//                           filtered  206 -> 117    218 -> 135   225 -> 164   227 -> 185
 //   313 (of 512, 80000)     greedy    193 -> 154    207 -> 174   209 -> 193   224 -> 222
 //                           draw      214 -> 164    226 -> 186   228 -> 211   231 -> 240
-//                           filtered  212 -> 229    226 -> 235   234 -> 244   249 -> 253
+//                           filtered  208 -> 167    224 -> 186   231 -> 217   239 -> 238
 //   384 (of 512, 98304)     greedy    198 -> 159    216 -> 178   238 -> 197   238 -> 224
 //                           draw      218 -> 169    232 -> 187   245 -> 214   241 -> 244
-//                           filtered  217 -> 230    233 -> 243   259 -> 254   263 -> 264
+//                           filtered  215 -> 169    234 -> 192   256 -> 228   257 -> 250
 //   448 (of 512, 114688)    greedy    214 -> 162    242 -> 182   290 -> 202   303 -> 230
 //                           draw      233 -> 174    254 -> 192   320 -> 220   327 -> 251
-//                           filtered  235 -> 235    263 -> 251   319 -> 265   335 -> 276
+//                           filtered  231 -> 175    261 -> 202   316 -> 239   332 -> 262
 //   501 (of 512, 128256)    greedy    282 -> 180    289 -> 198   298 -> 217   307 -> 247
 //                           draw      316 -> 189    321 -> 209   326 -> 238   332 -> 270
-//                           filtered  305 -> 254    316 -> 268   326 -> 277   342 -> 288
+//                           filtered  312 -> 193    317 -> 219   330 -> 253   343 -> 275
 //   594 (of 768, 151936)    greedy    262 -> 208    270 -> 227   283 -> 246   305 -> 271
 //                           draw      294 -> 222    302 -> 243   310 -> 274   331 -> 303
-//                           filtered  288 -> 281    301 -> 297   316 -> 309   341 -> 319
+//                           filtered  284 -> 224    298 -> 252   312 -> 283   337 -> 303
 // Behind other work that has turned the caches over the one launch is 40-60 us slower and the split 2-5.
 // Hence: up to 16 sequences, or more than two rounds, or a last round at least 7/8 full over all rounds, or hyper units that
 // would open another round in one launch.
@@ -367,15 +367,16 @@ static int pick_strip_for(const z2z_ctx* c, long long row_tiles, int n_vt, int w
 //                         126: 24 x 1024 79 -> 72 (113 -> 73), 40 x 1024 86 -> 86 (130 -> 87), 17 x 4096 (of 262) 149 -> 118 (198 -> 119)
 //                         160: 17 x 4096 151 -> 131 (205 -> 131)   197: 40 x 1024 149 -> 103 (205 -> 103)   254: 8 x 4096 143 -> 103 (196 -> 103)
 //             draw        112: 5 x 1024 85 -> 65, 24 x 2048 95 -> 96    126: 40 x 1024 93 -> 95, 17 x 4096 168 -> 126    254: 8 x 4096 163 -> 111
-//             filtered    126: 17 x 4096 169 -> 138    197: 40 x 1024 173 -> 148    254: 8 x 4096 164 -> 150, 64 x 4096 349 -> 332
+//             filtered    126: 17 x 4096 153 -> 129    197: 40 x 1024 164 -> 120    254: 8 x 4096 159 -> 112, 64 x 4096 344 -> 323
 //   d = 1024, greedy      112: 40 x 1024 46 -> 42 (58 -> 42)   126: 17 x 4096 58 -> 55 (77 -> 55)   197: 40 x 1024 64 -> 48 (83 -> 50)
 //             draw        112: 40 x 1024 71 -> 52    126: 17 x 4096 78 -> 65    254: 40 x 1024 86 -> 67
 //   d = 4096, greedy      126: 8 x 4096 106 -> 99 (148 -> 100)   160: 64 x 1024 197 -> 149 (242 -> 150)   254: 40 x 1024 204 -> 146 (263 -> 144)
 // (d = 512, 768, 1536, 2048 alike; 24 x 2048 over 112 tiles at d = 2048 62 -> 67 in a row, 85 -> 67 behind other writes.)  The split needs
 // halved tiles (up to 128) as long as all fits one round, and up to 208 tiles and units; above a round it needs 64 units, which
-// count whole however few entries they have, so that they are what opens it.  Filtered steps, which store their logits, stay in one launch
-// where all fits one round (5 x 1024 104 -> 124), and for short rows (d <= 1024) until the units fill half of another (d = 1024, 197 tiles: 40 x
-// 1024 86 -> 92, 64 x 1024 91 -> 97; 254: 8 x 4096 81 -> 92; d = 512, 126: 17 x 4096 79 -> 70, 50 x 2048 over 112 89 -> 72).
+// count whole however few entries they have, so that they are what opens it.  Filtered steps stay in one launch
+// where all fits one round, and for short rows (d <= 1024) until the units fill half of another.  That line was drawn when their split had hyper
+// units of 512 rows (5 x 1024 over 112 tiles 104 -> 124; d = 1024, 197 tiles: 40 x 1024 86 -> 92; 254: 8 x 4096 81 -> 92) and lies too high for
+// units of 64 to 256 (78 -> 64, 79 -> 60, 74 -> 58; d = 512, 126: 17 x 4096 75 -> 48, 50 x 2048 over 112 79 -> 60).
 static bool split_few(const z2z_ctx* c, int rows, bool filtered) {
   const long long tiles = z2z_logits_mid_tiles(c->cfg.V), slots = (tiles + 255) / 256 * 256;
   int base_columns, hyper_columns;
@@ -528,8 +529,11 @@ int z2z_launch_extended_logits(z2z_ctx* c, const void* H, int32_t rows, int32_t 
     return launch_combine(parts, n_parts, rows, argmax, mx, lse, s);
   }
 
-  // Both parts in one launch of the tile kernel (the measurement probes run the base part alone), up to 32768 tiles: 14875 rows x 128256 (29559
-  // tiles) 11.57 -> 11.45 ms, 32768 rows (64128) 23.42 -> 23.56, where the hyper part is a hundredth of the call and its launch full anyway.
+  // Both parts in one launch of the tile kernel (the measurement probes run the base part alone), up to 32768 tiles, where the hyper part is a hundredth
+  // of the call and its launch full anyway.  Two launches -> one, us: V = 32064, d = 3072 (126 tiles a row of them) 32 x 512 rows 2283 -> 2235, 128 x 128
+  // 2275 -> 2211, 500 x 66 5035 -> 4956, 8 x 1024, 8 x 4096 and 16 x 4096 (32256 tiles) within 0.8 % either way; V = 128256, d = 4096 (501) 8 x 512
+  // 2993 -> 2912, 8 x 1100 6964 -> 6872, 8 x 1800 level, 4 x 4100 (32565) 12463 -> 12403, 8 x 4096 (64128) 23420 -> 23560; V = 8192, d = 1024, 64 x 4000 (32000)
+  // 3998 -> 3810.  (The same code twice: 0.6 % at that length.)
   const bool one_launch = !mid_base && cap > 0 && !decode_split && !seq_split && c->opt_logits_kernel != 2 && c->opt_logits_kernel != 3 &&
                           c->cfg.B <= z2z_logits_fast_sequences() && tiles_b * base_vt <= 32768;
   if (one_launch) z2z_add_hyper_part(c, a, W_hyper, base_strips, strip_h, rows_per_seq, 0, c->cfg.B);
