@@ -147,6 +147,13 @@ __device__ __forceinline__ uint32_t bf16_bits_rne(float f) {
   return u >> 16;
 }
 
+// Two values, rounded to nearest even in one instruction; a NaN stays one, whatever its bits (the sum above carries 0xFFFFFFFF over to 0).
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+  typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+  typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
+
 // GELU(x) = x * Phi(x) with the exact (erf) Phi.  erf by the rational approximation 7.1.26 of Abramowitz and
 // Stegun, erf(z) = 1 - (a1 t + ... + a5 t^5) exp(-z^2), t = 1 / (1 + p z), z >= 0: absolute error below
 // 1.5e-7, far inside the bf16 rounding of the result, at a third of the instructions of the library erff (the

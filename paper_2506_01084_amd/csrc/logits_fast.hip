@@ -490,13 +490,6 @@ __device__ __forceinline__ uint4 eight_columns(uint2 lo, uint2 hi) {
   return uint4{x[0], y[0], x[1], y[1]};
 }
 
-// Rounds to nearest even (one instruction for two values).
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
-  typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
-  typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
-}
-
 // Stores two blocks' bf16 (columns col_base + i * 16 ..., and the next 16) of one row in 16-byte pieces; columns come in
 // fours, and n_valid and the row pitch are multiples of 8 (the layers' widths are).
 __device__ __forceinline__ void store_two_blocks(uint16_t* out_row, bool row_ok, int col_base, int i, uint2 lo, uint2 hi,

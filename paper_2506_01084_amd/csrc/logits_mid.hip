@@ -119,8 +119,7 @@ __device__ __forceinline__ void store_prob_tile(const f32x16 (&acc)[1][NJV], con
         x[e] = col + e < t.n_valid ? g * p : 0.f;
       }
       if (col < t.ldo)                     // (a multiple of 64)
-        *reinterpret_cast<uint2*>(out + col) =
-            uint2{bf16_bits_rne(x[0]) | (bf16_bits_rne(x[1]) << 16), bf16_bits_rne(x[2]) | (bf16_bits_rne(x[3]) << 16)};
+        *reinterpret_cast<uint2*>(out + col) = uint2{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3])};
     }
   }
 }

@@ -90,3 +90,38 @@ def test_log_probability(B, V, d, top_k, top_p):
 
     _check(H, run)
     ctx.close()
+
+
+@pytest.mark.parametrize("B,rows_per_seq,V,d,cap", [
+    (1, 70, 600, 64, 40),           # weight-streaming kernel, both parts
+    (4, 30, 33000, 64, 40),         # ... tiles of 256 columns, several sequences
+    (2, 150, 600, 64, 40),          # tile kernel
+])
+@pytest.mark.parametrize("bits", [0x7FC00000, 0x7FFFFFFF, -1])
+def test_gradient_of_a_loss_whose_weight_is_nan(B, rows_per_seq, V, d, cap, bits):
+    """A row whose loss has a NaN, of any bits, for its weight has NaN for its gradient; the other rows read the bits they have without it."""
+    import torch
+
+    print(f"[case] gradient, B={B} x {rows_per_seq} V={V} d={d} cap={cap} NaN {bits & 0xFFFFFFFF:#x}", flush=True)
+    ctx, E, W, H = _setup(B, rows_per_seq, V, d, cap, "bf16", fill=True)
+    E, W = E * d ** -0.5, W * d ** -0.5
+    rows = B * rows_per_seq
+    targets = torch.arange(rows, device="cuda", dtype=torch.int32) % V
+    nll, lse, weight = torch.zeros(rows, device="cuda"), torch.zeros(rows, device="cuda"), torch.ones(rows, device="cuda")
+    ctx.extended_nll(H, rows_per_seq, E, W, targets, nll, lse)
+
+    def run():
+        dH, dE, dW = torch.zeros_like(H), torch.zeros_like(E), torch.zeros_like(W)
+        ctx.extended_nll_backward(H, rows_per_seq, E, W, targets, lse, weight, dH, dE, dW)
+        torch.cuda.synchronize()
+        return dH, dE, dW
+
+    want = run()
+    assert not any(torch.isnan(x).any() for x in want)
+    row = rows // 2
+    weight.view(torch.int32)[row] = bits
+    dH, dE, dW = run()
+    others = torch.arange(rows, device="cuda") != row
+    assert torch.isnan(dH[row]).all() and torch.equal(dH[others], want[0][others])
+    assert torch.isnan(dE).all()
+    ctx.close()
