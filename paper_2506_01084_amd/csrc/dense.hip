@@ -31,41 +31,8 @@ __global__ void __launch_bounds__(256) linear_sum_kernel(const float* partial, i
     x.z += y.z;
     x.w += y.w;
   }
-  if (bias) {
-    const float4 b = *reinterpret_cast<const float4*>(bias + col);
-    x.x += b.x;
-    x.y += b.y;
-    x.z += b.z;
-    x.w += b.w;
-  }
-  if (act == 1) {
-    x.x = gelu_erf(x.x);
-    x.y = gelu_erf(x.y);
-    x.z = gelu_erf(x.z);
-    x.w = gelu_erf(x.w);
-  }
-  if (stream_f32) {                                  // fp32 residual and output: no rounding
-    if (residual) {
-      const float4 rv = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(residual) + at);
-      x.x += rv.x;
-      x.y += rv.y;
-      x.z += rv.z;
-      x.w += rv.w;
-    }
-    *reinterpret_cast<float4*>(reinterpret_cast<float*>(out) + at) = x;
-    return;
-  }
-  if (residual) {
-    const uint2 rv = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(residual) + at);
-    x.x += __uint_as_float(rv.x << 16);
-    x.y += __uint_as_float(rv.x & 0xFFFF0000u);
-    x.z += __uint_as_float(rv.y << 16);
-    x.w += __uint_as_float(rv.y & 0xFFFF0000u);
-  }
-  uint2 o;
-  o.x = bf16_bits_rne(x.x) | (bf16_bits_rne(x.y) << 16);
-  o.y = bf16_bits_rne(x.z) | (bf16_bits_rne(x.w) << 16);
-  *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(out) + at) = o;
+  const float4 b = bias ? *reinterpret_cast<const float4*>(bias + col) : float4{0.f, 0.f, 0.f, 0.f};
+  finish_linear(x, b, act, residual, out, stream_f32, at);
 }
 
 // The partial tiles' buffer, at least `need` bytes of it.

@@ -168,6 +168,39 @@ __device__ __forceinline__ float gelu_erf(float x) {
   return x * phi;
 }
 
+// A dense layer's epilogue on 4 columns of a row, whose first is element `at` of the output and the residual: out = act(x + bias) + residual.
+__device__ __forceinline__ void finish_linear(float4 x, const float4& bias, int act, const void* residual, void* out, bool stream_f32, size_t at) {
+  x.x += bias.x;
+  x.y += bias.y;
+  x.z += bias.z;
+  x.w += bias.w;
+  if (act == 1) {
+    x.x = gelu_erf(x.x);
+    x.y = gelu_erf(x.y);
+    x.z = gelu_erf(x.z);
+    x.w = gelu_erf(x.w);
+  }
+  if (stream_f32) {                                  // fp32 residual and output: no rounding
+    if (residual) {
+      const float4 rv = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(residual) + at);
+      x.x += rv.x;
+      x.y += rv.y;
+      x.z += rv.z;
+      x.w += rv.w;
+    }
+    *reinterpret_cast<float4*>(reinterpret_cast<float*>(out) + at) = x;
+    return;
+  }
+  if (residual) {
+    const uint2 rv = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(residual) + at);
+    x.x += __uint_as_float(rv.x << 16);
+    x.y += __uint_as_float(rv.x & 0xFFFF0000u);
+    x.z += __uint_as_float(rv.y << 16);
+    x.w += __uint_as_float(rv.y & 0xFFFF0000u);
+  }
+  *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(out) + at) = uint2{pack_bf16(x.x, x.y), pack_bf16(x.z, x.w)};
+}
+
 // ---- the counter-based generator of the sampling kernels: Philox4x32-10 (Salmon et al., SC'11) -------
 __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint32_t k0, uint32_t k1) {
 #pragma unroll

@@ -1235,40 +1235,6 @@ __global__ void __launch_bounds__(F_THREADS) logits_fast_kernel(LogitsArgs a) {
   __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): the requests past the end of the stream land in LDS
 }
 
-// A dense layer's epilogue on 4 columns of a row.
-__device__ __forceinline__ void finish_linear(const LogitsArgs& a, int row, int col, float4 x, const float4& bias) {
-  const size_t at = (size_t)row * a.ldo + col;
-  x.x += bias.x;
-  x.y += bias.y;
-  x.z += bias.z;
-  x.w += bias.w;
-  if (a.act == 1) {
-    x.x = gelu_erf(x.x);
-    x.y = gelu_erf(x.y);
-    x.z = gelu_erf(x.z);
-    x.w = gelu_erf(x.w);
-  }
-  if (a.stream_f32) {                                // fp32 residual and output: no rounding
-    if (a.residual) {
-      const float4 rv = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(a.residual) + at);
-      x.x += rv.x;
-      x.y += rv.y;
-      x.z += rv.z;
-      x.w += rv.w;
-    }
-    *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.out) + at) = x;
-    return;
-  }
-  if (a.residual) {
-    const uint2 rv = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(a.residual) + at);
-    x.x += __uint_as_float(rv.x << 16);
-    x.y += __uint_as_float(rv.x & 0xFFFF0000u);
-    x.z += __uint_as_float(rv.y << 16);
-    x.w += __uint_as_float(rv.y & 0xFFFF0000u);
-  }
-  *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.out) + at) = uint2{pack_bf16(x.x, x.y), pack_bf16(x.z, x.w)};
-}
-
 // The tiles of a dense layer's last round that were cut along K (last_round): out = act(sum of the parts + bias) + residual, 8 rows of a tile
 // at a time, a thread 4 columns of 2 of them and eight parts asked for at once.  A workgroup takes pieces of its XCD's tiles, or of all;
 // pieces of 16 rows leave CUs without one where 12 tiles have 21 parts each (27 us instead of 17), 4096 workgroups cost 1.5 us where nothing was cut.
@@ -1307,7 +1273,8 @@ __global__ void __launch_bounds__(256) tile_sum_kernel(LogitsArgs a) {
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i)
-      if (r0 + trow + i * 4 < r_end) finish_linear(a, r0 + trow + i * 4, col, x[i], bias);
+      if (r0 + trow + i * 4 < r_end)
+        finish_linear(x[i], bias, a.act, a.residual, a.out, a.stream_f32, (size_t)(r0 + trow + i * 4) * a.ldo + col);
   }
 }
 
